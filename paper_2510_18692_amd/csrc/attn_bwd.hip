@@ -4,56 +4,47 @@
 //   dV = P^T dO,  dP = dO V^T,  dS = P * (dP - delta),  dQ = scale dS K,  dK = scale dS^T Q.
 //
 // Three kernels, no atomics, results independent of scheduling:
-//   attn_bwd_delta   : delta[h][j] = sum_c dO[h][j][c] * O[h][j][c]
+//   attn_bwd_delta   : delta[h][j] = sum_c dO[h][j][c] * O[h][j][c]   (bf16)
 //   attn_bwd_dkdv    : a wave owns 32 key rows (K, V fragments and the dK^T, dV^T accumulators
 //                      live in registers) and sweeps the query tiles of its group;
 //   attn_bwd_dq      : a wave owns 32 query rows and sweeps the key tiles (mirror of forward).
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
 // read the transposed operands (dO^T, Q^T, K^T) from row-major LDS tiles with the transposing
-// LDS read.  The fp32 kernels below use one thread per row.
+// LDS read.  fp32 (attn_f32.h): the dQ kernel runs first and computes delta, the dK/dV kernel follows.
 #include <atomic>
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
+#include "attn_f32.h"
 
 namespace moga {
 
 
 // ---------------------------------------------------------------------------------------
-template <int LPR, bool BF16>
 __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const uintx4_t* __restrict__ d_oh,
                                                              const uintx4_t* __restrict__ oh,
                                                              const float* __restrict__ lse, int64_t rows,
-                                                             float inv_scale, float* __restrict__ delta,
+                                                             float inv_scale, float* __restrict__ neg_delta,
                                                              float* __restrict__ neg_lse_over_scale,
                                                              int* __restrict__ status) {
-  if (status && blockIdx.x == 0 && threadIdx.x == 0) *status = 0;   // read by the kernels that follow
-  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
-  const int part = threadIdx.x % LPR;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status = 0;   // read by the kernels that follow
+  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / 16;
+  const int part = threadIdx.x % 16;
   float s = 0.f;
   if (row < rows) {
-    const uintx4_t a = d_oh[row * LPR + part], b = oh[row * LPR + part];
-    if (BF16) {
+    const uintx4_t a = d_oh[row * 16 + part], b = oh[row * 16 + part];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s = fmaf(bf16_lo_to_f32(a[i]), bf16_lo_to_f32(b[i]), s);
-        s = fmaf(bf16_hi_to_f32(a[i]), bf16_hi_to_f32(b[i]), s);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) s = fmaf(__uint_as_float(a[i]), __uint_as_float(b[i]), s);
+    for (int i = 0; i < 4; ++i) {
+      s = fmaf(bf16_lo_to_f32(a[i]), bf16_lo_to_f32(b[i]), s);
+      s = fmaf(bf16_hi_to_f32(a[i]), bf16_hi_to_f32(b[i]), s);
     }
   }
 #pragma unroll
-  for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
-  if (row < rows && part == 0) {
-    if (neg_lse_over_scale) {   // bf16 kernels: both arrays negated, ready to start an accumulator from
-      delta[row] = -s;
-      neg_lse_over_scale[row] = -lse[row] * inv_scale;
-    } else {
-      delta[row] = s;
-    }
+  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  if (row < rows && part == 0) {   // both negated, ready to start an accumulator from
+    neg_delta[row] = -s;
+    neg_lse_over_scale[row] = -lse[row] * inv_scale;
   }
 }
 
@@ -119,139 +110,8 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// fp32 (head_dim 64): one thread per row
-// ---------------------------------------------------------------------------------------
-constexpr int kF32BM = 64, kF32BN = 32;
 constexpr int64_t kSmallGroupRows = 1280;   // mean rows per group below which the small-group bf16 kernels run
                                             // (398 against 334 TFLOP/s at 312 rows, equal at 1,560, slower above)
-
-template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dq_f32_kernel(
-    const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh,
-    const float* __restrict__ vh, const float* __restrict__ lse, const float* __restrict__ delta,
-    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
-    const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    int tiles_per_head, float* __restrict__ d_qh) {
-  __shared__ __attribute__((aligned(16))) float Ks[kF32BN][D];
-  __shared__ __attribute__((aligned(16))) float Vs[kF32BN][D];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
-  const int head = blockIdx.x / tiles_per_head;
-  const int tile = blockIdx.x - head * tiles_per_head;
-  TileInfo ti;
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_q, M, kF32BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, kF32BM, tile, s_start, &s_found, ti)) {
-    return;
-  }
-  const int ge = ti.row_end;
-  const int kbeg = cu_k[ti.group], kend = cu_k[ti.group + 1];   // key rows of the group
-  const int64_t head_off = (int64_t)head * Nq;
-  const int64_t head_off_k = (int64_t)head * Nk;
-  const int row = ti.tile_row + threadIdx.x;
-  const bool valid = row < ge;
-  const int64_t rr = head_off + (valid ? row : ge - 1);
-  float q[D], dO[D], dq[D];
-#pragma unroll
-  for (int cI = 0; cI < D; ++cI) { q[cI] = qh[rr * D + cI]; dO[cI] = d_oh[rr * D + cI]; dq[cI] = 0.f; }
-  const float l = lse[rr], dl = delta[rr];
-
-  for (int kv0 = kbeg; kv0 < kend; kv0 += kF32BN) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < kF32BN * (D / 4); idx += 64) {
-      const int r2 = idx / (D / 4), c4 = (idx - r2 * (D / 4)) * 4;
-      floatx4_t kk = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
-      if (kv0 + r2 < kend) {
-        kk = *(const floatx4_t*)(kh + (head_off_k + kv0 + r2) * D + c4);
-        vv = *(const floatx4_t*)(vh + (head_off_k + kv0 + r2) * D + c4);
-      }
-      *(floatx4_t*)&Ks[r2][c4] = kk;
-      *(floatx4_t*)&Vs[r2][c4] = vv;
-    }
-    __syncthreads();
-    const int nk = min(kF32BN, kend - kv0);
-    for (int j = 0; j < nk; ++j) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int cI = 0; cI < D; ++cI) { s = fmaf(q[cI], Ks[j][cI], s); dp = fmaf(dO[cI], Vs[j][cI], dp); }
-      const float p = expf(s * scale - l);
-      const float ds = p * (dp - dl);
-#pragma unroll
-      for (int cI = 0; cI < D; ++cI) dq[cI] = fmaf(ds, Ks[j][cI], dq[cI]);
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int cI = 0; cI < D; ++cI) d_qh[rr * D + cI] = dq[cI] * scale;
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(64) void attn_bwd_dkdv_f32_kernel(
-    const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh,
-    const float* __restrict__ vh, const float* __restrict__ lse, const float* __restrict__ delta,
-    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
-    const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    int tiles_per_head, float* __restrict__ d_kh, float* __restrict__ d_vh) {
-  __shared__ __attribute__((aligned(16))) float Qs[kF32BN][D];
-  __shared__ __attribute__((aligned(16))) float dOs[kF32BN][D];
-  __shared__ float s_lse[kF32BN], s_delta[kF32BN];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
-  const int head = blockIdx.x / tiles_per_head;
-  const int tile = blockIdx.x - head * tiles_per_head;
-  TileInfo ti;   // tiles run over the key rows of the groups
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_k, M, kF32BM, tile, ti)) return;
-  } else if (!find_tile(cu_k, M, kF32BM, tile, s_start, &s_found, ti)) {
-    return;
-  }
-  const int ge = ti.row_end;
-  const int qbeg = cu_q[ti.group], qend = cu_q[ti.group + 1];   // query rows of the group
-  const int64_t head_off = (int64_t)head * Nk;     // key-side tensors
-  const int64_t head_off_q = (int64_t)head * Nq;   // query-side tensors
-  const int row = ti.tile_row + threadIdx.x;
-  const bool valid = row < ge;
-  const int64_t rr = head_off + (valid ? row : ge - 1);
-  float k[D], v[D], dk[D], dv[D];
-#pragma unroll
-  for (int cI = 0; cI < D; ++cI) { k[cI] = kh[rr * D + cI]; v[cI] = vh[rr * D + cI]; dk[cI] = 0.f; dv[cI] = 0.f; }
-
-  for (int q0 = qbeg; q0 < qend; q0 += kF32BN) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < kF32BN * (D / 4); idx += 64) {
-      const int r2 = idx / (D / 4), c4 = (idx - r2 * (D / 4)) * 4;
-      floatx4_t qq = {0.f, 0.f, 0.f, 0.f}, dd = {0.f, 0.f, 0.f, 0.f};
-      if (q0 + r2 < qend) {
-        qq = *(const floatx4_t*)(qh + (head_off_q + q0 + r2) * D + c4);
-        dd = *(const floatx4_t*)(d_oh + (head_off_q + q0 + r2) * D + c4);
-      }
-      *(floatx4_t*)&Qs[r2][c4] = qq;
-      *(floatx4_t*)&dOs[r2][c4] = dd;
-    }
-    if (threadIdx.x < kF32BN) {
-      const int g = q0 + threadIdx.x;
-      s_lse[threadIdx.x] = g < qend ? lse[head_off_q + g] : INFINITY;
-      s_delta[threadIdx.x] = g < qend ? delta[head_off_q + g] : 0.f;
-    }
-    __syncthreads();
-    const int nq = min(kF32BN, qend - q0);
-    for (int i = 0; i < nq; ++i) {
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int cI = 0; cI < D; ++cI) { s = fmaf(k[cI], Qs[i][cI], s); dp = fmaf(v[cI], dOs[i][cI], dp); }
-      const float p = expf(s * scale - s_lse[i]);
-      const float ds = p * (dp - s_delta[i]);
-#pragma unroll
-      for (int cI = 0; cI < D; ++cI) { dv[cI] = fmaf(p, dOs[i][cI], dv[cI]); dk[cI] = fmaf(ds, Qs[i][cI], dk[cI]); }
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int cI = 0; cI < D; ++cI) { d_kh[rr * D + cI] = dk[cI] * scale; d_vh[rr * D + cI] = dv[cI]; }
-  }
-}
 
 }  // namespace moga
 
@@ -294,7 +154,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
     int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-    attn_bwd_delta_kernel<16, true><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
+    attn_bwd_delta_kernel<<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
@@ -334,38 +194,32 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
             (int)tiles, (unsigned short*)d_qh);
     }
   } else {
-    if (D == 64)
-      attn_bwd_delta_kernel<16, false><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
-          (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f, delta, nullptr, nullptr);
-    else
-      attn_bwd_delta_kernel<32, false><<<(unsigned)((rows * 32 + 255) / 256), 256, 0, st>>>(
-          (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f, delta, nullptr, nullptr);
-    if (Nk > 0) {
-      const int64_t tiles = max_tiles(Nk, M, kF32BM);
+    {
+      const int64_t tiles = max_tiles(Nq, M, kF32Rows);
       const int64_t blocks = tiles * H;
       if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-      if (ts_k) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32BM, ts_k);
-      if (D == 64)
-        attn_bwd_dkdv_f32_kernel<64><<<(unsigned)blocks, 64, 0, st>>>(
-            (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta,
-            cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh);
-      else
-        attn_bwd_dkdv_f32_kernel<128><<<(unsigned)blocks, 64, 0, st>>>(
-            (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta,
-            cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh);
+      if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
+#define MOGA_DQ_F32(DD)                                                                                   \
+  attn_bwd_dq_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                       \
+      (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, (const float*)oh, lse,    \
+      cu_q, cu_k, ts_q, M, Nq, Nk, softmax_scale, (int)tiles, delta, (float*)d_qh)
+      if (D == 64) MOGA_DQ_F32(64);
+      else MOGA_DQ_F32(128);
+#undef MOGA_DQ_F32
     }
-    const int64_t tiles = max_tiles(Nq, M, kF32BM);
-    const int64_t blocks = tiles * H;
-    if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32BM, ts_q);
-    if (D == 64)
-      attn_bwd_dq_f32_kernel<64><<<(unsigned)blocks, 64, 0, st>>>(
-          (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta,
-          cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_qh);
-    else
-      attn_bwd_dq_f32_kernel<128><<<(unsigned)blocks, 64, 0, st>>>(
-          (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta,
-          cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_qh);
+    if (Nk > 0) {
+      const int64_t tiles = max_tiles(Nk, M, kF32Rows);
+      const int64_t blocks = tiles * H;
+      if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+      if (ts_k) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
+#define MOGA_DKDV_F32(DD)                                                                                 \
+  attn_bwd_dkdv_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                     \
+      (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k,   \
+      ts_k, M, Nq, Nk, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh)
+      if (D == 64) MOGA_DKDV_F32(64);
+      else MOGA_DKDV_F32(128);
+#undef MOGA_DKDV_F32
+    }
   }
   return launch_status();
 }

@@ -9,116 +9,16 @@
 //     product O^T = V^T P^T, which therefore needs no data movement for P;
 //   * V^T is read from the row-major V tile in LDS with the transposing LDS read;
 //   * the kernel itself (software pipeline, LDS ring, direct-to-LDS loads) is in attn_pipe.h.
-// fp32 kernel: one thread per query row, plain FMA, for the full-precision configuration.
+// fp32 kernel (fp32 matrix instruction, full precision throughout): attn_f32.h.
 #include "attn_common.h"
+#include "attn_f32.h"
 #include "attn_pipe.h"
 #include "attn_pipe_small.h"
 
 namespace moga {
 
-// ---------------------------------------------------------------------------------------
-// fp32: one thread per query row
-// ---------------------------------------------------------------------------------------
-constexpr int kF32BM = 64, kF32BN = 32;
 constexpr int64_t kSmallGroupRows = 2560;   // mean rows per group below which the small-group bf16 kernel runs
                                             // (927 against 886 TFLOP/s at 1,560 rows, 1052 against 1063 at 3,224)
-
-template <int D>
-__global__ __launch_bounds__(64) void attn_fwd_f32_kernel(
-    const float* __restrict__ qh, const float* __restrict__ kh, const float* __restrict__ vh,
-    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
-    const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    int tiles_per_head, float* __restrict__ oh, float* __restrict__ lse) {
-  __shared__ __attribute__((aligned(16))) float Ks[kF32BN][D];
-  __shared__ __attribute__((aligned(16))) float Vs[kF32BN][D];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
-  const int head = blockIdx.x / tiles_per_head;
-  const int tile = blockIdx.x - head * tiles_per_head;
-  TileInfo ti;
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_q, M, kF32BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, kF32BM, tile, s_start, &s_found, ti)) {
-    return;
-  }
-  const int ge = ti.row_end;
-  const int kbeg = cu_k[ti.group], kend = cu_k[ti.group + 1];   // key rows of the group
-  const int64_t head_off = (int64_t)head * Nq;
-  const int64_t head_off_k = (int64_t)head * Nk;
-  const int row = ti.tile_row + threadIdx.x;
-  const bool valid = row < ge;
-  const float* qp = qh + (head_off + (valid ? row : ge - 1)) * D;
-  float q[D], o[D];
-#pragma unroll
-  for (int cI = 0; cI < D; cI += 4) {
-    const floatx4_t t = *(const floatx4_t*)(qp + cI);
-    q[cI] = t[0]; q[cI + 1] = t[1]; q[cI + 2] = t[2]; q[cI + 3] = t[3];
-  }
-#pragma unroll
-  for (int cI = 0; cI < D; ++cI) o[cI] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  for (int kv0 = kbeg; kv0 < kend; kv0 += kF32BN) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < kF32BN * (D / 4); idx += 64) {
-      const int rr = idx / (D / 4), c4 = (idx - rr * (D / 4)) * 4;
-      floatx4_t kk = {0.f, 0.f, 0.f, 0.f}, vv = {0.f, 0.f, 0.f, 0.f};
-      if (kv0 + rr < kend) {
-        kk = *(const floatx4_t*)(kh + (head_off_k + kv0 + rr) * D + c4);
-        vv = *(const floatx4_t*)(vh + (head_off_k + kv0 + rr) * D + c4);
-      }
-      *(floatx4_t*)&Ks[rr][c4] = kk;
-      *(floatx4_t*)&Vs[rr][c4] = vv;
-    }
-    __syncthreads();
-    const int nk = min(kF32BN, kend - kv0);
-    float s[kF32BN];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      float dot = 0.f;
-#pragma unroll
-      for (int cI = 0; cI < D; cI += 4) {
-        const floatx4_t kk = *(const floatx4_t*)&Ks[j][cI];
-        dot = fmaf(q[cI], kk[0], dot);
-        dot = fmaf(q[cI + 1], kk[1], dot);
-        dot = fmaf(q[cI + 2], kk[2], dot);
-        dot = fmaf(q[cI + 3], kk[3], dot);
-      }
-      s[j] = j < nk ? dot * scale : -INFINITY;
-      mx = fmaxf(mx, s[j]);
-    }
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = expf(m_run - m_new);
-    m_run = m_new;
-    l_run *= alpha;
-#pragma unroll
-    for (int cI = 0; cI < D; ++cI) o[cI] *= alpha;
-#pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      const float p = expf(s[j] - m_new);
-      l_run += p;
-#pragma unroll
-      for (int cI = 0; cI < D; cI += 4) {
-        const floatx4_t vv = *(const floatx4_t*)&Vs[j][cI];
-        o[cI] = fmaf(p, vv[0], o[cI]);
-        o[cI + 1] = fmaf(p, vv[1], o[cI + 1]);
-        o[cI + 2] = fmaf(p, vv[2], o[cI + 2]);
-        o[cI + 3] = fmaf(p, vv[3], o[cI + 3]);
-      }
-    }
-  }
-  if (valid) {
-    const float inv = l_run > 0.f ? 1.f / l_run : 0.f;   // no keys: zero output, lse = -inf
-    float* op = oh + (head_off + row) * D;
-#pragma unroll
-    for (int cI = 0; cI < D; cI += 4) {
-      floatx4_t t = {o[cI] * inv, o[cI + 1] * inv, o[cI + 2] * inv, o[cI + 3] * inv};
-      *(floatx4_t*)(op + cI) = t;
-    }
-    lse[head_off + row] = l_run > 0.f ? m_run + logf(l_run) : -INFINITY;
-  }
-}
 
 }  // namespace moga
 
@@ -132,7 +32,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
   const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, kSmallGroupRows);
-  const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32BM;
+  const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
   if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
@@ -146,12 +46,12 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, (unsigned short*)oh, lse);
   } else if (D == 64) {
-    attn_fwd_f32_kernel<64><<<(unsigned)blocks, 64, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
+    attn_fwd_f32_mfma_kernel<64><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
+        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk,
         softmax_scale, (int)tiles, (float*)oh, lse);
   } else {
-    attn_fwd_f32_kernel<128><<<(unsigned)blocks, 64, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
+    attn_fwd_f32_mfma_kernel<128><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
+        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk,
         softmax_scale, (int)tiles, (float*)oh, lse);
   }
   return launch_status();

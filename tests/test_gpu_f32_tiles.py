@@ -1,0 +1,44 @@
+"""fp32 attention kernels (32-row blocks, eight waves sharing the streamed rows) at the sizes where their
+split can go wrong: around one step (32 rows), around one round of the eight waves (256 rows), sides without
+rows, different query and key lists.  Against the float64 oracle, relative to the largest value: 1e-4, the
+bound of the fp32 configuration (fp32 sums of at most 600 terms of a convex combination err by a few 1e-6)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import stga_oracle as sto
+from paper_2510_18692_amd import binding as mg
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("nq,nk", [
+    ([1, 31, 32, 33], [1, 31, 32, 33]),
+    ([255, 256, 257], [255, 256, 257]),
+    ([32, 0, 40, 7, 64], [289, 33, 0, 1, 600]),      # more and fewer keys than queries, empty sides
+])
+def test_f32_attention_tile_edges(D, nq, nk):
+    print(f"f32 tiles D={D} nq={nq} nk={nk}", flush=True)
+    H, scale = 2, D ** -0.5
+    g = torch.Generator().manual_seed(D + sum(nq))
+    Nq, Nk = sum(nq), sum(nk)
+    q, dA = (torch.randn((Nq, H, D), generator=g) for _ in range(2))
+    k, v = (torch.randn((Nk, H, D), generator=g) for _ in range(2))
+    cu_q = np.concatenate([[0], np.cumsum(nq)]).astype(np.int32)
+    cu_k = np.concatenate([[0], np.cumsum(nk)]).astype(np.int32)
+    q64, k64, v64, dA64 = (P.to64(t) for t in (q, k, v, dA))
+    A, lse = sto.varlen_attention(q64, k64, v64, np.arange(Nq), cu_q, np.arange(Nk), cu_k, scale)
+    refs = sto.varlen_attention_bwd(q64, k64, v64, dA64, np.arange(Nq), cu_q, np.arange(Nk), cu_k, scale)
+    hat = lambda t: t.permute(1, 0, 2).contiguous().cuda()
+    cq, ck = torch.from_numpy(cu_q).cuda(), torch.from_numpy(cu_k).cuda()
+    oh, lse_g = mg.moga_varlen_attn_fwd(hat(q), hat(k), hat(v), cq, ck, scale)
+    P.assert_close_f32(P.unhat(oh), A, "O")
+    fin = np.isfinite(lse)
+    np.testing.assert_allclose(P.to64(lse_g).T[fin], lse[fin], rtol=1e-5, atol=1e-5)
+    assert np.all(np.isneginf(P.to64(lse_g).T[~fin]))
+    grads = mg.moga_varlen_attn_bwd(hat(dA), hat(q), hat(k), hat(v), oh, lse_g, cq, ck, scale)
+    torch.cuda.synchronize()
+    for name, got, ref in zip(("dQ", "dK", "dV"), grads, refs):
+        P.assert_close_f32(P.unhat(got), ref, name)
