@@ -301,29 +301,41 @@ __global__ __launch_bounds__(64 * NWV, 2) void route_mfma_kernel(
 constexpr int kRbTok = 64;  // tokens per staged tile
 constexpr int kRbMB = 32;   // groups per pass
 
-template <typename XT>
+// dW for fp32 X and for shapes the matrix-core path below does not cover, with fp32 FMAs.  A block takes
+// 64 columns and a range of tokens; its four waves take 16 tokens each of every 64-token tile, a lane one
+// column with all MB groups, and are added through LDS at the end.  The 16 activations of a tile are
+// loaded together (one round trip per tile), dr comes from LDS as broadcast 16-byte pieces.  The token
+// range is cut until about a thousand blocks exist or a block has a single tile: with one thread per
+// column and 2,048 tokens per block, 4,096 x 128 x 8 groups ran on two blocks (437 us for the call, 16 us now).
+template <typename XT, int MB>
 __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
     const XT* __restrict__ x, const float* __restrict__ probs, const int32_t* __restrict__ group,
     const float* __restrict__ gate, const float* __restrict__ d_gate, int64_t N, int d, int M,
     int64_t tokens_per_split, float* __restrict__ partial /* [splits][M][d] */) {
-  __shared__ float s_dr[kRbTok][kRbMB];
-  const int c = blockIdx.x * 256 + threadIdx.x;
+  constexpr int WT = kRbTok / 4;   // tokens per wave and tile
+  __shared__ __attribute__((aligned(16))) float s_dr[kRbTok][MB];
+  __shared__ float s_acc[3][MB][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int c = blockIdx.x * 64 + lane;
   const int split = blockIdx.y;
-  const int j0 = blockIdx.z * kRbMB;
-  const int mb = min(kRbMB, M - j0);
+  const int j0 = blockIdx.z * MB;
+  const int mb = min(MB, M - j0);
   const int64_t t0 = (int64_t)split * tokens_per_split;
   const int64_t t1 = min(N, t0 + tokens_per_split);
-  float acc[kRbMB];
+  const XT* xc = x + min(c, d - 1);
+  float acc[MB];
 #pragma unroll
-  for (int j = 0; j < kRbMB; ++j) acc[j] = 0.f;
+  for (int j = 0; j < MB; ++j) acc[j] = 0.f;
 
   for (int64_t tb = t0; tb < t1; tb += kRbTok) {
-    const int nt = (int)min((int64_t)kRbTok, t1 - tb);
+    float xv[WT];   // tokens past the end of the range have dr = 0
+#pragma unroll
+    for (int i = 0; i < WT; ++i) xv[i] = load_x<XT>(xc + min(tb + WT * wave + i, t1 - 1) * d);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < kRbTok * kRbMB; idx += 256) {
-      const int ti = idx / kRbMB, j = idx - ti * kRbMB;
+    for (int idx = threadIdx.x; idx < kRbTok * MB; idx += 256) {
+      const int ti = idx / MB, j = idx % MB;
       float v = 0.f;
-      if (ti < nt && j < mb) {
+      if (tb + ti < t1 && j < mb) {
         const int64_t tok = tb + ti;
         const float coef = d_gate[tok] * gate[tok];
         const float onehot = (group[tok] == j0 + j) ? 1.f : 0.f;
@@ -332,27 +344,53 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
       s_dr[ti][j] = v;
     }
     __syncthreads();
-    if (c < d) {
-      for (int ti = 0; ti < nt; ++ti) {
-        const float xv = load_x<XT>(x + (tb + ti) * (int64_t)d + c);
 #pragma unroll
-        for (int j = 0; j < kRbMB; ++j) acc[j] = fmaf(s_dr[ti][j], xv, acc[j]);
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+      for (int j4 = 0; j4 < MB; j4 += 4) {
+        const floatx4_t dr = *(const floatx4_t*)&s_dr[WT * wave + i][j4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[j4 + e] = fmaf(dr[e], xv[i], acc[j4 + e]);
       }
-    }
   }
-  if (c < d) {
-    for (int j = 0; j < mb; ++j)
-      partial[((int64_t)split * M + j0 + j) * d + c] = acc[j];
-  }
+  if (wave > 0)
+#pragma unroll
+    for (int j = 0; j < MB; ++j) s_acc[wave - 1][j][lane] = acc[j];
+  __syncthreads();
+  if (wave == 0 && c < d)
+#pragma unroll
+    for (int j = 0; j < MB; ++j)
+      if (j < mb)
+        partial[((int64_t)split * M + j0 + j) * d + c] = (acc[j] + s_acc[0][j][lane]) + (s_acc[1][j][lane] + s_acc[2][j][lane]);
 }
 
-__global__ __launch_bounds__(256) void route_bwd_dw_reduce_kernel(
-    const float* __restrict__ partial, int splits, int64_t md, float* __restrict__ d_w) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= md) return;
+// Sum of the splits, in a fixed order: 64 elements per block, eight waves that take every eighth split
+// each with eight loads in flight, then a sum over the waves.  (One thread per element took 59 us for the
+// 50 MB of 256 splits at d = 1536; the call at 62,400 x 1536, M = 5 went from 105 to 48 us with this and
+// with the groups rounded up to 8 instead of 32.)  Element i of a split is (j, c) = (i / d,
+// i % d), or for the matrix-core path (TRANSPOSED) (c, j) = (i / mp, i % mp).
+template <bool TRANSPOSED>
+__global__ __launch_bounds__(512) void route_bwd_dw_reduce_kernel(const float* __restrict__ partial, int splits, int64_t n,
+                                                                  int d, int M, int mp, float* __restrict__ d_w) {
+  __shared__ float s_sum[8][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const float* p = partial + min(i, n - 1);
   float s = 0.f;
-  for (int k = 0; k < splits; ++k) s += partial[(int64_t)k * md + i];
-  d_w[i] = s;
+#pragma unroll 8
+  for (int k = wave; k < splits; k += 8) s += p[(int64_t)k * n];
+  s_sum[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || i >= n) return;
+  s = 0.f;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) s += s_sum[w][lane];
+  if (!TRANSPOSED) {
+    d_w[i] = s;
+  } else {
+    const int c = (int)(i / mp), j = (int)(i - (int64_t)c * mp);
+    if (j < M) d_w[(int64_t)j * d + c] = s;
+  }
 }
 
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
@@ -464,7 +502,7 @@ __global__ __launch_bounds__(256) void route_bwd_dx_cols_kernel(
 // [16 tokens x 256 columns] tiles of X plus the two dr limb tiles into its own LDS ring with
 // direct-to-LDS loads (three stages in flight, no barriers: a wave only reads what it loaded),
 // reads X^T fragments with transposed LDS reads and accumulates eight 32x32 blocks of dW^T.
-// Partial sums go to partial[split][c][32] and a second kernel reduces over the splits.
+// Partial sums go to partial[split][c][M rounded up to 8] and a second kernel reduces over the splits.
 // ---------------------------------------------------------------------------------------
 constexpr int kDwCols = 256;                          // columns of X per wave
 constexpr int kDwTok = 16;                            // tokens per stage = one MFMA contraction step
@@ -509,7 +547,7 @@ __device__ __forceinline__ int dw_swizzle(int row) { return (row & 3) << 2; }
 __global__ __launch_bounds__(64) void route_bwd_dw_mfma_kernel(
     const unsigned short* __restrict__ x, const uintx4_t* __restrict__ dr_hi,
     const uintx4_t* __restrict__ dr_lo, int64_t N, int d, int nslabs, int splits,
-    int64_t steps_per_split, int64_t total_steps, float* __restrict__ partial) {
+    int64_t steps_per_split, int64_t total_steps, int mp, float* __restrict__ partial) {
   __shared__ __attribute__((aligned(1024))) unsigned char ring[kDwStages * kDwStageBytes];
   const int lane = threadIdx.x;
   const int r = lane & 31, h = lane >> 5;
@@ -579,36 +617,26 @@ __global__ __launch_bounds__(64) void route_bwd_dw_mfma_kernel(
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS after the block ends
 
   // accumulator register v of lane (r, h): column 8*(v/4) + 4*h + v%4 of the block, group r
-  float* out = partial + ((int64_t)split * d + (int64_t)slab * kDwCols) * 32 + r;
+  if (r >= mp) return;
+  float* out = partial + ((int64_t)split * d + (int64_t)slab * kDwCols) * mp + r;
 #pragma unroll
   for (int cb = 0; cb < 8; ++cb)
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      out[(int64_t)(32 * cb + 8 * (v >> 2) + 4 * h + (v & 3)) * 32] = acc[cb][v];
+      out[(int64_t)(32 * cb + 8 * (v >> 2) + 4 * h + (v & 3)) * mp] = acc[cb][v];
 }
 
-__global__ __launch_bounds__(256) void route_bwd_dw_reduce_t_kernel(
-    const float* __restrict__ partial /* [splits][d][32] */, int splits, int d, int M,
-    float* __restrict__ d_w) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t n = (int64_t)d * 32;
-  if (i >= n) return;
-  float s = 0.f;
-  for (int k = 0; k < splits; ++k) s += partial[(int64_t)k * n + i];
-  const int c = (int)(i >> 5), j = (int)(i & 31);
-  if (j < M) d_w[(int64_t)j * d + c] = s;
-}
+constexpr int dw_group_block(int M) { return M <= 8 ? 8 : kRbMB; }   // groups per block of the FMA path
 
-static int route_bwd_splits(int64_t N) {
-  int64_t s = (N + 2047) / 2048;
-  if (s < 1) s = 1;
-  if (s > 64) s = 64;
-  return (int)s;
+static int route_bwd_splits(int64_t N, int M, int d) {
+  const int64_t per_split = (int64_t)((d + 63) / 64) * ((M + dw_group_block(M) - 1) / dw_group_block(M));
+  int64_t s = std::min<int64_t>((1024 + per_split - 1) / per_split, (N + kRbTok - 1) / kRbTok);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(s, 256));
 }
 
 // Launch plan of the matrix-core dW path.
 struct DwPlan {
-  int nslabs, splits;
+  int nslabs, splits, mp;           // mp: groups per column in the partial sums
   int64_t total_steps, steps_per_split;
   size_t dr_bytes, partial_bytes;   // one dr limb array; the partial sums
 };
@@ -617,19 +645,23 @@ static bool route_bwd_mfma_ok(int x_dtype, int M, int d) {
   return x_dtype == MOGA_BF16 && M <= 32 && d % kDwCols == 0;
 }
 
-static DwPlan route_bwd_plan(int64_t N, int d) {
+static DwPlan route_bwd_plan(int64_t N, int M, int d) {
   DwPlan p;
+  p.mp = (M + 7) / 8 * 8;
   p.nslabs = d / kDwCols;
   p.total_steps = (N + kDwTok - 1) / kDwTok;
-  // 40 KB of LDS per one-wave block: 4 blocks per CU, 1024 on the chip; three rounds of them measured
-  // best at 580k tokens (1.21 ms against 1.29 ms for two or four rounds)
-  int64_t splits = 3072 / p.nslabs;
-  splits = std::min<int64_t>(splits, (p.total_steps + 7) / 8);   // at least 128 tokens per split
+  // 40 KB of LDS per one-wave block: 4 blocks per CU, 1024 on the chip; three rounds of them measured best
+  // at 580k tokens (1.21 ms against 1.29 ms for two or four rounds) and at 100k (237 us; 251 for half a
+  // round).  The partial sums cost 8 d mp bytes a split, so a split gets at least 512 tokens (20,000 x
+  // 5120, M = 8: 45 us with 25 splits, 55 with 153), and down to 128 where that would leave the chip with
+  // fewer than half a round of blocks.
+  int64_t splits = std::max(std::min<int64_t>(3072 / p.nslabs, p.total_steps / 32),
+                            std::min<int64_t>(512 / p.nslabs, (p.total_steps + 7) / 8));
   splits = std::max<int64_t>(1, std::min<int64_t>(splits, 256));
   p.steps_per_split = (p.total_steps + splits - 1) / splits;
   p.splits = (int)((p.total_steps + p.steps_per_split - 1) / p.steps_per_split);   // no empty split
   p.dr_bytes = (size_t)p.total_steps * 2 * 32 * 16;
-  p.partial_bytes = (size_t)p.splits * (size_t)d * 32 * sizeof(float);
+  p.partial_bytes = (size_t)p.splits * (size_t)d * p.mp * sizeof(float);
   return p;
 }
 
@@ -639,9 +671,9 @@ using namespace moga;
 
 extern "C" size_t moga_route_bwd_ws_bytes(int64_t N, int M, int d_model) {
   // the larger of the two paths, so the size does not depend on the dtype of X
-  size_t need = (size_t)route_bwd_splits(N) * (size_t)M * (size_t)d_model * sizeof(float);
+  size_t need = (size_t)route_bwd_splits(N, M, d_model) * (size_t)M * (size_t)d_model * sizeof(float);
   if (N > 0 && route_bwd_mfma_ok(MOGA_BF16, M, d_model)) {
-    const DwPlan p = route_bwd_plan(N, d_model);
+    const DwPlan p = route_bwd_plan(N, M, d_model);
     need = std::max(need, 2 * p.dr_bytes + p.partial_bytes);
   }
   return need;
@@ -702,7 +734,7 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   if (route_bwd_mfma_ok(x_dtype, M, d_model)) {
     if (!aligned16(x) || !aligned16(ws)) return MOGA_ERR_INVALID_ARG;
-    const DwPlan p = route_bwd_plan(N, d_model);
+    const DwPlan p = route_bwd_plan(N, M, d_model);
     uintx4_t* dr_hi = (uintx4_t*)ws;
     uintx4_t* dr_lo = (uintx4_t*)((char*)ws + p.dr_bytes);
     float* partial = (float*)((char*)ws + 2 * p.dr_bytes);
@@ -712,22 +744,28 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
     const unsigned blocks = (unsigned)((p.splits + 7) / 8 * 8 * p.nslabs);
     route_bwd_dw_mfma_kernel<<<blocks, 64, 0, st>>>((const unsigned short*)x, dr_hi, dr_lo, N, d_model,
                                                     p.nslabs, p.splits, p.steps_per_split,
-                                                    p.total_steps, partial);
-    route_bwd_dw_reduce_t_kernel<<<(unsigned)(((int64_t)d_model * 32 + 255) / 256), 256, 0, st>>>(
-        partial, p.splits, d_model, M, d_w);
+                                                    p.total_steps, p.mp, partial);
+    const int64_t n = (int64_t)d_model * p.mp;
+    route_bwd_dw_reduce_kernel<true><<<(unsigned)((n + 63) / 64), 512, 0, st>>>(partial, p.splits, n, d_model, M, p.mp, d_w);
   } else {
-    const int splits = route_bwd_splits(N);
+    const int splits = route_bwd_splits(N, M, d_model);
     int64_t tps = (N + splits - 1) / splits;
     tps = (tps + kRbTok - 1) / kRbTok * kRbTok;
-    dim3 grid((d_model + 255) / 256, splits, (M + kRbMB - 1) / kRbMB);
+    const int mb = dw_group_block(M);
+    dim3 grid((d_model + 63) / 64, splits, (M + mb - 1) / mb);
     float* partial = (float*)ws;
-    if (x_dtype == MOGA_F32)
-      route_bwd_dw_partial_kernel<float><<<grid, 256, 0, st>>>((const float*)x, probs, group, gate,
-                                                              d_gate, N, d_model, M, tps, partial);
-    else
-      route_bwd_dw_partial_kernel<unsigned short><<<grid, 256, 0, st>>>(
-          (const unsigned short*)x, probs, group, gate, d_gate, N, d_model, M, tps, partial);
-    route_bwd_dw_reduce_kernel<<<(unsigned)((md + 255) / 256), 256, 0, st>>>(partial, splits, md, d_w);
+#define MOGA_DW_PARTIAL(XT, MB)                                                                             \
+  route_bwd_dw_partial_kernel<XT, MB><<<grid, 256, 0, st>>>((const XT*)x, probs, group, gate, d_gate, N,    \
+                                                            d_model, M, tps, partial)
+    if (x_dtype == MOGA_F32) {
+      if (mb == 8) MOGA_DW_PARTIAL(float, 8);
+      else MOGA_DW_PARTIAL(float, kRbMB);
+    } else {
+      if (mb == 8) MOGA_DW_PARTIAL(unsigned short, 8);
+      else MOGA_DW_PARTIAL(unsigned short, kRbMB);
+    }
+#undef MOGA_DW_PARTIAL
+    route_bwd_dw_reduce_kernel<false><<<(unsigned)((md + 63) / 64), 512, 0, st>>>(partial, splits, md, d_model, M, M, d_w);
   }
   if (d_x) {
     if (M <= 32 && d_model % 4 == 0 && aligned16(d_x) && aligned16(w)) {
