@@ -1,4 +1,4 @@
-"""Build libmoga.so (the C-ABI HIP library) in-tree for gfx950 with hipcc."""
+"""Build libmoga.so (the C-ABI HIP library, gfx950, hipcc) and its torch binding in-tree."""
 from __future__ import annotations
 
 import os
@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoga.so")
+NATIVE = os.path.join(HERE, "_moga_torch.so")          # native half of the Python binding
 BENCH_LIB = os.path.join(HERE, "libmoga_bench.so")   # peak microbenchmarks for bench.py only
 EXAMPLE = os.path.join(HERE, "c_abi_example")
 SOURCES = ["api.hip", "route.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "balance.hip", "static_index.hip"]
@@ -26,6 +27,22 @@ def _hipcc() -> str:
         if c and (os.path.isabs(c) and os.path.exists(c) or not os.path.isabs(c)):
             return c
     raise RuntimeError("hipcc not found")
+
+
+def _build_native() -> None:
+    """Host code only: the torch binding of the C ABI, against this interpreter's torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+    inc = [ROOT + "/include", *ext.include_paths("cuda"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DTORCH_EXTENSION_NAME=_moga_torch", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for i in inc for x in ("-isystem", i)),
+           os.path.join(CSRC, "torch_binding.cpp"), "-o", NATIVE, "-L", HERE, "-lmoga", "-Wl,-rpath,$ORIGIN",
+           *(x for p in ext.library_paths("cuda") for x in ("-L", p)), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("native binding build failed:\n" + r.stdout + r.stderr)
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
@@ -52,6 +69,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
+    _build_native()
     # the two peak microbenchmarks bench.py reports beside the published peaks (a library of their own)
     r = subprocess.run([hipcc, *FLAGS, *extra_flags, "-shared", os.path.join(CSRC, "bench_peaks.hip"),
                         "-o", BENCH_LIB], capture_output=True, text=True)

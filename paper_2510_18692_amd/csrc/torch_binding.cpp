@@ -1,0 +1,408 @@
+// Native half of the Python binding: tensors in, C-ABI calls (moga.h), tensors out.
+//
+// Nothing is computed here.  Each function allocates its outputs and its workspace from torch's caching
+// allocator and makes one C-ABI call on the current stream (or the one given), so that a call costs its
+// kernel launches and little more.  Host time at a few hundred tokens, with ctypes and with this: the four
+// forward calls 72 and 32 us, the four backward calls 70 and 31 us, a training step through autograd 346 and
+// 101 us (its backward now runs in the engine's thread without the interpreter).
+#include <ATen/ATen.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/custom_function.h>
+#include <torch/csrc/utils/pybind.h>
+
+#include <optional>
+#include <tuple>
+
+#include "moga.h"
+
+namespace py = pybind11;
+using at::Tensor;
+using OptTensor = std::optional<Tensor>;
+using OptStream = std::optional<int64_t>;   // hipStream_t as an integer; none: the current stream
+
+namespace {
+
+// Python exceptions are raised with the interpreter lock held: the calls themselves run without it.
+[[noreturn]] void raise(PyObject* type, const std::string& text) {
+  py::gil_scoped_acquire gil;
+  PyErr_SetString(type, text.c_str());
+  throw py::error_already_set();
+}
+
+void check(const char* fn, int status) {
+  if (status == MOGA_OK) return;
+  py::gil_scoped_acquire gil;
+  py::object cls = py::module_::import("paper_2510_18692_amd.binding").attr("MogaError");
+  PyErr_SetObject(cls.ptr(), cls(fn, status).ptr());
+  throw py::error_already_set();
+}
+
+int dt(const Tensor& t) {
+  if (t.scalar_type() == at::kFloat) return MOGA_F32;
+  if (t.scalar_type() == at::kBFloat16) return MOGA_BF16;
+  raise(PyExc_TypeError, std::string("unsupported dtype ") + c10::toString(t.scalar_type()));
+}
+
+void* ptr(const Tensor& t) {
+  if (!t.is_cuda() || !t.is_contiguous()) raise(PyExc_AssertionError, "device-resident contiguous tensors only");
+  return t.data_ptr();
+}
+void* ptr(const OptTensor& t) { return t ? ptr(*t) : nullptr; }
+template <typename T> T* as(const Tensor& t) { return static_cast<T*>(ptr(t)); }
+template <typename T> T* as(const OptTensor& t) { return static_cast<T*>(ptr(t)); }
+
+void* stream_of(const OptStream& s) { return s ? reinterpret_cast<void*>(*s) : c10::hip::getCurrentHIPStream().stream(); }
+
+// Every function checks its tensors before anything touches the GPU.
+template <typename... T>
+void require(const T&... t) { (ptr(t), ...); }
+
+void need_dims(const Tensor& t, int64_t n) {
+  if (t.dim() != n) raise(PyExc_ValueError, "expected a tensor of " + std::to_string(n) + " dimensions");
+}
+
+Tensor make(at::IntArrayRef size, const Tensor& like, at::ScalarType type) { return at::empty(size, like.options().dtype(type)); }
+Tensor make(at::IntArrayRef size, const Tensor& like) { return at::empty(size, like.options()); }
+Tensor workspace(size_t bytes, const Tensor& like) { return make({std::max<int64_t>((int64_t)bytes, 16)}, like, at::kByte); }
+
+std::tuple<Tensor, Tensor, OptTensor, OptTensor> route(const Tensor& x, const Tensor& w, const OptTensor& bias,
+                                                       bool want_probs, bool want_logits, const OptStream& stream) {
+  require(x, w, bias);
+  need_dims(x, 2);
+  const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
+  Tensor group = make({N}, x, at::kInt), gate = make({N}, x, at::kFloat);
+  OptTensor probs, logits;
+  if (want_probs) probs = make({N, M}, x, at::kFloat);
+  if (want_logits) logits = make({N, M}, x, at::kFloat);
+  check("moga_route", moga_route(ptr(x), dt(x), as<float>(w), as<float>(bias), N, (int)d, (int)M, as<int32_t>(group),
+                                 as<float>(gate), as<float>(probs), as<float>(logits), nullptr, 0, stream_of(stream)));
+  return {group, gate, probs, logits};
+}
+
+struct Permuted {
+  Tensor counts, cu_seqlens, max_seqlen, perm, inv_perm;
+  OptTensor qh, kh, vh;
+};
+
+Permuted permute(const Tensor& group, int64_t M, const OptTensor& q, const OptTensor& k, const OptTensor& v,
+                 const OptStream& stream) {
+  require(group, q, k, v);
+  const int64_t N = group.size(0);
+  Permuted p;
+  p.counts = make({M}, group, at::kInt);
+  p.cu_seqlens = make({M + 1}, group, at::kInt);
+  p.max_seqlen = make({1}, group, at::kInt);
+  p.perm = make({N}, group, at::kInt);
+  p.inv_perm = make({N}, group, at::kInt);
+  int64_t H = 0, D = 0;
+  int type = MOGA_F32;
+  if (q) {
+    need_dims(*q, 3);
+    H = q->size(1);
+    D = q->size(2);
+    type = dt(*q);
+    p.qh = make({H, N, D}, *q);
+    p.kh = make({H, N, D}, k ? *k : *q);
+    p.vh = make({H, N, D}, v ? *v : *q);
+  }
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_PERMUTE, N, (int)H, (int)D, (int)M, 0, type), group);
+  check("moga_permute", moga_permute(as<int32_t>(group), N, (int)M, ptr(q), ptr(k), ptr(v), type, (int)H, (int)D,
+                                     as<int32_t>(p.counts), as<int32_t>(p.cu_seqlens), as<int32_t>(p.max_seqlen),
+                                     as<int32_t>(p.perm), as<int32_t>(p.inv_perm), ptr(p.qh), ptr(p.kh), ptr(p.vh),
+                                     ptr(ws), ws.numel(), stream_of(stream)));
+  return p;
+}
+
+std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& cu,
+                                          double scale, const OptStream& stream, const OptTensor& out, const OptTensor& lse_out) {
+  require(qh, kh, vh, cu, out, lse_out);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
+  Tensor oh = out ? *out : make({H, N, D}, qh);
+  Tensor lse = lse_out ? *lse_out : make({H, N}, qh, at::kFloat);
+  check("moga_group_attn_fwd", moga_group_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M,
+                                                   (float)scale, ptr(oh), as<float>(lse), nullptr, 0, stream_of(stream)));
+  return {oh, lse};
+}
+
+Tensor unpermute(const Tensor& oh, const Tensor& perm, const OptTensor& gate, const OptStream& stream, const OptTensor& out) {
+  require(oh, perm, gate, out);
+  need_dims(oh, 3);
+  const int64_t H = oh.size(0), N = oh.size(1), D = oh.size(2);
+  Tensor o = out ? *out : make({N, H, D}, oh);
+  check("moga_unpermute", moga_unpermute(ptr(oh), dt(oh), as<int32_t>(perm), as<float>(gate), N, (int)H, (int)D, ptr(o), stream_of(stream)));
+  return o;
+}
+
+std::tuple<Tensor, Tensor> unpermute_bwd(const Tensor& d_o, const Tensor& oh, const Tensor& perm, const Tensor& gate,
+                                         const OptStream& stream) {
+  require(d_o, oh, perm, gate);
+  need_dims(oh, 3);
+  const int64_t H = oh.size(0), N = oh.size(1), D = oh.size(2);
+  Tensor d_oh = make({H, N, D}, oh), d_gate = make({N}, oh, at::kFloat);
+  check("moga_unpermute_bwd", moga_unpermute_bwd(ptr(d_o), ptr(oh), dt(oh), as<int32_t>(perm), as<float>(gate), N, (int)H, (int)D,
+                                                 ptr(d_oh), as<float>(d_gate), stream_of(stream)));
+  return {d_oh, d_gate};
+}
+
+std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tensor& qh, const Tensor& kh, const Tensor& vh,
+                                                  const Tensor& oh, const Tensor& lse, const Tensor& cu, double scale,
+                                                  const OptStream& stream, const OptTensor& ws_in) {
+  require(d_oh, qh, kh, vh, oh, lse, cu, ws_in);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
+  Tensor d_qh = make({H, N, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
+  Tensor ws = ws_in ? *ws_in : workspace(moga_workspace_bytes(MOGA_OP_ATTN_BWD, N, (int)H, (int)D, (int)M, 0, dt(qh)), qh);
+  check("moga_group_attn_bwd", moga_group_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H,
+                                                   (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
+                                                   ptr(ws), ws.numel(), stream_of(stream)));
+  return {d_qh, d_kh, d_vh};
+}
+
+std::tuple<Tensor, Tensor, Tensor> permute_bwd(const Tensor& d_qh, const Tensor& d_kh, const Tensor& d_vh, const Tensor& perm,
+                                               const OptStream& stream) {
+  require(d_qh, d_kh, d_vh, perm);
+  need_dims(d_qh, 3);
+  const int64_t H = d_qh.size(0), N = d_qh.size(1), D = d_qh.size(2);
+  Tensor d_q = make({N, H, D}, d_qh), d_k = make({N, H, D}, d_kh), d_v = make({N, H, D}, d_vh);
+  check("moga_permute_bwd", moga_permute_bwd(ptr(d_qh), ptr(d_kh), ptr(d_vh), dt(d_qh), as<int32_t>(perm), N, (int)H, (int)D, ptr(d_q),
+                                             ptr(d_k), ptr(d_v), stream_of(stream)));
+  return {d_q, d_k, d_v};
+}
+
+std::tuple<Tensor, OptTensor> route_bwd(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
+                                        const Tensor& d_gate, bool want_dx, const OptStream& stream) {
+  require(x, w, probs, group, gate, d_gate);
+  need_dims(x, 2);
+  const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
+  Tensor d_w = make({M, d}, x, at::kFloat);
+  OptTensor d_x;
+  if (want_dx) d_x = make({N, d}, x, at::kFloat);
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), x);
+  check("moga_route_bwd", moga_route_bwd(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate),
+                                         as<float>(d_gate), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x), ptr(ws), ws.numel(),
+                                         stream_of(stream)));
+  return {d_w, d_x};
+}
+
+std::tuple<Tensor, Tensor> fused_attn_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& perm, const Tensor& gate,
+                                          const Tensor& cu, double scale, const OptStream& stream) {
+  require(q, k, v, perm, gate, cu);
+  need_dims(q, 3);
+  const int64_t N = q.size(0), H = q.size(1), D = q.size(2), M = cu.size(0) - 1;
+  Tensor o = make({N, H, D}, q), lse = make({H, N}, q, at::kFloat);
+  check("moga_fused_attn_fwd", moga_fused_attn_fwd(ptr(q), ptr(k), ptr(v), dt(q), N, (int)H, (int)D, as<int32_t>(perm), as<float>(gate),
+                                                   as<int32_t>(cu), (int)M, (float)scale, ptr(o), as<float>(lse), stream_of(stream)));
+  return {o, lse};
+}
+
+std::tuple<Tensor, Tensor, Tensor, Tensor> fused_attn_bwd(const Tensor& d_o, const Tensor& q, const Tensor& k, const Tensor& v,
+                                                          const Tensor& o, const Tensor& lse, const Tensor& perm, const Tensor& inv_perm,
+                                                          const Tensor& gate, const Tensor& cu, double scale, const OptStream& stream) {
+  require(d_o, q, k, v, o, lse, perm, inv_perm, gate, cu);
+  need_dims(q, 3);
+  const int64_t N = q.size(0), H = q.size(1), D = q.size(2), M = cu.size(0) - 1;
+  Tensor d_q = make({N, H, D}, q), d_k = make(k.sizes(), k), d_v = make(v.sizes(), v), d_gate = make({N}, q, at::kFloat);
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_ATTN_BWD, N, (int)H, (int)D, (int)M, 0, dt(q)), q);
+  check("moga_fused_attn_bwd", moga_fused_attn_bwd(ptr(d_o), ptr(q), ptr(k), ptr(v), ptr(o), as<float>(lse), dt(q), N, (int)H, (int)D,
+                                                   as<int32_t>(perm), as<int32_t>(inv_perm), as<float>(gate), as<int32_t>(cu), (int)M,
+                                                   (float)scale, ptr(d_q), ptr(d_k), ptr(d_v), as<float>(d_gate), ptr(ws), ws.numel(),
+                                                   stream_of(stream)));
+  return {d_q, d_k, d_v, d_gate};
+}
+
+std::tuple<Tensor, Tensor> varlen_attn_fwd(const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& cu_q, const Tensor& cu_k,
+                                           double scale, const OptStream& stream) {
+  require(qh, kh, vh, cu_q, cu_k);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
+  Tensor oh = make({H, Nq, D}, qh), lse = make({H, Nq}, qh, at::kFloat);
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_FWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh);
+  check("moga_varlen_attn_fwd", moga_varlen_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), Nq, Nk, (int)H, (int)D, as<int32_t>(cu_q),
+                                                     as<int32_t>(cu_k), (int)G, (float)scale, ptr(oh), as<float>(lse), ptr(ws), ws.numel(),
+                                                     stream_of(stream)));
+  return {oh, lse};
+}
+
+std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd(const Tensor& d_oh, const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& oh,
+                                                   const Tensor& lse, const Tensor& cu_q, const Tensor& cu_k, double scale,
+                                                   const OptStream& stream) {
+  require(d_oh, qh, kh, vh, oh, lse, cu_q, cu_k);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
+  Tensor d_qh = make({H, Nq, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_BWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh);
+  check("moga_varlen_attn_bwd", moga_varlen_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), Nq, Nk, (int)H,
+                                                     (int)D, as<int32_t>(cu_q), as<int32_t>(cu_k), (int)G, (float)scale, ptr(d_qh),
+                                                     ptr(d_kh), ptr(d_vh), ptr(ws), ws.numel(), stream_of(stream)));
+  return {d_qh, d_kh, d_vh};
+}
+
+Tensor gather_rows(const Tensor& src, const Tensor& index, const OptStream& stream) {
+  require(src, index);
+  need_dims(src, 3);
+  const int64_t H = src.size(1), D = src.size(2), Nk = index.size(0);
+  Tensor dst = make({H, Nk, D}, src);
+  check("moga_gather_rows", moga_gather_rows(ptr(src), dt(src), as<int32_t>(index), Nk, (int)H, (int)D, ptr(dst), stream_of(stream)));
+  return dst;
+}
+
+Tensor gather_rows_bwd(const Tensor& d_dst, const Tensor& inv_cu, const Tensor& inv_slots, int64_t N, const OptTensor& into,
+                       const OptStream& stream) {
+  require(d_dst, inv_cu, inv_slots, into);
+  need_dims(d_dst, 3);
+  const int64_t H = d_dst.size(0), Nk = d_dst.size(1), D = d_dst.size(2);
+  Tensor d_src = into ? *into : make({N, H, D}, d_dst);
+  check("moga_gather_rows_bwd", moga_gather_rows_bwd(ptr(d_dst), dt(d_dst), as<int32_t>(inv_cu), as<int32_t>(inv_slots), N, Nk, (int)H, (int)D,
+                                                     into ? 1 : 0, ptr(d_src), stream_of(stream)));
+  return d_src;
+}
+
+Tensor gather3_bwd(const Tensor& g_moga, const Tensor& inv_moga, const Tensor& g_stga, const Tensor& inv_cu, const Tensor& inv_slots,
+                   const Tensor& g_frame, const OptTensor& inv_frame, const OptStream& stream) {
+  require(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame);
+  need_dims(g_moga, 3);
+  const int64_t H = g_moga.size(0), N = g_moga.size(1), D = g_moga.size(2), Nk = g_stga.size(1);
+  Tensor d_src = make({N, H, D}, g_moga);
+  check("moga_gather3_bwd", moga_gather3_bwd(ptr(g_moga), as<int32_t>(inv_moga), ptr(g_stga), as<int32_t>(inv_cu), as<int32_t>(inv_slots), Nk,
+                                             ptr(g_frame), as<int32_t>(inv_frame), dt(g_moga), N, (int)H, (int)D, ptr(d_src),
+                                             stream_of(stream)));
+  return d_src;
+}
+
+Tensor merge3_fwd(const Tensor& a_moga, const Tensor& a_stga, const Tensor& a_frame, const OptTensor& inv_moga, const OptTensor& inv_stga,
+                  const OptTensor& inv_frame, const Tensor& gate, const OptStream& stream) {
+  require(a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate);
+  need_dims(a_moga, 3);
+  const int64_t H = a_moga.size(0), N = a_moga.size(1), D = a_moga.size(2);
+  Tensor o = make({N, H, D}, a_moga);
+  check("moga_merge3_fwd", moga_merge3_fwd(ptr(a_moga), ptr(a_stga), ptr(a_frame), dt(a_moga), as<int32_t>(inv_moga), as<int32_t>(inv_stga),
+                                           as<int32_t>(inv_frame), as<float>(gate), N, (int)H, (int)D, ptr(o), stream_of(stream)));
+  return o;
+}
+
+std::tuple<Tensor, Tensor, Tensor, Tensor> merge3_bwd(const Tensor& d_o, const Tensor& a_moga, const OptTensor& inv_moga,
+                                                      const OptTensor& inv_stga, const OptTensor& inv_frame, const Tensor& gate,
+                                                      const OptStream& stream) {
+  require(d_o, a_moga, inv_moga, inv_stga, inv_frame, gate);
+  need_dims(d_o, 3);
+  const int64_t N = d_o.size(0), H = d_o.size(1), D = d_o.size(2);
+  Tensor d_m = make({H, N, D}, d_o), d_s = make({H, N, D}, d_o), d_f = make({H, N, D}, d_o), d_gate = make({N}, d_o, at::kFloat);
+  check("moga_merge3_bwd", moga_merge3_bwd(ptr(d_o), ptr(a_moga), dt(d_o), as<int32_t>(inv_moga), as<int32_t>(inv_stga), as<int32_t>(inv_frame),
+                                           as<float>(gate), N, (int)H, (int)D, ptr(d_m), ptr(d_s), ptr(d_f), as<float>(d_gate),
+                                           stream_of(stream)));
+  return {d_m, d_s, d_f, d_gate};
+}
+
+// `loss` [1] or a scalar
+std::tuple<Tensor, Tensor> balance_into(const Tensor& loss, const Tensor& group, const Tensor& gate, int64_t M, double alpha,
+                                        const OptStream& stream) {
+  require(loss, group, gate);
+  const int64_t N = group.size(0);
+  Tensor frac = make({M}, group, at::kFloat), prob = make({M}, group, at::kFloat);
+  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_BALANCE_LOSS, N, 0, 0, (int)M, 0, MOGA_F32), group);
+  check("moga_balance_loss", moga_balance_loss(as<int32_t>(group), as<float>(gate), N, (int)M, (float)alpha, as<float>(loss), as<float>(frac),
+                                               as<float>(prob), ptr(ws), ws.numel(), stream_of(stream)));
+  return {frac, prob};
+}
+
+std::tuple<Tensor, Tensor, Tensor> balance_loss(const Tensor& group, const Tensor& gate, int64_t M, double alpha, const OptStream& stream) {
+  Tensor loss = make({1}, group, at::kFloat);
+  auto [frac, prob] = balance_into(loss, group, gate, M, alpha, stream);
+  return {loss, frac, prob};
+}
+
+Tensor balance_loss_bwd(const Tensor& group, const Tensor& frac, double alpha, double d_loss, const OptTensor& d_loss_dev,
+                        const OptTensor& into, const OptStream& stream) {
+  require(group, frac, into);
+  const int64_t N = group.size(0), M = frac.size(0);
+  Tensor d_gate = into ? *into : make({N}, group, at::kFloat);
+  OptTensor dev;
+  if (d_loss_dev) dev = d_loss_dev->reshape({1}).to(at::kFloat);
+  check("moga_balance_loss_bwd", moga_balance_loss_bwd(as<int32_t>(group), as<float>(frac), N, (int)M, (float)alpha, (float)d_loss,
+                                                       as<float>(dev), into ? 1 : 0, as<float>(d_gate), stream_of(stream)));
+  return d_gate;
+}
+
+// ---- autograd: Alg. 1 with Eq. 5 and, when alpha is given, the balancing loss of Eqs. 6-8 ----
+struct Attention : public torch::autograd::Function<Attention> {
+  static torch::autograd::variable_list forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& w, const Tensor& q,
+                                                const Tensor& k, const Tensor& v, double scale, std::optional<double> alpha, bool grad_x) {
+    const int64_t M = w.size(0);
+    auto [group, gate, probs, logits] = route(x, w, std::nullopt, true, false, std::nullopt);
+    Permuted p = permute(group, M, q, k, v, std::nullopt);
+    auto [oh, lse] = group_attn_fwd(*p.qh, *p.kh, *p.vh, p.cu_seqlens, scale, std::nullopt, std::nullopt, std::nullopt);
+    Tensor o = unpermute(oh, p.perm, gate, std::nullopt, std::nullopt);
+    Tensor loss, frac;
+    if (alpha) {
+      loss = make({}, x, at::kFloat);
+      frac = std::get<0>(balance_into(loss, group, gate, M, *alpha, std::nullopt));
+    } else {
+      loss = at::zeros({}, x.options().dtype(at::kFloat));
+    }
+    ctx->save_for_backward({x, w, group, gate, *probs, p.cu_seqlens, p.perm, *p.qh, *p.kh, *p.vh, oh, lse, frac});
+    ctx->saved_data["scale"] = scale;
+    ctx->saved_data["alpha"] = alpha;
+    ctx->saved_data["grad_x"] = grad_x;
+    ctx->mark_non_differentiable({group});
+    ctx->set_materialize_grads(false);
+    return {o, loss, group};
+  }
+
+  static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, const torch::autograd::variable_list& grads) {
+    const auto s = ctx->get_saved_variables();
+    const Tensor &x = s[0], &w = s[1], &group = s[2], &gate = s[3], &probs = s[4], &cu = s[5], &perm = s[6], &qh = s[7], &kh = s[8],
+                 &vh = s[9], &oh = s[10], &lse = s[11], &frac = s[12];
+    const double scale = ctx->saved_data["scale"].toDouble();
+    const auto alpha = ctx->saved_data["alpha"].toOptional<double>();
+    const bool grad_x = ctx->saved_data["grad_x"].toBool();
+    Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros({qh.size(1), qh.size(0), qh.size(2)}, qh.options());
+    auto [d_oh, d_gate] = unpermute_bwd(d_o, oh, perm, gate, std::nullopt);
+    auto [d_qh, d_kh, d_vh] = group_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu, scale, std::nullopt, std::nullopt);
+    d_oh.reset();
+    auto [d_q, d_k, d_v] = permute_bwd(d_qh, d_kh, d_vh, perm, std::nullopt);
+    if (alpha && grads[1].defined()) balance_loss_bwd(group, frac, *alpha, 1.0, grads[1], d_gate, std::nullopt);
+    auto [d_w, d_x] = route_bwd(x, w, probs, group, gate, d_gate, grad_x, std::nullopt);
+    Tensor dx;
+    if (d_x) dx = d_x->to(x.scalar_type());
+    return {dx, d_w, d_q, d_k, d_v, Tensor(), Tensor(), Tensor()};
+  }
+};
+
+std::tuple<Tensor, Tensor, Tensor> attention(const Tensor& x, const Tensor& w, const Tensor& q, const Tensor& k, const Tensor& v, double scale,
+                                             std::optional<double> alpha, bool grad_x) {
+  auto r = Attention::apply(x, w, q, k, v, scale, alpha, grad_x);
+  return {r[0], r[1], r[2]};
+}
+
+}  // namespace
+
+PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
+  const auto nogil = py::call_guard<py::gil_scoped_release>();
+  m.def("route", &route, nogil);
+  m.def(
+      "permute",
+      [](const Tensor& group, int64_t M, const OptTensor& q, const OptTensor& k, const OptTensor& v, const OptStream& stream) {
+        Permuted p = permute(group, M, q, k, v, stream);
+        return std::make_tuple(p.counts, p.cu_seqlens, p.max_seqlen, p.perm, p.inv_perm, p.qh, p.kh, p.vh);
+      },
+      nogil);
+  m.def("group_attn_fwd", &group_attn_fwd, nogil);
+  m.def("unpermute", &unpermute, nogil);
+  m.def("unpermute_bwd", &unpermute_bwd, nogil);
+  m.def("group_attn_bwd", &group_attn_bwd, nogil);
+  m.def("permute_bwd", &permute_bwd, nogil);
+  m.def("route_bwd", &route_bwd, nogil);
+  m.def("fused_attn_fwd", &fused_attn_fwd, nogil);
+  m.def("fused_attn_bwd", &fused_attn_bwd, nogil);
+  m.def("varlen_attn_fwd", &varlen_attn_fwd, nogil);
+  m.def("varlen_attn_bwd", &varlen_attn_bwd, nogil);
+  m.def("gather_rows", &gather_rows, nogil);
+  m.def("gather_rows_bwd", &gather_rows_bwd, nogil);
+  m.def("gather3_bwd", &gather3_bwd, nogil);
+  m.def("merge3_fwd", &merge3_fwd, nogil);
+  m.def("merge3_bwd", &merge3_bwd, nogil);
+  m.def("balance_loss", &balance_loss, nogil);
+  m.def("balance_loss_bwd", &balance_loss_bwd, nogil);
+  m.def("attention", &attention, nogil);
+}

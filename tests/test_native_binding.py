@@ -1,0 +1,57 @@
+"""The native half of the binding: errors reach Python as before (CPU), and the native autograd function handles
+outputs that do not take part in the loss (GPU)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_18692_amd import binding as mg
+from paper_2510_18692_amd import workloads as wl
+from paper_2510_18692_amd.autograd import moga_attention
+
+
+def test_host_tensors_are_refused():
+    x, w = torch.zeros(8, 64), torch.zeros(4, 64)
+    with pytest.raises(AssertionError):
+        mg.moga_route(x, w)
+    with pytest.raises(AssertionError):
+        mg.moga_permute(torch.zeros(8, dtype=torch.int32), 4)
+
+
+@pytest.mark.gpu
+def test_status_codes_and_layout_errors_raise():
+    x, w = torch.zeros(8, 64).cuda(), torch.zeros(300, 64).cuda()
+    with pytest.raises(mg.MogaError) as e:
+        mg.moga_route(x, w)
+    assert e.value.status == -2 and "MOGA_ERR_UNSUPPORTED" in str(e.value)
+    with pytest.raises(AssertionError):
+        mg.moga_route(torch.zeros(64, 8).cuda().t(), w[:4])
+    with pytest.raises(TypeError):
+        mg.moga_gather_rows(torch.zeros(8, 2, 64, dtype=torch.float64).cuda(), torch.zeros(3, dtype=torch.int32).cuda())
+    with pytest.raises(ValueError):
+        mg.moga_route(torch.zeros(64).cuda(), w[:4])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("use", ["output", "loss", "both"])
+def test_autograd_with_unused_outputs(use):
+    w = wl.scaled(wl.WORKLOADS["C1b"], N=300)
+    inp = wl.make_inputs(w, "cuda")
+    t = {k: inp[k].clone().requires_grad_() for k in ("W", "Q", "K", "V")}
+    o, lb, _ = moga_attention(inp["X"], t["W"], t["Q"], t["K"], t["V"], w.scale, balance_alpha=0.1)
+    if use == "both":
+        ((o * inp["dO"]).sum() + lb * 2.0).backward()
+    else:
+        ((o * inp["dO"]).sum() if use == "output" else lb * 2.0).backward()
+    # the same gradients from the single calls
+    f = mg.moga_forward(inp["X"], inp["W"], inp["Q"], inp["K"], inp["V"], w.scale)
+    d_o = inp["dO"] if use != "loss" else torch.zeros_like(inp["dO"])
+    d_oh, d_gate = mg.moga_unpermute_bwd(d_o, f["oh"], f["perm"], f["gate"])
+    if use != "output":
+        _, frac, _ = mg.moga_balance_loss(f["group"], f["gate"], w.M, 0.1)
+        mg.moga_balance_loss_bwd(f["group"], frac, 0.1, d_loss=2.0, d_gate=d_gate)
+    hats = mg.moga_group_attn_bwd(d_oh, f["qh"], f["kh"], f["vh"], f["oh"], f["lse"], f["cu_seqlens"], w.scale)
+    ref = dict(zip("QKV", mg.moga_permute_bwd(*hats, f["perm"])))
+    ref["W"], _ = mg.moga_route_bwd(inp["X"], inp["W"], f["probs"], f["group"], f["gate"], d_gate)
+    torch.cuda.synchronize()
+    for k, r in ref.items():
+        assert np.array_equal(t[k].grad.cpu().numpy(), r.cpu().numpy()), k
