@@ -285,8 +285,9 @@ extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void
   }
   const size_t need = moga_varlen_attn_bwd_ws_bytes(Nq, H, G);
   if (!ws || ws_bytes < need || !aligned16(ws)) return MOGA_ERR_WORKSPACE;
-  int32_t* ts_q = (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16);
-  int32_t* ts_k = ts_q + (G + 1);
+  const bool presum = G > MOGA_MAX_GROUPS;   // few groups: every block looks its tile up itself
+  int32_t* ts_q = presum ? (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16) : nullptr;
+  int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
                          ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, st);
 }

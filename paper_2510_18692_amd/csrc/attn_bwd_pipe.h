@@ -142,8 +142,6 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[NB][64 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[NB][64 * kHeadDim];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
 
   const int64_t total = (int64_t)H * tiles_per_head;
   const int64_t work = xcd_work_index(blockIdx.x, total);
@@ -153,7 +151,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   TileInfo ti;
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_q, M, BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, BM, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_q, M, BM, tile, ti)) {
     return;
   }
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -459,8 +457,6 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   __shared__ __attribute__((aligned(256))) float Ls[NB][64];      // -lse / scale
   __shared__ __attribute__((aligned(256))) float Ds[NB][64];      // -delta
   __shared__ int s_flag[NPAIR];   // per pair: number of tiles whose P has been written
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
 
   const int64_t total = (int64_t)H * tiles_per_head;
   const int64_t work = xcd_work_index(blockIdx.x, total);
@@ -471,7 +467,7 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   TileInfo ti;   // tiles run over the key rows of the groups
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_k, M, BK, tile, ti)) return;
-  } else if (!find_tile(cu_k, M, BK, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_k, M, BK, tile, ti)) {
     return;
   }
   const int ge = ti.row_end, k0 = ti.tile_row;

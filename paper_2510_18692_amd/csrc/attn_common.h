@@ -9,9 +9,9 @@ constexpr int kHeadDim = 128;  // head_dim of the bf16 MFMA kernels
 
 // Tile schedule.  Every group g with n_g rows contributes ceil(n_g / rows_per_tile) tiles;
 // tiles never straddle a group boundary.  `tile` is a flat index over all groups in order.
-// Every thread of the block must call this (it contains block-wide barriers).  Returns false
-// when `tile` lies beyond the last real tile (the grid is sized from an upper bound because
-// the group sizes live on the device).
+// Both lookups are done by every wave for itself, with all 64 lanes and no LDS or barrier, and
+// return wave-uniform values (scalar registers).  They return false when `tile` lies beyond the
+// last real tile (the grid is sized from an upper bound because the group sizes live on the device).
 struct TileInfo {
   int group;      // group id
   int row_begin;  // first row of the group (sorted slot)
@@ -19,51 +19,46 @@ struct TileInfo {
   int tile_row;   // first row of this tile
 };
 
-__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ cu_seqlens, int M,
-                                          int rows_per_tile, int tile, int* s_start /*[M+1]*/,
-                                          int* s_found, TileInfo& out) {
+// A lane per group, 64 groups at a time: one round trip to memory and some twenty instructions.  (Through
+// LDS, with two barriers and the group's bounds read again, it took 2 us more of a block's prologue.)
+__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ cu_seqlens, int M, int rows_per_tile, int tile,
+                                          TileInfo& out) {
   const int lane = threadIdx.x & 63;
-  if (threadIdx.x < 64) {
-    int running = 0;
-    for (int g0 = 0; g0 < M; g0 += 64) {
-      const int g = g0 + lane;
-      const int n = g < M ? cu_seqlens[g + 1] - cu_seqlens[g] : 0;
-      const int t = (n + rows_per_tile - 1) / rows_per_tile;
-      int incl = t;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += up;
-      }
-      if (g < M) s_start[g] = running + incl - t;
-      running += __shfl(incl, 63, kWave);
+  int running = 0;
+  for (int g0 = 0; g0 < M; g0 += 64) {
+    const int beg = cu_seqlens[min(g0 + lane, M)], end = cu_seqlens[min(g0 + lane + 1, M)];
+    const int t = (end - beg + rows_per_tile - 1) / rows_per_tile;
+    const int incl = running + wave_scan_add(t);
+    const unsigned long long hit = __ballot(incl - t <= tile && tile < incl);
+    if (hit) {
+      const int l = __builtin_ctzll(hit);
+      out.group = g0 + l;
+      out.row_begin = __builtin_amdgcn_readlane(beg, l);
+      out.row_end = __builtin_amdgcn_readlane(end, l);
+      out.tile_row = out.row_begin + (tile - __builtin_amdgcn_readlane(incl - t, l)) * rows_per_tile;
+      return true;
     }
-    if (lane == 0) { s_start[M] = running; *s_found = -1; }
+    running = __builtin_amdgcn_readlane(incl, 63);
   }
-  __syncthreads();
-  for (int g = threadIdx.x; g < M; g += blockDim.x)
-    if (s_start[g] <= tile && tile < s_start[g + 1]) *s_found = g;
-  __syncthreads();
-  const int g = *s_found;
-  if (g < 0) return false;
-  out.group = g;
-  out.row_begin = cu_seqlens[g];
-  out.row_end = cu_seqlens[g + 1];
-  out.tile_row = out.row_begin + (tile - s_start[g]) * rows_per_tile;
-  return true;
+  return false;
 }
 
-// The same lookup for calls with many groups: `tile_start[g]` (M + 1 entries, written by
-// tile_start_kernel) is the flat index of group g's first tile; every thread binary-searches it.
+// The same lookup for calls with more than MOGA_MAX_GROUPS groups: `tile_start[g]` (M + 1 entries, written
+// by tile_start_kernel) is the flat index of group g's first tile.  The 64 lanes probe 64 entries at
+// once, so 4,096 groups take two dependent loads (a binary search: twelve).
 __device__ __forceinline__ bool find_tile_presummed(const int32_t* __restrict__ tile_start,
                                                     const int32_t* __restrict__ cu_seqlens, int M,
                                                     int rows_per_tile, int tile, TileInfo& out) {
   if (tile >= tile_start[M]) return false;
-  int lo = 0, hi = M;   // invariant: tile_start[lo] <= tile < tile_start[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (tile_start[mid] <= tile) lo = mid; else hi = mid;
-  }
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = M, step;   // tile_start[lo] <= tile, and tile < tile_start[hi]
+  do {
+    step = (hi - lo + 63) >> 6;
+    const int idx = lo + lane * step;
+    const unsigned long long below = __ballot(idx < hi && tile_start[min(idx, M)] <= tile);   // lane 0 always
+    lo += (63 - __builtin_clzll(below)) * step;
+    hi = min(hi, lo + step);
+  } while (step > 1);
   out.group = lo;
   out.row_begin = cu_seqlens[lo];
   out.row_end = cu_seqlens[lo + 1];

@@ -147,14 +147,12 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
   __shared__ __attribute__((aligned(16))) F32Tile<D> Qs;
   __shared__ float s_buf[NW / 2][DT * 16][64];
   __shared__ float s_m[NW][32], s_l[NW][32];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
   const int head = blockIdx.x / tiles_per_head;
   const int tile = blockIdx.x - head * tiles_per_head;
   TileInfo ti;
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_q, M, kF32Rows, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, kF32Rows, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_q, M, kF32Rows, tile, ti)) {
     return;
   }
   const int gs = cu_k[ti.group], n = cu_k[ti.group + 1] - gs;   // keys of the group
@@ -244,14 +242,12 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dq_f32_mfma_kernel(
   __shared__ __attribute__((aligned(16))) F32Tile<D> Qs, Ds;
   __shared__ float s_buf[NW / 2][DT * 16][64];
   __shared__ float s_delta[kF32Rows];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
   const int head = blockIdx.x / tiles_per_head;
   const int tile = blockIdx.x - head * tiles_per_head;
   TileInfo ti;
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_q, M, kF32Rows, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, kF32Rows, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_q, M, kF32Rows, tile, ti)) {
     return;
   }
   const int gs = cu_k[ti.group], n = cu_k[ti.group + 1] - gs;
@@ -320,14 +316,12 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dkdv_f32_mfma_kernel(
   constexpr int NW = kF32Waves, DT = D / 32;
   __shared__ __attribute__((aligned(16))) F32Tile<D> Ks, Vs;
   __shared__ float s_buf[NW / 2][DT * 16][64];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
   const int head = blockIdx.x / tiles_per_head;
   const int tile = blockIdx.x - head * tiles_per_head;
   TileInfo ti;   // tiles run over the key rows of the groups
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_k, M, kF32Rows, tile, ti)) return;
-  } else if (!find_tile(cu_k, M, kF32Rows, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_k, M, kF32Rows, tile, ti)) {
     return;
   }
   const int gs = cu_q[ti.group], n = cu_q[ti.group + 1] - gs;   // queries of the group

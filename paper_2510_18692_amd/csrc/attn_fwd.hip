@@ -119,6 +119,7 @@ extern "C" int moga_varlen_attn_fwd(const void* qh, const void* kh, const void* 
   if (Nk > 0 && (!kh || !vh)) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
   if (!ws || ws_bytes < moga_varlen_attn_fwd_ws_bytes(G)) return MOGA_ERR_WORKSPACE;
-  return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, (int32_t*)ws, G,
+  int32_t* ts = G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)ws;   // few groups: every block looks its tile up itself
+  return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts, G,
                          softmax_scale, oh, lse, (hipStream_t)stream);
 }

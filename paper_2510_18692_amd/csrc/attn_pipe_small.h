@@ -39,8 +39,6 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   constexpr int kAhead = 2;        // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[4][32 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[4][32 * kHeadDim];
-  __shared__ int s_start[MOGA_MAX_GROUPS + 1];
-  __shared__ int s_found;
 
   const int64_t total = (int64_t)H * tiles_per_head;
   const int64_t work = xcd_work_index(blockIdx.x, total);
@@ -50,7 +48,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   TileInfo ti;
   if (tile_start) {
     if (!find_tile_presummed(tile_start, cu_q, M, BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, BM, tile, s_start, &s_found, ti)) {
+  } else if (!find_tile(cu_q, M, BM, tile, ti)) {
     return;
   }
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge

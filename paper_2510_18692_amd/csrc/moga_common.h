@@ -58,6 +58,17 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
+// Inclusive sum over the lanes of a wave with cross-lane data paths of the vector unit (no LDS).
+__device__ __forceinline__ int wave_scan_add(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // rows of 16 lanes: shift by 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // last lane of row 0 / 2 into row 1 / 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // last lane of row 1 into rows 2 and 3
+  return x;
+}
+
 // Value held by the lane 32 away (the other half of the wave).
 __device__ __forceinline__ float other_half(float v) { return __shfl_xor(v, 32, kWave); }
 __device__ __forceinline__ int other_half_i(int v) { return __shfl_xor(v, 32, kWave); }
