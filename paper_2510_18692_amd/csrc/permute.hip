@@ -7,6 +7,7 @@
 //                    first slot for that group; also counts, cu_seqlens, max_seqlen;
 //   3. chunk_rank  : each wave walks its chunk in token order; a token's slot is its chunk's
 //                    running base for the group plus its rank among equal ids in the batch.
+// Up to 16,384 tokens and 32 groups one block does all three (permute_single_block).
 // Data part: 16-byte-per-lane row copies between token order [N, H, D] and head-major
 // group-contiguous order [H, N, D]; the scatter back multiplies by the gate (Eq. 5).
 #include <mutex>
@@ -17,17 +18,33 @@ namespace moga {
 
 // Lanes of this wave (among `valid` ones) that hold the same group id as the caller.
 __device__ __forceinline__ unsigned long long match_group(int g, bool valid, int nbits) {
-  unsigned long long mask = __ballot(valid);
+  const unsigned long long v = __ballot(valid);
+  unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
   for (int b = 0; b < nbits; ++b) {
-    const bool bit = (g >> b) & 1;
-    const unsigned long long bal = __ballot(bit);
-    mask &= bit ? bal : ~bal;
+    const int bit = __builtin_amdgcn_sbfe(g, b, 1);   // 0 or -1
+    const unsigned long long bal = __ballot(bit != 0);
+    lo &= ~((unsigned)bal ^ (unsigned)bit);
+    hi &= ~((unsigned)(bal >> 32) ^ (unsigned)bit);
   }
-  return mask;
+  return lo | ((unsigned long long)hi << 32);
 }
 
 __device__ __forceinline__ int clamp_group(int g, int M) { return g < 0 ? 0 : (g >= M ? M - 1 : g); }
 
+// Group ids of eight consecutive 64-token batches starting at tb, -1 past `end`: all loads in flight
+// together.
+constexpr int kBatches = 8;
+__device__ __forceinline__ void load_groups(int (&g)[kBatches], const int32_t* __restrict__ group, int64_t tb, int64_t end,
+                                            int M) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int b = 0; b < kBatches; ++b) {
+    const int64_t tok = tb + 64 * b + lane;
+    g[b] = tok < end ? clamp_group(group[tok], M) : -1;
+  }
+}
+
+// hist is [M][num_chunks], so that the scan below reads it in rows.
 __global__ __launch_bounds__(256) void chunk_hist_kernel(const int32_t* __restrict__ group,
                                                          int64_t N, int M, int nbits,
                                                          int chunk_len, int num_chunks,
@@ -35,81 +52,86 @@ __global__ __launch_bounds__(256) void chunk_hist_kernel(const int32_t* __restri
   __shared__ int s_hist[4][MOGA_MAX_GROUPS];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int chunk = blockIdx.x * 4 + wave;
+  if (chunk >= num_chunks) return;  // no block-wide barrier below
   volatile int* my = s_hist[wave];
   for (int j = lane; j < M; j += 64) my[j] = 0;
-  if (chunk < num_chunks) {
-    const int64_t t0 = (int64_t)chunk * chunk_len;
-    const int64_t t1 = min(N, t0 + chunk_len);
-    for (int64_t tb = t0; tb < t1; tb += 64) {
-      const int64_t tok = tb + lane;
-      const bool valid = tok < t1;
-      const int g = valid ? clamp_group(group[tok], M) : 0;
-      const unsigned long long mask = match_group(g, valid, nbits);
+  const int64_t t0 = (int64_t)chunk * chunk_len;
+  const int64_t t1 = min(N, t0 + chunk_len);
+  for (int64_t tb = t0; tb < t1; tb += 64 * kBatches) {
+    int g[kBatches];
+    load_groups(g, group, tb, t1, M);
+#pragma unroll
+    for (int b = 0; b < kBatches; ++b) {
+      const unsigned long long mask = match_group(g[b], g[b] >= 0, nbits);
       const unsigned long long below = mask & ((1ull << lane) - 1ull);
-      if (valid && below == 0) my[g] += __popcll(mask);  // one leader per distinct id
+      if (g[b] >= 0 && below == 0) my[g[b]] += __popcll(mask);  // one leader per distinct id
     }
-    for (int j = lane; j < M; j += 64) hist[(int64_t)chunk * M + j] = my[j];
+  }
+  for (int j = lane; j < M; j += 64) hist[(int64_t)j * num_chunks + chunk] = my[j];
+}
+
+// counts, exclusive prefix sum and largest count of the groups: wave 0 of a block, from s_count.
+__device__ __forceinline__ void scan_groups(const int* s_count, int* s_cu, int M, int32_t* __restrict__ counts,
+                                            int32_t* __restrict__ cu_seqlens, int32_t* __restrict__ max_seqlen) {
+  const int lane = threadIdx.x & 63;
+  int running = 0, mx = 0;
+  for (int g0 = 0; g0 < M; g0 += 64) {
+    const int g = g0 + lane;
+    const int v = g < M ? s_count[g] : 0;
+    const int incl = running + wave_scan_add(v);
+    if (g < M) {
+      s_cu[g] = incl - v;
+      cu_seqlens[g] = incl - v;
+      counts[g] = v;
+    }
+    running = __builtin_amdgcn_readlane(incl, 63);
+    mx = max(mx, v);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+  if (lane == 0) {
+    cu_seqlens[M] = running;
+    max_seqlen[0] = mx;
   }
 }
 
-// One block of 1024 threads.  hist [num_chunks][M] is overwritten with each chunk's first slot.
+// One block of 1024 threads.  hist [M][num_chunks] is overwritten with each chunk's first slot for the group.
 __global__ __launch_bounds__(1024) void chunk_scan_kernel(int32_t* __restrict__ hist,
                                                           int num_chunks, int M, int64_t N,
                                                           int32_t* __restrict__ counts,
                                                           int32_t* __restrict__ cu_seqlens,
                                                           int32_t* __restrict__ max_seqlen) {
   __shared__ int s_count[MOGA_MAX_GROUPS];
-  __shared__ int s_cu[MOGA_MAX_GROUPS + 1];
+  __shared__ int s_cu[MOGA_MAX_GROUPS];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int g = wave; g < M; g += 16) {
+    const int32_t* row = hist + (int64_t)g * num_chunks;
     int tot = 0;
-    for (int c = lane; c < num_chunks; c += 64) tot += hist[(int64_t)c * M + g];
+#pragma unroll 8
+    for (int c = lane; c < num_chunks; c += 64) tot += row[c];
     tot = wave_sum_i(tot);
     if (lane == 0) s_count[g] = tot;
   }
   __syncthreads();
-  if (wave == 0) {
-    int running = 0, mx = 0;
-    for (int g0 = 0; g0 < M; g0 += 64) {
-      const int g = g0 + lane;
-      const int v = g < M ? s_count[g] : 0;
-      int incl = v;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += up;
-      }
-      if (g < M) {
-        s_cu[g] = running + incl - v;
-        cu_seqlens[g] = running + incl - v;
-        counts[g] = v;
-      }
-      running += __shfl(incl, 63, kWave);
-      int m = v;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
-      mx = max(mx, m);
-    }
-    if (lane == 0) {
-      s_cu[M] = running;
-      cu_seqlens[M] = running;
-      max_seqlen[0] = mx;
-    }
-  }
+  if (wave == 0) scan_groups(s_count, s_cu, M, counts, cu_seqlens, max_seqlen);
   __syncthreads();
   for (int g = wave; g < M; g += 16) {
+    int32_t* row = hist + (int64_t)g * num_chunks;
     int running = s_cu[g];
-    for (int c0 = 0; c0 < num_chunks; c0 += 64) {
-      const int c = c0 + lane;
-      const int v = c < num_chunks ? hist[(int64_t)c * M + g] : 0;
-      int incl = v;
+    for (int c0 = 0; c0 < num_chunks; c0 += 64 * 8) {
+      int v[8];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += up;
+      for (int i = 0; i < 8; ++i) {
+        const int c = c0 + 64 * i + lane;
+        v[i] = c < num_chunks ? row[c] : 0;
       }
-      if (c < num_chunks) hist[(int64_t)c * M + g] = running + incl - v;
-      running += __shfl(incl, 63, kWave);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = c0 + 64 * i + lane;
+        const int incl = running + wave_scan_add(v[i]);
+        if (c < num_chunks) row[c] = incl - v[i];
+        running = __builtin_amdgcn_readlane(incl, 63);
+      }
     }
   }
 }
@@ -125,24 +147,114 @@ __global__ __launch_bounds__(256) void chunk_rank_kernel(const int32_t* __restri
   const int chunk = blockIdx.x * 4 + wave;
   if (chunk >= num_chunks) return;  // no block-wide barrier below
   volatile int* next = s_next[wave];
-  for (int j = lane; j < M; j += 64) next[j] = base[(int64_t)chunk * M + j];
+  for (int j = lane; j < M; j += 64) next[j] = base[(int64_t)j * num_chunks + chunk];
   const int64_t t0 = (int64_t)chunk * chunk_len;
   const int64_t t1 = min(N, t0 + chunk_len);
-  for (int64_t tb = t0; tb < t1; tb += 64) {
-    const int64_t tok = tb + lane;
-    const bool valid = tok < t1;
-    const int g = valid ? clamp_group(group[tok], M) : 0;
-    const unsigned long long mask = match_group(g, valid, nbits);
-    const int rank = __popcll(mask & ((1ull << lane) - 1ull));
-    int slot = 0;
-    if (valid) slot = next[g] + rank;
-    __builtin_amdgcn_wave_barrier();
-    if (valid) {
-      perm[slot] = (int32_t)tok;
-      inv_perm[tok] = slot;
-      if (rank == 0) next[g] += __popcll(mask);
+  for (int64_t tb = t0; tb < t1; tb += 64 * kBatches) {
+    int g[kBatches];
+    load_groups(g, group, tb, t1, M);
+#pragma unroll
+    for (int b = 0; b < kBatches; ++b) {
+      const bool valid = g[b] >= 0;
+      const unsigned long long mask = match_group(g[b], valid, nbits);
+      const int rank = __popcll(mask & ((1ull << lane) - 1ull));
+      int slot = 0;
+      if (valid) slot = next[g[b]] + rank;
+      __builtin_amdgcn_wave_barrier();
+      if (valid) {
+        const int64_t tok = tb + 64 * b + lane;
+        perm[slot] = (int32_t)tok;
+        inv_perm[tok] = slot;
+        if (rank == 0) next[g[b]] += __popcll(mask);
+      }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// The whole counting sort in one block, for up to 16,384 tokens and 32 groups, where three launches cost
+// more than the work.  A thread takes PER consecutive tokens and counts them in counters of its own
+// (16 bits, [group][thread] in LDS: no conflict and no ballots), which also gives each token its rank among
+// the thread's; a wave then scans a group's 1,024 counters, 16 per lane.  Ids come in and both lists leave
+// through LDS, so that every access to memory is coalesced: one CU takes a cycle per cache line, and with
+// scattered stores 10,007 tokens took 14 us.
+// 4.4 us up to 4,096 and 9.8 us at 10,007 tokens, against 16.5 us for the three kernels.
+constexpr int64_t kSingleBlockTokens = 16384;
+constexpr int kSingleBlockGroups = 32;
+
+template <int PER>
+__global__ __launch_bounds__(1024) void permute_single_block_kernel(const int32_t* __restrict__ group, int N, int M,
+                                                                    int32_t* __restrict__ counts,
+                                                                    int32_t* __restrict__ cu_seqlens,
+                                                                    int32_t* __restrict__ max_seqlen,
+                                                                    int32_t* __restrict__ perm,
+                                                                    int32_t* __restrict__ inv_perm) {
+  constexpr int CAP = 1024 * PER, W = PER / 4;
+  __shared__ unsigned short s_cnt[kSingleBlockGroups][1024];
+  __shared__ unsigned char s_id[CAP];
+  __shared__ unsigned short s_perm[CAP], s_inv[CAP];
+  __shared__ int s_count[kSingleBlockGroups];
+  __shared__ int s_cu[kSingleBlockGroups];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = 1024 * i + tid;
+    s_id[t] = (unsigned char)(t < N ? clamp_group(group[t], M) : 255);
+  }
+  for (int j = 0; j < M; ++j) s_cnt[j][tid] = 0;
+  __syncthreads();
+  unsigned id[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) id[w] = ((const unsigned*)s_id)[tid * W + w];
+  int pos[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const unsigned g = (id[i >> 2] >> (8 * (i & 3))) & 255u;
+    if (g != 255u) {
+      pos[i] = s_cnt[g][tid];
+      s_cnt[g][tid] = (unsigned short)(pos[i] + 1);
+    }
+  }
+  __syncthreads();
+  for (int j = wave; j < M; j += 16) {   // counters of group j -> exclusive sums over the threads
+    unsigned* p = (unsigned*)&s_cnt[j][16 * lane];
+    unsigned c[8];
+    int sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      c[i] = p[i];
+      sum += (c[i] & 0xffff) + (c[i] >> 16);
+    }
+    const int incl = wave_scan_add(sum);
+    int run = incl - sum;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int next = run + (c[i] & 0xffff);
+      p[i] = (unsigned)run | ((unsigned)next << 16);
+      run = next + (c[i] >> 16);
+    }
+    if (lane == 63) s_count[j] = incl;
+  }
+  __syncthreads();
+  if (wave == 0) scan_groups(s_count, s_cu, M, counts, cu_seqlens, max_seqlen);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const unsigned g = (id[i >> 2] >> (8 * (i & 3))) & 255u;
+    if (g != 255u) {
+      const int slot = s_cu[g] + s_cnt[g][tid] + pos[i];
+      s_perm[slot] = (unsigned short)(tid * PER + i);
+      s_inv[tid * PER + i] = (unsigned short)slot;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = 1024 * i + tid;
+    if (t < N) {
+      perm[t] = s_perm[t];
+      inv_perm[t] = s_inv[t];
+    }
   }
 }
 
@@ -586,13 +698,22 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int chunk_len = perm_chunk_len(N);
   const int num_chunks = perm_num_chunks(N);
   const int nbits = bits_for(M);
-  if (num_chunks > 0)
-    chunk_hist_kernel<<<(num_chunks + 3) / 4, 256, 0, st>>>(group, N, M, nbits, chunk_len,
-                                                           num_chunks, hist);
-  chunk_scan_kernel<<<1, 1024, 0, st>>>(hist, num_chunks, M, N, counts, cu_seqlens, max_seqlen);
-  if (num_chunks > 0)
-    chunk_rank_kernel<<<(num_chunks + 3) / 4, 256, 0, st>>>(group, N, M, nbits, chunk_len,
-                                                           num_chunks, hist, perm, inv_perm);
+  if (N <= kSingleBlockTokens && M <= kSingleBlockGroups) {
+#define MOGA_PERMUTE_ONE(PER) \
+  permute_single_block_kernel<PER><<<1, 1024, 0, st>>>(group, (int)N, M, counts, cu_seqlens, max_seqlen, perm, inv_perm)
+    if (N <= 4096) MOGA_PERMUTE_ONE(4);
+    else if (N <= 8192) MOGA_PERMUTE_ONE(8);
+    else MOGA_PERMUTE_ONE(16);
+#undef MOGA_PERMUTE_ONE
+  } else {
+    if (num_chunks > 0)
+      chunk_hist_kernel<<<(num_chunks + 3) / 4, 256, 0, st>>>(group, N, M, nbits, chunk_len,
+                                                             num_chunks, hist);
+    chunk_scan_kernel<<<1, 1024, 0, st>>>(hist, num_chunks, M, N, counts, cu_seqlens, max_seqlen);
+    if (num_chunks > 0)
+      chunk_rank_kernel<<<(num_chunks + 3) / 4, 256, 0, st>>>(group, N, M, nbits, chunk_len,
+                                                             num_chunks, hist, perm, inv_perm);
+  }
   if (with_data && N > 0) {
     Rows3 p;
     p.src[0] = q; p.src[1] = k; p.src[2] = v;
