@@ -20,9 +20,10 @@ def test_host_tensors_are_refused():
 @pytest.mark.gpu
 def test_status_codes_and_layout_errors_raise():
     x, w = torch.zeros(8, 64).cuda(), torch.zeros(300, 64).cuda()
-    with pytest.raises(mg.MogaError) as e:
+    # not `as e`: the exception would keep this frame and its tensors until the next collection of cycles, which the
+    # memory counts of other tests may see
+    with pytest.raises(mg.MogaError, match=r"MOGA_ERR_UNSUPPORTED \(-2\)"):
         mg.moga_route(x, w)
-    assert e.value.status == -2 and "MOGA_ERR_UNSUPPORTED" in str(e.value)
     with pytest.raises(AssertionError):
         mg.moga_route(torch.zeros(64, 8).cuda().t(), w[:4])
     with pytest.raises(TypeError):
