@@ -183,12 +183,12 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
       if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
       if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, ts_q);
       if (small)
-        attn_bwd_dq_pipe_kernel<4, 1, false, 2><<<(unsigned)blocks, 256, 0, st>>>(
+        attn_bwd_dq_pipe_kernel<4, false, 2><<<(unsigned)blocks, 256, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
             (int)tiles, (unsigned short*)d_qh);
       else
-        attn_bwd_dq_pipe_kernel<8, 1><<<(unsigned)blocks, 512, 0, st>>>(
+        attn_bwd_dq_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
             (int)tiles, (unsigned short*)d_qh);
@@ -330,7 +330,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     const int64_t tiles = max_tiles(N, M, 256);
     const int64_t blocks = (tiles * H + 7) / 8 * 8;
     if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    attn_bwd_dq_pipe_kernel<8, 1, true><<<(unsigned)blocks, 512, 0, st>>>(
+    attn_bwd_dq_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
         lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (int)tiles, (unsigned short*)d_q,
         perm);

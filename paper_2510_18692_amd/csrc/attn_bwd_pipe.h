@@ -1,6 +1,6 @@
 // bf16 backward kernels of the group attention (head_dim 128) on the LDS ring of attn_pipe.h.
 //
-//   attn_bwd_dq_pipe_kernel   : a wave owns 32*QW query rows (Q, dO fragments, lse, delta and
+//   attn_bwd_dq_pipe_kernel   : a wave owns 32 query rows (Q, dO fragments, lse, delta and
 //                               the dQ^T accumulators in registers) and sweeps 64-key tiles of
 //                               K and V; three MFMA products per tile (S^T, dP^T, dQ^T).
 //   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 32 key rows and sweeps 64-query
@@ -9,6 +9,8 @@
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both kernels also come as 4-wave blocks with a two-slot
 // ring (64 KB of LDS), two blocks per CU, for groups of a few thousand rows or less.
+// At the power cap like the forward.  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40
+// heads, 32 groups; 2.73 and 2.67 ms at 32,760 x 12, 8 groups.
 #pragma once
 
 #include "attn_pipe.h"
@@ -27,29 +29,29 @@ __device__ __forceinline__ floatx4_t lds_read_f32x4(unsigned addr) {
   return *(const floatx4_t __attribute__((address_space(3)))*)(uintptr_t)addr;
 }
 
-// dQ kernel: P = exp2(s*c - lse2) and dS = P * (dP - delta) for the 16 scores of a lane (one query
-// column per lane, so lse2 and delta are per-lane scalars), dS packed to bf16.
+// dQ kernel: P = exp2(s*c - lse2) and dS = P * (dP - delta) for a lane's eight scores per query column (lse2 and delta
+// are per-lane scalars), dS packed to bf16.
 // `limit`: keys >= limit (relative to the step's first) get P = 0 (MASK only).
 template <bool MASK>
-__device__ __forceinline__ void softmax_bwd_cols(const floatx16_t& s, const floatx16_t& dp, float lse2,
-                                                 float dlt, float c, int h, int limit, bf16x8_t (&dsf)[2]) {
+__device__ __forceinline__ void softmax_bwd_cols(const StepScores& s, const StepScores& dp, const float (&lse2)[2],
+                                                 const float (&dlt)[2], float c, int g, int limit, bf16x8_t (&dsf)[2]) {
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep) {
+  for (int q = 0; q < 2; ++q) {
     unsigned int dd[4];
 #pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      const int v = 8 * kstep + j;
-      float pa = fast_exp2(fmaf(s[v], c, -lse2));
-      float pb = fast_exp2(fmaf(s[v + 1], c, -lse2));
-      if (MASK) {
-        const int idx = 16 * kstep + 8 * h + j;
-        if (idx >= limit) pa = 0.f;
-        if (idx + 1 >= limit) pb = 0.f;
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        float pa = fast_exp2(fmaf(s[t][q][i], c, -lse2[q]));
+        float pb = fast_exp2(fmaf(s[t][q][i + 1], c, -lse2[q]));
+        if (MASK) {
+          const int idx = 8 * g + 4 * t + i;
+          if (idx >= limit) pa = 0.f;
+          if (idx + 1 >= limit) pb = 0.f;
+        }
+        dd[2 * t + (i >> 1)] = pack_bf16x2(pa * (dp[t][q][i] - dlt[q]), pb * (dp[t][q][i + 1] - dlt[q]));
       }
-      dd[j >> 1] = pack_bf16x2(pa * (dp[v] - dlt), pb * (dp[v + 1] - dlt));
-    }
-    const uintx4_t du = {dd[0], dd[1], dd[2], dd[3]};
-    dsf[kstep] = __builtin_bit_cast(bf16x8_t, du);
+    dsf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{dd[0], dd[1], dd[2], dd[3]});
   }
 }
 
@@ -57,70 +59,78 @@ __device__ __forceinline__ void softmax_bwd_cols(const floatx16_t& s, const floa
 // dQ: query-stationary
 // ---------------------------------------------------------------------------------------
 struct DqLane {
-  unsigned k_nat[8];     // K fragment (row = permuted lane row) for d chunk pair ks, slot 0, half 0
-  unsigned v_nat[8];     // same for V
-  unsigned k_tr[4][2];   // transposed K read for d tile dt, rows +0 / +4
+  unsigned k_nat[4];   // K rows, slot 0, half 0
+  unsigned v_nat[4];   // V rows
+  unsigned k_tr[8];    // K transposed
 };
 
 // S^T = K Q^T and dP^T = V dO^T for one 32-key half of a tile
-template <int QW, int SOFF>
-__device__ __forceinline__ void dq_scores(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[QW][8],
-                                          const bf16x8_t (&dof)[QW][8], floatx16_t (&s)[QW],
-                                          floatx16_t (&dp)[QW]) {
+template <int SOFF>
+__device__ __forceinline__ void dq_scores(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[2][4],
+                                          const bf16x8_t (&dof)[2][4], StepScores& s, StepScores& dp) {
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw)
+  for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { s[qw][v] = 0.f; dp[qw][v] = 0.f; }
+    for (int q = 0; q < 2; ++q) s[t][q] = dp[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    const bf16x8_t kf = lds_read_b128(ln.k_nat[ks] + off + SOFF);
-    const bf16x8_t vf = lds_read_b128(ln.v_nat[ks] + off + SOFF);
+  for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-      s[qw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[qw][ks], s[qw], 0, 0, 0);
-      dp[qw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, dof[qw][ks], dp[qw], 0, 0, 0);
+    for (int t = 0; t < 2; ++t) {
+      const bf16x8_t kf = lds_read_b128(ln.k_nat[ks] + off + SOFF + t * kRow4Bytes);
+      const bf16x8_t vf = lds_read_b128(ln.v_nat[ks] + off + SOFF + t * kRow4Bytes);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        s[t][q] = mfma16(kf, qf[q][ks], s[t][q]);
+        dp[t][q] = mfma16(vf, dof[q][ks], dp[t][q]);
+      }
     }
-  }
 }
 
 // dQ^T += K^T dS^T for one 32-key half
-template <int QW, int SOFF>
-__device__ __forceinline__ void dq_accumulate(const DqLane& ln, unsigned off, const bf16x8_t (&dsf)[QW][2],
-                                              floatx16_t (&dq)[QW][4]) {
+template <int SOFF>
+__device__ __forceinline__ void dq_accumulate(const DqLane& ln, unsigned off, const bf16x8_t (&dsf)[2], floatx4_t (&dq)[8][2]) {
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep)
+  for (int dt = 0; dt < 8; ++dt) {
+    const bf16x8_t a = lds_read_tr_frag(ln.k_tr[dt] + off + SOFF);
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      const bf16x8_t a = concat_tr(lds_read_tr16_addr(ln.k_tr[dt][0] + off + SOFF + kstep * 16 * 256),
-                                   lds_read_tr16_addr(ln.k_tr[dt][1] + off + SOFF + kstep * 16 * 256));
-#pragma unroll
-      for (int qw = 0; qw < QW; ++qw)
-        dq[qw][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsf[qw][kstep], dq[qw][dt], 0, 0, 0);
-    }
+    for (int q = 0; q < 2; ++q) dq[dt][q] = mfma16(a, dsf[q], dq[dt][q]);
+  }
 }
 
 // One 64-key tile in four phases, so that the vector work of one half overlaps the matrix
 // work of the other: scores(A) | scores(B) + softmax(A) | dQ(A) + softmax(B) | dQ(B).
-template <int QW, bool MASK, int SOFF>
-__device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[QW][8],
-                                        const bf16x8_t (&dof)[QW][8], const float (&lse2)[QW],
-                                        const float (&dlt)[QW], floatx16_t (&dq)[QW][4], float c, int h,
-                                        int left) {
-  floatx16_t s_a[QW], dp_a[QW], s_b[QW], dp_b[QW];
-  bf16x8_t dsf_a[QW][2], dsf_b[QW][2];
-  dq_scores<QW, SOFF>(ln, off, qf, dof, s_a, dp_a);
+template <bool MASK, int SOFF>
+__device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[2][4],
+                                        const bf16x8_t (&dof)[2][4], const float (&lse2)[2], const float (&dlt)[2],
+                                        floatx4_t (&dq)[8][2], float c, int g, int left) {
+  StepScores s_a, dp_a, s_b, dp_b;
+  bf16x8_t dsf_a[2], dsf_b[2];
+  dq_scores<SOFF>(ln, off, qf, dof, s_a, dp_a);
   __builtin_amdgcn_sched_barrier(0);
-  dq_scores<QW, SOFF + 8192>(ln, off, qf, dof, s_b, dp_b);
+  dq_scores<SOFF + 8192>(ln, off, qf, dof, s_b, dp_b);
+  softmax_bwd_cols<MASK>(s_a, dp_a, lse2, dlt, c, g, left, dsf_a);
+  __builtin_amdgcn_sched_barrier(0);
+  dq_accumulate<SOFF>(ln, off, dsf_a, dq);
+  softmax_bwd_cols<MASK>(s_b, dp_b, lse2, dlt, c, g, left - 32, dsf_b);
+  __builtin_amdgcn_sched_barrier(0);
+  dq_accumulate<SOFF + 8192>(ln, off, dsf_b, dq);
+}
+
+// Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f.
+template <bool GATHER>
+__device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], float f, int row0, int ge, int head, int64_t head_off,
+                                               int H, unsigned short* __restrict__ out, const int32_t* __restrict__ perm) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw)
-    softmax_bwd_cols<MASK>(s_a[qw], dp_a[qw], lse2[qw], dlt[qw], c, h, left, dsf_a[qw]);
-  __builtin_amdgcn_sched_barrier(0);
-  dq_accumulate<QW, SOFF>(ln, off, dsf_a, dq);
+  for (int c = 0; c < 2; ++c) {
+    const int row = row0 + 16 * c + r;
+    if (row < ge) {
+      const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
+      unsigned short* op = out + orow * kHeadDim + 4 * g;
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw)
-    softmax_bwd_cols<MASK>(s_b[qw], dp_b[qw], lse2[qw], dlt[qw], c, h, left - 32, dsf_b[qw]);
-  __builtin_amdgcn_sched_barrier(0);
-  dq_accumulate<QW, SOFF + 8192>(ln, off, dsf_b, dq);
+      for (int dt = 0; dt < 8; ++dt) *(uintx2_t*)(op + 16 * dt) = pack4(acc[dt][c], f);
+    }
+  }
 }
 
 // GATHER (both backward kernels): d_oh, qh, kh, vh and the gradient outputs are token-major
@@ -129,7 +139,7 @@ __device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf
 // raw upstream gradient of the gated output.
 // NB: ring slots of 64 keys (4: two tiles ahead, one block per CU; 2: one tile ahead, 64 KB of LDS, so
 // that two 4-wave blocks share a CU -- the variant for small groups).
-template <int NW, int QW, bool GATHER = false, int NB = 4>
+template <int NW, bool GATHER = false, int NB = 4>
 __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
@@ -137,7 +147,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     int tiles_per_head, unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr) {
-  constexpr int BM = NW * 32 * QW;
+  constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[NB][64 * kHeadDim];
@@ -159,42 +169,25 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   const int n = cu_k[ti.group + 1] - gs;         // number of keys
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int r = lane & 31, h = lane >> 5;
+  const int q0w = q0 + wave * 32;   // first query row of this wave
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
   const float c = scale * 1.4426950408889634f;
 
   if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
-#pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-      const int qrow = q0 + (wave * QW + qw) * 32 + r;
-      if (qrow < ge) {
-        const int64_t orow = GATHER ? (int64_t)perm[qrow] * H + head : head_off + qrow;
-        uintx4_t* op = (uintx4_t*)(d_qh + orow * kHeadDim + 64 * h);
-        const uintx4_t z = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) op[i] = z;
-      }
-    }
+    store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm);
     return;
   }
 
-  bf16x8_t qf[QW][8], dof[QW][8];
-  float lq[QW], dl[QW];
+  bf16x8_t qf[2][4], dof[2][4];
+  load_columns<GATHER>(qf, qh, q0w, ge, head, head_off, H, perm);
+  load_columns<GATHER>(dof, d_oh, q0w, ge, head, head_off, H, perm);
+  float lq[2], dl[2];
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    int qrow = q0 + (wave * QW + qw) * 32 + r;
-    if (qrow > ge - 1) qrow = ge - 1;
-    const int64_t irow = GATHER ? (int64_t)perm[qrow] * H + head : head_off + qrow;
-    const unsigned short* qp = qh + irow * kHeadDim + 8 * h;
-    const unsigned short* dp = d_oh + irow * kHeadDim + 8 * h;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      qf[qw][ks] = *(const bf16x8_t*)(qp + 16 * ks);
-      dof[qw][ks] = *(const bf16x8_t*)(dp + 16 * ks);
-    }
-    lq[qw] = -neg_lse_over_scale[head_off + qrow] * c;   // lse * log2(e)
-    dl[qw] = -neg_delta[head_off + qrow];
+  for (int q = 0; q < 2; ++q) {
+    const int qrow = min(q0w + 16 * q + (lane & 15), ge - 1);
+    lq[q] = -neg_lse_over_scale[head_off + qrow] * c;   // lse * log2(e)
+    dl[q] = -neg_delta[head_off + qrow];
   }
 
   PipeDma dma;
@@ -216,45 +209,25 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   for (int t = 0; t <= kAhead; ++t) pipe_issue<NW, GATHER>(dma, 64 * t, t);
 
   DqLane ln;
-  {
-    const int krow_a = swap_bits_2_3(r);
-    const int k_sw = lds_swizzle(krow_a);
-    const unsigned kb = (unsigned)(uintptr_t)&Ks[0][0];
-    const unsigned vb = (unsigned)(uintptr_t)&Vs[0][0];
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      ln.k_nat[ks] = kb + krow_a * 256 + (((2 * ks + h) ^ k_sw) << 4);
-      ln.v_nat[ks] = vb + krow_a * 256 + (((2 * ks + h) ^ k_sw) << 4);
-    }
-    const int tr_r = 8 * h + ((lane & 15) >> 2);
-    const int tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    const int tr_e = 4 * (lane & 1);
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      ln.k_tr[dt][0] = kb + tr_e * 2 + tr_r * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r)) << 4);
-      ln.k_tr[dt][1] = kb + tr_e * 2 + (tr_r + 4) * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r + 4)) << 4);
-    }
-  }
+  nat_addresses(ln.k_nat, &Ks[0][0], lane);
+  nat_addresses(ln.v_nat, &Vs[0][0], lane);
+  tr_addresses(ln.k_tr, &Ks[0][0], lane);
 
-  floatx16_t dq[QW][4];
+  floatx4_t dq[8][2];
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw)
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dq[qw][dt][v] = 0.f;
+  for (int dt = 0; dt < 8; ++dt) dq[dt][0] = dq[dt][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
   // tile T lives in ring slot T % 4; at the top of tile T the block waits for it, and refills the
   // slot of tile T-1 (which every wave has left) with tile T+3
   const int nfull = n >> 6;   // tiles whose 64 keys are all inside the group
   // a wave whose query rows all lie past the end of the group only moves its share of the tiles
-  const bool active = q0 + wave * 32 * QW < ge;
+  const bool active = q0w < ge;
   int T = 0;
 #define MOGA_DQ_TILE(B)                                                                  \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                      \
   __syncthreads();                                                                       \
   pipe_issue<NW, GATHER>(dma, 64 * (T + (B) + 1 + kAhead), ((B) + 1 + kAhead) & (NB - 1)); \
-  if (active) dq_tile<QW, false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, h, 64);
+  if (active) dq_tile<false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
     MOGA_DQ_TILE(0)
     MOGA_DQ_TILE(1)
@@ -266,31 +239,16 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
     pipe_issue<NW, GATHER>(dma, 64 * (T + 1 + kAhead), (T + 1 + kAhead) & (NB - 1));
-    if (active) dq_tile<QW, false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, h, 64);
+    if (active) dq_tile<false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   }
   if (n & 63) {   // last, partial tile: masked keys contribute zero
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
-    if (active) dq_tile<QW, true, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, h, n - 64 * T);
+    if (active) dq_tile<true, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, n - 64 * T);
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-#pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    const int qrow = q0 + (wave * QW + qw) * 32 + r;
-    if (qrow < ge) {
-      const int64_t orow = GATHER ? (int64_t)perm[qrow] * H + head : head_off + qrow;
-      unsigned short* op = d_qh + orow * kHeadDim + 4 * h;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uintx2_t pk = {pack_bf16x2(dq[qw][dt][4 * b] * scale, dq[qw][dt][4 * b + 1] * scale),
-                         pack_bf16x2(dq[qw][dt][4 * b + 2] * scale, dq[qw][dt][4 * b + 3] * scale)};
-          *(uintx2_t*)(op + 32 * dt + 8 * b) = pk;
-        }
-    }
-  }
+  store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, perm);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -310,87 +268,82 @@ __device__ __forceinline__ void lds_write_b128(unsigned addr, bf16x8_t v) {
 }
 
 struct AbLane {
-  unsigned nat[8];      // rows of Q (A) or dO (B): A operand of the score product, slot 0, half 0
-  unsigned tr[4][2];    // transposed reads of dO (A) or Q (B) for d tile dt, rows +0 / +4
+  unsigned nat[4];      // rows of Q (A) or dO (B): A operand of the score product, slot 0, half 0
+  unsigned tr[8];       // dO (A) or Q (B) transposed
   unsigned init_addr;   // -lse/scale (A) or -delta (B) of the lane's first row
-  unsigned p_addr;      // this lane's 16 bytes in the pair's P buffer (unit 0, kstep 0)
+  unsigned p_addr;      // this lane's 16 bytes in the pair's P buffer (unit 0, key half 0)
 };
 
-// scores of one 32-query unit: acc starts from the per-row constants, then 8 chained MFMAs
+// scores of one 32-query unit ([query operand t][key half]): started from the per-row constants
 template <int SOFF, int SROW>
 __device__ __forceinline__ void ab_scores(const AbLane& ln, unsigned off, unsigned off_row,
-                                          const bf16x8_t (&kvf)[8], floatx16_t& acc) {
-  bf16x8_t nat[8];
+                                          const bf16x8_t (&kvf)[2][4], StepScores& acc) {
+  bf16x8_t nat[2][4];
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) nat[ks] = lds_read_b128(ln.nat[ks] + off + SOFF);
+  for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep)
+    for (int t = 0; t < 2; ++t) nat[t][ks] = lds_read_b128(ln.nat[ks] + off + SOFF + t * kRow4Bytes);
 #pragma unroll
-    for (int half4 = 0; half4 < 2; ++half4) {
-      const floatx4_t iv = lds_read_f32x4(ln.init_addr + off_row + SROW + (16 * kstep + 4 * half4) * 4);
+  for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = lds_read_f32x4(ln.init_addr + off_row + SROW + t * 16);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[8 * kstep + 4 * half4 + e] = iv[e];
-    }
+  for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(nat[ks], kvf[ks], acc, 0, 0, 0);
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k = 0; k < 2; ++k) acc[t][k] = mfma16(nat[t][ks], kvf[k][ks], acc[t][k]);
 }
 
 template <int SOFF>
-__device__ __forceinline__ void ab_load_tr(const AbLane& ln, unsigned off, bf16x8_t (&tr)[2][4]) {
+__device__ __forceinline__ void ab_load_tr(const AbLane& ln, unsigned off, bf16x8_t (&tr)[8]) {
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int kstep = 0; kstep < 2; ++kstep)
-      tr[kstep][dt] = concat_tr(lds_read_tr16_addr(ln.tr[dt][0] + off + SOFF + kstep * 16 * 256),
-                                lds_read_tr16_addr(ln.tr[dt][1] + off + SOFF + kstep * 16 * 256));
+  for (int dt = 0; dt < 8; ++dt) tr[dt] = lds_read_tr_frag(ln.tr[dt] + off + SOFF);
 }
 
-__device__ __forceinline__ void ab_accumulate(const bf16x8_t (&tr)[2][4], const bf16x8_t (&bop)[2],
-                                              floatx16_t (&acc)[4]) {
+__device__ __forceinline__ void ab_accumulate(const bf16x8_t (&tr)[8], const bf16x8_t (&bop)[2], floatx4_t (&acc)[8][2]) {
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep)
+  for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr[kstep][dt], bop[kstep], acc[dt], 0, 0, 0);
+    for (int k = 0; k < 2; ++k) acc[dt][k] = mfma16(tr[dt], bop[k], acc[dt][k]);
 }
 
 // A: P of one 32-query unit from its scores, also written to LDS for the partner.
 template <bool MASK>
-__device__ __forceinline__ void ab_make_p(const AbLane& ln, const floatx16_t& sc, float c, int h, int left, int u,
+__device__ __forceinline__ void ab_make_p(const AbLane& ln, const StepScores& sc, float c, int g, int left, int u,
                                           bf16x8_t (&pf)[2]) {
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep) {
+  for (int k = 0; k < 2; ++k) {
     unsigned int pp[4];
 #pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      const int v = 8 * kstep + j;
-      float pa = fast_exp2(sc[v] * c), pb = fast_exp2(sc[v + 1] * c);
-      if (MASK) {
-        const int idx = 32 * u + 16 * kstep + 8 * h + j;
-        if (idx >= left) pa = 0.f;
-        if (idx + 1 >= left) pb = 0.f;
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        float pa = fast_exp2(sc[t][k][i] * c), pb = fast_exp2(sc[t][k][i + 1] * c);
+        if (MASK) {
+          const int idx = 32 * u + 8 * g + 4 * t + i;
+          if (idx >= left) pa = 0.f;
+          if (idx + 1 >= left) pb = 0.f;
+        }
+        pp[2 * t + (i >> 1)] = pack_bf16x2(pa, pb);
       }
-      pp[j >> 1] = pack_bf16x2(pa, pb);
-    }
-    const uintx4_t pu = {pp[0], pp[1], pp[2], pp[3]};
-    pf[kstep] = __builtin_bit_cast(bf16x8_t, pu);
-    lds_write_b128(ln.p_addr + u * 2048 + kstep * 1024, pf[kstep]);
+    pf[k] = __builtin_bit_cast(bf16x8_t, uintx4_t{pp[0], pp[1], pp[2], pp[3]});
+    lds_write_b128(ln.p_addr + u * 2048 + k * 1024, pf[k]);
   }
 }
 
 // B: dS = P * dP of one unit, P read from LDS.
-__device__ __forceinline__ void ab_take_p(const AbLane& ln, const floatx16_t& dp, int u, bf16x8_t (&dsf)[2]) {
+__device__ __forceinline__ void ab_take_p(const AbLane& ln, const StepScores& dp, int u, bf16x8_t (&dsf)[2]) {
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep) {
-    const uintx4_t pu = __builtin_bit_cast(uintx4_t, lds_read_b128(ln.p_addr + u * 2048 + kstep * 1024));
+  for (int k = 0; k < 2; ++k) {
+    const uintx4_t pu = __builtin_bit_cast(uintx4_t, lds_read_b128(ln.p_addr + u * 2048 + k * 1024));
     unsigned int dd[4];
 #pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      const int v = 8 * kstep + j;
-      dd[j >> 1] = pack_bf16x2(bf16_lo_to_f32(pu[j >> 1]) * dp[v], bf16_hi_to_f32(pu[j >> 1]) * dp[v + 1]);
-    }
-    const uintx4_t du = {dd[0], dd[1], dd[2], dd[3]};
-    dsf[kstep] = __builtin_bit_cast(bf16x8_t, du);
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        const unsigned w = pu[2 * t + (i >> 1)];
+        dd[2 * t + (i >> 1)] = pack_bf16x2(bf16_lo_to_f32(w) * dp[t][k][i], bf16_hi_to_f32(w) * dp[t][k][i + 1]);
+      }
+    dsf[k] = __builtin_bit_cast(bf16x8_t, uintx4_t{dd[0], dd[1], dd[2], dd[3]});
   }
 }
 
@@ -406,18 +359,18 @@ __device__ __forceinline__ void ab_take_p(const AbLane& ln, const floatx16_t& dp
 // pair is only rewritten after that barrier, which B reaches only after it has consumed P.
 template <bool MASK, int SOFF, int SROW>
 __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off, unsigned off_row,
-                                        const bf16x8_t (&kvf)[8], floatx16_t (&acc)[4], float c, int h, int left,
+                                        const bf16x8_t (&kvf)[2][4], floatx4_t (&acc)[8][2], float c, int g, int left,
                                         int* flag, int tile_no, int spin_limit, int* status) {
-  floatx16_t sc[2];   // S (A) or dP (B) of the two 32-query units
-  bf16x8_t bop[2][2]; // B operand of the second product: P (A) or dS (B), per unit and 16-query step
-  bf16x8_t tr0[2][4], tr1[2][4];
+  StepScores sc[2];      // S (A) or dP (B) of the two 32-query units
+  bf16x8_t bop[2][2];    // B operand of the second product: P (A) or dS (B), per unit and key half
+  bf16x8_t tr0[8], tr1[8];
   ab_scores<SOFF, SROW>(ln, off, off_row, kvf, sc[0]);
   ab_scores<SOFF + 8192, SROW + 128>(ln, off, off_row, kvf, sc[1]);
   ab_load_tr<SOFF>(ln, off, tr0);   // in flight while P is computed (A) or awaited (B)
   __builtin_amdgcn_sched_barrier(0);
   if (role == 0) {
-    ab_make_p<MASK>(ln, sc[0], c, h, left, 0, bop[0]);
-    ab_make_p<MASK>(ln, sc[1], c, h, left, 1, bop[1]);
+    ab_make_p<MASK>(ln, sc[0], c, g, left, 0, bop[0]);
+    ab_make_p<MASK>(ln, sc[1], c, g, left, 1, bop[1]);
     __hip_atomic_store(flag, tile_no, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);   // P of this tile is in LDS
   } else {
     int polls = 0;
@@ -477,33 +430,19 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int role = wave / NPAIR, pair = wave % NPAIR;
   int* flag = &s_flag[pair];
-  const int r = lane & 31, h = lane >> 5;
   const int64_t head_off = (int64_t)head * Nk;
   const int64_t head_off_q = (int64_t)head * Nq;
   const float c = scale * 1.4426950408889634f;
-  const int krow = k0 + pair * 32 + r;
+  const int k0w = k0 + pair * 32;   // first key row of this pair
   unsigned short* outp = role == 0 ? d_vh : d_kh;
 
   if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
-    if (krow < ge) {
-      const int64_t orow = GATHER ? (int64_t)perm[krow] * H + head : head_off + krow;
-      uintx4_t* o4 = (uintx4_t*)(outp + orow * kHeadDim + 64 * h);
-      const uintx4_t z = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o4[i] = z;
-    }
+    store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm);
     return;
   }
 
-  // K (A) or V (B) fragments of the pair's 32 key rows: B operand, lane (r, h) holds row r, d = 16*ks + 8*h + 0..7
-  const int krow_c = krow < ge ? krow : ge - 1;
-  bf16x8_t kvf[8];
-  {
-    const int64_t irow = GATHER ? (int64_t)perm[krow_c] * H + head : head_off + krow_c;
-    const unsigned short* kp = (role == 0 ? kh : vh) + irow * kHeadDim + 8 * h;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) kvf[ks] = *(const bf16x8_t*)(kp + 16 * ks);
-  }
+  bf16x8_t kvf[2][4];   // K (A) or V (B) of the pair's 32 key rows
+  load_columns<GATHER>(kvf, role == 0 ? kh : vh, k0w, ge, head, head_off, H, perm);
 
   PipeDma dma;   // "k" = Q rows, "v" = dO rows of this head's group
   dma.kbase = uniform_ptr(GATHER ? qh + (int64_t)head * kHeadDim : qh + (head_off_q + gs) * kHeadDim);
@@ -534,41 +473,25 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   for (int t = 0; t <= kAhead; ++t) issue_tile(t);
 
   AbLane ln;
-  {
-    const int row_a = swap_bits_2_3(r);
-    const int sw = lds_swizzle(row_a);
-    const unsigned nb = role == 0 ? (unsigned)(uintptr_t)&Qs[0][0] : (unsigned)(uintptr_t)&dOs[0][0];
-    const unsigned tb = role == 0 ? (unsigned)(uintptr_t)&dOs[0][0] : (unsigned)(uintptr_t)&Qs[0][0];
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) ln.nat[ks] = nb + row_a * 256 + (((2 * ks + h) ^ sw) << 4);
-    const int tr_r = 8 * h + ((lane & 15) >> 2);
-    const int tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    const int tr_e = 4 * (lane & 1);
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      ln.tr[dt][0] = tb + tr_e * 2 + tr_r * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r)) << 4);
-      ln.tr[dt][1] = tb + tr_e * 2 + (tr_r + 4) * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r + 4)) << 4);
-    }
-    ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&Ls[0][0] : (unsigned)(uintptr_t)&Ds[0][0]) + 8 * h * 4;
-    ln.p_addr = (unsigned)(uintptr_t)&Ps[0][0] + pair * 4096 + lane * 16;
-  }
+  nat_addresses(ln.nat, role == 0 ? &Qs[0][0] : &dOs[0][0], lane);
+  tr_addresses(ln.tr, role == 0 ? &dOs[0][0] : &Qs[0][0], lane);
+  ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&Ls[0][0] : (unsigned)(uintptr_t)&Ds[0][0]) + 8 * (lane >> 4) * 4;
+  ln.p_addr = (unsigned)(uintptr_t)&Ps[0][0] + pair * 4096 + lane * 16;
 
-  floatx16_t acc[4];   // dV^T (A) or dK^T (B): 128 x 32
+  floatx4_t acc[8][2];   // dV^T (A) or dK^T (B): d tile, key half
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
+  for (int dt = 0; dt < 8; ++dt) acc[dt][0] = acc[dt][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
   const int nfull = n >> 6;   // tiles whose 64 queries are all inside the group
   // a pair whose 32 key rows lie past the end of the group (both of its waves) only moves its share of the tiles
-  const bool active = k0 + pair * 32 < ge;
+  const bool active = k0w < ge;
   int T = 0;
 #define MOGA_AB_TILE(B)                                                          \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));              \
   __syncthreads();                                                               \
   issue_tile(T + (B) + 1 + kAhead);                                          \
   if (active)                                                                    \
-    ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, h, 64, flag, \
+    ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
                                                                               T + (B) + 1, spin_limit, status);
   for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
     MOGA_AB_TILE(0)
@@ -583,30 +506,18 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
     issue_tile(T + 1 + kAhead);
     if (active)
       ab_tile<false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                           ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, h, 64, flag, T + 1, spin_limit, status);
+                           ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
   }
   if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
     if (active)
       ab_tile<true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                          ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, h, n - 64 * T, flag, T + 1, spin_limit, status);
+                          ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  if (krow < ge) {
-    const float f = role == 0 ? 1.f : scale;
-    const int64_t orow = GATHER ? (int64_t)perm[krow] * H + head : head_off + krow;
-    unsigned short* op = outp + orow * kHeadDim + 4 * h;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        uintx2_t pk = {pack_bf16x2(acc[dt][4 * b] * f, acc[dt][4 * b + 1] * f),
-                       pack_bf16x2(acc[dt][4 * b + 2] * f, acc[dt][4 * b + 3] * f)};
-        *(uintx2_t*)(op + 32 * dt + 8 * b) = pk;
-      }
-  }
+  store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, perm);
 }
 
 }  // namespace moga

@@ -109,16 +109,51 @@ __device__ __forceinline__ int64_t xcd_work_index(int64_t block, int64_t total) 
   return (block & 7) * per + (block >> 3);
 }
 
-// Row permutation that makes the 32x32 MFMA accumulator registers of a lane hold eight
-// consecutive contraction indices: swap bits 2 and 3 of the row index.
-__device__ __forceinline__ int swap_bits_2_3(int x) {
-  return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1);
+// Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
+// column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a
+// register-resident loop of random operands reaches 2.04-2.18 PFLOP/s with this shape and 1.83-1.86 with 32x32x16
+// (whose accumulators are read and written twice as often per product), and an A fragment from LDS still feeds 32
+// columns when a wave keeps two B fragments.
+__device__ __forceinline__ floatx4_t mfma16(bf16x8_t a, bf16x8_t b, floatx4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// XOR swizzle of the 16-byte chunk index inside an unpadded 256-byte LDS row (128 bf16):
-// chunk' = chunk ^ lds_swizzle(row).  The two low row bits land in chunk bits 3:2 and row bits
-// 3:2 in chunk bits 1:0, which spreads both the row-per-lane 16-byte reads and the 4-row
-// transposed reads over all banks.
-__device__ __forceinline__ int lds_swizzle(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
+// A step takes 32 rows of an LDS tile as two 16-row A operands t = 0, 1; operand row 4 a + b is tile row
+// 8 a + 4 t + b.  A lane's eight results are then eight consecutive rows: the B operand of the second product.
+__device__ __forceinline__ int step_row(int r) { return 8 * (r >> 2) + (r & 3); }   // t = 0; t = 1 is 4 rows further
+constexpr int kRow4Bytes = 4 * kHeadDim * 2;
+
+// XOR swizzle of the 16-byte chunk index inside an unpadded 256-byte LDS row (128 bf16): chunk' = chunk ^
+// lds_swizzle(row).  Row bits 1:0 land in chunk bits 3:2, row bits 4:3 (a) in chunk bits 1:0 as 0, 2, 3, 1: a 16-byte
+// read is served in groups of lanes {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} (and the same plus 32), which then
+// hit all banks once (with 0, 2, 1, 3 every such read took four cycles more), and so do both halves of a transposed read
+// (rows 8 g .. 8 g + 3).  Bit 2 does not count: the second operand and the upper rows of a transposed fragment are
+// constant offsets.
+__device__ __forceinline__ int lds_swizzle(int row) {
+  return ((row & 3) << 2) | (((row >> 2) ^ (row >> 3)) & 2) | ((row >> 4) & 1);
+}
+
+// Per-lane LDS byte addresses (slot 0, first step) of the A operands of a tile at `base`.
+// nat: rows as they are, d = 32 ks + 8 g ..; operand t adds t * kRow4Bytes.  tr: transposed, d = 16 dt + r, 32 tile rows.
+__device__ __forceinline__ void nat_addresses(unsigned (&nat)[4], const void* base, int lane) {
+  const int g = lane >> 4, row = step_row(lane & 15);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+    nat[ks] = (unsigned)(uintptr_t)base + row * 256 + (((4 * ks + g) ^ lds_swizzle(row)) << 4);
+}
+__device__ __forceinline__ void tr_addresses(unsigned (&tr)[8], const void* base, int lane) {
+  const int row = 8 * (lane >> 4) + ((lane & 15) >> 2), c = (lane & 3) >> 1;
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt)
+    tr[dt] = (unsigned)(uintptr_t)base + row * 256 + (((2 * dt + c) ^ lds_swizzle(row)) << 4) + (lane & 1) * 8;
+}
+__device__ __forceinline__ bf16x8_t lds_read_tr_frag(unsigned addr) {
+  return concat_tr(lds_read_tr16_addr(addr), lds_read_tr16_addr(addr + kRow4Bytes));
+}
+
+// Four results of a column (d = 16 dt + 4 g ..) as bf16, scaled.
+__device__ __forceinline__ uintx2_t pack4(const floatx4_t& v, float f) {
+  return uintx2_t{pack_bf16x2(v[0] * f, v[1] * f), pack_bf16x2(v[2] * f, v[3] * f)};
+}
 
 }  // namespace moga

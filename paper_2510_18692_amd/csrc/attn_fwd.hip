@@ -1,12 +1,12 @@
 // Variable-length attention inside groups (Alg. 1 step 3 of the paper; Eq. 1 per group/head).
 //
-// bf16 kernel, head_dim 128, 32x32x16 bf16 MFMA:
-//   * scores are computed transposed, S^T = K Q^T, so that each lane owns one query column:
-//     its softmax statistics are per-lane scalars and a row reduction is 16 registers plus
-//     one exchange with the other half of the wave;
-//   * the K rows fed to the MFMA are permuted (bits 2,3 of the row swapped) so a lane's
-//     accumulator registers hold 8 consecutive keys -- exactly the B operand of the second
-//     product O^T = V^T P^T, which therefore needs no data movement for P;
+// bf16 kernel, head_dim 128, 16x16x32 bf16 MFMA:
+//   * scores are computed transposed, S^T = K Q^T, so that each lane owns two query columns:
+//     their softmax statistics are per-lane scalars, and the four lanes of a query only meet when
+//     its maximum is raised and at the end;
+//   * the K rows fed to the MFMA are permuted (attn_common.h, step_row) so a lane's eight scores of a
+//     query are eight consecutive keys -- exactly the B operand of the second product
+//     O^T = V^T P^T, which therefore needs no data movement for P;
 //   * V^T is read from the row-major V tile in LDS with the transposing LDS read;
 //   * the kernel itself (software pipeline, LDS ring, direct-to-LDS loads) is in attn_pipe.h.
 // fp32 kernel (fp32 matrix instruction, full precision throughout): attn_f32.h.
@@ -42,7 +42,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, (unsigned short*)oh, lse);
   } else if (dtype == MOGA_BF16) {
-    attn_fwd_bf16_pipe_kernel<8, 1><<<(unsigned)blocks, 512, 0, st>>>(
+    attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, (unsigned short*)oh, lse);
   } else if (D == 64) {
@@ -98,7 +98,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   const int64_t tiles = max_tiles(N, M, 256);
   const int64_t blocks = (tiles * H + 7) / 8 * 8;
   if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-  attn_fwd_bf16_pipe_kernel<8, 1, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(
+  attn_fwd_bf16_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(
       (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, cu_seqlens, cu_seqlens,
       nullptr, M, N, N, H, softmax_scale, (int)tiles, (unsigned short*)o, lse, perm, gate);
   return launch_status();

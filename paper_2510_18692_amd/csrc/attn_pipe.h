@@ -6,6 +6,10 @@
 // accumulate O^T += V^T P^T of step s, the vector units reduce the maximum of step s+1.
 // K/V tiles of 64 keys (two steps) are streamed global -> LDS with direct-to-LDS loads into
 // a ring of four buffers, two tiles ahead of their use; one block-wide barrier per tile.
+//
+// Bound by the energy of the matrix instructions at the board's power cap and by the issue of a wave's own
+// instruction stream.  Against the same kernel on 32x32x16: 182.1 -> 175.4 ms at 580,320 x 40 heads, 32 groups,
+// 0.817 -> 0.793 ms at 32,760 x 12, 8 groups (clock 1.80 -> 1.94 GHz for 8 % more cycles).
 #pragma once
 
 #include "attn_common.h"
@@ -17,125 +21,217 @@ constexpr int kPipeAhead = 2;                     // tiles in flight beyond the 
 constexpr int kPipeTileBytes = 64 * kHeadDim * 2; // 16 KB per K (or V) tile
 
 struct PipeLane {
-  // per-lane LDS byte addresses inside buffer 0 (swizzle applied); other buffers, the second
-  // 32-key half and the second 16-key MFMA step are compile-time offsets
-  unsigned k_addr[8];      // K fragment for d chunk pair ks (row = permuted lane row)
-  unsigned v_addr[4][2];   // transposed V read for d tile dt, rows +0 / +4
+  unsigned k[4];   // K rows
+  unsigned v[8];   // V transposed
 };
+
+// Raw scores of a step: [key operand t][query half]; register i is key 8 g + 4 t + i of query column r
+typedef floatx4_t StepScores[2][2];
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// Maximum of a lane's 16 scores combined with the other wave half (all 32 keys of the step).
-__device__ __forceinline__ float step_max(const floatx16_t& s) {
-  float t = max3(s[0], s[1], s[2]);
-  t = max3(t, s[3], s[4]);
-  t = max3(t, s[5], s[6]);
-  t = max3(t, s[7], s[8]);
-  t = max3(t, s[9], s[10]);
-  t = max3(t, s[11], s[12]);
-  t = max3(t, s[13], s[14]);
-  t = fmaxf(t, s[15]);
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// keys of this lane in a 32-key step: register v is key 16*(v/8) + 8*h + v%8
-__device__ __forceinline__ void mask_step(floatx16_t& s, int first_key, int h, int end) {
+// Maximum of a lane's own eight scores per query (the other keys of the step are in three other lanes)
+__device__ __forceinline__ void step_max(const StepScores& s, float (&mx)[2]) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v)
-    if (first_key + 16 * (v >> 3) + 8 * h + (v & 7) >= end) s[v] = -INFINITY;
+  for (int q = 0; q < 2; ++q) {
+    float t = max3(s[0][q][0], s[0][q][1], s[0][q][2]);
+    t = max3(t, s[0][q][3], s[1][q][0]);
+    t = max3(t, s[1][q][1], s[1][q][2]);
+    mx[q] = fmaxf(t, s[1][q][3]);
+  }
 }
 
-template <int QW>
+__device__ __forceinline__ void mask_step(StepScores& s, int first_key, int g, int end) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (first_key + 8 * g + 4 * t + i >= end) s[t][q][i] = -INFINITY;
+}
+
+__device__ __forceinline__ void copy_scores(StepScores& to, const StepScores& from) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) to[t][q] = from[t][q];
+}
+
+__device__ __forceinline__ floatx4_t quarter(const floatx16_t& v, int k) {
+  return floatx4_t{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
+}
+
 struct PipeState {
-  floatx16_t o[QW][4];
-  float m[QW], l[QW], negmc[QW];   // running max (raw score units), row sum, -m*c
-  float thresh[QW];                // m + tau: the max is raised only when a score exceeds this
+  // O^T: [d tiles 4 D .. 4 D + 3][query half], 16 registers each.  As sixteen vectors of four the compiler joins the two
+  // sides of the rare branch in maybe_rescale by moving all 64 registers in every step.
+  floatx16_t o[2][2];
+  float m[2], l[2], negmc[2];     // running max (raw score units), this lane's share of the row sum, -m*c
+  float thresh[2];                // m + tau: the max is raised only when a score exceeds this
 };
 
-template <int QW>
-__device__ __forceinline__ void maybe_rescale(PipeState<QW>& st, const float (&mx)[QW], float c, float tau) {
-  bool need = false;
+__device__ __forceinline__ void pipe_state_init(PipeState& st) {
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw) need |= mx[qw] > st.thresh[qw];
-  if (__any(need)) {   // wave-uniform; after the first step this is rare
+  for (int q = 0; q < 2; ++q) {
+    st.m[q] = -INFINITY;
+    st.l[q] = 0.f;
+    st.negmc[q] = 0.f;
+    st.thresh[q] = -INFINITY;
 #pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-      const float m_new = fmaxf(st.m[qw], mx[qw]);
-      const float alpha = fast_exp2((st.m[qw] - m_new) * c);
-      st.m[qw] = m_new;
-      st.negmc[qw] = -m_new * c;
-      st.thresh[qw] = m_new + tau;
-      st.l[qw] *= alpha;
+    for (int e = 0; e < 16; ++e) st.o[0][q][e] = st.o[1][q][e] = 0.f;
+  }
+}
+
+// The four lanes of a query compare their own maxima with the common threshold; only when one exceeds it is the
+// maximum taken over all four.
+__device__ __forceinline__ void maybe_rescale(PipeState& st, const float (&mx)[2], float c, float tau) {
+  if (__builtin_amdgcn_ballot_w64(mx[0] > st.thresh[0] || mx[1] > st.thresh[1]) != 0) {   // wave-uniform; after the first step this is rare
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+    for (int q = 0; q < 2; ++q) {
+      float all = fmaxf(mx[q], __shfl_xor(mx[q], 16, kWave));
+      all = fmaxf(all, __shfl_xor(all, 32, kWave));
+      const float m_new = fmaxf(st.m[q], all);
+      const float alpha = fast_exp2((st.m[q] - m_new) * c);
+      st.m[q] = m_new;
+      st.negmc[q] = -m_new * c;
+      st.thresh[q] = m_new + tau;
+      st.l[q] *= alpha;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) st.o[qw][dt][v] *= alpha;
+      for (int D = 0; D < 2; ++D)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st.o[D][q][i] *= alpha;
     }
   }
+}
+
+// Scores of a whole step from its K rows at byte offset `off`.
+__device__ __forceinline__ void step_scores(const PipeLane& ln, unsigned off, const bf16x8_t (&qf)[2][4], StepScores& s) {
+  bf16x8_t kf[2][4];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kf[t][ks] = lds_read_b128(ln.k[ks] + off + t * kRow4Bytes);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        s[t][q] = mfma16(kf[t][ks], qf[q][ks], ks == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : s[t][q]);
 }
 
 // One pipeline step.  koff: byte offset (ring slot + half) of the NEXT step's keys; voff: byte
 // offset of the CURRENT step's values.  s_cur holds the current step's raw scores; s_next
-// receives the next step's raw scores (if HAS_NEXT) and mx their maximum.
-template <int QW, bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
-__device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff,
-                                          const bf16x8_t (&qf)[QW][8], PipeState<QW>& st,
-                                          const floatx16_t (&s_cur)[QW], floatx16_t (&s_next)[QW],
-                                          float (&mx)[QW], float c) {
-  bf16x8_t kf[8];
+// receives the next step's raw scores (if HAS_NEXT) and mx their lane maxima.
+template <bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
+__device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff, const bf16x8_t (&qf)[2][4],
+                                          PipeState& st, const StepScores& s_cur, StepScores& s_next, float (&mx)[2],
+                                          float c) {
+  bf16x8_t kf[2][4];
   if (HAS_NEXT) {
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) kf[ks] = lds_read_b128(ln.k_addr[ks] + koff + KOFF);
-  }
-  bf16x8_t vf[2][4];
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    const unsigned a0 = ln.v_addr[dt][0] + voff + VOFF, a1 = ln.v_addr[dt][1] + voff + VOFF;
-#pragma unroll
-    for (int kstep = 0; kstep < 2; ++kstep)
-      vf[kstep][dt] = concat_tr(lds_read_tr16_addr(a0 + kstep * 16 * 256), lds_read_tr16_addr(a1 + kstep * 16 * 256));
+      for (int t = 0; t < 2; ++t) kf[t][ks] = lds_read_b128(ln.k[ks] + koff + KOFF + t * kRow4Bytes);
   }
+  bf16x8_t vf[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) vf[dt] = lds_read_tr_frag(ln.v[dt] + voff + VOFF);
 
   // P = exp2(S*c - m*c), packed to bf16; row sum from the rounded values
   typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
   const bf16x2v ones = {(__bf16)1.0f, (__bf16)1.0f};
-  unsigned int pk[QW][8];
+  unsigned int pk[2][4];
   if (HAS_NEXT) {
 #pragma unroll
-    for (int qw = 0; qw < QW; ++qw)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) s_next[qw][v] = 0.f;
+      for (int q = 0; q < 2; ++q) s_next[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-      if (HAS_NEXT) s_next[qw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[qw][i], s_next[qw], 0, 0, 0);
-      const float p0 = fast_exp2(fmaf(s_cur[qw][2 * i], c, st.negmc[qw]));
-      const float p1 = fast_exp2(fmaf(s_cur[qw][2 * i + 1], c, st.negmc[qw]));
-      pk[qw][i] = pack_bf16x2(p0, p1);
-      st.l[qw] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pk[qw][i]), ones, st.l[qw], false);
+    for (int q = 0; q < 2; ++q) {
+      if (HAS_NEXT) {
+        s_next[0][q] = mfma16(kf[0][ks], qf[q][ks], s_next[0][q]);
+        s_next[1][q] = mfma16(kf[1][ks], qf[q][ks], s_next[1][q]);
+      }
+      const floatx4_t& v = s_cur[ks >> 1][q];
+      const float p0 = fast_exp2(fmaf(v[2 * (ks & 1)], c, st.negmc[q]));
+      const float p1 = fast_exp2(fmaf(v[2 * (ks & 1) + 1], c, st.negmc[q]));
+      pk[q][ks] = pack_bf16x2(p0, p1);
+      st.l[q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pk[q][ks]), ones, st.l[q], false);
     }
   }
-  bf16x8_t pf[QW][2];
+  bf16x8_t pf[2];
 #pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    const uintx4_t plo = {pk[qw][0], pk[qw][1], pk[qw][2], pk[qw][3]};
-    const uintx4_t phi = {pk[qw][4], pk[qw][5], pk[qw][6], pk[qw][7]};
-    pf[qw][0] = __builtin_bit_cast(bf16x8_t, plo);
-    pf[qw][1] = __builtin_bit_cast(bf16x8_t, phi);
+  for (int q = 0; q < 2; ++q) pf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{pk[q][0], pk[q][1], pk[q][2], pk[q][3]});
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      floatx16_t& o = st.o[dt >> 2][q];
+      const floatx4_t t = mfma16(vf[dt], pf[q], quarter(o, dt & 3));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[4 * (dt & 3) + e] = t[e];
+    }
+  if (HAS_NEXT) step_max(s_next, mx);
+}
+
+// Output rows of a wave (query columns r and 16 + r of its 32 rows from q0w): O / l, times the row's gate in gather mode,
+// and the log-sum-exp.  Register i of d tile dt is d = 16 dt + 4 g + i.
+template <bool GATHER>
+__device__ __forceinline__ void store_output(const PipeState& st, int q0w, int ge, int head, int64_t head_off, int H, float scale,
+                                             unsigned short* __restrict__ oh, float* __restrict__ lse,
+                                             const int32_t* __restrict__ perm, const float* __restrict__ gate) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float lt = st.l[q] + __shfl_xor(st.l[q], 16, kWave);
+    lt += __shfl_xor(lt, 32, kWave);
+    float inv = 1.f / lt;
+    const int qrow = q0w + 16 * q + r;
+    if (qrow < ge) {
+      int64_t orow = head_off + qrow;
+      if (GATHER) {
+        const int tok = perm[qrow];
+        orow = (int64_t)tok * H + head;
+        inv *= gate[tok];
+      }
+      unsigned short* op = oh + orow * kHeadDim + 4 * g;
+#pragma unroll
+      for (int dt = 0; dt < 8; ++dt) *(uintx2_t*)(op + 16 * dt) = pack4(quarter(st.o[dt >> 2][q], dt & 3), inv);
+      if (g == 0) lse[head_off + qrow] = st.m[q] * scale + logf(lt);
+    }
   }
+}
+
+// Zero output rows of a wave whose group has no keys (lse = -inf if given).
+template <bool GATHER>
+__device__ __forceinline__ void store_zero_rows(int row0, int ge, int head, int64_t head_off, int H, unsigned short* __restrict__ out,
+                                                float* __restrict__ lse, const int32_t* __restrict__ perm) {
+  const int lane = threadIdx.x & 63, row = row0 + (lane & 31), h = lane >> 5;
+  if (row >= ge) return;
+  const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
+  uintx4_t* op = (uintx4_t*)(out + orow * kHeadDim + 64 * h);
+  const uintx4_t z = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int kstep = 0; kstep < 2; ++kstep)
+  for (int i = 0; i < 8; ++i) op[i] = z;
+  if (lse && h == 0) lse[head_off + row] = -INFINITY;
+}
+
+// B fragments of a wave's 32 rows from row0 (clamped to the last row of the group): columns 16 c + r, d = 32 ks + 8 g ..
+template <bool GATHER>
+__device__ __forceinline__ void load_columns(bf16x8_t (&f)[2][4], const unsigned short* __restrict__ src, int row0, int ge, int head,
+                                             int64_t head_off, int H, const int32_t* __restrict__ perm) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+  for (int c = 0; c < 2; ++c) {
+    const int row = min(row0 + 16 * c + (lane & 15), ge - 1);
+    const int64_t irow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
+    const unsigned short* p = src + irow * kHeadDim + 8 * (lane >> 4);
 #pragma unroll
-      for (int qw = 0; qw < QW; ++qw)
-        st.o[qw][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kstep][dt], pf[qw][kstep], st.o[qw][dt], 0, 0, 0);
-  if (HAS_NEXT) {
-#pragma unroll
-    for (int qw = 0; qw < QW; ++qw) mx[qw] = step_max(s_next[qw]);
+    for (int ks = 0; ks < 4; ++ks) f[c][ks] = *(const bf16x8_t*)(p + 32 * ks);
   }
 }
 
@@ -166,7 +262,8 @@ __device__ __forceinline__ void pipe_issue_tile(const PipeDma& d, int kv0, int b
 #pragma unroll
   for (int i = 0; i < 16 / NW; ++i) {
     const int row = min(kv0 + d.row0 + 4 * NW * i, d.last_row);
-    const unsigned off = (unsigned)row * (kHeadDim * 2) + d.chunk_off;
+    // four waves: every other round is 16 rows further, which the swizzle turns into chunk ^ 3
+    const unsigned off = (unsigned)row * (kHeadDim * 2) + (NW == 4 && (i & 1) ? d.chunk_off ^ 48u : d.chunk_off);
     lds_dma16_soff(d.kbase, off, d.lds_k + boff + i * 4 * NW * 256);
     lds_dma16_soff(d.vbase, off, d.lds_v + boff + i * 4 * NW * 256);
   }
@@ -252,7 +349,7 @@ __device__ __forceinline__ void pipe_issue(PipeDma& d, int kv0, int buf) {
 // GATHER: qh, kh, vh and oh are token-major [N, H, 128]; row j of a group is token perm[j] (the
 // permutation of Alg. 1 is applied while loading, nothing is materialised) and the output row is
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
-template <int NW, int QW, bool GATHER = false>
+template <int NW, bool GATHER = false>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
@@ -260,7 +357,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, unsigned short* __restrict__ oh,
     float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
     const float* __restrict__ gate = nullptr) {
-  constexpr int BM = NW * 32 * QW;
+  constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);   // direct-to-LDS instructions per thread per tile
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[kPipeNBuf][64 * kHeadDim];
@@ -282,39 +379,19 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   const int n = cu_k[ti.group + 1] - gs;         // number of keys
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int r = lane & 31, h = lane >> 5;
+  const int q0w = q0 + wave * 32;   // first query row of this wave
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
   const float c = scale * 1.4426950408889634f;
   const float tau = 8.f / c;
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-#pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-      const int qrow = q0 + (wave * QW + qw) * 32 + r;
-      if (qrow < ge) {
-        const int64_t orow = GATHER ? (int64_t)perm[qrow] * H + head : head_off + qrow;
-        uintx4_t* op = (uintx4_t*)(oh + orow * kHeadDim + 64 * h);
-        const uintx4_t z = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) op[i] = z;
-        if (h == 0) lse[head_off + qrow] = -INFINITY;
-      }
-    }
+    store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm);
     return;
   }
 
-  // ---- Q fragments (B operand): lane (r, h) holds Q[q = r][d = 16*ks + 8*h + 0..7]
-  bf16x8_t qf[QW][8];
-#pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    int qrow = q0 + (wave * QW + qw) * 32 + r;
-    if (qrow > ge - 1) qrow = ge - 1;
-    const int64_t irow = GATHER ? (int64_t)perm[qrow] * H + head : head_off + qrow;
-    const unsigned short* qp = qh + irow * kHeadDim + 8 * h;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[qw][ks] = *(const bf16x8_t*)(qp + 16 * ks);
-  }
+  bf16x8_t qf[2][4];
+  load_columns<GATHER>(qf, qh, q0w, ge, head, head_off, H, perm);
 
   // ---- direct-to-LDS loads: first kPipeAhead + 1 tiles (always issued; rows are clamped)
   PipeDma dma;
@@ -335,37 +412,11 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
 #pragma unroll
   for (int t = 0; t <= kPipeAhead; ++t) pipe_issue<NW, GATHER>(dma, 64 * t, t);
 
-  // ---- per-lane LDS read addresses
   PipeLane ln;
-  {
-    const int krow_a = swap_bits_2_3(r);
-    const int k_sw = lds_swizzle(krow_a);
-    const unsigned kb = (unsigned)(uintptr_t)&Ks[0][0] + krow_a * 256;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) ln.k_addr[ks] = kb + (((2 * ks + h) ^ k_sw) << 4);
-    const int tr_r = 8 * h + ((lane & 15) >> 2);
-    const int tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    const int tr_e = 4 * (lane & 1);
-    const unsigned vb = (unsigned)(uintptr_t)&Vs[0][0] + tr_e * 2;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      ln.v_addr[dt][0] = vb + tr_r * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r)) << 4);
-      ln.v_addr[dt][1] = vb + (tr_r + 4) * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r + 4)) << 4);
-    }
-  }
-
-  PipeState<QW> st;
-#pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    st.m[qw] = -INFINITY;
-    st.l[qw] = 0.f;
-    st.negmc[qw] = 0.f;
-    st.thresh[qw] = -INFINITY;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) st.o[qw][dt][v] = 0.f;
-  }
+  nat_addresses(ln.k, &Ks[0][0], lane);
+  tr_addresses(ln.v, &Vs[0][0], lane);
+  PipeState st;
+  pipe_state_init(st);
 
   const int nsteps = (n + 31) >> 5;
   const int nfull = n >> 5;   // steps whose 32 keys are all inside the group
@@ -373,7 +424,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   // ---- prologue: scores of step 0
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kPipeAhead));
   __syncthreads();
-  if (q0 + wave * 32 * QW >= ge) {
+  if (q0w >= ge) {
     // Every query row of this wave lies past the end of the group (last tile of a group): it only moves
     // its share of the K/V tiles and keeps the barriers of the loops below, one for one, so that no
     // matrix or vector work is spent on padding.
@@ -402,23 +453,11 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     return;
   }
-  floatx16_t s_a[QW], s_b[QW];   // scores of even / odd steps
-  float mx[QW];
-  {
-    bf16x8_t kf[8];
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) kf[ks] = lds_read_b128(ln.k_addr[ks]);
-#pragma unroll
-    for (int qw = 0; qw < QW; ++qw) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) s_a[qw][v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        s_a[qw] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[qw][ks], s_a[qw], 0, 0, 0);
-      if (nfull == 0) mask_step(s_a[qw], 0, h, n);
-      mx[qw] = step_max(s_a[qw]);
-    }
-  }
+  StepScores s_a, s_b;   // scores of even / odd steps
+  float mx[2];
+  step_scores(ln, 0, qf, s_a);
+  if (nfull == 0) mask_step(s_a, 0, lane >> 4, n);
+  step_max(s_a, mx);
 
   // ---- main loop.  Tile T (64 keys, two steps) lives in ring slot T % 4.  Step 2T reads its
   // values and the next step's keys from that slot; then the block waits for tile T+1, refills
@@ -426,13 +465,13 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   // of tile T+1.  Four tiles per iteration so that every LDS offset is an immediate.
   int s = 0;
 #define MOGA_FWD_TILE(B)                                                                        \
-  maybe_rescale<QW>(st, mx, c, tau);                                                            \
-  pipe_step<QW, true, (B) * kPipeTileBytes + 8192, (B) * kPipeTileBytes>(ln, 0, 0, qf, st, s_a, s_b, mx, c); \
+  maybe_rescale(st, mx, c, tau);                                                            \
+  pipe_step<true, (B) * kPipeTileBytes + 8192, (B) * kPipeTileBytes>(ln, 0, 0, qf, st, s_a, s_b, mx, c); \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));                       \
   __syncthreads();                                                                              \
   pipe_issue<NW, GATHER>(dma, 32 * s + 64 * ((B) + 1 + kPipeAhead), ((B) + 1 + kPipeAhead) & 3); \
-  maybe_rescale<QW>(st, mx, c, tau);                                                            \
-  pipe_step<QW, true, (((B) + 1) & 3) * kPipeTileBytes, (B) * kPipeTileBytes + 8192>(ln, 0, 0, qf, st, s_b, s_a, mx, c);
+  maybe_rescale(st, mx, c, tau);                                                            \
+  pipe_step<true, (((B) + 1) & 3) * kPipeTileBytes, (B) * kPipeTileBytes + 8192>(ln, 0, 0, qf, st, s_b, s_a, mx, c);
   for (; s + 8 <= nfull - 1; s += 8) {   // steps s .. s+7 and their successors are full
     MOGA_FWD_TILE(0)
     MOGA_FWD_TILE(1)
@@ -444,13 +483,13 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   while (s + 2 <= nfull - 1) {
     const unsigned slot = ((unsigned)(s >> 1) & 3u) * kPipeTileBytes;
     const unsigned slot_next = ((unsigned)((s >> 1) + 1) & 3u) * kPipeTileBytes;
-    maybe_rescale<QW>(st, mx, c, tau);
-    pipe_step<QW, true>(ln, slot + 8192, slot, qf, st, s_a, s_b, mx, c);
+    maybe_rescale(st, mx, c, tau);
+    pipe_step<true>(ln, slot + 8192, slot, qf, st, s_a, s_b, mx, c);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
     __syncthreads();
     pipe_issue<NW, GATHER>(dma, 32 * (s + 2) + 64 * kPipeAhead, ((s >> 1) + 1 + kPipeAhead) & 3);
-    maybe_rescale<QW>(st, mx, c, tau);
-    pipe_step<QW, true>(ln, slot_next, slot + 8192, qf, st, s_b, s_a, mx, c);
+    maybe_rescale(st, mx, c, tau);
+    pipe_step<true>(ln, slot_next, slot + 8192, qf, st, s_b, s_a, mx, c);
     s += 2;
   }
 
@@ -463,49 +502,23 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
       __syncthreads();
       pipe_issue<NW, GATHER>(dma, 32 * (s + 1) + 64 * kPipeAhead, (buf + 1 + kPipeAhead) & 3);
     }
-    maybe_rescale<QW>(st, mx, c, tau);
+    maybe_rescale(st, mx, c, tau);
     const unsigned voff = buf * kPipeTileBytes + half * 8192;
     const unsigned koff = (half ? ((buf + 1) & 3) : buf) * kPipeTileBytes + (half ? 0 : 8192);
     if (has_next) {
-      pipe_step<QW, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
-#pragma unroll
-      for (int qw = 0; qw < QW; ++qw) {
-        if (s + 1 >= nfull) mask_step(s_b[qw], 32 * (s + 1), h, n);
-        s_a[qw] = s_b[qw];
-        if (s + 1 >= nfull) mx[qw] = step_max(s_a[qw]);
+      pipe_step<true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      if (s + 1 >= nfull) {
+        mask_step(s_b, 32 * (s + 1), lane >> 4, n);
+        step_max(s_b, mx);
       }
+      copy_scores(s_a, s_b);
     } else {
-      pipe_step<QW, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
     }
   }
 
-  // ---- epilogue: register v of d tile dt is d = 32*dt + 8*(v/4) + 4*h + v%4 of query column r
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-#pragma unroll
-  for (int qw = 0; qw < QW; ++qw) {
-    const auto rr = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.l[qw]), __float_as_uint(st.l[qw]), false, false);
-    const float lt = __uint_as_float(rr[0]) + __uint_as_float(rr[1]);
-    float inv = 1.f / lt;
-    const int qrow = q0 + (wave * QW + qw) * 32 + r;
-    if (qrow < ge) {
-      int64_t orow = head_off + qrow;
-      if (GATHER) {
-        const int tok = perm[qrow];
-        orow = (int64_t)tok * H + head;
-        inv *= gate[tok];
-      }
-      unsigned short* op = oh + orow * kHeadDim + 4 * h;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uintx2_t pk = {pack_bf16x2(st.o[qw][dt][4 * b] * inv, st.o[qw][dt][4 * b + 1] * inv),
-                         pack_bf16x2(st.o[qw][dt][4 * b + 2] * inv, st.o[qw][dt][4 * b + 3] * inv)};
-          *(uintx2_t*)(op + 32 * dt + 8 * b) = pk;
-        }
-      if (h == 0) lse[head_off + qrow] = st.m[qw] * scale + logf(lt);
-    }
-  }
+  store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate);
 }
 
 }  // namespace moga

@@ -21,7 +21,7 @@ __device__ __forceinline__ void small_issue_tile(const PipeDma& d, int kv0, int 
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int row = min(kv0 + d.row0 + 16 * i, d.last_row);
-    const unsigned off = (unsigned)row * (kHeadDim * 2) + d.chunk_off;
+    const unsigned off = (unsigned)row * (kHeadDim * 2) + (i ? d.chunk_off ^ 48u : d.chunk_off);   // 16 rows: chunk ^ 3
     lds_dma16_soff(d.kbase, off, d.lds_k + boff + i * 4096);
     lds_dma16_soff(d.vbase, off, d.lds_v + boff + i * 4096);
   }
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, unsigned short* __restrict__ oh,
     float* __restrict__ lse) {
-  constexpr int NW = 4, QW = 1, BM = 128;
+  constexpr int BM = 128;
   constexpr int kDmaPerTile = 4;   // direct-to-LDS instructions per thread per tile
   constexpr int kAhead = 2;        // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[4][32 * kHeadDim];
@@ -56,32 +56,19 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   const int n = cu_k[ti.group + 1] - gs;         // number of keys
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int r = lane & 31, h = lane >> 5;
+  const int q0w = q0 + wave * 32;   // first query row of this wave
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
   const float c = scale * 1.4426950408889634f;
   const float tau = 8.f / c;
-  const int qrow = q0 + wave * 32 + r;
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-    if (qrow < ge) {
-      uintx4_t* op = (uintx4_t*)(oh + (head_off + qrow) * kHeadDim + 64 * h);
-      const uintx4_t z = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) op[i] = z;
-      if (h == 0) lse[head_off + qrow] = -INFINITY;
-    }
+    store_zero_rows<false>(q0w, ge, head, head_off, H, oh, lse, nullptr);
     return;
   }
 
-  // Q fragments (B operand): lane (r, h) holds Q[q = r][d = 16*ks + 8*h + 0..7]
-  bf16x8_t qf[QW][8];
-  {
-    const int qr = qrow > ge - 1 ? ge - 1 : qrow;
-    const unsigned short* qp = qh + (head_off + qr) * kHeadDim + 8 * h;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[0][ks] = *(const bf16x8_t*)(qp + 16 * ks);
-  }
+  bf16x8_t qf[2][4];
+  load_columns<false>(qf, qh, q0w, ge, head, head_off, H, nullptr);
 
   PipeDma dma;
   dma.kbase = uniform_ptr(kh + (head_off_k + gs) * kHeadDim);
@@ -95,32 +82,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   for (int t = 0; t <= kAhead; ++t) small_issue_tile(dma, 32 * t, t);   // rows are clamped: always issued
 
   PipeLane ln;
-  {
-    const int krow_a = swap_bits_2_3(r);
-    const int k_sw = lds_swizzle(krow_a);
-    const unsigned kb = (unsigned)(uintptr_t)&Ks[0][0] + krow_a * 256;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) ln.k_addr[ks] = kb + (((2 * ks + h) ^ k_sw) << 4);
-    const int tr_r = 8 * h + ((lane & 15) >> 2);
-    const int tr_c = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
-    const int tr_e = 4 * (lane & 1);
-    const unsigned vb = (unsigned)(uintptr_t)&Vs[0][0] + tr_e * 2;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-      ln.v_addr[dt][0] = vb + tr_r * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r)) << 4);
-      ln.v_addr[dt][1] = vb + (tr_r + 4) * 256 + (((4 * dt + tr_c) ^ lds_swizzle(tr_r + 4)) << 4);
-    }
-  }
-
-  PipeState<QW> st;
-  st.m[0] = -INFINITY;
-  st.l[0] = 0.f;
-  st.negmc[0] = 0.f;
-  st.thresh[0] = -INFINITY;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) st.o[0][dt][v] = 0.f;
+  nat_addresses(ln.k, &Ks[0][0], lane);
+  tr_addresses(ln.v, &Vs[0][0], lane);
+  PipeState st;
+  pipe_state_init(st);
 
   const int nsteps = (n + 31) >> 5;
   const int nfull = n >> 5;   // steps whose 32 keys are all inside the group
@@ -128,7 +93,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   // prologue: scores of step 0 (tile 0)
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
   __syncthreads();
-  if (q0 + wave * 32 >= ge) {
+  if (q0w >= ge) {
     // every query row of this wave lies past the end of the group: it only moves its share of the K/V
     // tiles and keeps the barriers of the loops below, one per step
     for (int s = 0; s < nsteps; ++s) {
@@ -139,20 +104,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     return;
   }
-  floatx16_t s_a[QW], s_b[QW];   // scores of even / odd steps
-  float mx[QW];
-  {
-    bf16x8_t kf[8];
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) kf[ks] = lds_read_b128(ln.k_addr[ks]);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) s_a[0][v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      s_a[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[0][ks], s_a[0], 0, 0, 0);
-    if (nfull == 0) mask_step(s_a[0], 0, h, n);
-    mx[0] = step_max(s_a[0]);
-  }
+  StepScores s_a, s_b;   // scores of even / odd steps
+  float mx[2];
+  step_scores(ln, 0, qf, s_a);
+  if (nfull == 0) mask_step(s_a, 0, lane >> 4, n);
+  step_max(s_a, mx);
 
   // main loop.  Step s (= tile s) lives in ring slot s % 4: it reads its values from that slot and
   // the keys of step s+1 from the next one.  At the top of a step the block waits for tile s+1 and
@@ -163,8 +119,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));                     \
   __syncthreads();                                                                        \
   small_issue_tile(dma, 32 * (s + (B) + 1 + kAhead), ((B) + 1 + kAhead) & 3);             \
-  maybe_rescale<QW>(st, mx, c, tau);                                                      \
-  pipe_step<QW, true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c);
+  maybe_rescale(st, mx, c, tau);                                                      \
+  pipe_step<true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c);
   for (; s + 4 <= nfull - 1; s += 4) {   // steps s .. s+3 and their successors are full
     MOGA_SMALL_STEP(0, s_a, s_b)
     MOGA_SMALL_STEP(1, s_b, s_a)
@@ -179,38 +135,23 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     __syncthreads();
     small_issue_tile(dma, 32 * (s + 1 + kAhead), (s + 1 + kAhead) & 3);
     const bool has_next = s + 1 < nsteps;
-    maybe_rescale<QW>(st, mx, c, tau);
+    maybe_rescale(st, mx, c, tau);
     const unsigned voff = (unsigned)(s & 3) * kSmallTileBytes;
     const unsigned koff = (unsigned)((s + 1) & 3) * kSmallTileBytes;
     if (has_next) {
-      pipe_step<QW, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
-      if (s + 1 >= nfull) mask_step(s_b[0], 32 * (s + 1), h, n);
-      s_a[0] = s_b[0];
-      if (s + 1 >= nfull) mx[0] = step_max(s_a[0]);
+      pipe_step<true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      if (s + 1 >= nfull) {
+        mask_step(s_b, 32 * (s + 1), lane >> 4, n);
+        step_max(s_b, mx);
+      }
+      copy_scores(s_a, s_b);
     } else {
-      pipe_step<QW, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
     }
   }
 
-  // epilogue: register v of d tile dt is d = 32*dt + 8*(v/4) + 4*h + v%4 of query column r
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  {
-    const auto rr = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.l[0]), __float_as_uint(st.l[0]), false, false);
-    const float lt = __uint_as_float(rr[0]) + __uint_as_float(rr[1]);
-    const float inv = 1.f / lt;
-    if (qrow < ge) {
-      unsigned short* op = oh + (head_off + qrow) * kHeadDim + 4 * h;
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uintx2_t pk = {pack_bf16x2(st.o[0][dt][4 * b] * inv, st.o[0][dt][4 * b + 1] * inv),
-                         pack_bf16x2(st.o[0][dt][4 * b + 2] * inv, st.o[0][dt][4 * b + 3] * inv)};
-          *(uintx2_t*)(op + 32 * dt + 8 * b) = pk;
-        }
-      if (h == 0) lse[head_off + qrow] = st.m[0] * scale + logf(lt);
-    }
-  }
+  store_output<false>(st, q0w, ge, head, head_off, H, scale, oh, lse, nullptr, nullptr);
 }
 
 }  // namespace moga
