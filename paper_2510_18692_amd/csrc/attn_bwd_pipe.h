@@ -99,17 +99,19 @@ __device__ __forceinline__ void dq_accumulate(const DqLane& ln, unsigned off, co
 
 // One 64-key tile in four phases, so that the vector work of one half overlaps the matrix
 // work of the other: scores(A) | scores(B) + softmax(A) | dQ(A) + softmax(B) | dQ(B).
-template <bool MASK, int SOFF>
+template <bool PRIO, bool MASK, int SOFF>
 __device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[2][4],
                                         const bf16x8_t (&dof)[2][4], const float (&lse2)[2], const float (&dlt)[2],
                                         floatx4_t (&dq)[8][2], float c, int g, int left) {
   StepScores s_a, dp_a, s_b, dp_b;
   bf16x8_t dsf_a[2], dsf_b[2];
+  wave_priority<PRIO, 1>();   // scores and softmax before the other wave's dQ products (the other way round: no gain)
   dq_scores<SOFF>(ln, off, qf, dof, s_a, dp_a);
   __builtin_amdgcn_sched_barrier(0);
   dq_scores<SOFF + 8192>(ln, off, qf, dof, s_b, dp_b);
   softmax_bwd_cols<MASK>(s_a, dp_a, lse2, dlt, c, g, left, dsf_a);
   __builtin_amdgcn_sched_barrier(0);
+  wave_priority<PRIO, 0>();
   dq_accumulate<SOFF>(ln, off, dsf_a, dq);
   softmax_bwd_cols<MASK>(s_b, dp_b, lse2, dlt, c, g, left - 32, dsf_b);
   __builtin_amdgcn_sched_barrier(0);
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                      \
   __syncthreads();                                                                       \
   pipe_issue<NW, GATHER>(dma, 64 * (T + (B) + 1 + kAhead), ((B) + 1 + kAhead) & (NB - 1)); \
-  if (active) dq_tile<false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, lane >> 4, 64);
+  if (active) dq_tile<NB == 4, false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
     MOGA_DQ_TILE(0)
     MOGA_DQ_TILE(1)
@@ -239,12 +241,12 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
     pipe_issue<NW, GATHER>(dma, 64 * (T + 1 + kAhead), (T + 1 + kAhead) & (NB - 1));
-    if (active) dq_tile<false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, 64);
+    if (active) dq_tile<NB == 4, false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   }
   if (n & 63) {   // last, partial tile: masked keys contribute zero
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
-    if (active) dq_tile<true, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, n - 64 * T);
+    if (active) dq_tile<NB == 4, true, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, n - 64 * T);
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
@@ -357,7 +359,7 @@ __device__ __forceinline__ void ab_take_p(const AbLane& ln, const StepScores& dp
 // Progress does not depend on the bound: A publishes the stamp of tile t before it reaches the
 // block barrier of tile t + 1 and never waits for B anywhere else, and the single P buffer of a
 // pair is only rewritten after that barrier, which B reaches only after it has consumed P.
-template <bool MASK, int SOFF, int SROW>
+template <bool PRIO, bool MASK, int SOFF, int SROW>
 __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off, unsigned off_row,
                                         const bf16x8_t (&kvf)[2][4], floatx4_t (&acc)[8][2], float c, int g, int left,
                                         int* flag, int tile_no, int spin_limit, int* status) {
@@ -385,8 +387,12 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
     ab_take_p(ln, sc[1], 1, bop[1]);
   }
   ab_load_tr<SOFF + 8192>(ln, off, tr1);   // in flight while the first unit is accumulated
+  // The second products go first: they free the wave for the next barrier, which both partners wait at.  With the
+  // priorities of the dQ kernel 593 -> 582 ms at 580,320 x 40 heads (scores first instead: no gain).
+  wave_priority<PRIO, 1>();
   ab_accumulate(tr0, bop[0], acc);
   ab_accumulate(tr1, bop[1], acc);
+  wave_priority<PRIO, 0>();
 }
 
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
@@ -491,7 +497,7 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   __syncthreads();                                                               \
   issue_tile(T + (B) + 1 + kAhead);                                          \
   if (active)                                                                    \
-    ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
+    ab_tile<NB == 4, false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
                                                                               T + (B) + 1, spin_limit, status);
   for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
     MOGA_AB_TILE(0)
@@ -505,14 +511,14 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
     __syncthreads();
     issue_tile(T + 1 + kAhead);
     if (active)
-      ab_tile<false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+      ab_tile<NB == 4, false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
                            ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
   }
   if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
     if (active)
-      ab_tile<true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+      ab_tile<NB == 4, true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
                           ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
   }
 

@@ -123,7 +123,7 @@ __device__ __forceinline__ void step_scores(const PipeLane& ln, unsigned off, co
 // One pipeline step.  koff: byte offset (ring slot + half) of the NEXT step's keys; voff: byte
 // offset of the CURRENT step's values.  s_cur holds the current step's raw scores; s_next
 // receives the next step's raw scores (if HAS_NEXT) and mx their lane maxima.
-template <bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
+template <bool PRIO, bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
 __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff, const bf16x8_t (&qf)[2][4],
                                           PipeState& st, const StepScores& s_cur, StepScores& s_next, float (&mx)[2],
                                           float c) {
@@ -148,6 +148,9 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
 #pragma unroll
       for (int q = 0; q < 2; ++q) s_next[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
+  // The scores and exponentials are the long chain of a step: they go first when the SIMD's two waves compete, and the
+  // other wave's PV products fill the gaps (580,320 x 40 heads: 175.4 -> 169.4 ms; the other way round 5 % slower).
+  wave_priority<PRIO, 1>();
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
@@ -163,6 +166,7 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
       st.l[q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pk[q][ks]), ones, st.l[q], false);
     }
   }
+  wave_priority<PRIO, 0>();
   bf16x8_t pf[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) pf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{pk[q][0], pk[q][1], pk[q][2], pk[q][3]});
@@ -466,12 +470,12 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   int s = 0;
 #define MOGA_FWD_TILE(B)                                                                        \
   maybe_rescale(st, mx, c, tau);                                                            \
-  pipe_step<true, (B) * kPipeTileBytes + 8192, (B) * kPipeTileBytes>(ln, 0, 0, qf, st, s_a, s_b, mx, c); \
+  pipe_step<true, true, (B) * kPipeTileBytes + 8192, (B) * kPipeTileBytes>(ln, 0, 0, qf, st, s_a, s_b, mx, c); \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));                       \
   __syncthreads();                                                                              \
   pipe_issue<NW, GATHER>(dma, 32 * s + 64 * ((B) + 1 + kPipeAhead), ((B) + 1 + kPipeAhead) & 3); \
   maybe_rescale(st, mx, c, tau);                                                            \
-  pipe_step<true, (((B) + 1) & 3) * kPipeTileBytes, (B) * kPipeTileBytes + 8192>(ln, 0, 0, qf, st, s_b, s_a, mx, c);
+  pipe_step<true, true, (((B) + 1) & 3) * kPipeTileBytes, (B) * kPipeTileBytes + 8192>(ln, 0, 0, qf, st, s_b, s_a, mx, c);
   for (; s + 8 <= nfull - 1; s += 8) {   // steps s .. s+7 and their successors are full
     MOGA_FWD_TILE(0)
     MOGA_FWD_TILE(1)
@@ -484,12 +488,12 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     const unsigned slot = ((unsigned)(s >> 1) & 3u) * kPipeTileBytes;
     const unsigned slot_next = ((unsigned)((s >> 1) + 1) & 3u) * kPipeTileBytes;
     maybe_rescale(st, mx, c, tau);
-    pipe_step<true>(ln, slot + 8192, slot, qf, st, s_a, s_b, mx, c);
+    pipe_step<true, true>(ln, slot + 8192, slot, qf, st, s_a, s_b, mx, c);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
     __syncthreads();
     pipe_issue<NW, GATHER>(dma, 32 * (s + 2) + 64 * kPipeAhead, ((s >> 1) + 1 + kPipeAhead) & 3);
     maybe_rescale(st, mx, c, tau);
-    pipe_step<true>(ln, slot_next, slot + 8192, qf, st, s_b, s_a, mx, c);
+    pipe_step<true, true>(ln, slot_next, slot + 8192, qf, st, s_b, s_a, mx, c);
     s += 2;
   }
 
@@ -506,14 +510,14 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     const unsigned voff = buf * kPipeTileBytes + half * 8192;
     const unsigned koff = (half ? ((buf + 1) & 3) : buf) * kPipeTileBytes + (half ? 0 : 8192);
     if (has_next) {
-      pipe_step<true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<true, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
       if (s + 1 >= nfull) {
         mask_step(s_b, 32 * (s + 1), lane >> 4, n);
         step_max(s_b, mx);
       }
       copy_scores(s_a, s_b);
     } else {
-      pipe_step<false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<true, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
     }
   }
 

@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   __syncthreads();                                                                        \
   small_issue_tile(dma, 32 * (s + (B) + 1 + kAhead), ((B) + 1 + kAhead) & 3);             \
   maybe_rescale(st, mx, c, tau);                                                      \
-  pipe_step<true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c);
+  pipe_step<false, true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c);
   for (; s + 4 <= nfull - 1; s += 4) {   // steps s .. s+3 and their successors are full
     MOGA_SMALL_STEP(0, s_a, s_b)
     MOGA_SMALL_STEP(1, s_b, s_a)
@@ -139,14 +139,14 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     const unsigned voff = (unsigned)(s & 3) * kSmallTileBytes;
     const unsigned koff = (unsigned)((s + 1) & 3) * kSmallTileBytes;
     if (has_next) {
-      pipe_step<true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<false, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
       if (s + 1 >= nfull) {
         mask_step(s_b, 32 * (s + 1), lane >> 4, n);
         step_max(s_b, mx);
       }
       copy_scores(s_a, s_b);
     } else {
-      pipe_step<false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<false, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
     }
   }
 
