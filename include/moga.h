@@ -65,6 +65,12 @@ int moga_version(void);
 
 /* Bytes of device workspace the given call needs for these sizes (0 if none). Host-only. */
 size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model, int dtype);
+/*
+ * Bytes with which the call runs fastest (>= moga_workspace_bytes; Nk = number of key rows, N for MoGA's own calls).  The
+ * bf16 attention calls with a few rounds of long blocks use room past what they need to split the last round
+ * (34 MB).  moga_group_attn_fwd, which needs none, uses it too.  Host-only.
+ */
+size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, int H, int D, int M, int d_model, int dtype);
 
 /*
  * Router, Eqs. 2-4, plus the gate that Eq. 5 multiplies by.

@@ -28,6 +28,7 @@ _SIGNATURES = {
     "moga_status_string": (_c.c_char_p, [_i32]),
     "moga_version": (_i32, []),
     "moga_workspace_bytes": (_sz, [_i32, _i64, _i32, _i32, _i32, _i32, _i32]),
+    "moga_workspace_preferred_bytes": (_sz, [_i32, _i64, _i64, _i32, _i32, _i32, _i32, _i32]),
     "moga_route": (_i32, [_vp, _i32, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_permute": (_i32, [_vp, _i64, _i32, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp,
                             _vp, _vp, _vp, _vp, _sz, _vp]),

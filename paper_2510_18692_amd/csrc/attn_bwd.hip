@@ -126,6 +126,11 @@ extern "C" size_t moga_attn_bwd_status_offset(int64_t Nq, int H) {
   return bwd_rows_bytes(Nq, H);
 }
 
+bool moga::bwd_splits(int64_t Nq, int64_t Nk, int H, int M) {
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, kSmallGroupRows) &&
+         (split_pays(max_tiles(Nq, M, 256) * H) || split_pays(max_tiles(Nk, M, 128) * H));
+}
+
 extern "C" size_t moga_attn_bwd_ws_bytes(int64_t N, int H, int D, int dtype) {
   (void)D; (void)dtype;
   if (N <= 0 || H < 1) return 0;
@@ -142,12 +147,13 @@ extern "C" void moga_debug_set_spin_limit(int polls) { g_spin_limit.store(polls 
 static bool bf16_rows_ok(int64_t Nq, int64_t Nk) { return Nq < ((int64_t)1 << 24) && Nk < ((int64_t)1 << 24); }
 
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
-// space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).
+// space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: NULL or kSplitBytes
+// for the pieces of a last round (dK/dV and dQ use it one after the other; only without ts_q / ts_k).
 static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
                            const void* oh, const float* lse, int dtype, int64_t Nq, int64_t Nk, int H, int D,
                            const int32_t* cu_q, const int32_t* cu_k, int32_t* ts_q, int32_t* ts_k,
                            int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
-                           float* delta, hipStream_t st) {
+                           float* delta, void* split, hipStream_t st) {
   const int64_t rows = Nq * (int64_t)H;
   if ((rows * 32 + 255) / 256 >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;   // grid of the delta kernel
   if (dtype == MOGA_BF16) {
@@ -169,12 +175,19 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         attn_bwd_dkdv_ab_kernel<false, 2, 2><<<(unsigned)blocks, 256, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (int)tiles, (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
-      else
+            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
+      else if (split && split_pays(tiles * H)) {
+        attn_bwd_dkdv_ab_kernel<false, 4, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
+            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
+            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
+            g_spin_limit.load(), status, nullptr, split_ws(split).part);
+        split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 2, 1.f, softmax_scale,
+                                                            (unsigned short*)d_vh, (unsigned short*)d_kh);
+      } else
         attn_bwd_dkdv_ab_kernel<false><<<(unsigned)blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (int)tiles, (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
+            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
     }
     {
       const int bm = small ? 128 : 256;
@@ -186,12 +199,18 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         attn_bwd_dq_pipe_kernel<4, false, 2><<<(unsigned)blocks, 256, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (int)tiles, (unsigned short*)d_qh);
-      else
+            (unsigned short*)d_qh);
+      else if (split && split_pays(tiles * H)) {
+        attn_bwd_dq_pipe_kernel<8, false, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
+            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
+            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, nullptr, split_ws(split).part);
+        split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
+                                                            (unsigned short*)d_qh, nullptr);
+      } else
         attn_bwd_dq_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (int)tiles, (unsigned short*)d_qh);
+            (unsigned short*)d_qh);
     }
   } else {
     {
@@ -251,7 +270,8 @@ extern "C" int moga_group_attn_bwd(const void* d_oh, const void* qh, const void*
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr,
-                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, (hipStream_t)stream);
+                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, split_region(ws, need, ws_bytes),
+                         (hipStream_t)stream);
 }
 
 extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
@@ -289,7 +309,8 @@ extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void
   int32_t* ts_q = presum ? (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16) : nullptr;
   int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
-                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, st);
+                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws,
+                         presum ? nullptr : split_region(ws, need, ws_bytes), st);
 }
 
 extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k, const void* v,
@@ -323,7 +344,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
     attn_bwd_dkdv_ab_kernel<true><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (int)tiles, (unsigned short*)d_k,
+        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
         (unsigned short*)d_v, g_spin_limit.load(), status, perm);
   }
   {
@@ -332,8 +353,17 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
     attn_bwd_dq_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (int)tiles, (unsigned short*)d_q,
+        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q,
         perm);
   }
   return launch_status();
+}
+
+extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, int H, int D, int M, int d_model, int dtype) {
+  const size_t need = moga_workspace_bytes(op, N, H, D, M, d_model, dtype);
+  if (dtype != MOGA_BF16 || D != 128 || N <= 0 || Nk <= 0 || H < 1 || M < 1) return need;
+  const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
+  const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD;
+  const bool splits = (fwd && fwd_splits(N, H, M)) || (bwd && bwd_splits(N, Nk, H, M));
+  return splits ? round_up(need, 256) + 256 + kSplitBytes : need;
 }

@@ -135,40 +135,50 @@ __device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], flo
   }
 }
 
+__device__ __forceinline__ void store_gradient_piece(const floatx4_t (&acc)[8][2], float* rows) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) store_partial(rows, dt, c, acc[dt][c]);
+}
+__device__ __forceinline__ void store_zero_piece(float* rows) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) store_partial(rows, dt, c, floatx4_t{0.f, 0.f, 0.f, 0.f});
+}
+
+// SPLIT (both backward kernels): the last round is cut into pieces (find_work), partial sums in `part`.
 // GATHER (both backward kernels): d_oh, qh, kh, vh and the gradient outputs are token-major
 // [N, H, 128] and row j of a group is token perm[j]; neg_lse_over_scale / neg_delta stay in
 // sorted order [H, N] and carry the gate (see attn_bwd_fused_prepass_kernel), so d_oh is the
 // raw upstream gradient of the gated output.
 // NB: ring slots of 64 keys (4: two tiles ahead, one block per CU; 2: one tile ahead, 64 KB of LDS, so
 // that two 4-wave blocks share a CU -- the variant for small groups).
-template <int NW, bool GATHER = false, int NB = 4>
+template <int NW, bool GATHER = false, int NB = 4, bool SPLIT = false>
 __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    int tiles_per_head, unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr) {
+    unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
+    float* __restrict__ part = nullptr) {
   constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[NB][64 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[NB][64 * kHeadDim];
 
-  const int64_t total = (int64_t)H * tiles_per_head;
-  const int64_t work = xcd_work_index(blockIdx.x, total);
-  if (work >= total) return;
-  const int head = (int)(work / tiles_per_head);
-  const int tile = (int)(work - (int64_t)head * tiles_per_head);
-  TileInfo ti;
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_q, M, BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, BM, tile, ti)) {
-    return;
-  }
+  WorkTile sp;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  const TileInfo& ti = sp.ti;
+  const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
-  const int gs = cu_k[ti.group];                 // first key row of the group
-  const int n = cu_k[ti.group + 1] - gs;         // number of keys
+  int gs = cu_k[ti.group];                       // first key row of the group
+  int n = cu_k[ti.group + 1] - gs;               // number of keys
+  const bool piece = SPLIT && sp.splits > 1;
+  if (piece) split_range(sp, gs, n);
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int q0w = q0 + wave * 32;   // first query row of this wave
@@ -176,8 +186,10 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   const int64_t head_off_k = (int64_t)head * Nk;
   const float c = scale * 1.4426950408889634f;
 
+  float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 32 * wave) * kHeadDim : nullptr;
   if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
-    store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm);
+    if (piece) store_zero_piece(piece_rows);
+    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm);
     return;
   }
 
@@ -250,7 +262,8 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, perm);
+  if (piece) store_gradient_piece(dq, piece_rows);
+  else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, perm);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -397,15 +410,16 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
 
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
 // NB: ring slots of 64 queries (4 or 2, as in the dQ kernel).
-template <bool GATHER = false, int NPAIR = 4, int NB = 4>
+template <bool GATHER = false, int NPAIR = 4, int NB = 4, bool SPLIT = false>
 __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    int tiles_per_head, unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
-    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr) {
+    unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
+    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
+    float* __restrict__ part = nullptr) {
   constexpr int NW = 2 * NPAIR;
   constexpr int BK = 32 * NPAIR;                   // pairs of waves x 32 keys
   constexpr int kAhead = NB - 2;
@@ -417,21 +431,16 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   __shared__ __attribute__((aligned(256))) float Ds[NB][64];      // -delta
   __shared__ int s_flag[NPAIR];   // per pair: number of tiles whose P has been written
 
-  const int64_t total = (int64_t)H * tiles_per_head;
-  const int64_t work = xcd_work_index(blockIdx.x, total);
-  if (work >= total) return;
-  const int head = (int)(work / tiles_per_head);
-  const int tile = (int)(work - (int64_t)head * tiles_per_head);
   if (threadIdx.x < NPAIR) s_flag[threadIdx.x] = 0;   // ordered before its first use by the barriers below
-  TileInfo ti;   // tiles run over the key rows of the groups
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_k, M, BK, tile, ti)) return;
-  } else if (!find_tile(cu_k, M, BK, tile, ti)) {
-    return;
-  }
+  WorkTile sp;
+  if (!find_work<SPLIT>(cu_k, tile_start, M, H, BK, blockIdx.x, sp)) return;
+  const TileInfo& ti = sp.ti;
+  const int head = sp.head;
   const int ge = ti.row_end, k0 = ti.tile_row;
-  const int gs = cu_q[ti.group];
-  const int n = cu_q[ti.group + 1] - gs;
+  int gs = cu_q[ti.group];
+  int n = cu_q[ti.group + 1] - gs;
+  const bool piece = SPLIT && sp.splits > 1;
+  if (piece) split_range(sp, gs, n);
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int role = wave / NPAIR, pair = wave % NPAIR;
@@ -442,8 +451,10 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   const int k0w = k0 + pair * 32;   // first key row of this pair
   unsigned short* outp = role == 0 ? d_vh : d_kh;
 
+  float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 32 * pair) * kHeadDim : nullptr;   // dV, then dK
   if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
-    store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm);
+    if (piece) store_zero_piece(piece_rows);
+    else store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm);
     return;
   }
 
@@ -523,7 +534,8 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, perm);
+  if (piece) store_gradient_piece(acc, piece_rows);
+  else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, perm);
 }
 
 }  // namespace moga

@@ -43,7 +43,7 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ cu_seqlens
   return false;
 }
 
-// The same lookup for calls with more than MOGA_MAX_GROUPS groups: `tile_start[g]` (M + 1 entries, written
+// The lookup of find_tile for calls with more than MOGA_MAX_GROUPS groups: `tile_start[g]` (M + 1 entries, written
 // by tile_start_kernel) is the flat index of group g's first tile.  The 64 lanes probe 64 entries at
 // once, so 4,096 groups take two dependent loads (a binary search: twelve).
 __device__ __forceinline__ bool find_tile_presummed(const int32_t* __restrict__ tile_start,
@@ -64,6 +64,160 @@ __device__ __forceinline__ bool find_tile_presummed(const int32_t* __restrict__ 
   out.row_end = cu_seqlens[lo + 1];
   out.tile_row = out.row_begin + (tile - tile_start[lo]) * rows_per_tile;
   return true;
+}
+
+// Splitting the last round.  Blocks of one size run in rounds of kCus; the tiles of the
+// last, partly filled round are cut along the other side into equal runs of 64-row tiles, so that the round is full and
+// shorter.  Such a piece writes fp32 partial results to slot `slot` of the workspace, and split_*_kernel puts the pieces
+// of a tile together.  Without: 6.2 rounds of work took the time of 7 (forward, 32,760 rows x 12 heads, 8 groups).
+constexpr int kCus = 256;
+constexpr int kMaxSplits = 8;
+struct WorkTile {
+  TileInfo ti;
+  int head;
+  int split, splits;   // splits == 1: a whole tile
+  int slot;
+};
+struct SplitShape { int full, left, splits; };   // whole tiles in full rounds, tiles of the last round, pieces of each
+
+__device__ __forceinline__ SplitShape split_shape(int tiles) {
+  SplitShape s = {tiles / kCus * kCus, tiles % kCus, 1};
+  if (s.left > 0) s.splits = min(kMaxSplits, kCus / s.left);
+  return s;
+}
+
+// Tiles of one head.
+__device__ __forceinline__ int count_tiles(const int32_t* __restrict__ cu_seqlens, int M, int rows_per_tile) {
+  const int lane = threadIdx.x & 63;
+  int sum = 0;
+  for (int g0 = 0; g0 < M; g0 += 64) {
+    const int n = cu_seqlens[min(g0 + lane + 1, M)] - cu_seqlens[min(g0 + lane, M)];
+    sum += __builtin_amdgcn_readlane(wave_scan_add((n + rows_per_tile - 1) / rows_per_tile), 63);
+  }
+  return sum;
+}
+
+// Position w of the work list -> (head, tile of the head).  The hardware deals blocks round-robin to the 8 XCDs, so
+// w % 8 is the XCD: each gets an eighth of the heads whole (a head's K/V tiles are streamed through a single L2), and the
+// tiles of the remaining heads are dealt in runs of 16, the last ones singly, so that the XCDs' shares are equal whatever
+// the group sizes are.  (As one list with bounds per head, cut into eighths, 62,400 rows x 4 heads in 8 Zipf(1.1) groups
+// took 8.1 ms instead of 5.3; dealt singly throughout, groups of 1,560 rows lose 6 %: their rows go to every L2.)
+__device__ __forceinline__ void decode_work(int w, int per_head, int H, int& head, int& tile) {
+  const int whole = (H & ~7) * per_head;
+  const bool rest = w >= whole;
+  int i = rest ? w - whole : w >> 3;
+  if (rest && i < ((H & 7) * per_head & ~127)) i = (i & ~127) + (i & 7) * 16 + ((i >> 3) & 15);
+  const int h = i / per_head;
+  head = rest ? (H & ~7) + h : (w & 7) * (H >> 3) + h;
+  tile = i - h * per_head;
+}
+
+// What block `block` works on; false: nothing.  tile_start: NULL, or the pre-summed tiles (more than MOGA_MAX_GROUPS groups).
+template <bool SPLIT>
+__device__ __forceinline__ bool find_work(const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ tile_start, int M, int H,
+                                          int rows_per_tile, int block, WorkTile& out) {
+  // up to 64 groups (a lane each) the bounds are read once, for the count and for the lookup
+  const int lane = threadIdx.x & 63;
+  const bool one_scan = !tile_start && M <= 64;
+  int beg = 0, end = 0, incl = 0, per_head;
+  if (one_scan) {
+    beg = cu_seqlens[min(lane, M)];
+    end = cu_seqlens[min(lane + 1, M)];
+    incl = wave_scan_add((end - beg + rows_per_tile - 1) / rows_per_tile);
+    per_head = __builtin_amdgcn_readlane(incl, 63);
+  } else {
+    per_head = tile_start ? tile_start[M] : count_tiles(cu_seqlens, M, rows_per_tile);
+  }
+  const int total = per_head * H;
+  int w = block, tile;
+  out.split = out.slot = 0;
+  out.splits = 1;
+  if constexpr (SPLIT) {
+    const SplitShape s = split_shape(total);
+    if (block >= s.full) {
+      const int p = block - s.full;
+      if (p >= s.left * s.splits) return false;
+      w = s.full + p % s.left;
+      out.split = p / s.left;
+      out.splits = s.splits;
+      out.slot = (p % s.left) * s.splits + out.split;
+    }
+  }
+  if (w >= total) return false;
+  decode_work(w, per_head, H, out.head, tile);
+  if (!one_scan)
+    return tile_start ? find_tile_presummed(tile_start, cu_seqlens, M, rows_per_tile, tile, out.ti)
+                      : find_tile(cu_seqlens, M, rows_per_tile, tile, out.ti);
+  const int g = __builtin_ctzll(__ballot(incl > tile));
+  out.ti.group = g;
+  out.ti.row_begin = __builtin_amdgcn_readlane(beg, g);
+  out.ti.row_end = __builtin_amdgcn_readlane(end, g);
+  const int first = __builtin_amdgcn_readlane(incl, g) - (out.ti.row_end - out.ti.row_begin + rows_per_tile - 1) / rows_per_tile;
+  out.ti.tile_row = out.ti.row_begin + (tile - first) * rows_per_tile;
+  return true;
+}
+
+// Rows (first, count) of the other side that a piece sweeps.
+__device__ __forceinline__ void split_range(const WorkTile& s, int& first, int& n) {
+  const int tiles = (n + 63) >> 6, t0 = tiles * s.split / s.splits, t1 = tiles * (s.split + 1) / s.splits;
+  const int end = min(n, 64 * t1);
+  first += 64 * t0;
+  n = end - 64 * t0;
+}
+
+// A wave's 32 result columns as fp32 rows of a slot; `base` is the wave's first row.
+__device__ __forceinline__ void store_partial(float* base, int dt, int col_half, const floatx4_t& v) {
+  const int lane = threadIdx.x & 63;
+  *(floatx4_t*)(base + (16 * col_half + (lane & 15)) * kHeadDim + 16 * dt + 4 * (lane >> 4)) = v;
+}
+
+constexpr size_t kSplitRows = 256;   // result rows of a piece, in every kernel
+constexpr size_t kSplitBytes = kCus * kSplitRows * (kHeadDim + 2) * sizeof(float);   // results, then (max, sum) of the forward
+struct SplitWs {
+  float *part, *stat;
+};
+// The part of a workspace past its first `used` bytes, if the pieces fit there; else NULL.
+inline void* split_region(void* ws, size_t used, size_t ws_bytes) {
+  if (!ws) return nullptr;
+  const size_t off = round_up((size_t)(uintptr_t)ws + used, 256) - (size_t)(uintptr_t)ws;
+  return ws_bytes >= off + kSplitBytes ? (char*)ws + off : nullptr;
+}
+bool fwd_splits(int64_t Nq, int H, int M);
+bool bwd_splits(int64_t Nq, int64_t Nk, int H, int M);
+inline SplitWs split_ws(void* ws) {
+  return {(float*)ws, (float*)ws + kCus * kSplitRows * kHeadDim};
+}
+// Worth it for a few rounds of the kernels with long blocks; beyond 32 rounds the last one is under 3 %.
+inline bool split_pays(int64_t tiles) { return tiles <= 32 * kCus; }
+
+constexpr int kSplitGridY = kSplitRows / 8;
+// Sum of the pieces of every tile of the last round, times f, as bf16 rows of `out`.  A tile has `arrays` results of
+// kSplitRows / arrays rows each (dV and dK: two, 128 rows).  Grid (kCus / 2, kSplitGridY): eight rows per block, one trip
+// to memory (with 64 rows per block, one after the other, 45 us instead of 9).
+static __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ part, const int32_t* __restrict__ cu, int M,
+                                                               int H, int64_t N, int arrays, float f0, float f1,
+                                                               unsigned short* __restrict__ out0,
+                                                               unsigned short* __restrict__ out1) {
+  const int rows = kSplitRows / arrays;
+  const int per_head = count_tiles(cu, M, rows);
+  const SplitShape s = split_shape(per_head * H);
+  if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
+  int head, tile;
+  decode_work(s.full + blockIdx.x, per_head, H, head, tile);
+  TileInfo ti;
+  if (!find_tile(cu, M, rows, tile, ti)) return;
+  const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
+  const int a = r / rows, row = ti.tile_row + r % rows;
+  if (row >= ti.row_end) return;
+  const float* p = part + ((size_t)blockIdx.x * s.splits * kSplitRows + r) * kHeadDim + col;
+  floatx4_t v[kMaxSplits];   // all in flight together
+#pragma unroll
+  for (int k = 0; k < kMaxSplits; ++k) v[k] = k < s.splits ? *(const floatx4_t*)(p + (size_t)k * kSplitRows * kHeadDim) : floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 1; k < kMaxSplits; ++k) v[0] += v[k];
+  unsigned short* o = (a ? out1 : out0) + ((int64_t)head * N + row) * kHeadDim + col;
+  const float f = a ? f1 : f0;
+  *(uintx2_t*)o = uintx2_t{pack_bf16x2(v[0][0] * f, v[0][1] * f), pack_bf16x2(v[0][2] * f, v[0][3] * f)};
 }
 
 // One block: exclusive scan of ceil(n_g / rows_per_tile) over the groups, M + 1 results.
@@ -99,14 +253,6 @@ static __global__ __launch_bounds__(1024) void tile_start_kernel(const int32_t* 
 // Upper bound on the number of tiles for N rows in M groups (host side).
 inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
   return (N + rows_per_tile - 1) / rows_per_tile + M;
-}
-
-// Work item of a block: blocks are dealt round-robin to the 8 XCDs by the hardware, so block
-// b runs on XCD b % 8.  Give each XCD one contiguous eighth of the (head-major) work list, so
-// that the K/V tiles of a head are streamed through a single L2.
-__device__ __forceinline__ int64_t xcd_work_index(int64_t block, int64_t total) {
-  const int64_t per = (total + 7) / 8;
-  return (block & 7) * per + (block >> 3);
 }
 
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or

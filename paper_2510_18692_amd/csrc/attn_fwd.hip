@@ -24,11 +24,12 @@ constexpr int64_t kSmallGroupRows = 2560;   // mean rows per group below which t
 
 using namespace moga;
 
-// Shared launcher.  tile_start == NULL: tile lookup inside the kernels (M <= MOGA_MAX_GROUPS).
+// Shared launcher.  tile_start == NULL: tile lookup inside the kernels (M <= MOGA_MAX_GROUPS).  split: NULL or
+// kSplitBytes for the pieces of the last round (only with tile_start == NULL).
 static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype, int64_t Nq,
                            int64_t Nk, int H, int D, const int32_t* cu_q, const int32_t* cu_k,
                            int32_t* tile_start, int M, float softmax_scale, void* oh, float* lse,
-                           hipStream_t st) {
+                           void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
   const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, kSmallGroupRows);
@@ -40,11 +41,17 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   if (small) {
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
-        tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, (unsigned short*)oh, lse);
+        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse);
+  } else if (dtype == MOGA_BF16 && split && split_pays(tiles * H)) {
+    const SplitWs sw = split_ws(split);
+    attn_fwd_bf16_pipe_kernel<8, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
+        (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,
+        softmax_scale, (unsigned short*)oh, lse, nullptr, nullptr, sw);
+    split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, M, H, Nq, softmax_scale, (unsigned short*)oh, lse);
   } else if (dtype == MOGA_BF16) {
     attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
-        tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, (unsigned short*)oh, lse);
+        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse);
   } else if (D == 64) {
     attn_fwd_f32_mfma_kernel<64><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
         (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk,
@@ -74,7 +81,6 @@ extern "C" int moga_group_attn_fwd(const void* qh, const void* kh, const void* v
                                    int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
                                    float softmax_scale, void* oh, float* lse, void* ws,
                                    size_t ws_bytes, void* stream) {
-  (void)ws; (void)ws_bytes;
   const int bad = check_attn_args(N, N, H, D, M, softmax_scale, dtype);
   if (bad) return bad;
   if (M > MOGA_MAX_GROUPS) return MOGA_ERR_UNSUPPORTED;
@@ -82,7 +88,7 @@ extern "C" int moga_group_attn_fwd(const void* qh, const void* kh, const void* v
   if (!qh || !kh || !vh || !cu_seqlens || !oh || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
   return launch_attn_fwd(qh, kh, vh, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, M,
-                         softmax_scale, oh, lse, (hipStream_t)stream);
+                         softmax_scale, oh, lse, split_region(ws, 0, ws_bytes), (hipStream_t)stream);
 }
 
 extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, int dtype, int64_t N,
@@ -100,8 +106,13 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
   attn_fwd_bf16_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(
       (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, cu_seqlens, cu_seqlens,
-      nullptr, M, N, N, H, softmax_scale, (int)tiles, (unsigned short*)o, lse, perm, gate);
+      nullptr, M, N, N, H, softmax_scale, (unsigned short*)o, lse, perm, gate);
   return launch_status();
+}
+
+// True where the forward can split its last round.
+bool moga::fwd_splits(int64_t Nq, int H, int M) {
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, kSmallGroupRows) && split_pays(max_tiles(Nq, M, 256) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }
@@ -120,6 +131,7 @@ extern "C" int moga_varlen_attn_fwd(const void* qh, const void* kh, const void* 
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
   if (!ws || ws_bytes < moga_varlen_attn_fwd_ws_bytes(G)) return MOGA_ERR_WORKSPACE;
   int32_t* ts = G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)ws;   // few groups: every block looks its tile up itself
+  void* split = ts ? nullptr : split_region(ws, moga_varlen_attn_fwd_ws_bytes(G), ws_bytes);
   return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts, G,
-                         softmax_scale, oh, lse, (hipStream_t)stream);
+                         softmax_scale, oh, lse, split, (hipStream_t)stream);
 }

@@ -210,6 +210,30 @@ __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int g
   }
 }
 
+// A piece's O, maximum and sum of this wave's rows, not yet divided.
+__device__ __forceinline__ void store_piece(const PipeState& st, const SplitWs& sw, int slot, int wave) {
+  const int lane = threadIdx.x & 63;
+  const size_t row0 = slot * kSplitRows + 32 * wave;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float lt = st.l[q] + __shfl_xor(st.l[q], 16, kWave);
+    lt += __shfl_xor(lt, 32, kWave);
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) store_partial(sw.part + row0 * kHeadDim, dt, q, quarter(st.o[dt >> 2][q], dt & 3));
+    if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{st.m[q], lt};
+  }
+}
+__device__ __forceinline__ void store_empty_piece(const SplitWs& sw, int slot, int wave) {
+  const int lane = threadIdx.x & 63;
+  const size_t row0 = slot * kSplitRows + 32 * wave;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt) store_partial(sw.part + row0 * kHeadDim, dt, q, floatx4_t{0.f, 0.f, 0.f, 0.f});
+    if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{-INFINITY, 0.f};
+  }
+}
+
 // Zero output rows of a wave whose group has no keys (lse = -inf if given).
 template <bool GATHER>
 __device__ __forceinline__ void store_zero_rows(int row0, int ge, int head, int64_t head_off, int H, unsigned short* __restrict__ out,
@@ -353,34 +377,30 @@ __device__ __forceinline__ void pipe_issue(PipeDma& d, int kv0, int buf) {
 // GATHER: qh, kh, vh and oh are token-major [N, H, 128]; row j of a group is token perm[j] (the
 // permutation of Alg. 1 is applied while loading, nothing is materialised) and the output row is
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
-template <int NW, bool GATHER = false>
+// SPLIT: the last round is cut into pieces (find_work).
+template <int NW, bool GATHER = false, bool SPLIT = false>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
-    int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, unsigned short* __restrict__ oh,
+    int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
     float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
-    const float* __restrict__ gate = nullptr) {
+    const float* __restrict__ gate = nullptr, SplitWs sw = {}) {
   constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);   // direct-to-LDS instructions per thread per tile
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[kPipeNBuf][64 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[kPipeNBuf][64 * kHeadDim];
 
-  const int64_t total = (int64_t)H * tiles_per_head;
-  const int64_t work = xcd_work_index(blockIdx.x, total);
-  if (work >= total) return;
-  const int head = (int)(work / tiles_per_head);
-  const int tile = (int)(work - (int64_t)head * tiles_per_head);
-  TileInfo ti;
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_q, M, BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, BM, tile, ti)) {
-    return;
-  }
+  WorkTile sp;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  const TileInfo& ti = sp.ti;
+  const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
-  const int gs = cu_k[ti.group];                 // first key row of the group
-  const int n = cu_k[ti.group + 1] - gs;         // number of keys
+  int gs = cu_k[ti.group];                       // first key row of the group
+  int n = cu_k[ti.group + 1] - gs;               // number of keys
+  const bool piece = SPLIT && sp.splits > 1;
+  if (piece) split_range(sp, gs, n);
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int q0w = q0 + wave * 32;   // first query row of this wave
@@ -390,7 +410,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   const float tau = 8.f / c;
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-    store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm);
+    if (piece) store_empty_piece(sw, sp.slot, wave);
+    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm);
     return;
   }
 
@@ -522,7 +543,46 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate);
+  if (piece) store_piece(st, sw, sp.slot, wave);
+  else store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate);
+}
+
+// Pieces of every query tile of the last round: O = sum O_k 2^((m_k - m) c) / l, l = sum l_k 2^((m_k - m) c).
+static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const int32_t* __restrict__ cu, int M, int H, int64_t N,
+                                                               float scale, unsigned short* __restrict__ oh,
+                                                               float* __restrict__ lse) {
+  const int per_head = count_tiles(cu, M, kSplitRows);
+  const SplitShape s = split_shape(per_head * H);
+  if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
+  int head, tile;
+  decode_work(s.full + blockIdx.x, per_head, H, head, tile);
+  TileInfo ti;
+  if (!find_tile(cu, M, kSplitRows, tile, ti)) return;
+  const float c = scale * 1.4426950408889634f;
+  const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
+  if (ti.tile_row + r >= ti.row_end) return;
+  const size_t first = (size_t)blockIdx.x * s.splits * kSplitRows + r;   // piece k is k * kSplitRows rows further
+  floatx4_t v[kMaxSplits];
+  floatx2_t ml[kMaxSplits];
+#pragma unroll
+  for (int k = 0; k < kMaxSplits; ++k) {
+    const size_t row = first + (k < s.splits ? k : 0) * kSplitRows;
+    v[k] = *(const floatx4_t*)(sw.part + row * kHeadDim + col);
+    ml[k] = *(const floatx2_t*)(sw.stat + row * 2);
+  }
+  float m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int k = 0; k < kMaxSplits; ++k) m = fmaxf(m, ml[k][0]);
+  floatx4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < kMaxSplits; ++k) {
+    const float w = k < s.splits && m > -INFINITY ? fast_exp2((ml[k][0] - m) * c) : 0.f;   // m = -inf: no keys at all, zero row
+    l += ml[k][1] * w;
+    o += v[k] * w;
+  }
+  const int64_t orow = (int64_t)head * N + ti.tile_row + r;
+  *(uintx2_t*)(oh + orow * kHeadDim + col) = pack4(o, l > 0.f ? 1.f / l : 0.f);
+  if (col == 0) lse[orow] = l > 0.f ? m * scale + logf(l) : -INFINITY;
 }
 
 }  // namespace moga

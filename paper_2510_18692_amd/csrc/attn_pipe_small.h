@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
-    int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, unsigned short* __restrict__ oh,
+    int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
     float* __restrict__ lse) {
   constexpr int BM = 128;
   constexpr int kDmaPerTile = 4;   // direct-to-LDS instructions per thread per tile
@@ -40,17 +40,10 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[4][32 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[4][32 * kHeadDim];
 
-  const int64_t total = (int64_t)H * tiles_per_head;
-  const int64_t work = xcd_work_index(blockIdx.x, total);
-  if (work >= total) return;
-  const int head = (int)(work / tiles_per_head);
-  const int tile = (int)(work - (int64_t)head * tiles_per_head);
-  TileInfo ti;
-  if (tile_start) {
-    if (!find_tile_presummed(tile_start, cu_q, M, BM, tile, ti)) return;
-  } else if (!find_tile(cu_q, M, BM, tile, ti)) {
-    return;
-  }
+  WorkTile sp;
+  if (!find_work<false>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  const TileInfo& ti = sp.ti;
+  const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
   const int gs = cu_k[ti.group];                 // first key row of the group
   const int n = cu_k[ti.group + 1] - gs;         // number of keys

@@ -65,6 +65,22 @@ Tensor make(at::IntArrayRef size, const Tensor& like, at::ScalarType type) { ret
 Tensor make(at::IntArrayRef size, const Tensor& like) { return at::empty(size, like.options()); }
 Tensor workspace(size_t bytes, const Tensor& like) { return make({std::max<int64_t>((int64_t)bytes, 16)}, like, at::kByte); }
 
+size_t bytes_of(const OptTensor& ws) { return ws ? (size_t)ws->numel() : 0; }
+
+// Workspace of an attention call: what it runs fastest with if the device has it, else what it needs.
+OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like) {
+  const size_t need = moga_workspace_bytes(op, N, (int)H, (int)D, (int)M, 0, dt(like));
+  const size_t preferred = moga_workspace_preferred_bytes(op, N, Nk, (int)H, (int)D, (int)M, 0, dt(like));
+  if (preferred > need) {
+    try {
+      return workspace(preferred, like);
+    } catch (const c10::OutOfMemoryError&) {
+    }
+  }
+  if (need == 0) return std::nullopt;
+  return workspace(need, like);
+}
+
 std::tuple<Tensor, Tensor, OptTensor, OptTensor> route(const Tensor& x, const Tensor& w, const OptTensor& bias,
                                                        bool want_probs, bool want_logits, const OptStream& stream) {
   require(x, w, bias);
@@ -120,8 +136,9 @@ std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, co
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
   Tensor oh = out ? *out : make({H, N, D}, qh);
   Tensor lse = lse_out ? *lse_out : make({H, N}, qh, at::kFloat);
+  OptTensor ws = attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
   check("moga_group_attn_fwd", moga_group_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M,
-                                                   (float)scale, ptr(oh), as<float>(lse), nullptr, 0, stream_of(stream)));
+                                                   (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws), stream_of(stream)));
   return {oh, lse};
 }
 
@@ -152,10 +169,10 @@ std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tens
   need_dims(qh, 3);
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
   Tensor d_qh = make({H, N, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  Tensor ws = ws_in ? *ws_in : workspace(moga_workspace_bytes(MOGA_OP_ATTN_BWD, N, (int)H, (int)D, (int)M, 0, dt(qh)), qh);
+  OptTensor ws = ws_in ? ws_in : attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
   check("moga_group_attn_bwd", moga_group_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H,
                                                    (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
-                                                   ptr(ws), ws.numel(), stream_of(stream)));
+                                                   ptr(ws), bytes_of(ws), stream_of(stream)));
   return {d_qh, d_kh, d_vh};
 }
 
@@ -217,9 +234,9 @@ std::tuple<Tensor, Tensor> varlen_attn_fwd(const Tensor& qh, const Tensor& kh, c
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
   Tensor oh = make({H, Nq, D}, qh), lse = make({H, Nq}, qh, at::kFloat);
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_FWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh);
+  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_FWD, Nq, Nk, H, D, G, qh);
   check("moga_varlen_attn_fwd", moga_varlen_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), Nq, Nk, (int)H, (int)D, as<int32_t>(cu_q),
-                                                     as<int32_t>(cu_k), (int)G, (float)scale, ptr(oh), as<float>(lse), ptr(ws), ws.numel(),
+                                                     as<int32_t>(cu_k), (int)G, (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws),
                                                      stream_of(stream)));
   return {oh, lse};
 }
@@ -231,10 +248,10 @@ std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd(const Tensor& d_oh, const Ten
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
   Tensor d_qh = make({H, Nq, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_BWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh);
+  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, Nq, Nk, H, D, G, qh);
   check("moga_varlen_attn_bwd", moga_varlen_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), Nq, Nk, (int)H,
                                                      (int)D, as<int32_t>(cu_q), as<int32_t>(cu_k), (int)G, (float)scale, ptr(d_qh),
-                                                     ptr(d_kh), ptr(d_vh), ptr(ws), ws.numel(), stream_of(stream)));
+                                                     ptr(d_kh), ptr(d_vh), ptr(ws), bytes_of(ws), stream_of(stream)));
   return {d_qh, d_kh, d_vh};
 }
 

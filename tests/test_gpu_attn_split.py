@@ -1,0 +1,77 @@
+"""Attention calls that split their last round against the same calls without room for it: numbers of tiles around the
+edges of the rule (256 blocks a round, at most 8 pieces a tile), groups with fewer keys than pieces, and no keys at all.
+
+Both ways round P and dS to bf16 (2^-9 relative at most, relative to another maximum per piece in the forward) and the
+results once: 2-norms differ by less than 4 * 2^-9.  1e-5: where dP - delta cancels, fp32 rounding is left."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_18692_amd import binding as mg
+
+pytestmark = pytest.mark.gpu
+
+
+def p(t):
+    return t.data_ptr()
+
+
+def close(a, b, name):
+    a, b = a.double(), b.double()
+    assert torch.isfinite(a).all(), name
+    assert (a - b).norm() <= 4 * 2 ** -9 * b.norm() + 1e-5 * b.numel() ** 0.5, name
+
+
+@pytest.mark.parametrize("nq,nk,H", [
+    ([1], [1], 1), ([300, 5, 70], [300, 5, 700], 1),          # 4 tiles, 8 pieces each, most of them empty
+    ([200, 257, 0, 600], [500, 0, 64, 449], 3),               # sides without rows
+    ([256] * 32 + [1], [90] * 33, 1),                         # 33 tiles: 7 pieces
+    ([256] * 64, [130] * 64, 2), ([256] * 43, [130] * 43, 3),   # 128 tiles: two pieces; 129: none
+    ([100] * 257, None, 1), ([100] * 255, None, 1),           # a round and one tile; a tile less than a round
+    ([3000, 2500, 100], None, 12),                            # a few rounds
+])
+def test_split_against_whole_tiles(nq, nk, H):
+    nk = nk or nq
+    if len(nq) > 256:
+        nq, nk = nq[:255] + [sum(nq[255:])], nk[:255] + [sum(nk[255:])]
+    g = torch.Generator().manual_seed(len(nq) + H)
+    Nq, Nk, G = sum(nq), sum(nk), len(nq)
+    q, d = (torch.randn((H, Nq, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    k, v = (torch.randn((H, Nk, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    cq, ck = (torch.from_numpy(np.concatenate([[0], np.cumsum(n)]).astype(np.int32)).cuda() for n in (nq, nk))
+    s = 128 ** -0.5
+    lib, stream = mg.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    mg.set_small_group_rows(0)   # the kernels with long blocks, whatever the mean size
+    try:
+        out = {}
+        for op, name in ((mg.OP_VARLEN_ATTN_FWD, "fwd"), (mg.OP_VARLEN_ATTN_BWD, "bwd")):
+            need = mg.workspace_bytes(op, Nq, H, 128, G, 0, mg.MOGA_BF16)
+            pref = lib.moga_workspace_preferred_bytes(op, Nq, Nk, H, 128, G, 0, mg.MOGA_BF16)
+            assert pref > need
+            for size in (need, pref):
+                ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever nothing is written
+                if name == "fwd":
+                    oh, lse = torch.empty_like(q), torch.empty((H, Nq), device="cuda")
+                    st = lib.moga_varlen_attn_fwd(p(q), p(k), p(v), mg.MOGA_BF16, Nq, Nk, H, 128, p(cq), p(ck), G, s, p(oh), p(lse),
+                                                  p(ws), size, stream)
+                    out[size == pref] = [oh, lse]
+                else:
+                    o, l = out[False][:2]
+                    gr = [torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)]
+                    st = lib.moga_varlen_attn_bwd(p(d), p(q), p(k), p(v), p(o), p(l), mg.MOGA_BF16, Nq, Nk, H, 128, p(cq), p(ck), G, s,
+                                                  *(p(t) for t in gr), p(ws), size, stream)
+                    out[size == pref] += gr
+                assert st == 0
+        torch.cuda.synchronize()
+    finally:
+        mg.set_small_group_rows(-1)
+    none = out[False][1] == -torch.inf   # queries without keys
+    assert torch.equal(out[True][1] == -torch.inf, none)
+    for t in out.values():
+        t[1] = t[1].masked_fill(none, 0.0)
+    for a, b, name in zip(out[True], out[False], ("O", "lse", "dQ", "dK", "dV")):
+        close(a, b, name)
+    if none.any():
+        assert (out[True][0][none] == 0).all() and (out[True][2][none] == 0).all()
