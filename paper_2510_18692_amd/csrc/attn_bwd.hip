@@ -110,8 +110,10 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
   }
 }
 
-constexpr int64_t kSmallGroupRows = 1280;   // mean rows per group below which the small-group bf16 kernels run
-                                            // (398 against 334 TFLOP/s at 312 rows, equal at 1,560, slower above)
+// Mean rows per group below which the small-group bf16 kernels run: against the others 11 % faster at 520 rows, 5 % at 710,
+// equal at 1,060 (32,760 x 12 heads), 3 % faster at 510, 6 % slower at 1,030 (99,840 x 40), 7 % faster at 700, 5 % slower at
+// 1,090 (12,000 x 3).
+constexpr int64_t kSmallGroupRows = 900;
 
 }  // namespace moga
 

@@ -17,8 +17,14 @@
 
 namespace moga {
 
-constexpr int64_t kSmallGroupRows = 2560;   // mean rows per group below which the small-group bf16 kernel runs
-                                            // (927 against 886 TFLOP/s at 1,560 rows, 1052 against 1063 at 3,224)
+// Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of the other one: it wins by
+// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) equal at 1,030 rows,
+// 1.5 % slower at 1,560; 6 rounds (32,760 x 12) 4 % faster at 1,560, equal at 2,730, 4 % slower at 4,680; half a round
+// (12,000 x 3) 10 % faster at 2,400, equal at 6,000.
+static int64_t small_group_rows(int64_t Nq, int H) {
+  const int64_t rounds = Nq * H / (256 * kCus);
+  return rounds >= 16 ? 1152 : rounds >= 1 ? 2560 : 6144;
+}
 
 }  // namespace moga
 
@@ -32,7 +38,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
                            void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
-  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, kSmallGroupRows);
+  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
   const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
@@ -112,7 +118,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
 
 // True where the forward can split its last round.
 bool moga::fwd_splits(int64_t Nq, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, kSmallGroupRows) && split_pays(max_tiles(Nq, M, 256) * H);
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, 256) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }
