@@ -67,11 +67,13 @@ Tensor workspace(size_t bytes, const Tensor& like) { return make({std::max<int64
 
 size_t bytes_of(const OptTensor& ws) { return ws ? (size_t)ws->numel() : 0; }
 
-// Workspace of an attention call: what it runs fastest with if the device has it, else what it needs.
-OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like) {
+// Workspace of an attention call: what it runs fastest with if the device has it, else what it needs.  The workspace
+// goes back to the allocator when the call returns, which is in order only on the stream it was allocated on: a call on
+// another stream gets no more than it needs.
+OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like, const OptStream& stream) {
   const size_t need = moga_workspace_bytes(op, N, (int)H, (int)D, (int)M, 0, dt(like));
   const size_t preferred = moga_workspace_preferred_bytes(op, N, Nk, (int)H, (int)D, (int)M, 0, dt(like));
-  if (preferred > need) {
+  if (preferred > need && stream_of(stream) == stream_of(std::nullopt)) {
     try {
       return workspace(preferred, like);
     } catch (const c10::OutOfMemoryError&) {
@@ -136,7 +138,7 @@ std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, co
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
   Tensor oh = out ? *out : make({H, N, D}, qh);
   Tensor lse = lse_out ? *lse_out : make({H, N}, qh, at::kFloat);
-  OptTensor ws = attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
+  OptTensor ws = attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh, stream);
   check("moga_group_attn_fwd", moga_group_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M,
                                                    (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws), stream_of(stream)));
   return {oh, lse};
@@ -169,7 +171,7 @@ std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tens
   need_dims(qh, 3);
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
   Tensor d_qh = make({H, N, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  OptTensor ws = ws_in ? ws_in : attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
+  OptTensor ws = ws_in ? ws_in : attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh, stream);
   check("moga_group_attn_bwd", moga_group_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H,
                                                    (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
                                                    ptr(ws), bytes_of(ws), stream_of(stream)));
@@ -234,7 +236,7 @@ std::tuple<Tensor, Tensor> varlen_attn_fwd(const Tensor& qh, const Tensor& kh, c
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
   Tensor oh = make({H, Nq, D}, qh), lse = make({H, Nq}, qh, at::kFloat);
-  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_FWD, Nq, Nk, H, D, G, qh);
+  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_FWD, Nq, Nk, H, D, G, qh, stream);
   check("moga_varlen_attn_fwd", moga_varlen_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), Nq, Nk, (int)H, (int)D, as<int32_t>(cu_q),
                                                      as<int32_t>(cu_k), (int)G, (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws),
                                                      stream_of(stream)));
@@ -248,7 +250,7 @@ std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd(const Tensor& d_oh, const Ten
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
   Tensor d_qh = make({H, Nq, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, Nq, Nk, H, D, G, qh);
+  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, Nq, Nk, H, D, G, qh, stream);
   check("moga_varlen_attn_bwd", moga_varlen_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), Nq, Nk, (int)H,
                                                      (int)D, as<int32_t>(cu_q), as<int32_t>(cu_k), (int)G, (float)scale, ptr(d_qh),
                                                      ptr(d_kh), ptr(d_vh), ptr(ws), bytes_of(ws), stream_of(stream)));

@@ -75,3 +75,23 @@ def test_split_against_whole_tiles(nq, nk, H):
         close(a, b, name)
     if none.any():
         assert (out[True][0][none] == 0).all() and (out[True][2][none] == 0).all()
+
+
+def test_call_on_another_stream_takes_no_workspace_of_this_one():
+    g = torch.Generator().manual_seed(3)
+    q, k, v = (torch.randn((12, 8000, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    cu = torch.tensor([0, 4100, 8000], dtype=torch.int32, device="cuda")
+    assert mg.load().moga_workspace_preferred_bytes(mg.OP_ATTN_FWD, 8000, 8000, 12, 128, 2, 0, mg.MOGA_BF16) > 0
+    mg.set_small_group_rows(0)
+    try:
+        ref, _ = mg.moga_group_attn_fwd(q, k, v, cu, 128 ** -0.5)   # split
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        got, lse = mg.moga_group_attn_fwd(q, k, v, cu, 128 ** -0.5, stream=side)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before + 2   # the two outputs
+        torch.cuda.current_stream().wait_stream(side)
+        close(got, ref, "O")
+        torch.cuda.synchronize()
+    finally:
+        mg.set_small_group_rows(-1)
