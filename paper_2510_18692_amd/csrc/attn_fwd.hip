@@ -53,7 +53,8 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
     attn_fwd_bf16_pipe_kernel<8, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,
         softmax_scale, (unsigned short*)oh, lse, nullptr, nullptr, sw);
-    split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, M, H, Nq, softmax_scale, (unsigned short*)oh, lse);
+    split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, cu_k, M, H, Nq, softmax_scale, (unsigned short*)oh,
+                                                                  lse);
   } else if (dtype == MOGA_BF16) {
     attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,

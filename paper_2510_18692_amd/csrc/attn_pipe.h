@@ -547,17 +547,20 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   else store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate);
 }
 
-// Pieces of every query tile of the last round: O = sum O_k 2^((m_k - m) c) / l, l = sum l_k 2^((m_k - m) c).
-static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const int32_t* __restrict__ cu, int M, int H, int64_t N,
+// Pieces of every query tile of the last round: O = sum O_k 2^((m_k - m) c) / l, l = sum l_k 2^((m_k - m) c).  NaN and
+// infinite scores end as in a whole tile; only a group without keys gets zero rows.
+static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const int32_t* __restrict__ cu_q,
+                                                               const int32_t* __restrict__ cu_k, int M, int H, int64_t N,
                                                                float scale, unsigned short* __restrict__ oh,
                                                                float* __restrict__ lse) {
-  const int per_head = count_tiles(cu, M, kSplitRows);
+  const int per_head = count_tiles(cu_q, M, kSplitRows);
   const SplitShape s = split_shape(per_head * H);
   if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
   int head, tile;
   decode_work(s.full + blockIdx.x, per_head, H, head, tile);
   TileInfo ti;
-  if (!find_tile(cu, M, kSplitRows, tile, ti)) return;
+  if (!find_tile(cu_q, M, kSplitRows, tile, ti)) return;
+  const bool keys = cu_k[ti.group + 1] > cu_k[ti.group];
   const float c = scale * 1.4426950408889634f;
   const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
   if (ti.tile_row + r >= ti.row_end) return;
@@ -575,14 +578,15 @@ static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const
   for (int k = 0; k < kMaxSplits; ++k) m = fmaxf(m, ml[k][0]);
   floatx4_t o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int k = 0; k < kMaxSplits; ++k) {
-    const float w = k < s.splits && m > -INFINITY ? fast_exp2((ml[k][0] - m) * c) : 0.f;   // m = -inf: no keys at all, zero row
-    l += ml[k][1] * w;
-    o += v[k] * w;
-  }
+  for (int k = 0; k < kMaxSplits; ++k)
+    if (k < s.splits) {
+      const float w = ml[k][0] == m ? 1.f : fast_exp2((ml[k][0] - m) * c);   // equal: also both -inf
+      l += ml[k][1] * w;
+      o += v[k] * w;
+    }
   const int64_t orow = (int64_t)head * N + ti.tile_row + r;
-  *(uintx2_t*)(oh + orow * kHeadDim + col) = pack4(o, l > 0.f ? 1.f / l : 0.f);
-  if (col == 0) lse[orow] = l > 0.f ? m * scale + logf(l) : -INFINITY;
+  *(uintx2_t*)(oh + orow * kHeadDim + col) = pack4(o, keys ? 1.f / l : 0.f);
+  if (col == 0) lse[orow] = keys ? m * scale + logf(l) : -INFINITY;
 }
 
 }  // namespace moga

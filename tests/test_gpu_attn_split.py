@@ -95,3 +95,46 @@ def test_call_on_another_stream_takes_no_workspace_of_this_one():
         torch.cuda.synchronize()
     finally:
         mg.set_small_group_rows(-1)
+
+
+@pytest.mark.parametrize("what", ["nan query", "nan key", "inf score", "all scores -inf", "inf value"])
+def test_split_keeps_nan_and_infinities(what):
+    """One row of Q, K or V that is not finite: NaN and infinities come out at the same places as from whole tiles."""
+    nq, H, s = [300, 900], 2, 128 ** -0.5
+    N = sum(nq)
+    g = torch.Generator().manual_seed(7)
+    q, k, v = (torch.randn((H, N, 128), generator=g) for _ in range(3))
+    if what == "nan query":
+        q[0, 40] = torch.nan
+    elif what == "nan key":
+        k[1, 310] = torch.nan
+    elif what == "inf score":
+        k[0, 17] = 3e38
+        q[0, 5] = 1.0
+    elif what == "all scores -inf":
+        k[0, :300] = -k[0, :300].abs()
+        q[0, 5] = 3e38
+    else:
+        v[1, 400, 3] = torch.inf
+    q, k, v = (t.to(torch.bfloat16).cuda() for t in (q, k, v))
+    cu = torch.tensor([0, 300, N], dtype=torch.int32, device="cuda")
+    lib, stream = mg.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    mg.set_small_group_rows(0)
+    try:
+        out = []
+        for size in (mg.workspace_bytes(mg.OP_VARLEN_ATTN_FWD, N, H, 128, 2, 0, mg.MOGA_BF16),
+                     lib.moga_workspace_preferred_bytes(mg.OP_VARLEN_ATTN_FWD, N, N, H, 128, 2, 0, mg.MOGA_BF16)):
+            ws, oh, lse = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty_like(q), torch.empty((H, N), device="cuda")
+            assert lib.moga_varlen_attn_fwd(p(q), p(k), p(v), mg.MOGA_BF16, N, N, H, 128, p(cu), p(cu), 2, s, p(oh), p(lse), p(ws), size,
+                                            stream) == 0
+            out.append((oh, lse))
+        torch.cuda.synchronize()
+    finally:
+        mg.set_small_group_rows(-1)
+    (o0, l0), (o1, l1) = out
+    assert not (torch.isfinite(o0).all() and torch.isfinite(l0).all())
+    for a, b in ((o0, o1), (l0, l1)):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isinf(a), torch.isinf(b))
+        assert torch.equal(a[torch.isinf(a)], b[torch.isinf(b)])
+        fin = torch.isfinite(a)
+        close(b[fin], a[fin], what)
