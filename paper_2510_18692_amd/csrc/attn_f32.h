@@ -188,13 +188,14 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
     float mx = p[0];
 #pragma unroll
     for (int v = 1; v < 16; ++v) mx = fmaxf(mx, p[v]);
-    const float m_new = fmaxf(m, f32_halves_max(mx));   // finite: every step has a key
-    const float alpha = fast_exp2((m - m_new) * c);
+    const float m_new = fmaxf(m, f32_halves_max(mx));
+    const float ref = m_new == -INFINITY ? 0.f : m_new;   // every score so far may be -inf: weights of zero, not NaN
+    const float alpha = fast_exp2((m - ref) * c);
     m = m_new;
     float sum = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      p[v] = fast_exp2((p[v] - m) * c);
+      p[v] = fast_exp2((p[v] - ref) * c);
       sum += p[v];
     }
     l = fmaf(l, alpha, sum);
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
     f32_accumulate<D>(o, vb, 32 * s, n - 1, p, r, h);
   }
 
-  // common maximum of the waves (a wave without keys has m = -inf and weight 0)
+  // common maximum of the waves (a wave without keys, or with none but scores of -inf, has m = -inf and weight 0)
   l = f32_halves_sum(l);
   if (h == 0) { s_m[wave][r] = m; s_l[wave][r] = l; }
   __syncthreads();
@@ -214,9 +215,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
   for (int w = 1; w < NW; ++w) mt = fmaxf(mt, s_m[w][r]);
   float lt = 0.f;
   if (nsteps > 0) {
+    const float ref = mt == -INFINITY ? 0.f : mt;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) lt = fmaf(s_l[w][r], fast_exp2((s_m[w][r] - mt) * c), lt);
-    const float f = fast_exp2((m - mt) * c);
+    for (int w = 0; w < NW; ++w) lt = fmaf(s_l[w][r], fast_exp2((s_m[w][r] - ref) * c), lt);
+    const float f = fast_exp2((m - ref) * c);
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

@@ -42,3 +42,22 @@ def test_f32_attention_tile_edges(D, nq, nk):
     torch.cuda.synchronize()
     for name, got, ref in zip(("dQ", "dK", "dV"), grads, refs):
         P.assert_close_f32(P.unhat(got), ref, name)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("first,count", [(0, 32), (32, 32), (5, 300), (224, 76)])
+def test_f32_keys_with_scores_of_minus_infinity_have_no_weight(D, first, count):
+    """A run of keys so large that their scores overflow to -inf (whole steps of a wave, the first ones among them):
+    the rows equal those without these keys.  Group of 300 queries and 700 keys, every query entry positive."""
+    g = torch.Generator().manual_seed(D + first)
+    q, k, v = torch.rand((2, 300, D), generator=g) + 0.5, torch.randn((2, 700, D), generator=g), torch.randn((2, 700, D), generator=g)
+    keep = torch.ones(700, dtype=torch.bool)
+    keep[first:first + count] = False
+    k[:, ~keep] = -3e38
+    cq = torch.tensor([0, 300], dtype=torch.int32, device="cuda")
+    out = []
+    for kk, vv in ((k, v), (k[:, keep], v[:, keep])):
+        ck = torch.tensor([0, kk.shape[1]], dtype=torch.int32, device="cuda")
+        out.append(mg.moga_varlen_attn_fwd(q.cuda(), kk.contiguous().cuda(), vv.contiguous().cuda(), cq, ck, D ** -0.5))
+    for a, b, name in zip(out[0], out[1], ("O", "lse")):
+        P.assert_close_f32(P.to64(a), P.to64(b), name)
