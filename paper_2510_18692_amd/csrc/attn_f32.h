@@ -32,9 +32,20 @@ namespace moga {
 constexpr int kF32Rows = 32;   // stationary rows per block
 constexpr int kF32Waves = 8;
 
+// DT adjacent channels of a row, from a buffer.
 template <int DT> struct F32Piece;
-template <> struct F32Piece<2> { typedef floatx2_t type; };
-template <> struct F32Piece<4> { typedef floatx4_t type; };
+template <> struct F32Piece<2> {
+  typedef floatx2_t type;
+  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t rows, int byte) {
+    return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b64(rows, byte, 0, 0));
+  }
+};
+template <> struct F32Piece<4> {
+  typedef floatx4_t type;
+  static __device__ __forceinline__ type load(__amdgpu_buffer_rsrc_t rows, int byte) {
+    return __builtin_bit_cast(type, __builtin_amdgcn_raw_buffer_load_b128(rows, byte, 0, 0));
+  }
+};
 
 // Stationary rows in LDS: padded by 16 bytes, so that the 16-byte reads of 16 lanes (one row each)
 // cover all banks.
@@ -74,17 +85,23 @@ __device__ __forceinline__ void f32_scores(floatx16_t& acc, const F32Row<D>& f, 
 // Streamed row of accumulator register v, relative to the step's first row.
 __device__ __forceinline__ int f32_acc_row(int v, int h) { return 8 * (v >> 2) + 4 * h + (v & 3); }
 
-// acc[dt] += (streamed rows)^T x b, the streamed rows read with DT adjacent channels per lane.
+// acc[dt] += (streamed rows)^T x b, the streamed rows read with DT adjacent channels per lane.  Rows past `last` lie outside
+// the buffer of the step's rows and read as zero: a copy of the last row times b = 0 would be NaN where that row has an
+// infinity.  Selects for those rows made the D = 128 kernels spill (dQ, dK/dV and the forward 6 to 12 % slower); the buffer's
+// own check needs fewer registers than clamped addresses (4,096 x 2 x 128, 8 groups: forward and backward 34.3 / 100.6 before,
+// 33.4 / 97.4 us; x 64: 19.5 / 56.0 and 17.9 / 51.1).
 template <int D>
 __device__ __forceinline__ void f32_accumulate(floatx16_t (&acc)[D / 32], const float* __restrict__ base, int row0,
                                                int last, const floatx16_t& b, int r, int h) {
   constexpr int DT = D / 32;
-  typedef typename F32Piece<DT>::type piece;
+  const auto rows = __builtin_amdgcn_make_buffer_rsrc((void*)(base + (int64_t)row0 * D), 0, min(32, last + 1 - row0) * D * 4, 0x00027000);
+  int lane_off = (4 * h * D + DT * r) * 4;
+  asm("" : "+v"(lane_off));   // not a loop invariant: the sixteen offsets are immediates, not registers kept through the loop
 #pragma unroll
   for (int v0 = 0; v0 < 16; v0 += 8) {   // two batches of eight loads in flight
-    piece a[8];
+    typename F32Piece<DT>::type a[8];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) a[v] = *(const piece*)(base + (int64_t)min(row0 + f32_acc_row(v0 + v, h), last) * D + DT * r);
+    for (int v = 0; v < 8; ++v) a[v] = F32Piece<DT>::load(rows, lane_off + f32_acc_row(v0 + v, 0) * D * 4);
 #pragma unroll
     for (int v = 0; v < 8; ++v)
 #pragma unroll
@@ -370,8 +387,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dkdv_f32_mfma_kernel(
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const float e = fast_exp2(fmaf(p[v], c, -lv[v] * 1.4426950408889634f));
-      p[v] = 32 * s + f32_acc_row(v, h) < n ? e : 0.f;
-      ds[v] = p[v] * (ds[v] - dl[v]);
+      const bool valid = 32 * s + f32_acc_row(v, h) < n;
+      p[v] = valid ? e : 0.f;
+      ds[v] = valid ? e * (ds[v] - dl[v]) : 0.f;
     }
     f32_accumulate<D>(dv, ob, 32 * s, n - 1, p, r, h);
     f32_accumulate<D>(dk, qb, 32 * s, n - 1, ds, r, h);

@@ -61,3 +61,24 @@ def test_f32_keys_with_scores_of_minus_infinity_have_no_weight(D, first, count):
         out.append(mg.moga_varlen_attn_fwd(q.cuda(), kk.contiguous().cuda(), vv.contiguous().cuda(), cq, ck, D ** -0.5))
     for a, b, name in zip(out[0], out[1], ("O", "lse")):
         P.assert_close_f32(P.to64(a), P.to64(b), name)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_infinity_in_the_last_row_of_a_group(D):
+    """Groups that end inside a step (33 and 300 rows): an infinite entry of V in the last row makes its channel of O
+    infinite, one of dO its channel of dV, and nothing there NaN."""
+    g = torch.Generator().manual_seed(D)
+    q, k, v, d = (torch.randn((1, 333, D), generator=g) for _ in range(4))
+    cu = torch.tensor([0, 33, 333], dtype=torch.int32, device="cuda")
+    hv, hd = v.clone(), d.clone()
+    for row in (32, 332):
+        hv[0, row, 7] = hd[0, row, 7] = torch.inf
+    q, k, v, d, hv, hd = (t.cuda() for t in (q, k, v, d, hv, hd))
+    o, _ = mg.moga_group_attn_fwd(q, k, hv, cu, D ** -0.5)
+    o0, lse = mg.moga_group_attn_fwd(q, k, v, cu, D ** -0.5)
+    dv = mg.moga_group_attn_bwd(hd, q, k, v, o0, lse, cu, D ** -0.5)[2]
+    dv0 = mg.moga_group_attn_bwd(d, q, k, v, o0, lse, cu, D ** -0.5)[2]
+    for a, b in ((o, o0), (dv, dv0)):
+        a, b = a.cpu(), b.cpu()
+        assert (a[..., 7] == torch.inf).all()
+        assert torch.equal(a[..., :7], b[..., :7]) and torch.equal(a[..., 8:], b[..., 8:])
