@@ -82,3 +82,30 @@ def test_f32_infinity_in_the_last_row_of_a_group(D):
         a, b = a.cpu(), b.cpu()
         assert (a[..., 7] == torch.inf).all()
         assert torch.equal(a[..., :7], b[..., :7]) and torch.equal(a[..., 8:], b[..., 8:])
+
+
+def test_f32_backward_probabilities_keep_their_precision_at_large_logits():
+    """P = exp(scale s - lse) of the backward, read off the gradients: dot products that are exact in fp32, dO = unit rows
+    (dV = P^T), V = ones and O = 0 (dS = P, which dQ and dK show in channels of their own).  With x = scale s - lse rounded
+    once, times log2(e), and exp2 good to two units, P is off by at most (2.3 |x| + 8) 2^-24 of itself; logits are
+    64 to 136 here, and anything rounded at their size shows (100 * 2^-24 = 6e-6 against 5e-7 to 2e-6)."""
+    D, nq, nk, scale = 64, 31, 32, float(np.float32(0.1))
+    a, b = 32.0 + np.arange(nq), (20.0 + np.arange(nk) / 16.0)
+    q, k, d = np.zeros((nq, D)), np.zeros((nk, D)), np.zeros((nq, D))
+    q[:, 0], k[:, 0] = a, b
+    k[np.arange(nk), 1 + np.arange(nk)] = 1.0               # channels 1 .. 32: a key each
+    q[np.arange(nq), 33 + np.arange(nq)] = 1.0              # channels 33 .. 63: a query each
+    d[np.arange(nq), np.arange(nq)] = 1.0
+    logits = scale * np.outer(a, b)
+    lse = (logits.max(1) + 0.5).astype(np.float32)
+    x = logits - lse.astype(np.float64)[:, None]
+    assert logits.max() > 100 and -16 < x.min() and x.max() < 0
+    f = lambda t: torch.from_numpy(t.astype(np.float32))[None].cuda()
+    cu = lambda n: torch.tensor([0, n], dtype=torch.int32, device="cuda")
+    dq, dk, dv = mg.moga_varlen_attn_bwd(f(d), f(q), f(k), torch.ones((1, nk, D), device="cuda"), torch.zeros((1, nq, D), device="cuda"),
+                                         f(lse), cu(nq), cu(nk), scale)
+    bound = (2.3 * np.abs(x) + 8) * 2.0 ** -24
+    for name, got in (("dV", P.to64(dv)[0][:, :nq].T), ("dQ", P.to64(dq)[0][:, 1:33] / scale), ("dK", P.to64(dk)[0][:, 33:].T / scale)):
+        e = np.abs(got / np.exp(x) - 1)
+        print(f"  {name}: largest error {e.max():.2e}, {(e / bound).max():.2f} of its bound", flush=True)
+        assert (e <= bound).all(), name
