@@ -328,9 +328,13 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
   for (int j = 0; j < MB; ++j) acc[j] = 0.f;
 
   for (int64_t tb = t0; tb < t1; tb += kRbTok) {
-    float xv[WT];   // tokens past the end of the range have dr = 0
+    float xv[WT];   // tokens past the end of the range have dr = 0 and x = 0 (not a copy: 0 times an infinity is NaN)
 #pragma unroll
-    for (int i = 0; i < WT; ++i) xv[i] = load_x<XT>(xc + min(tb + WT * wave + i, t1 - 1) * d);
+    for (int i = 0; i < WT; ++i) {
+      const int64_t tok = tb + WT * wave + i;
+      xv[i] = load_x<XT>(xc + min(tok, t1 - 1) * d);
+      if (tok >= t1) xv[i] = 0.f;
+    }
     __syncthreads();
     for (int idx = threadIdx.x; idx < kRbTok * MB; idx += 256) {
       const int ti = idx / MB, j = idx % MB;

@@ -36,3 +36,23 @@ def test_router_weight_gradient_splits(N, d, M, dtype):
     d_w, _ = mg.moga_route_bwd(x.cuda(), w.cuda(), *dev, d_gate.cuda())
     torch.cuda.synchronize()
     P.assert_close_f32(P.to64(d_w), dW, "dW")
+
+
+@pytest.mark.parametrize("N,d,M,dtype", [(65, 64, 8, "f32"), (200, 96, 33, "f32"), (129, 100, 32, "bf16")])
+def test_infinity_in_the_last_token_stays_one(N, d, M, dtype):
+    """The last tile of 64 tokens is not full: an infinite activation of the last token makes its column of dW infinite
+    with the sign of dr, as the sum says, and no other column changes."""
+    g = torch.Generator().manual_seed(N)
+    x = torch.randn((N, d), generator=g).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    probs = torch.softmax(torch.randn((N, M), generator=g), 1)
+    group = probs.argmax(1).to(torch.int32)
+    gate = probs.max(1).values
+    d_gate = torch.rand(N, generator=g) + 0.5
+    hx = x.clone()
+    hx[N - 1, 5] = torch.inf
+    dev = [t.cuda() for t in (torch.zeros((M, d)), probs, group, gate, d_gate)]
+    a, b = (mg.moga_route_bwd(t.cuda(), *dev)[0].cpu() for t in (hx, x))
+    sign = torch.where(torch.arange(M) == group[N - 1], torch.inf, -torch.inf)
+    assert torch.equal(a[:, 5], sign)
+    a[:, 5] = b[:, 5]
+    assert torch.equal(a, b)
