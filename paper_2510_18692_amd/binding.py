@@ -347,6 +347,10 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
     a_s, lse_s = moga_varlen_attn_fwd(qs, ks, vs, si["cu_q"], si["cu_k"], softmax_scale, stream=stream)
     ident = torch.arange(N + 1, dtype=torch.int32, device=dev)
     cu_f = torch.arange(T + 1, dtype=torch.int32, device=dev) * (Hh * Ww)
+    if stream is not None and stream != torch.cuda.current_stream():   # made on the current stream, read on `stream`
+        stream.wait_stream(torch.cuda.current_stream())
+        for t in (ident, cu_f):
+            t.record_stream(stream)
     qf, kf, vf = (moga_gather_rows(t, ident[:N], stream=stream) for t in (q, k, v))
     a_f, lse_f = moga_varlen_attn_fwd(qf, kf, vf, cu_f, cu_f, softmax_scale, stream=stream)
     o = moga_merge3_fwd(a_m, a_s, a_f, pm["inv_perm"], si["q_slot"], None, gate, stream=stream)

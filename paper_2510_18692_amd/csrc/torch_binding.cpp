@@ -6,6 +6,7 @@
 // forward calls 72 and 32 us, the four backward calls 70 and 31 us, a training step through autograd 346 and
 // 101 us (its backward now runs in the engine's thread without the interpreter).
 #include <ATen/ATen.h>
+#include <c10/core/StreamGuard.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/utils/pybind.h>
@@ -51,8 +52,6 @@ void* ptr(const OptTensor& t) { return t ? ptr(*t) : nullptr; }
 template <typename T> T* as(const Tensor& t) { return static_cast<T*>(ptr(t)); }
 template <typename T> T* as(const OptTensor& t) { return static_cast<T*>(ptr(t)); }
 
-void* stream_of(const OptStream& s) { return s ? reinterpret_cast<void*>(*s) : c10::hip::getCurrentHIPStream().stream(); }
-
 // Every function checks its tensors before anything touches the GPU.
 template <typename... T>
 void require(const T&... t) { (ptr(t), ...); }
@@ -61,39 +60,64 @@ void need_dims(const Tensor& t, int64_t n) {
   if (t.dim() != n) raise(PyExc_ValueError, "expected a tensor of " + std::to_string(n) + " dimensions");
 }
 
-Tensor make(at::IntArrayRef size, const Tensor& like, at::ScalarType type) { return at::empty(size, like.options().dtype(type)); }
-Tensor make(at::IntArrayRef size, const Tensor& like) { return at::empty(size, like.options()); }
-Tensor workspace(size_t bytes, const Tensor& like) { return make({std::max<int64_t>((int64_t)bytes, 16)}, like, at::kByte); }
-
 size_t bytes_of(const OptTensor& ws) { return ws ? (size_t)ws->numel() : 0; }
 
-// Workspace of an attention call: what it runs fastest with if the device has it, else what it needs.  The workspace
-// goes back to the allocator when the call returns, which is in order only on the stream it was allocated on: a call on
-// another stream gets no more than it needs.
-OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like, const OptStream& stream) {
-  const size_t need = moga_workspace_bytes(op, N, (int)H, (int)D, (int)M, 0, dt(like));
-  const size_t preferred = moga_workspace_preferred_bytes(op, N, Nk, (int)H, (int)D, (int)M, 0, dt(like));
-  if (preferred > need && stream_of(stream) == stream_of(std::nullopt)) {
-    try {
-      return workspace(preferred, like);
-    } catch (const c10::OutOfMemoryError&) {
+// The stream of a call and what is allocated for it.  Memory comes from the pool of torch's current stream.  Where the
+// kernels run on another stream, every tensor is recorded as used there: a workspace or an intermediate result is dropped on
+// the host while they may still run, and its memory must not go to the current stream before they are done.
+class Call {
+ public:
+  explicit Call(const OptStream& given) {
+    const auto current = c10::hip::getCurrentHIPStream();
+    handle_ = given ? reinterpret_cast<hipStream_t>(*given) : current.stream();
+    if (handle_ != current.stream()) {   // torch's tensors are on "cuda" devices
+      const auto s = c10::hip::getStreamFromExternal(handle_, current.device_index());
+      other_ = c10::Stream(c10::Stream::UNSAFE, c10::Device(c10::kCUDA, current.device_index()), s.id());
     }
   }
-  if (need == 0) return std::nullopt;
-  return workspace(need, like);
-}
+  void* stream() const { return handle_; }
+  const std::optional<c10::Stream>& other() const { return other_; }
+
+  Tensor make(at::IntArrayRef size, const Tensor& like, at::ScalarType type) const {
+    Tensor t = at::empty(size, like.options().dtype(type));
+    if (other_) t.record_stream(*other_);
+    return t;
+  }
+  Tensor make(at::IntArrayRef size, const Tensor& like) const { return make(size, like, like.scalar_type()); }
+  Tensor workspace(size_t bytes, const Tensor& like) const { return make({std::max<int64_t>((int64_t)bytes, 16)}, like, at::kByte); }
+
+  // Workspace of an attention call: what it runs fastest with if the device has it, else what it needs; on another stream
+  // than torch's current one no more than it needs.
+  OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like) const {
+    const size_t need = moga_workspace_bytes(op, N, (int)H, (int)D, (int)M, 0, dt(like));
+    const size_t preferred = moga_workspace_preferred_bytes(op, N, Nk, (int)H, (int)D, (int)M, 0, dt(like));
+    if (preferred > need && !other_) {
+      try {
+        return workspace(preferred, like);
+      } catch (const c10::OutOfMemoryError&) {
+      }
+    }
+    if (need == 0) return std::nullopt;
+    return workspace(need, like);
+  }
+
+ private:
+  hipStream_t handle_;
+  std::optional<c10::Stream> other_;   // the call's stream, if it is not torch's current one
+};
 
 std::tuple<Tensor, Tensor, OptTensor, OptTensor> route(const Tensor& x, const Tensor& w, const OptTensor& bias,
                                                        bool want_probs, bool want_logits, const OptStream& stream) {
   require(x, w, bias);
+  const Call call(stream);
   need_dims(x, 2);
   const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
-  Tensor group = make({N}, x, at::kInt), gate = make({N}, x, at::kFloat);
+  Tensor group = call.make({N}, x, at::kInt), gate = call.make({N}, x, at::kFloat);
   OptTensor probs, logits;
-  if (want_probs) probs = make({N, M}, x, at::kFloat);
-  if (want_logits) logits = make({N, M}, x, at::kFloat);
+  if (want_probs) probs = call.make({N, M}, x, at::kFloat);
+  if (want_logits) logits = call.make({N, M}, x, at::kFloat);
   check("moga_route", moga_route(ptr(x), dt(x), as<float>(w), as<float>(bias), N, (int)d, (int)M, as<int32_t>(group),
-                                 as<float>(gate), as<float>(probs), as<float>(logits), nullptr, 0, stream_of(stream)));
+                                 as<float>(gate), as<float>(probs), as<float>(logits), nullptr, 0, call.stream()));
   return {group, gate, probs, logits};
 }
 
@@ -105,13 +129,14 @@ struct Permuted {
 Permuted permute(const Tensor& group, int64_t M, const OptTensor& q, const OptTensor& k, const OptTensor& v,
                  const OptStream& stream) {
   require(group, q, k, v);
+  const Call call(stream);
   const int64_t N = group.size(0);
   Permuted p;
-  p.counts = make({M}, group, at::kInt);
-  p.cu_seqlens = make({M + 1}, group, at::kInt);
-  p.max_seqlen = make({1}, group, at::kInt);
-  p.perm = make({N}, group, at::kInt);
-  p.inv_perm = make({N}, group, at::kInt);
+  p.counts = call.make({M}, group, at::kInt);
+  p.cu_seqlens = call.make({M + 1}, group, at::kInt);
+  p.max_seqlen = call.make({1}, group, at::kInt);
+  p.perm = call.make({N}, group, at::kInt);
+  p.inv_perm = call.make({N}, group, at::kInt);
   int64_t H = 0, D = 0;
   int type = MOGA_F32;
   if (q) {
@@ -119,48 +144,51 @@ Permuted permute(const Tensor& group, int64_t M, const OptTensor& q, const OptTe
     H = q->size(1);
     D = q->size(2);
     type = dt(*q);
-    p.qh = make({H, N, D}, *q);
-    p.kh = make({H, N, D}, k ? *k : *q);
-    p.vh = make({H, N, D}, v ? *v : *q);
+    p.qh = call.make({H, N, D}, *q);
+    p.kh = call.make({H, N, D}, k ? *k : *q);
+    p.vh = call.make({H, N, D}, v ? *v : *q);
   }
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_PERMUTE, N, (int)H, (int)D, (int)M, 0, type), group);
+  Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_PERMUTE, N, (int)H, (int)D, (int)M, 0, type), group);
   check("moga_permute", moga_permute(as<int32_t>(group), N, (int)M, ptr(q), ptr(k), ptr(v), type, (int)H, (int)D,
                                      as<int32_t>(p.counts), as<int32_t>(p.cu_seqlens), as<int32_t>(p.max_seqlen),
                                      as<int32_t>(p.perm), as<int32_t>(p.inv_perm), ptr(p.qh), ptr(p.kh), ptr(p.vh),
-                                     ptr(ws), ws.numel(), stream_of(stream)));
+                                     ptr(ws), ws.numel(), call.stream()));
   return p;
 }
 
 std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& cu,
                                           double scale, const OptStream& stream, const OptTensor& out, const OptTensor& lse_out) {
   require(qh, kh, vh, cu, out, lse_out);
+  const Call call(stream);
   need_dims(qh, 3);
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
-  Tensor oh = out ? *out : make({H, N, D}, qh);
-  Tensor lse = lse_out ? *lse_out : make({H, N}, qh, at::kFloat);
-  OptTensor ws = attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh, stream);
+  Tensor oh = out ? *out : call.make({H, N, D}, qh);
+  Tensor lse = lse_out ? *lse_out : call.make({H, N}, qh, at::kFloat);
+  OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
   check("moga_group_attn_fwd", moga_group_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M,
-                                                   (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws), stream_of(stream)));
+                                                   (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws), call.stream()));
   return {oh, lse};
 }
 
 Tensor unpermute(const Tensor& oh, const Tensor& perm, const OptTensor& gate, const OptStream& stream, const OptTensor& out) {
   require(oh, perm, gate, out);
+  const Call call(stream);
   need_dims(oh, 3);
   const int64_t H = oh.size(0), N = oh.size(1), D = oh.size(2);
-  Tensor o = out ? *out : make({N, H, D}, oh);
-  check("moga_unpermute", moga_unpermute(ptr(oh), dt(oh), as<int32_t>(perm), as<float>(gate), N, (int)H, (int)D, ptr(o), stream_of(stream)));
+  Tensor o = out ? *out : call.make({N, H, D}, oh);
+  check("moga_unpermute", moga_unpermute(ptr(oh), dt(oh), as<int32_t>(perm), as<float>(gate), N, (int)H, (int)D, ptr(o), call.stream()));
   return o;
 }
 
 std::tuple<Tensor, Tensor> unpermute_bwd(const Tensor& d_o, const Tensor& oh, const Tensor& perm, const Tensor& gate,
                                          const OptStream& stream) {
   require(d_o, oh, perm, gate);
+  const Call call(stream);
   need_dims(oh, 3);
   const int64_t H = oh.size(0), N = oh.size(1), D = oh.size(2);
-  Tensor d_oh = make({H, N, D}, oh), d_gate = make({N}, oh, at::kFloat);
+  Tensor d_oh = call.make({H, N, D}, oh), d_gate = call.make({N}, oh, at::kFloat);
   check("moga_unpermute_bwd", moga_unpermute_bwd(ptr(d_o), ptr(oh), dt(oh), as<int32_t>(perm), as<float>(gate), N, (int)H, (int)D,
-                                                 ptr(d_oh), as<float>(d_gate), stream_of(stream)));
+                                                 ptr(d_oh), as<float>(d_gate), call.stream()));
   return {d_oh, d_gate};
 }
 
@@ -168,50 +196,54 @@ std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tens
                                                   const Tensor& oh, const Tensor& lse, const Tensor& cu, double scale,
                                                   const OptStream& stream, const OptTensor& ws_in) {
   require(d_oh, qh, kh, vh, oh, lse, cu, ws_in);
+  const Call call(stream);
   need_dims(qh, 3);
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
-  Tensor d_qh = make({H, N, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  OptTensor ws = ws_in ? ws_in : attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh, stream);
+  Tensor d_qh = call.make({H, N, D}, qh), d_kh = call.make(kh.sizes(), kh), d_vh = call.make(vh.sizes(), vh);
+  OptTensor ws = ws_in ? ws_in : call.attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
   check("moga_group_attn_bwd", moga_group_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H,
                                                    (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
-                                                   ptr(ws), bytes_of(ws), stream_of(stream)));
+                                                   ptr(ws), bytes_of(ws), call.stream()));
   return {d_qh, d_kh, d_vh};
 }
 
 std::tuple<Tensor, Tensor, Tensor> permute_bwd(const Tensor& d_qh, const Tensor& d_kh, const Tensor& d_vh, const Tensor& perm,
                                                const OptStream& stream) {
   require(d_qh, d_kh, d_vh, perm);
+  const Call call(stream);
   need_dims(d_qh, 3);
   const int64_t H = d_qh.size(0), N = d_qh.size(1), D = d_qh.size(2);
-  Tensor d_q = make({N, H, D}, d_qh), d_k = make({N, H, D}, d_kh), d_v = make({N, H, D}, d_vh);
+  Tensor d_q = call.make({N, H, D}, d_qh), d_k = call.make({N, H, D}, d_kh), d_v = call.make({N, H, D}, d_vh);
   check("moga_permute_bwd", moga_permute_bwd(ptr(d_qh), ptr(d_kh), ptr(d_vh), dt(d_qh), as<int32_t>(perm), N, (int)H, (int)D, ptr(d_q),
-                                             ptr(d_k), ptr(d_v), stream_of(stream)));
+                                             ptr(d_k), ptr(d_v), call.stream()));
   return {d_q, d_k, d_v};
 }
 
 std::tuple<Tensor, OptTensor> route_bwd(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
                                         const Tensor& d_gate, bool want_dx, const OptStream& stream) {
   require(x, w, probs, group, gate, d_gate);
+  const Call call(stream);
   need_dims(x, 2);
   const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
-  Tensor d_w = make({M, d}, x, at::kFloat);
+  Tensor d_w = call.make({M, d}, x, at::kFloat);
   OptTensor d_x;
-  if (want_dx) d_x = make({N, d}, x, at::kFloat);
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), x);
+  if (want_dx) d_x = call.make({N, d}, x, at::kFloat);
+  Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), x);
   check("moga_route_bwd", moga_route_bwd(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate),
                                          as<float>(d_gate), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x), ptr(ws), ws.numel(),
-                                         stream_of(stream)));
+                                         call.stream()));
   return {d_w, d_x};
 }
 
 std::tuple<Tensor, Tensor> fused_attn_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& perm, const Tensor& gate,
                                           const Tensor& cu, double scale, const OptStream& stream) {
   require(q, k, v, perm, gate, cu);
+  const Call call(stream);
   need_dims(q, 3);
   const int64_t N = q.size(0), H = q.size(1), D = q.size(2), M = cu.size(0) - 1;
-  Tensor o = make({N, H, D}, q), lse = make({H, N}, q, at::kFloat);
+  Tensor o = call.make({N, H, D}, q), lse = call.make({H, N}, q, at::kFloat);
   check("moga_fused_attn_fwd", moga_fused_attn_fwd(ptr(q), ptr(k), ptr(v), dt(q), N, (int)H, (int)D, as<int32_t>(perm), as<float>(gate),
-                                                   as<int32_t>(cu), (int)M, (float)scale, ptr(o), as<float>(lse), stream_of(stream)));
+                                                   as<int32_t>(cu), (int)M, (float)scale, ptr(o), as<float>(lse), call.stream()));
   return {o, lse};
 }
 
@@ -219,27 +251,29 @@ std::tuple<Tensor, Tensor, Tensor, Tensor> fused_attn_bwd(const Tensor& d_o, con
                                                           const Tensor& o, const Tensor& lse, const Tensor& perm, const Tensor& inv_perm,
                                                           const Tensor& gate, const Tensor& cu, double scale, const OptStream& stream) {
   require(d_o, q, k, v, o, lse, perm, inv_perm, gate, cu);
+  const Call call(stream);
   need_dims(q, 3);
   const int64_t N = q.size(0), H = q.size(1), D = q.size(2), M = cu.size(0) - 1;
-  Tensor d_q = make({N, H, D}, q), d_k = make(k.sizes(), k), d_v = make(v.sizes(), v), d_gate = make({N}, q, at::kFloat);
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_ATTN_BWD, N, (int)H, (int)D, (int)M, 0, dt(q)), q);
+  Tensor d_q = call.make({N, H, D}, q), d_k = call.make(k.sizes(), k), d_v = call.make(v.sizes(), v), d_gate = call.make({N}, q, at::kFloat);
+  Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_ATTN_BWD, N, (int)H, (int)D, (int)M, 0, dt(q)), q);
   check("moga_fused_attn_bwd", moga_fused_attn_bwd(ptr(d_o), ptr(q), ptr(k), ptr(v), ptr(o), as<float>(lse), dt(q), N, (int)H, (int)D,
                                                    as<int32_t>(perm), as<int32_t>(inv_perm), as<float>(gate), as<int32_t>(cu), (int)M,
                                                    (float)scale, ptr(d_q), ptr(d_k), ptr(d_v), as<float>(d_gate), ptr(ws), ws.numel(),
-                                                   stream_of(stream)));
+                                                   call.stream()));
   return {d_q, d_k, d_v, d_gate};
 }
 
 std::tuple<Tensor, Tensor> varlen_attn_fwd(const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& cu_q, const Tensor& cu_k,
                                            double scale, const OptStream& stream) {
   require(qh, kh, vh, cu_q, cu_k);
+  const Call call(stream);
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
-  Tensor oh = make({H, Nq, D}, qh), lse = make({H, Nq}, qh, at::kFloat);
-  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_FWD, Nq, Nk, H, D, G, qh, stream);
+  Tensor oh = call.make({H, Nq, D}, qh), lse = call.make({H, Nq}, qh, at::kFloat);
+  OptTensor ws = call.attn_workspace(MOGA_OP_VARLEN_ATTN_FWD, Nq, Nk, H, D, G, qh);
   check("moga_varlen_attn_fwd", moga_varlen_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), Nq, Nk, (int)H, (int)D, as<int32_t>(cu_q),
                                                      as<int32_t>(cu_k), (int)G, (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws),
-                                                     stream_of(stream)));
+                                                     call.stream()));
   return {oh, lse};
 }
 
@@ -247,56 +281,61 @@ std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd(const Tensor& d_oh, const Ten
                                                    const Tensor& lse, const Tensor& cu_q, const Tensor& cu_k, double scale,
                                                    const OptStream& stream) {
   require(d_oh, qh, kh, vh, oh, lse, cu_q, cu_k);
+  const Call call(stream);
   need_dims(qh, 3);
   const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
-  Tensor d_qh = make({H, Nq, D}, qh), d_kh = make(kh.sizes(), kh), d_vh = make(vh.sizes(), vh);
-  OptTensor ws = attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, Nq, Nk, H, D, G, qh, stream);
+  Tensor d_qh = call.make({H, Nq, D}, qh), d_kh = call.make(kh.sizes(), kh), d_vh = call.make(vh.sizes(), vh);
+  OptTensor ws = call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, Nq, Nk, H, D, G, qh);
   check("moga_varlen_attn_bwd", moga_varlen_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), Nq, Nk, (int)H,
                                                      (int)D, as<int32_t>(cu_q), as<int32_t>(cu_k), (int)G, (float)scale, ptr(d_qh),
-                                                     ptr(d_kh), ptr(d_vh), ptr(ws), bytes_of(ws), stream_of(stream)));
+                                                     ptr(d_kh), ptr(d_vh), ptr(ws), bytes_of(ws), call.stream()));
   return {d_qh, d_kh, d_vh};
 }
 
 Tensor gather_rows(const Tensor& src, const Tensor& index, const OptStream& stream) {
   require(src, index);
+  const Call call(stream);
   need_dims(src, 3);
   const int64_t H = src.size(1), D = src.size(2), Nk = index.size(0);
-  Tensor dst = make({H, Nk, D}, src);
-  check("moga_gather_rows", moga_gather_rows(ptr(src), dt(src), as<int32_t>(index), Nk, (int)H, (int)D, ptr(dst), stream_of(stream)));
+  Tensor dst = call.make({H, Nk, D}, src);
+  check("moga_gather_rows", moga_gather_rows(ptr(src), dt(src), as<int32_t>(index), Nk, (int)H, (int)D, ptr(dst), call.stream()));
   return dst;
 }
 
 Tensor gather_rows_bwd(const Tensor& d_dst, const Tensor& inv_cu, const Tensor& inv_slots, int64_t N, const OptTensor& into,
                        const OptStream& stream) {
   require(d_dst, inv_cu, inv_slots, into);
+  const Call call(stream);
   need_dims(d_dst, 3);
   const int64_t H = d_dst.size(0), Nk = d_dst.size(1), D = d_dst.size(2);
-  Tensor d_src = into ? *into : make({N, H, D}, d_dst);
+  Tensor d_src = into ? *into : call.make({N, H, D}, d_dst);
   check("moga_gather_rows_bwd", moga_gather_rows_bwd(ptr(d_dst), dt(d_dst), as<int32_t>(inv_cu), as<int32_t>(inv_slots), N, Nk, (int)H, (int)D,
-                                                     into ? 1 : 0, ptr(d_src), stream_of(stream)));
+                                                     into ? 1 : 0, ptr(d_src), call.stream()));
   return d_src;
 }
 
 Tensor gather3_bwd(const Tensor& g_moga, const Tensor& inv_moga, const Tensor& g_stga, const Tensor& inv_cu, const Tensor& inv_slots,
                    const Tensor& g_frame, const OptTensor& inv_frame, const OptStream& stream) {
   require(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame);
+  const Call call(stream);
   need_dims(g_moga, 3);
   const int64_t H = g_moga.size(0), N = g_moga.size(1), D = g_moga.size(2), Nk = g_stga.size(1);
-  Tensor d_src = make({N, H, D}, g_moga);
+  Tensor d_src = call.make({N, H, D}, g_moga);
   check("moga_gather3_bwd", moga_gather3_bwd(ptr(g_moga), as<int32_t>(inv_moga), ptr(g_stga), as<int32_t>(inv_cu), as<int32_t>(inv_slots), Nk,
                                              ptr(g_frame), as<int32_t>(inv_frame), dt(g_moga), N, (int)H, (int)D, ptr(d_src),
-                                             stream_of(stream)));
+                                             call.stream()));
   return d_src;
 }
 
 Tensor merge3_fwd(const Tensor& a_moga, const Tensor& a_stga, const Tensor& a_frame, const OptTensor& inv_moga, const OptTensor& inv_stga,
                   const OptTensor& inv_frame, const Tensor& gate, const OptStream& stream) {
   require(a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate);
+  const Call call(stream);
   need_dims(a_moga, 3);
   const int64_t H = a_moga.size(0), N = a_moga.size(1), D = a_moga.size(2);
-  Tensor o = make({N, H, D}, a_moga);
+  Tensor o = call.make({N, H, D}, a_moga);
   check("moga_merge3_fwd", moga_merge3_fwd(ptr(a_moga), ptr(a_stga), ptr(a_frame), dt(a_moga), as<int32_t>(inv_moga), as<int32_t>(inv_stga),
-                                           as<int32_t>(inv_frame), as<float>(gate), N, (int)H, (int)D, ptr(o), stream_of(stream)));
+                                           as<int32_t>(inv_frame), as<float>(gate), N, (int)H, (int)D, ptr(o), call.stream()));
   return o;
 }
 
@@ -304,12 +343,13 @@ std::tuple<Tensor, Tensor, Tensor, Tensor> merge3_bwd(const Tensor& d_o, const T
                                                       const OptTensor& inv_stga, const OptTensor& inv_frame, const Tensor& gate,
                                                       const OptStream& stream) {
   require(d_o, a_moga, inv_moga, inv_stga, inv_frame, gate);
+  const Call call(stream);
   need_dims(d_o, 3);
   const int64_t N = d_o.size(0), H = d_o.size(1), D = d_o.size(2);
-  Tensor d_m = make({H, N, D}, d_o), d_s = make({H, N, D}, d_o), d_f = make({H, N, D}, d_o), d_gate = make({N}, d_o, at::kFloat);
+  Tensor d_m = call.make({H, N, D}, d_o), d_s = call.make({H, N, D}, d_o), d_f = call.make({H, N, D}, d_o), d_gate = call.make({N}, d_o, at::kFloat);
   check("moga_merge3_bwd", moga_merge3_bwd(ptr(d_o), ptr(a_moga), dt(d_o), as<int32_t>(inv_moga), as<int32_t>(inv_stga), as<int32_t>(inv_frame),
                                            as<float>(gate), N, (int)H, (int)D, ptr(d_m), ptr(d_s), ptr(d_f), as<float>(d_gate),
-                                           stream_of(stream)));
+                                           call.stream()));
   return {d_m, d_s, d_f, d_gate};
 }
 
@@ -317,16 +357,18 @@ std::tuple<Tensor, Tensor, Tensor, Tensor> merge3_bwd(const Tensor& d_o, const T
 std::tuple<Tensor, Tensor> balance_into(const Tensor& loss, const Tensor& group, const Tensor& gate, int64_t M, double alpha,
                                         const OptStream& stream) {
   require(loss, group, gate);
+  const Call call(stream);
   const int64_t N = group.size(0);
-  Tensor frac = make({M}, group, at::kFloat), prob = make({M}, group, at::kFloat);
-  Tensor ws = workspace(moga_workspace_bytes(MOGA_OP_BALANCE_LOSS, N, 0, 0, (int)M, 0, MOGA_F32), group);
+  Tensor frac = call.make({M}, group, at::kFloat), prob = call.make({M}, group, at::kFloat);
+  Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_BALANCE_LOSS, N, 0, 0, (int)M, 0, MOGA_F32), group);
   check("moga_balance_loss", moga_balance_loss(as<int32_t>(group), as<float>(gate), N, (int)M, (float)alpha, as<float>(loss), as<float>(frac),
-                                               as<float>(prob), ptr(ws), ws.numel(), stream_of(stream)));
+                                               as<float>(prob), ptr(ws), ws.numel(), call.stream()));
   return {frac, prob};
 }
 
 std::tuple<Tensor, Tensor, Tensor> balance_loss(const Tensor& group, const Tensor& gate, int64_t M, double alpha, const OptStream& stream) {
-  Tensor loss = make({1}, group, at::kFloat);
+  require(group, gate);
+  Tensor loss = Call(stream).make({1}, group, at::kFloat);
   auto [frac, prob] = balance_into(loss, group, gate, M, alpha, stream);
   return {loss, frac, prob};
 }
@@ -334,12 +376,17 @@ std::tuple<Tensor, Tensor, Tensor> balance_loss(const Tensor& group, const Tenso
 Tensor balance_loss_bwd(const Tensor& group, const Tensor& frac, double alpha, double d_loss, const OptTensor& d_loss_dev,
                         const OptTensor& into, const OptStream& stream) {
   require(group, frac, into);
+  const Call call(stream);
   const int64_t N = group.size(0), M = frac.size(0);
-  Tensor d_gate = into ? *into : make({N}, group, at::kFloat);
+  Tensor d_gate = into ? *into : call.make({N}, group, at::kFloat);
   OptTensor dev;
-  if (d_loss_dev) dev = d_loss_dev->reshape({1}).to(at::kFloat);
+  if (d_loss_dev) {   // a conversion runs in order with the kernel that reads it
+    c10::OptionalStreamGuard guard;
+    if (call.other()) guard.reset_stream(*call.other());
+    dev = d_loss_dev->reshape({1}).to(at::kFloat);
+  }
   check("moga_balance_loss_bwd", moga_balance_loss_bwd(as<int32_t>(group), as<float>(frac), N, (int)M, (float)alpha, (float)d_loss,
-                                                       as<float>(dev), into ? 1 : 0, as<float>(d_gate), stream_of(stream)));
+                                                       as<float>(dev), into ? 1 : 0, as<float>(d_gate), call.stream()));
   return d_gate;
 }
 
@@ -354,7 +401,7 @@ struct Attention : public torch::autograd::Function<Attention> {
     Tensor o = unpermute(oh, p.perm, gate, std::nullopt, std::nullopt);
     Tensor loss, frac;
     if (alpha) {
-      loss = make({}, x, at::kFloat);
+      loss = at::empty({}, x.options().dtype(at::kFloat));
       frac = std::get<0>(balance_into(loss, group, gate, M, *alpha, std::nullopt));
     } else {
       loss = at::zeros({}, x.options().dtype(at::kFloat));
