@@ -68,7 +68,9 @@ size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model,
 /*
  * Bytes with which the call runs fastest (>= moga_workspace_bytes; Nk = number of key rows, N for MoGA's own calls).  The
  * bf16 attention calls with a few rounds of long blocks use room past what they need to split the last round
- * (34 MB).  moga_group_attn_fwd, which needs none, uses it too.  Host-only.
+ * (34 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd and the moga_varlen_* calls.  A split row is
+ * summed in pieces, so its rounding differs from that of a call with less room: results repeat bit by bit between calls
+ * that both have these bytes, or both less.  Host-only.
  */
 size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, int H, int D, int M, int d_model, int dtype);
 
@@ -138,6 +140,12 @@ int moga_group_attn_fwd(const void* qh, const void* kh, const void* vh, int dtyp
                         int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
                         float softmax_scale, void* oh, float* lse,
                         void* ws, size_t ws_bytes, void* stream);
+/* The same with the workspace in use: moga_group_attn_fwd leaves `ws` alone, this call writes it when it has
+ * moga_workspace_preferred_bytes(MOGA_OP_ATTN_FWD, ...); with less (or NULL) the two are the same. */
+int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int dtype,
+                           int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                           float softmax_scale, void* oh, float* lse,
+                           void* ws, size_t ws_bytes, void* stream);
 
 /*
  * repermute of Alg. 1 with the gate of Eq. 5:

@@ -3,7 +3,8 @@
 // With P = exp(scale*S - lse) and delta = rowsum(dO * O):
 //   dV = P^T dO,  dP = dO V^T,  dS = P * (dP - delta),  dQ = scale dS K,  dK = scale dS^T Q.
 //
-// Three kernels, no atomics, results independent of scheduling:
+// Three kernels, no atomics; results do not depend on scheduling, only (in their rounding) on whether the workspace has room
+// to split the last round:
 //   attn_bwd_delta   : delta[h][j] = sum_c dO[h][j][c] * O[h][j][c]   (bf16)
 //   attn_bwd_dkdv    : a wave owns 32 key rows (K, V fragments and the dK^T, dV^T accumulators
 //                      live in registers) and sweeps the query tiles of its group;

@@ -84,10 +84,10 @@ static int check_attn_args(int64_t Nq, int64_t Nk, int H, int D, int M, float so
   return MOGA_OK;
 }
 
-extern "C" int moga_group_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype,
-                                   int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
-                                   float softmax_scale, void* oh, float* lse, void* ws,
-                                   size_t ws_bytes, void* stream) {
+extern "C" int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int dtype,
+                                      int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                                      float softmax_scale, void* oh, float* lse, void* ws,
+                                      size_t ws_bytes, void* stream) {
   const int bad = check_attn_args(N, N, H, D, M, softmax_scale, dtype);
   if (bad) return bad;
   if (M > MOGA_MAX_GROUPS) return MOGA_ERR_UNSUPPORTED;
@@ -96,6 +96,15 @@ extern "C" int moga_group_attn_fwd(const void* qh, const void* kh, const void* v
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
   return launch_attn_fwd(qh, kh, vh, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, M,
                          softmax_scale, oh, lse, split_region(ws, 0, ws_bytes), (hipStream_t)stream);
+}
+
+// Needs no workspace and touches none: a caller may pass one that other streams are using.
+extern "C" int moga_group_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype,
+                                   int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                                   float softmax_scale, void* oh, float* lse, void* ws,
+                                   size_t ws_bytes, void* stream) {
+  (void)ws; (void)ws_bytes;
+  return moga_group_attn_fwd_ws(qh, kh, vh, dtype, N, H, D, cu_seqlens, M, softmax_scale, oh, lse, nullptr, 0, stream);
 }
 
 extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, int dtype, int64_t N,

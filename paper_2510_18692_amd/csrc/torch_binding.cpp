@@ -87,7 +87,8 @@ class Call {
   Tensor workspace(size_t bytes, const Tensor& like) const { return make({std::max<int64_t>((int64_t)bytes, 16)}, like, at::kByte); }
 
   // Workspace of an attention call: what it runs fastest with if the device has it, else what it needs; on another stream
-  // than torch's current one no more than it needs.
+  // than torch's current one no more than it needs.  Without the room no last round is split, and the rounding of those
+  // rows differs (moga.h): a call that finds the device full gives its result all the same, not the same bits.
   OptTensor attn_workspace(int op, int64_t N, int64_t Nk, int64_t H, int64_t D, int64_t M, const Tensor& like) const {
     const size_t need = moga_workspace_bytes(op, N, (int)H, (int)D, (int)M, 0, dt(like));
     const size_t preferred = moga_workspace_preferred_bytes(op, N, Nk, (int)H, (int)D, (int)M, 0, dt(like));
@@ -165,8 +166,9 @@ std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, co
   Tensor oh = out ? *out : call.make({H, N, D}, qh);
   Tensor lse = lse_out ? *lse_out : call.make({H, N}, qh, at::kFloat);
   OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
-  check("moga_group_attn_fwd", moga_group_attn_fwd(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M,
-                                                   (float)scale, ptr(oh), as<float>(lse), ptr(ws), bytes_of(ws), call.stream()));
+  check("moga_group_attn_fwd",
+        moga_group_attn_fwd_ws(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(oh),
+                               as<float>(lse), ptr(ws), bytes_of(ws), call.stream()));
   return {oh, lse};
 }
 

@@ -138,3 +138,24 @@ def test_split_keeps_nan_and_infinities(what):
         assert torch.equal(a[torch.isinf(a)], b[torch.isinf(b)])
         fin = torch.isfinite(a)
         close(b[fin], a[fin], what)
+
+
+def test_forward_without_ws_leaves_the_workspace_alone():
+    """moga_group_attn_fwd needs no workspace: what a caller passes all the same may be in use on other streams."""
+    N, H, s = 6000, 4, 128 ** -0.5
+    g = torch.Generator().manual_seed(1)
+    q, k, v = (torch.randn((H, N, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    cu = torch.tensor([0, N], dtype=torch.int32, device="cuda")
+    lib, stream = mg.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    mg.set_small_group_rows(0)
+    try:
+        size = lib.moga_workspace_preferred_bytes(mg.OP_ATTN_FWD, N, N, H, 128, 1, 0, mg.MOGA_BF16)
+        used = []
+        for fn in (lib.moga_group_attn_fwd, lib.moga_group_attn_fwd_ws):
+            ws, oh, lse = torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda"), torch.empty_like(q), torch.empty((H, N), device="cuda")
+            assert fn(p(q), p(k), p(v), mg.MOGA_BF16, N, H, 128, p(cu), 1, s, p(oh), p(lse), p(ws), size, stream) == 0
+            used.append(bool((ws != 0x5A).any()))
+        torch.cuda.synchronize()
+    finally:
+        mg.set_small_group_rows(-1)
+    assert used == [False, True]
