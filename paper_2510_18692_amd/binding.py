@@ -10,13 +10,15 @@ ctypes.  There is no fallback: if a library cannot be loaded the first call rais
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
+import threading
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmoga.so")
-NATIVE_PATH = os.path.join(_HERE, "_moga_torch.so")
 
 MOGA_F32, MOGA_BF16 = 0, 1
 (OP_ROUTE, OP_PERMUTE, OP_ATTN_FWD, OP_ATTN_BWD, OP_ROUTE_BWD, OP_BALANCE_LOSS, OP_VARLEN_ATTN_FWD,
@@ -105,18 +107,32 @@ def workspace_bytes(op, N, H, D, M, d_model, dtype) -> int:
     return int(load().moga_workspace_bytes(op, N, H, D, M, d_model, dtype))
 
 
+_nat_lock = threading.Lock()
+
+
+def _load_native():
+    """The native module for this torch (building it first only if none is there)."""
+    from . import build as _build
+    load()
+    path = _build.native_path()
+    if not os.path.exists(path):
+        _build.build_native()
+    name = __package__ + "._moga_torch"
+    spec = importlib.util.spec_from_file_location(name, path, loader=importlib.machinery.ExtensionFileLoader(name, path))
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module
+
+
 class _LazyNative:
-    """Stands in for the native module until its first use (building the libraries only if none is there)."""
+    """Stands in for the native module until its first use."""
 
     def __getattr__(self, name):
         global _nat
-        load()
-        if not os.path.exists(NATIVE_PATH):
-            from . import build as _build
-            _build.build()
-        from . import _moga_torch
-        _nat = _moga_torch
-        return getattr(_moga_torch, name)
+        with _nat_lock:
+            if _nat is self:
+                _nat = _load_native()
+        return getattr(_nat, name)
 
 
 _nat = _LazyNative()

@@ -2,15 +2,16 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoga.so")
-NATIVE = os.path.join(HERE, "_moga_torch.so")          # native half of the Python binding
 BENCH_LIB = os.path.join(HERE, "libmoga_bench.so")   # peak microbenchmarks for bench.py only
 EXAMPLE = os.path.join(HERE, "c_abi_example")
 SOURCES = ["api.hip", "route.hip", "permute.hip", "attn_fwd.hip", "attn_bwd.hip", "balance.hip", "static_index.hip"]
@@ -29,20 +30,30 @@ def _hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def _build_native() -> None:
-    """Host code only: the torch binding of the C ABI, against this interpreter's torch."""
-    import sysconfig
+def native_path() -> str:
+    """The native half of the Python binding.  It follows the ABI of one torch and one interpreter: the name says which,
+    so that another one in the same tree gets a file of its own."""
+    import torch
+    tag = re.sub(r"[^A-Za-z0-9.]+", "_", f"{torch.__version__}-{sysconfig.get_config_var('SOABI')}")
+    return os.path.join(HERE, f"_moga_torch-{tag}.so")
 
+
+def build_native() -> str:
+    """Host code only (g++ and torch's headers): the torch binding of the C ABI, against this interpreter's torch."""
     import torch
     from torch.utils import cpp_extension as ext
+    path = native_path()
+    tmp = f"{path}.{os.getpid()}"   # processes that find it missing at the same time each move a whole file into place
     inc = [ROOT + "/include", *ext.include_paths("cuda"), sysconfig.get_paths()["include"]]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-DTORCH_EXTENSION_NAME=_moga_torch", "-D__HIP_PLATFORM_AMD__=1",
            "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(x for i in inc for x in ("-isystem", i)),
-           os.path.join(CSRC, "torch_binding.cpp"), "-o", NATIVE, "-L", HERE, "-lmoga", "-Wl,-rpath,$ORIGIN",
+           os.path.join(CSRC, "torch_binding.cpp"), "-o", tmp, "-L", HERE, "-lmoga", "-Wl,-rpath,$ORIGIN",
            *(x for p in ext.library_paths("cuda") for x in ("-L", p)), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("native binding build failed:\n" + r.stdout + r.stderr)
+    os.replace(tmp, path)
+    return path
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
@@ -69,7 +80,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
-    _build_native()
+    build_native()
     # the two peak microbenchmarks bench.py reports beside the published peaks (a library of their own)
     r = subprocess.run([hipcc, *FLAGS, *extra_flags, "-shared", os.path.join(CSRC, "bench_peaks.hip"),
                         "-o", BENCH_LIB], capture_output=True, text=True)

@@ -1,10 +1,13 @@
 """The native half of the binding: errors reach Python as before (CPU), and the native autograd function handles
 outputs that do not take part in the loss (GPU)."""
+import os
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2510_18692_amd import binding as mg
+from paper_2510_18692_amd import build
 from paper_2510_18692_amd import workloads as wl
 from paper_2510_18692_amd.autograd import moga_attention
 
@@ -15,6 +18,28 @@ def test_host_tensors_are_refused():
         mg.moga_route(x, w)
     with pytest.raises(AssertionError):
         mg.moga_permute(torch.zeros(8, dtype=torch.int32), 4)
+
+
+def test_native_module_belongs_to_one_torch(monkeypatch):
+    """Another torch in the same tree does not load the module built for this one: it asks for a build of its own."""
+    path = build.native_path()
+    mg._load_native()
+    assert os.path.exists(path)
+    built = []
+
+    class Asked(Exception):
+        pass
+
+    def no_compiler():
+        built.append(build.native_path())
+        raise Asked
+
+    monkeypatch.setattr(build, "build_native", no_compiler)
+    mg._load_native()   # there already
+    monkeypatch.setattr(torch, "__version__", "0.0.1+other")
+    with pytest.raises(Asked):
+        mg._load_native()
+    assert built and built[0] != path
 
 
 @pytest.mark.gpu
