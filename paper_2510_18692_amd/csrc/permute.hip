@@ -190,8 +190,9 @@ __global__ __launch_bounds__(1024) void permute_single_block_kernel(const int32_
                                                                     int32_t* __restrict__ perm,
                                                                     int32_t* __restrict__ inv_perm) {
   constexpr int CAP = 1024 * PER, W = PER / 4;
-  __shared__ unsigned short s_cnt[kSingleBlockGroups][1024];
-  __shared__ unsigned char s_id[CAP];
+  typedef unsigned __attribute__((may_alias)) word_t;   // four ids, or two counters, at once
+  __shared__ __attribute__((aligned(16))) unsigned short s_cnt[kSingleBlockGroups][1024];
+  __shared__ __attribute__((aligned(16))) unsigned char s_id[CAP];
   __shared__ unsigned short s_perm[CAP], s_inv[CAP];
   __shared__ int s_count[kSingleBlockGroups];
   __shared__ int s_cu[kSingleBlockGroups];
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(1024) void permute_single_block_kernel(const int32_
   __syncthreads();
   unsigned id[W];
 #pragma unroll
-  for (int w = 0; w < W; ++w) id[w] = ((const unsigned*)s_id)[tid * W + w];
+  for (int w = 0; w < W; ++w) id[w] = ((const word_t*)s_id)[tid * W + w];
   int pos[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(1024) void permute_single_block_kernel(const int32_
   }
   __syncthreads();
   for (int j = wave; j < M; j += 16) {   // counters of group j -> exclusive sums over the threads
-    unsigned* p = (unsigned*)&s_cnt[j][16 * lane];
+    word_t* p = (word_t*)&s_cnt[j][16 * lane];
     unsigned c[8];
     int sum = 0;
 #pragma unroll
