@@ -81,3 +81,24 @@ def test_autograd_with_unused_outputs(use):
     torch.cuda.synchronize()
     for k, r in ref.items():
         assert np.array_equal(t[k].grad.cpu().numpy(), r.cpu().numpy()), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("grad_x", [False, True])
+def test_autograd_without_the_balancing_loss(grad_x):
+    w = wl.scaled(wl.WORKLOADS["C1b"], N=300)
+    inp = wl.make_inputs(w, "cuda")
+    t = {k: inp[k].clone().requires_grad_() for k in ("X", "W", "Q", "K", "V")}
+    o, loss, group = moga_attention(t["X"], t["W"], t["Q"], t["K"], t["V"], w.scale, grad_x=grad_x)
+    assert loss is None and not group.requires_grad
+    (o * inp["dO"]).sum().backward()
+    f = mg.moga_forward(inp["X"], inp["W"], inp["Q"], inp["K"], inp["V"], w.scale)
+    b = mg.moga_backward(f, inp["X"], inp["W"], inp["dO"], w.scale, want_dx=grad_x)
+    torch.cuda.synchronize()
+    assert torch.equal(o, f["o"]) and torch.equal(group, f["group"])
+    for k, r in (("W", "d_w"), ("Q", "d_q"), ("K", "d_k"), ("V", "d_v")):
+        assert torch.equal(t[k].grad, b[r]), k
+    if grad_x:
+        assert torch.equal(t["X"].grad, b["d_x"].to(t["X"].dtype))
+    else:
+        assert t["X"].grad is None
