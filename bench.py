@@ -122,7 +122,7 @@ def measured_peaks(torch):
     gb = best(lambda: lib.moga_bench_copy(dst.data_ptr(), src.data_ptr(), src.numel(), st)) / 1e9
     del sink, src, dst
     return {"mfma_bf16_tflops": round(tf, 1), "hbm_copy_gbs": round(gb, 1),
-            "how": "register-resident 32x32x16 bf16 MFMA loop (1024 blocks x 4 waves); plain 1 GiB copy kernel"}
+            "how": "register-resident 16x16x32 bf16 MFMA loop (1024 blocks x 4 waves); plain 1 GiB copy kernel"}
 
 
 def cpu_baseline(w, inp, budget_s=20.0):

@@ -6,10 +6,10 @@
 // common maximum).  Full precision is used at a few thousand tokens: 4,096 tokens x 2 heads are only
 // 256 such blocks, and the earlier kernels (one thread per row, plain FMAs against rows broadcast from
 // LDS) kept 128 one-wave blocks busy for as long as one lane takes for a whole row.  Measured, before
-// and after, forward / backward in us: 4,096 x 2 x 64, 8 groups 341 / 1143 and 20 / 57; 8,192 x 4 x
-// 128, 2 groups 9,133 / 36,215 and 717 / 2,304 (96 / 75 TFLOP/s of the 157 that the instruction has).
-// Bound by the matrix instruction at large groups, by the latency of a few dependent steps at small
-// ones.  Two waves per SIMD: with one (more registers, D = 128) the large forward took 889 us.
+// and after, forward / backward in us: 4,096 x 2 x 64, 8 groups of 512 341 / 1143 and 17.5 / 51; 8,192 x 4 x
+// 128, 2 groups 9,133 / 36,215 and 692 / 2,180 (99 / 79 TFLOP/s of the 157 that the instruction has).
+// Bound by the matrix instruction at large groups, at small ones by the latency of a few dependent steps and by
+// the CUs that get a block more than others (8 groups of 480 to 534 make 262 blocks on 256 CUs: 33 / 93).  Two waves per SIMD: with one (more registers, D = 128) the large forward took 889 us.
 //
 // Operand layout (lane = (r, h), r = lane % 32, h = lane / 32):
 //   * first products (scores): streamed rows are the A operand, one row per lane, stationary rows

@@ -1,15 +1,16 @@
 // Two microbenchmarks that measure what this GPU delivers, built into libmoga_bench.so (not part
 // of libmoga.so and not declared in moga.h): bench.py times them with HIP events and reports the
 // results next to the published peaks as a second denominator.
-//   moga_bench_mfma_loop : every wave issues 32x32x16 bf16 MFMAs whose operands and accumulators
+//   moga_bench_mfma_loop : every wave issues 16x16x32 bf16 MFMAs (the attention kernels' instruction) in
+//                          pairs that share their A operand, as there; operands and accumulators
 //                          never leave the registers (no LDS, no memory): the matrix-core rate the
 //                          chip sustains under its own power and clock management.
 //   moga_bench_copy      : a plain device-to-device copy, 16 bytes per lane: the HBM rate a
 //                          streaming kernel can reach.
-//   moga_bench_mix_loop  : the MFMA loop with two waves per SIMD and, per MFMA, a chosen number of
+//   moga_bench_mix_loop  : the MFMA loop with two waves per SIMD and, per pair, a chosen number of
 //                          1 KB LDS fragment reads, fp32 fmas and exp2s on random or all-zero data.
 //                          Run at the board's power limit, the rate it sustains prices each extra
-//                          in units of the energy of one MFMA (python -m paper_2510_18692_amd.profiling energy).
+//                          in units of the energy of one pair (python -m paper_2510_18692_amd.profiling energy).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -18,7 +19,7 @@ namespace moga_bench {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int uintx4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ unsigned int hash32(unsigned int x) {
@@ -40,34 +41,41 @@ __device__ __forceinline__ bf16x8_t random_fragment(unsigned int key) {
   return __builtin_bit_cast(bf16x8_t, u);
 }
 
-constexpr int kAcc = 8;   // independent accumulators per wave (128 registers)
+constexpr int kPairs = 8;   // pairs of products per iteration, with 8 A and 8 B fragments
+constexpr double kPairFlops = 2.0 * 2 * 16 * 16 * 32;
 
-__global__ __launch_bounds__(256) void mfma_loop_kernel(int iters, float* __restrict__ sink) {
-  bf16x8_t a[kAcc], b[kAcc];
-  floatx16_t acc[kAcc];
+__device__ __forceinline__ void mfma_pair(floatx4_t (&acc)[2], bf16x8_t a, bf16x8_t b0, bf16x8_t b1) {
+  acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, acc[0], 0, 0, 0);
+  acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, acc[1], 0, 0, 0);
+}
+
+// Two blocks per CU at least: with all 512 registers the compiler copies accumulators inside the loop (1.74 PFLOP/s).
+__global__ __launch_bounds__(256, 2) void mfma_loop_kernel(int iters, float* __restrict__ sink) {
+  bf16x8_t a[kPairs], b[kPairs];
+  floatx4_t acc[kPairs][2];
   const unsigned int id = blockIdx.x * 256u + threadIdx.x;
 #pragma unroll
-  for (int j = 0; j < kAcc; ++j) {
+  for (int j = 0; j < kPairs; ++j) {
     a[j] = random_fragment(id * 16u + j);
     b[j] = random_fragment(id * 16u + 8u + j);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    for (int v = 0; v < 8; ++v) acc[j][v >> 2][v & 3] = 0.f;
   }
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int j = 0; j < kAcc; ++j)
-      acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j], b[(j + 3) & (kAcc - 1)], acc[j], 0, 0, 0);
+    for (int j = 0; j < kPairs; ++j)
+      mfma_pair(acc[j], a[j], b[(j + 3) & (kPairs - 1)], b[(j + 4) & (kPairs - 1)]);
   }
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < kAcc; ++j)
+  for (int j = 0; j < kPairs; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s += acc[j][v];
+    for (int v = 0; v < 8; ++v) s += acc[j][v >> 2][v & 3];
   if (s == 12345.678f) sink[id] = s;   // keeps the loop alive; practically never taken
 }
 
 // A operands come from LDS when NL >= 1 (B operands too when NL == 2): 16 bytes per lane, a different
-// conflict-free 1 KB row each time, loaded six MFMAs before their use.  NF fmas and NE exp2s per MFMA keep
+// conflict-free 1 KB row each time, loaded six pairs before their use.  NF fmas and NE exp2s per pair keep
 // 16 values per lane bounded.  zero != 0 clears every operand (same instruction stream, no toggling).
 template <int NL, int NF, int NE>
 __global__ __launch_bounds__(512) void mix_loop_kernel(int iters, int zero, float* __restrict__ sink) {
@@ -76,32 +84,32 @@ __global__ __launch_bounds__(512) void mix_loop_kernel(int iters, int zero, floa
   for (int i = threadIdx.x; i < 4096; i += 512)
     rows[i] = zero ? uintx4_t{0u, 0u, 0u, 0u} : __builtin_bit_cast(uintx4_t, random_fragment(0x40000000u + i));
   __syncthreads();
-  bf16x8_t a[kAcc], b[kAcc];
-  floatx16_t acc[4];
+  bf16x8_t a[kPairs], b[kPairs];
+  floatx4_t acc[kPairs][2];
 #pragma unroll
-  for (int j = 0; j < kAcc; ++j) {
+  for (int j = 0; j < kPairs; ++j) {
     a[j] = random_fragment(id * 16u + j);
     b[j] = random_fragment(id * 16u + 8u + j);
     if (zero) { a[j] = __builtin_bit_cast(bf16x8_t, uintx4_t{0u, 0u, 0u, 0u}); b[j] = a[j]; }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < kPairs; ++j)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    for (int v = 0; v < 8; ++v) acc[j][v >> 2][v & 3] = 0.f;
   float x[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) x[j] = zero ? 0.f : (float)(hash32(id * 16u + j) & 0xffffu) * (1.f / 65536.f) - 0.5f;
   const float fa = zero ? 0.f : -0.9990234f, fb = zero ? 0.f : 0.37f;
-  const unsigned int lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  unsigned int first = (threadIdx.x >> 6) * 6u * 64u + (threadIdx.x & 63u);   // a wave's rows: 6 per wave apart, 16 at most
   for (int it = 0; it < iters; ++it) {
+    asm volatile("" : "+v"(first));   // read again in every iteration, at immediate offsets
 #pragma unroll
-    for (int m = 0; m < kAcc; ++m) {
-      acc[m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[(m + 3) & (kAcc - 1)], acc[m & 3], 0, 0, 0);
+    for (int m = 0; m < kPairs; ++m) {
+      mfma_pair(acc[m], a[m], b[(m + 3) & (kPairs - 1)], b[(m + 4) & (kPairs - 1)]);
 #pragma unroll
       for (int t = 0; t < NL; ++t) {
-        const unsigned int row = (unsigned int)(it * kAcc * NL + m * NL + t + wave * 7) & 63u;
-        const bf16x8_t f = __builtin_bit_cast(bf16x8_t, rows[row * 64u + lane]);
-        if (t == 0) a[(m + 6) & (kAcc - 1)] = f; else b[(m + 1) & (kAcc - 1)] = f;
+        const bf16x8_t f = __builtin_bit_cast(bf16x8_t, rows[first + (m * NL + t) * 64u]);
+        if (t == 0) a[(m + 6) & (kPairs - 1)] = f; else b[(m + 1) & (kPairs - 1)] = f;
       }
 #pragma unroll
       for (int t = 0; t < NF; ++t) x[(m * NF + t) & 15] = __builtin_fmaf(x[(m * NF + t) & 15], fa, fb);
@@ -111,11 +119,11 @@ __global__ __launch_bounds__(512) void mix_loop_kernel(int iters, int zero, floa
   }
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    s += x[j];
+  for (int j = 0; j < 16; ++j) s += x[j];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) s += acc[q][j];
-  }
+  for (int j = 0; j < kPairs; ++j)
+#pragma unroll
+    for (int v = 0; v < 8; ++v) s += acc[j][v >> 2][v & 3];
   if (s == 12345.678f) sink[id] = s;   // keeps the loop alive; practically never taken
 }
 
@@ -137,17 +145,17 @@ __global__ __launch_bounds__(256) void copy_kernel(uintx4_t* __restrict__ dst, c
 
 using namespace moga_bench;
 
-// Launches `blocks` blocks of 4 waves, each wave issuing iters * 8 MFMAs; returns the FLOPs of the
-// launch (2 * 32 * 32 * 16 per MFMA) or -1 on a bad argument / failed launch.  sink: device, >= blocks * 256 floats.
+// Launches `blocks` blocks of 4 waves, each wave issuing iters * 8 pairs of MFMAs; returns the FLOPs of the
+// launch (2 * 2 * 16 * 16 * 32 per pair) or -1 on a bad argument / failed launch.  sink: device, >= blocks * 256 floats.
 extern "C" double moga_bench_mfma_loop(int blocks, int iters, float* sink, void* stream) {
   if (blocks < 1 || iters < 1 || !sink) return -1.0;
   mfma_loop_kernel<<<blocks, 256, 0, (hipStream_t)stream>>>(iters, sink);
   if (hipGetLastError() != hipSuccess) return -1.0;
-  return (double)blocks * 4.0 * (double)iters * kAcc * 32768.0;
+  return (double)blocks * 4.0 * (double)iters * kPairs * kPairFlops;
 }
 
-// One launch of the mixed loop: `blocks` blocks of 8 waves (two per SIMD), each wave issuing iters * 8 MFMAs
-// plus, per MFMA, lds_reads (0..2) fragment reads, fmas (0, 2, 4 or 6) and exps (0..2); the combinations
+// One launch of the mixed loop: `blocks` blocks of 8 waves (two per SIMD), each wave issuing iters * 8 pairs
+// of MFMAs plus, per pair, lds_reads (0..2) fragment reads, fmas (0, 2, 4 or 6) and exps (0..2); the combinations
 // built are the ones listed below.  Returns the MFMA FLOPs of the launch, or -1 for a bad argument, a
 // combination that is not built, or a failed launch.  sink: device, >= blocks * 512 floats.
 extern "C" double moga_bench_mix_loop(int lds_reads, int fmas, int exps, int blocks, int iters, int zero, float* sink,
@@ -166,7 +174,7 @@ extern "C" double moga_bench_mix_loop(int lds_reads, int fmas, int exps, int blo
   }
 #undef MOGA_MIX
   if (hipGetLastError() != hipSuccess) return -1.0;
-  return (double)blocks * 8.0 * (double)iters * kAcc * 32768.0;
+  return (double)blocks * 8.0 * (double)iters * kPairs * kPairFlops;
 }
 
 // Copies `bytes` (a multiple of 16, both pointers 16-byte aligned) from src to dst; returns the bytes

@@ -31,8 +31,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _KERNEL_CALL = [
     ("route_mfma", "moga_route"), ("route_generic", "moga_route"),
     ("chunk_hist", "moga_permute"), ("chunk_scan", "moga_permute"), ("chunk_rank", "moga_permute"),
-    ("gather_rows_kernel", "moga_permute"),
-    ("attn_fwd", "moga_group_attn_fwd"),
+    ("permute_single_block", "moga_permute"), ("gather_rows_kernel", "moga_permute"),
+    ("attn_fwd", "moga_group_attn_fwd"), ("split_fwd", "moga_group_attn_fwd"), ("split_sum", "moga_group_attn_bwd"),
     ("unpermute_bwd", "moga_unpermute_bwd"),
     ("attn_bwd", "moga_group_attn_bwd"),
     ("route_bwd", "moga_route_bwd"),
@@ -377,13 +377,13 @@ at the rate reported above: that rate, not 2.5 PFLOP/s, is what bf16 matrix work
     print(txt)
 
 
-# (LDS fragment reads, fmas, exp2s) per MFMA: the combinations libmoga_bench.so builds
+# (LDS fragment reads, fmas, exp2s) per pair of MFMAs: the combinations libmoga_bench.so builds
 _ENERGY_VARIANTS = [(0, 0, 0), (1, 0, 0), (2, 0, 0), (0, 2, 0), (0, 4, 0), (0, 6, 0), (0, 0, 1), (0, 0, 2), (1, 4, 1)]
 
 
 def write_energy(args):
     """Runs the mixed MFMA loop of libmoga_bench.so at the board's power limit and prices an LDS fragment
-    read, an fma and an exp2 in units of the energy of one MFMA."""
+    read, an fma and an exp2 in units of the energy of one pair of MFMAs."""
     import ctypes
 
     import torch
@@ -434,29 +434,28 @@ def write_energy(args):
     lds1 = per_unit((0, 1, 0, 0), 1)
     fma1 = per_unit((0, 0, 6, 0), 6)
     exp1 = per_unit((0, 0, 0, 2), 2)
-    txt = f"""# What an MFMA, an LDS fragment read, an fma and an exp2 cost at the board's power limit
+    txt = f"""# What a pair of MFMAs, an LDS fragment read, an fma and an exp2 cost at the board's power limit
 
 Command (from the repository root on one MI355X):
 
     python -m paper_2510_18692_amd.profiling energy --out profiles/mfma_energy_probe.md
 
 `moga_bench_mix_loop` (libmoga_bench.so): 256 blocks of 8 waves (two per SIMD), {reps} launches of {iters} iterations of
-8 register-resident 32x32x16 bf16 MFMAs per wave; per MFMA the stated number of 1 KB LDS fragment reads (16 bytes per
-lane, conflict-free, the fragment is the A or B operand six MFMAs later), fp32 fmas and exp2s.  Power: hwmon
+8 pairs of register-resident 16x16x32 bf16 MFMAs per wave (a pair shares its A operand, as in the attention kernels); per
+pair the stated number of 1 KB LDS fragment reads (16 bytes per
+lane, conflict-free, the fragment is the A or B operand six pairs later), fp32 fmas and exp2s.  Power: hwmon
 `power1_input` sampled every 10 ms during the launches (cap {cap} W, idle {idle} W).  "busy x GHz" = MFMA pipe cycles
 per SIMD per nanosecond (2.4 = every cycle of the top clock).  J/PFLOP = board power / MFMA rate.
 
-| operands | LDS reads / MFMA | fma / MFMA | exp2 / MFMA | MFMA TFLOP/s | busy x GHz | board W | J/PFLOP |
+| operands | LDS reads / pair | fma / pair | exp2 / pair | MFMA TFLOP/s | busy x GHz | board W | J/PFLOP |
 |---|---|---|---|---|---|---|---|
 """ + "\n".join(rows) + f"""
 
-On random operands every variant sits at the same board power: the power management trades clock for switching
-activity, so the rate is set by the energy per MFMA and its companions.  Differences against the plain loop
-({jpf(base):.0f} J/PFLOP): one 1 KB LDS fragment read per MFMA costs {lds1:.0f} J/PFLOP ({100 * lds1 / jpf(base):.0f} % of an MFMA), one fma
-{fma1:.0f} ({100 * fma1 / jpf(base):.1f} %), one exp2 {exp1:.0f} ({100 * exp1 / jpf(base):.1f} %).  The attention kernels read one 1 KB fragment per MFMA
-(32 rows per wave), evaluate about one exp2 and three to four other vector instructions per MFMA and keep the matrix
-pipes busy 57-69 % of the cycles; the sum of those prices plus the idle power over the longer run time is what separates
-their 1.15-1.3 PFLOP/s of executed MFMA work from the plain loop's rate.
+On random operands the power management trades clock for switching activity, so the rate is set by the energy per
+pair and its companions.  Differences against the plain loop
+({jpf(base):.0f} J/PFLOP): one 1 KB LDS fragment read per pair costs {lds1:.0f} J/PFLOP ({100 * lds1 / jpf(base):.0f} % of a pair), one fma
+{fma1:.0f} ({100 * fma1 / jpf(base):.1f} %), one exp2 {exp1:.0f} ({100 * exp1 / jpf(base):.1f} %).  The forward kernel reads one 1 KB fragment and evaluates one
+exp2 per pair (32 rows per wave).
 """
     open(args.out, "w").write(txt)
     print(txt)
