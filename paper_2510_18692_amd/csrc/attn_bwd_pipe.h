@@ -9,7 +9,7 @@
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both kernels also come as 4-wave blocks with a two-slot
 // ring (64 KB of LDS), two blocks per CU, for groups of a few thousand rows or less.
-// dQ is at the power cap like the forward; dK/dV, at 2.20-2.26 of 2.39 GHz with the matrix pipes busy 0.54 of the time, is
+// dQ is at the power cap like the forward; dK/dV, at 2.20-2.29 of 2.39 GHz with the matrix pipes busy 0.54 of the time, is
 // bound by issue and by the exchange of P.  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40
 // heads, 32 groups; 2.73 and 2.67 ms at 32,760 x 12, 8 groups.
 #pragma once

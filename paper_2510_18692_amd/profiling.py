@@ -370,7 +370,7 @@ Board power over the timed steps (hwmon sensor, `roofline.board_power` of the tw
 
 MFMA busy (cycles the matrix pipes are occupied / SIMD cycles) is a property of the instruction stream and is the
 same in both runs; what changes is the clock the power management grants.  On random data the kernels are held at
-1.7-2.0 GHz of the 2.4 GHz the chip reaches on zeros, and a loop of nothing but MFMAs on random operands is held
+a lower clock than the 2.4 GHz the chip reaches on zeros, and a loop of nothing but MFMAs on random operands is held
 at the rate reported above: that rate, not 2.5 PFLOP/s, is what bf16 matrix work can reach on this chip.
 """
     open(args.out, "w").write(txt)
