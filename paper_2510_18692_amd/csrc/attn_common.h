@@ -257,7 +257,7 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
 
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
 // column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a
-// register-resident loop of random operands reaches 1.94-2.18 PFLOP/s (box to box) with this shape and 1.83-1.86 with 32x32x16
+// register-resident loop of random operands reaches 1.94-2.18 PFLOP/s (card to card) with this shape and 1.83-1.86 with 32x32x16
 // (whose accumulators are read and written twice as often per product), and an A fragment from LDS still feeds 32
 // columns when a wave keeps two B fragments.
 __device__ __forceinline__ floatx4_t mfma16(bf16x8_t a, bf16x8_t b, floatx4_t c) {

@@ -64,7 +64,8 @@ size_t bytes_of(const OptTensor& ws) { return ws ? (size_t)ws->numel() : 0; }
 
 // The stream of a call and what is allocated for it.  Memory comes from the pool of torch's current stream.  Where the
 // kernels run on another stream, every tensor is recorded as used there: a workspace or an intermediate result is dropped on
-// the host while they may still run, and its memory must not go to the current stream before they are done.
+// the host while they may still run, and its memory must not go to the current stream before they are done.  (The stream must
+// outlive these tensors, as for Tensor.record_stream.)
 class Call {
  public:
   explicit Call(const OptStream& given) {
