@@ -263,6 +263,14 @@ __device__ __forceinline__ void load_columns(bf16x8_t (&f)[2][4], const unsigned
   }
 }
 
+// The fragments are in their registers: the compiler waits for their loads here and nowhere later.
+__device__ __forceinline__ void settle(bf16x8_t (&f)[2][4]) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(f[c][ks]));
+}
+
 struct PipeDma {
   const void* kbase;   // first K row of this head's group (wave-uniform)
   const void* vbase;
