@@ -68,7 +68,7 @@ size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model,
 /*
  * Bytes with which the call runs fastest (>= moga_workspace_bytes; Nk = number of key rows, N for MoGA's own calls).  The
  * bf16 attention calls with a few rounds of long blocks use room past what they need to split the last round
- * (34 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd and the moga_varlen_* calls.  A split row is
+ * (34 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
  * summed in pieces, so its rounding differs from that of a call with less room: results repeat bit by bit between calls
  * that both have these bytes, or both less.  Host-only.
  */
@@ -148,6 +148,18 @@ int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int d
                            void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * Steps 3 and 4 of Alg. 1 in one call: moga_group_attn_fwd_ws, whose kernels also write their rows in token order,
+ *   o[perm[j]][h][:] = gate[perm[j]] * oh[h][j][:]
+ * so that the output is not read again.  The same bits as moga_group_attn_fwd_ws followed by moga_unpermute.  perm and gate
+ * as for moga_unpermute, both required.
+ */
+int moga_group_attn_fwd_tokens(const void* qh, const void* kh, const void* vh, int dtype,
+                               int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                               float softmax_scale, const int32_t* perm, const float* gate,
+                               void* oh, float* lse, void* o,
+                               void* ws, size_t ws_bytes, void* stream);
+
+/*
  * repermute of Alg. 1 with the gate of Eq. 5:
  *   o[perm[j]][h][:] = gate[perm[j]] * oh[h][j][:]      (gate NULL: plain scatter)
  */
@@ -176,7 +188,22 @@ int moga_group_attn_bwd(const void* d_oh, const void* qh, const void* kh, const 
                         void* ws, size_t ws_bytes, void* stream);
 
 /*
- * Diagnostics of the BF16 backward calls (moga_group_attn_bwd, moga_varlen_attn_bwd,
+ * The backward of moga_group_attn_fwd_tokens: moga_unpermute_bwd, moga_group_attn_bwd and moga_permute_bwd in one call, with
+ * the same bits.  The row constants of the attention backward are computed where d_oh is written, and its kernels write their
+ * rows in token order.  Outputs: d_oh [H, N, D], d_gate [N]; d_q, d_k, d_v [N, H, D]; the sorted d_qh, d_kh, d_vh [H, N, D],
+ * or all three NULL.  Workspace and status word as for moga_group_attn_bwd.
+ */
+int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, const void* vh,
+                               const void* oh, const float* lse, int dtype,
+                               int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                               float softmax_scale, const int32_t* perm, const float* gate,
+                               void* d_oh, float* d_gate,
+                               void* d_qh_or_null, void* d_kh_or_null, void* d_vh_or_null,
+                               void* d_q, void* d_k, void* d_v,
+                               void* ws, size_t ws_bytes, void* stream);
+
+/*
+ * Diagnostics of the BF16 backward calls (moga_group_attn_bwd, moga_group_attn_bwd_tokens, moga_varlen_attn_bwd,
  * moga_fused_attn_bwd).  Inside the dK/dV kernel one wave of a pair waits for values its partner
  * publishes through LDS; the wait is bounded, and a wave that gives up sets an int32 status word in
  * the workspace to a nonzero value and carries on, so the kernel always drains (the gradients of

@@ -40,10 +40,14 @@ _SIGNATURES = {
                                    _vp, _sz, _vp]),
     "moga_group_attn_fwd_ws": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32, _f32, _vp, _vp,
                                       _vp, _sz, _vp]),
+    "moga_group_attn_fwd_tokens": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32, _f32, _vp, _vp, _vp, _vp, _vp,
+                                          _vp, _sz, _vp]),
     "moga_unpermute": (_i32, [_vp, _i32, _vp, _vp, _i64, _i32, _i32, _vp, _vp]),
     "moga_unpermute_bwd": (_i32, [_vp, _vp, _i32, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp]),
     "moga_group_attn_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32,
                                    _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "moga_group_attn_bwd_tokens": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32, _f32, _vp, _vp,
+                                          _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_attn_bwd_status_offset": (_sz, [_i64, _i32]),
     "moga_debug_set_spin_limit": (None, [_i32]),
     "moga_debug_set_small_group_rows": (None, [_i64]),
@@ -204,6 +208,11 @@ def moga_group_attn_fwd(qh, kh, vh, cu_seqlens, softmax_scale, stream=None, out=
     return _nat.group_attn_fwd(qh, kh, vh, cu_seqlens, softmax_scale, _st(stream), out, lse)
 
 
+def moga_group_attn_fwd_tokens(qh, kh, vh, cu_seqlens, softmax_scale, perm, gate, stream=None):
+    """moga_group_attn_fwd and moga_unpermute in one call -> (oh [H, N, D], lse f32 [H, N], o [N, H, D])"""
+    return _nat.group_attn_fwd_tokens(qh, kh, vh, cu_seqlens, softmax_scale, perm, gate, _st(stream))
+
+
 def moga_unpermute(oh, perm, gate=None, stream=None, out=None):
     """-> o [N, H, D]"""
     return _nat.unpermute(oh, perm, gate, _st(stream), out)
@@ -232,6 +241,12 @@ def set_spin_limit(polls: int) -> None:
 def moga_group_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu_seqlens, softmax_scale, stream=None, ws=None):
     """-> (d_qh, d_kh, d_vh) each [H, N, D].  `ws`: the caller's workspace (uint8), else one is allocated."""
     return _nat.group_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu_seqlens, softmax_scale, _st(stream), ws)
+
+
+def moga_group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu_seqlens, softmax_scale, perm, gate, want_sorted=True, stream=None):
+    """moga_unpermute_bwd, moga_group_attn_bwd and moga_permute_bwd in one call
+    -> (d_oh [H, N, D], d_gate f32 [N], d_qh, d_kh, d_vh [H, N, D] | None, d_q, d_k, d_v [N, H, D])"""
+    return _nat.group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu_seqlens, softmax_scale, perm, gate, want_sorted, _st(stream))
 
 
 def moga_permute_bwd(d_qh, d_kh, d_vh, perm, stream=None):
@@ -326,22 +341,20 @@ def moga_balance_loss_bwd(group, frac, alpha, d_loss=1.0, d_gate=None, stream=No
 
 
 def moga_forward(x, w, q, k, v, softmax_scale, want_probs=True, stream=None):
-    """Alg. 1 end to end: the four forward calls in order on one stream.  Returns a dict."""
+    """Alg. 1 end to end: the forward calls in order on one stream.  Returns a dict."""
     group, gate, probs, _ = moga_route(x, w, want_probs=want_probs, stream=stream)
     pm = moga_permute(group, w.shape[0], q, k, v, stream=stream)
-    oh, lse = moga_group_attn_fwd(pm["qh"], pm["kh"], pm["vh"], pm["cu_seqlens"], softmax_scale,
-                                  stream=stream)
-    o = moga_unpermute(oh, pm["perm"], gate, stream=stream)
+    oh, lse, o = moga_group_attn_fwd_tokens(pm["qh"], pm["kh"], pm["vh"], pm["cu_seqlens"], softmax_scale, pm["perm"], gate,
+                                            stream=stream)
     pm.update({"group": group, "gate": gate, "probs": probs, "oh": oh, "lse": lse, "o": o})
     return pm
 
 
 def moga_backward(fwd, x, w, d_o, softmax_scale, want_dx=False, stream=None):
-    """Backward of `moga_forward`: the four backward calls in reverse order.  Returns a dict."""
-    d_oh, d_gate = moga_unpermute_bwd(d_o, fwd["oh"], fwd["perm"], fwd["gate"], stream=stream)
-    d_qh, d_kh, d_vh = moga_group_attn_bwd(d_oh, fwd["qh"], fwd["kh"], fwd["vh"], fwd["oh"], fwd["lse"],
-                                           fwd["cu_seqlens"], softmax_scale, stream=stream)
-    d_q, d_k, d_v = moga_permute_bwd(d_qh, d_kh, d_vh, fwd["perm"], stream=stream)
+    """Backward of `moga_forward`: the backward calls in reverse order.  Returns a dict."""
+    d_oh, d_gate, d_qh, d_kh, d_vh, d_q, d_k, d_v = moga_group_attn_bwd_tokens(
+        d_o, fwd["qh"], fwd["kh"], fwd["vh"], fwd["oh"], fwd["lse"], fwd["cu_seqlens"], softmax_scale, fwd["perm"],
+        fwd["gate"], stream=stream)
     d_w, d_x = moga_route_bwd(x, w, fwd["probs"], fwd["group"], fwd["gate"], d_gate, want_dx=want_dx,
                               stream=stream)
     return {"d_q": d_q, "d_k": d_k, "d_v": d_v, "d_w": d_w, "d_x": d_x, "d_gate": d_gate,

@@ -149,6 +149,13 @@ extern "C" void moga_debug_set_spin_limit(int polls) { g_spin_limit.store(polls 
 // a group: a group (hence a tensor) must have fewer than 2^24 rows.
 static bool bf16_rows_ok(int64_t Nq, int64_t Nk) { return Nq < ((int64_t)1 << 24) && Nk < ((int64_t)1 << 24); }
 
+// The gradients in token order [N, H, D] as well, row j of the sorted order at token perm[j]; all NULL: none.  With them the
+// sorted ones (d_qh, d_kh, d_vh) may be NULL, and the row constants (bf16) are already in the workspace.
+struct TokenGrads {
+  void *d_q, *d_k, *d_v;
+  const int32_t* perm;
+};
+
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
 // space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: NULL or kSplitBytes
 // for the pieces of a last round (dK/dV and dQ use it one after the other; only without ts_q / ts_k).
@@ -156,14 +163,15 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
                            const void* oh, const float* lse, int dtype, int64_t Nq, int64_t Nk, int H, int D,
                            const int32_t* cu_q, const int32_t* cu_k, int32_t* ts_q, int32_t* ts_k,
                            int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
-                           float* delta, void* split, hipStream_t st) {
+                           float* delta, const TokenGrads& tok, void* split, hipStream_t st) {
+  unsigned short *d_q_tok = (unsigned short*)tok.d_q, *d_k_tok = (unsigned short*)tok.d_k, *d_v_tok = (unsigned short*)tok.d_v;
   const int64_t rows = Nq * (int64_t)H;
   if ((rows * 32 + 255) / 256 >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;   // grid of the delta kernel
   if (dtype == MOGA_BF16) {
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
     int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-    attn_bwd_delta_kernel<<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
+    if (!tok.perm) attn_bwd_delta_kernel<<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
@@ -178,19 +186,19 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         attn_bwd_dkdv_ab_kernel<false, 2, 2><<<(unsigned)blocks, 256, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
+            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
       else if (split && split_pays(tiles * H)) {
         attn_bwd_dkdv_ab_kernel<false, 4, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
-            g_spin_limit.load(), status, nullptr, split_ws(split).part);
+            g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
         split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 2, 1.f, softmax_scale,
-                                                            (unsigned short*)d_vh, (unsigned short*)d_kh);
+                                                            (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
       } else
         attn_bwd_dkdv_ab_kernel<false><<<(unsigned)blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status);
+            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
     }
     {
       const int bm = small ? 128 : 256;
@@ -202,18 +210,18 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         attn_bwd_dq_pipe_kernel<4, false, 2><<<(unsigned)blocks, 256, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_qh);
+            (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
       else if (split && split_pays(tiles * H)) {
         attn_bwd_dq_pipe_kernel<8, false, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
-            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, nullptr, split_ws(split).part);
+            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
         split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
-                                                            (unsigned short*)d_qh, nullptr);
+                                                            (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
       } else
         attn_bwd_dq_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_qh);
+            (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
     }
   } else {
     {
@@ -224,7 +232,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
 #define MOGA_DQ_F32(DD)                                                                                   \
   attn_bwd_dq_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                       \
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, (const float*)oh, lse,    \
-      cu_q, cu_k, ts_q, M, Nq, Nk, softmax_scale, (int)tiles, delta, (float*)d_qh)
+      cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale, (int)tiles, delta, (float*)d_qh, tok.perm, (float*)tok.d_q)
       if (D == 64) MOGA_DQ_F32(64);
       else MOGA_DQ_F32(128);
 #undef MOGA_DQ_F32
@@ -237,7 +245,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
 #define MOGA_DKDV_F32(DD)                                                                                 \
   attn_bwd_dkdv_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                     \
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k,   \
-      ts_k, M, Nq, Nk, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh)
+      ts_k, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh, tok.perm, (float*)tok.d_k, (float*)tok.d_v)
       if (D == 64) MOGA_DKDV_F32(64);
       else MOGA_DKDV_F32(128);
 #undef MOGA_DKDV_F32
@@ -273,8 +281,35 @@ extern "C" int moga_group_attn_bwd(const void* d_oh, const void* qh, const void*
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr,
-                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, split_region(ws, need, ws_bytes),
+                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{}, split_region(ws, need, ws_bytes),
                          (hipStream_t)stream);
+}
+
+extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh,
+                                          const float* lse, int dtype, int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                                          float softmax_scale, const int32_t* perm, const float* gate, void* d_oh, float* d_gate,
+                                          void* d_qh, void* d_kh, void* d_vh, void* d_q, void* d_k, void* d_v, void* ws,
+                                          size_t ws_bytes, void* stream) {
+  const int bad = check_attn_bwd_args(N, N, H, D, M, softmax_scale, dtype);
+  if (bad) return bad;
+  if (M > MOGA_MAX_GROUPS) return MOGA_ERR_UNSUPPORTED;
+  if (dtype == MOGA_BF16 && !bf16_rows_ok(N, N)) return MOGA_ERR_UNSUPPORTED;
+  if (N == 0) return MOGA_OK;
+  if (!d_o || !qh || !kh || !vh || !oh || !lse || !cu_seqlens || !perm || !gate || !d_oh || !d_gate || !d_q || !d_k || !d_v)
+    return MOGA_ERR_INVALID_ARG;
+  if (!d_qh != !d_kh || !d_qh != !d_vh) return MOGA_ERR_INVALID_ARG;
+  if (!(aligned16(d_o) && aligned16(d_oh) && aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh) &&
+        aligned16(d_qh) && aligned16(d_kh) && aligned16(d_vh) && aligned16(d_q) && aligned16(d_k) && aligned16(d_v)))
+    return MOGA_ERR_INVALID_ARG;
+  const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
+  if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
+  float* delta = (float*)ws;
+  const RowConstants rc = {lse, 1.f / softmax_scale, delta, delta + N * (int64_t)H, (int*)((char*)ws + bwd_rows_bytes(N, H))};
+  const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, &rc, (hipStream_t)stream);
+  if (rows != MOGA_OK) return rows;
+  return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
+                         softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm},
+                         split_region(ws, need, ws_bytes), (hipStream_t)stream);
 }
 
 extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
@@ -312,7 +347,7 @@ extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void
   int32_t* ts_q = presum ? (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16) : nullptr;
   int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
-                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws,
+                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{},
                          presum ? nullptr : split_region(ws, need, ws_bytes), st);
 }
 

@@ -123,19 +123,26 @@ __device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf
   dq_accumulate<SOFF + 8192>(ln, off, dsf_b, dq);
 }
 
-// Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f.
+// Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f: to `out` (sorted order, or token order in
+// gather mode) and, not in gather mode, to `tok` in token order; either may be NULL.
 template <bool GATHER>
 __device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], float f, int row0, int ge, int head, int64_t head_off,
-                                               int H, unsigned short* __restrict__ out, const int32_t* __restrict__ perm) {
+                                               int H, unsigned short* __restrict__ out, unsigned short* __restrict__ tok,
+                                               const int32_t* __restrict__ perm) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const int row = row0 + 16 * c + r;
     if (row < ge) {
-      const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
-      unsigned short* op = out + orow * kHeadDim + 4 * g;
+      const int64_t trow = GATHER || tok ? (int64_t)perm[row] * H + head : 0;
+      unsigned short* op = out + (GATHER ? trow : head_off + row) * kHeadDim + 4 * g;
+      unsigned short* tp = tok + trow * kHeadDim + 4 * g;
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) *(uintx2_t*)(op + 16 * dt) = pack4(acc[dt][c], f);
+      for (int dt = 0; dt < 8; ++dt) {
+        const uintx2_t v = pack4(acc[dt][c], f);
+        if (GATHER || out) *(uintx2_t*)(op + 16 * dt) = v;
+        if (!GATHER && tok) *(uintx2_t*)(tp + 16 * dt) = v;
+      }
     }
   }
 }
@@ -168,7 +175,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
-    float* __restrict__ part = nullptr) {
+    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
   constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
@@ -194,7 +201,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 32 * wave) * kHeadDim : nullptr;
   if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
     if (piece) store_zero_piece(piece_rows);
-    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm);
+    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
     return;
   }
 
@@ -278,7 +285,7 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   if (piece) store_gradient_piece(dq, piece_rows);
-  else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, perm);
+  else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, d_q_tok, perm);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -434,7 +441,8 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
-    float* __restrict__ part = nullptr) {
+    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
+    unsigned short* __restrict__ d_v_tok = nullptr) {
   constexpr int NW = 2 * NPAIR;
   constexpr int BK = 32 * NPAIR;                   // pairs of waves x 32 keys
   constexpr int kAhead = NB - 2;
@@ -465,11 +473,12 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   const float c = scale * 1.4426950408889634f;
   const int k0w = k0 + pair * 32;   // first key row of this pair
   unsigned short* outp = role == 0 ? d_vh : d_kh;
+  unsigned short* tokp = role == 0 ? d_v_tok : d_k_tok;
 
   float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 32 * pair) * kHeadDim : nullptr;   // dV, then dK
   if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
     if (piece) store_zero_piece(piece_rows);
-    else store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm);
+    else store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);
     return;
   }
 
@@ -550,7 +559,7 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   if (piece) store_gradient_piece(acc, piece_rows);
-  else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, perm);
+  else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, tokp, perm);
 }
 
 }  // namespace moga

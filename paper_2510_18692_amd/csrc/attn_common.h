@@ -191,13 +191,17 @@ inline SplitWs split_ws(void* ws) {
 inline bool split_pays(int64_t tiles) { return tiles <= 32 * kCus; }
 
 constexpr int kSplitGridY = kSplitRows / 8;
-// Sum of the pieces of every tile of the last round, times f, as bf16 rows of `out`.  A tile has `arrays` results of
+// Sum of the pieces of every tile of the last round, times f, as bf16 rows of `out` (sorted order) and `tok` (token order),
+// each of which may be NULL.  A tile has `arrays` results of
 // kSplitRows / arrays rows each (dV and dK: two, 128 rows).  Grid (kCus / 2, kSplitGridY): eight rows per block, one trip
 // to memory (with 64 rows per block, one after the other, 45 us instead of 9).
 static __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ part, const int32_t* __restrict__ cu, int M,
                                                                int H, int64_t N, int arrays, float f0, float f1,
                                                                unsigned short* __restrict__ out0,
-                                                               unsigned short* __restrict__ out1) {
+                                                               unsigned short* __restrict__ out1,
+                                                               unsigned short* __restrict__ tok0,
+                                                               unsigned short* __restrict__ tok1,
+                                                               const int32_t* __restrict__ perm) {
   const int rows = kSplitRows / arrays;
   const int per_head = count_tiles(cu, M, rows);
   const SplitShape s = split_shape(per_head * H);
@@ -215,9 +219,11 @@ static __global__ __launch_bounds__(256) void split_sum_kernel(const float* __re
   for (int k = 0; k < kMaxSplits; ++k) v[k] = k < s.splits ? *(const floatx4_t*)(p + (size_t)k * kSplitRows * kHeadDim) : floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 1; k < kMaxSplits; ++k) v[0] += v[k];
-  unsigned short* o = (a ? out1 : out0) + ((int64_t)head * N + row) * kHeadDim + col;
+  unsigned short *o = a ? out1 : out0, *t = a ? tok1 : tok0;
   const float f = a ? f1 : f0;
-  *(uintx2_t*)o = uintx2_t{pack_bf16x2(v[0][0] * f, v[0][1] * f), pack_bf16x2(v[0][2] * f, v[0][3] * f)};
+  const uintx2_t w = {pack_bf16x2(v[0][0] * f, v[0][1] * f), pack_bf16x2(v[0][2] * f, v[0][3] * f)};
+  if (o) *(uintx2_t*)(o + ((int64_t)head * N + row) * kHeadDim + col) = w;
+  if (t) *(uintx2_t*)(t + ((int64_t)perm[row] * H + head) * kHeadDim + col) = w;
 }
 
 // One block: exclusive scan of ceil(n_g / rows_per_tile) over the groups, M + 1 results.
@@ -307,6 +313,12 @@ __device__ __forceinline__ void wave_priority() {
 // Four results of a column (d = 16 dt + 4 g ..) as bf16, scaled.
 __device__ __forceinline__ uintx2_t pack4(const floatx4_t& v, float f) {
   return uintx2_t{pack_bf16x2(v[0] * f, v[1] * f), pack_bf16x2(v[2] * f, v[3] * f)};
+}
+
+// Four bf16 values times f, rounded again.
+__device__ __forceinline__ uintx2_t scale4(uintx2_t v, float f) {
+  return uintx2_t{pack_bf16x2(bf16_lo_to_f32(v[0]) * f, bf16_hi_to_f32(v[0]) * f),
+                  pack_bf16x2(bf16_lo_to_f32(v[1]) * f, bf16_hi_to_f32(v[1]) * f)};
 }
 
 }  // namespace moga

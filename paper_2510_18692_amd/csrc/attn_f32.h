@@ -126,9 +126,10 @@ __device__ __forceinline__ void f32_reduce_waves(floatx16_t (&acc)[DT], float (*
   }
 }
 
-// Write acc * f (channel DT*i + dt of stationary row r) to `row`.
+// Write acc * f (channel DT*i + dt of stationary row r) to `row`, and that times g to `tok`; either may be NULL.
 template <int D>
-__device__ __forceinline__ void f32_store_row(float* __restrict__ row, const floatx16_t (&acc)[D / 32], float f, int h) {
+__device__ __forceinline__ void f32_store_row(float* __restrict__ row, float* __restrict__ tok, const floatx16_t (&acc)[D / 32],
+                                              float f, float g, int h) {
   constexpr int DT = D / 32;
 #pragma unroll
   for (int b = 0; b < 4; ++b) {   // registers 4b .. 4b+3: channels DT*(8b + 4h) .. + 4*DT - 1
@@ -140,9 +141,18 @@ __device__ __forceinline__ void f32_store_row(float* __restrict__ row, const flo
 #pragma unroll
     for (int i = 0; i < DT; ++i) {
       const floatx4_t q = {t[4 * i], t[4 * i + 1], t[4 * i + 2], t[4 * i + 3]};
-      *(floatx4_t*)(row + DT * (8 * b + 4 * h) + 4 * i) = q;
+      if (row) *(floatx4_t*)(row + DT * (8 * b + 4 * h) + 4 * i) = q;
+      if (tok) *(floatx4_t*)(tok + DT * (8 * b + 4 * h) + 4 * i) = floatx4_t{q[0] * g, q[1] * g, q[2] * g, q[3] * g};
     }
   }
+}
+
+// Row `row` of a [H, N, D] tensor and of its token-order counterpart [N, H, D]; NULL where the tensor is.
+template <int D>
+__device__ __forceinline__ float* f32_sorted_row(float* t, int64_t row) { return t ? t + row * D : nullptr; }
+template <int D>
+__device__ __forceinline__ float* f32_token_row(float* t, const int32_t* __restrict__ perm, int row, int head, int H) {
+  return t ? t + ((int64_t)perm[row] * H + head) * D : nullptr;
 }
 
 __device__ __forceinline__ float f32_halves_max(float v) {
@@ -166,7 +176,8 @@ template <int D>
 __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
     const float* __restrict__ qh, const float* __restrict__ kh, const float* __restrict__ vh,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
-    int64_t Nq, int64_t Nk, float scale, int tiles_per_head, float* __restrict__ oh, float* __restrict__ lse) {
+    int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, float* __restrict__ oh, float* __restrict__ lse,
+    const int32_t* __restrict__ perm, const float* __restrict__ gate, float* __restrict__ o_tok) {
   constexpr int NW = kF32Waves, DT = D / 32;
   __shared__ __attribute__((aligned(16))) F32Tile<D> Qs;
   __shared__ float s_buf[NW / 2][DT * 16][64];
@@ -251,7 +262,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_fwd_f32_mfma_kernel(
   f32_reduce_waves<NW, DT>(o, s_buf, wave, lane);
   const int row = ti.tile_row + r;
   if (wave == 0 && row < ti.row_end) {   // no keys: zero output, lse = -inf
-    f32_store_row<D>(oh + (head_off + row) * D, o, nsteps > 0 ? 1.f / lt : 0.f, h);
+    f32_store_row<D>(oh + (head_off + row) * D, f32_token_row<D>(o_tok, perm, row, head, H), o, nsteps > 0 ? 1.f / lt : 0.f,
+                     o_tok ? gate[perm[row]] : 1.f, h);
     if (h == 0) lse[head_off + row] = nsteps > 0 ? mt * scale + logf(lt) : -INFINITY;
   }
 }
@@ -263,7 +275,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dq_f32_mfma_kernel(
     const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh,
     const float* __restrict__ vh, const float* __restrict__ oh, const float* __restrict__ lse,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
-    int64_t Nq, int64_t Nk, float scale, int tiles_per_head, float* __restrict__ delta, float* __restrict__ d_qh) {
+    int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, float* __restrict__ delta, float* __restrict__ d_qh,
+    const int32_t* __restrict__ perm, float* __restrict__ d_q_tok) {
   constexpr int NW = kF32Waves, DT = D / 32, LPR = D / 4;
   __shared__ __attribute__((aligned(16))) F32Tile<D> Qs, Ds;
   __shared__ float s_buf[NW / 2][DT * 16][64];
@@ -328,7 +341,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dq_f32_mfma_kernel(
     f32_accumulate<D>(dq, kb, 32 * s, n - 1, p, r, h);
   }
   f32_reduce_waves<NW, DT>(dq, s_buf, wave, lane);
-  if (wave == 0 && first + r <= last) f32_store_row<D>(d_qh + (first + r) * D, dq, scale, h);
+  if (wave == 0 && first + r <= last)
+    f32_store_row<D>(f32_sorted_row<D>(d_qh, first + r), f32_token_row<D>(d_q_tok, perm, ti.tile_row + r, head, H), dq, scale, 1.f, h);
 }
 
 // ---- backward, key-stationary: dK and dV --------------------------------------------------
@@ -337,7 +351,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dkdv_f32_mfma_kernel(
     const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh,
     const float* __restrict__ vh, const float* __restrict__ lse, const float* __restrict__ delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
-    int64_t Nq, int64_t Nk, float scale, int tiles_per_head, float* __restrict__ d_kh, float* __restrict__ d_vh) {
+    int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, float* __restrict__ d_kh, float* __restrict__ d_vh,
+    const int32_t* __restrict__ perm, float* __restrict__ d_k_tok, float* __restrict__ d_v_tok) {
   constexpr int NW = kF32Waves, DT = D / 32;
   __shared__ __attribute__((aligned(16))) F32Tile<D> Ks, Vs;
   __shared__ float s_buf[NW / 2][DT * 16][64];
@@ -402,8 +417,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dkdv_f32_mfma_kernel(
   f32_reduce_waves<NW, DT>(dv, s_buf, wave, lane);
   f32_reduce_waves<NW, DT>(dk, s_buf, wave, lane);
   if (wave == 0 && first + r <= last) {
-    f32_store_row<D>(d_vh + (first + r) * D, dv, 1.f, h);
-    f32_store_row<D>(d_kh + (first + r) * D, dk, scale, h);
+    const int row = ti.tile_row + r;
+    f32_store_row<D>(f32_sorted_row<D>(d_vh, first + r), f32_token_row<D>(d_v_tok, perm, row, head, H), dv, 1.f, 1.f, h);
+    f32_store_row<D>(f32_sorted_row<D>(d_kh, first + r), f32_token_row<D>(d_k_tok, perm, row, head, H), dk, scale, 1.f, h);
   }
 }
 

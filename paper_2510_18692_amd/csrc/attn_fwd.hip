@@ -32,12 +32,20 @@ static int64_t small_group_rows(int64_t Nq, int H) {
 
 using namespace moga;
 
+// Where the output rows go in token order as well: o [N, H, D] or NULL, row j of the sorted order at token perm[j], times
+// gate[perm[j]].
+struct TokenRows {
+  void* o;
+  const int32_t* perm;
+  const float* gate;
+};
+
 // Shared launcher.  tile_start == NULL: tile lookup inside the kernels (M <= MOGA_MAX_GROUPS).  split: NULL or
 // kSplitBytes for the pieces of the last round (only with tile_start == NULL).
 static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype, int64_t Nq,
                            int64_t Nk, int H, int D, const int32_t* cu_q, const int32_t* cu_k,
                            int32_t* tile_start, int M, float softmax_scale, void* oh, float* lse,
-                           void* split, hipStream_t st) {
+                           const TokenRows& tok, void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
   const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
@@ -49,26 +57,26 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   if (small) {
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
-        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse);
+        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, (unsigned short*)tok.o);
   } else if (dtype == MOGA_BF16 && split && split_pays(tiles * H)) {
     const SplitWs sw = split_ws(split);
     attn_fwd_bf16_pipe_kernel<8, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,
-        softmax_scale, (unsigned short*)oh, lse, nullptr, nullptr, sw);
+        softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, sw, (unsigned short*)tok.o);
     split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, cu_k, M, H, Nq, softmax_scale, (unsigned short*)oh,
-                                                                  lse);
+                                                                  lse, tok.perm, tok.gate, (unsigned short*)tok.o);
   } else if (dtype == MOGA_BF16) {
     attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
-        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse);
+        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, SplitWs{}, (unsigned short*)tok.o);
   } else if (D == 64) {
     attn_fwd_f32_mfma_kernel<64><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk,
-        softmax_scale, (int)tiles, (float*)oh, lse);
+        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
+        softmax_scale, (int)tiles, (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o);
   } else {
     attn_fwd_f32_mfma_kernel<128><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk,
-        softmax_scale, (int)tiles, (float*)oh, lse);
+        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
+        softmax_scale, (int)tiles, (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o);
   }
   return launch_status();
 }
@@ -86,18 +94,33 @@ static int check_attn_args(int64_t Nq, int64_t Nk, int H, int D, int M, float so
   return MOGA_OK;
 }
 
-extern "C" int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int dtype,
-                                      int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
-                                      float softmax_scale, void* oh, float* lse, void* ws,
-                                      size_t ws_bytes, void* stream) {
+static int group_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype, int64_t N, int H, int D,
+                          const int32_t* cu_seqlens, int M, float softmax_scale, void* oh, float* lse, const TokenRows& tok,
+                          void* ws, size_t ws_bytes, void* stream) {
   const int bad = check_attn_args(N, N, H, D, M, softmax_scale, dtype);
   if (bad) return bad;
   if (M > MOGA_MAX_GROUPS) return MOGA_ERR_UNSUPPORTED;
   if (N == 0) return MOGA_OK;
   if (!qh || !kh || !vh || !cu_seqlens || !oh || !lse) return MOGA_ERR_INVALID_ARG;
-  if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
+  if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh) && aligned16(tok.o))) return MOGA_ERR_INVALID_ARG;
   return launch_attn_fwd(qh, kh, vh, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, M,
-                         softmax_scale, oh, lse, split_region(ws, 0, ws_bytes), (hipStream_t)stream);
+                         softmax_scale, oh, lse, tok, split_region(ws, 0, ws_bytes), (hipStream_t)stream);
+}
+
+extern "C" int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int dtype,
+                                      int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                                      float softmax_scale, void* oh, float* lse, void* ws,
+                                      size_t ws_bytes, void* stream) {
+  return group_attn_fwd(qh, kh, vh, dtype, N, H, D, cu_seqlens, M, softmax_scale, oh, lse, TokenRows{}, ws, ws_bytes, stream);
+}
+
+extern "C" int moga_group_attn_fwd_tokens(const void* qh, const void* kh, const void* vh, int dtype,
+                                          int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
+                                          float softmax_scale, const int32_t* perm, const float* gate,
+                                          void* oh, float* lse, void* o, void* ws, size_t ws_bytes, void* stream) {
+  if (N > 0 && (!perm || !gate || !o)) return MOGA_ERR_INVALID_ARG;
+  return group_attn_fwd(qh, kh, vh, dtype, N, H, D, cu_seqlens, M, softmax_scale, oh, lse, TokenRows{o, perm, gate}, ws,
+                        ws_bytes, stream);
 }
 
 // Needs no workspace and touches none: a caller may pass one that other streams are using.
@@ -151,5 +174,5 @@ extern "C" int moga_varlen_attn_fwd(const void* qh, const void* kh, const void* 
   int32_t* ts = G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)ws;   // few groups: every block looks its tile up itself
   void* split = ts ? nullptr : split_region(ws, moga_varlen_attn_fwd_ws_bytes(G), ws_bytes);
   return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts, G,
-                         softmax_scale, oh, lse, split, (hipStream_t)stream);
+                         softmax_scale, oh, lse, TokenRows{}, split, (hipStream_t)stream);
 }

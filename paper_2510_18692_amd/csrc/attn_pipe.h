@@ -184,10 +184,12 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
 
 // Output rows of a wave (query columns r and 16 + r of its 32 rows from q0w): O / l, times the row's gate in gather mode,
 // and the log-sum-exp.  Register i of d tile dt is d = 16 dt + 4 g + i.
+// o_tok (not in gather mode): NULL, or where the rows also go in token order [N, H, 128], rounded and then times the gate.
 template <bool GATHER>
 __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int ge, int head, int64_t head_off, int H, float scale,
                                              unsigned short* __restrict__ oh, float* __restrict__ lse,
-                                             const int32_t* __restrict__ perm, const float* __restrict__ gate) {
+                                             const int32_t* __restrict__ perm, const float* __restrict__ gate,
+                                             unsigned short* __restrict__ o_tok) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
@@ -203,8 +205,19 @@ __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int g
         inv *= gate[tok];
       }
       unsigned short* op = oh + orow * kHeadDim + 4 * g;
+      unsigned short* tp = nullptr;
+      float gt = 1.f;
+      if (!GATHER && o_tok) {
+        const int tok = perm[qrow];
+        tp = o_tok + ((int64_t)tok * H + head) * kHeadDim + 4 * g;
+        gt = gate[tok];
+      }
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) *(uintx2_t*)(op + 16 * dt) = pack4(quarter(st.o[dt >> 2][q], dt & 3), inv);
+      for (int dt = 0; dt < 8; ++dt) {
+        const uintx2_t v = pack4(quarter(st.o[dt >> 2][q], dt & 3), inv);
+        *(uintx2_t*)(op + 16 * dt) = v;
+        if (!GATHER && o_tok) *(uintx2_t*)(tp + 16 * dt) = scale4(v, gt);
+      }
       if (g == 0) lse[head_off + qrow] = st.m[q] * scale + logf(lt);
     }
   }
@@ -234,17 +247,25 @@ __device__ __forceinline__ void store_empty_piece(const SplitWs& sw, int slot, i
   }
 }
 
-// Zero output rows of a wave whose group has no keys (lse = -inf if given).
+// Zero output rows of a wave whose group has no keys (lse = -inf if given); `tok`: NULL, or the rows in token order.
 template <bool GATHER>
 __device__ __forceinline__ void store_zero_rows(int row0, int ge, int head, int64_t head_off, int H, unsigned short* __restrict__ out,
-                                                float* __restrict__ lse, const int32_t* __restrict__ perm) {
+                                                float* __restrict__ lse, const int32_t* __restrict__ perm,
+                                                unsigned short* __restrict__ tok) {
   const int lane = threadIdx.x & 63, row = row0 + (lane & 31), h = lane >> 5;
   if (row >= ge) return;
-  const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
-  uintx4_t* op = (uintx4_t*)(out + orow * kHeadDim + 64 * h);
   const uintx4_t z = {0u, 0u, 0u, 0u};
+  if (out) {
+    const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
+    uintx4_t* op = (uintx4_t*)(out + orow * kHeadDim + 64 * h);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) op[i] = z;
+    for (int i = 0; i < 8; ++i) op[i] = z;
+  }
+  if (!GATHER && tok) {
+    uintx4_t* op = (uintx4_t*)(tok + ((int64_t)perm[row] * H + head) * kHeadDim + 64 * h);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) op[i] = z;
+  }
   if (lse && h == 0) lse[head_off + row] = -INFINITY;
 }
 
@@ -382,6 +403,8 @@ __device__ __forceinline__ void pipe_issue(PipeDma& d, int kv0, int buf) {
 // tile_start: NULL (tile lookup from cu_q inside the block, M <= MOGA_MAX_GROUPS) or the
 // pre-summed first-tile index of every group.
 //
+// o_tok: NULL, or [N, H, 128] for the rows in token order times their gate as well (Alg. 1 step 4, the scatter, without
+// reading the output again): row j is token perm[j].
 // GATHER: qh, kh, vh and oh are token-major [N, H, 128]; row j of a group is token perm[j] (the
 // permutation of Alg. 1 is applied while loading, nothing is materialised) and the output row is
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
@@ -393,7 +416,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
     float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
-    const float* __restrict__ gate = nullptr, SplitWs sw = {}) {
+    const float* __restrict__ gate = nullptr, SplitWs sw = {}, unsigned short* __restrict__ o_tok = nullptr) {
   constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);   // direct-to-LDS instructions per thread per tile
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
@@ -419,7 +442,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
     if (piece) store_empty_piece(sw, sp.slot, wave);
-    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm);
+    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
     return;
   }
 
@@ -552,7 +575,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   if (piece) store_piece(st, sw, sp.slot, wave);
-  else store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate);
+  else store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate, o_tok);
 }
 
 // Pieces of every query tile of the last round: O = sum O_k 2^((m_k - m) c) / l, l = sum l_k 2^((m_k - m) c).  NaN and
@@ -560,7 +583,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
 static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const int32_t* __restrict__ cu_q,
                                                                const int32_t* __restrict__ cu_k, int M, int H, int64_t N,
                                                                float scale, unsigned short* __restrict__ oh,
-                                                               float* __restrict__ lse) {
+                                                               float* __restrict__ lse, const int32_t* __restrict__ perm,
+                                                               const float* __restrict__ gate, unsigned short* __restrict__ o_tok) {
   const int per_head = count_tiles(cu_q, M, kSplitRows);
   const SplitShape s = split_shape(per_head * H);
   if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
@@ -593,7 +617,12 @@ static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const
       o += v[k] * w;
     }
   const int64_t orow = (int64_t)head * N + ti.tile_row + r;
-  *(uintx2_t*)(oh + orow * kHeadDim + col) = pack4(o, keys ? 1.f / l : 0.f);
+  const uintx2_t w = pack4(o, keys ? 1.f / l : 0.f);
+  *(uintx2_t*)(oh + orow * kHeadDim + col) = w;
+  if (o_tok) {
+    const int tok = perm[ti.tile_row + r];
+    *(uintx2_t*)(o_tok + ((int64_t)tok * H + head) * kHeadDim + col) = scale4(w, gate[tok]);
+  }
   if (col == 0) lse[orow] = keys ? m * scale + logf(l) : -INFINITY;
 }
 

@@ -33,7 +33,8 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
-    float* __restrict__ lse) {
+    float* __restrict__ lse, const int32_t* __restrict__ perm, const float* __restrict__ gate,
+    unsigned short* __restrict__ o_tok) {
   constexpr int BM = 128;
   constexpr int kDmaPerTile = 4;   // direct-to-LDS instructions per thread per tile
   constexpr int kAhead = 2;        // tiles in flight beyond the one being waited for
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   const float tau = 8.f / c;
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-    store_zero_rows<false>(q0w, ge, head, head_off, H, oh, lse, nullptr);
+    store_zero_rows<false>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
     return;
   }
 
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  store_output<false>(st, q0w, ge, head, head_off, H, scale, oh, lse, nullptr, nullptr);
+  store_output<false>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate, o_tok);
 }
 
 }  // namespace moga

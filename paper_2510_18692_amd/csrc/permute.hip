@@ -371,14 +371,18 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(Rows3 p, const int32_
 }
 
 // d_oh[h][j] = gate[t] * d_o[t][h],  d_gate[t] = sum_{h,c} d_o[t][h][c] * oh[h][j][c],  t = perm[j]
-template <int LPR, bool BF16>
+// DELTA (bf16): also the row constants of the attention backward, -delta = -rowsum(d_oh * oh) (of the rounded d_oh) and
+// -lse / scale, and its status word.  Both tensors are in registers here; attn_bwd_delta_kernel reads them again (62,400 x 12
+// heads: 71 us; 10,007 x 12: 12 us, and 9.9 us more here).  Same sums in the same order as there.
+template <int LPR, bool BF16, bool DELTA>
 __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
     const uintx4_t* __restrict__ d_o, const uintx4_t* __restrict__ oh,
     const int32_t* __restrict__ perm, const float* __restrict__ gate, int64_t N, int H,
-    uintx4_t* __restrict__ d_oh, float* __restrict__ d_gate) {
+    uintx4_t* __restrict__ d_oh, float* __restrict__ d_gate, RowConstants rc) {
   constexpr int RPW = 64 / LPR;
   constexpr int IT = kSlotsPerBlock / RPW;
   __shared__ float s_part[4][kSlotsPerBlock];
+  if (DELTA && blockIdx.x == 0 && threadIdx.x == 0) *rc.status = 0;   // read by the kernels that follow
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
   const int64_t j0 = (int64_t)blockIdx.x * kSlotsPerBlock;
@@ -395,20 +399,32 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
   }
   for (int h = wave; h < H; h += 4) {
     uintx4_t a[IT], b[IT];
+    float l[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int64_t j = j0 + it * RPW + rsub;
       if (ok[it]) {
         a[it] = d_o[(tok[it] * H + h) * LPR + part];
         b[it] = oh[((int64_t)h * N + j) * LPR + part];
+        if (DELTA) l[it] = rc.lse[(int64_t)h * N + j];
       }
     }
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const int64_t j = j0 + it * RPW + rsub;
-      if (ok[it]) {
+      if (ok[it]) {   // the same for all lanes of a row
         acc[it] += dot16<BF16>(a[it], b[it]);
-        d_oh[((int64_t)h * N + j) * LPR + part] = scale16<BF16>(a[it], g[it]);
+        const uintx4_t s = scale16<BF16>(a[it], g[it]);
+        d_oh[((int64_t)h * N + j) * LPR + part] = s;
+        if (DELTA) {
+          float dl = dot16<BF16>(s, b[it]);
+#pragma unroll
+          for (int o = LPR / 2; o > 0; o >>= 1) dl += __shfl_xor(dl, o, kWave);
+          if (part == 0) {
+            rc.neg_delta[(int64_t)h * N + j] = -dl;
+            rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[it] * rc.inv_scale;
+          }
+        }
       }
     }
   }
@@ -850,27 +866,30 @@ extern "C" int moga_permute_bwd(const void* d_qh, const void* d_kh, const void* 
   return scatter_dispatch(p, 3, dtype, D, perm, nullptr, N, H, (hipStream_t)stream);
 }
 
-extern "C" int moga_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32_t* perm,
-                                  const float* gate, int64_t N, int H, int D, void* d_oh,
-                                  float* d_gate, void* stream) {
-  const int rc = check_rows_args(dtype, N, H, D);
-  if (rc != MOGA_OK) return rc;
+int moga::launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32_t* perm, const float* gate, int64_t N,
+                               int H, int D, void* d_oh, float* d_gate, const RowConstants* rc, hipStream_t st) {
+  const int bad = check_rows_args(dtype, N, H, D);
+  if (bad != MOGA_OK) return bad;
   if (N == 0) return MOGA_OK;
   if (!d_o || !oh || !perm || !gate || !d_oh || !d_gate) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(d_o) && aligned16(oh) && aligned16(d_oh))) return MOGA_ERR_INVALID_ARG;
-  hipStream_t st = (hipStream_t)stream;
   const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
   const int lpr = lanes_per_row(dtype, D);
-  if (dtype == MOGA_BF16)
-    unpermute_bwd_kernel<16, true><<<blocks, 256, 0, st>>>(
-        (const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, N, H, (uintx4_t*)d_oh, d_gate);
-  else if (lpr == 16)
-    unpermute_bwd_kernel<16, false><<<blocks, 256, 0, st>>>(
-        (const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, N, H, (uintx4_t*)d_oh, d_gate);
-  else
-    unpermute_bwd_kernel<32, false><<<blocks, 256, 0, st>>>(
-        (const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, N, H, (uintx4_t*)d_oh, d_gate);
+#define MOGA_UNPERMUTE_BWD(LPR, BF, DELTA)                                                                              \
+  unpermute_bwd_kernel<LPR, BF, DELTA><<<blocks, 256, 0, st>>>((const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, N, \
+                                                               H, (uintx4_t*)d_oh, d_gate, rc ? *rc : RowConstants{})
+  if (dtype == MOGA_BF16 && rc) MOGA_UNPERMUTE_BWD(16, true, true);
+  else if (dtype == MOGA_BF16) MOGA_UNPERMUTE_BWD(16, true, false);
+  else if (lpr == 16) MOGA_UNPERMUTE_BWD(16, false, false);
+  else MOGA_UNPERMUTE_BWD(32, false, false);
+#undef MOGA_UNPERMUTE_BWD
   return launch_status();
+}
+
+extern "C" int moga_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32_t* perm,
+                                  const float* gate, int64_t N, int H, int D, void* d_oh,
+                                  float* d_gate, void* stream) {
+  return launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, nullptr, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -173,6 +173,20 @@ std::tuple<Tensor, Tensor> group_attn_fwd(const Tensor& qh, const Tensor& kh, co
   return {oh, lse};
 }
 
+std::tuple<Tensor, Tensor, Tensor> group_attn_fwd_tokens(const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& cu, double scale,
+                                                         const Tensor& perm, const Tensor& gate, const OptStream& stream) {
+  require(qh, kh, vh, cu, perm, gate);
+  const Call call(stream);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
+  Tensor oh = call.make({H, N, D}, qh), lse = call.make({H, N}, qh, at::kFloat), o = call.make({N, H, D}, qh);
+  OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
+  check("moga_group_attn_fwd_tokens",
+        moga_group_attn_fwd_tokens(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, as<int32_t>(cu), (int)M, (float)scale,
+                                   as<int32_t>(perm), as<float>(gate), ptr(oh), as<float>(lse), ptr(o), ptr(ws), bytes_of(ws), call.stream()));
+  return {oh, lse, o};
+}
+
 Tensor unpermute(const Tensor& oh, const Tensor& perm, const OptTensor& gate, const OptStream& stream, const OptTensor& out) {
   require(oh, perm, gate, out);
   const Call call(stream);
@@ -208,6 +222,38 @@ std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tens
                                                    (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
                                                    ptr(ws), bytes_of(ws), call.stream()));
   return {d_qh, d_kh, d_vh};
+}
+
+struct TokenGrads {
+  Tensor d_oh, d_gate;
+  OptTensor d_qh, d_kh, d_vh;   // sorted order, if asked for
+  Tensor d_q, d_k, d_v;
+};
+
+TokenGrads group_attn_bwd_tokens(const Tensor& d_o, const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& oh, const Tensor& lse,
+                                 const Tensor& cu, double scale, const Tensor& perm, const Tensor& gate, bool want_sorted,
+                                 const OptStream& stream) {
+  require(d_o, qh, kh, vh, oh, lse, cu, perm, gate);
+  const Call call(stream);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
+  TokenGrads g;
+  g.d_oh = call.make({H, N, D}, oh);
+  g.d_gate = call.make({N}, oh, at::kFloat);
+  if (want_sorted) {
+    g.d_qh = call.make({H, N, D}, qh);
+    g.d_kh = call.make(kh.sizes(), kh);
+    g.d_vh = call.make(vh.sizes(), vh);
+  }
+  g.d_q = call.make({N, H, D}, qh);
+  g.d_k = call.make({N, H, D}, kh);
+  g.d_v = call.make({N, H, D}, vh);
+  OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
+  check("moga_group_attn_bwd_tokens",
+        moga_group_attn_bwd_tokens(ptr(d_o), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H, (int)D, as<int32_t>(cu),
+                                   (int)M, (float)scale, as<int32_t>(perm), as<float>(gate), ptr(g.d_oh), as<float>(g.d_gate), ptr(g.d_qh),
+                                   ptr(g.d_kh), ptr(g.d_vh), ptr(g.d_q), ptr(g.d_k), ptr(g.d_v), ptr(ws), bytes_of(ws), call.stream()));
+  return g;
 }
 
 std::tuple<Tensor, Tensor, Tensor> permute_bwd(const Tensor& d_qh, const Tensor& d_kh, const Tensor& d_vh, const Tensor& perm,
@@ -400,8 +446,7 @@ struct Attention : public torch::autograd::Function<Attention> {
     const int64_t M = w.size(0);
     auto [group, gate, probs, logits] = route(x, w, std::nullopt, true, false, std::nullopt);
     Permuted p = permute(group, M, q, k, v, std::nullopt);
-    auto [oh, lse] = group_attn_fwd(*p.qh, *p.kh, *p.vh, p.cu_seqlens, scale, std::nullopt, std::nullopt, std::nullopt);
-    Tensor o = unpermute(oh, p.perm, gate, std::nullopt, std::nullopt);
+    auto [oh, lse, o] = group_attn_fwd_tokens(*p.qh, *p.kh, *p.vh, p.cu_seqlens, scale, p.perm, gate, std::nullopt);
     Tensor loss, frac;
     if (alpha) {
       loss = at::empty({}, x.options().dtype(at::kFloat));
@@ -426,15 +471,13 @@ struct Attention : public torch::autograd::Function<Attention> {
     const auto alpha = ctx->saved_data["alpha"].toOptional<double>();
     const bool grad_x = ctx->saved_data["grad_x"].toBool();
     Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros({qh.size(1), qh.size(0), qh.size(2)}, qh.options());
-    auto [d_oh, d_gate] = unpermute_bwd(d_o, oh, perm, gate, std::nullopt);
-    auto [d_qh, d_kh, d_vh] = group_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu, scale, std::nullopt, std::nullopt);
-    d_oh.reset();
-    auto [d_q, d_k, d_v] = permute_bwd(d_qh, d_kh, d_vh, perm, std::nullopt);
-    if (alpha && grads[1].defined()) balance_loss_bwd(group, frac, *alpha, 1.0, grads[1], d_gate, std::nullopt);
-    auto [d_w, d_x] = route_bwd(x, w, probs, group, gate, d_gate, grad_x, std::nullopt);
+    TokenGrads g = group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu, scale, perm, gate, false, std::nullopt);
+    g.d_oh.reset();
+    if (alpha && grads[1].defined()) balance_loss_bwd(group, frac, *alpha, 1.0, grads[1], g.d_gate, std::nullopt);
+    auto [d_w, d_x] = route_bwd(x, w, probs, group, gate, g.d_gate, grad_x, std::nullopt);
     Tensor dx;
     if (d_x) dx = d_x->to(x.scalar_type());
-    return {dx, d_w, d_q, d_k, d_v, Tensor(), Tensor(), Tensor()};
+    return {dx, d_w, g.d_q, g.d_k, g.d_v, Tensor(), Tensor(), Tensor()};
   }
 };
 
@@ -457,9 +500,18 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
       },
       nogil);
   m.def("group_attn_fwd", &group_attn_fwd, nogil);
+  m.def("group_attn_fwd_tokens", &group_attn_fwd_tokens, nogil);
   m.def("unpermute", &unpermute, nogil);
   m.def("unpermute_bwd", &unpermute_bwd, nogil);
   m.def("group_attn_bwd", &group_attn_bwd, nogil);
+  m.def(
+      "group_attn_bwd_tokens",
+      [](const Tensor& d_o, const Tensor& qh, const Tensor& kh, const Tensor& vh, const Tensor& oh, const Tensor& lse, const Tensor& cu,
+         double scale, const Tensor& perm, const Tensor& gate, bool want_sorted, const OptStream& stream) {
+        TokenGrads g = group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu, scale, perm, gate, want_sorted, stream);
+        return std::make_tuple(g.d_oh, g.d_gate, g.d_qh, g.d_kh, g.d_vh, g.d_q, g.d_k, g.d_v);
+      },
+      nogil);
   m.def("permute_bwd", &permute_bwd, nogil);
   m.def("route_bwd", &route_bwd, nogil);
   m.def("fused_attn_fwd", &fused_attn_fwd, nogil);
