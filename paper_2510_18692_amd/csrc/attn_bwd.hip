@@ -175,54 +175,46 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
-    const bool small = use_small_group_kernels(Nq, M, kSmallGroupRows);
+    const bool small = use_small_group_kernels(Nq, M, kSmallGroupRows) &&
+                       (max_tiles(Nq, M, 128) + max_tiles(Nk, M, 64)) * H + 16 < ((int64_t)1 << 31);   // one launch
+    const int bk = small ? 64 : 128, bm = small ? 128 : 256;
+    const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
+    const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
+    if (k_blocks >= ((int64_t)1 << 31) || q_blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+    if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, bk, ts_k);
+    if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, ts_q);
+    if (small) {
+      attn_bwd_small_kernel<<<(unsigned)(q_blocks + k_blocks), 256, 0, st>>>(
+          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta,
+          cu_q, cu_k, ts_q, ts_k, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, (unsigned short*)d_kh, (unsigned short*)d_vh,
+          g_spin_limit.load(), status, tok.perm, d_q_tok, d_k_tok, d_v_tok, (int)q_blocks);
+      return launch_status();
+    }
     if (Nk > 0) {
-      const int bk = small ? 64 : 128;
-      const int64_t tiles = max_tiles(Nk, M, bk);
-      const int64_t blocks = (tiles * H + 7) / 8 * 8;
-      if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-      if (ts_k) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, bk, ts_k);
-      if (small)
-        attn_bwd_dkdv_ab_kernel<false, 2, 2><<<(unsigned)blocks, 256, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
-            (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
-      else if (split && split_pays(tiles * H)) {
-        attn_bwd_dkdv_ab_kernel<false, 4, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
+      if (split && split_pays(k_tiles * H)) {
+        attn_bwd_dkdv_ab_kernel<false, 4, 4, true><<<(unsigned)(k_blocks + kCus), 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
             g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
         split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 2, 1.f, softmax_scale,
                                                             (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
       } else
-        attn_bwd_dkdv_ab_kernel<false><<<(unsigned)blocks, 512, 0, st>>>(
+        attn_bwd_dkdv_ab_kernel<false><<<(unsigned)k_blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
             (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
     }
-    {
-      const int bm = small ? 128 : 256;
-      const int64_t tiles = max_tiles(Nq, M, bm);
-      const int64_t blocks = (tiles * H + 7) / 8 * 8;
-      if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-      if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, ts_q);
-      if (small)
-        attn_bwd_dq_pipe_kernel<4, false, 2><<<(unsigned)blocks, 256, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
-            (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
-      else if (split && split_pays(tiles * H)) {
-        attn_bwd_dq_pipe_kernel<8, false, 4, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
-            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
-        split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
-                                                            (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
-      } else
-        attn_bwd_dq_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
-            (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
-    }
+    if (split && split_pays(q_tiles * H)) {
+      attn_bwd_dq_pipe_kernel<8, false, 4, true><<<(unsigned)(q_blocks + kCus), 512, 0, st>>>(
+          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
+          delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
+      split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
+                                                          (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
+    } else
+      attn_bwd_dq_pipe_kernel<8><<<(unsigned)q_blocks, 512, 0, st>>>(
+          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
+          (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
+          (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
   } else {
     {
       const int64_t tiles = max_tiles(Nq, M, kF32Rows);

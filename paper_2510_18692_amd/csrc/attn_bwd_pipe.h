@@ -167,23 +167,26 @@ __device__ __forceinline__ void store_zero_piece(float* rows) {
 // raw upstream gradient of the gated output.
 // NB: ring slots of 64 keys (4: two tiles ahead, one block per CU; 2: one tile ahead, 64 KB of LDS, so
 // that two 4-wave blocks share a CU -- the variant for small groups).
-template <int NW, bool GATHER = false, int NB = 4, bool SPLIT = false>
-__global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_kernel(
-    const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+template <int NB>
+struct DqLds {
+  __attribute__((aligned(1024))) unsigned short k[NB][64 * kHeadDim], v[NB][64 * kHeadDim];
+};
+
+template <int NW, bool GATHER, int NB, bool SPLIT>
+__device__ __forceinline__ void attn_bwd_dq_block(
+    DqLds<NB>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
-    unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
-    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
+    unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm, float* __restrict__ part,
+    unsigned short* __restrict__ d_q_tok) {
   constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * (16 / NW);
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
-  __shared__ __attribute__((aligned(1024))) unsigned short Ks[NB][64 * kHeadDim];
-  __shared__ __attribute__((aligned(1024))) unsigned short Vs[NB][64 * kHeadDim];
 
   WorkTile sp;
-  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, block, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -221,8 +224,8 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   PipeDma dma;
   dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
   dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&Ks[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&Vs[0][0]) + wave * 1024;
+  dma.lds_k = lds_addr_uniform(&lds.k[0][0]) + wave * 1024;
+  dma.lds_v = lds_addr_uniform(&lds.v[0][0]) + wave * 1024;
   dma.row0 = 4 * wave + (lane >> 4);
   dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
   dma.last_row = n - 1;
@@ -237,9 +240,9 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   for (int t = 0; t <= kAhead; ++t) pipe_issue<NW, GATHER>(dma, 64 * t, t);
 
   DqLane ln;
-  nat_addresses(ln.k_nat, &Ks[0][0], lane);
-  nat_addresses(ln.v_nat, &Vs[0][0], lane);
-  tr_addresses(ln.k_tr, &Ks[0][0], lane);
+  nat_addresses(ln.k_nat, &lds.k[0][0], lane);
+  nat_addresses(ln.v_nat, &lds.v[0][0], lane);
+  tr_addresses(ln.k_tr, &lds.k[0][0], lane);
   // All of the wave's own operands are here before the loop.  Otherwise the compiler, which sees the loads above and not the
   // direct-to-LDS loads, waits for them at their first use, inside the loop: vmcnt(4) .. vmcnt(0) in every tile, that is for
   // the tiles that were issued a moment ago.  With the accumulators of dP started from -delta (a subtraction less per score)
@@ -286,6 +289,20 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   if (piece) store_gradient_piece(dq, piece_rows);
   else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, d_q_tok, perm);
+}
+
+template <int NW, bool GATHER = false, int NB = 4, bool SPLIT = false>
+__global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_kernel(
+    const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
+    const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
+    const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
+    unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
+    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
+  __shared__ DqLds<NB> lds;
+  attn_bwd_dq_block<NW, GATHER, NB, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
+                                           M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -432,31 +449,32 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
 
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
 // NB: ring slots of 64 queries (4 or 2, as in the dQ kernel).
-template <bool GATHER = false, int NPAIR = 4, int NB = 4, bool SPLIT = false>
-__global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab_kernel(
-    const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+template <int NPAIR, int NB>
+struct DkdvLds {
+  __attribute__((aligned(1024))) unsigned short q[NB][64 * kHeadDim], d_o[NB][64 * kHeadDim];
+  __attribute__((aligned(1024))) unsigned char p[NPAIR][4096];   // P of one tile, per pair
+  __attribute__((aligned(256))) float l[NB][64], d[NB][64];      // -lse / scale, -delta
+  int flag[NPAIR];   // per pair: number of tiles whose P has been written
+};
+
+template <bool GATHER, int NPAIR, int NB, bool SPLIT>
+__device__ __forceinline__ void attn_bwd_dkdv_block(
+    DkdvLds<NPAIR, NB>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
-    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
-    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
-    unsigned short* __restrict__ d_v_tok = nullptr) {
+    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm, float* __restrict__ part,
+    unsigned short* __restrict__ d_k_tok, unsigned short* __restrict__ d_v_tok) {
   constexpr int NW = 2 * NPAIR;
   constexpr int BK = 32 * NPAIR;                   // pairs of waves x 32 keys
   constexpr int kAhead = NB - 2;
   constexpr int kDmaPerTile = 2 * (16 / NW) + 2;
-  __shared__ __attribute__((aligned(1024))) unsigned short Qs[NB][64 * kHeadDim];
-  __shared__ __attribute__((aligned(1024))) unsigned short dOs[NB][64 * kHeadDim];
-  __shared__ __attribute__((aligned(1024))) unsigned char Ps[NPAIR][4096];   // P of one tile, per pair
-  __shared__ __attribute__((aligned(256))) float Ls[NB][64];      // -lse / scale
-  __shared__ __attribute__((aligned(256))) float Ds[NB][64];      // -delta
-  __shared__ int s_flag[NPAIR];   // per pair: number of tiles whose P has been written
 
-  if (threadIdx.x < NPAIR) s_flag[threadIdx.x] = 0;   // ordered before its first use by the barriers below
+  if (threadIdx.x < NPAIR) lds.flag[threadIdx.x] = 0;   // ordered before its first use by the barriers below
   WorkTile sp;
-  if (!find_work<SPLIT>(cu_k, tile_start, M, H, BK, blockIdx.x, sp)) return;
+  if (!find_work<SPLIT>(cu_k, tile_start, M, H, BK, block, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, k0 = ti.tile_row;
@@ -467,7 +485,7 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int role = wave / NPAIR, pair = wave % NPAIR;
-  int* flag = &s_flag[pair];
+  int* flag = &lds.flag[pair];
   const int64_t head_off = (int64_t)head * Nk;
   const int64_t head_off_q = (int64_t)head * Nq;
   const float c = scale * 1.4426950408889634f;
@@ -488,8 +506,8 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   PipeDma dma;   // "k" = Q rows, "v" = dO rows of this head's group
   dma.kbase = uniform_ptr(GATHER ? qh + (int64_t)head * kHeadDim : qh + (head_off_q + gs) * kHeadDim);
   dma.vbase = uniform_ptr(GATHER ? d_oh + (int64_t)head * kHeadDim : d_oh + (head_off_q + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&Qs[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&dOs[0][0]) + wave * 1024;
+  dma.lds_k = lds_addr_uniform(&lds.q[0][0]) + wave * 1024;
+  dma.lds_v = lds_addr_uniform(&lds.d_o[0][0]) + wave * 1024;
   dma.row0 = 4 * wave + (lane >> 4);
   dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
   dma.last_row = n - 1;
@@ -502,7 +520,7 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   }
   const void* lbase = uniform_ptr(neg_lse_over_scale + head_off_q + gs);
   const void* dbase = uniform_ptr(neg_delta + head_off_q + gs);
-  const unsigned lds_l = lds_addr_uniform(&Ls[0][0]), lds_d = lds_addr_uniform(&Ds[0][0]);
+  const unsigned lds_l = lds_addr_uniform(&lds.l[0][0]), lds_d = lds_addr_uniform(&lds.d[0][0]);
   auto issue_tile = [&](int T) {   // every wave issues the (identical) row-constant loads so that all count alike
     const int slot = T & (NB - 1);
     pipe_issue<NW, GATHER>(dma, 64 * T, slot);
@@ -514,10 +532,10 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   for (int t = 0; t <= kAhead; ++t) issue_tile(t);
 
   AbLane ln;
-  nat_addresses(ln.nat, role == 0 ? &Qs[0][0] : &dOs[0][0], lane);
-  tr_addresses(ln.tr, role == 0 ? &dOs[0][0] : &Qs[0][0], lane);
-  ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&Ls[0][0] : (unsigned)(uintptr_t)&Ds[0][0]) + 8 * (lane >> 4) * 4;
-  ln.p_addr = (unsigned)(uintptr_t)&Ps[0][0] + pair * 4096 + lane * 16;
+  nat_addresses(ln.nat, role == 0 ? &lds.q[0][0] : &lds.d_o[0][0], lane);
+  tr_addresses(ln.tr, role == 0 ? &lds.d_o[0][0] : &lds.q[0][0], lane);
+  ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&lds.l[0][0] : (unsigned)(uintptr_t)&lds.d[0][0]) + 8 * (lane >> 4) * 4;
+  ln.p_addr = (unsigned)(uintptr_t)&lds.p[0][0] + pair * 4096 + lane * 16;
 
   floatx4_t acc[8][2];   // dV^T (A) or dK^T (B): d tile, key half
 #pragma unroll
@@ -560,6 +578,47 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   if (piece) store_gradient_piece(acc, piece_rows);
   else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, tokp, perm);
+}
+
+template <bool GATHER = false, int NPAIR = 4, int NB = 4, bool SPLIT = false>
+__global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab_kernel(
+    const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
+    const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
+    const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
+    unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
+    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
+    float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
+    unsigned short* __restrict__ d_v_tok = nullptr) {
+  __shared__ DkdvLds<NPAIR, NB> lds;
+  attn_bwd_dkdv_block<GATHER, NPAIR, NB, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k,
+                                                tile_start, M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok,
+                                                d_v_tok);
+}
+
+// Both for small groups, in one launch: blocks below `dq_blocks` (a multiple of 8, for the XCDs) are dQ's, the others dK/dV's.
+// Neither needs the other, and each alone leaves the chip idle in its last round and at a few hundred blocks from the first.
+__global__ __launch_bounds__(256, 2) void attn_bwd_small_kernel(
+    const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
+    const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
+    const int32_t* __restrict__ ts_q, const int32_t* __restrict__ ts_k, int M, int64_t Nq, int64_t Nk, int H, float scale,
+    unsigned short* __restrict__ d_qh, unsigned short* __restrict__ d_kh, unsigned short* __restrict__ d_vh,
+    int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm, unsigned short* __restrict__ d_q_tok,
+    unsigned short* __restrict__ d_k_tok, unsigned short* __restrict__ d_v_tok, int dq_blocks) {
+  __shared__ union {
+    DqLds<2> dq;
+    DkdvLds<2, 2> dkdv;
+  } lds;
+  if ((int)blockIdx.x < dq_blocks)
+    attn_bwd_dq_block<4, false, 2, false>(lds.dq, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, ts_q, M, Nq,
+                                          Nk, H, scale, d_qh, perm, nullptr, d_q_tok);
+  else
+    attn_bwd_dkdv_block<false, 2, 2, false>(lds.dkdv, blockIdx.x - dq_blocks, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q,
+                                            cu_k, ts_k, M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, nullptr, d_k_tok,
+                                            d_v_tok);
 }
 
 }  // namespace moga
