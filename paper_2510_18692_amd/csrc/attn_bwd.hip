@@ -17,12 +17,14 @@
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
-#include "attn_f32.h"
+#include "attn_f32_small.h"
 
 namespace moga {
 
 
 // ---------------------------------------------------------------------------------------
+// LPR lanes of 16 bytes a row.  neg_lse_over_scale and its lse: bf16 only.
+template <int LPR, bool BF16>
 __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const uintx4_t* __restrict__ d_oh,
                                                              const uintx4_t* __restrict__ oh,
                                                              const float* __restrict__ lse, int64_t rows,
@@ -30,22 +32,26 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const uintx4_t* __r
                                                              float* __restrict__ neg_lse_over_scale,
                                                              int* __restrict__ status) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *status = 0;   // read by the kernels that follow
-  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / 16;
-  const int part = threadIdx.x % 16;
+  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
+  const int part = threadIdx.x % LPR;
   float s = 0.f;
   if (row < rows) {
-    const uintx4_t a = d_oh[row * 16 + part], b = oh[row * 16 + part];
+    const uintx4_t a = d_oh[row * LPR + part], b = oh[row * LPR + part];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      s = fmaf(bf16_lo_to_f32(a[i]), bf16_lo_to_f32(b[i]), s);
-      s = fmaf(bf16_hi_to_f32(a[i]), bf16_hi_to_f32(b[i]), s);
+      if (BF16) {
+        s = fmaf(bf16_lo_to_f32(a[i]), bf16_lo_to_f32(b[i]), s);
+        s = fmaf(bf16_hi_to_f32(a[i]), bf16_hi_to_f32(b[i]), s);
+      } else {
+        s = fmaf(__uint_as_float(a[i]), __uint_as_float(b[i]), s);
+      }
     }
   }
 #pragma unroll
-  for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
   if (row < rows && part == 0) {   // both negated, ready to start an accumulator from
     neg_delta[row] = -s;
-    neg_lse_over_scale[row] = -lse[row] * inv_scale;
+    if (BF16) neg_lse_over_scale[row] = -lse[row] * inv_scale;
   }
 }
 
@@ -171,7 +177,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
     int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-    if (!tok.perm) attn_bwd_delta_kernel<<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
+    if (!tok.perm) attn_bwd_delta_kernel<16, true><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
@@ -215,6 +221,30 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
           (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
           (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
           (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
+  } else if (use_f32_small(Nq, H, M)) {
+    const int64_t q_tiles = max_tiles(Nq, M, kF32SmallRows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32SmallRows) : 0;
+    const int64_t blocks = (q_tiles + k_tiles) * H;
+    if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+    if (!tok.perm) {
+      int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
+      const unsigned grid = (unsigned)((rows * (D / 4) + 255) / 256);
+      if (D == 64)
+        attn_bwd_delta_kernel<16, false><<<grid, 256, 0, st>>>((const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 0.f, delta,
+                                                               nullptr, status);
+      else
+        attn_bwd_delta_kernel<32, false><<<grid, 256, 0, st>>>((const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 0.f, delta,
+                                                               nullptr, status);
+    }
+    if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32SmallRows, ts_k);
+    if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32SmallRows, ts_q);
+#define MOGA_BWD_F32_SMALL(DD)                                                                                              \
+  attn_bwd_f32_small_kernel<DD><<<(unsigned)blocks, 64 * kF32SmallWaves, 0, st>>>(                                          \
+      (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k, ts_q, ts_k, M, Nq,   \
+      Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)(k_tiles * H), (float*)d_qh, (float*)d_kh, (float*)d_vh,        \
+      tok.perm, (float*)tok.d_q, (float*)tok.d_k, (float*)tok.d_v)
+    if (D == 64) MOGA_BWD_F32_SMALL(64);
+    else MOGA_BWD_F32_SMALL(128);
+#undef MOGA_BWD_F32_SMALL
   } else {
     {
       const int64_t tiles = max_tiles(Nq, M, kF32Rows);
@@ -296,8 +326,9 @@ extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   float* delta = (float*)ws;
+  const bool with_delta = dtype == MOGA_BF16 || use_f32_small(N, H, M);
   const RowConstants rc = {lse, 1.f / softmax_scale, delta, delta + N * (int64_t)H, (int*)((char*)ws + bwd_rows_bytes(N, H))};
-  const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, &rc, (hipStream_t)stream);
+  const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, with_delta ? &rc : nullptr, (hipStream_t)stream);
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
                          softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm},

@@ -84,14 +84,14 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // ---- host side ------------------------------------------------------------
 // true when groups of mean size rows / groups should run on the small-group bf16 attention kernels
 bool use_small_group_kernels(int64_t rows, int groups, int64_t default_threshold);
-// Row constants of the bf16 attention backward, [H, N] in sorted order, and its status word.
+// Row constants of the attention backward, [H, N] in sorted order, and its status word (fp32: -delta and the word).
 struct RowConstants {
   const float* lse;
   float inv_scale;
   float *neg_delta, *neg_lse_over_scale;
   int* status;
 };
-// moga_unpermute_bwd; rc (bf16 only): NULL, or the row constants as well
+// moga_unpermute_bwd; rc: NULL, or the row constants as well
 int launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32_t* perm, const float* gate, int64_t N, int H,
                          int D, void* d_oh, float* d_gate, const RowConstants* rc, hipStream_t st);
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }

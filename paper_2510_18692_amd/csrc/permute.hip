@@ -371,9 +371,9 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(Rows3 p, const int32_
 }
 
 // d_oh[h][j] = gate[t] * d_o[t][h],  d_gate[t] = sum_{h,c} d_o[t][h][c] * oh[h][j][c],  t = perm[j]
-// DELTA (bf16): also the row constants of the attention backward, -delta = -rowsum(d_oh * oh) (of the rounded d_oh) and
-// -lse / scale, and its status word.  Both tensors are in registers here; attn_bwd_delta_kernel reads them again (62,400 x 12
-// heads: 71 us; 10,007 x 12: 12 us, and 9.9 us more here).  Same sums in the same order as there.
+// DELTA: also the row constants of the attention backward, -delta = -rowsum(d_oh * oh) (of the rounded d_oh) and, in bf16,
+// -lse / scale, and its status word.  Both tensors are in registers here; attn_bwd_delta_kernel reads them again (10,007 x 12
+// heads: 12 us, 32,760 x 12: 38 us).  Same sums in the same order as there.
 template <int LPR, bool BF16, bool DELTA>
 __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
     const uintx4_t* __restrict__ d_o, const uintx4_t* __restrict__ oh,
@@ -406,7 +406,7 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
       if (ok[it]) {
         a[it] = d_o[(tok[it] * H + h) * LPR + part];
         b[it] = oh[((int64_t)h * N + j) * LPR + part];
-        if (DELTA) l[it] = rc.lse[(int64_t)h * N + j];
+        if (DELTA && BF16) l[it] = rc.lse[(int64_t)h * N + j];
       }
     }
 #pragma unroll
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
           for (int o = LPR / 2; o > 0; o >>= 1) dl += __shfl_xor(dl, o, kWave);
           if (part == 0) {
             rc.neg_delta[(int64_t)h * N + j] = -dl;
-            rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[it] * rc.inv_scale;
+            if (BF16) rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[it] * rc.inv_scale;
           }
         }
       }
@@ -880,7 +880,9 @@ int moga::launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const
                                                                H, (uintx4_t*)d_oh, d_gate, rc ? *rc : RowConstants{})
   if (dtype == MOGA_BF16 && rc) MOGA_UNPERMUTE_BWD(16, true, true);
   else if (dtype == MOGA_BF16) MOGA_UNPERMUTE_BWD(16, true, false);
+  else if (lpr == 16 && rc) MOGA_UNPERMUTE_BWD(16, false, true);
   else if (lpr == 16) MOGA_UNPERMUTE_BWD(16, false, false);
+  else if (rc) MOGA_UNPERMUTE_BWD(32, false, true);
   else MOGA_UNPERMUTE_BWD(32, false, false);
 #undef MOGA_UNPERMUTE_BWD
   return launch_status();
