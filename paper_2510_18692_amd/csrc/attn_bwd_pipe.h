@@ -135,13 +135,13 @@ __device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], flo
     const int row = row0 + 16 * c + r;
     if (row < ge) {
       const int64_t trow = GATHER || tok ? (int64_t)perm[row] * H + head : 0;
-      unsigned short* op = out + (GATHER ? trow : head_off + row) * kHeadDim + 4 * g;
-      unsigned short* tp = tok + trow * kHeadDim + 4 * g;
+      unsigned short* op = out + (GATHER ? trow : head_off + row) * kHeadDim + join_channel(g);
+      unsigned short* tp = tok + trow * kHeadDim + join_channel(g);
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        const uintx2_t v = pack4(acc[dt][c], f);
-        if (GATHER || out) *(uintx2_t*)(op + 16 * dt) = v;
-        if (!GATHER && tok) *(uintx2_t*)(tp + 16 * dt) = v;
+      for (int dt = 0; dt < 8; dt += 2) {
+        const uintx4_t v = join_tiles(pack4(acc[dt][c], f), pack4(acc[dt + 1][c], f));
+        if (GATHER || out) *(uintx4_t*)(op + 16 * dt) = v;
+        if (!GATHER && tok) *(uintx4_t*)(tp + 16 * dt) = v;
       }
     }
   }

@@ -315,7 +315,24 @@ __device__ __forceinline__ uintx2_t pack4(const floatx4_t& v, float f) {
   return uintx2_t{pack_bf16x2(v[0] * f, v[1] * f), pack_bf16x2(v[2] * f, v[3] * f)};
 }
 
-// Four bf16 values times f, rounded again.
+// Results of two neighbouring d tiles (dt even, dt + 1) of a column, four values of each per lane, as 16 adjacent bytes per
+// lane: lane groups g and g ^ 1 exchange halves, so that an even group ends up with eight values of tile dt and an odd one with
+// eight of tile dt + 1, from channel 16 dt + join_channel(g) on.  A store then covers 64 bytes of each of 16 rows instead of
+// 32, in half as many instructions.  Lanes of a column are active together.
+__device__ __forceinline__ uintx4_t join_tiles(uintx2_t lo, uintx2_t hi) {
+  const auto a = __builtin_amdgcn_permlane16_swap(lo[0], hi[0], false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(lo[1], hi[1], false, false);
+  return uintx4_t{a[0], b[0], a[1], b[1]};
+}
+__device__ __forceinline__ int join_channel(int g) { return 16 * (g & 1) + 4 * (g & 2); }
+
+// Eight bf16 values times f, rounded again.
+__device__ __forceinline__ uintx4_t scale8(uintx4_t v, float f) {
+  uintx4_t r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = pack_bf16x2(bf16_lo_to_f32(v[i]) * f, bf16_hi_to_f32(v[i]) * f);
+  return r;
+}
 __device__ __forceinline__ uintx2_t scale4(uintx2_t v, float f) {
   return uintx2_t{pack_bf16x2(bf16_lo_to_f32(v[0]) * f, bf16_hi_to_f32(v[0]) * f),
                   pack_bf16x2(bf16_lo_to_f32(v[1]) * f, bf16_hi_to_f32(v[1]) * f)};

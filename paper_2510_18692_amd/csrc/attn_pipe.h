@@ -204,19 +204,20 @@ __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int g
         orow = (int64_t)tok * H + head;
         inv *= gate[tok];
       }
-      unsigned short* op = oh + orow * kHeadDim + 4 * g;
+      unsigned short* op = oh + orow * kHeadDim + join_channel(g);
       unsigned short* tp = nullptr;
       float gt = 1.f;
       if (!GATHER && o_tok) {
         const int tok = perm[qrow];
-        tp = o_tok + ((int64_t)tok * H + head) * kHeadDim + 4 * g;
+        tp = o_tok + ((int64_t)tok * H + head) * kHeadDim + join_channel(g);
         gt = gate[tok];
       }
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) {
-        const uintx2_t v = pack4(quarter(st.o[dt >> 2][q], dt & 3), inv);
-        *(uintx2_t*)(op + 16 * dt) = v;
-        if (!GATHER && o_tok) *(uintx2_t*)(tp + 16 * dt) = scale4(v, gt);
+      for (int dt = 0; dt < 8; dt += 2) {
+        const floatx16_t& o = st.o[dt >> 2][q];
+        const uintx4_t v = join_tiles(pack4(quarter(o, dt & 3), inv), pack4(quarter(o, (dt & 3) + 1), inv));
+        *(uintx4_t*)(op + 16 * dt) = v;
+        if (!GATHER && o_tok) *(uintx4_t*)(tp + 16 * dt) = scale8(v, gt);
       }
       if (g == 0) lse[head_off + qrow] = st.m[q] * scale + logf(lt);
     }
