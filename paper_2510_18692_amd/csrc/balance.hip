@@ -22,15 +22,12 @@ struct BalanceAcc {
   unsigned long long count;
 };
 
-__global__ __launch_bounds__(256) void balance_accumulate_kernel(
-    const int32_t* __restrict__ group, const float* __restrict__ gate, int64_t N, int M,
-    BalanceAcc* __restrict__ acc) {
-  __shared__ unsigned long long s_sum[MOGA_MAX_GROUPS];
-  __shared__ unsigned int s_cnt[MOGA_MAX_GROUPS];
-  for (int j = threadIdx.x; j < M; j += 256) { s_sum[j] = 0ull; s_cnt[j] = 0u; }
+// Sums of the tokens t, t + stride, ... of every thread, in LDS.
+__device__ __forceinline__ void balance_sums(const int32_t* __restrict__ group, const float* __restrict__ gate, int64_t N, int M,
+                                             int64_t t, int64_t stride, unsigned long long* s_sum, unsigned int* s_cnt) {
+  for (int j = threadIdx.x; j < M; j += blockDim.x) { s_sum[j] = 0ull; s_cnt[j] = 0u; }
   __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < N; t += stride) {
+  for (; t < N; t += stride) {
     const int g = group[t];
     if (g >= 0 && g < M) {
       const long long fx = __double2ll_rn((double)gate[t] * kGateFixedScale);
@@ -39,6 +36,32 @@ __global__ __launch_bounds__(256) void balance_accumulate_kernel(
     }
   }
   __syncthreads();
+}
+
+// F, P and L from the sums, by one block.
+__device__ __forceinline__ void balance_result(unsigned long long gate_sum, unsigned long long count, int j, double inv_n, double* s_fp,
+                                               float* __restrict__ frac, float* __restrict__ prob) {
+  const double f = (double)count * inv_n;
+  const double p = (double)(long long)gate_sum / kGateFixedScale * inv_n;
+  frac[j] = (float)f;
+  prob[j] = (float)p;
+  s_fp[j] = f * p;
+}
+__device__ __forceinline__ void balance_loss_value(const double* s_fp, int M, float alpha, float* __restrict__ loss) {
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int j = 0; j < M; ++j) s += s_fp[j];
+    loss[0] = (float)((double)alpha * (double)M * s);
+  }
+}
+
+__global__ __launch_bounds__(256) void balance_accumulate_kernel(
+    const int32_t* __restrict__ group, const float* __restrict__ gate, int64_t N, int M,
+    BalanceAcc* __restrict__ acc) {
+  __shared__ unsigned long long s_sum[MOGA_MAX_GROUPS];
+  __shared__ unsigned int s_cnt[MOGA_MAX_GROUPS];
+  balance_sums(group, gate, N, M, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256, s_sum, s_cnt);
   for (int j = threadIdx.x; j < M; j += 256) {
     if (s_cnt[j]) {
       atomicAdd(&acc[j].gate_sum, s_sum[j]);
@@ -52,19 +75,23 @@ __global__ __launch_bounds__(256) void balance_finalize_kernel(
     float* __restrict__ frac, float* __restrict__ prob) {
   __shared__ double s_fp[MOGA_MAX_GROUPS];
   const double inv_n = 1.0 / (double)N;
-  for (int j = threadIdx.x; j < M; j += 256) {
-    const double f = (double)acc[j].count * inv_n;
-    const double p = (double)(long long)acc[j].gate_sum / kGateFixedScale * inv_n;
-    frac[j] = (float)f;
-    prob[j] = (float)p;
-    s_fp[j] = f * p;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int j = 0; j < M; ++j) s += s_fp[j];
-    loss[0] = (float)((double)alpha * (double)M * s);
-  }
+  for (int j = threadIdx.x; j < M; j += 256) balance_result(acc[j].gate_sum, acc[j].count, j, inv_n, s_fp, frac, prob);
+  balance_loss_value(s_fp, M, alpha, loss);
+}
+
+// All of it in one block for up to kBalanceOneBlock tokens, where the three launches (fill, accumulate, finalize) cost more than
+// the work.  The same integers, so the same bits.
+constexpr int64_t kBalanceOneBlock = 8192;
+__global__ __launch_bounds__(1024) void balance_one_block_kernel(
+    const int32_t* __restrict__ group, const float* __restrict__ gate, int64_t N, int M, float alpha, float* __restrict__ loss,
+    float* __restrict__ frac, float* __restrict__ prob) {
+  __shared__ unsigned long long s_sum[MOGA_MAX_GROUPS];
+  __shared__ unsigned int s_cnt[MOGA_MAX_GROUPS];
+  __shared__ double s_fp[MOGA_MAX_GROUPS];
+  balance_sums(group, gate, N, M, threadIdx.x, 1024, s_sum, s_cnt);
+  const double inv_n = 1.0 / (double)N;
+  for (int j = threadIdx.x; j < M; j += 1024) balance_result(s_sum[j], s_cnt[j], j, inv_n, s_fp, frac, prob);
+  balance_loss_value(s_fp, M, alpha, loss);
 }
 
 __global__ __launch_bounds__(256) void balance_bwd_kernel(
@@ -100,6 +127,10 @@ extern "C" int moga_balance_loss(const int32_t* group, const float* gate, int64_
   if (!group || !gate) return MOGA_ERR_INVALID_ARG;
   if (!ws || ws_bytes < moga_balance_ws_bytes(M)) return MOGA_ERR_WORKSPACE;
   if (!aligned16(ws)) return MOGA_ERR_INVALID_ARG;
+  if (N <= kBalanceOneBlock) {
+    balance_one_block_kernel<<<1, 1024, 0, st>>>(group, gate, N, M, alpha, loss, frac, prob);
+    return launch_status();
+  }
   BalanceAcc* acc = (BalanceAcc*)ws;
   const int64_t ws_floats = (int64_t)(moga_balance_ws_bytes(M) / sizeof(float));
   fill_zero_kernel<<<(unsigned)((ws_floats + 255) / 256), 256, 0, st>>>((float*)ws, ws_floats);
