@@ -301,6 +301,89 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t
   }
 }
 
+// Sort and gather in one launch, for up to 4,096 tokens and 32 groups.  A block moves the rows of 16 tokens of one tensor and
+// finds their slots by itself: it counts the ids of all tokens and of those before its own (a few per thread, 8-bit counters
+// packed four to a word, summed over the waves), which costs about a microsecond while its rows are on the way.  The sort as a
+// launch of its own was one block, and the chip waited for it.
+constexpr int64_t kFusedSortTokens = 4096;
+
+template <int LPR, int WORDS, int PER>   // WORDS * 4 >= groups, PER * 256 >= tokens
+__global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int32_t* __restrict__ group, int N, int H, int M, int nbits,
+                                                             int32_t* __restrict__ counts, int32_t* __restrict__ cu_seqlens,
+                                                             int32_t* __restrict__ max_seqlen, int32_t* __restrict__ perm,
+                                                             int32_t* __restrict__ inv_perm) {
+  constexpr int RPW = 64 / LPR;  // rows per wave instruction
+  constexpr int IT = kSlotsPerBlock / RPW;
+  __shared__ int s_sum[4][2][2 * WORDS];   // per wave: all tokens, those before the block's; groups 4 w + f and 4 w + f + 2 at 2 w + f
+  __shared__ int s_count[4 * WORDS], s_cu[4 * WORDS];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int part = lane % LPR, rsub = lane / LPR;
+  const int t0 = blockIdx.x * kSlotsPerBlock;
+  const uintx4_t* __restrict__ src = (const uintx4_t*)p.src[blockIdx.y];
+  uintx4_t* __restrict__ dst = (uintx4_t*)p.dst[blockIdx.y];
+  int id[PER];   // all ids in flight together, then the rows
+#pragma unroll
+  for (int i = 0; i < PER; ++i) id[i] = group[min(256 * i + (int)threadIdx.x, N - 1)];
+  const bool own = lane < kSlotsPerBlock && t0 + lane < N;
+  const int g = clamp_group(group[min(t0 + (lane & (kSlotsPerBlock - 1)), N - 1)], M);
+  uintx4_t v[IT];
+  auto load_rows = [&](int h) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it) v[it] = src[((int64_t)min(t0 + it * RPW + rsub, N - 1) * H + h) * LPR + part];
+  };
+  if (wave < H) load_rows(wave);
+
+  unsigned all[WORDS], before[WORDS];
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) all[w] = before[w] = 0u;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int t = 256 * i + threadIdx.x, k = clamp_group(id[i], M);
+    const unsigned one = t < N ? 1u << (8 * (k & 3)) : 0u, b = t < t0 ? one : 0u;
+#pragma unroll
+    for (int w = 0; w < WORDS; ++w) {
+      all[w] += (k >> 2) == w ? one : 0u;
+      before[w] += (k >> 2) == w ? b : 0u;
+    }
+  }
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {   // two 16-bit sums at once: at most 1,024 per wave
+      const int x = wave_scan_add((int)((all[w] >> (8 * f)) & 0x00ff00ffu));
+      const int y = wave_scan_add((int)((before[w] >> (8 * f)) & 0x00ff00ffu));
+      if (lane == 63) { s_sum[wave][0][2 * w + f] = x; s_sum[wave][1][2 * w + f] = y; }
+    }
+  const int rank = __popcll(match_group(g, own, nbits) & ((1ull << lane) - 1ull));
+  __syncthreads();
+  int sum[2] = {0, 0};   // of group `lane`; every wave for itself
+  if (lane < 4 * WORDS) {
+    const int idx = 2 * (lane >> 2) + (lane & 1), shift = 8 * (lane & 2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) sum[b] += (s_sum[k][b][idx] >> shift) & 0xffff;
+  }
+  const int base = wave_scan_add(sum[0]) - sum[0] + sum[1];
+  const int slot = __shfl(base, g, kWave) + rank;   // lane i < 16: of token t0 + i
+  if (blockIdx.y == 0 && wave == 0) {
+    if (own) { perm[slot] = t0 + lane; inv_perm[t0 + lane] = slot; }
+    if (blockIdx.x == 0) {
+      if (lane < 4 * WORDS) s_count[lane] = sum[0];
+      scan_groups(s_count, s_cu, M, counts, cu_seqlens, max_seqlen);
+    }
+  }
+  int64_t to[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) to[it] = (int64_t)__shfl(slot, it * RPW + rsub, kWave) * LPR + part;
+  for (int h = wave; h < H; h += 4) {
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+      if (t0 + it * RPW + rsub < N) dst[(int64_t)h * N * LPR + to[it]] = v[it];
+    if (h + 4 < H) load_rows(h + 4);
+  }
+}
+
 template <bool BF16>
 __device__ __forceinline__ uintx4_t scale16(uintx4_t v, float g) {
   uintx4_t r;
@@ -715,6 +798,24 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int chunk_len = perm_chunk_len(N);
   const int num_chunks = perm_num_chunks(N);
   const int nbits = bits_for(M);
+  if (with_data && N > 0 && N <= kFusedSortTokens && M <= kSingleBlockGroups) {
+    const Rows3 p = {{q, k, v}, {qh, kh, vh}};
+    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), 3);
+#define MOGA_PERMUTE_GATHER(LPR, WORDS, PER)                                                                                  \
+  permute_gather_kernel<LPR, WORDS, PER><<<grid, 256, 0, st>>>(p, group, (int)N, H, M, nbits, counts, cu_seqlens, max_seqlen, \
+                                                               perm, inv_perm)
+#define MOGA_PERMUTE_GATHER_N(LPR, WORDS)                         \
+  if (N <= 2048) MOGA_PERMUTE_GATHER(LPR, WORDS, 8);              \
+  else MOGA_PERMUTE_GATHER(LPR, WORDS, 16)
+    if (lanes_per_row(dtype, D) == 16) {
+      if (M <= 8) { MOGA_PERMUTE_GATHER_N(16, 2); } else { MOGA_PERMUTE_GATHER_N(16, 8); }
+    } else {
+      if (M <= 8) { MOGA_PERMUTE_GATHER_N(32, 2); } else { MOGA_PERMUTE_GATHER_N(32, 8); }
+    }
+#undef MOGA_PERMUTE_GATHER_N
+#undef MOGA_PERMUTE_GATHER
+    return launch_status();
+  }
   if (N <= kSingleBlockTokens && M <= kSingleBlockGroups) {
 #define MOGA_PERMUTE_ONE(PER) \
   permute_single_block_kernel<PER><<<1, 1024, 0, st>>>(group, (int)N, M, counts, cu_seqlens, max_seqlen, perm, inv_perm)
