@@ -169,6 +169,133 @@ __device__ __forceinline__ void route_mfma_block(floatx16_t (&acc)[TT],
   }
 }
 
+// argmax, softmax and stores of one 32-token tile: accumulator register v of lane (r, h) is group row 8*(v/4) + 4*h + v%4 of
+// token `tok`, the tile's r-th.
+__device__ __forceinline__ void route_finish(const floatx16_t& total, int64_t tok, int h, const float* __restrict__ bias, int64_t N,
+                                             int M, int32_t* __restrict__ group, float* __restrict__ gate, float* __restrict__ probs,
+                                             float* __restrict__ logits) {
+  const bool vec4 = (M & 3) == 0 && (((uintptr_t)probs | (uintptr_t)logits) & 15) == 0;
+  float vals[16];
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+    float val = total[v];
+    if (row < M) {
+      if (bias) val += bias[row];
+    } else {
+      val = -INFINITY;
+    }
+    vals[v] = val;
+    if (val > best) { best = val; bi = row; }
+  }
+  const float ob = other_half(best);
+  const int oi = other_half_i(bi);
+  if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+  float sum = 0.f;
+  float e[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) { e[v] = expf(vals[v] - best); sum += e[v]; }
+  sum += other_half(sum);
+  const float g = 1.f / sum;
+  if (tok < N) {
+    if (h == 0) { group[tok] = bi; gate[tok] = g; }
+    if (vec4) {   // a lane's registers 4q .. 4q+3 are four consecutive groups: one 16-byte store
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = 8 * q + 4 * h;
+        if (row < M) {
+          if (probs) {
+            const floatx4_t pv = {e[4 * q] * g, e[4 * q + 1] * g, e[4 * q + 2] * g, e[4 * q + 3] * g};
+            *(floatx4_t*)(probs + tok * M + row) = pv;
+          }
+          if (logits) {
+            const floatx4_t lv = {vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
+            *(floatx4_t*)(logits + tok * M + row) = lv;
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = 8 * (v >> 2) + 4 * h + (v & 3);
+        if (row < M) {
+          if (probs) probs[tok * M + row] = e[v] * g;
+          if (logits) logits[tok * M + row] = vals[v];
+        }
+      }
+    }
+  }
+}
+
+// Few tokens: a block per 32 tokens, whose waves share the k blocks (wave w takes w, w + NWV, ..) and add their logits through
+// LDS.  W goes from L2 straight to registers and is split there.  The kernel below has 128 tokens per block and walks all of W
+// with a barrier per chunk: at 1,560 tokens its 13 blocks took as long as a full chip.  Theirs against ours: 1,560 x 512, 8
+// groups 9.6 and 5.4 us, 1,560 x 1536, 16 groups 18.7 and 9.9, 8,192 x 5120, 16 groups 60 and 29, 16,384 x 1536, 8 groups 21.6
+// and 14.8; 24,000 x 1536, 20 groups 24.2 and 26.1, from where splitting W for every 32 tokens costs more.
+template <int NWV>
+__global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
+    const unsigned short* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias, int64_t N, int d, int M,
+    int32_t* __restrict__ group, float* __restrict__ gate, float* __restrict__ probs, float* __restrict__ logits) {
+  __shared__ float s_tot[NWV][16][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = lane & 31, h = lane >> 5;
+  const int64_t tok = (int64_t)blockIdx.x * 32 + r;
+  const unsigned short* xr = x + min(tok, N - 1) * (int64_t)d + 32 * h;
+  const float* wr = w + (int64_t)min(r, M - 1) * d + 32 * h;
+  const bool row = r < M;   // rows of W beyond M count as zero
+
+  floatx16_t total;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) total[v] = 0.f;
+  uintx4_t xv[4];
+  floatx4_t wv[8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) xv[s] = *(const uintx4_t*)(xr + k0 + 8 * s);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) wv[s] = *(const floatx4_t*)(wr + k0 + 4 * s);
+  };
+  if (64 * wave < d) load(64 * wave);
+  for (int k0 = 64 * wave; k0 < d; k0 += 64 * NWV) {
+    floatx16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      uintx4_t limb[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float w0 = wv[2 * s + (e >> 1)][2 * (e & 1)], w1 = wv[2 * s + (e >> 1)][2 * (e & 1) + 1];
+        if (!row) w0 = w1 = 0.f;
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {   // as split3: what is left after each limb is exact
+          limb[l][e] = pack_bf16x2(w0, w1);
+          w0 -= bf16_lo_to_f32(limb[l][e]);
+          w1 -= bf16_hi_to_f32(limb[l][e]);
+        }
+      }
+#pragma unroll
+      for (int l = 0; l < 3; ++l)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, limb[l]), __builtin_bit_cast(bf16x8_t, xv[s]), acc, 0, 0, 0);
+    }
+    if (k0 + 64 * NWV < d) load(k0 + 64 * NWV);
+    total += acc;   // short chains
+  }
+#pragma unroll
+  for (int v = 0; v < 16; ++v) s_tot[wave][v][lane] = total[v];
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+#pragma unroll
+    for (int k = 1; k < NWV; ++k) total[v] += s_tot[k][v][lane];
+  route_finish(total, tok, h, bias, N, M, group, gate, probs, logits);
+}
+
+constexpr int64_t kRouteFewTokens = 16384;
+
 // The weight chunk is double-buffered: while the matrix cores work on chunk c, the fp32 weights of
 // chunk c+1 are in flight from L2; they are split and stored after the chunk's MFMAs, one block
 // barrier per chunk.  X lives in a ring of four k-block register sets with fixed roles (the loop
@@ -235,64 +362,8 @@ __global__ __launch_bounds__(64 * NWV, 2) void route_mfma_kernel(
   }
 #undef MOGA_ROUTE_CHUNK
 
-  // Epilogue: accumulator register v of lane (r, h) is group row 8*(v/4) + 4*h + v%4 of token r.
-  const bool vec4 = (M & 3) == 0 && (((uintptr_t)probs | (uintptr_t)logits) & 15) == 0;
 #pragma unroll
-  for (int t = 0; t < TT; ++t) {
-    const int64_t tok = tok0 + 32 * t + r;
-    float vals[16];
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = 8 * (v >> 2) + 4 * h + (v & 3);
-      float val = total[t][v];
-      if (row < M) {
-        if (bias) val += bias[row];
-      } else {
-        val = -INFINITY;
-      }
-      vals[v] = val;
-      if (val > best) { best = val; bi = row; }
-    }
-    const float ob = other_half(best);
-    const int oi = other_half_i(bi);
-    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-    float sum = 0.f;
-    float e[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { e[v] = expf(vals[v] - best); sum += e[v]; }
-    sum += other_half(sum);
-    const float g = 1.f / sum;
-    if (tok < N) {
-      if (h == 0) { group[tok] = bi; gate[tok] = g; }
-      if (vec4) {   // a lane's registers 4q .. 4q+3 are four consecutive groups: one 16-byte store
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = 8 * q + 4 * h;
-          if (row < M) {
-            if (probs) {
-              const floatx4_t pv = {e[4 * q] * g, e[4 * q + 1] * g, e[4 * q + 2] * g, e[4 * q + 3] * g};
-              *(floatx4_t*)(probs + tok * M + row) = pv;
-            }
-            if (logits) {
-              const floatx4_t lv = {vals[4 * q], vals[4 * q + 1], vals[4 * q + 2], vals[4 * q + 3]};
-              *(floatx4_t*)(logits + tok * M + row) = lv;
-            }
-          }
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = 8 * (v >> 2) + 4 * h + (v & 3);
-          if (row < M) {
-            if (probs) probs[tok * M + row] = e[v] * g;
-            if (logits) logits[tok * M + row] = vals[v];
-          }
-        }
-      }
-    }
-  }
+  for (int t = 0; t < TT; ++t) route_finish(total[t], tok0 + 32 * t + r, h, bias, N, M, group, gate, probs, logits);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -701,6 +772,10 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
       const unsigned blocks = (unsigned)((N + 255) / 256);
       route_mfma_kernel<1, 8><<<blocks, 512, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                      group, gate, probs, logits);
+    } else if (N <= kRouteFewTokens) {
+      const unsigned blocks = (unsigned)((N + 31) / 32);
+      route_mfma_few_kernel<4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
+                                                       group, gate, probs, logits);
     } else {
       const unsigned blocks = (unsigned)((N + 127) / 128);
       route_mfma_kernel<1, 4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
