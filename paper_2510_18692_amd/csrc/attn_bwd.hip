@@ -47,8 +47,7 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const uintx4_t* __r
       }
     }
   }
-#pragma unroll
-  for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  s = lanes_sum<LPR>(s);
   if (row < rows && part == 0) {   // both negated, ready to start an accumulator from
     neg_delta[row] = -s;
     if (BF16) neg_lse_over_scale[row] = -lse[row] * inv_scale;
@@ -95,8 +94,7 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
         s = fmaf(bf16_lo_to_f32(a[i]), bf16_lo_to_f32(b[i]), s);
         s = fmaf(bf16_hi_to_f32(a[i]), bf16_hi_to_f32(b[i]), s);
       }
-#pragma unroll
-      for (int o2 = 8; o2 > 0; o2 >>= 1) s += __shfl_xor(s, o2, kWave);
+      s = lanes_sum<16>(s);
       const float dg = s / g[it];
       acc[it] += dg;
       if (part == 0) {

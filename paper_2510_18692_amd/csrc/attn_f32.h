@@ -307,8 +307,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void attn_bwd_dq_f32_mfma_kernel(
     float s = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; ++e) s = fmaf(a[e], b[e], s);
-#pragma unroll
-    for (int q = LPR / 2; q > 0; q >>= 1) s += __shfl_xor(s, q, kWave);
+    s = lanes_sum<LPR>(s);
     if (i % LPR == 0) {
       s_delta[row] = s;
       if (first + row <= last) delta[first + row] = s;

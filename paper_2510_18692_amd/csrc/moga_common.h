@@ -41,22 +41,48 @@ __device__ __forceinline__ unsigned short f32_to_bf16_bits(float f) {
   return (unsigned short)(pack_bf16x2(f, 0.f) & 0xffffu);
 }
 
-// Butterfly reductions over the 64 lanes of a wave.
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+// Butterfly reductions over L = 16, 32 or 64 neighbouring lanes (distances L / 2 .. 1) with cross-lane data paths of the vector
+// unit.  (__shfl_xor goes through LDS, some 120 cycles a step: the fp32 router at 4,096 x 128, 8 groups and the row sums of the
+// scatter backward wait for little else.)  All L lanes are active.
+template <int CTRL>
+__device__ __forceinline__ int dpp_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false); }
+// The value X lanes away (xor), X = 1, 2, 4, 8.
+template <int X>
+__device__ __forceinline__ int xor_lane(int v) {
+  if (X == 8) return dpp_lane<0x128>(v);                  // rotation of a row of 16 by 8
+  if (X == 4) return dpp_lane<0x1b>(dpp_lane<0x141>(v));  // 7 - i of eight, then 3 - i of four
+  return X == 2 ? dpp_lane<0x4e>(v) : dpp_lane<0xb1>(v);  // within four lanes
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-  return v;
+template <int X, typename F>
+__device__ __forceinline__ int combine_xor(int v, F f) {
+  if constexpr (X == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // the lower halves, the upper halves
+    return f((int)r[0], (int)r[1]);
+  } else if constexpr (X == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // the even rows, the odd rows
+    return f((int)r[0], (int)r[1]);
+  } else {
+    return f(v, xor_lane<X>(v));
+  }
 }
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-  return v;
+template <int L, typename F>
+__device__ __forceinline__ int lanes_reduce(int v, F f) {
+  if constexpr (L >= 64) v = combine_xor<32>(v, f);
+  if constexpr (L >= 32) v = combine_xor<16>(v, f);
+  v = combine_xor<8>(v, f);
+  v = combine_xor<4>(v, f);
+  v = combine_xor<2>(v, f);
+  return combine_xor<1>(v, f);
 }
+struct AddF { __device__ int operator()(int a, int b) const { return __float_as_int(__int_as_float(a) + __int_as_float(b)); } };
+struct MaxF { __device__ int operator()(int a, int b) const { return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b))); } };
+struct AddI { __device__ int operator()(int a, int b) const { return a + b; } };
+struct MaxI { __device__ int operator()(int a, int b) const { return a > b ? a : b; } };
+template <int L> __device__ __forceinline__ float lanes_sum(float v) { return __int_as_float(lanes_reduce<L>(__float_as_int(v), AddF{})); }
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<64>(v); }
+__device__ __forceinline__ float wave_max(float v) { return __int_as_float(lanes_reduce<64>(__float_as_int(v), MaxF{})); }
+__device__ __forceinline__ int wave_sum_i(int v) { return lanes_reduce<64>(v, AddI{}); }
+__device__ __forceinline__ int wave_max_i(int v) { return lanes_reduce<64>(v, MaxI{}); }
 
 // Inclusive sum over the lanes of a wave with cross-lane data paths of the vector unit (no LDS).
 __device__ __forceinline__ int wave_scan_add(int x) {

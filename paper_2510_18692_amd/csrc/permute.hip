@@ -87,8 +87,7 @@ __device__ __forceinline__ void scan_groups(const int* s_count, int* s_cu, int M
     running = __builtin_amdgcn_readlane(incl, 63);
     mx = max(mx, v);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+  mx = wave_max_i(mx);
   if (lane == 0) {
     cu_seqlens[M] = running;
     max_seqlen[0] = mx;
@@ -501,8 +500,7 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
         d_oh[((int64_t)h * N + j) * LPR + part] = s;
         if (DELTA) {
           float dl = dot16<BF16>(s, b[it]);
-#pragma unroll
-          for (int o = LPR / 2; o > 0; o >>= 1) dl += __shfl_xor(dl, o, kWave);
+          dl = lanes_sum<LPR>(dl);
           if (part == 0) {
             rc.neg_delta[(int64_t)h * N + j] = -dl;
             if (BF16) rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[it] * rc.inv_scale;
@@ -514,9 +512,7 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
   // reduce over the LPR lanes of a row, then over the four waves
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    float s = acc[it];
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+    const float s = lanes_sum<LPR>(acc[it]);
     if (part == 0) s_part[wave][it * RPW + rsub] = s;
   }
   __syncthreads();
@@ -732,9 +728,7 @@ __global__ __launch_bounds__(256) void merge3_bwd_kernel(
   }
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
-    float s = acc[it];
-#pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+    const float s = lanes_sum<LPR>(acc[it]);
     if (part == 0) s_part[wave][it * RPW + rsub] = s;
   }
   __syncthreads();

@@ -65,12 +65,9 @@ __global__ __launch_bounds__(256) void route_generic_kernel(
     const float r = s_logit[wave][j];
     if (r > best) { best = r; bi = j; }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ob = __shfl_xor(best, o, kWave);
-    const int oi = __shfl_xor(bi, o, kWave);
-    if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-  }
+  const float top = wave_max(best);
+  bi = lanes_reduce<64>(best == top ? bi : 0x7fffffff, [](int a, int b) { return a < b ? a : b; });
+  best = top;
   float sum = 0.f;
   for (int j = lane; j < M; j += 64) sum += expf(s_logit[wave][j] - best);
   sum = wave_sum(sum);
