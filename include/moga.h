@@ -342,6 +342,20 @@ int moga_gather_rows_bwd(const void* d_dst, int dtype, const int32_t* inv_cu, co
                          int64_t N, int64_t Nk, int H, int D, int accumulate, void* d_src, void* stream);
 
 /*
+ * Q, K and V to all three branches of Section 3.2 in one launch, every row read once (q, k, v [N, H, D] token order):
+ *   qm[h][inv_moga[t]] = q[t][h]                 (as the gather of moga_permute; inv_moga is its inv_perm; km, vm alike)
+ *   qs[h][q_slot[t]] = q[t][h]                   qs [H, N, D]
+ *   ks[h][j] = k[t][h] for every slot j that lists token t (inv_cu, inv_slots as for moga_gather_rows_bwd); ks, vs [H, Nk, D]
+ *   qf[h][inv_frame[t]] = q[t][h]                (inv_frame NULL: the identity; kf, vf alike)
+ * The same bytes as moga_permute's gather and six moga_gather_rows calls.
+ */
+int moga_gather3_fwd(const void* q, const void* k, const void* v, int dtype, int64_t N, int H, int D,
+                     const int32_t* inv_moga, const int32_t* q_slot, const int32_t* inv_cu, const int32_t* inv_slots,
+                     int64_t Nk, const int32_t* inv_frame_or_null,
+                     void* qm, void* km, void* vm, void* qs, void* ks, void* vs, void* qf, void* kf, void* vf,
+                     void* stream);
+
+/*
  * Gradient of a token-order tensor (Q, K or V) that fed all three branches of Section 3.2, in one
  * pass:  d_src[t][h][:] = g_moga[h][inv_moga[t]][:]
  *                         + sum of g_stga[h][j][:] over the slots j that list token t

@@ -66,6 +66,8 @@ _SIGNATURES = {
                                      _vp, _vp]),
     "moga_gather_rows": (_i32, [_vp, _i32, _vp, _i64, _i32, _i32, _vp, _vp]),
     "moga_gather_rows_bwd": (_i32, [_vp, _i32, _vp, _vp, _i64, _i64, _i32, _i32, _i32, _vp, _vp]),
+    "moga_gather3_fwd": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _vp, _vp, _vp,
+                                _vp, _vp, _vp, _vp, _vp]),
     "moga_gather3_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp]),
     "moga_merge3_fwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp]),
     "moga_merge3_bwd": (_i32, [_vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
@@ -313,6 +315,11 @@ def moga_gather_rows_bwd(d_dst, inv_cu, inv_slots, N, d_src=None, stream=None):
     return _nat.gather_rows_bwd(d_dst, inv_cu, inv_slots, N, d_src, _st(stream))
 
 
+def moga_gather3_fwd(q, k, v, inv_moga, q_slot, inv_cu, inv_slots, inv_frame=None, stream=None):
+    """q, k, v [N, H, D] -> (qm, km, vm [H, N, D], qs [H, N, D], ks, vs [H, Nk, D], qf, kf, vf [H, N, D]) in one launch."""
+    return _nat.gather3_fwd(q, k, v, inv_moga, q_slot, inv_cu, inv_slots, inv_frame, _st(stream))
+
+
 def moga_gather3_bwd(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame=None, stream=None):
     """g_moga, g_frame [H, N, D], g_stga [H, Nk, D] -> their token-order sum [N, H, D] (one pass)."""
     return _nat.gather3_bwd(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame, _st(stream))
@@ -370,19 +377,17 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
     si = static_index
     dev = q.device
     group, gate, probs, _ = moga_route(x, w, want_probs=True, stream=stream)
-    pm = moga_permute(group, w.shape[0], q, k, v, stream=stream)
+    pm = moga_permute(group, w.shape[0], stream=stream)
+    pm["qh"], pm["kh"], pm["vh"], qs, ks, vs, qf, kf, vf = moga_gather3_fwd(q, k, v, pm["inv_perm"], si["q_slot"], si["inv_cu"],
+                                                                            si["inv_slots"], stream=stream)
     a_m, lse_m = moga_group_attn_fwd(pm["qh"], pm["kh"], pm["vh"], pm["cu_seqlens"], softmax_scale, stream=stream)
-    qs = moga_gather_rows(q, si["q_index"], stream=stream)
-    ks = moga_gather_rows(k, si["kv_index"], stream=stream)
-    vs = moga_gather_rows(v, si["kv_index"], stream=stream)
     a_s, lse_s = moga_varlen_attn_fwd(qs, ks, vs, si["cu_q"], si["cu_k"], softmax_scale, stream=stream)
     ident = torch.arange(N + 1, dtype=torch.int32, device=dev)
-    cu_f = torch.arange(T + 1, dtype=torch.int32, device=dev) * (Hh * Ww)
+    cu_f = torch.arange(0, N + 1, Hh * Ww, dtype=torch.int32, device=dev)
     if stream is not None and stream != torch.cuda.current_stream():   # made on the current stream, read on `stream`
         stream.wait_stream(torch.cuda.current_stream())
         for t in (ident, cu_f):
             t.record_stream(stream)
-    qf, kf, vf = (moga_gather_rows(t, ident[:N], stream=stream) for t in (q, k, v))
     a_f, lse_f = moga_varlen_attn_fwd(qf, kf, vf, cu_f, cu_f, softmax_scale, stream=stream)
     o = moga_merge3_fwd(a_m, a_s, a_f, pm["inv_perm"], si["q_slot"], None, gate, stream=stream)
     return {"o": o, "group": group, "gate": gate, "probs": probs, "pm": pm, "a_m": a_m, "lse_m": lse_m,

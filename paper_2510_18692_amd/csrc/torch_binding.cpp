@@ -363,6 +363,23 @@ Tensor gather_rows_bwd(const Tensor& d_dst, const Tensor& inv_cu, const Tensor& 
   return d_src;
 }
 
+py::tuple gather3_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& inv_moga, const Tensor& q_slot, const Tensor& inv_cu,
+                      const Tensor& inv_slots, const OptTensor& inv_frame, const OptStream& stream) {
+  Tensor t[9];
+  {
+    py::gil_scoped_release nogil;
+    require(q, k, v, inv_moga, q_slot, inv_cu, inv_slots, inv_frame);
+    const Call call(stream);
+    need_dims(q, 3);
+    const int64_t N = q.size(0), H = q.size(1), D = q.size(2), Nk = inv_slots.size(0);
+    for (int i = 0; i < 9; ++i) t[i] = call.make({H, i == 4 || i == 5 ? Nk : N, D}, i % 3 == 0 ? q : i % 3 == 1 ? k : v);
+    check("moga_gather3_fwd", moga_gather3_fwd(ptr(q), ptr(k), ptr(v), dt(q), N, (int)H, (int)D, as<int32_t>(inv_moga), as<int32_t>(q_slot),
+                                               as<int32_t>(inv_cu), as<int32_t>(inv_slots), Nk, as<int32_t>(inv_frame), ptr(t[0]), ptr(t[1]),
+                                               ptr(t[2]), ptr(t[3]), ptr(t[4]), ptr(t[5]), ptr(t[6]), ptr(t[7]), ptr(t[8]), call.stream()));
+  }
+  return py::make_tuple(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7], t[8]);
+}
+
 Tensor gather3_bwd(const Tensor& g_moga, const Tensor& inv_moga, const Tensor& g_stga, const Tensor& inv_cu, const Tensor& inv_slots,
                    const Tensor& g_frame, const OptTensor& inv_frame, const OptStream& stream) {
   require(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame);
@@ -520,6 +537,7 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("varlen_attn_bwd", &varlen_attn_bwd, nogil);
   m.def("gather_rows", &gather_rows, nogil);
   m.def("gather_rows_bwd", &gather_rows_bwd, nogil);
+  m.def("gather3_fwd", &gather3_fwd);
   m.def("gather3_bwd", &gather3_bwd, nogil);
   m.def("merge3_fwd", &merge3_fwd, nogil);
   m.def("merge3_bwd", &merge3_bwd, nogil);
