@@ -328,17 +328,21 @@ struct AbLane {
   unsigned p_addr;      // this lane's 16 bytes in the pair's P buffer (unit 0, key half 0)
 };
 
-// scores of one 32-query unit ([query operand t][key half]): started from the per-row constants
+// Row fragments and row constants of one 32-query unit.
 template <int SOFF, int SROW>
-__device__ __forceinline__ void ab_scores(const AbLane& ln, unsigned off, unsigned off_row,
-                                          const bf16x8_t (&kvf)[2][4], StepScores& acc) {
-  bf16x8_t nat[2][4];
+__device__ __forceinline__ void ab_load_nat(const AbLane& ln, unsigned off, unsigned off_row, bf16x8_t (&nat)[2][4], floatx4_t (&ini)[2]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t) ini[t] = lds_read_f32x4(ln.init_addr + off_row + SROW + t * 16);
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int t = 0; t < 2; ++t) nat[t][ks] = lds_read_b128(ln.nat[ks] + off + SOFF + t * kRow4Bytes);
+}
+// Its scores ([query operand t][key half]), started from the constants.
+__device__ __forceinline__ void ab_scores(const bf16x8_t (&nat)[2][4], const floatx4_t (&ini)[2],
+                                          const bf16x8_t (&kvf)[2][4], StepScores& acc) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = lds_read_f32x4(ln.init_addr + off_row + SROW + t * 16);
+  for (int t = 0; t < 2; ++t) acc[t][0] = acc[t][1] = ini[t];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
@@ -401,7 +405,19 @@ __device__ __forceinline__ void ab_take_p(const AbLane& ln, const StepScores& dp
   }
 }
 
-// One 64-query tile for either role (role is wave-uniform; the common parts are written once so that
+// Waits until *flag reaches `value`; after `spin_limit` polls it records a give-up in *status and goes on.
+__device__ __forceinline__ void spin_until(int* flag, int value, int spin_limit, int* status) {
+  int polls = 0;
+  while (__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < value) {
+    if (++polls > spin_limit) {   // wave-uniform
+      if ((threadIdx.x & 63) == 0) atomicOr(status, 1);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+}
+
+// One 64-query tile of the two-slot kernel for either role (role is wave-uniform; the common parts are written once so that
 // the two roles share one instruction stream, with one short role-specific piece in the middle):
 //   A: S(u0), S(u1) | P -> LDS, stamp          | dV(u0), dV(u1)
 //   B: dP(u0), dP(u1) | wait for the stamp, dS = P * dP | dK(u0), dK(u1)
@@ -411,40 +427,92 @@ __device__ __forceinline__ void ab_take_p(const AbLane& ln, const StepScores& dp
 // Progress does not depend on the bound: A publishes the stamp of tile t before it reaches the
 // block barrier of tile t + 1 and never waits for B anywhere else, and the single P buffer of a
 // pair is only rewritten after that barrier, which B reaches only after it has consumed P.
-template <bool PRIO, bool MASK, int SOFF, int SROW>
+template <bool MASK, int SOFF, int SROW>
 __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off, unsigned off_row,
                                         const bf16x8_t (&kvf)[2][4], floatx4_t (&acc)[8][2], float c, int g, int left,
                                         int* flag, int tile_no, int spin_limit, int* status) {
   StepScores sc[2];      // S (A) or dP (B) of the two 32-query units
   bf16x8_t bop[2][2];    // B operand of the second product: P (A) or dS (B), per unit and key half
   bf16x8_t tr0[8], tr1[8];
-  ab_scores<SOFF, SROW>(ln, off, off_row, kvf, sc[0]);
-  ab_scores<SOFF + 8192, SROW + 128>(ln, off, off_row, kvf, sc[1]);
+  bf16x8_t nat0[2][4], nat1[2][4];
+  floatx4_t ini0[2], ini1[2];
+  ab_load_nat<SOFF, SROW>(ln, off, off_row, nat0, ini0);   // all fragments on their way before the first product
+  ab_load_nat<SOFF + 8192, SROW + 128>(ln, off, off_row, nat1, ini1);
+  __builtin_amdgcn_sched_barrier(0);
+  ab_scores(nat0, ini0, kvf, sc[0]);
+  __builtin_amdgcn_sched_barrier(0);
   ab_load_tr<SOFF>(ln, off, tr0);   // in flight while P is computed (A) or awaited (B)
+  ab_scores(nat1, ini1, kvf, sc[1]);
   __builtin_amdgcn_sched_barrier(0);
   if (role == 0) {
     ab_make_p<MASK>(ln, sc[0], c, g, left, 0, bop[0]);
     ab_make_p<MASK>(ln, sc[1], c, g, left, 1, bop[1]);
     __hip_atomic_store(flag, tile_no, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);   // P of this tile is in LDS
   } else {
-    int polls = 0;
-    while (__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < tile_no) {
-      if (++polls > spin_limit) {   // wave-uniform
-        if ((threadIdx.x & 63) == 0) atomicOr(status, 1);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
+    spin_until(flag, tile_no, spin_limit, status);
     ab_take_p(ln, sc[0], 0, bop[0]);
     ab_take_p(ln, sc[1], 1, bop[1]);
   }
   ab_load_tr<SOFF + 8192>(ln, off, tr1);   // in flight while the first unit is accumulated
-  // The second products go first: they free the wave for the next barrier, which both partners wait at.  With the
-  // priorities of the dQ kernel 593 -> 582 ms at 580,320 x 40 heads (scores first instead: no gain).
-  wave_priority<PRIO, 1>();
   ab_accumulate(tr0, bop[0], acc);
   ab_accumulate(tr1, bop[1], acc);
-  wave_priority<PRIO, 0>();
+}
+
+// The tile of the four-slot kernel.  Its first row fragments (nat0, ini0) were read during the tile before, and the block barrier
+// (`barrier`, which also waits for the next tile and issues a later one) stands where P is ready: it is the hand-over of P, and
+// behind it the next tile's first fragments are read under the second products, so that no wave starts a tile with its matrix
+// pipe waiting for LDS.  With the barrier at the start of the tile and a flag for P: 13.0 against 12.4-12.7 ms for the whole
+// backward at 62,400 x 12 heads, 5 groups, 2.34 against 2.27-2.31 at 32,760 x 12, 8 groups, 574 against 562 at 580,320 x 40, 32
+// groups.  (Tried on top, no gain: B one tile behind A; the same pipeline in the dQ kernel and in the forward, 0.5 to 1 % slower.)
+//   A: S | wait until B has taken the P before, P -> LDS | barrier | dV
+//   B: dP                                                | barrier | take P, dS = P * dP | dK
+// `left`: valid query rows of the tile.  `taken`: tiles whose P B has taken; the single P buffer of a pair is rewritten only then.
+// B says so right behind the barrier and waits for nobody in between, so the wait of A ends; it is bounded all the same (see ab_tile).
+template <int SOFF, int SROW, int NOFF, int NROW, typename F>
+__device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigned off, unsigned off_row, unsigned noff, unsigned noff_row,
+                                             const bf16x8_t (&kvf)[2][4], floatx4_t (&acc)[8][2], float c, int g, int left,
+                                             bf16x8_t (&nat0)[2][4], floatx4_t (&ini0)[2], int* taken, int tile_no, int spin_limit,
+                                             int* status, F&& barrier) {
+  StepScores sc[2];      // S (A) or dP (B) of the two 32-query units
+  bf16x8_t bop[2][2];    // B operand of the second product: P (A) or dS (B), per unit and key half
+  bf16x8_t nat1[2][4], tr0[8], tr1[8];
+  floatx4_t ini1[2];
+  ab_load_nat<SOFF + 8192, SROW + 128>(ln, off, off_row, nat1, ini1);
+  __builtin_amdgcn_sched_barrier(0);
+  ab_scores(nat0, ini0, kvf, sc[0]);
+  __builtin_amdgcn_sched_barrier(0);
+  ab_load_tr<SOFF>(ln, off, tr0);
+  ab_scores(nat1, ini1, kvf, sc[1]);
+  __builtin_amdgcn_sched_barrier(0);
+  if (role == 0) {
+    if (left < 64) {   // queries past the end of the group: P = 0
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (32 * u + 8 * g + 4 * t + i >= left) sc[u][t][k][i] = -INFINITY;
+    }
+    spin_until(taken, tile_no, spin_limit, status);
+    ab_make_p<false>(ln, sc[0], c, g, 64, 0, bop[0]);
+    ab_make_p<false>(ln, sc[1], c, g, 64, 1, bop[1]);
+  }
+  ab_load_tr<SOFF + 8192>(ln, off, tr1);
+  barrier();
+  if (role == 1) {
+    ab_take_p(ln, sc[0], 0, bop[0]);
+    ab_take_p(ln, sc[1], 1, bop[1]);
+    __hip_atomic_store(taken, tile_no + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
+  ab_load_nat<NOFF, NROW>(ln, noff, noff_row, nat0, ini0);
+  // The second products go first when the SIMD's two waves compete (with the scores first: 593 against 582 ms at 580,320 x 40 heads).
+  wave_priority<true, 1>();
+  ab_accumulate(tr0, bop[0], acc);
+  ab_accumulate(tr1, bop[1], acc);
+  wave_priority<true, 0>();
 }
 
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
@@ -537,6 +605,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&lds.l[0][0] : (unsigned)(uintptr_t)&lds.d[0][0]) + 8 * (lane >> 4) * 4;
   ln.p_addr = (unsigned)(uintptr_t)&lds.p[0][0] + pair * 4096 + lane * 16;
 
+  settle(kvf);
   floatx4_t acc[8][2];   // dV^T (A) or dK^T (B): d tile, key half
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) acc[dt][0] = acc[dt][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -545,34 +614,71 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   // a pair whose 32 key rows lie past the end of the group (both of its waves) only moves its share of the tiles
   const bool active = k0w < ge;
   int T = 0;
-#define MOGA_AB_TILE(B)                                                          \
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));              \
-  __syncthreads();                                                               \
-  issue_tile(T + (B) + 1 + kAhead);                                          \
-  if (active)                                                                    \
-    ab_tile<NB == 4, false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
-                                                                              T + (B) + 1, spin_limit, status);
-  for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
-    MOGA_AB_TILE(0)
-    MOGA_AB_TILE(1)
-    MOGA_AB_TILE(2)
-    MOGA_AB_TILE(3)
-  }
+  if constexpr (NB == 4) {
+    const int ntiles = (n + 63) >> 6;
+    bf16x8_t nat0[2][4];
+    floatx4_t ini0[2];
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+    __syncthreads();
+    if (active) ab_load_nat<0, 0>(ln, 0, 0, nat0, ini0);
+    // In tile t: tile t + 1 has landed (for this wave, then for all), and every wave has left the slot of tile t - 1.
+    auto barrier = [&](int t) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
+      __syncthreads();
+      issue_tile(t + 3);
+    };
+#define MOGA_AB_TILE(B)                                                                                                  \
+  if (active)                                                                                                            \
+    ab_tile_long<(B) * kPipeTileBytes, (B) * 256, (((B) + 1) & 3) * kPipeTileBytes, (((B) + 1) & 3) * 256>(              \
+        ln, role, 0, 0, 0, 0, kvf, acc, c, lane >> 4, 64, nat0, ini0, flag, T + (B), spin_limit, status,                 \
+        [&]() { barrier(T + (B)); });                                                                                    \
+  else                                                                                                                   \
+    barrier(T + (B));
+    for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
+      MOGA_AB_TILE(0)
+      MOGA_AB_TILE(1)
+      MOGA_AB_TILE(2)
+      MOGA_AB_TILE(3)
+    }
 #undef MOGA_AB_TILE
-  for (; T < nfull; ++T) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-    __syncthreads();
-    issue_tile(T + 1 + kAhead);
-    if (active)
-      ab_tile<NB == 4, false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                           ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
-  }
-  if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-    __syncthreads();
-    if (active)
-      ab_tile<NB == 4, true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                          ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
+    for (; T < ntiles; ++T) {
+      const unsigned slot = (unsigned)T & 3u, next = (unsigned)(T + 1) & 3u;
+      if (active)
+        ab_tile_long<0, 0, 0, 0>(ln, role, slot * kPipeTileBytes, slot * 256, next * kPipeTileBytes, next * 256, kvf, acc, c,
+                                 lane >> 4, n - 64 * T, nat0, ini0, flag, T, spin_limit, status, [&]() { barrier(T); });
+      else
+        barrier(T);
+    }
+  } else {
+#define MOGA_AB_TILE(B)                                                          \
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                  \
+  __syncthreads();                                                               \
+  issue_tile(T + (B) + 1 + kAhead);                                              \
+  if (active)                                                                    \
+    ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
+                                                                              T + (B) + 1, spin_limit, status);
+    for (; T + 4 <= nfull; T += 4) {
+      MOGA_AB_TILE(0)
+      MOGA_AB_TILE(1)
+      MOGA_AB_TILE(2)
+      MOGA_AB_TILE(3)
+    }
+#undef MOGA_AB_TILE
+    for (; T < nfull; ++T) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+      __syncthreads();
+      issue_tile(T + 1 + kAhead);
+      if (active)
+        ab_tile<false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+                             ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
+    }
+    if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+      __syncthreads();
+      if (active)
+        ab_tile<true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+                            ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
+    }
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
