@@ -219,9 +219,9 @@ void moga_debug_set_spin_limit(int polls);
  * The BF16 attention calls have two sets of kernels: 8-wave blocks with 256-row (forward, dQ) or
  * 128-row (dK/dV) tiles, and 4-wave blocks with tiles half as large, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
- * group size N / M (forward: below 1152 rows from 16 rounds of 256 256-row tiles on, below 2560 from one round on, else
- * below 6144; backward: below 900; the moga_fused_* calls always take the first set).  The F32 calls
- * have 32-row and 16-row blocks, and take the latter up to 1,152 of the former.  Both sets give the same results up
+ * group size N / M (forward: below 1792 rows from 16 rounds of 256 256-row tiles on, below 2560 from one round on, else
+ * below 6144; backward: below 500, 860 and 3900; the moga_fused_* calls always take the first set).  The F32 calls have 32-row
+ * and 16-row blocks, and take the latter up to 1,152 of the former.  Both sets give the same results up
  * to rounding order.  moga_debug_set_small_group_rows overrides all thresholds (0: never the small
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.
  */

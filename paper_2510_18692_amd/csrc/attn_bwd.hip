@@ -115,10 +115,14 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
   }
 }
 
-// Mean rows per group below which the small-group bf16 kernels run: against the others 11 % faster at 520 rows, 5 % at 710,
-// equal at 1,060 (32,760 x 12 heads), 3 % faster at 510, 6 % slower at 1,030 (99,840 x 40), 7 % faster at 700, 5 % slower at
-// 1,090 (12,000 x 3).
-constexpr int64_t kSmallGroupRows = 900;
+// Mean rows per group below which the small-group bf16 kernels run, by rounds of 256 blocks of 256 rows: their finer tiles win
+// where there are few.  Against the long-group kernels: half a round (12,000 x 3 heads) 36 % faster at 900 rows, 3 % at 3,000,
+// equal at 4,000; 6 rounds (32,760 x 12) 2 % faster at 700, 1 % slower at 900; 61 rounds (99,840 x 40) 7 % faster at 400, 1 %
+// slower at 520, 4.5 % at 780.
+static int64_t small_group_rows(int64_t Nq, int H) {
+  const int64_t rounds = Nq * H / (256 * kCus);
+  return rounds >= 16 ? 500 : rounds >= 1 ? 860 : 3900;
+}
 
 }  // namespace moga
 
@@ -134,7 +138,7 @@ extern "C" size_t moga_attn_bwd_status_offset(int64_t Nq, int H) {
 }
 
 bool moga::bwd_splits(int64_t Nq, int64_t Nk, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, kSmallGroupRows) &&
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
          (split_pays(max_tiles(Nq, M, 256) * H) || split_pays(max_tiles(Nk, M, 128) * H));
 }
 
@@ -179,7 +183,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
-    const bool small = use_small_group_kernels(Nq, M, kSmallGroupRows) &&
+    const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
                        (max_tiles(Nq, M, 128) + max_tiles(Nk, M, 64)) * H + 16 < ((int64_t)1 << 31);   // one launch
     const int bk = small ? 64 : 128, bm = small ? 128 : 256;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);

@@ -18,14 +18,12 @@
 namespace moga {
 
 // Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of the other one: it wins by
-// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) equal at 1,040 rows,
-// 3.5 % slower at 1,560; 32 rounds (52,429 x 40) the same; 6 rounds (32,760 x 12) 7 % faster at 1,560, equal at 2,180,
-// 3.5 % slower at 3,280; half a round (12,000 x 3) 10 % faster at 2,400, equal at 6,000.  In between the line is not sharp:
-// with 12 heads it is equal at 1,560 rows (12 rounds), 1,800 (16) and 2,050 (24), so that what the rule takes there
-// costs 3.5 % at most (16 rounds, 1,300 rows) on either side.
+// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) 4 % faster at 780 rows, even
+// from 1,560 to 2,080, 3 % slower at 3,120; 6 rounds (32,760 x 12) 10 % faster at 1,560, 6 % at 2,050, equal at 2,730; half a
+// round (12,000 x 3) 14 % faster at 2,000, 6 % at 4,000, equal at 6,000.
 static int64_t small_group_rows(int64_t Nq, int H) {
   const int64_t rounds = Nq * H / (256 * kCus);
-  return rounds >= 16 ? 1152 : rounds >= 1 ? 2560 : 6144;
+  return rounds >= 16 ? 1792 : rounds >= 1 ? 2560 : 6144;
 }
 
 }  // namespace moga
