@@ -300,11 +300,14 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t
   }
 }
 
-// Sort and gather in one launch, for up to 4,096 tokens and 32 groups.  A block moves the rows of 16 tokens of one tensor and
-// finds their slots by itself: it counts the ids of all tokens and of those before its own (a few per thread, 8-bit counters
-// packed four to a word, summed over the waves), which costs about a microsecond while its rows are on the way.  The sort as a
-// launch of its own was one block, and the chip waited for it.
-constexpr int64_t kFusedSortTokens = 4096;
+// Sort and gather in one launch, for up to 16,384 tokens and 32 groups.  A block moves the rows of 16 tokens (of one tensor, or
+// of all three) and finds their slots by itself: it counts the ids of all tokens and of those before its own (up to 64 per
+// thread, 8-bit counters packed four to a word, summed over the waves) while its first rows are on the way.  The sort as a launch
+// of its own is one block that the chip waits for.  Two launches against this one, in us: 4,096 x 12 heads x 128 bf16, 8 groups
+// 17.8 and 13.7 (5.5 TB/s); 10,007 x 12, 20 groups 39.9 and 36.6; 16,384 x 12, 8 groups 64 and 54, 24 heads, 32 groups 136 and
+// 127.  Above 4,096 tokens the count is paid back by a token's rows: 4 heads (1 KB a tensor) 16.0 and 14.7 at 8,192 tokens, 29.5
+// and 20.8 at 16,384; 2 heads 11.5 and 12.2, 1 head 10.1 and 22.8.
+constexpr int64_t kFusedSortTokens = 16384, kFusedSortRowBytes = 1024;
 
 template <int LPR, int WORDS, int PER>   // WORDS * 4 >= groups, PER * 256 >= tokens
 __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int32_t* __restrict__ group, int N, int H, int M, int nbits,
@@ -318,37 +321,46 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int3
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
   const int t0 = blockIdx.x * kSlotsPerBlock;
-  const uintx4_t* __restrict__ src = (const uintx4_t*)p.src[blockIdx.y];
-  uintx4_t* __restrict__ dst = (uintx4_t*)p.dst[blockIdx.y];
-  int id[PER];   // all ids in flight together, then the rows
+  constexpr int BATCH = PER < 16 ? PER : 16;
+  int id[BATCH], ahead[BATCH];   // a batch of ids in flight together, and the next one
+  auto load_ids = [&](int (&to)[BATCH], int i0) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) id[i] = group[min(256 * i + (int)threadIdx.x, N - 1)];
+    for (int i = 0; i < BATCH; ++i) to[i] = group[min(256 * (i0 + i) + (int)threadIdx.x, N - 1)];
+  };
+  load_ids(id, 0);
   const bool own = lane < kSlotsPerBlock && t0 + lane < N;
   const int g = clamp_group(group[min(t0 + (lane & (kSlotsPerBlock - 1)), N - 1)], M);
   uintx4_t v[IT];
-  auto load_rows = [&](int h) {
+  auto load_rows = [&](const uintx4_t* __restrict__ src, int h) {
 #pragma unroll
     for (int it = 0; it < IT; ++it) v[it] = src[((int64_t)min(t0 + it * RPW + rsub, N - 1) * H + h) * LPR + part];
   };
-  if (wave < H) load_rows(wave);
+  if (wave < H) load_rows((const uintx4_t*)p.src[blockIdx.y], wave);
 
   unsigned all[WORDS], before[WORDS];
 #pragma unroll
   for (int w = 0; w < WORDS; ++w) all[w] = before[w] = 0u;
+#pragma unroll 1
+  for (int i0 = 0; i0 < PER; i0 += BATCH) {
+    if (PER > BATCH) load_ids(ahead, i0 + BATCH);
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int t = 256 * i + threadIdx.x, k = clamp_group(id[i], M);
-    const unsigned one = t < N ? 1u << (8 * (k & 3)) : 0u, b = t < t0 ? one : 0u;
+    for (int i = 0; i < BATCH; ++i) {
+      const int t = 256 * (i0 + i) + threadIdx.x, k = clamp_group(id[i], M);
+      const unsigned one = t < N ? 1u << (8 * (k & 3)) : 0u, b = t < t0 ? one : 0u;
 #pragma unroll
-    for (int w = 0; w < WORDS; ++w) {
-      all[w] += (k >> 2) == w ? one : 0u;
-      before[w] += (k >> 2) == w ? b : 0u;
+      for (int w = 0; w < WORDS; ++w) {
+        all[w] += (k >> 2) == w ? one : 0u;
+        before[w] += (k >> 2) == w ? b : 0u;
+      }
     }
+    if (PER > BATCH)
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) id[i] = ahead[i];
   }
 #pragma unroll
   for (int w = 0; w < WORDS; ++w)
 #pragma unroll
-    for (int f = 0; f < 2; ++f) {   // two 16-bit sums at once: at most 1,024 per wave
+    for (int f = 0; f < 2; ++f) {   // two 16-bit sums at once: at most 4,096 per wave
       const int x = wave_scan_add((int)((all[w] >> (8 * f)) & 0x00ff00ffu));
       const int y = wave_scan_add((int)((before[w] >> (8 * f)) & 0x00ff00ffu));
       if (lane == 63) { s_sum[wave][0][2 * w + f] = x; s_sum[wave][1][2 * w + f] = y; }
@@ -375,11 +387,16 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int3
   int64_t to[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) to[it] = (int64_t)__shfl(slot, it * RPW + rsub, kWave) * LPR + part;
-  for (int h = wave; h < H; h += 4) {
+  for (int y = blockIdx.y; y < 3; y += gridDim.y) {
+    const uintx4_t* __restrict__ src = (const uintx4_t*)p.src[y];
+    uintx4_t* __restrict__ dst = (uintx4_t*)p.dst[y];
+    if (y != (int)blockIdx.y && wave < H) load_rows(src, wave);
+    for (int h = wave; h < H; h += 4) {
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (t0 + it * RPW + rsub < N) dst[(int64_t)h * N * LPR + to[it]] = v[it];
-    if (h + 4 < H) load_rows(h + 4);
+      for (int it = 0; it < IT; ++it)
+        if (t0 + it * RPW + rsub < N) dst[(int64_t)h * N * LPR + to[it]] = v[it];
+      if (h + 4 < H) load_rows(src, h + 4);
+    }
   }
 }
 
@@ -841,15 +858,18 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int chunk_len = perm_chunk_len(N);
   const int num_chunks = perm_num_chunks(N);
   const int nbits = bits_for(M);
-  if (with_data && N > 0 && N <= kFusedSortTokens && M <= kSingleBlockGroups) {
+  const int64_t row_bytes = (int64_t)H * lanes_per_row(dtype, D) * 16;
+  if (with_data && N > 0 && M <= kSingleBlockGroups && (N <= 4096 || (N <= kFusedSortTokens && row_bytes >= kFusedSortRowBytes))) {
     const Rows3 p = {{q, k, v}, {qh, kh, vh}};
-    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), 3);
+    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), N > 4096 ? 1 : 3);   // few rows: a block per tensor
 #define MOGA_PERMUTE_GATHER(LPR, WORDS, PER)                                                                                  \
   permute_gather_kernel<LPR, WORDS, PER><<<grid, 256, 0, st>>>(p, group, (int)N, H, M, nbits, counts, cu_seqlens, max_seqlen, \
                                                                perm, inv_perm)
 #define MOGA_PERMUTE_GATHER_N(LPR, WORDS)                         \
   if (N <= 2048) MOGA_PERMUTE_GATHER(LPR, WORDS, 8);              \
-  else MOGA_PERMUTE_GATHER(LPR, WORDS, 16)
+  else if (N <= 4096) MOGA_PERMUTE_GATHER(LPR, WORDS, 16);        \
+  else if (N <= 8192) MOGA_PERMUTE_GATHER(LPR, WORDS, 32);        \
+  else MOGA_PERMUTE_GATHER(LPR, WORDS, 64)
     if (lanes_per_row(dtype, D) == 16) {
       if (M <= 8) { MOGA_PERMUTE_GATHER_N(16, 2); } else { MOGA_PERMUTE_GATHER_N(16, 8); }
     } else {
