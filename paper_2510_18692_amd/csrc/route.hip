@@ -227,35 +227,60 @@ __device__ __forceinline__ void route_finish(const floatx16_t& total, int64_t to
 }
 
 // Few tokens: a block per 32 tokens, whose waves share the k blocks (wave w takes w, w + NWV, ..) and add their logits through
-// LDS.  W goes from L2 straight to registers and is split there.  The kernel below has 128 tokens per block and walks all of W
-// with a barrier per chunk: at 1,560 tokens its 13 blocks took as long as a full chip.  Theirs against ours: 1,560 x 512, 8
-// groups 9.6 and 5.4 us, 1,560 x 1536, 16 groups 18.7 and 9.9, 8,192 x 5120, 16 groups 60 and 29, 16,384 x 1536, 8 groups 21.6
-// and 14.8; 24,000 x 1536, 20 groups 24.2 and 26.1, from where splitting W for every 32 tokens costs more.
+// LDS.  The kernel below has 128 tokens per block and walks all of W with a barrier per chunk: at 1,560 tokens its 13 blocks took
+// as long as a full chip.  A wave's k block of W (fp32) and of X goes to its own LDS with direct-to-LDS loads, whole rows of 256
+// and 128 bytes at a time, and is read from there as operands: straight from memory every lane would touch a cache line of its
+// own in each of twelve loads (10,007 x 1536, 20 groups: 17.1 us).  16-byte chunks are XOR-swizzled by the row so that the reads
+// hit all banks.  W is split into its limbs in registers.  The other kernel's time and this one's, in us: 1,560 x 512, 8 groups
+// 9.5 and 5.1; 1,560 x 1536, 16 groups 18.6 and 8.1; 10,007 x 1536, 20 groups 19.1 and 11.7; 8,192 x 5120, 16 groups 60 and 23;
+// 16,384 x 1536, 8 groups 21.7 and 13.8 (3.6 TB/s).  Eight waves to a block are slower from 10,007 tokens on (15.0).
+constexpr int kFewW = 32 * 256, kFewX = 32 * 128;   // bytes of a wave's k block
+
 template <int NWV>
 __global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
     const unsigned short* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias, int64_t N, int d, int M,
     int32_t* __restrict__ group, float* __restrict__ gate, float* __restrict__ probs, float* __restrict__ logits) {
-  __shared__ float s_tot[NWV][16][64];
+  __shared__ __attribute__((aligned(1024))) unsigned char s_k[NWV][kFewW + kFewX];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
-  const int64_t tok = (int64_t)blockIdx.x * 32 + r;
-  const unsigned short* xr = x + min(tok, N - 1) * (int64_t)d + 32 * h;
-  const float* wr = w + (int64_t)min(r, M - 1) * d + 32 * h;
-  const bool row = r < M;   // rows of W beyond M count as zero
+  const int64_t tok0 = (int64_t)blockIdx.x * 32;
+  const void* xb = uniform_ptr(x + tok0 * d);
+  const void* wb = uniform_ptr(w);
+  const int last = (int)min((int64_t)31, N - 1 - tok0);
+  const unsigned lds = lds_addr_uniform(&s_k[0][0]) + wave * (kFewW + kFewX);
+  auto issue = [&](int k0) {   // rows of W beyond M and of X beyond N: the last one, not used
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int row = 4 * q + (lane >> 4), chunk = (lane & 15) ^ (row & 15);
+      lds_dma16_soff(wb, (unsigned)((min(row, M - 1) * d + k0 + 4 * chunk) * 4), lds + q * 1024);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = 8 * q + (lane >> 3), chunk = (lane & 7) ^ ((row >> 1) & 7);
+      lds_dma16_soff(xb, (unsigned)((min(row, last) * d + k0 + 8 * chunk) * 2), lds + kFewW + q * 1024);
+    }
+  };
+  // lane half h takes elements 32 h .. 32 h + 31 of its rows' k block
+  unsigned wa[8], xa[4];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) wa[s] = lds + r * 256 + (((8 * h + s) ^ (r & 15)) << 4);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) xa[s] = lds + kFewW + r * 128 + (((4 * h + s) ^ ((r >> 1) & 7)) << 4);
 
   floatx16_t total;
 #pragma unroll
   for (int v = 0; v < 16; ++v) total[v] = 0.f;
-  uintx4_t xv[4];
-  floatx4_t wv[8];
-  auto load = [&](int k0) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) xv[s] = *(const uintx4_t*)(xr + k0 + 8 * s);
-#pragma unroll
-    for (int s = 0; s < 8; ++s) wv[s] = *(const floatx4_t*)(wr + k0 + 4 * s);
-  };
-  if (64 * wave < d) load(64 * wave);
+  if (64 * wave < d) issue(64 * wave);
   for (int k0 = 64 * wave; k0 < d; k0 += 64 * NWV) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uintx4_t xv[4];
+    floatx4_t wv[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) wv[s] = *(const floatx4_t __attribute__((address_space(3)))*)(uintptr_t)wa[s];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) xv[s] = *(const uintx4_t __attribute__((address_space(3)))*)(uintptr_t)xa[s];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // read before the next block overwrites it
+    if (k0 + 64 * NWV < d) issue(k0 + 64 * NWV);
     floatx16_t acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -265,7 +290,7 @@ __global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float w0 = wv[2 * s + (e >> 1)][2 * (e & 1)], w1 = wv[2 * s + (e >> 1)][2 * (e & 1) + 1];
-        if (!row) w0 = w1 = 0.f;
+        if (r >= M) w0 = w1 = 0.f;
 #pragma unroll
         for (int l = 0; l < 3; ++l) {   // as split3: what is left after each limb is exact
           limb[l][e] = pack_bf16x2(w0, w1);
@@ -277,9 +302,10 @@ __global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
       for (int l = 0; l < 3; ++l)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, limb[l]), __builtin_bit_cast(bf16x8_t, xv[s]), acc, 0, 0, 0);
     }
-    if (k0 + 64 * NWV < d) load(k0 + 64 * NWV);
     total += acc;   // short chains
   }
+  __syncthreads();   // the k blocks' memory now takes the waves' logits
+  float (*s_tot)[16][64] = (float (*)[16][64])&s_k[0][0];
 #pragma unroll
   for (int v = 0; v < 16; ++v) s_tot[wave][v][lane] = total[v];
   __syncthreads();
@@ -288,10 +314,15 @@ __global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
   for (int v = 0; v < 16; ++v)
 #pragma unroll
     for (int k = 1; k < NWV; ++k) total[v] += s_tot[k][v][lane];
-  route_finish(total, tok, h, bias, N, M, group, gate, probs, logits);
+  route_finish(total, tok0 + r, h, bias, N, M, group, gate, probs, logits);
 }
 
-constexpr int64_t kRouteFewTokens = 16384;
+// The other kernel's blocks of 128 tokens run 256 at a time; it is the better one where their last round is almost full.  Its
+// time and that of the kernel above in us (1536 channels): 24,000 tokens 24.2 and 21.4, 28,000 25.2 and 24.9, 32,768 25.1 and
+// 26.1; 33,000 40.0 and 26.6, 50,000 42.5 and 37.2, 62,400 44.9 and 43.0 (5120 channels: 143 and 149, 512: 18.4 and 19.8).
+inline bool use_route_few(int64_t N, int d_model) {
+  return ((N + 127) / 128 - 1) % 256 < 224 && d_model <= (1 << 20);   // 32-bit offsets within W
+}
 
 // The weight chunk is double-buffered: while the matrix cores work on chunk c, the fp32 weights of
 // chunk c+1 are in flight from L2; they are split and stored after the chunk's MFMAs, one block
@@ -769,7 +800,7 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
       const unsigned blocks = (unsigned)((N + 255) / 256);
       route_mfma_kernel<1, 8><<<blocks, 512, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                      group, gate, probs, logits);
-    } else if (N <= kRouteFewTokens) {
+    } else if (use_route_few(N, d_model)) {
       const unsigned blocks = (unsigned)((N + 31) / 32);
       route_mfma_few_kernel<4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                        group, gate, probs, logits);
