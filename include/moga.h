@@ -303,6 +303,14 @@ int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const
                          float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
                          void* ws, size_t ws_bytes, void* stream);
 
+/* The same where moga_merge3_bwd_rows has written the call's row constants to ws: they are not computed again. */
+int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, const void* vh,
+                              const void* oh, const float* lse, int dtype,
+                              int64_t Nq, int64_t Nk, int H, int D,
+                              const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k, int G,
+                              float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
+                              void* ws, size_t ws_bytes, void* stream);
+
 /*
  * Static groups of Section 3.2 ("Spatial-Temporal Group Attention"), built on the HOST: the lists
  * depend only on the latent grid (T frames of Hh x Ww tokens, token = (t*Hh + y)*Ww + x), the window
@@ -392,6 +400,17 @@ int moga_merge3_bwd(const void* d_o, const void* a_moga, int dtype, const int32_
                     const int32_t* inv_stga, const int32_t* inv_frame, const float* gate,
                     int64_t N, int H, int D, void* d_a_moga, void* d_a_stga, void* d_a_frame,
                     float* d_gate, void* stream);
+/*
+ * The same, and the row constants (-rowsum(d_a * a), -lse / softmax_scale) of the three attention backwards that follow, written
+ * to the start of their workspaces, which those calls (moga_varlen_attn_bwd_rows, Nq = N, the same softmax_scale) are then given.
+ * a_stga, a_frame [H, N, D] are the outputs of the static branches, lse_* [H, N] the three log-sum-exps; ws_bytes: what every
+ * workspace has at least (MOGA_OP_ATTN_BWD).
+ */
+int moga_merge3_bwd_rows(const void* d_o, const void* a_moga, const void* a_stga, const void* a_frame, int dtype,
+                         const int32_t* inv_moga_or_null, const int32_t* inv_stga_or_null, const int32_t* inv_frame_or_null,
+                         const float* gate, const float* lse_moga, const float* lse_stga, const float* lse_frame,
+                         float softmax_scale, int64_t N, int H, int D, void* d_a_moga, void* d_a_stga, void* d_a_frame,
+                         float* d_gate, void* ws_moga, void* ws_stga, void* ws_frame, size_t ws_bytes, void* stream);
 
 /*
  * Group balancing loss, Eqs. 6-8 (Section 3.2; alpha = 0.1 in the paper's training setup):

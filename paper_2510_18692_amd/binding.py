@@ -61,6 +61,8 @@ _SIGNATURES = {
                                     _vp, _sz, _vp]),
     "moga_varlen_attn_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i64, _i32, _i32, _vp, _vp, _i32,
                                     _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "moga_varlen_attn_bwd_rows": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i64, _i32, _i32, _vp, _vp, _i32,
+                                         _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_stga_index_sizes": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _vp, _vp]),
     "moga_stga_build_index": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _vp, _vp, _vp, _vp, _vp,
                                      _vp, _vp]),
@@ -71,6 +73,8 @@ _SIGNATURES = {
     "moga_gather3_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp]),
     "moga_merge3_fwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp]),
     "moga_merge3_bwd": (_i32, [_vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
+    "moga_merge3_bwd_rows": (_i32, [_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _f32, _i64, _i32, _i32, _vp, _vp, _vp,
+                                    _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_balance_loss": (_i32, [_vp, _vp, _i64, _i32, _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_balance_loss_bwd": (_i32, [_vp, _vp, _i64, _i32, _f32, _f32, _vp, _i32, _vp, _vp]),
 }
@@ -335,6 +339,19 @@ def moga_merge3_bwd(d_o, a_moga, inv_moga, inv_stga, inv_frame, gate, stream=Non
     return _nat.merge3_bwd(d_o, a_moga, inv_moga, inv_stga, inv_frame, gate, _st(stream))
 
 
+def moga_merge3_bwd_rows(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, lse, softmax_scale, cu_moga, cu_q, n_keys,
+                         cu_frame, stream=None):
+    """moga_merge3_bwd with the row constants of the three attention backwards; `lse`: those of the three branches
+    -> (d_a_moga, d_a_stga, d_a_frame [H, N, D], d_gate f32 [N], three workspaces for moga_varlen_attn_bwd_rows)"""
+    return _nat.merge3_bwd_rows(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, *lse, softmax_scale, cu_moga, cu_q,
+                                n_keys, cu_frame, _st(stream))
+
+
+def moga_varlen_attn_bwd_rows(d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, softmax_scale, ws, stream=None):
+    """moga_varlen_attn_bwd with the row constants already in `ws` (from moga_merge3_bwd_rows)."""
+    return _nat.varlen_attn_bwd_rows(d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, softmax_scale, ws, _st(stream))
+
+
 def moga_balance_loss(group, gate, M, alpha, stream=None):
     """Eqs. 6-8 -> (loss f32 [1], frac f32 [M], prob f32 [M]), all on the device."""
     return _nat.balance_loss(group, gate, M, alpha, _st(stream))
@@ -398,17 +415,19 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
 def visual_backward(fwd, x, w, d_o, softmax_scale, stream=None):
     """Backward of `visual_forward` -> dict(d_q, d_k, d_v [N, H, D], d_w [M, d_model], d_gate [N])."""
     pm, si, ident = fwd["pm"], fwd["si"], fwd["ident"]
-    d_m, d_s, d_f, d_gate = moga_merge3_bwd(d_o, fwd["a_m"], pm["inv_perm"], si["q_slot"], None, fwd["gate"],
-                                            stream=stream)
-    dqm, dkm, dvm = moga_group_attn_bwd(d_m, pm["qh"], pm["kh"], pm["vh"], fwd["a_m"], fwd["lse_m"],
-                                        pm["cu_seqlens"], softmax_scale, stream=stream)
-    del d_m
-    dqs, dks, dvs = moga_varlen_attn_bwd(d_s, fwd["qs"], fwd["ks"], fwd["vs"], fwd["a_s"], fwd["lse_s"],
-                                         si["cu_q"], si["cu_k"], softmax_scale, stream=stream)
-    del d_s
-    dqf, dkf, dvf = moga_varlen_attn_bwd(d_f, fwd["qf"], fwd["kf"], fwd["vf"], fwd["a_f"], fwd["lse_f"],
-                                         fwd["cu_f"], fwd["cu_f"], softmax_scale, stream=stream)
-    del d_f
+    d_m, d_s, d_f, d_gate, ws_m, ws_s, ws_f = moga_merge3_bwd_rows(
+        d_o, fwd["a_m"], fwd["a_s"], fwd["a_f"], pm["inv_perm"], si["q_slot"], None, fwd["gate"],
+        (fwd["lse_m"], fwd["lse_s"], fwd["lse_f"]), softmax_scale, pm["cu_seqlens"], si["cu_q"], fwd["ks"].shape[1], fwd["cu_f"],
+        stream=stream)
+    dqm, dkm, dvm = moga_varlen_attn_bwd_rows(d_m, pm["qh"], pm["kh"], pm["vh"], fwd["a_m"], fwd["lse_m"],
+                                              pm["cu_seqlens"], pm["cu_seqlens"], softmax_scale, ws_m, stream=stream)
+    del d_m, ws_m
+    dqs, dks, dvs = moga_varlen_attn_bwd_rows(d_s, fwd["qs"], fwd["ks"], fwd["vs"], fwd["a_s"], fwd["lse_s"],
+                                              si["cu_q"], si["cu_k"], softmax_scale, ws_s, stream=stream)
+    del d_s, ws_s
+    dqf, dkf, dvf = moga_varlen_attn_bwd_rows(d_f, fwd["qf"], fwd["kf"], fwd["vf"], fwd["a_f"], fwd["lse_f"],
+                                              fwd["cu_f"], fwd["cu_f"], softmax_scale, ws_f, stream=stream)
+    del d_f, ws_f
     # every token-order gradient is written once: MoGA rows through inv_perm, the static rows through
     # their slot lists (queries are listed once, keys possibly several times), the frame rows in place
     d_q = moga_gather3_bwd(dqm, pm["inv_perm"], dqs, ident, si["q_slot"], dqf, stream=stream)

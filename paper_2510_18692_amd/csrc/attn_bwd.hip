@@ -158,10 +158,11 @@ extern "C" void moga_debug_set_spin_limit(int polls) { g_spin_limit.store(polls 
 static bool bf16_rows_ok(int64_t Nq, int64_t Nk) { return Nq < ((int64_t)1 << 24) && Nk < ((int64_t)1 << 24); }
 
 // The gradients in token order [N, H, D] as well, row j of the sorted order at token perm[j]; all NULL: none.  With them the
-// sorted ones (d_qh, d_kh, d_vh) may be NULL, and the row constants (bf16) are already in the workspace.
+// sorted ones (d_qh, d_kh, d_vh) may be NULL.
 struct TokenGrads {
   void *d_q, *d_k, *d_v;
   const int32_t* perm;
+  bool row_constants;   // already in the workspace
 };
 
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
@@ -179,7 +180,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
     int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-    if (!tok.perm) attn_bwd_delta_kernel<16, true><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
+    if (!tok.row_constants) attn_bwd_delta_kernel<16, true><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
@@ -227,7 +228,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     const int64_t q_tiles = max_tiles(Nq, M, kF32SmallRows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32SmallRows) : 0;
     const int64_t blocks = (q_tiles + k_tiles) * H;
     if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    if (!tok.perm) {
+    if (!tok.row_constants) {
       int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
       const unsigned grid = (unsigned)((rows * (D / 4) + 255) / 256);
       if (D == 64)
@@ -333,7 +334,7 @@ extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const
   const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, with_delta ? &rc : nullptr, (hipStream_t)stream);
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
-                         softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm},
+                         softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm, true},
                          split_region(ws, need, ws_bytes), (hipStream_t)stream);
 }
 
@@ -342,12 +343,10 @@ extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
   return bwd_rows_bytes(Nq, H) + 16 + 2 * ((size_t)G + 1) * sizeof(int32_t);
 }
 
-extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
-                                    const void* oh, const float* lse, int dtype, int64_t Nq,
-                                    int64_t Nk, int H, int D, const int32_t* cu_seqlens_q,
-                                    const int32_t* cu_seqlens_k, int G, float softmax_scale,
-                                    void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
-                                    void* stream) {
+static int varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse,
+                           int dtype, int64_t Nq, int64_t Nk, int H, int D, const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k,
+                           int G, float softmax_scale, void* d_qh, void* d_kh, void* d_vh, bool row_constants, void* ws,
+                           size_t ws_bytes, void* stream) {
   const int bad = check_attn_bwd_args(Nq, Nk, H, D, G, softmax_scale, dtype);
   if (bad) return bad;
   if (G > MOGA_MAX_SEGMENTS) return MOGA_ERR_UNSUPPORTED;
@@ -372,8 +371,28 @@ extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void
   int32_t* ts_q = presum ? (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16) : nullptr;
   int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
-                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{},
+                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
                          presum ? nullptr : split_region(ws, need, ws_bytes), st);
+}
+
+extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
+                                    const void* oh, const float* lse, int dtype, int64_t Nq,
+                                    int64_t Nk, int H, int D, const int32_t* cu_seqlens_q,
+                                    const int32_t* cu_seqlens_k, int G, float softmax_scale,
+                                    void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
+                                    void* stream) {
+  return varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, G, softmax_scale, d_qh, d_kh,
+                         d_vh, false, ws, ws_bytes, stream);
+}
+
+extern "C" int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, const void* vh,
+                                         const void* oh, const float* lse, int dtype, int64_t Nq,
+                                         int64_t Nk, int H, int D, const int32_t* cu_seqlens_q,
+                                         const int32_t* cu_seqlens_k, int G, float softmax_scale,
+                                         void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
+                                         void* stream) {
+  return varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, G, softmax_scale, d_qh, d_kh,
+                         d_vh, true, ws, ws_bytes, stream);
 }
 
 extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k, const void* v,

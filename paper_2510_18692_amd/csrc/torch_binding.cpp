@@ -419,6 +419,42 @@ std::tuple<Tensor, Tensor, Tensor, Tensor> merge3_bwd(const Tensor& d_o, const T
   return {d_m, d_s, d_f, d_gate};
 }
 
+using Rows3Out = std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor, Tensor, Tensor>;
+Rows3Out merge3_bwd_rows(const Tensor& d_o, const Tensor& a_moga, const Tensor& a_stga, const Tensor& a_frame, const OptTensor& inv_moga,
+                         const OptTensor& inv_stga, const OptTensor& inv_frame, const Tensor& gate, const Tensor& lse_moga,
+                         const Tensor& lse_stga, const Tensor& lse_frame, double scale, const Tensor& cu_moga, const Tensor& cu_q,
+                         int64_t n_keys, const Tensor& cu_frame, const OptStream& stream) {
+  require(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, lse_moga, lse_stga, lse_frame, cu_moga, cu_q, cu_frame);
+  const Call call(stream);
+  need_dims(d_o, 3);
+  const int64_t N = d_o.size(0), H = d_o.size(1), D = d_o.size(2);
+  Tensor d_m = call.make({H, N, D}, d_o), d_s = call.make({H, N, D}, d_o), d_f = call.make({H, N, D}, d_o), d_gate = call.make({N}, d_o, at::kFloat);
+  auto ws = [&](int64_t Nk, const Tensor& cu) { return *call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, N, Nk, H, D, cu.size(0) - 1, d_o); };
+  Tensor ws_m = ws(N, cu_moga), ws_s = ws(n_keys, cu_q), ws_f = ws(N, cu_frame);
+  const size_t bytes = std::min({ws_m.numel(), ws_s.numel(), ws_f.numel()});
+  check("moga_merge3_bwd_rows",
+        moga_merge3_bwd_rows(ptr(d_o), ptr(a_moga), ptr(a_stga), ptr(a_frame), dt(d_o), as<int32_t>(inv_moga), as<int32_t>(inv_stga),
+                             as<int32_t>(inv_frame), as<float>(gate), as<float>(lse_moga), as<float>(lse_stga), as<float>(lse_frame),
+                             (float)scale, N, (int)H, (int)D, ptr(d_m), ptr(d_s), ptr(d_f), as<float>(d_gate), ptr(ws_m), ptr(ws_s), ptr(ws_f),
+                             bytes, call.stream()));
+  return {d_m, d_s, d_f, d_gate, ws_m, ws_s, ws_f};
+}
+
+std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd_rows(const Tensor& d_oh, const Tensor& qh, const Tensor& kh, const Tensor& vh,
+                                                        const Tensor& oh, const Tensor& lse, const Tensor& cu_q, const Tensor& cu_k,
+                                                        double scale, const Tensor& ws, const OptStream& stream) {
+  require(d_oh, qh, kh, vh, oh, lse, cu_q, cu_k, ws);
+  const Call call(stream);
+  need_dims(qh, 3);
+  const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
+  Tensor d_qh = call.make({H, Nq, D}, qh), d_kh = call.make(kh.sizes(), kh), d_vh = call.make(vh.sizes(), vh);
+  check("moga_varlen_attn_bwd_rows",
+        moga_varlen_attn_bwd_rows(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), Nq, Nk, (int)H, (int)D,
+                                  as<int32_t>(cu_q), as<int32_t>(cu_k), (int)G, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh), ptr(ws),
+                                  (size_t)ws.numel(), call.stream()));
+  return {d_qh, d_kh, d_vh};
+}
+
 // `loss` [1] or a scalar
 std::tuple<Tensor, Tensor> balance_into(const Tensor& loss, const Tensor& group, const Tensor& gate, int64_t M, double alpha,
                                         const OptStream& stream) {
@@ -541,6 +577,8 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("gather3_bwd", &gather3_bwd, nogil);
   m.def("merge3_fwd", &merge3_fwd, nogil);
   m.def("merge3_bwd", &merge3_bwd, nogil);
+  m.def("merge3_bwd_rows", &merge3_bwd_rows, nogil);
+  m.def("varlen_attn_bwd_rows", &varlen_attn_bwd_rows, nogil);
   m.def("balance_loss", &balance_loss, nogil);
   m.def("balance_loss_bwd", &balance_loss_bwd, nogil);
   m.def("attention", &attention, nogil);
