@@ -12,12 +12,12 @@
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
 // read the transposed operands (dO^T, Q^T, K^T) from row-major LDS tiles with the transposing
-// LDS read.  fp32 (attn_f32.h): the dQ kernel runs first and computes delta, the dK/dV kernel follows.
+// LDS read.  fp32 (attn_f32.h): delta, then dQ and dK/dV in one launch.
 #include <atomic>
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
-#include "attn_f32_small.h"
+#include "attn_f32.h"
 
 namespace moga {
 
@@ -224,8 +224,8 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
           (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
           (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
           (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
-  } else if (use_f32_small(Nq, H, M)) {
-    const int64_t q_tiles = max_tiles(Nq, M, kF32SmallRows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32SmallRows) : 0;
+  } else {
+    const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
     const int64_t blocks = (q_tiles + k_tiles) * H;
     if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
     if (!tok.row_constants) {
@@ -238,43 +238,16 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         attn_bwd_delta_kernel<32, false><<<grid, 256, 0, st>>>((const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 0.f, delta,
                                                                nullptr, status);
     }
-    if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32SmallRows, ts_k);
-    if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32SmallRows, ts_q);
-#define MOGA_BWD_F32_SMALL(DD)                                                                                              \
-  attn_bwd_f32_small_kernel<DD><<<(unsigned)blocks, 64 * kF32SmallWaves, 0, st>>>(                                          \
+    if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
+    if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
+#define MOGA_BWD_F32(DD)                                                                                              \
+  attn_bwd_f32_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                          \
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k, ts_q, ts_k, M, Nq,   \
       Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)(k_tiles * H), (float*)d_qh, (float*)d_kh, (float*)d_vh,        \
       tok.perm, (float*)tok.d_q, (float*)tok.d_k, (float*)tok.d_v)
-    if (D == 64) MOGA_BWD_F32_SMALL(64);
-    else MOGA_BWD_F32_SMALL(128);
-#undef MOGA_BWD_F32_SMALL
-  } else {
-    {
-      const int64_t tiles = max_tiles(Nq, M, kF32Rows);
-      const int64_t blocks = tiles * H;
-      if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-      if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
-#define MOGA_DQ_F32(DD)                                                                                   \
-  attn_bwd_dq_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                       \
-      (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, (const float*)oh, lse,    \
-      cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale, (int)tiles, delta, (float*)d_qh, tok.perm, (float*)tok.d_q)
-      if (D == 64) MOGA_DQ_F32(64);
-      else MOGA_DQ_F32(128);
-#undef MOGA_DQ_F32
-    }
-    if (Nk > 0) {
-      const int64_t tiles = max_tiles(Nk, M, kF32Rows);
-      const int64_t blocks = tiles * H;
-      if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-      if (ts_k) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
-#define MOGA_DKDV_F32(DD)                                                                                 \
-  attn_bwd_dkdv_f32_mfma_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                     \
-      (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k,   \
-      ts_k, M, Nq, Nk, H, softmax_scale, (int)tiles, (float*)d_kh, (float*)d_vh, tok.perm, (float*)tok.d_k, (float*)tok.d_v)
-      if (D == 64) MOGA_DKDV_F32(64);
-      else MOGA_DKDV_F32(128);
-#undef MOGA_DKDV_F32
-    }
+    if (D == 64) MOGA_BWD_F32(64);
+    else MOGA_BWD_F32(128);
+#undef MOGA_BWD_F32
   }
   return launch_status();
 }
@@ -329,9 +302,8 @@ extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   float* delta = (float*)ws;
-  const bool with_delta = dtype == MOGA_BF16 || use_f32_small(N, H, M);
   const RowConstants rc = {lse, 1.f / softmax_scale, delta, delta + N * (int64_t)H, (int*)((char*)ws + bwd_rows_bytes(N, H))};
-  const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, with_delta ? &rc : nullptr, (hipStream_t)stream);
+  const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, &rc, (hipStream_t)stream);
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
                          softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm, true},

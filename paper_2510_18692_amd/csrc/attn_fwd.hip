@@ -11,7 +11,7 @@
 //   * the kernel itself (software pipeline, LDS ring, direct-to-LDS loads) is in attn_pipe.h.
 // fp32 kernel (fp32 matrix instruction, full precision throughout): attn_f32.h.
 #include "attn_common.h"
-#include "attn_f32_small.h"
+#include "attn_f32.h"
 #include "attn_pipe.h"
 #include "attn_pipe_small.h"
 
@@ -46,20 +46,20 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
                            const TokenRows& tok, void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
-  const bool small = dtype == MOGA_BF16 ? use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) : use_f32_small(Nq, H, M);
-  const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : (small ? kF32SmallRows : kF32Rows);
+  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
+  const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
   if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
   if (tile_start) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, tile_start);
-  if (small && dtype == MOGA_F32) {
-#define MOGA_FWD_F32_SMALL(DD)                                                                                             \
-  attn_fwd_f32_small_kernel<DD><<<(unsigned)blocks, 64 * kF32SmallWaves, 0, st>>>(                                         \
+  if (dtype == MOGA_F32) {
+#define MOGA_FWD_F32(DD)                                                                                                   \
+  attn_fwd_f32_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                                    \
       (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, \
       (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o)
-    if (D == 64) MOGA_FWD_F32_SMALL(64);
-    else MOGA_FWD_F32_SMALL(128);
-#undef MOGA_FWD_F32_SMALL
+    if (D == 64) MOGA_FWD_F32(64);
+    else MOGA_FWD_F32(128);
+#undef MOGA_FWD_F32
   } else if (small) {
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
@@ -71,18 +71,10 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
         softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, sw, (unsigned short*)tok.o);
     split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, cu_k, M, H, Nq, softmax_scale, (unsigned short*)oh,
                                                                   lse, tok.perm, tok.gate, (unsigned short*)tok.o);
-  } else if (dtype == MOGA_BF16) {
+  } else {
     attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, SplitWs{}, (unsigned short*)tok.o);
-  } else if (D == 64) {
-    attn_fwd_f32_mfma_kernel<64><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
-        softmax_scale, (int)tiles, (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o);
-  } else {
-    attn_fwd_f32_mfma_kernel<128><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(
-        (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,
-        softmax_scale, (int)tiles, (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o);
   }
   return launch_status();
 }
