@@ -243,6 +243,15 @@ int moga_route_bwd(const void* x, int x_dtype, const float* w, const float* prob
                    void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * moga_balance_loss_bwd (accumulating into d_gate, which is not changed here) and moga_route_bwd in one call, with the same
+ * bits: frac [M] from moga_balance_loss of the same M groups; alpha, d_loss and d_loss_device_or_null as there.
+ */
+int moga_route_bwd_balanced(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group,
+                            const float* gate, const float* d_gate, const float* frac, float alpha, float d_loss,
+                            const float* d_loss_device_or_null, int64_t N, int d_model, int M, float* d_w, float* d_x_or_null,
+                            void* ws, size_t ws_bytes, void* stream);
+
+/*
  * Alg. 1 steps 3-4 without materialising the permuted tensors: the kernel loads the rows of group g
  * through perm (row j of the sorted order is token perm[j]) from the token-order tensors
  * q, k, v [N, H, D], and writes o[perm[j]][h][:] = gate[perm[j]] * attention row j (Eq. 5) in

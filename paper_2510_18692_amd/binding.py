@@ -54,6 +54,8 @@ _SIGNATURES = {
     "moga_permute_bwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp]),
     "moga_route_bwd": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp,
                               _sz, _vp]),
+    "moga_route_bwd_balanced": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _f32, _f32, _vp, _i64, _i32, _i32, _vp, _vp, _vp,
+                                       _sz, _vp]),
     "moga_fused_attn_fwd": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _i32, _f32, _vp, _vp, _vp]),
     "moga_fused_attn_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _f32,
                                    _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
@@ -263,6 +265,11 @@ def moga_permute_bwd(d_qh, d_kh, d_vh, perm, stream=None):
 def moga_route_bwd(x, w, probs, group, gate, d_gate, want_dx=False, stream=None):
     """-> (d_w f32 [M, d_model], d_x f32 [N, d_model] | None)"""
     return _nat.route_bwd(x, w, probs, group, gate, d_gate, want_dx, _st(stream))
+
+
+def moga_route_bwd_balanced(x, w, probs, group, gate, d_gate, frac, alpha, d_loss, want_dx=False, stream=None):
+    """moga_balance_loss_bwd (accumulating; d_loss a device scalar) and moga_route_bwd in one call -> (d_w, d_x | None)"""
+    return _nat.route_bwd_balanced(x, w, probs, group, gate, d_gate, frac, alpha, d_loss, want_dx, _st(stream))
 
 
 def moga_fused_attn_fwd(q, k, v, perm, gate, cu_seqlens, softmax_scale, stream=None):

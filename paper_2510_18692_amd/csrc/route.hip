@@ -397,6 +397,20 @@ __global__ __launch_bounds__(64 * NWV, 2) void route_mfma_kernel(
 // ---------------------------------------------------------------------------------------
 // backward: dr = d_gate * gate * (onehot(group) - probs);  dW = dr^T X;  dX = dr W
 // ---------------------------------------------------------------------------------------
+// The gate's gradient: d_gate, and with frac the balancing loss's, rounded as moga_balance_loss_bwd adds it.
+struct GateGrad {
+  const float* d_gate;
+  const float* frac;
+  float coef;
+  const float* d_loss;   // or NULL: on the device
+};
+__device__ __forceinline__ float gate_grad(const GateGrad& gg, int64_t tok, int g, int M) {
+  const float d = gg.d_gate[tok];
+  if (!gg.frac) return d;
+  const float c = gg.d_loss ? gg.coef * gg.d_loss[0] : gg.coef;
+  return d + (g >= 0 && g < M ? c * gg.frac[g] : 0.f);
+}
+
 constexpr int kRbTok = 64;  // tokens per staged tile
 constexpr int kRbMB = 32;   // groups per pass
 
@@ -409,7 +423,7 @@ constexpr int kRbMB = 32;   // groups per pass
 template <typename XT, int MB>
 __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
     const XT* __restrict__ x, const float* __restrict__ probs, const int32_t* __restrict__ group,
-    const float* __restrict__ gate, const float* __restrict__ d_gate, int64_t N, int d, int M,
+    const float* __restrict__ gate, GateGrad gg, int64_t N, int d, int M,
     int64_t tokens_per_split, float* __restrict__ partial /* [splits][M][d] */) {
   constexpr int WT = kRbTok / 4;   // tokens per wave and tile
   __shared__ __attribute__((aligned(16))) float s_dr[kRbTok][MB];
@@ -440,8 +454,9 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
       float v = 0.f;
       if (tb + ti < t1 && j < mb) {
         const int64_t tok = tb + ti;
-        const float coef = d_gate[tok] * gate[tok];
-        const float onehot = (group[tok] == j0 + j) ? 1.f : 0.f;
+        const int g = group[tok];
+        const float coef = gate_grad(gg, tok, g, M) * gate[tok];
+        const float onehot = (g == j0 + j) ? 1.f : 0.f;
         v = coef * (onehot - probs[tok * M + j0 + j]);
       }
       s_dr[ti][j] = v;
@@ -465,6 +480,103 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
     for (int j = 0; j < MB; ++j)
       if (j < mb)
         partial[((int64_t)split * M + j0 + j) * d + c] = (acc[j] + s_acc[0][j][lane]) + (s_acc[1][j][lane] + s_acc[2][j][lane]);
+}
+
+// dW of few tokens in one launch (where the matrix-core path below applies): a block takes 64 columns and all tokens, its sixteen waves
+// every sixteenth run of 16 tokens, and they are added through LDS at the end.  dr is made in registers, in two bf16 limbs as in
+// route_bwd_dr_pack_kernel, as the A operand (groups x tokens) of the 32x32x16 matrix instruction; X is the B operand: a lane loads
+// columns 2 r and 2 r + 1 of eight tokens, one column for each of two accumulators.  The three launches of that path against this
+// one, in us: 64 x 512, 8 groups 10.3 and 4.6; 390 x 1536, 8 groups 12.3 and 4.9; 1,560 x 1536, 4 groups 13.2 and 10.3; 1,560 x
+// 5120, 32 groups 20.8 and 10.7; 2,048 x 1536 13.3 and 12.5, from where they draw level (d / 64 blocks do all the work).
+constexpr int kDwFewWaves = 16, kDwFewTok = 16;   // waves per block, tokens per run
+constexpr int kDwFewTokens = 2048;
+
+__global__ __launch_bounds__(64 * kDwFewWaves) void route_bwd_dw_few_kernel(
+    const unsigned short* __restrict__ x, const float* __restrict__ probs, const int32_t* __restrict__ group, const float* __restrict__ gate,
+    GateGrad gg, int N, int d, int M, float* __restrict__ d_w) {
+  constexpr int STEP = kDwFewTok * kDwFewWaves;
+  __shared__ float s_acc[kDwFewWaves][2][16][64];
+  __shared__ __attribute__((aligned(16))) float s_coef[kDwFewTokens];   // of all tokens, 0 past the end
+  __shared__ __attribute__((aligned(16))) int s_group[kDwFewTokens];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  const unsigned short* xc = x + 64 * blockIdx.x + 2 * r;
+  const float* pc = probs + min(r, M - 1);
+  struct Run {
+    unsigned x[8];
+    float p[8];
+  };
+  auto load = [&](Run& b, int t0) {   // tokens past the end: the last one, not used
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int tok = min(t0 + 8 * h + e, N - 1);
+      b.x[e] = *(const unsigned*)(xc + (int64_t)tok * d);
+      b.p[e] = pc[tok * M];
+    }
+  };
+  Run cur, next;
+  const int first = kDwFewTok * wave;
+  if (first < N) load(cur, first);
+  for (int t = threadIdx.x; t < kDwFewTokens; t += 64 * kDwFewWaves) {
+    const int g = t < N ? group[t] : -1;
+    s_coef[t] = t < N ? gate_grad(gg, t, g, M) * gate[t] : 0.f;
+    s_group[t] = g;
+  }
+  __syncthreads();
+  floatx16_t acc[2];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+  for (int t0 = first; t0 < N; t0 += STEP) {
+    load(next, t0 + STEP);
+    uintx4_t hi, lo, xe, xo;
+#pragma unroll
+    for (int e = 0; e < 8; e += 4) {
+      const floatx4_t coef = *(const floatx4_t*)&s_coef[t0 + 8 * h + e];
+      const uintx4_t g = *(const uintx4_t*)&s_group[t0 + 8 * h + e];
+      float v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float onehot = (int)g[k] == r ? 1.f : 0.f;
+        v[k] = coef[k] * (onehot - cur.p[e + k]);
+        if (r >= M || t0 + 8 * h + e + k >= N) v[k] = 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 4; k += 2) {
+        const unsigned top = pack_bf16x2(v[k], v[k + 1]);
+        hi[(e + k) / 2] = top;
+        lo[(e + k) / 2] = pack_bf16x2(v[k] - bf16_lo_to_f32(top), v[k + 1] - bf16_hi_to_f32(top));
+      }
+    }
+    if (t0 + kDwFewTok > N)   // not a copy of the last row: 0 times an infinity is NaN
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (t0 + 8 * h + e >= N) cur.x[e] = 0u;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      xe[e / 2] = __builtin_amdgcn_perm(cur.x[e + 1], cur.x[e], 0x05040100u);
+      xo[e / 2] = __builtin_amdgcn_perm(cur.x[e + 1], cur.x[e], 0x07060302u);
+    }
+    const bf16x8_t a0 = __builtin_bit_cast(bf16x8_t, hi), a1 = __builtin_bit_cast(bf16x8_t, lo);
+    const bf16x8_t b0 = __builtin_bit_cast(bf16x8_t, xe), b1 = __builtin_bit_cast(bf16x8_t, xo);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b0, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b1, acc[1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b0, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1], 0, 0, 0);
+    cur = next;
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) s_acc[wave][c][v][lane] = acc[c][v];
+  __syncthreads();
+  // wave w: register w of both accumulators, group 8 (w / 4) + 4 h + w % 4, columns 2 r and 2 r + 1
+  floatx2_t sum = {0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < kDwFewWaves; ++k) {
+    sum[0] += s_acc[k][0][wave][lane];
+    sum[1] += s_acc[k][1][wave][lane];
+  }
+  const int j = 8 * (wave >> 2) + 4 * h + (wave & 3);
+  if (j < M) *(floatx2_t*)(d_w + (int64_t)j * d + 64 * blockIdx.x + 2 * r) = sum;
 }
 
 // Sum of the splits, in a fixed order: 64 elements per block, eight waves that take every eighth split
@@ -499,7 +611,7 @@ __global__ __launch_bounds__(512) void route_bwd_dw_reduce_kernel(const float* _
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
     const float* __restrict__ w, const float* __restrict__ probs,
     const int32_t* __restrict__ group, const float* __restrict__ gate,
-    const float* __restrict__ d_gate, int64_t N, int d, int M, float* __restrict__ d_x) {
+    GateGrad gg, int64_t N, int d, int M, float* __restrict__ d_x) {
   __shared__ float s_dr[kRbTok][kRbMB];
   const int c = blockIdx.y * 256 + threadIdx.x;
   const int64_t tb = (int64_t)blockIdx.x * kRbTok;
@@ -515,8 +627,9 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
       float v = 0.f;
       if (ti < nt && j < mb) {
         const int64_t tok = tb + ti;
-        const float coef = d_gate[tok] * gate[tok];
-        const float onehot = (group[tok] == j0 + j) ? 1.f : 0.f;
+        const int g = group[tok];
+        const float coef = gate_grad(gg, tok, g, M) * gate[tok];
+        const float onehot = (g == j0 + j) ? 1.f : 0.f;
         v = coef * (onehot - probs[tok * M + j0 + j]);
       }
       s_dr[ti][j] = v;
@@ -547,7 +660,7 @@ constexpr int kDxTokens = 512;   // tokens per block
 __global__ __launch_bounds__(256) void route_bwd_dx_cols_kernel(
     const float* __restrict__ w, const float* __restrict__ probs,
     const int32_t* __restrict__ group, const float* __restrict__ gate,
-    const float* __restrict__ d_gate, int64_t N, int d, int M, float* __restrict__ d_x) {
+    GateGrad gg, int64_t N, int d, int M, float* __restrict__ d_x) {
   __shared__ __attribute__((aligned(16))) float s_dr[kRbTok][32];
   const int c0 = (blockIdx.y * 256 + threadIdx.x) * 4;
   const bool valid = c0 < d;
@@ -567,8 +680,9 @@ __global__ __launch_bounds__(256) void route_bwd_dx_cols_kernel(
       float v = 0.f;
       if (ti < nt && j < M) {
         const int64_t tok = tb + ti;
-        const float coef = d_gate[tok] * gate[tok];
-        const float onehot = (group[tok] == j) ? 1.f : 0.f;
+        const int g = group[tok];
+        const float coef = gate_grad(gg, tok, g, M) * gate[tok];
+        const float onehot = (g == j) ? 1.f : 0.f;
         v = coef * (onehot - probs[tok * M + j]);
       }
       s_dr[ti][j] = v;
@@ -616,7 +730,7 @@ constexpr int kDwDmaPerStage = kDwXBytes / 1024 + 2;  // direct-to-LDS instructi
 
 __global__ __launch_bounds__(256) void route_bwd_dr_pack_kernel(
     const float* __restrict__ probs, const int32_t* __restrict__ group,
-    const float* __restrict__ gate, const float* __restrict__ d_gate, int64_t N, int M,
+    const float* __restrict__ gate, GateGrad gg, int64_t N, int M,
     int64_t blocks8, uintx4_t* __restrict__ dr_hi, uintx4_t* __restrict__ dr_lo) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t tb = idx >> 5;
@@ -628,8 +742,9 @@ __global__ __launch_bounds__(256) void route_bwd_dr_pack_kernel(
     const int64_t tok = tb * 8 + i;
     float v = 0.f;
     if (tok < N && j < M) {
-      const float coef = d_gate[tok] * gate[tok];
-      const float onehot = (group[tok] == j) ? 1.f : 0.f;
+      const int g = group[tok];
+      const float coef = gate_grad(gg, tok, g, M) * gate[tok];
+      const float onehot = (g == j) ? 1.f : 0.f;
       v = coef * (onehot - probs[tok * M + j]);
     }
     hi[i] = f32_to_bf16_bits(v);
@@ -821,10 +936,9 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
   return launch_status();
 }
 
-extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const float* probs,
-                              const int32_t* group, const float* gate, const float* d_gate,
-                              int64_t N, int d_model, int M, float* d_w, float* d_x,
-                              void* ws, size_t ws_bytes, void* stream) {
+static int launch_route_bwd(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group, const float* gate,
+                            const GateGrad& gg, int64_t N, int d_model, int M, float* d_w, float* d_x, void* ws, size_t ws_bytes,
+                            void* stream) {
   if (N < 0 || d_model < 1 || M < 1) return MOGA_ERR_INVALID_ARG;
   if (x_dtype != MOGA_F32 && x_dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
   if (M > MOGA_MAX_GROUPS || N >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
@@ -836,18 +950,22 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
     fill_zero_kernel<<<(unsigned)((md + 255) / 256), 256, 0, st>>>(d_w, md);
     return launch_status();
   }
-  if (!x || !w || !probs || !group || !gate || !d_gate) return MOGA_ERR_INVALID_ARG;
+  if (!x || !w || !probs || !group || !gate || !gg.d_gate) return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_route_bwd_ws_bytes(N, M, d_model);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
-  if (route_bwd_mfma_ok(x_dtype, M, d_model)) {
-    if (!aligned16(x) || !aligned16(ws)) return MOGA_ERR_INVALID_ARG;
+  const bool mfma = route_bwd_mfma_ok(x_dtype, M, d_model);
+  if (mfma && (!aligned16(x) || !aligned16(ws))) return MOGA_ERR_INVALID_ARG;
+  if (mfma && N <= kDwFewTokens && ((uintptr_t)d_w & 7) == 0) {
+    route_bwd_dw_few_kernel<<<(unsigned)(d_model / 64), 64 * kDwFewWaves, 0, st>>>((const unsigned short*)x, probs, group, gate, gg,
+                                                                                  (int)N, d_model, M, d_w);
+  } else if (mfma) {
     const DwPlan p = route_bwd_plan(N, M, d_model);
     uintx4_t* dr_hi = (uintx4_t*)ws;
     uintx4_t* dr_lo = (uintx4_t*)((char*)ws + p.dr_bytes);
     float* partial = (float*)((char*)ws + 2 * p.dr_bytes);
     const int64_t blocks8 = p.total_steps * 2;
     route_bwd_dr_pack_kernel<<<(unsigned)((blocks8 * 32 + 255) / 256), 256, 0, st>>>(
-        probs, group, gate, d_gate, N, M, blocks8, dr_hi, dr_lo);
+        probs, group, gate, gg, N, M, blocks8, dr_hi, dr_lo);
     const unsigned blocks = (unsigned)((p.splits + 7) / 8 * 8 * p.nslabs);
     route_bwd_dw_mfma_kernel<<<blocks, 64, 0, st>>>((const unsigned short*)x, dr_hi, dr_lo, N, d_model,
                                                     p.nslabs, p.splits, p.steps_per_split,
@@ -862,7 +980,7 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
     dim3 grid((d_model + 63) / 64, splits, (M + mb - 1) / mb);
     float* partial = (float*)ws;
 #define MOGA_DW_PARTIAL(XT, MB)                                                                             \
-  route_bwd_dw_partial_kernel<XT, MB><<<grid, 256, 0, st>>>((const XT*)x, probs, group, gate, d_gate, N,    \
+  route_bwd_dw_partial_kernel<XT, MB><<<grid, 256, 0, st>>>((const XT*)x, probs, group, gate, gg, N,    \
                                                             d_model, M, tps, partial)
     if (x_dtype == MOGA_F32) {
       if (mb == 8) MOGA_DW_PARTIAL(float, 8);
@@ -877,11 +995,29 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
   if (d_x) {
     if (M <= 32 && d_model % 4 == 0 && aligned16(d_x) && aligned16(w)) {
       dim3 gx((unsigned)((N + kDxTokens - 1) / kDxTokens), (d_model + 1023) / 1024);
-      route_bwd_dx_cols_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, d_gate, N, d_model, M, d_x);
+      route_bwd_dx_cols_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, gg, N, d_model, M, d_x);
     } else {
       dim3 gx((unsigned)((N + kRbTok - 1) / kRbTok), (d_model + 255) / 256);
-      route_bwd_dx_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, d_gate, N, d_model, M, d_x);
+      route_bwd_dx_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, gg, N, d_model, M, d_x);
     }
   }
   return launch_status();
+}
+
+extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const float* probs,
+                              const int32_t* group, const float* gate, const float* d_gate,
+                              int64_t N, int d_model, int M, float* d_w, float* d_x,
+                              void* ws, size_t ws_bytes, void* stream) {
+  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, nullptr, 0.f, nullptr}, N, d_model, M, d_w, d_x, ws,
+                          ws_bytes, stream);
+}
+
+extern "C" int moga_route_bwd_balanced(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group,
+                                       const float* gate, const float* d_gate, const float* frac, float alpha, float d_loss,
+                                       const float* d_loss_dev, int64_t N, int d_model, int M, float* d_w, float* d_x, void* ws,
+                                       size_t ws_bytes, void* stream) {
+  if (N > 0 && !frac) return MOGA_ERR_INVALID_ARG;
+  const float coef = N > 0 ? (float)((double)d_loss * (double)alpha * (double)M / (double)N) : 0.f;   // as moga_balance_loss_bwd
+  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, frac, coef, d_loss_dev}, N, d_model, M, d_w, d_x, ws,
+                          ws_bytes, stream);
 }

@@ -268,20 +268,49 @@ std::tuple<Tensor, Tensor, Tensor> permute_bwd(const Tensor& d_qh, const Tensor&
   return {d_q, d_k, d_v};
 }
 
-std::tuple<Tensor, OptTensor> route_bwd(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
-                                        const Tensor& d_gate, bool want_dx, const OptStream& stream) {
-  require(x, w, probs, group, gate, d_gate);
+// An upstream gradient on the device as an fp32 scalar; a conversion runs in order with the kernel that reads it.
+Tensor device_scalar(const Tensor& t, const Call& call) {
+  c10::OptionalStreamGuard guard;
+  if (call.other()) guard.reset_stream(*call.other());
+  return t.reshape({1}).to(at::kFloat);
+}
+
+// frac: also the balancing loss's share of the gate's gradient.
+std::tuple<Tensor, OptTensor> route_bwd_with(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
+                                             const Tensor& d_gate, const OptTensor& frac, double alpha, const OptTensor& d_loss, bool want_dx,
+                                             const OptStream& stream) {
+  require(x, w, probs, group, gate, d_gate, frac);
   const Call call(stream);
   need_dims(x, 2);
   const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
   Tensor d_w = call.make({M, d}, x, at::kFloat);
-  OptTensor d_x;
+  OptTensor d_x, dev;
   if (want_dx) d_x = call.make({N, d}, x, at::kFloat);
   Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), x);
-  check("moga_route_bwd", moga_route_bwd(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate),
-                                         as<float>(d_gate), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x), ptr(ws), ws.numel(),
-                                         call.stream()));
+  if (frac) {
+    TORCH_CHECK(frac->size(0) == M, "frac of ", frac->size(0), " groups for a router of ", M);
+    if (d_loss) dev = device_scalar(*d_loss, call);
+    check("moga_route_bwd_balanced",
+          moga_route_bwd_balanced(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate), as<float>(d_gate),
+                                  as<float>(frac), (float)alpha, 1.f, as<float>(dev), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x),
+                                  ptr(ws), ws.numel(), call.stream()));
+  } else {
+    check("moga_route_bwd", moga_route_bwd(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate),
+                                           as<float>(d_gate), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x), ptr(ws), ws.numel(),
+                                           call.stream()));
+  }
   return {d_w, d_x};
+}
+
+std::tuple<Tensor, OptTensor> route_bwd(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
+                                        const Tensor& d_gate, bool want_dx, const OptStream& stream) {
+  return route_bwd_with(x, w, probs, group, gate, d_gate, std::nullopt, 0., std::nullopt, want_dx, stream);
+}
+
+std::tuple<Tensor, OptTensor> route_bwd_balanced(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group,
+                                                 const Tensor& gate, const Tensor& d_gate, const Tensor& frac, double alpha,
+                                                 const Tensor& d_loss, bool want_dx, const OptStream& stream) {
+  return route_bwd_with(x, w, probs, group, gate, d_gate, frac, alpha, d_loss, want_dx, stream);
 }
 
 std::tuple<Tensor, Tensor> fused_attn_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& perm, const Tensor& gate,
@@ -482,11 +511,7 @@ Tensor balance_loss_bwd(const Tensor& group, const Tensor& frac, double alpha, d
   const int64_t N = group.size(0), M = frac.size(0);
   Tensor d_gate = into ? *into : call.make({N}, group, at::kFloat);
   OptTensor dev;
-  if (d_loss_dev) {   // a conversion runs in order with the kernel that reads it
-    c10::OptionalStreamGuard guard;
-    if (call.other()) guard.reset_stream(*call.other());
-    dev = d_loss_dev->reshape({1}).to(at::kFloat);
-  }
+  if (d_loss_dev) dev = device_scalar(*d_loss_dev, call);
   check("moga_balance_loss_bwd", moga_balance_loss_bwd(as<int32_t>(group), as<float>(frac), N, (int)M, (float)alpha, (float)d_loss,
                                                        as<float>(dev), into ? 1 : 0, as<float>(d_gate), call.stream()));
   return d_gate;
@@ -526,8 +551,9 @@ struct Attention : public torch::autograd::Function<Attention> {
     Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros({qh.size(1), qh.size(0), qh.size(2)}, qh.options());
     TokenGrads g = group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu, scale, perm, gate, false, std::nullopt);
     g.d_oh.reset();
-    if (alpha && grads[1].defined()) balance_loss_bwd(group, frac, *alpha, 1.0, grads[1], g.d_gate, std::nullopt);
-    auto [d_w, d_x] = route_bwd(x, w, probs, group, gate, g.d_gate, grad_x, std::nullopt);
+    const bool balanced = alpha && grads[1].defined();
+    auto [d_w, d_x] = route_bwd_with(x, w, probs, group, gate, g.d_gate, balanced ? OptTensor(frac) : std::nullopt, alpha.value_or(0.),
+                                     balanced ? OptTensor(grads[1]) : std::nullopt, grad_x, std::nullopt);
     Tensor dx;
     if (d_x) dx = d_x->to(x.scalar_type());
     return {dx, d_w, g.d_q, g.d_k, g.d_v, Tensor(), Tensor(), Tensor()};
@@ -567,6 +593,7 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
       nogil);
   m.def("permute_bwd", &permute_bwd, nogil);
   m.def("route_bwd", &route_bwd, nogil);
+  m.def("route_bwd_balanced", &route_bwd_balanced, nogil);
   m.def("fused_attn_fwd", &fused_attn_fwd, nogil);
   m.def("fused_attn_bwd", &fused_attn_bwd, nogil);
   m.def("varlen_attn_fwd", &varlen_attn_fwd, nogil);
