@@ -23,7 +23,23 @@ constexpr int kPipeTileBytes = 64 * kHeadDim * 2; // 16 KB per K (or V) tile
 struct PipeLane {
   unsigned k[4];   // K rows
   unsigned v[8];   // V transposed
+  bf16x8_t pairs;  // A operand of the row sums: lane (r, g) has row r's ones if they are among its keys 8 g .. 8 g + 7
 };
+
+__device__ __forceinline__ bf16x8_t pair_ones(int lane) {
+  const int r = lane & 15;
+  uintx4_t v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = r == 4 * (lane >> 4) + i ? 0x3f803f80u : 0u;
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+
+// The sum of a row's sixteen shares, four in each of its four lanes.
+__device__ __forceinline__ float row_sum(const floatx4_t& l) {
+  float s = (l[0] + l[1]) + (l[2] + l[3]);
+  s += __shfl_xor(s, 16, kWave);
+  return s + __shfl_xor(s, 32, kWave);
+}
 
 // Raw scores of a step: [key operand t][query half]; register i is key 8 g + 4 t + i of query column r
 typedef floatx4_t StepScores[2][2];
@@ -66,7 +82,8 @@ struct PipeState {
   // O^T: [d tiles 4 D .. 4 D + 3][query half], 16 registers each.  As sixteen vectors of four the compiler joins the two
   // sides of the rare branch in maybe_rescale by moving all 64 registers in every step.
   floatx16_t o[2][2];
-  float m[2], l[2], negmc[2];     // running max (raw score units), this lane's share of the row sum, -m*c
+  floatx4_t l[2];                 // this lane's shares of the row sum: register i has the keys 8 g + 2 i and + 1 of all steps
+  float m[2], negmc[2];           // running max (raw score units), -m*c
   float thresh[2];                // m + tau: the max is raised only when a score exceeds this
 };
 
@@ -74,7 +91,7 @@ __device__ __forceinline__ void pipe_state_init(PipeState& st) {
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     st.m[q] = -INFINITY;
-    st.l[q] = 0.f;
+    st.l[q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
     st.negmc[q] = 0.f;
     st.thresh[q] = -INFINITY;
 #pragma unroll
@@ -139,8 +156,6 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
   for (int dt = 0; dt < 8; ++dt) vf[dt] = lds_read_tr_frag(ln.v[dt] + voff + VOFF);
 
   // P = exp2(S*c - m*c), packed to bf16; row sum from the rounded values
-  typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-  const bf16x2v ones = {(__bf16)1.0f, (__bf16)1.0f};
   unsigned int pk[2][4];
   if (HAS_NEXT) {
 #pragma unroll
@@ -163,13 +178,18 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
       const float p0 = fast_exp2(fmaf(v[2 * (ks & 1)], c, st.negmc[q]));
       const float p1 = fast_exp2(fmaf(v[2 * (ks & 1) + 1], c, st.negmc[q]));
       pk[q][ks] = pack_bf16x2(p0, p1);
-      st.l[q] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, pk[q][ks]), ones, st.l[q], false);
     }
   }
   wave_priority<PRIO, 0>();
   bf16x8_t pf[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) pf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{pk[q][0], pk[q][1], pk[q][2], pk[q][3]});
+  // The row sums are one more d tile, whose row j has ones at keys 2 j and 2 j + 1 of the step: v_dot2c_f32_bf16, which summed two of the rounded weights at a time, does not run
+  // beside the matrix instructions (alternating with them it adds its 8 cycles to their 16, where an fma or a conversion adds
+  // none), and eight of them a step cost more than these two products: 62,400 x 12 heads, 5 groups 3.89 -> 3.70 ms (on zeros
+  // 3.33 -> 3.07), 32,760 x 12, 8 groups 698 -> 676 us, 99,840 x 40, 16 groups 10.7 -> 10.35 ms.
+#pragma unroll
+  for (int q = 0; q < 2; ++q) st.l[q] = mfma16(ln.pairs, pf[q], st.l[q]);
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
@@ -193,8 +213,7 @@ __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int g
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    float lt = st.l[q] + __shfl_xor(st.l[q], 16, kWave);
-    lt += __shfl_xor(lt, 32, kWave);
+    const float lt = row_sum(st.l[q]);
     float inv = 1.f / lt;
     const int qrow = q0w + 16 * q + r;
     if (qrow < ge) {
@@ -230,8 +249,7 @@ __device__ __forceinline__ void store_piece(const PipeState& st, const SplitWs& 
   const size_t row0 = slot * kSplitRows + 32 * wave;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
-    float lt = st.l[q] + __shfl_xor(st.l[q], 16, kWave);
-    lt += __shfl_xor(lt, 32, kWave);
+    const float lt = row_sum(st.l[q]);
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) store_partial(sw.part + row0 * kHeadDim, dt, q, quarter(st.o[dt >> 2][q], dt & 3));
     if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{st.m[q], lt};
@@ -472,6 +490,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   PipeLane ln;
   nat_addresses(ln.k, &Ks[0][0], lane);
   tr_addresses(ln.v, &Vs[0][0], lane);
+  ln.pairs = pair_ones(lane);
   PipeState st;
   pipe_state_init(st);
 

@@ -78,6 +78,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   PipeLane ln;
   nat_addresses(ln.k, &Ks[0][0], lane);
   tr_addresses(ln.v, &Vs[0][0], lane);
+  ln.pairs = pair_ones(lane);
   PipeState st;
   pipe_state_init(st);
 
