@@ -9,8 +9,10 @@
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both kernels also come as 4-wave blocks with a two-slot
 // ring (64 KB of LDS), two blocks per CU, for groups of a few thousand rows or less.
-// dQ is at the power cap like the forward; dK/dV, at 2.20-2.29 of 2.39 GHz with the matrix pipes busy 0.54 of the time, is
-// bound by issue and by the exchange of P.  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40
+// dQ is at the power cap like the forward; dK/dV runs at 2.20-2.29 of 2.39 GHz with the matrix pipes busy 0.54 of the time.  The
+// exchange of P does not bound it (B a whole tile behind A: the same time).  LDS fragments read beside the products cost both
+// kernels matrix time: a loop of 16x16x32 products takes 7.2 ns each at the top clock, and with a fragment read for every two 8.3
+// (row fragments) or 8.6 (transposing reads).  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40
 // heads, 32 groups; 2.73 and 2.67 ms at 32,760 x 12, 8 groups.
 #pragma once
 
@@ -507,9 +509,10 @@ __device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigne
     ab_take_p(ln, sc[1], 1, bop[1]);
     __hip_atomic_store(taken, tile_no + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
-  ab_load_nat<NOFF, NROW>(ln, noff, noff_row, nat0, ini0);
-  // The second products go first when the SIMD's two waves compete (with the scores first: 593 against 582 ms at 580,320 x 40 heads).
+  // The reads for the next tile and the second products go first when the SIMD's two waves compete (with the scores first: 593
+  // against 582 ms at 580,320 x 40 heads; the products alone: 1 % more on zeros, 0.6 % at 32,760 x 12).
   wave_priority<true, 1>();
+  ab_load_nat<NOFF, NROW>(ln, noff, noff_row, nat0, ini0);
   ab_accumulate(tr0, bop[0], acc);
   ab_accumulate(tr1, bop[1], acc);
   wave_priority<true, 0>();

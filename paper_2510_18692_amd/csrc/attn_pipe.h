@@ -144,6 +144,11 @@ template <bool PRIO, bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
 __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff, const bf16x8_t (&qf)[2][4],
                                           PipeState& st, const StepScores& s_cur, StepScores& s_next, float (&mx)[2],
                                           float c) {
+  // The scores and exponentials are the long chain of a step: they go first when the SIMD's two waves compete, and the
+  // other wave's PV products fill the gaps (580,320 x 40 heads: 175.4 -> 169.4 ms; the other way round 5 % slower).
+  // From the step's first LDS reads on, and the row sums last among the products: 62,400 x 12 heads on zeros 3.08 -> 3.00 ms,
+  // 32,760 x 12 669 -> 666 us, within the noise where the power limit binds.
+  wave_priority<PRIO, 1>();
   bf16x8_t kf[2][4];
   if (HAS_NEXT) {
 #pragma unroll
@@ -163,9 +168,6 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
 #pragma unroll
       for (int q = 0; q < 2; ++q) s_next[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
-  // The scores and exponentials are the long chain of a step: they go first when the SIMD's two waves compete, and the
-  // other wave's PV products fill the gaps (580,320 x 40 heads: 175.4 -> 169.4 ms; the other way round 5 % slower).
-  wave_priority<PRIO, 1>();
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
@@ -189,8 +191,6 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
   // none), and eight of them a step cost more than these two products: 62,400 x 12 heads, 5 groups 3.89 -> 3.70 ms (on zeros
   // 3.33 -> 3.07), 32,760 x 12, 8 groups 698 -> 676 us, 99,840 x 40, 16 groups 10.7 -> 10.35 ms.
 #pragma unroll
-  for (int q = 0; q < 2; ++q) st.l[q] = mfma16(ln.pairs, pf[q], st.l[q]);
-#pragma unroll
   for (int dt = 0; dt < 8; ++dt)
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -199,6 +199,8 @@ __device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, uns
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[4 * (dt & 3) + e] = t[e];
     }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) st.l[q] = mfma16(ln.pairs, pf[q], st.l[q]);
   if (HAS_NEXT) step_max(s_next, mx);
 }
 
