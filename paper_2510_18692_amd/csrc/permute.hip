@@ -1253,7 +1253,8 @@ extern "C" int moga_merge3_bwd_rows(const void* d_o, const void* a_moga, const v
   const int bad = check_rows_args(dtype, N, H, D);
   if (bad) return bad;
   if (N == 0) return MOGA_OK;
-  if (!a_stga || !a_frame || !lse_moga || !lse_stga || !lse_frame || !aligned16(a_stga) || !aligned16(a_frame) || !(softmax_scale > 0.f))
+  if (!a_stga || !a_frame || !lse_moga || !lse_stga || !lse_frame || !aligned16(a_stga) || !aligned16(a_frame) || !(softmax_scale > 0.f) ||
+      !(softmax_scale < INFINITY))
     return MOGA_ERR_INVALID_ARG;
   const size_t status = moga_attn_bwd_status_offset(N, H);
   if (!ws_moga || !ws_stga || !ws_frame || ws_bytes < status + 16) return MOGA_ERR_WORKSPACE;

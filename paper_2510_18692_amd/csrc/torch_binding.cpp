@@ -458,7 +458,10 @@ Rows3Out merge3_bwd_rows(const Tensor& d_o, const Tensor& a_moga, const Tensor& 
   need_dims(d_o, 3);
   const int64_t N = d_o.size(0), H = d_o.size(1), D = d_o.size(2);
   Tensor d_m = call.make({H, N, D}, d_o), d_s = call.make({H, N, D}, d_o), d_f = call.make({H, N, D}, d_o), d_gate = call.make({N}, d_o, at::kFloat);
-  auto ws = [&](int64_t Nk, const Tensor& cu) { return *call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, N, Nk, H, D, cu.size(0) - 1, d_o); };
+  auto ws = [&](int64_t Nk, const Tensor& cu) {
+    const OptTensor t = call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, N, Nk, H, D, cu.size(0) - 1, d_o);
+    return t ? *t : call.workspace(0, d_o);   // no rows
+  };
   Tensor ws_m = ws(N, cu_moga), ws_s = ws(n_keys, cu_q), ws_f = ws(N, cu_frame);
   const size_t bytes = std::min({ws_m.numel(), ws_s.numel(), ws_f.numel()});
   check("moga_merge3_bwd_rows",
