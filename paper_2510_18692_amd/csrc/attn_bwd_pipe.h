@@ -9,7 +9,7 @@
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both kernels also come as 4-wave blocks with a two-slot
 // ring (64 KB of LDS), two blocks per CU, for groups of a few thousand rows or less.
-// dQ is at the power cap like the forward; dK/dV runs at 2.20-2.29 of 2.39 GHz with the matrix pipes busy 0.54 of the time.  The
+// dQ is at the power cap like the forward; dK/dV runs at 2.14 of 2.38 GHz with the matrix pipes busy 0.61 of the time.  The
 // exchange of P does not bound it (B a whole tile behind A: the same time).  LDS fragments read beside the products cost both
 // kernels matrix time: a loop of 16x16x32 products takes 7.2 ns each at the top clock, and with a fragment read for every two 8.3
 // (row fragments) or 8.6 (transposing reads).  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40

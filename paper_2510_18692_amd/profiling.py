@@ -31,7 +31,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 _KERNEL_CALL = [
     ("route_mfma", "moga_route"), ("route_generic", "moga_route"),
     ("chunk_hist", "moga_permute"), ("chunk_scan", "moga_permute"), ("chunk_rank", "moga_permute"),
-    ("permute_single_block", "moga_permute"), ("gather_rows_kernel", "moga_permute"),
+    ("permute_single_block", "moga_permute"), ("permute_gather", "moga_permute"), ("gather_rows_kernel", "moga_permute"),
     ("attn_fwd", "moga_group_attn_fwd"), ("split_fwd", "moga_group_attn_fwd"), ("split_sum", "moga_group_attn_bwd"),
     ("unpermute_bwd", "moga_unpermute_bwd"),
     ("attn_bwd", "moga_group_attn_bwd"),
