@@ -207,8 +207,8 @@ int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, 
  * moga_varlen_attn_bwd_rows, moga_fused_attn_bwd).  Inside the dK/dV kernels one wave of a pair waits for values
  * (small groups) or for a word (large ones) that its partner publishes through LDS; the wait is bounded, and a
  * wave that gives up sets an int32 status word in the workspace to a nonzero value and carries on, so the
- * kernel always drains (the gradients of that call are then invalid).  The word lies at byte offset moga_attn_bwd_status_offset(Nq, H) of
- * ws, is cleared by every call and is valid in stream order after it; it reads 0 after every
+ * kernel always drains (the gradients of that call are then invalid).  The word lies at byte offset
+ * moga_attn_bwd_status_offset(Nq, H) of ws, is cleared by every call and is valid in stream order after it; it reads 0 after every
  * correct run.  moga_debug_set_spin_limit sets the number of polls before a give-up (default 2^24;
  * 0 makes every not-yet-satisfied wait give up at once: for tests of this path only).  Host-only.
  */
@@ -220,8 +220,9 @@ void moga_debug_set_spin_limit(int polls);
  * 128-row (dK/dV) tiles, and 4-wave blocks with tiles half as large, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
  * group size N / M (forward: below 1792 rows from 16 rounds of 256 256-row tiles on, below 2560 from one round on, else
- * below 6144; backward: below 500, 860 and 3900; the moga_fused_* calls always take the first set).  Both sets give the same results up
- * to rounding order.  moga_debug_set_small_group_rows overrides all thresholds (0: never the small
+ * below 5632; backward: below 500, 860 and, below one round, 1450 from three quarters of it on, else 2000; the
+ * moga_fused_* calls always take the first set).  Both sets give the same results up to rounding order.
+ * moga_debug_set_small_group_rows overrides all thresholds (0: never the small
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.
  */
 void moga_debug_set_small_group_rows(int64_t rows);

@@ -116,12 +116,13 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
 }
 
 // Mean rows per group below which the small-group bf16 kernels run, by rounds of 256 blocks of 256 rows: their finer tiles win
-// where there are few.  Against the long-group kernels: half a round (12,000 x 3 heads) 36 % faster at 900 rows, 3 % at 3,000,
-// equal at 4,000; 6 rounds (32,760 x 12) 2 % faster at 700, 1 % slower at 900; 61 rounds (99,840 x 40) 7 % faster at 400, 1 %
-// slower at 520, 4.5 % at 780.
+// where there are few.  Against the long-group kernels: half a round (12,000 x 3 heads) 32 % faster at 900 rows, 8 % at 2,000; 0.4
+// rounds (6,000 x 4) 3 % at 1,500, 1 % slower at 2,000; 0.7 rounds (12,000 x 4) 7 % faster at 1,500, 1 and 7 % slower at 2,000 and
+// 3,000; 0.9 rounds (15,000 x 4) 3.5 % faster at 1,000, 1 and 6 % slower at 1,500 and 2,143; 6 rounds (32,760 x 12) 2 % faster at
+// 700, 1 % slower at 900; 61 rounds (99,840 x 40) 3 % faster at 400, 5 % slower at 520.
 static int64_t small_group_rows(int64_t Nq, int H) {
-  const int64_t rounds = Nq * H / (256 * kCus);
-  return rounds >= 16 ? 500 : rounds >= 1 ? 860 : 3900;
+  const int64_t quarters = 4 * Nq * H / (256 * kCus);
+  return quarters >= 64 ? 500 : quarters >= 4 ? 860 : quarters >= 3 ? 1450 : 2000;
 }
 
 }  // namespace moga

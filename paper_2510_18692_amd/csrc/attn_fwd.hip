@@ -18,12 +18,12 @@
 namespace moga {
 
 // Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of the other one: it wins by
-// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) 4 % faster at 780 rows, even
-// from 1,560 to 2,080, 3 % slower at 3,120; 6 rounds (32,760 x 12) 10 % faster at 1,560, 6 % at 2,050, equal at 2,730; half a
-// round (12,000 x 3) 14 % faster at 2,000, 6 % at 4,000, equal at 6,000.
+// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) 3 % faster at 780 rows, 1 % at
+// 1,560, 2 % slower at 2,080; 6 rounds (32,760 x 12) 3 % faster at 1,560 and 2,340, equal at 2,047, 1 % slower at 2,730; half a
+// round (9,000 to 12,000 x 3) 10 % faster at 2,000 and 4,500, 8 % at 5,000, 4 % slower at 6,000.
 static int64_t small_group_rows(int64_t Nq, int H) {
   const int64_t rounds = Nq * H / (256 * kCus);
-  return rounds >= 16 ? 1792 : rounds >= 1 ? 2560 : 6144;
+  return rounds >= 16 ? 1792 : rounds >= 1 ? 2560 : 5632;
 }
 
 }  // namespace moga
