@@ -185,8 +185,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
         (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
-    const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
-                       (max_tiles(Nq, M, 128) + max_tiles(Nk, M, 64)) * H + 16 < ((int64_t)1 << 31);   // one launch
+    const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
     const int bk = small ? 64 : 128, bm = small ? 128 : 256;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
     const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
@@ -194,10 +193,18 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, bk, ts_k);
     if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, ts_q);
     if (small) {
-      attn_bwd_small_kernel<<<(unsigned)(q_blocks + k_blocks), 256, 0, st>>>(
-          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta,
-          cu_q, cu_k, ts_q, ts_k, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, (unsigned short*)d_kh, (unsigned short*)d_vh,
-          g_spin_limit.load(), status, tok.perm, d_q_tok, d_k_tok, d_v_tok, (int)q_blocks);
+      auto launch = [&](int64_t dq_blocks, int64_t dkdv_blocks) {
+        attn_bwd_small_kernel<<<(unsigned)(dq_blocks + dkdv_blocks), 256, 0, st>>>(
+            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta,
+            cu_q, cu_k, ts_q, ts_k, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, (unsigned short*)d_kh, (unsigned short*)d_vh,
+            g_spin_limit.load(), status, tok.perm, d_q_tok, d_k_tok, d_v_tok, (int)dq_blocks);
+      };
+      if (grid_fits(q_blocks + k_blocks, 256)) {
+        launch(q_blocks, k_blocks);
+      } else {   // millions of groups
+        launch(q_blocks, 0);
+        if (k_blocks > 0) launch(0, k_blocks);
+      }
       return launch_status();
     }
     if (Nk > 0) {
@@ -227,8 +234,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
           (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
   } else {
     const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
-    const int64_t blocks = (q_tiles + k_tiles) * H;
-    if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+    if ((q_tiles + k_tiles) * H >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
     if (!tok.row_constants) {
       int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
       const unsigned grid = (unsigned)((rows * (D / 4) + 255) / 256);
@@ -241,14 +247,22 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     }
     if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
     if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
+    auto launch = [&](int64_t dq_blocks, int64_t dkdv_blocks) {
 #define MOGA_BWD_F32(DD)                                                                                              \
-  attn_bwd_f32_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                          \
+  attn_bwd_f32_kernel<DD><<<(unsigned)(dq_blocks + dkdv_blocks), 64 * kF32Waves, 0, st>>>(                           \
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k, ts_q, ts_k, M, Nq,   \
-      Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)(k_tiles * H), (float*)d_qh, (float*)d_kh, (float*)d_vh,        \
+      Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)dkdv_blocks, (float*)d_qh, (float*)d_kh, (float*)d_vh,          \
       tok.perm, (float*)tok.d_q, (float*)tok.d_k, (float*)tok.d_v)
-    if (D == 64) MOGA_BWD_F32(64);
-    else MOGA_BWD_F32(128);
+      if (D == 64) MOGA_BWD_F32(64);
+      else MOGA_BWD_F32(128);
 #undef MOGA_BWD_F32
+    };
+    if (grid_fits((q_tiles + k_tiles) * H, 64 * kF32Waves)) {
+      launch(q_tiles * H, k_tiles * H);
+    } else {
+      if (k_tiles > 0) launch(0, k_tiles * H);
+      launch(q_tiles * H, 0);
+    }
   }
   return launch_status();
 }

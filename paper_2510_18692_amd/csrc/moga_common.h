@@ -120,6 +120,8 @@ struct RowConstants {
 // moga_unpermute_bwd; rc: NULL, or the row constants as well
 int launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32_t* perm, const float* gate, int64_t N, int H,
                          int D, void* d_oh, float* d_gate, const RowConstants* rc, hipStream_t st);
+// HIP takes fewer than 2^32 threads in a grid; of more it launches what is left of the number in 32 bits, without an error.
+inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < ((int64_t)1 << 32); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int launch_status() { return hipGetLastError() == hipSuccess ? MOGA_OK : MOGA_ERR_HIP; }
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
