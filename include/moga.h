@@ -21,8 +21,10 @@
  *     D head_dim.  Token-order tensors are [N, H, D] row-major; group-contiguous
  *     ("hat") tensors are head-major [H, N, D], row j of a head being sorted slot j.
  *   - Supported: M in [1, 256]; N < 2^31 (N < 2^24 for the BF16 attention calls, whose kernels
- *     address the rows of a group with 32-bit byte offsets); dtype F32 with D in {64, 128} and
- *     dtype BF16 with D = 128.  Anything else returns MOGA_ERR_UNSUPPORTED.
+ *     address the rows of a group with 32-bit byte offsets, and N < 2^28 for the calls that move rows);
+ *     dtype F32 with D in {64, 128} and dtype BF16 with D = 128; launches of fewer than 2^32 threads (an
+ *     attention call has, per head, 256 for every group and 256 for every 16 rows (F32), 128 queries or 64
+ *     keys (BF16), half as many with the large-group kernels).  Anything else returns MOGA_ERR_UNSUPPORTED.
  */
 #ifndef MOGA_H_
 #define MOGA_H_

@@ -13,6 +13,7 @@
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
 // read the transposed operands (dO^T, Q^T, K^T) from row-major LDS tiles with the transposing
 // LDS read.  fp32 (attn_f32.h): delta, then dQ and dK/dV in one launch.
+#include <algorithm>
 #include <atomic>
 
 #include "attn_common.h"
@@ -52,6 +53,16 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const uintx4_t* __r
     neg_delta[row] = -s;
     if (BF16) neg_lse_over_scale[row] = -lse[row] * inv_scale;
   }
+}
+
+template <int LPR, bool BF16>
+static void launch_delta(const void* d_oh, const void* oh, const float* lse, int64_t rows, float inv_scale, float* neg_delta,
+                         float* neg_lse_over_scale, int* status, hipStream_t st) {
+  constexpr int64_t kRows = (int64_t)1 << 26;   // of a launch: 16 or 32 threads each, 2^32 are too many
+  for (int64_t r = 0; r < rows; r += kRows)
+    attn_bwd_delta_kernel<LPR, BF16><<<(unsigned)((std::min(rows - r, kRows) * LPR + 255) / 256), 256, 0, st>>>(
+        (const uintx4_t*)d_oh + r * LPR, (const uintx4_t*)oh + r * LPR, lse + r, std::min(rows - r, kRows), inv_scale, neg_delta + r,
+        BF16 ? neg_lse_over_scale + r : nullptr, status);
 }
 
 // Pre-pass of the gather-fused backward (bf16, head_dim 128; token-major inputs).  With O = gate * A
@@ -176,20 +187,18 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
                            float* delta, const TokenGrads& tok, void* split, hipStream_t st) {
   unsigned short *d_q_tok = (unsigned short*)tok.d_q, *d_k_tok = (unsigned short*)tok.d_k, *d_v_tok = (unsigned short*)tok.d_v;
   const int64_t rows = Nq * (int64_t)H;
-  if ((rows * 32 + 255) / 256 >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;   // grid of the delta kernel
+  int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
   if (dtype == MOGA_BF16) {
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
-    float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
-    int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-    if (!tok.row_constants) attn_bwd_delta_kernel<16, true><<<(unsigned)((rows * 16 + 255) / 256), 256, 0, st>>>(
-        (const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 1.f / softmax_scale, delta, lse2, status);
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
     const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
     const int bk = small ? 64 : 128, bm = small ? 128 : 256;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
     const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
-    if (k_blocks >= ((int64_t)1 << 31) || q_blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+    if (!grid_fits(std::max(k_blocks, q_blocks), small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
+    float* lse2 = delta + rows;   // holds -lse/scale; `delta` holds -delta
+    if (!tok.row_constants) launch_delta<16, true>(d_oh, oh, lse, rows, 1.f / softmax_scale, delta, lse2, status, st);
     if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, bk, ts_k);
     if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, ts_q);
     if (small) {
@@ -234,17 +243,9 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
           (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
   } else {
     const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
-    if ((q_tiles + k_tiles) * H >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    if (!tok.row_constants) {
-      int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
-      const unsigned grid = (unsigned)((rows * (D / 4) + 255) / 256);
-      if (D == 64)
-        attn_bwd_delta_kernel<16, false><<<grid, 256, 0, st>>>((const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 0.f, delta,
-                                                               nullptr, status);
-      else
-        attn_bwd_delta_kernel<32, false><<<grid, 256, 0, st>>>((const uintx4_t*)d_oh, (const uintx4_t*)oh, lse, rows, 0.f, delta,
-                                                               nullptr, status);
-    }
+    if (!grid_fits(std::max(q_tiles, k_tiles) * H, 64 * kF32Waves)) return MOGA_ERR_UNSUPPORTED;
+    if (!tok.row_constants && D == 64) launch_delta<16, false>(d_oh, oh, lse, rows, 0.f, delta, nullptr, status, st);
+    if (!tok.row_constants && D == 128) launch_delta<32, false>(d_oh, oh, lse, rows, 0.f, delta, nullptr, status, st);
     if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
     if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
     auto launch = [&](int64_t dq_blocks, int64_t dkdv_blocks) {
@@ -347,9 +348,8 @@ static int varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
   hipStream_t st = (hipStream_t)stream;
   if (Nq == 0) {   // keys without any query: zero gradients
     const int64_t nf = Nk * (int64_t)H * D / (dtype == MOGA_BF16 ? 2 : 1);
-    if ((nf + 255) / 256 >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;   // grid of the fill kernel
-    fill_zero_kernel<<<(unsigned)((nf + 255) / 256), 256, 0, st>>>((float*)d_kh, nf);
-    fill_zero_kernel<<<(unsigned)((nf + 255) / 256), 256, 0, st>>>((float*)d_vh, nf);
+    launch_fill_zero((float*)d_kh, nf, st);
+    launch_fill_zero((float*)d_vh, nf, st);
     return launch_status();
   }
   const size_t need = moga_varlen_attn_bwd_ws_bytes(Nq, H, G);
@@ -404,27 +404,19 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
+  const int64_t k_blocks = (max_tiles(N, M, 128) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, 256) * H + 7) / 8 * 8;
+  if (!grid_fits(k_blocks, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + 15) / 16), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate,
       status);
-  {
-    const int64_t tiles = max_tiles(N, M, 128);
-    const int64_t blocks = (tiles * H + 7) / 8 * 8;
-    if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    attn_bwd_dkdv_ab_kernel<true><<<(unsigned)blocks, 512, 0, st>>>(
-        (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
-        (unsigned short*)d_v, g_spin_limit.load(), status, perm);
-  }
-  {
-    const int64_t tiles = max_tiles(N, M, 256);
-    const int64_t blocks = (tiles * H + 7) / 8 * 8;
-    if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-    attn_bwd_dq_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, st>>>(
-        (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-        lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q,
-        perm);
-  }
+  attn_bwd_dkdv_ab_kernel<true><<<(unsigned)k_blocks, 512, 0, st>>>(
+      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
+      lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
+      (unsigned short*)d_v, g_spin_limit.load(), status, perm);
+  attn_bwd_dq_pipe_kernel<8, true><<<(unsigned)q_blocks, 512, 0, st>>>(
+      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
+      lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q,
+      perm);
   return launch_status();
 }
 

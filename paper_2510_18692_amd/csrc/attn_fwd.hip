@@ -50,7 +50,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
-  if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+  if (!grid_fits(blocks, dtype == MOGA_BF16 && !small ? 512 : 256)) return MOGA_ERR_UNSUPPORTED;
   if (tile_start) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, tile_start);
   if (dtype == MOGA_F32) {
 #define MOGA_FWD_F32(DD)                                                                                                   \
@@ -142,7 +142,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (!(aligned16(q) && aligned16(k) && aligned16(v) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
   const int64_t tiles = max_tiles(N, M, 256);
   const int64_t blocks = (tiles * H + 7) / 8 * 8;
-  if (blocks >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
+  if (!grid_fits(blocks, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_fwd_bf16_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(
       (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, cu_seqlens, cu_seqlens,
       nullptr, M, N, N, H, softmax_scale, (unsigned short*)o, lse, perm, gate);

@@ -119,9 +119,9 @@ extern "C" int moga_balance_loss(const int32_t* group, const float* gate, int64_
   if (!loss || !frac || !prob) return MOGA_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (N == 0) {   // no tokens: F = P = 0, L = 0
-    fill_zero_kernel<<<1, 256, 0, st>>>(frac, M);
-    fill_zero_kernel<<<1, 256, 0, st>>>(prob, M);
-    fill_zero_kernel<<<1, 256, 0, st>>>(loss, 1);
+    launch_fill_zero(frac, M, st);
+    launch_fill_zero(prob, M, st);
+    launch_fill_zero(loss, 1, st);
     return launch_status();
   }
   if (!group || !gate) return MOGA_ERR_INVALID_ARG;
@@ -133,7 +133,7 @@ extern "C" int moga_balance_loss(const int32_t* group, const float* gate, int64_
   }
   BalanceAcc* acc = (BalanceAcc*)ws;
   const int64_t ws_floats = (int64_t)(moga_balance_ws_bytes(M) / sizeof(float));
-  fill_zero_kernel<<<(unsigned)((ws_floats + 255) / 256), 256, 0, st>>>((float*)ws, ws_floats);
+  launch_fill_zero((float*)ws, ws_floats, st);
   const unsigned blocks = (unsigned)std::min<int64_t>(1024, (N + 1023) / 1024);
   balance_accumulate_kernel<<<blocks, 256, 0, st>>>(group, gate, N, M, acc);
   balance_finalize_kernel<<<1, 256, 0, st>>>(acc, N, M, alpha, loss, frac, prob);

@@ -102,9 +102,8 @@ __device__ __forceinline__ int other_half_i(int v) { return __shfl_xor(v, 32, kW
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Zero fill as a kernel (a memset node inside a captured graph is avoided on purpose).
-[[maybe_unused]] static __global__ void fill_zero_kernel(float* p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.f;
+[[maybe_unused]] static __global__ __launch_bounds__(256) void fill_zero_kernel(float* p, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0.f;
 }
 
 // ---- host side ------------------------------------------------------------
@@ -122,6 +121,9 @@ int launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const int32
                          int D, void* d_oh, float* d_gate, const RowConstants* rc, hipStream_t st);
 // HIP takes fewer than 2^32 threads in a grid; of more it launches what is left of the number in 32 bits, without an error.
 inline bool grid_fits(int64_t blocks, int threads) { return blocks * threads < ((int64_t)1 << 32); }
+[[maybe_unused]] static void launch_fill_zero(float* p, int64_t n, hipStream_t st) {
+  fill_zero_kernel<<<(unsigned)((n + 255) / 256 < (1 << 20) ? (n + 255) / 256 : 1 << 20), 256, 0, st>>>(p, n);
+}
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int launch_status() { return hipGetLastError() == hipSuccess ? MOGA_OK : MOGA_ERR_HIP; }
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }

@@ -869,7 +869,7 @@ static int lanes_per_row(int dtype, int D) {
 static int check_rows_args(int dtype, int64_t N, int H, int D) {
   if (N < 0 || H < 1 || D < 1) return MOGA_ERR_INVALID_ARG;
   if (dtype != MOGA_F32 && dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
-  if (N >= ((int64_t)1 << 31) || lanes_per_row(dtype, D) == 0) return MOGA_ERR_UNSUPPORTED;
+  if (!grid_fits((N + kSlotsPerBlock - 1) / kSlotsPerBlock, 256) || lanes_per_row(dtype, D) == 0) return MOGA_ERR_UNSUPPORTED;
   return MOGA_OK;
 }
 

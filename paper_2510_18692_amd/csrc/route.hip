@@ -26,6 +26,8 @@ template <> __device__ __forceinline__ float load_x<unsigned short>(const unsign
   return bf16_bits_to_f32(*p);
 }
 
+constexpr int64_t kGenericTokens = (int64_t)1 << 25;   // of a launch: 64 threads each, 2^32 are too many
+
 template <typename XT>
 __global__ __launch_bounds__(256) void route_generic_kernel(
     const XT* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
@@ -925,13 +927,17 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
                                                      group, gate, probs, logits);
     }
   } else {
-    const unsigned blocks = (unsigned)((N + 3) / 4);
-    if (x_dtype == MOGA_F32)
-      route_generic_kernel<float><<<blocks, 256, 0, st>>>((const float*)x, w, bias, N, d_model, M,
-                                                         group, gate, probs, logits);
-    else
-      route_generic_kernel<unsigned short><<<blocks, 256, 0, st>>>(
-          (const unsigned short*)x, w, bias, N, d_model, M, group, gate, probs, logits);
+    for (int64_t t = 0; t < N; t += kGenericTokens) {
+      const int64_t n = std::min(N - t, kGenericTokens);
+      const unsigned blocks = (unsigned)((n + 3) / 4);
+      float *const pr = probs ? probs + t * M : nullptr, *const lo = logits ? logits + t * M : nullptr;
+      if (x_dtype == MOGA_F32)
+        route_generic_kernel<float><<<blocks, 256, 0, st>>>((const float*)x + t * d_model, w, bias, n, d_model, M, group + t, gate + t,
+                                                           pr, lo);
+      else
+        route_generic_kernel<unsigned short><<<blocks, 256, 0, st>>>((const unsigned short*)x + t * d_model, w, bias, n, d_model, M,
+                                                                     group + t, gate + t, pr, lo);
+    }
   }
   return launch_status();
 }
@@ -942,12 +948,14 @@ static int launch_route_bwd(const void* x, int x_dtype, const float* w, const fl
   if (N < 0 || d_model < 1 || M < 1) return MOGA_ERR_INVALID_ARG;
   if (x_dtype != MOGA_F32 && x_dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
   if (M > MOGA_MAX_GROUPS || N >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
-  if (d_model > (1 << 24)) return MOGA_ERR_UNSUPPORTED;   // keeps every grid size below 2^31 blocks
+  if (d_model > (1 << 24)) return MOGA_ERR_UNSUPPORTED;
   if (!d_w) return MOGA_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int64_t md = (int64_t)M * d_model;
+  if (!grid_fits(((int64_t)(M + 7) / 8 * 8 * d_model + 63) / 64, 512) || (d_x && !grid_fits((N + kRbTok - 1) / kRbTok, 256)))
+    return MOGA_ERR_UNSUPPORTED;
   if (N == 0) {
-    fill_zero_kernel<<<(unsigned)((md + 255) / 256), 256, 0, st>>>(d_w, md);
+    launch_fill_zero(d_w, md, st);
     return launch_status();
   }
   if (!x || !w || !probs || !group || !gate || !gg.d_gate) return MOGA_ERR_INVALID_ARG;
