@@ -7,7 +7,8 @@
 //                    first slot for that group; also counts, cu_seqlens, max_seqlen;
 //   3. chunk_rank  : each wave walks its chunk in token order; a token's slot is its chunk's
 //                    running base for the group plus its rank among equal ids in the batch.
-// Up to 16,384 tokens and 32 groups one block does all three (permute_single_block).
+// Up to 16,384 tokens and 32 groups one block does all three (permute_single_block), and with rows to move, where that pays,
+// every block of the gather for itself (permute_gather).
 // Data part: 16-byte-per-lane row copies between token order [N, H, D] and head-major
 // group-contiguous order [H, N, D]; the scatter back multiplies by the gate (Eq. 5).
 #include <mutex>
@@ -304,10 +305,16 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t
 // of all three) and finds their slots by itself: it counts the ids of all tokens and of those before its own (up to 64 per
 // thread, 8-bit counters packed four to a word, summed over the waves) while its first rows are on the way.  The sort as a launch
 // of its own is one block that the chip waits for.  Two launches against this one, in us: 4,096 x 12 heads x 128 bf16, 8 groups
-// 17.8 and 13.7 (5.5 TB/s); 10,007 x 12, 20 groups 39.9 and 36.6; 16,384 x 12, 8 groups 64 and 54, 24 heads, 32 groups 136 and
-// 127.  Above 4,096 tokens the count is paid back by a token's rows: 4 heads (1 KB a tensor) 16.0 and 14.7 at 8,192 tokens, 29.5
-// and 20.8 at 16,384; 2 heads 11.5 and 12.2, 1 head 10.1 and 22.8.
-constexpr int64_t kFusedSortTokens = 16384, kFusedSortRowBytes = 1024;
+// 18.3 and 13.7 (5.5 TB/s); 10,007 x 12, 20 groups 39.3 and 37.8; 16,384 x 12, 8 groups 64 and 54, 32 groups 71 and 59.
+// The count is paid back by a token's rows (bytes of one tensor) where the tokens are many, and it has four times the counters
+// above 8 groups.  Two launches against one: 8 groups, 256-byte rows 7.6 and 6.3 at 4,096 tokens, 10.1 and 22.8 at 16,384; 1 KB rows
+// 16.1 and 12.1 at 8,192, 29.3 and 21.5 at 16,384.  20 groups, 256-byte rows 7.3 and 6.2 at 2,048, 17 % slower at 4,096; 1 KB rows 7 to
+// 30 % slower from 4,097 to 14,000, 2 KB rows 2 % faster on the mean and 8 % slower at 8,193, 3 KB rows 3 % slower at 5,000 and 18 %
+// faster at 16,384.
+inline bool use_permute_gather(int64_t N, int M, int64_t row_bytes) {
+  if (M <= 8) return N <= 4096 || (N <= 16384 && row_bytes >= 1024);
+  return M <= 32 && (N <= 2048 || (N <= 16384 && row_bytes >= 3072));
+}
 
 template <int LPR, int WORDS, int PER>   // WORDS * 4 >= groups, PER * 256 >= tokens
 __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int32_t* __restrict__ group, int N, int H, int M, int nbits,
@@ -892,7 +899,7 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int num_chunks = perm_num_chunks(N);
   const int nbits = bits_for(M);
   const int64_t row_bytes = (int64_t)H * lanes_per_row(dtype, D) * 16;
-  if (with_data && N > 0 && M <= kSingleBlockGroups && (N <= 4096 || (N <= kFusedSortTokens && row_bytes >= kFusedSortRowBytes))) {
+  if (with_data && N > 0 && use_permute_gather(N, M, row_bytes)) {
     const Rows3 p = {{q, k, v}, {qh, kh, vh}};
     const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), N > 4096 ? 1 : 3);   // few rows: a block per tensor
 #define MOGA_PERMUTE_GATHER(LPR, WORDS, PER)                                                                                  \
