@@ -319,11 +319,16 @@ __global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
   route_finish(total, tok0 + r, h, bias, N, M, group, gate, probs, logits);
 }
 
-// The other kernel's blocks of 128 tokens run 256 at a time; it is the better one where their last round is almost full.  Its
-// time and that of the kernel above in us (1536 channels): 24,000 tokens 24.2 and 21.4, 28,000 25.2 and 24.9, 32,768 25.1 and
-// 26.1; 33,000 40.0 and 26.6, 50,000 42.5 and 37.2, 62,400 44.9 and 43.0 (5120 channels: 143 and 149, 512: 18.4 and 19.8).
-inline bool use_route_few(int64_t N, int d_model) {
-  return ((N + 127) / 128 - 1) % 256 < 224 && d_model <= (1 << 20);   // 32-bit offsets within W
+// The other kernel's blocks of 128 tokens run 256 at a time; it is the better one where their last round is well filled, from an
+// earlier point on where a token brings few channels.  Its time and that of the kernel above in us: 24,000 tokens x 1536, 20 groups 20.9
+// and 18.7, x 128, 8 groups 7.1 and 5.8; 28,672 x 1536 21.5 and 21.9, x 5120, 32 groups 71 and 80, x 128 7.1 and 8.0; 35,000 x 1536
+// 34.3 and 25.6, x 512 15.1 and 12.5, x 128 8.9 and 9.0; 50,000 x 128 8.9 and 11.0, x 512 15.7 and 17.0, x 1536 34.6 and 33.2;
+// 53,000 x 5120, 16 groups 135 and 125, 32 groups 143 and 148.
+inline bool use_route_few(int64_t N, int d_model, int M) {
+  if (d_model > (1 << 20)) return false;   // 32-bit offsets within W
+  const int64_t blocks = (N + 127) / 128;
+  if (blocks <= 256) return blocks <= 192;
+  return d_model >= 256 && blocks > 257 && blocks <= (d_model >= 2560 && M <= 20 ? 448 : 384);
 }
 
 // The weight chunk is double-buffered: while the matrix cores work on chunk c, the fp32 weights of
@@ -917,7 +922,7 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
       const unsigned blocks = (unsigned)((N + 255) / 256);
       route_mfma_kernel<1, 8><<<blocks, 512, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                      group, gate, probs, logits);
-    } else if (use_route_few(N, d_model)) {
+    } else if (use_route_few(N, d_model, M)) {
       const unsigned blocks = (unsigned)((N + 31) / 32);
       route_mfma_few_kernel<4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                        group, gate, probs, logits);

@@ -34,7 +34,8 @@ def test_fp32_infinite_last_row_is_counted_once(n, D):
 # blocks of 32 tokens whose four waves share 64-channel blocks: remainders of both, fewer channel blocks than waves, both sides of
 # the lines to the other kernel
 @pytest.mark.parametrize("N,d,M", [(1, 64, 1), (31, 128, 32), (32, 256, 5), (33, 320, 20), (500, 576, 31), (16384, 192, 8),
-                                   (28672, 128, 20), (28673, 128, 20), (32768, 128, 20), (32769, 128, 20)])
+                                   (28672, 128, 20), (28673, 128, 20), (32768, 128, 20), (32769, 128, 20), (24576, 128, 20), (24577, 128, 20),
+                                   (32896, 256, 20), (32897, 256, 20), (49152, 256, 20), (49153, 256, 20)])
 def test_router_of_few_tokens(N, d, M):
     tf.test_route_matches_oracle(N, d, M, "bf16", N % 2 == 1)
 
