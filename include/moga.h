@@ -221,8 +221,8 @@ void moga_debug_set_spin_limit(int polls);
  * The BF16 attention calls have two sets of kernels: 8-wave blocks with 256-row (forward, dQ) or
  * 128-row (dK/dV) tiles, and 4-wave blocks with tiles half as large, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
- * group size N / M (forward: below 1792 rows from 16 rounds of 256 256-row tiles on, below 2560 from one round on, else
- * below 5632; backward: below 500, 860 and, below one round, 1450 from three quarters of it on, else 2000; the
+ * group size N / M (forward: below 1152 rows from 16 rounds of 256 256-row tiles on, 2560 from one round on, 6144 from
+ * half a round on, else 5632; backward: below 500, 860 and, below one round, 1450 from three quarters of it on, else 2000; the
  * moga_fused_* calls always take the first set).  Both sets give the same results up to rounding order.
  * moga_debug_set_small_group_rows overrides all thresholds (0: never the small
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.

@@ -18,12 +18,14 @@
 namespace moga {
 
 // Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of the other one: it wins by
-// finer tiles where there are few.  Small against large kernel: 61 rounds (99,840 x 40 heads) 3 % faster at 780 rows, 1 % at
-// 1,560, 2 % slower at 2,080; 6 rounds (32,760 x 12) 3 % faster at 1,560 and 2,340, equal at 2,047, 1 % slower at 2,730; half a
-// round (9,000 to 12,000 x 3) 10 % faster at 2,000 and 4,500, 8 % at 5,000, 4 % slower at 6,000.
+// finer tiles where there are few.  Small against large kernel, groups of equal size / Zipf(1.45): 23 rounds (38,400 x 40 heads) 3 and
+// 6 % slower at 1,200 rows, 29 (48,000 x 40) 2 and 6 % at 1,500; 6 rounds (32,760 x 12), equal groups, 3 % faster at 1,560 and 2,340,
+// equal at 2,047, 1 % slower at 2,730; 0.5 rounds (11,400 x 3) equal and 22 % faster at 5,700, 0.7 (45,600 x 1) 8 % slower and 18 %
+// faster; 0.35 (22,800 x 1), where the other kernel splits all of its tiles, 4 and 32 % slower at 5,700, and at 2,000 to 4,500 (9,000 to
+// 12,000 x 3), equal groups, 10 % faster.
 static int64_t small_group_rows(int64_t Nq, int H) {
-  const int64_t rounds = Nq * H / (256 * kCus);
-  return rounds >= 16 ? 1792 : rounds >= 1 ? 2560 : 5632;
+  const int64_t quarters = 4 * Nq * H / (256 * kCus);
+  return quarters >= 64 ? 1152 : quarters >= 4 ? 2560 : quarters >= 2 ? 6144 : 5632;
 }
 
 }  // namespace moga
