@@ -543,7 +543,9 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   constexpr int kAhead = NB - 2;
   constexpr int kDmaPerTile = 2 * (16 / NW) + 2;
 
-  if (threadIdx.x < NPAIR) lds.flag[threadIdx.x] = 0;   // ordered before its first use by the barriers below
+  // Ordered before its first use by the barriers below.  With NB == 4 and no polls the first wait (of P nobody needs yet) finds its
+  // word not there, so that a test reaches the give-up for certain.
+  if (threadIdx.x < NPAIR) lds.flag[threadIdx.x] = NB == 4 && spin_limit == 0 ? -1 : 0;
   WorkTile sp;
   if (!find_work<SPLIT>(cu_k, tile_start, M, H, BK, block, sp)) return;
   const TileInfo& ti = sp.ti;

@@ -177,7 +177,8 @@ def test_single_group_backward_has_zero_router_gradient():
     P.assert_close_f32(P.to64(bg["d_q"]), b["dQ"], "dQ (M=1)")
 
 
-def test_bounded_wait_of_the_dkdv_kernel_reports_a_give_up_and_never_fires_normally():
+@pytest.mark.parametrize("small_rows", [0, 1 << 40], ids=["large-group kernel", "small-group kernel"])
+def test_bounded_wait_of_the_dkdv_kernel_reports_a_give_up_and_never_fires_normally(small_rows):
     """The partner wait inside the dK/dV kernel is bounded: the status word of the workspace reads 0
     after a normal run; with the poll limit forced to 0 from the host every unsatisfied wait gives up,
     the word becomes nonzero and the kernel still drains; afterwards a normal run is correct again."""
@@ -202,14 +203,17 @@ def test_bounded_wait_of_the_dkdv_kernel_reports_a_give_up_and_never_fires_norma
         for name, got, ref in (("dQ", d_qh, dQ), ("dK", d_kh, dK), ("dV", d_vh, dV)):
             check(P.unhat(got), ref, name, "bf16")
 
-    run_and_check()
     try:
+        mg.set_small_group_rows(small_rows)
+        run_and_check()
         mg.set_spin_limit(0)
         mg.moga_group_attn_bwd(*args, ws=ws)
         torch.cuda.synchronize()            # the kernel drained
         flagged = int(status.item())
+        mg.set_spin_limit(1 << 24)
+        say(f"  status word with the poll limit forced to 0: {flagged}")
+        assert flagged != 0
+        run_and_check()
     finally:
         mg.set_spin_limit(1 << 24)
-    say(f"  status word with the poll limit forced to 0: {flagged}")
-    assert flagged != 0
-    run_and_check()
+        mg.set_small_group_rows(-1)

@@ -67,8 +67,19 @@ def test_balancing_loss_in_one_block(N, M):
     tl.test_balance_loss_matches_oracle(N, M, True)
 
 
-@pytest.mark.parametrize("N,H,D,dtype", [(1, 1, 64, torch.float32), (17, 5, 128, torch.float32), (700, 3, 128, torch.bfloat16), (2500, 2, 128, torch.bfloat16)])
-def test_branch_rows_and_constants_are_those_of_the_separate_calls(N, H, D, dtype):
+# bf16: the small-group kernels (`large` False), and the large-group ones with a split round
+@pytest.mark.parametrize("N,H,D,dtype,large", [
+    (1, 1, 64, torch.float32, False), (17, 5, 128, torch.float32, False), (700, 3, 128, torch.bfloat16, False),
+    (2500, 2, 128, torch.bfloat16, False), (700, 3, 128, torch.bfloat16, True), (2500, 2, 128, torch.bfloat16, True)])
+def test_branch_rows_and_constants_are_those_of_the_separate_calls(N, H, D, dtype, large):
+    try:
+        mg.set_small_group_rows(0 if large else 1 << 40)
+        branch_rows_and_constants(N, H, D, dtype, large)
+    finally:
+        mg.set_small_group_rows(-1)
+
+
+def branch_rows_and_constants(N, H, D, dtype, split):
     g = torch.Generator(device="cuda").manual_seed(N)
     q, k, v, d_o = (torch.randn((N, H, D), generator=g, device="cuda").to(dtype) for _ in range(4))
     inv_m, q_slot = (torch.randperm(N, generator=g, device="cuda").to(torch.int32) for _ in range(2))
@@ -95,6 +106,8 @@ def test_branch_rows_and_constants_are_those_of_the_separate_calls(N, H, D, dtyp
     for x, y in zip(r[:4], want_d):
         assert torch.equal(x, y)
     for (t, cq, ck), (o, lse), d, ws in zip(branches, fwd, want_d, r[4:]):
+        need = mg.workspace_bytes(mg.OP_VARLEN_ATTN_BWD, N, H, D, cq.numel() - 1, 0, mg.MOGA_BF16 if dtype == torch.bfloat16 else mg.MOGA_F32)
+        assert (ws.numel() > need + (32 << 20)) == split   # room for the pieces
         want_g = mg.moga_varlen_attn_bwd(d, *t, o, lse, cq, ck, scale)
         for x, y in zip(mg.moga_varlen_attn_bwd_rows(d, *t, o, lse, cq, ck, scale, ws), want_g):
             assert torch.equal(x, y)
