@@ -3,12 +3,14 @@
 // With P = exp(scale*S - lse) and delta = rowsum(dO * O):
 //   dV = P^T dO,  dP = dO V^T,  dS = P * (dP - delta),  dQ = scale dS K,  dK = scale dS^T Q.
 //
-// Three kernels, no atomics; results do not depend on scheduling, only (in their rounding) on whether the workspace has room
+// No atomics; results do not depend on scheduling, only (in their rounding) on whether the workspace has room
 // to split the last round:
-//   attn_bwd_delta   : delta[h][j] = sum_c dO[h][j][c] * O[h][j][c]   (bf16)
-//   attn_bwd_dkdv    : a wave owns 32 key rows (K, V fragments and the dK^T, dV^T accumulators
-//                      live in registers) and sweeps the query tiles of its group;
-//   attn_bwd_dq      : a wave owns 32 query rows and sweeps the key tiles (mirror of forward).
+//   attn_bwd_delta   : -delta[h][j] = -sum_c dO[h][j][c] * O[h][j][c], and in bf16 -lse / scale; the calls that
+//                      write dO themselves (_tokens) or are given these constants (_rows) do without it;
+//   attn_bwd_dkdv_ab : a pair of waves owns 32 key rows and sweeps the query tiles of its group, one wave with
+//                      the K fragments and the dV^T accumulators, the other with the V fragments and dK^T;
+//   attn_bwd_dq_pipe : a wave owns 32 query rows and sweeps the key tiles (mirror of forward);
+//   attn_bwd_small   : both with smaller tiles in one launch, for small groups.
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
 // read the transposed operands (dO^T, Q^T, K^T) from row-major LDS tiles with the transposing
@@ -21,7 +23,6 @@
 #include "attn_f32.h"
 
 namespace moga {
-
 
 // ---------------------------------------------------------------------------------------
 // LPR lanes of 16 bytes a row.  neg_lse_over_scale and its lse: bf16 only.
@@ -164,7 +165,7 @@ extern "C" size_t moga_attn_bwd_ws_bytes(int64_t N, int H, int D, int dtype) {
   return bwd_rows_bytes(N, H) + 16;
 }
 
-// Polls after which a wave of the dK/dV kernel that waits for its partner's P gives up (and sets the
+// Polls after which a wave of the dK/dV kernels that waits for its partner gives up (and sets the
 // status word).  In normal operation a wait lasts a few hundred polls at most.
 static std::atomic<int> g_spin_limit{1 << 24};
 extern "C" void moga_debug_set_spin_limit(int polls) { g_spin_limit.store(polls < 0 ? 0 : polls); }
@@ -222,26 +223,26 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     }
     if (Nk > 0) {
       if (split && split_pays(k_tiles * H)) {
-        attn_bwd_dkdv_ab_kernel<false, 4, 4, true><<<(unsigned)(k_blocks + kCus), 512, 0, st>>>(
+        attn_bwd_dkdv_ab_kernel<false, true><<<(unsigned)(k_blocks + kCus), 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
             g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
         split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 2, 1.f, softmax_scale,
                                                             (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
       } else
-        attn_bwd_dkdv_ab_kernel<false><<<(unsigned)k_blocks, 512, 0, st>>>(
+        attn_bwd_dkdv_ab_kernel<<<(unsigned)k_blocks, 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
             (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
     }
     if (split && split_pays(q_tiles * H)) {
-      attn_bwd_dq_pipe_kernel<8, false, 4, true><<<(unsigned)(q_blocks + kCus), 512, 0, st>>>(
+      attn_bwd_dq_pipe_kernel<false, true><<<(unsigned)(q_blocks + kCus), 512, 0, st>>>(
           (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
           delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
       split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
                                                           (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
     } else
-      attn_bwd_dq_pipe_kernel<8><<<(unsigned)q_blocks, 512, 0, st>>>(
+      attn_bwd_dq_pipe_kernel<<<(unsigned)q_blocks, 512, 0, st>>>(
           (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
           (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
           (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
@@ -417,7 +418,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
       lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
       (unsigned short*)d_v, g_spin_limit.load(), status, perm);
-  attn_bwd_dq_pipe_kernel<8, true><<<(unsigned)q_blocks, 512, 0, st>>>(
+  attn_bwd_dq_pipe_kernel<true><<<(unsigned)q_blocks, 512, 0, st>>>(
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
       lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q,
       perm);

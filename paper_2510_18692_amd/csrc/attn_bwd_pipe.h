@@ -7,8 +7,8 @@
 //                               tiles of Q, dO, lse and delta; one wave computes S, P and dV^T,
 //                               the other dP, dS and dK^T (P handed over through LDS).
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
-// ahead; one block-wide barrier per tile.  Both kernels also come as 4-wave blocks with a two-slot
-// ring (64 KB of LDS), two blocks per CU, for groups of a few thousand rows or less.
+// ahead; one block-wide barrier per tile.  Both also come as 4-wave blocks with a two-slot ring (64 KB of
+// LDS), two blocks per CU, in one launch (attn_bwd_small_kernel), for groups of a few thousand rows or less.
 // dQ is at the power cap like the forward; dK/dV runs at 2.14 of 2.38 GHz with the matrix pipes busy 0.61 of the time.  The
 // exchange of P does not bound it (B a whole tile behind A: the same time).  LDS fragments read beside the products cost both
 // kernels matrix time: a loop of 16x16x32 products takes 7.2 ns each at the top clock, and with a fragment read for every two 8.3
@@ -293,8 +293,8 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, d_q_tok, perm);
 }
 
-template <int NW, bool GATHER = false, int NB = 4, bool SPLIT = false>
-__global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_kernel(
+template <bool GATHER = false, bool SPLIT = false>
+__global__ __launch_bounds__(512, 1) void attn_bwd_dq_pipe_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
@@ -302,9 +302,9 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
-  __shared__ DqLds<NB> lds;
-  attn_bwd_dq_block<NW, GATHER, NB, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
-                                           M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
+  __shared__ DqLds<4> lds;
+  attn_bwd_dq_block<8, GATHER, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
+                                         M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -312,12 +312,18 @@ __global__ __launch_bounds__(NW * 64, NB == 2 ? 2 : 1) void attn_bwd_dq_pipe_ker
 // same 32 key rows.  Wave A (waves 0-3) holds K and the dV^T accumulators: it computes S = Q K^T,
 // P = exp2(c*S - lse*log2e), hands P to its partner through LDS and accumulates dV^T += dO^T P.
 // Wave B (waves 4-7, same SIMD as its partner) holds V and the dK^T accumulators: it computes
-// dP = dO V^T - delta, waits for P, forms dS = P * dP and accumulates dK^T += Q^T dS.  Each wave
+// dP = dO V^T - delta, takes P, forms dS = P * dP and accumulates dK^T += Q^T dS.  Each wave
 // needs 64 accumulator registers instead of 128, so two waves fit on a SIMD and fill each other's
-// waits.  One block-wide barrier per 64-query tile (tile landed, ring slot free); P is handed over
-// inside the pair with a flag in LDS (release store by A, acquire spin by B), so the pairs and the
-// two roles drift apart instead of meeting twice per tile.  A never waits for B outside the block
-// barrier, so every spin ends.
+// waits.  There is one block-wide barrier per 64-query tile (tile landed, ring slot free) and one P buffer
+// per pair, and P is handed over in one of two ways:
+//   * two-slot ring (small groups, ab_tile): by a stamp in LDS.  A writes P and then the tile's number
+//     (release), B spins on the number (acquire); the roles drift apart between the barriers.  A publishes
+//     the stamp of a tile before it reaches the next barrier and waits for B nowhere else, so the spin ends,
+//     and it rewrites P only behind that barrier, which B reaches after it has taken P.
+//   * four-slot ring (ab_tile_long): by the barrier itself, which stands behind A's writes of P.  B takes P
+//     behind it and then counts the tile in LDS (release); A spins on that count (acquire) before it rewrites
+//     P in the next tile.  B waits for nothing between the barrier and the count, so the spin ends.
+// Both spins are bounded (spin_until), so the kernels drain whatever happens.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ void lds_write_b128(unsigned addr, bf16x8_t v) {
   *(bf16x8_t __attribute__((address_space(3)))*)(uintptr_t)addr = v;
@@ -525,7 +531,7 @@ struct DkdvLds {
   __attribute__((aligned(1024))) unsigned short q[NB][64 * kHeadDim], d_o[NB][64 * kHeadDim];
   __attribute__((aligned(1024))) unsigned char p[NPAIR][4096];   // P of one tile, per pair
   __attribute__((aligned(256))) float l[NB][64], d[NB][64];      // -lse / scale, -delta
-  int flag[NPAIR];   // per pair: number of tiles whose P has been written
+  int flag[NPAIR];   // per pair: number of tiles whose P has been written (NB == 2) or taken (NB == 4)
 };
 
 template <bool GATHER, int NPAIR, int NB, bool SPLIT>
@@ -691,8 +697,8 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, tokp, perm);
 }
 
-template <bool GATHER = false, int NPAIR = 4, int NB = 4, bool SPLIT = false>
-__global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab_kernel(
+template <bool GATHER = false, bool SPLIT = false>
+__global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_ab_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
@@ -702,10 +708,9 @@ __global__ __launch_bounds__(NPAIR * 128, NB == 2 ? 2 : 1) void attn_bwd_dkdv_ab
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
     unsigned short* __restrict__ d_v_tok = nullptr) {
-  __shared__ DkdvLds<NPAIR, NB> lds;
-  attn_bwd_dkdv_block<GATHER, NPAIR, NB, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k,
-                                                tile_start, M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok,
-                                                d_v_tok);
+  __shared__ DkdvLds<4, 4> lds;
+  attn_bwd_dkdv_block<GATHER, 4, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
+                                           M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok, d_v_tok);
 }
 
 // Both for small groups, in one launch: blocks below `dq_blocks` (a multiple of 8, for the XCDs) are dQ's, the others dK/dV's.

@@ -238,10 +238,10 @@ __device__ __forceinline__ void route_finish(const floatx16_t& total, int64_t to
 // 16,384 x 1536, 8 groups 21.7 and 13.8 (3.6 TB/s).  Eight waves to a block are slower from 10,007 tokens on (15.0).
 constexpr int kFewW = 32 * 256, kFewX = 32 * 128;   // bytes of a wave's k block
 
-template <int NWV>
-__global__ __launch_bounds__(64 * NWV, 3) void route_mfma_few_kernel(
+__global__ __launch_bounds__(256, 3) void route_mfma_few_kernel(
     const unsigned short* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias, int64_t N, int d, int M,
     int32_t* __restrict__ group, float* __restrict__ gate, float* __restrict__ probs, float* __restrict__ logits) {
+  constexpr int NWV = 4;
   __shared__ __attribute__((aligned(1024))) unsigned char s_k[NWV][kFewW + kFewX];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
@@ -924,7 +924,7 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
                                                      group, gate, probs, logits);
     } else if (use_route_few(N, d_model, M)) {
       const unsigned blocks = (unsigned)((N + 31) / 32);
-      route_mfma_few_kernel<4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
+      route_mfma_few_kernel<<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
                                                        group, gate, probs, logits);
     } else {
       const unsigned blocks = (unsigned)((N + 127) / 128);
