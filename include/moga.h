@@ -207,12 +207,14 @@ int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, 
 /*
  * Diagnostics of the BF16 backward calls (moga_group_attn_bwd, moga_group_attn_bwd_tokens, moga_varlen_attn_bwd,
  * moga_varlen_attn_bwd_rows, moga_fused_attn_bwd).  Inside the dK/dV kernels one wave of a pair waits for values
- * (small groups) or for a word (large ones) that its partner publishes through LDS; the wait is bounded, and a
+ * (small groups) or for a count (large ones) that its partner publishes through LDS; the wait is bounded, and a
  * wave that gives up sets an int32 status word in the workspace to a nonzero value and carries on, so the
  * kernel always drains (the gradients of that call are then invalid).  The word lies at byte offset
  * moga_attn_bwd_status_offset(Nq, H) of ws, is cleared by every call and is valid in stream order after it; it reads 0 after every
- * correct run.  moga_debug_set_spin_limit sets the number of polls before a give-up (default 2^24;
- * 0 makes every not-yet-satisfied wait give up at once: for tests of this path only).  Host-only.
+ * correct run.  The exception is moga_varlen_attn_bwd_rows: its word is cleared by the moga_merge3_bwd_rows that writes
+ * its row constants, and a second call on the same workspace leaves what the first one recorded.
+ * moga_debug_set_spin_limit sets the number of polls before a give-up (default 2^24; 0 makes every not-yet-satisfied
+ * wait give up at once, and with large groups the first one for certain: for tests of this path only).  Host-only.
  */
 size_t moga_attn_bwd_status_offset(int64_t Nq, int H);
 void moga_debug_set_spin_limit(int polls);
@@ -314,7 +316,8 @@ int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const
                          float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
                          void* ws, size_t ws_bytes, void* stream);
 
-/* The same where moga_merge3_bwd_rows has written the call's row constants to ws: they are not computed again. */
+/* The same where moga_merge3_bwd_rows has written the call's row constants to ws and cleared its status word: they are not
+ * computed again, and the word is not cleared again. */
 int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, const void* vh,
                               const void* oh, const float* lse, int dtype,
                               int64_t Nq, int64_t Nk, int H, int D,

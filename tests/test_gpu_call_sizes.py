@@ -111,3 +111,4 @@ def branch_rows_and_constants(N, H, D, dtype, split):
         want_g = mg.moga_varlen_attn_bwd(d, *t, o, lse, cq, ck, scale)
         for x, y in zip(mg.moga_varlen_attn_bwd_rows(d, *t, o, lse, cq, ck, scale, ws), want_g):
             assert torch.equal(x, y)
+        assert int(mg.attn_bwd_status(ws, N, H)) == 0   # cleared by the merge
