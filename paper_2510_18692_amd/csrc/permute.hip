@@ -306,14 +306,27 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t
 // thread, 8-bit counters packed four to a word, summed over the waves) while its first rows are on the way.  The sort as a launch
 // of its own is one block that the chip waits for.  Two launches against this one, in us: 4,096 x 12 heads x 128 bf16, 8 groups
 // 18.3 and 13.7 (5.5 TB/s); 10,007 x 12, 20 groups 39.3 and 37.8; 16,384 x 12, 8 groups 64 and 54, 32 groups 71 and 59.
-// The count is paid back by a token's rows (bytes of one tensor) where the tokens are many, and it has four times the counters
-// above 8 groups.  Two launches against one: 8 groups, 256-byte rows 7.6 and 6.3 at 4,096 tokens, 10.1 and 22.8 at 16,384; 1 KB rows
-// 16.1 and 12.1 at 8,192, 29.3 and 21.5 at 16,384.  20 groups, 256-byte rows 7.3 and 6.2 at 2,048, 17 % slower at 4,096; 1 KB rows 7 to
-// 30 % slower from 4,097 to 14,000, 2 KB rows 2 % faster on the mean and 8 % slower at 8,193, 3 KB rows 3 % slower at 5,000 and 18 %
-// faster at 16,384.
+// The count is paid back by a token's rows (bytes of one tensor) where the tokens are many, doubles at 8,193 tokens, and has four
+// times the counters above 8 groups.  Two launches against one, up to 8 groups: 256-byte rows 7.6 and 6.3 at 4,096 tokens, 10.1 and
+// 22.8 at 16,384; 1 KB rows 16.1 and 12.1 at 8,192, 29.3 and 21.5 at 16,384.  20 groups: 256-byte rows 6.8 and 5.7 at 2,048, 7.3 and
+// 8.8 at 3,000 (in a graph; call by call, where the host's time counts, 12.4 and 9.9); 1.5 KB 10.7 and 11.0 at 3,500, 14.8 and 15.4 at
+// 5,000, 16.9 and 16.2 at 6,000; 1 KB 16.5 and 14.7 at 8,192, 17.3 and 22.2 at 8,193; 2 KB 27.8 and 27.2 at 9,000, 30.2 and 27.7 at
+// 10,007; 4 KB, 9 groups 44.0 and 46.9 at 9,300, 65.4 and 62.3 at 12,288.
 inline bool use_permute_gather(int64_t N, int M, int64_t row_bytes) {
   if (M <= 8) return N <= 4096 || (N <= 16384 && row_bytes >= 1024);
-  return M <= 32 && (N <= 2048 || (N <= 16384 && row_bytes >= 3072));
+  if (M > 32 || N > 16384) return false;
+  if (N <= 2048) return true;
+  if (N <= 4096) return row_bytes >= 1536;
+  if (N <= 5600) return row_bytes >= 6144 && N > 4608;
+  if (N <= 8192) return row_bytes >= 1024;
+  return row_bytes >= 6144 || N > (row_bytes >= 4096 ? 10240 : row_bytes >= 2048 ? 9216 : 16384);
+}
+// A block per 16 tokens and tensor instead of one for all three: three times the counts, but no second or third round of blocks that
+// holds a few long ones.  Two launches, one block for all, one per tensor, 40 heads: 5,000 tokens, 8 groups 59.7, 68.4 and 54.8, 9
+// groups 59.6, 71.6 and 56.5; 9,000, 8 groups 121, 123 and 114; 8,192 (two full rounds) 107, 97 and 103.  16 heads, 10,007, 8 groups
+// 53.7, 52.3 and 48.0, 9 groups 54.7, 56.1 and 57.5.
+inline bool permute_gather_per_tensor(int64_t N, int M, int64_t row_bytes) {
+  return N <= 4096 || (row_bytes >= (M <= 8 ? 4096 : 6144) && (N - 1) / kSlotsPerBlock % 256 < 224);
 }
 
 template <int LPR, int WORDS, int PER>   // WORDS * 4 >= groups, PER * 256 >= tokens
@@ -901,7 +914,7 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int64_t row_bytes = (int64_t)H * lanes_per_row(dtype, D) * 16;
   if (with_data && N > 0 && use_permute_gather(N, M, row_bytes)) {
     const Rows3 p = {{q, k, v}, {qh, kh, vh}};
-    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), N > 4096 ? 1 : 3);   // few rows: a block per tensor
+    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), permute_gather_per_tensor(N, M, row_bytes) ? 3 : 1);
 #define MOGA_PERMUTE_GATHER(LPR, WORDS, PER)                                                                                  \
   permute_gather_kernel<LPR, WORDS, PER><<<grid, 256, 0, st>>>(p, group, (int)N, H, M, nbits, counts, cu_seqlens, max_seqlen, \
                                                                perm, inv_perm)

@@ -1,5 +1,5 @@
-"""Sort and gather in one launch (up to 16,384 tokens and 32 groups; above 8 groups and 2,048 tokens with rows of 3 KB): every
-integer and every row against a stable sort."""
+"""Sort and gather in one launch (up to 16,384 tokens and 32 groups, by the bytes of a token's rows) or two: every integer and
+every row against a stable sort."""
 import pytest
 import torch
 
@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N", [1, 15, 16, 17, 255, 257, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 8192, 8193, 16383, 16384, 16385])
 @pytest.mark.parametrize("M,H,D,dtype", [(1, 1, 64, torch.float32), (8, 5, 128, torch.bfloat16), (9, 2, 128, torch.float32), (32, 3, 128, torch.bfloat16), (20, 9, 128, torch.bfloat16),
-                                         (32, 12, 128, torch.bfloat16), (9, 6, 128, torch.float32)])
+                                         (32, 12, 128, torch.bfloat16), (9, 6, 128, torch.float32),
+                                         (8, 16, 128, torch.bfloat16), (20, 12, 128, torch.float32)])   # a block per tensor
 def test_sort_and_gather(N, M, H, D, dtype):
     g = torch.Generator(device="cuda").manual_seed(N + M)
     group = torch.randint(-1, M + 1, (N,), generator=g, device="cuda", dtype=torch.int32)   # ids outside are clamped
