@@ -169,7 +169,7 @@ extern "C" double moga_bench_mix_loop(int lds_reads, int fmas, int exps, int blo
     MOGA_MIX(0, 0, 0) MOGA_MIX(1, 0, 0) MOGA_MIX(2, 0, 0)
     MOGA_MIX(0, 2, 0) MOGA_MIX(0, 4, 0) MOGA_MIX(0, 6, 0)
     MOGA_MIX(0, 0, 1) MOGA_MIX(0, 0, 2)
-    MOGA_MIX(1, 4, 1)
+    MOGA_MIX(1, 2, 0) MOGA_MIX(1, 2, 1) MOGA_MIX(1, 4, 1)
     default: return -1.0;
   }
 #undef MOGA_MIX

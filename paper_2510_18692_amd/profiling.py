@@ -378,7 +378,8 @@ at the rate reported above: that rate, not 2.5 PFLOP/s, is what bf16 matrix work
 
 
 # (LDS fragment reads, fmas, exp2s) per pair of MFMAs: the combinations libmoga_bench.so builds
-_ENERGY_VARIANTS = [(0, 0, 0), (1, 0, 0), (2, 0, 0), (0, 2, 0), (0, 4, 0), (0, 6, 0), (0, 0, 1), (0, 0, 2), (1, 4, 1)]
+_ENERGY_VARIANTS = [(0, 0, 0), (1, 0, 0), (2, 0, 0), (0, 2, 0), (0, 4, 0), (0, 6, 0), (0, 0, 1), (0, 0, 2), (1, 2, 0), (1, 2, 1),
+                    (1, 4, 1)]
 
 
 def write_energy(args):
