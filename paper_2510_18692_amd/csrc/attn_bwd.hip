@@ -227,7 +227,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
             g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
-        split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 2, 1.f, softmax_scale,
+        split_sum_kernel<<<dim3(kCus / 2, 32), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 128, 1.f, softmax_scale,
                                                             (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
       } else
         attn_bwd_dkdv_ab_kernel<<<(unsigned)k_blocks, 512, 0, st>>>(
@@ -239,7 +239,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
       attn_bwd_dq_pipe_kernel<false, true><<<(unsigned)(q_blocks + kCus), 512, 0, st>>>(
           (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
           delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
-      split_sum_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 1, softmax_scale, 0.f,
+      split_sum_kernel<<<dim3(kCus / 2, 32), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 256, softmax_scale, 0.f,
                                                           (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
     } else
       attn_bwd_dq_pipe_kernel<<<(unsigned)q_blocks, 512, 0, st>>>(

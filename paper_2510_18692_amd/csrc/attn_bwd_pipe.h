@@ -20,14 +20,6 @@
 
 namespace moga {
 
-__device__ __forceinline__ void lds_dma4_soff(const void* base, unsigned byte_off, unsigned lds_wave_base) {
-  lds_wave_base = __builtin_amdgcn_readfirstlane(lds_wave_base);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-               :
-               : "s"(lds_wave_base), "v"(byte_off), "s"(base)
-               : "memory");
-}
-
 __device__ __forceinline__ floatx4_t lds_read_f32x4(unsigned addr) {
   return *(const floatx4_t __attribute__((address_space(3)))*)(uintptr_t)addr;
 }
@@ -62,9 +54,9 @@ __device__ __forceinline__ void softmax_bwd_cols(const StepScores& s, const Step
 // dQ: query-stationary
 // ---------------------------------------------------------------------------------------
 struct DqLane {
-  unsigned k_nat[4];   // K rows, slot 0, half 0
-  unsigned v_nat[4];   // V rows
-  unsigned k_tr[8];    // K transposed
+  unsigned k_nat;     // K rows, slot 0, half 0
+  unsigned v_nat;     // V rows
+  unsigned k_tr[2];   // K transposed
 };
 
 // S^T = K Q^T and dP'^T = V dO^T - delta for one 32-key half of a tile
@@ -83,8 +75,8 @@ __device__ __forceinline__ void dq_scores(const DqLane& ln, unsigned off, const 
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const bf16x8_t kf = lds_read_b128(ln.k_nat[ks] + off + SOFF + t * kRow4Bytes);
-      const bf16x8_t vf = lds_read_b128(ln.v_nat[ks] + off + SOFF + t * kRow4Bytes);
+      const bf16x8_t kf = read_nat<64>(ln.k_nat + off + SOFF, t, ks);
+      const bf16x8_t vf = read_nat<64>(ln.v_nat + off + SOFF, t, ks);
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         s[t][q] = mfma16(kf, qf[q][ks], s[t][q]);
@@ -98,7 +90,7 @@ template <int SOFF>
 __device__ __forceinline__ void dq_accumulate(const DqLane& ln, unsigned off, const bf16x8_t (&dsf)[2], floatx4_t (&dq)[8][2]) {
 #pragma unroll
   for (int dt = 0; dt < 8; ++dt) {
-    const bf16x8_t a = lds_read_tr_frag(ln.k_tr[dt] + off + SOFF);
+    const bf16x8_t a = read_tr<64>(ln.k_tr, off + SOFF, dt);
 #pragma unroll
     for (int q = 0; q < 2; ++q) dq[dt][q] = mfma16(a, dsf[q], dq[dt][q]);
   }
@@ -115,14 +107,14 @@ __device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf
   wave_priority<PRIO, 1>();   // scores and softmax before the other wave's dQ products (the other way round: no gain)
   dq_scores<SOFF>(ln, off, qf, dof, neg_dlt, s_a, dp_a);
   __builtin_amdgcn_sched_barrier(0);
-  dq_scores<SOFF + 8192>(ln, off, qf, dof, neg_dlt, s_b, dp_b);
+  dq_scores<SOFF + kRow32Bytes>(ln, off, qf, dof, neg_dlt, s_b, dp_b);
   softmax_bwd_cols<MASK>(s_a, dp_a, lse2, c, g, left, dsf_a);
   __builtin_amdgcn_sched_barrier(0);
   wave_priority<PRIO, 0>();
   dq_accumulate<SOFF>(ln, off, dsf_a, dq);
   softmax_bwd_cols<MASK>(s_b, dp_b, lse2, c, g, left - 32, dsf_b);
   __builtin_amdgcn_sched_barrier(0);
-  dq_accumulate<SOFF + 8192>(ln, off, dsf_b, dq);
+  dq_accumulate<SOFF + kRow32Bytes>(ln, off, dsf_b, dq);
 }
 
 // Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f: to `out` (sorted order, or token order in
@@ -169,14 +161,15 @@ __device__ __forceinline__ void store_zero_piece(float* rows) {
 // raw upstream gradient of the gated output.
 // NB: ring slots of 64 keys (4: two tiles ahead, one block per CU; 2: one tile ahead, 64 KB of LDS, so
 // that two 4-wave blocks share a CU -- the variant for small groups).
-template <int NB>
+template <int NB, bool GATHER>
 struct DqLds {
   __attribute__((aligned(1024))) unsigned short k[NB][64 * kHeadDim], v[NB][64 * kHeadDim];
+  __attribute__((aligned(256))) int tok[GATHER ? 512 : 1];   // gather mode: tokens of eight tiles
 };
 
 template <int NW, bool GATHER, int NB, bool SPLIT>
 __device__ __forceinline__ void attn_bwd_dq_block(
-    DqLds<NB>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    DqLds<NB, GATHER>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
@@ -184,7 +177,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm, float* __restrict__ part,
     unsigned short* __restrict__ d_q_tok) {
   constexpr int BM = NW * 32;
-  constexpr int kDmaPerTile = 2 * (16 / NW);
+  constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64>;
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
 
   WorkTile sp;
@@ -206,7 +199,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 32 * wave) * kHeadDim : nullptr;
   if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
     if (piece) store_zero_piece(piece_rows);
-    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
+    else store_zero_rows<GATHER, 2>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
     return;
   }
 
@@ -226,24 +219,25 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   PipeDma dma;
   dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
   dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&lds.k[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&lds.v[0][0]) + wave * 1024;
-  dma.row0 = 4 * wave + (lane >> 4);
-  dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
+  dma_lanes<NW, 64>(dma, &lds.k[0][0], &lds.v[0][0], wave, lane);
   dma.last_row = n - 1;
-  if (GATHER) {
-    dma.rows = (const int32_t*)uniform_ptr(perm + gs);
+  if constexpr (GATHER) {
+    dma.rows = uniform_ptr(perm + gs);
     dma.tok_stride = (int64_t)H * kHeadDim * 2;
-    dma.wave_row = 4 * wave;
-    dma.last_index = (int)(Nk - 1) - gs;
-    pipe_load_tokens<NW>(dma, 0);
+    dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
+    pipe_issue_tokens(dma, 0);
+    pipe_issue_tokens(dma, 64);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   }
 #pragma unroll
-  for (int t = 0; t <= kAhead; ++t) pipe_issue<NW, GATHER>(dma, 64 * t, t);
+  for (int t = 0; t <= kAhead; ++t) {
+    if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
+    pipe_issue<NW, 64, GATHER>(dma, 64 * t, t * kPipeTileBytes);
+  }
 
   DqLane ln;
-  nat_addresses(ln.k_nat, &lds.k[0][0], lane);
-  nat_addresses(ln.v_nat, &lds.v[0][0], lane);
+  ln.k_nat = nat_address(&lds.k[0][0], lane);
+  ln.v_nat = nat_address(&lds.v[0][0], lane);
   tr_addresses(ln.k_tr, &lds.k[0][0], lane);
   // All of the wave's own operands are here before the loop.  Otherwise the compiler, which sees the loads above and not the
   // direct-to-LDS loads, waits for them at their first use, inside the loop: vmcnt(4) .. vmcnt(0) in every tile, that is for
@@ -267,7 +261,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
 #define MOGA_DQ_TILE(B)                                                                  \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                      \
   __syncthreads();                                                                       \
-  pipe_issue<NW, GATHER>(dma, 64 * (T + (B) + 1 + kAhead), ((B) + 1 + kAhead) & (NB - 1)); \
+  pipe_issue<NW, 64, GATHER>(dma, 64 * (T + (B) + 1 + kAhead), (((B) + 1 + kAhead) & (NB - 1)) * kPipeTileBytes); \
   if (active) dq_tile<NB == 4, false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
     MOGA_DQ_TILE(0)
@@ -279,7 +273,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   for (; T < nfull; ++T) {
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
     __syncthreads();
-    pipe_issue<NW, GATHER>(dma, 64 * (T + 1 + kAhead), (T + 1 + kAhead) & (NB - 1));
+    pipe_issue<NW, 64, GATHER>(dma, 64 * (T + 1 + kAhead), ((T + 1 + kAhead) & (NB - 1)) * kPipeTileBytes);
     if (active) dq_tile<NB == 4, false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, 64);
   }
   if (n & 63) {   // last, partial tile: masked keys contribute zero
@@ -302,7 +296,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_pipe_kernel(
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
-  __shared__ DqLds<4> lds;
+  __shared__ DqLds<4, GATHER> lds;
   attn_bwd_dq_block<8, GATHER, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
                                          M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
 }
@@ -330,8 +324,8 @@ __device__ __forceinline__ void lds_write_b128(unsigned addr, bf16x8_t v) {
 }
 
 struct AbLane {
-  unsigned nat[4];      // rows of Q (A) or dO (B): A operand of the score product, slot 0, half 0
-  unsigned tr[8];       // dO (A) or Q (B) transposed
+  unsigned nat;         // rows of Q (A) or dO (B): A operand of the score product, slot 0, half 0
+  unsigned tr[2];       // dO (A) or Q (B) transposed
   unsigned init_addr;   // -lse/scale (A) or -delta (B) of the lane's first row
   unsigned p_addr;      // this lane's 16 bytes in the pair's P buffer (unit 0, key half 0)
 };
@@ -344,7 +338,7 @@ __device__ __forceinline__ void ab_load_nat(const AbLane& ln, unsigned off, unsi
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) nat[t][ks] = lds_read_b128(ln.nat[ks] + off + SOFF + t * kRow4Bytes);
+    for (int t = 0; t < 2; ++t) nat[t][ks] = read_nat<64>(ln.nat + off + SOFF, t, ks);
 }
 // Its scores ([query operand t][key half]), started from the constants.
 __device__ __forceinline__ void ab_scores(const bf16x8_t (&nat)[2][4], const floatx4_t (&ini)[2],
@@ -362,7 +356,7 @@ __device__ __forceinline__ void ab_scores(const bf16x8_t (&nat)[2][4], const flo
 template <int SOFF>
 __device__ __forceinline__ void ab_load_tr(const AbLane& ln, unsigned off, bf16x8_t (&tr)[8]) {
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) tr[dt] = lds_read_tr_frag(ln.tr[dt] + off + SOFF);
+  for (int dt = 0; dt < 8; ++dt) tr[dt] = read_tr<64>(ln.tr, off + SOFF, dt);
 }
 
 __device__ __forceinline__ void ab_accumulate(const bf16x8_t (&tr)[8], const bf16x8_t (&bop)[2], floatx4_t (&acc)[8][2]) {
@@ -445,7 +439,7 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
   bf16x8_t nat0[2][4], nat1[2][4];
   floatx4_t ini0[2], ini1[2];
   ab_load_nat<SOFF, SROW>(ln, off, off_row, nat0, ini0);   // all fragments on their way before the first product
-  ab_load_nat<SOFF + 8192, SROW + 128>(ln, off, off_row, nat1, ini1);
+  ab_load_nat<SOFF + kRow32Bytes, SROW + 128>(ln, off, off_row, nat1, ini1);
   __builtin_amdgcn_sched_barrier(0);
   ab_scores(nat0, ini0, kvf, sc[0]);
   __builtin_amdgcn_sched_barrier(0);
@@ -461,7 +455,7 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
     ab_take_p(ln, sc[0], 0, bop[0]);
     ab_take_p(ln, sc[1], 1, bop[1]);
   }
-  ab_load_tr<SOFF + 8192>(ln, off, tr1);   // in flight while the first unit is accumulated
+  ab_load_tr<SOFF + kRow32Bytes>(ln, off, tr1);   // in flight while the first unit is accumulated
   ab_accumulate(tr0, bop[0], acc);
   ab_accumulate(tr1, bop[1], acc);
 }
@@ -485,7 +479,7 @@ __device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigne
   bf16x8_t bop[2][2];    // B operand of the second product: P (A) or dS (B), per unit and key half
   bf16x8_t nat1[2][4], tr0[8], tr1[8];
   floatx4_t ini1[2];
-  ab_load_nat<SOFF + 8192, SROW + 128>(ln, off, off_row, nat1, ini1);
+  ab_load_nat<SOFF + kRow32Bytes, SROW + 128>(ln, off, off_row, nat1, ini1);
   __builtin_amdgcn_sched_barrier(0);
   ab_scores(nat0, ini0, kvf, sc[0]);
   __builtin_amdgcn_sched_barrier(0);
@@ -508,7 +502,7 @@ __device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigne
     ab_make_p<false>(ln, sc[0], c, g, 64, 0, bop[0]);
     ab_make_p<false>(ln, sc[1], c, g, 64, 1, bop[1]);
   }
-  ab_load_tr<SOFF + 8192>(ln, off, tr1);
+  ab_load_tr<SOFF + kRow32Bytes>(ln, off, tr1);
   barrier();
   if (role == 1) {
     ab_take_p(ln, sc[0], 0, bop[0]);
@@ -526,17 +520,18 @@ __device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigne
 
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
 // NB: ring slots of 64 queries (4 or 2, as in the dQ kernel).
-template <int NPAIR, int NB>
+template <int NPAIR, int NB, bool GATHER>
 struct DkdvLds {
   __attribute__((aligned(1024))) unsigned short q[NB][64 * kHeadDim], d_o[NB][64 * kHeadDim];
   __attribute__((aligned(1024))) unsigned char p[NPAIR][4096];   // P of one tile, per pair
   __attribute__((aligned(256))) float l[NB][64], d[NB][64];      // -lse / scale, -delta
+  __attribute__((aligned(256))) int tok[GATHER ? 512 : 1];       // gather mode: tokens of eight tiles
   int flag[NPAIR];   // per pair: number of tiles whose P has been written (NB == 2) or taken (NB == 4)
 };
 
 template <bool GATHER, int NPAIR, int NB, bool SPLIT>
 __device__ __forceinline__ void attn_bwd_dkdv_block(
-    DkdvLds<NPAIR, NB>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    DkdvLds<NPAIR, NB, GATHER>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
@@ -547,7 +542,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   constexpr int NW = 2 * NPAIR;
   constexpr int BK = 32 * NPAIR;                   // pairs of waves x 32 keys
   constexpr int kAhead = NB - 2;
-  constexpr int kDmaPerTile = 2 * (16 / NW) + 2;
+  constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64> + 2;
 
   // Ordered before its first use by the barriers below.  With NB == 4 and no polls the first wait (of P nobody needs yet) finds its
   // word not there, so that a test reaches the give-up for certain.
@@ -575,7 +570,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 32 * pair) * kHeadDim : nullptr;   // dV, then dK
   if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
     if (piece) store_zero_piece(piece_rows);
-    else store_zero_rows<GATHER>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);
+    else store_zero_rows<GATHER, 2>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);
     return;
   }
 
@@ -585,33 +580,34 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   PipeDma dma;   // "k" = Q rows, "v" = dO rows of this head's group
   dma.kbase = uniform_ptr(GATHER ? qh + (int64_t)head * kHeadDim : qh + (head_off_q + gs) * kHeadDim);
   dma.vbase = uniform_ptr(GATHER ? d_oh + (int64_t)head * kHeadDim : d_oh + (head_off_q + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&lds.q[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&lds.d_o[0][0]) + wave * 1024;
-  dma.row0 = 4 * wave + (lane >> 4);
-  dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
+  dma_lanes<NW, 64>(dma, &lds.q[0][0], &lds.d_o[0][0], wave, lane);
   dma.last_row = n - 1;
-  if (GATHER) {
-    dma.rows = (const int32_t*)uniform_ptr(perm + gs);
+  if constexpr (GATHER) {
+    dma.rows = uniform_ptr(perm + gs);
     dma.tok_stride = (int64_t)H * kHeadDim * 2;
-    dma.wave_row = 4 * wave;
-    dma.last_index = (int)(Nq - 1) - gs;
-    pipe_load_tokens<NW>(dma, 0);
+    dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
+    pipe_issue_tokens(dma, 0);
+    pipe_issue_tokens(dma, 64);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   }
   const void* lbase = uniform_ptr(neg_lse_over_scale + head_off_q + gs);
   const void* dbase = uniform_ptr(neg_delta + head_off_q + gs);
   const unsigned lds_l = lds_addr_uniform(&lds.l[0][0]), lds_d = lds_addr_uniform(&lds.d[0][0]);
   auto issue_tile = [&](int T) {   // every wave issues the (identical) row-constant loads so that all count alike
     const int slot = T & (NB - 1);
-    pipe_issue<NW, GATHER>(dma, 64 * T, slot);
+    pipe_issue<NW, 64, GATHER>(dma, 64 * T, slot * kPipeTileBytes);
     const unsigned roff = (unsigned)min(64 * T + lane, n - 1) * 4u;
     lds_dma4_soff(lbase, roff, lds_l + slot * 256);
     lds_dma4_soff(dbase, roff, lds_d + slot * 256);
   };
 #pragma unroll
-  for (int t = 0; t <= kAhead; ++t) issue_tile(t);
+  for (int t = 0; t <= kAhead; ++t) {
+    if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
+    issue_tile(t);
+  }
 
   AbLane ln;
-  nat_addresses(ln.nat, role == 0 ? &lds.q[0][0] : &lds.d_o[0][0], lane);
+  ln.nat = nat_address(role == 0 ? &lds.q[0][0] : &lds.d_o[0][0], lane);
   tr_addresses(ln.tr, role == 0 ? &lds.d_o[0][0] : &lds.q[0][0], lane);
   ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&lds.l[0][0] : (unsigned)(uintptr_t)&lds.d[0][0]) + 8 * (lane >> 4) * 4;
   ln.p_addr = (unsigned)(uintptr_t)&lds.p[0][0] + pair * 4096 + lane * 16;
@@ -708,7 +704,7 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_ab_kernel(
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
     unsigned short* __restrict__ d_v_tok = nullptr) {
-  __shared__ DkdvLds<4, 4> lds;
+  __shared__ DkdvLds<4, 4, GATHER> lds;
   attn_bwd_dkdv_block<GATHER, 4, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
                                            M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok, d_v_tok);
 }
@@ -725,8 +721,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_kernel(
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm, unsigned short* __restrict__ d_q_tok,
     unsigned short* __restrict__ d_k_tok, unsigned short* __restrict__ d_v_tok, int dq_blocks) {
   __shared__ union {
-    DqLds<2> dq;
-    DkdvLds<2, 2> dkdv;
+    DqLds<2, false> dq;
+    DkdvLds<2, 2, false> dkdv;
   } lds;
   if ((int)blockIdx.x < dq_blocks)
     attn_bwd_dq_block<4, false, 2, false>(lds.dq, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, ts_q, M, Nq,

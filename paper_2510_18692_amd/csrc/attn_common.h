@@ -171,7 +171,7 @@ __device__ __forceinline__ void store_partial(float* base, int dt, int col_half,
   *(floatx4_t*)(base + (16 * col_half + (lane & 15)) * kHeadDim + 16 * dt + 4 * (lane >> 4)) = v;
 }
 
-constexpr size_t kSplitRows = 256;   // result rows of a piece, in every kernel
+constexpr size_t kSplitRows = 384;   // room for the result rows of a piece
 constexpr size_t kSplitBytes = kCus * kSplitRows * (kHeadDim + 2) * sizeof(float);   // results, then (max, sum) of the forward
 struct SplitWs {
   float *part, *stat;
@@ -190,19 +190,17 @@ inline SplitWs split_ws(void* ws) {
 // Worth it for a few rounds of the kernels with long blocks; beyond 32 rounds the last one is under 3 %.
 inline bool split_pays(int64_t tiles) { return tiles <= 32 * kCus; }
 
-constexpr int kSplitGridY = kSplitRows / 8;
 // Sum of the pieces of every tile of the last round, times f, as bf16 rows of `out` (sorted order) and `tok` (token order),
 // each of which may be NULL.  A tile has `arrays` results of
-// kSplitRows / arrays rows each (dV and dK: two, 128 rows).  Grid (kCus / 2, kSplitGridY): eight rows per block, one trip
+// `rows` rows each.  Grid (kCus / 2, arrays * rows / 8): eight rows per block, one trip
 // to memory (with 64 rows per block, one after the other, 45 us instead of 9).
 static __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ part, const int32_t* __restrict__ cu, int M,
-                                                               int H, int64_t N, int arrays, float f0, float f1,
+                                                               int H, int64_t N, int rows, float f0, float f1,
                                                                unsigned short* __restrict__ out0,
                                                                unsigned short* __restrict__ out1,
                                                                unsigned short* __restrict__ tok0,
                                                                unsigned short* __restrict__ tok1,
                                                                const int32_t* __restrict__ perm) {
-  const int rows = kSplitRows / arrays;
   const int per_head = count_tiles(cu, M, rows);
   const SplitShape s = split_shape(per_head * H);
   if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
@@ -273,34 +271,40 @@ __device__ __forceinline__ floatx4_t mfma16(bf16x8_t a, bf16x8_t b, floatx4_t c)
 // A step takes 32 rows of an LDS tile as two 16-row A operands t = 0, 1; operand row 4 a + b is tile row
 // 8 a + 4 t + b.  A lane's eight results are then eight consecutive rows: the B operand of the second product.
 __device__ __forceinline__ int step_row(int r) { return 8 * (r >> 2) + (r & 3); }   // t = 0; t = 1 is 4 rows further
-constexpr int kRow4Bytes = 4 * kHeadDim * 2;
 
-// XOR swizzle of the 16-byte chunk index inside an unpadded 256-byte LDS row (128 bf16): chunk' = chunk ^
-// lds_swizzle(row).  Row bits 1:0 land in chunk bits 3:2, row bits 4:3 (a) in chunk bits 1:0 as 0, 2, 3, 1: a 16-byte
+// LDS layout of a tile of ROWS rows of 128 bf16: four quarters (channels 32 ks .. 32 ks + 31), each [ROWS][64 bytes], so that the
+// quarter is an immediate offset of a read and a lane needs one address register for row fragments and two for transposed ones
+// (as [ROWS][256 bytes], with the 16-byte chunk index XOR-swizzled by the row, it needs 4 and 8).  Inside a row the four
+// 16-byte chunks are XOR-swizzled by row bits 4:3 (a) as 0, 2, 3, 1: a 16-byte
 // read is served in groups of lanes {0-3, 12-15, 20-27} and {4-11, 16-19, 28-31} (and the same plus 32), which then
-// hit all banks once (with 0, 2, 1, 3 every such read took four cycles more), and so do both halves of a transposed read
-// (rows 8 g .. 8 g + 3).  Bit 2 does not count: the second operand and the upper rows of a transposed fragment are
-// constant offsets.
-__device__ __forceinline__ int lds_swizzle(int row) {
-  return ((row & 3) << 2) | (((row >> 2) ^ (row >> 3)) & 2) | ((row >> 4) & 1);
-}
+// hit all banks once, and so do both halves of a transposed read (rows 8 g .. 8 g + 3).  Row bit 2 does not count: the second
+// operand and the upper rows of a transposed fragment are constant offsets, and so are the upper 32 rows.
+constexpr int kRow4Bytes = 4 * 64, kRow32Bytes = 32 * 64;
+template <int ROWS>
+constexpr int kQuarterBytes = ROWS * 64;
+__device__ __forceinline__ int lds_swizzle(int row) { return (((row >> 2) ^ (row >> 3)) & 2) | ((row >> 4) & 1); }
 
 // Per-lane LDS byte addresses (slot 0, first step) of the A operands of a tile at `base`.
-// nat: rows as they are, d = 32 ks + 8 g ..; operand t adds t * kRow4Bytes.  tr: transposed, d = 16 dt + r, 32 tile rows.
-__device__ __forceinline__ void nat_addresses(unsigned (&nat)[4], const void* base, int lane) {
+// nat: rows as they are, d = 8 g .. of a quarter; operand t adds t * kRow4Bytes.
+// tr: transposed, d = 16 p + r of a quarter for p = 0, 1, 32 tile rows.
+__device__ __forceinline__ unsigned nat_address(const void* base, int lane) {
   const int g = lane >> 4, row = step_row(lane & 15);
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
-    nat[ks] = (unsigned)(uintptr_t)base + row * 256 + (((4 * ks + g) ^ lds_swizzle(row)) << 4);
+  return (unsigned)(uintptr_t)base + row * 64 + ((g ^ lds_swizzle(row)) << 4);
 }
-__device__ __forceinline__ void tr_addresses(unsigned (&tr)[8], const void* base, int lane) {
+__device__ __forceinline__ void tr_addresses(unsigned (&tr)[2], const void* base, int lane) {
   const int row = 8 * (lane >> 4) + ((lane & 15) >> 2), c = (lane & 3) >> 1;
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt)
-    tr[dt] = (unsigned)(uintptr_t)base + row * 256 + (((2 * dt + c) ^ lds_swizzle(row)) << 4) + (lane & 1) * 8;
+  for (int p = 0; p < 2; ++p) tr[p] = (unsigned)(uintptr_t)base + row * 64 + (((2 * p + c) ^ lds_swizzle(row)) << 4) + (lane & 1) * 8;
 }
-__device__ __forceinline__ bf16x8_t lds_read_tr_frag(unsigned addr) {
-  return concat_tr(lds_read_tr16_addr(addr), lds_read_tr16_addr(addr + kRow4Bytes));
+// The fragments: rows of operand t at k block ks; transposed d tile dt.
+template <int ROWS>
+__device__ __forceinline__ bf16x8_t read_nat(unsigned nat, int t, int ks) {
+  return lds_read_b128(nat + ks * kQuarterBytes<ROWS> + t * kRow4Bytes);
+}
+template <int ROWS>
+__device__ __forceinline__ bf16x8_t read_tr(const unsigned (&tr)[2], unsigned off, int dt) {
+  const unsigned a = tr[dt & 1] + off + (dt >> 1) * kQuarterBytes<ROWS>;
+  return concat_tr(lds_read_tr16_addr(a), lds_read_tr16_addr(a + kRow4Bytes));
 }
 
 // Priority of this wave among the waves of its SIMD, in the kernels with one block per CU.  Where two blocks share a

@@ -10,6 +10,8 @@
 //   * V^T is read from the row-major V tile in LDS with the transposing LDS read;
 //   * the kernel itself (software pipeline, LDS ring, direct-to-LDS loads) is in attn_pipe.h.
 // fp32 kernel (fp32 matrix instruction, full precision throughout): attn_f32.h.
+#include <algorithm>
+
 #include "attn_common.h"
 #include "attn_f32.h"
 #include "attn_pipe.h"
@@ -26,6 +28,19 @@ namespace moga {
 static int64_t small_group_rows(int64_t Nq, int H) {
   const int64_t quarters = 4 * Nq * H / (256 * kCus);
   return quarters >= 64 ? 1152 : quarters >= 4 ? 2560 : quarters >= 2 ? 6144 : 5632;
+}
+
+// Query rows of a block of the large kernel.  384 take 3 to 6 % less time per row (a fragment read from LDS feeds three products instead
+// of two), but where there are hardly more blocks than CUs, 256 may fill their last round so much better that the call is
+// faster: 16,384 rows x 4 heads, 2 groups 0.247 ms with 384 (176 blocks), 0.219 with 256 (256 blocks); 12,000 x 12, 3 groups 0.265 and
+// 0.260 (396 and 576 blocks; a split of the last round counted: 2 and 2.25 rounds); 20,000 x 12, 4 groups 0.511 and 0.517 (672 and 960: 3
+// and 4 rounds).  The host knows the mean group only, and takes it for all.
+static int fwd_rows(int64_t Nq, int H, int M) {
+  auto eighths = [&](int64_t rows) {   // of a round, the last one split if half of it is free
+    const int64_t tiles = (((Nq + M - 1) / M + rows - 1) / rows) * M * H, left = tiles % kCus;
+    return rows * (8 * (tiles / kCus) + (left ? 8 / std::min<int64_t>(kMaxSplits, kCus / left) : 0));
+  };
+  return 5 * eighths(256) < 4 * eighths(384) ? 256 : 384;
 }
 
 }  // namespace moga
@@ -49,7 +64,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
   const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
-  const int bm = dtype == MOGA_BF16 ? (small ? 128 : 256) : kF32Rows;
+  const int rows = fwd_rows(Nq, H, M), bm = dtype == MOGA_BF16 ? (small ? 128 : rows) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
   if (!grid_fits(blocks, dtype == MOGA_BF16 && !small ? 512 : 256)) return MOGA_ERR_UNSUPPORTED;
@@ -66,17 +81,25 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, (unsigned short*)tok.o);
-  } else if (dtype == MOGA_BF16 && split && split_pays(tiles * H)) {
+  } else if (split && split_pays(tiles * H)) {
     const SplitWs sw = split_ws(split);
-    attn_fwd_bf16_pipe_kernel<8, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(
-        (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,
-        softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, sw, (unsigned short*)tok.o);
-    split_fwd_kernel<<<dim3(kCus / 2, kSplitGridY), 256, 0, st>>>(sw, cu_q, cu_k, M, H, Nq, softmax_scale, (unsigned short*)oh,
-                                                                  lse, tok.perm, tok.gate, (unsigned short*)tok.o);
+#define MOGA_FWD_SPLIT(RR)                                                                                                     \
+  attn_fwd_bf16_pipe_kernel<RR, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(                                       \
+      (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,      \
+      softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, sw, (unsigned short*)tok.o)
+    if (rows == 384) MOGA_FWD_SPLIT(384);
+    else MOGA_FWD_SPLIT(256);
+#undef MOGA_FWD_SPLIT
+    split_fwd_kernel<<<dim3(kCus / 2, rows / 8), 256, 0, st>>>(sw, rows, cu_q, cu_k, M, H, Nq, (unsigned short*)oh, lse, tok.perm,
+                                                               tok.gate, (unsigned short*)tok.o);
   } else {
-    attn_fwd_bf16_pipe_kernel<8><<<(unsigned)blocks, 512, 0, st>>>(
-        (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
-        tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, SplitWs{}, (unsigned short*)tok.o);
+#define MOGA_FWD(RR)                                                                                                           \
+  attn_fwd_bf16_pipe_kernel<RR><<<(unsigned)blocks, 512, 0, st>>>(                                                             \
+      (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H,   \
+      softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, SplitWs{}, (unsigned short*)tok.o)
+    if (rows == 384) MOGA_FWD(384);
+    else MOGA_FWD(256);
+#undef MOGA_FWD
   }
   return launch_status();
 }
@@ -142,18 +165,22 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (N == 0) return MOGA_OK;
   if (!q || !k || !v || !perm || !gate || !cu_seqlens || !o || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(q) && aligned16(k) && aligned16(v) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
-  const int64_t tiles = max_tiles(N, M, 256);
-  const int64_t blocks = (tiles * H + 7) / 8 * 8;
+  const int rows = fwd_rows(N, H, M);
+  const int64_t blocks = (max_tiles(N, M, rows) * H + 7) / 8 * 8;
   if (!grid_fits(blocks, 512)) return MOGA_ERR_UNSUPPORTED;
-  attn_fwd_bf16_pipe_kernel<8, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(
-      (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, cu_seqlens, cu_seqlens,
-      nullptr, M, N, N, H, softmax_scale, (unsigned short*)o, lse, perm, gate);
+#define MOGA_FWD(RR)                                                                                                             \
+  attn_fwd_bf16_pipe_kernel<RR, true><<<(unsigned)blocks, 512, 0, (hipStream_t)stream>>>(                                        \
+      (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, \
+      softmax_scale, (unsigned short*)o, lse, perm, gate)
+  if (rows == 384) MOGA_FWD(384);
+  else MOGA_FWD(256);
+#undef MOGA_FWD
   return launch_status();
 }
 
 // True where the forward can split its last round.
 bool moga::fwd_splits(int64_t Nq, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, 256) * H);
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, fwd_rows(Nq, H, M)) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }

@@ -1,16 +1,20 @@
 // Software-pipelined bf16 forward kernel of the group attention (head_dim 128).
 //
-// 8 waves per block, 32 query rows per wave (256-row query tiles), two waves per SIMD.
+// 8 waves per block, two per SIMD, 48 query rows per wave (384-row query tiles; 32 and 256 where that suits the call better).
 // Keys are consumed in steps of 32.  While the matrix cores compute the scores of step s+1
-// (S^T = K Q^T), the vector units exponentiate the scores of step s; while the matrix cores
-// accumulate O^T += V^T P^T of step s, the vector units reduce the maximum of step s+1.
+// (S^T = K Q^T), the vector units exponentiate the exponents of step s; while the matrix cores
+// accumulate O^T += V^T P^T of step s, the vector units turn the scores of step s+1 into exponents and take their maximum.
 // K/V tiles of 64 keys (two steps) are streamed global -> LDS with direct-to-LDS loads into
 // a ring of four buffers, two tiles ahead of their use; one block-wide barrier per tile.
 //
-// Bound by the energy of the matrix instructions at the board's power cap and by the issue of a wave's own
-// instruction stream.  Against the same kernel on 32x32x16: 182.1 -> 175.4 ms at 580,320 x 40 heads, 32 groups,
-// 0.817 -> 0.793 ms at 32,760 x 12, 8 groups (clock 1.80 -> 1.94 GHz for 8 % more cycles).
+// Bound by energy at the board's power cap, that of the matrix instructions and of what goes with them: fragment reads, which 48 rows share
+// instead of 32, vector instructions (1.6 per product) and the stream of tiles, which 384 rows share instead of 256.  580,320 x 40 heads, 32
+// groups: 1.90 -> 1.62 vector instructions per product with 0.71 -> 0.47 LDS ones; 145,080 x 40, 8 groups 43.6 -> 41.0 ms (on zeros
+// 33.2 -> 31.2), 99,840 x 40, 16 groups 10.55 -> 10.1, 62,400 x 12, 5 groups 3.74 -> 3.63, 32,760 x 12, 8 groups 0.685 -> 0.670.  64 rows
+// per wave do not fit 256 registers.
 #pragma once
+
+#include <type_traits>
 
 #include "attn_common.h"
 
@@ -20,79 +24,96 @@ constexpr int kPipeNBuf = 4;                      // LDS ring: tiles of 64 keys
 constexpr int kPipeAhead = 2;                     // tiles in flight beyond the one being waited for
 constexpr int kPipeTileBytes = 64 * kHeadDim * 2; // 16 KB per K (or V) tile
 
+__device__ __forceinline__ float uniform_float(float x) {
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x)));
+}
+
+// A value that the compiler takes as it is: what is added to it later is not folded into it.
+__device__ __forceinline__ unsigned in_register(unsigned x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
+// All waves of the block are here.  Unlike __syncthreads it does not wait for the wave's own LDS reads.
+__device__ __forceinline__ void block_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 struct PipeLane {
-  unsigned k[4];   // K rows
-  unsigned v[8];   // V transposed
-  bf16x8_t pairs;  // A operand of the row sums: lane (r, g) has row r's ones if they are among its keys 8 g .. 8 g + 7
+  unsigned k;      // K rows
+  unsigned v[2];   // V transposed
+  bf16x8_t ones;   // A operand of the row sums
 };
 
-__device__ __forceinline__ bf16x8_t pair_ones(int lane) {
-  const int r = lane & 15;
-  uintx4_t v;
+__device__ __forceinline__ bf16x8_t all_ones() {
+  uintx4_t v = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = r == 4 * (lane >> 4) + i ? 0x3f803f80u : 0u;
+  for (int i = 0; i < 4; ++i) asm("" : "+v"(v[i]));   // in registers, not made again in every step
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// The sum of a row's sixteen shares, four in each of its four lanes.
-__device__ __forceinline__ float row_sum(const floatx4_t& l) {
-  float s = (l[0] + l[1]) + (l[2] + l[3]);
-  s += __shfl_xor(s, 16, kWave);
-  return s + __shfl_xor(s, 32, kWave);
-}
-
-// Raw scores of a step: [key operand t][query half]; register i is key 8 g + 4 t + i of query column r
-typedef floatx4_t StepScores[2][2];
+// Scores of a step, or the exponents s*c - m*c of its weights: [key operand t][query column]; register i is key 8 g + 4 t + i of
+// query 16 q + r
+template <int NC>
+using Scores = floatx4_t[2][NC];
+typedef Scores<2> StepScores;
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
-// Maximum of a lane's own eight scores per query (the other keys of the step are in three other lanes)
-__device__ __forceinline__ void step_max(const StepScores& s, float (&mx)[2]) {
+// Maximum of a lane's own eight values of a query (the other keys of the step are in three other lanes)
+template <int NC>
+__device__ __forceinline__ float column_max(const floatx4_t (&s)[2][NC], int q) {
+  float t = max3(s[0][q][0], s[0][q][1], s[0][q][2]);
+  t = max3(t, s[0][q][3], s[1][q][0]);
+  t = max3(t, s[1][q][1], s[1][q][2]);
+  return fmaxf(t, s[1][q][3]);
+}
+template <int NC>
+__device__ __forceinline__ void step_max(const floatx4_t (&s)[2][NC], float (&mx)[NC]) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    float t = max3(s[0][q][0], s[0][q][1], s[0][q][2]);
-    t = max3(t, s[0][q][3], s[1][q][0]);
-    t = max3(t, s[1][q][1], s[1][q][2]);
-    mx[q] = fmaxf(t, s[1][q][3]);
-  }
+  for (int q = 0; q < NC; ++q) mx[q] = column_max(s, q);
 }
 
-__device__ __forceinline__ void mask_step(StepScores& s, int first_key, int g, int end) {
+template <int NC>
+__device__ __forceinline__ void mask_step(floatx4_t (&s)[2][NC], int first_key, int g, int end) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+    for (int q = 0; q < NC; ++q)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (first_key + 8 * g + 4 * t + i >= end) s[t][q][i] = -INFINITY;
 }
 
-__device__ __forceinline__ void copy_scores(StepScores& to, const StepScores& from) {
+template <int NC>
+__device__ __forceinline__ void copy_scores(floatx4_t (&to)[2][NC], const floatx4_t (&from)[2][NC]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) to[t][q] = from[t][q];
+    for (int q = 0; q < NC; ++q) to[t][q] = from[t][q];
 }
 
 __device__ __forceinline__ floatx4_t quarter(const floatx16_t& v, int k) {
   return floatx4_t{v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]};
 }
 
+template <int NC>
 struct PipeState {
-  // O^T: [d tiles 4 D .. 4 D + 3][query half], 16 registers each.  As sixteen vectors of four the compiler joins the two
+  // O^T: [d tiles 4 D .. 4 D + 3][query column], 16 registers each.  As sixteen vectors of four the compiler joins the two
   // sides of the rare branch in maybe_rescale by moving all 64 registers in every step.
-  floatx16_t o[2][2];
-  floatx4_t l[2];                 // this lane's shares of the row sum: register i has the keys 8 g + 2 i and + 1 of all steps
-  float m[2], negmc[2];           // running max (raw score units), -m*c
-  float thresh[2];                // m + tau: the max is raised only when a score exceeds this
+  floatx16_t o[2][NC];
+  float l[NC];       // row sums
+  float negmc[NC];   // -m*c of the running maximum m (0: none yet)
+  float thresh[NC];  // an exponent s*c - m*c above it raises the maximum: 8, or -inf before the first one
 };
 
-__device__ __forceinline__ void pipe_state_init(PipeState& st) {
+template <int NC>
+__device__ __forceinline__ void pipe_state_init(PipeState<NC>& st) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    st.m[q] = -INFINITY;
-    st.l[q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-    st.negmc[q] = 0.f;
+  for (int q = 0; q < NC; ++q) {
+    st.l[q] = st.negmc[q] = 0.f;
     st.thresh[q] = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 16; ++e) st.o[0][q][e] = st.o[1][q][e] = 0.f;
@@ -100,19 +121,27 @@ __device__ __forceinline__ void pipe_state_init(PipeState& st) {
 }
 
 // The four lanes of a query compare their own maxima with the common threshold; only when one exceeds it is the
-// maximum taken over all four.
-__device__ __forceinline__ void maybe_rescale(PipeState& st, const float (&mx)[2], float c, float tau) {
-  if (__builtin_amdgcn_ballot_w64(mx[0] > st.thresh[0] || mx[1] > st.thresh[1]) != 0) {   // wave-uniform; after the first step this is rare
+// maximum taken over all four, and what depends on it brought to the new one: the sums and the exponents `x` of the coming step.
+template <int NC>
+__device__ __forceinline__ void maybe_rescale(PipeState<NC>& st, const float (&mx)[NC], floatx4_t (&x)[2][NC]) {
+  bool up = false;
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < NC; ++q) up = up || mx[q] > st.thresh[q];
+  if (__builtin_amdgcn_ballot_w64(up) != 0) {   // wave-uniform; after the first step this is rare
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
       float all = fmaxf(mx[q], __shfl_xor(mx[q], 16, kWave));
       all = fmaxf(all, __shfl_xor(all, 32, kWave));
-      const float m_new = fmaxf(st.m[q], all);
-      const float alpha = fast_exp2((st.m[q] - m_new) * c);
-      st.m[q] = m_new;
-      st.negmc[q] = -m_new * c;
-      st.thresh[q] = m_new + tau;
+      const bool first = st.thresh[q] == -INFINITY;
+      const float by = first ? (all == -INFINITY ? 0.f : all) : fmaxf(all, 0.f);
+      const float alpha = first ? 0.f : fast_exp2(-by);
+      if (all != -INFINITY) st.thresh[q] = 8.f;
+      st.negmc[q] -= by;
       st.l[q] *= alpha;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[t][q][i] -= by;
 #pragma unroll
       for (int D = 0; D < 2; ++D)
 #pragma unroll
@@ -121,101 +150,141 @@ __device__ __forceinline__ void maybe_rescale(PipeState& st, const float (&mx)[2
   }
 }
 
+// Exponents of a column's keys from its scores, and their maximum.
+template <int NC>
+__device__ __forceinline__ float column_exponents(floatx4_t (&s)[2][NC], int q, float c, float negmc) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s[t][q][i] = fmaf(s[t][q][i], c, negmc);
+  return column_max(s, q);
+}
+
 // Scores of a whole step from its K rows at byte offset `off`.
-__device__ __forceinline__ void step_scores(const PipeLane& ln, unsigned off, const bf16x8_t (&qf)[2][4], StepScores& s) {
+template <int ROWS, int NC>
+__device__ __forceinline__ void step_scores(const PipeLane& ln, unsigned off, const bf16x8_t (&qf)[NC][4], floatx4_t (&s)[2][NC]) {
   bf16x8_t kf[2][4];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) kf[t][ks] = lds_read_b128(ln.k[ks] + off + t * kRow4Bytes);
+    for (int ks = 0; ks < 4; ++ks) kf[t][ks] = read_nat<ROWS>(ln.k + off, t, ks);
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
+      for (int q = 0; q < NC; ++q)
         s[t][q] = mfma16(kf[t][ks], qf[q][ks], ks == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : s[t][q]);
 }
 
-// One pipeline step.  koff: byte offset (ring slot + half) of the NEXT step's keys; voff: byte
-// offset of the CURRENT step's values.  s_cur holds the current step's raw scores; s_next
-// receives the next step's raw scores (if HAS_NEXT) and mx their lane maxima.
-template <bool PRIO, bool HAS_NEXT, int KOFF = 0, int VOFF = 0>
-__device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff, const bf16x8_t (&qf)[2][4],
-                                          PipeState& st, const StepScores& s_cur, StepScores& s_next, float (&mx)[2],
-                                          float c) {
+// One pipeline step.  KOFF: byte offset (half of a tile, or ring slot too) of the NEXT step's keys; VOFF: of the CURRENT step's
+// values; with SLOT koff and voff are added to them.  s_cur holds the current step's exponents; s_next
+// receives those of the next step (if HAS_NEXT) and mx their lane maxima.
+//
+// The step's sixteen fragments (K rows, then V transposed) are read kWin ahead of their products, three products each, and the
+// exponentials stay where they are put among the products: with all fragments read first, as 32 rows per wave allow, the registers
+// spill, and the compiler's own order of loads and exponentials takes 2 to 5 % longer.  The exponents are made where the scores are, not
+// where they are used: the vector instructions are spread over both halves of the step, the maximum needs no canonical copies of
+// its operands, and no maximum but the scaled one is kept (zeros, 145,080 x 40 heads: 33.1 -> 31.4 ms with the addresses).
+// `mid` is called among the PV products, kWin d tiles before their end: the barrier of the tiles.  There, once a tile, it also keeps
+// the two waves of a SIMD in step, one at its scores while the other is at its PV products; with a barrier for two tiles zeros take 8 % longer.
+constexpr int kWin = 2, kSumAt = 3, kMaxAt = 3;   // d tile where the row sums, and from which on the maxima, are taken
+template <int ROWS, bool SLOT, bool PRIO, bool HAS_NEXT, int KOFF, int VOFF, int NC, typename F>
+__device__ __forceinline__ void pipe_step(const PipeLane& ln, unsigned koff, unsigned voff, const bf16x8_t (&qf)[NC][4],
+                                          PipeState<NC>& st, const floatx4_t (&s_cur)[2][NC], floatx4_t (&s_next)[2][NC],
+                                          float (&mx)[NC], float c, F&& mid) {
   // The scores and exponentials are the long chain of a step: they go first when the SIMD's two waves compete, and the
-  // other wave's PV products fill the gaps (580,320 x 40 heads: 175.4 -> 169.4 ms; the other way round 5 % slower).
-  // From the step's first LDS reads on, and the row sums last among the products: 62,400 x 12 heads on zeros 3.08 -> 3.00 ms,
-  // 32,760 x 12 669 -> 666 us, within the noise where the power limit binds.
+  // other wave's PV products fill the gaps (without priorities 4 % slower, on zeros 8 %).
   wave_priority<PRIO, 1>();
-  bf16x8_t kf[2][4];
-  if (HAS_NEXT) {
+  unsigned int pk[NC][4];
+  constexpr int kKeep = 0x2 | 0x4 | 0x400;   // what may cross: vector, scalar and transcendental instructions
+  bf16x8_t fr[16];   // K rows (t, ks), then V transposed (dt)
+  // One address per kind of read, so that everything else is an immediate of the read: left to itself the compiler adds
+  // each offset by an instruction of its own.
+  unsigned ka = ln.k, va[2] = {ln.v[0], ln.v[1]};
+  if (SLOT) {
+    ka = in_register(ka + koff);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) kf[t][ks] = lds_read_b128(ln.k[ks] + koff + KOFF + t * kRow4Bytes);
+    for (int p = 0; p < 2; ++p) va[p] = in_register(va[p] + voff);
   }
-  bf16x8_t vf[8];
+  auto load = [&](int f) {
+    if (f < 8) {
+      if constexpr (HAS_NEXT) fr[f] = read_nat<ROWS>(ka + KOFF, f >> 2, f & 3);
+    } else if (f < 16) {
+      fr[f] = read_tr<ROWS>(va, VOFF, f - 8);
+    }
+  };
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) vf[dt] = lds_read_tr_frag(ln.v[dt] + voff + VOFF);
-
-  // P = exp2(S*c - m*c), packed to bf16; row sum from the rounded values
-  unsigned int pk[2][4];
-  if (HAS_NEXT) {
+  for (int f = 0; f < kWin; ++f) load(f);
+  if constexpr (HAS_NEXT) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) s_next[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < NC; ++q) s_next[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   }
+  // P = exp2 of the exponents, packed to bf16
+  auto word = [&](int q, int w) {   // keys 8 g + 2 w and + 1
+    const floatx4_t& v = s_cur[w >> 1][q];
+    pk[q][w] = pack_bf16x2(fast_exp2(v[2 * (w & 1)]), fast_exp2(v[2 * (w & 1) + 1]));
+  };
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
+  for (int f = 0; f < 8; ++f) {
+    __builtin_amdgcn_sched_barrier(0);
+    load(f + kWin);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (HAS_NEXT) {
-        s_next[0][q] = mfma16(kf[0][ks], qf[q][ks], s_next[0][q]);
-        s_next[1][q] = mfma16(kf[1][ks], qf[q][ks], s_next[1][q]);
-      }
-      const floatx4_t& v = s_cur[ks >> 1][q];
-      const float p0 = fast_exp2(fmaf(v[2 * (ks & 1)], c, st.negmc[q]));
-      const float p1 = fast_exp2(fmaf(v[2 * (ks & 1) + 1], c, st.negmc[q]));
-      pk[q][ks] = pack_bf16x2(p0, p1);
-    }
+    for (int q = 0; q < NC; ++q)
+      if constexpr (HAS_NEXT) s_next[f >> 2][q] = mfma16(fr[f], qf[q][f & 3], s_next[f >> 2][q]);
+#pragma unroll
+    for (int j = 4 * NC * f / 8; j < 4 * NC * (f + 1) / 8; ++j) word(j % NC, j / NC);
   }
+  __builtin_amdgcn_sched_barrier(0);
   wave_priority<PRIO, 0>();
-  bf16x8_t pf[2];
+  bf16x8_t pf[NC];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) pf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{pk[q][0], pk[q][1], pk[q][2], pk[q][3]});
-  // The row sums are one more d tile, whose row j has ones at keys 2 j and 2 j + 1 of the step: v_dot2c_f32_bf16, which summed two of the rounded weights at a time, does not run
-  // beside the matrix instructions (alternating with them it adds its 8 cycles to their 16, where an fma or a conversion adds
-  // none), and eight of them a step cost more than these two products: 62,400 x 12 heads, 5 groups 3.89 -> 3.70 ms (on zeros
-  // 3.33 -> 3.07), 32,760 x 12, 8 groups 698 -> 676 us, 99,840 x 40, 16 groups 10.7 -> 10.35 ms.
+  for (int q = 0; q < NC; ++q) pf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{pk[q][0], pk[q][1], pk[q][2], pk[q][3]});
+  floatx4_t sum[NC];
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt)
+  for (int dt = 0; dt < 8; ++dt) {
+    // The row sums are one more d tile, of ones (two weights at a time v_dot2c_f32_bf16 would sum, but that does not run beside the
+    // matrix instructions: it adds its 8 cycles to their 16), and are added up where no product waits for them.
+    if (dt == kSumAt) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+      for (int q = 0; q < NC; ++q) sum[q] = mfma16(ln.ones, pf[q], floatx4_t{0.f, 0.f, 0.f, 0.f});
+    }
+    if (dt == 7)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) st.l[q] += sum[q][0];
+    if (dt == 8 - kWin) mid();
+    if constexpr (HAS_NEXT)   // a column's maximum at a time
+      if (dt >= kMaxAt && dt < kMaxAt + NC) mx[dt - kMaxAt] = column_exponents(s_next, dt - kMaxAt, c, st.negmc[dt - kMaxAt]);
+    __builtin_amdgcn_sched_barrier(kKeep);
+    load(8 + dt + kWin);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
       floatx16_t& o = st.o[dt >> 2][q];
-      const floatx4_t t = mfma16(vf[dt], pf[q], quarter(o, dt & 3));
+      const floatx4_t t = mfma16(fr[8 + dt], pf[q], quarter(o, dt & 3));
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[4 * (dt & 3) + e] = t[e];
     }
+  }
+  if constexpr (HAS_NEXT) {   // in its registers here: not after the products, behind the branches that follow
 #pragma unroll
-  for (int q = 0; q < 2; ++q) st.l[q] = mfma16(ln.pairs, pf[q], st.l[q]);
-  if (HAS_NEXT) step_max(s_next, mx);
+    for (int q = 0; q < NC; ++q) asm volatile("" : "+v"(mx[q]));
+  }
 }
 
-// Output rows of a wave (query columns r and 16 + r of its 32 rows from q0w): O / l, times the row's gate in gather mode,
+// Output rows of a wave (query columns r, 16 + r .. of its 16 NC rows from q0w): O / l, times the row's gate in gather mode,
 // and the log-sum-exp.  Register i of d tile dt is d = 16 dt + 4 g + i.
 // o_tok (not in gather mode): NULL, or where the rows also go in token order [N, H, 128], rounded and then times the gate.
-template <bool GATHER>
-__device__ __forceinline__ void store_output(const PipeState& st, int q0w, int ge, int head, int64_t head_off, int H, float scale,
+template <bool GATHER, int NC>
+__device__ __forceinline__ void store_output(const PipeState<NC>& st, int q0w, int ge, int head, int64_t head_off, int H,
                                              unsigned short* __restrict__ oh, float* __restrict__ lse,
                                              const int32_t* __restrict__ perm, const float* __restrict__ gate,
                                              unsigned short* __restrict__ o_tok) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const float lt = row_sum(st.l[q]);
+  for (int q = 0; q < NC; ++q) {
+    const float lt = st.l[q];
     float inv = 1.f / lt;
     const int qrow = q0w + 16 * q + r;
     if (qrow < ge) {
@@ -240,28 +309,30 @@ __device__ __forceinline__ void store_output(const PipeState& st, int q0w, int g
         *(uintx4_t*)(op + 16 * dt) = v;
         if (!GATHER && o_tok) *(uintx4_t*)(tp + 16 * dt) = scale8(v, gt);
       }
-      if (g == 0) lse[head_off + qrow] = st.m[q] * scale + logf(lt);
+      if (g == 0) lse[head_off + qrow] = logf(lt) - st.negmc[q] * 0.6931471805599453f;
     }
   }
 }
 
 // A piece's O, maximum and sum of this wave's rows, not yet divided.
-__device__ __forceinline__ void store_piece(const PipeState& st, const SplitWs& sw, int slot, int wave) {
+template <int NC>
+__device__ __forceinline__ void store_piece(const PipeState<NC>& st, const SplitWs& sw, int slot, int wave) {
   const int lane = threadIdx.x & 63;
-  const size_t row0 = slot * kSplitRows + 32 * wave;
+  const size_t row0 = slot * kSplitRows + 16 * NC * wave;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const float lt = row_sum(st.l[q]);
+  for (int q = 0; q < NC; ++q) {
+    const float lt = st.l[q];
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) store_partial(sw.part + row0 * kHeadDim, dt, q, quarter(st.o[dt >> 2][q], dt & 3));
-    if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{st.m[q], lt};
+    if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{st.thresh[q] == -INFINITY ? -INFINITY : -st.negmc[q], lt};
   }
 }
+template <int NC>
 __device__ __forceinline__ void store_empty_piece(const SplitWs& sw, int slot, int wave) {
   const int lane = threadIdx.x & 63;
-  const size_t row0 = slot * kSplitRows + 32 * wave;
+  const size_t row0 = slot * kSplitRows + 16 * NC * wave;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < NC; ++q) {
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) store_partial(sw.part + row0 * kHeadDim, dt, q, floatx4_t{0.f, 0.f, 0.f, 0.f});
     if (lane < 16) *(floatx2_t*)(sw.stat + (row0 + 16 * q + lane) * 2) = floatx2_t{-INFINITY, 0.f};
@@ -269,34 +340,35 @@ __device__ __forceinline__ void store_empty_piece(const SplitWs& sw, int slot, i
 }
 
 // Zero output rows of a wave whose group has no keys (lse = -inf if given); `tok`: NULL, or the rows in token order.
-template <bool GATHER>
+template <bool GATHER, int NC>
 __device__ __forceinline__ void store_zero_rows(int row0, int ge, int head, int64_t head_off, int H, unsigned short* __restrict__ out,
                                                 float* __restrict__ lse, const int32_t* __restrict__ perm,
                                                 unsigned short* __restrict__ tok) {
-  const int lane = threadIdx.x & 63, row = row0 + (lane & 31), h = lane >> 5;
-  if (row >= ge) return;
+  const int lane = threadIdx.x & 63, h = lane >> 5;
   const uintx4_t z = {0u, 0u, 0u, 0u};
-  if (out) {
-    const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
-    uintx4_t* op = (uintx4_t*)(out + orow * kHeadDim + 64 * h);
+  for (int row = row0 + (lane & 31); row < min(ge, row0 + 16 * NC); row += 32) {
+    if (out) {
+      const int64_t orow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
+      uintx4_t* op = (uintx4_t*)(out + orow * kHeadDim + 64 * h);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) op[i] = z;
-  }
-  if (!GATHER && tok) {
-    uintx4_t* op = (uintx4_t*)(tok + ((int64_t)perm[row] * H + head) * kHeadDim + 64 * h);
+      for (int i = 0; i < 8; ++i) op[i] = z;
+    }
+    if (!GATHER && tok) {
+      uintx4_t* op = (uintx4_t*)(tok + ((int64_t)perm[row] * H + head) * kHeadDim + 64 * h);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) op[i] = z;
+      for (int i = 0; i < 8; ++i) op[i] = z;
+    }
+    if (lse && h == 0) lse[head_off + row] = -INFINITY;
   }
-  if (lse && h == 0) lse[head_off + row] = -INFINITY;
 }
 
-// B fragments of a wave's 32 rows from row0 (clamped to the last row of the group): columns 16 c + r, d = 32 ks + 8 g ..
-template <bool GATHER>
-__device__ __forceinline__ void load_columns(bf16x8_t (&f)[2][4], const unsigned short* __restrict__ src, int row0, int ge, int head,
+// B fragments of a wave's 16 NC rows from row0 (clamped to the last row of the group): columns 16 c + r, d = 32 ks + 8 g ..
+template <bool GATHER, int NC>
+__device__ __forceinline__ void load_columns(bf16x8_t (&f)[NC][4], const unsigned short* __restrict__ src, int row0, int ge, int head,
                                              int64_t head_off, int H, const int32_t* __restrict__ perm) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
+  for (int c = 0; c < NC; ++c) {
     const int row = min(row0 + 16 * c + (lane & 15), ge - 1);
     const int64_t irow = GATHER ? (int64_t)perm[row] * H + head : head_off + row;
     const unsigned short* p = src + irow * kHeadDim + 8 * (lane >> 4);
@@ -306,117 +378,80 @@ __device__ __forceinline__ void load_columns(bf16x8_t (&f)[2][4], const unsigned
 }
 
 // The fragments are in their registers: the compiler waits for their loads here and nowhere later.
-__device__ __forceinline__ void settle(bf16x8_t (&f)[2][4]) {
+template <int NC>
+__device__ __forceinline__ void settle(bf16x8_t (&f)[NC][4]) {
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(f[c][ks]));
 }
 
+// Direct-to-LDS loads of tiles of ROWS rows: a load of a wave moves one quarter of 16 rows (1 KB), and a wave moves
+// neighbouring quarters of the same rows, ROWS / (4 NW) of them per tensor.
 struct PipeDma {
   const void* kbase;   // first K row of this head's group (wave-uniform)
   const void* vbase;
-  unsigned lds_k, lds_v;   // LDS byte address of this wave's first row in buffer 0 (wave-uniform)
-  int row0;                // this lane's row inside a tile for round 0 (round i is + 4*NW*i)
-  unsigned chunk_off;      // swizzled 16-byte chunk inside the row, in bytes
+  unsigned lds_k, lds_v;   // LDS byte address of this wave's first load in buffer 0 (wave-uniform)
+  int row0;                // this lane's row inside a tile
+  unsigned chunk_off;      // its 16-byte chunk inside the row, in bytes
   int last_row;            // last valid row, relative to the group's first row
   // gather mode: rows are fetched through an index list from token-major tensors; kbase / vbase
   // then point at token 0 of this head
-  const int32_t* rows;     // index list at the group's first row (wave-uniform)
+  const void* rows;        // index list at the group's first row (wave-uniform)
   int64_t tok_stride;      // bytes between two tokens
-  int wave_row;            // 4 * wave (wave-uniform)
-  int last_index;          // last readable entry of `rows` (the list ends there; entries past the
-                           // group's own rows belong to other groups and are harmless: those rows are masked)
-  // tokens of the rows this wave moves in the next tile to be issued, rounds 0 and 1 (wave-uniform;
-  // separate scalars so that they stay in scalar registers)
-  int ta0, ta1, ta2, ta3, tb0, tb1, tb2, tb3;
+  unsigned lds_tok;        // LDS byte address of the tokens of a tile, eight slots of 256 bytes (wave-uniform)
 };
 
-// Issue the loads of the 64-key tile starting at group-relative row kv0 into ring slot `buf`:
-// 16/NW rounds, each wave moving 4 rows of K and 4 rows of V per round.
-template <int NW>
-__device__ __forceinline__ void pipe_issue_tile(const PipeDma& d, int kv0, int buf) {
-  const unsigned boff = (unsigned)buf * kPipeTileBytes;
+__device__ __forceinline__ void lds_dma4_soff(const void* base, unsigned byte_off, unsigned lds_wave_base) {
+  lds_wave_base = __builtin_amdgcn_readfirstlane(lds_wave_base);
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :
+               : "s"(lds_wave_base), "v"(byte_off), "s"(base)
+               : "memory");
+}
+
+template <int NW, int ROWS>
+constexpr int kDmaLoads = ROWS / (4 * NW);   // per tensor, wave and tile
+
+template <int NW, int ROWS>
+__device__ __forceinline__ void dma_lanes(PipeDma& d, const void* lds_k, const void* lds_v, int wave, int lane) {
+  const int unit = wave * kDmaLoads<NW, ROWS>, quarter = unit & 3;   // first of the wave's loads
+  const unsigned lds_off = quarter * kQuarterBytes<ROWS> + (unit >> 2) * 1024;
+  d.lds_k = lds_addr_uniform(lds_k) + lds_off;
+  d.lds_v = lds_addr_uniform(lds_v) + lds_off;
+  d.row0 = 16 * (unit >> 2) + (lane >> 2);
+  d.chunk_off = (unsigned)(quarter * 64 + (((lane & 3) ^ lds_swizzle(d.row0)) << 4));
+}
+
+// Gather mode: the tokens of the tile at kv0, two tiles before its rows are issued: the kernels' waits, which count the loads of
+// rows only, cover them by then (every wave moves the same 256 bytes).  Eight slots: before the first barrier a wave may be five
+// tiles ahead of one that has not read its first tokens.
+__device__ __forceinline__ void pipe_issue_tokens(const PipeDma& d, int kv0) {
+  lds_dma4_soff(d.rows, (unsigned)min(kv0 + (int)(threadIdx.x & 63), d.last_row) * 4u, d.lds_tok + ((kv0 >> 6) & 7) * 256);
+}
+
+// Issue the loads of the tile starting at group-relative row kv0 into the ring slot `boff` bytes into the ring.
+template <int NW, int ROWS, bool GATHER>
+__device__ __forceinline__ void pipe_issue(const PipeDma& d, int kv0, unsigned boff) {
+  if constexpr (GATHER) {
+    static_assert(ROWS == 64, "64 tokens at a time");
+    pipe_issue_tokens(d, kv0 + 2 * ROWS);
+    const unsigned slot = d.lds_tok + ((kv0 >> 6) & 7) * 256;
+    const int tok = *(const int __attribute__((address_space(3)))*)(uintptr_t)(slot + d.row0 * 4);
+    const int64_t off = tok * d.tok_stride + d.chunk_off;
 #pragma unroll
-  for (int i = 0; i < 16 / NW; ++i) {
-    const int row = min(kv0 + d.row0 + 4 * NW * i, d.last_row);
-    // four waves: every other round is 16 rows further, which the swizzle turns into chunk ^ 3
-    const unsigned off = (unsigned)row * (kHeadDim * 2) + (NW == 4 && (i & 1) ? d.chunk_off ^ 48u : d.chunk_off);
-    lds_dma16_soff(d.kbase, off, d.lds_k + boff + i * 4 * NW * 256);
-    lds_dma16_soff(d.vbase, off, d.lds_v + boff + i * 4 * NW * 256);
+    for (int i = 0; i < kDmaLoads<NW, ROWS>; ++i) {
+      lds_dma16((const char*)d.kbase + off + 64 * i, d.lds_k + boff + i * kQuarterBytes<ROWS>);
+      lds_dma16((const char*)d.vbase + off + 64 * i, d.lds_v + boff + i * kQuarterBytes<ROWS>);
+    }
+  } else {
+    const unsigned off = (unsigned)min(kv0 + d.row0, d.last_row) * (kHeadDim * 2) + d.chunk_off;
+#pragma unroll
+    for (int i = 0; i < kDmaLoads<NW, ROWS>; ++i) {
+      lds_dma16_soff(d.kbase, off + 64 * i, d.lds_k + boff + i * kQuarterBytes<ROWS>);
+      lds_dma16_soff(d.vbase, off + 64 * i, d.lds_v + boff + i * kQuarterBytes<ROWS>);
+    }
   }
-}
-
-// Gather mode: the tokens of the tile's rows were read (as scalars) while the previous tile was
-// issued; select this lane's token, form the two 64-bit addresses, issue, then read the tokens of
-// the following tile.
-// Scalar (constant-address-space) read of one index: address and result are wave-uniform.
-__device__ __forceinline__ int scalar_load_index(const int32_t* p, int i) {
-  typedef const int32_t __attribute__((address_space(4))) * cptr;
-  return __builtin_amdgcn_readfirstlane(((cptr)(uintptr_t)p)[i]);
-}
-
-typedef int intx4_t __attribute__((ext_vector_type(4)));
-
-// Four consecutive indices with one 16-byte scalar load.
-__device__ __forceinline__ intx4_t scalar_load_index4(const int32_t* p, int i) {
-  typedef const intx4_t __attribute__((address_space(4), aligned(4))) * cptr4;
-  return *(cptr4)(uintptr_t)(p + i);
-}
-
-template <int NW>
-__device__ __forceinline__ void pipe_load_tokens(PipeDma& d, int kv0) {
-  const int r0 = kv0 + d.wave_row;
-  if (NW == 8 && r0 + 35 <= d.last_index) {   // the common case: two 16-byte scalar loads, no clamping
-    const intx4_t a = scalar_load_index4(d.rows, r0), b = scalar_load_index4(d.rows, r0 + 32);
-    d.ta0 = __builtin_amdgcn_readfirstlane(a[0]);
-    d.ta1 = __builtin_amdgcn_readfirstlane(a[1]);
-    d.ta2 = __builtin_amdgcn_readfirstlane(a[2]);
-    d.ta3 = __builtin_amdgcn_readfirstlane(a[3]);
-    d.tb0 = __builtin_amdgcn_readfirstlane(b[0]);
-    d.tb1 = __builtin_amdgcn_readfirstlane(b[1]);
-    d.tb2 = __builtin_amdgcn_readfirstlane(b[2]);
-    d.tb3 = __builtin_amdgcn_readfirstlane(b[3]);
-    return;
-  }
-  d.ta0 = scalar_load_index(d.rows, min(r0 + 0, d.last_row));
-  d.ta1 = scalar_load_index(d.rows, min(r0 + 1, d.last_row));
-  d.ta2 = scalar_load_index(d.rows, min(r0 + 2, d.last_row));
-  d.ta3 = scalar_load_index(d.rows, min(r0 + 3, d.last_row));
-  if (NW == 8) {
-    d.tb0 = scalar_load_index(d.rows, min(r0 + 32, d.last_row));
-    d.tb1 = scalar_load_index(d.rows, min(r0 + 33, d.last_row));
-    d.tb2 = scalar_load_index(d.rows, min(r0 + 34, d.last_row));
-    d.tb3 = scalar_load_index(d.rows, min(r0 + 35, d.last_row));
-  }
-}
-
-__device__ __forceinline__ int select4(int sub, int a, int b, int c, int e) {
-  int t = a;
-  t = sub == 1 ? b : t;
-  t = sub == 2 ? c : t;
-  t = sub == 3 ? e : t;
-  return t;
-}
-
-template <int NW>
-__device__ __forceinline__ void pipe_issue_tile_gather(PipeDma& d, int kv0, int buf) {
-  static_assert(NW == 8, "gather mode moves two rounds of four rows per wave");
-  const unsigned boff = (unsigned)buf * kPipeTileBytes;
-  const int sub = d.row0 & 3;
-  const int64_t off_a = (int64_t)select4(sub, d.ta0, d.ta1, d.ta2, d.ta3) * d.tok_stride + d.chunk_off;
-  const int64_t off_b = (int64_t)select4(sub, d.tb0, d.tb1, d.tb2, d.tb3) * d.tok_stride + d.chunk_off;
-  lds_dma16((const char*)d.kbase + off_a, d.lds_k + boff);
-  lds_dma16((const char*)d.vbase + off_a, d.lds_v + boff);
-  lds_dma16((const char*)d.kbase + off_b, d.lds_k + boff + 4 * NW * 256);
-  lds_dma16((const char*)d.vbase + off_b, d.lds_v + boff + 4 * NW * 256);
-  pipe_load_tokens<NW>(d, kv0 + 64);
-}
-
-template <int NW, bool GATHER>
-__device__ __forceinline__ void pipe_issue(PipeDma& d, int kv0, int buf) {
-  if constexpr (GATHER) pipe_issue_tile_gather<NW>(d, kv0, buf);
-  else pipe_issue_tile<NW>(d, kv0, buf);
 }
 
 // Queries are the rows cu_q[g] .. cu_q[g+1] of qh [H, Nq, 128]; their keys and values the rows
@@ -430,22 +465,23 @@ __device__ __forceinline__ void pipe_issue(PipeDma& d, int kv0, int buf) {
 // permutation of Alg. 1 is applied while loading, nothing is materialised) and the output row is
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
 // SPLIT: the last round is cut into pieces (find_work).
-template <int NW, bool GATHER = false, bool SPLIT = false>
-__global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
+// ROWS: query rows of a block, 384 or 256 (fwd_rows chooses).
+template <int ROWS, bool GATHER = false, bool SPLIT = false>
+__global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
     float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
     const float* __restrict__ gate = nullptr, SplitWs sw = {}, unsigned short* __restrict__ o_tok = nullptr) {
-  constexpr int BM = NW * 32;
-  constexpr int kDmaPerTile = 2 * (16 / NW);   // direct-to-LDS instructions per thread per tile
-  static_assert(NW == 4 || NW == 8, "4 or 8 waves");
+  constexpr int NW = 8;
+  constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64>;   // direct-to-LDS instructions per thread per tile
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[kPipeNBuf][64 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[kPipeNBuf][64 * kHeadDim];
+  __shared__ __attribute__((aligned(256))) int toks[GATHER ? 512 : 1];   // gather mode: tokens of eight tiles
 
   WorkTile sp;
-  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, ROWS, blockIdx.x, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -455,167 +491,122 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_bf16_pipe_kernel(
   if (piece) split_range(sp, gs, n);
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int q0w = q0 + wave * 32;   // first query row of this wave
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
-  const float c = scale * 1.4426950408889634f;
-  const float tau = 8.f / c;
+  const float c = uniform_float(scale * 1.4426950408889634f);
 
-  if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-    if (piece) store_empty_piece(sw, sp.slot, wave);
-    else store_zero_rows<GATHER>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
-    return;
-  }
-
-  bf16x8_t qf[2][4];
-  load_columns<GATHER>(qf, qh, q0w, ge, head, head_off, H, perm);
-
-  // ---- direct-to-LDS loads: first kPipeAhead + 1 tiles (always issued; rows are clamped)
-  PipeDma dma;
-  dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
-  dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&Ks[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&Vs[0][0]) + wave * 1024;
-  dma.row0 = 4 * wave + (lane >> 4);
-  dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
-  dma.last_row = n - 1;
-  if constexpr (GATHER) {
-    dma.rows = (const int32_t*)uniform_ptr(perm + gs);
-    dma.tok_stride = (int64_t)H * kHeadDim * 2;
-    dma.wave_row = 4 * wave;
-    dma.last_index = (int)(Nk - 1) - gs;
-    pipe_load_tokens<NW>(dma, 0);
-  }
-#pragma unroll
-  for (int t = 0; t <= kPipeAhead; ++t) pipe_issue<NW, GATHER>(dma, 64 * t, t);
-
-  PipeLane ln;
-  nat_addresses(ln.k, &Ks[0][0], lane);
-  tr_addresses(ln.v, &Vs[0][0], lane);
-  ln.pairs = pair_ones(lane);
-  PipeState st;
-  pipe_state_init(st);
-
-  const int nsteps = (n + 31) >> 5;
-  const int nfull = n >> 5;   // steps whose 32 keys are all inside the group
-
-  // ---- prologue: scores of step 0
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kPipeAhead));
-  __syncthreads();
-  if (q0w >= ge) {
-    // Every query row of this wave lies past the end of the group (last tile of a group): it only moves
-    // its share of the K/V tiles and keeps the barriers of the loops below, one for one, so that no
-    // matrix or vector work is spent on padding.
-    int s = 0;
-    for (; s + 8 <= nfull - 1; s += 8) {
-#pragma unroll
-      for (int B = 0; B < 4; ++B) {
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
-        __syncthreads();
-        pipe_issue<NW, GATHER>(dma, 32 * s + 64 * (B + 1 + kPipeAhead), (B + 1 + kPipeAhead) & 3);
-      }
+  // A wave owns 16 NC query rows: three columns, or two where that is enough for the last tile of a group, which then takes
+  // two thirds of the time.
+  auto sweep = [&](auto columns) {
+    constexpr int NC = columns.value;
+    const int q0w = q0 + wave * 16 * NC;   // first query row of this wave
+    if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
+      if (piece) store_empty_piece<NC>(sw, sp.slot, wave);
+      else store_zero_rows<GATHER, NC>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
+      return;
     }
-    while (s + 2 <= nfull - 1) {
+
+    bf16x8_t qf[NC][4];
+    load_columns<GATHER>(qf, qh, q0w, ge, head, head_off, H, perm);
+
+    // the first kPipeAhead + 1 tiles (always issued; rows are clamped)
+    PipeDma dma;
+    dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
+    dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
+    dma_lanes<NW, 64>(dma, &Ks[0][0], &Vs[0][0], wave, lane);
+    dma.last_row = n - 1;
+    if constexpr (GATHER) {
+      dma.rows = uniform_ptr(perm + gs);
+      dma.tok_stride = (int64_t)H * kHeadDim * 2;
+      dma.lds_tok = lds_addr_uniform(&toks[0]);
+      pipe_issue_tokens(dma, 0);
+      pipe_issue_tokens(dma, 64);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
+#pragma unroll
+    for (int t = 0; t <= kPipeAhead; ++t) {
+      if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
+      pipe_issue<NW, 64, GATHER>(dma, 64 * t, t * kPipeTileBytes);
+    }
+
+    PipeLane ln;
+    ln.k = nat_address(&Ks[0][0], lane);
+    tr_addresses(ln.v, &Vs[0][0], lane);
+    ln.ones = all_ones();
+    PipeState<NC> st;
+    pipe_state_init(st);
+
+    // Tile T (64 keys, two steps) lives in ring slot T % 4.  Step 2T reads its values and the next step's keys from that slot;
+    // then the block waits for tile T+1, refills the slot of tile T-1 with tile T+3, and step 2T+1 reads the keys of step 2T+2
+    // from the slot of tile T+1.
+    auto next_tile = [&](int T) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
-      __syncthreads();
-      pipe_issue<NW, GATHER>(dma, 32 * (s + 2) + 64 * kPipeAhead, ((s >> 1) + 1 + kPipeAhead) & 3);
-      s += 2;
-    }
-    for (; s < nsteps; ++s) {
-      if ((s & 1) == 1 && s + 1 < nsteps) {
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
-        __syncthreads();
-        pipe_issue<NW, GATHER>(dma, 32 * (s + 1) + 64 * kPipeAhead, (((s >> 1) & 3) + 1 + kPipeAhead) & 3);
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    return;
-  }
-  StepScores s_a, s_b;   // scores of even / odd steps
-  float mx[2];
-  step_scores(ln, 0, qf, s_a);
-  if (nfull == 0) mask_step(s_a, 0, lane >> 4, n);
-  step_max(s_a, mx);
-
-  // ---- main loop.  Tile T (64 keys, two steps) lives in ring slot T % 4.  Step 2T reads its
-  // values and the next step's keys from that slot; then the block waits for tile T+1, refills
-  // the slot of tile T-1 with tile T+3, and step 2T+1 reads the keys of step 2T+2 from the slot
-  // of tile T+1.  Four tiles per iteration so that every LDS offset is an immediate.
-  int s = 0;
-#define MOGA_FWD_TILE(B)                                                                        \
-  maybe_rescale(st, mx, c, tau);                                                            \
-  pipe_step<true, true, (B) * kPipeTileBytes + 8192, (B) * kPipeTileBytes>(ln, 0, 0, qf, st, s_a, s_b, mx, c); \
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));                       \
-  __syncthreads();                                                                              \
-  pipe_issue<NW, GATHER>(dma, 32 * s + 64 * ((B) + 1 + kPipeAhead), ((B) + 1 + kPipeAhead) & 3); \
-  maybe_rescale(st, mx, c, tau);                                                            \
-  pipe_step<true, true, (((B) + 1) & 3) * kPipeTileBytes, (B) * kPipeTileBytes + 8192>(ln, 0, 0, qf, st, s_b, s_a, mx, c);
-  for (; s + 8 <= nfull - 1; s += 8) {   // steps s .. s+7 and their successors are full
-    MOGA_FWD_TILE(0)
-    MOGA_FWD_TILE(1)
-    MOGA_FWD_TILE(2)
-    MOGA_FWD_TILE(3)
-  }
-#undef MOGA_FWD_TILE
-  // remaining whole tiles, ring offsets at run time (s / 2 is a multiple of 4 on entry)
-  while (s + 2 <= nfull - 1) {
-    const unsigned slot = ((unsigned)(s >> 1) & 3u) * kPipeTileBytes;
-    const unsigned slot_next = ((unsigned)((s >> 1) + 1) & 3u) * kPipeTileBytes;
-    maybe_rescale(st, mx, c, tau);
-    pipe_step<true, true>(ln, slot + 8192, slot, qf, st, s_a, s_b, mx, c);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
+      block_barrier();
+      pipe_issue<NW, 64, GATHER>(dma, 64 * (T + 1 + kPipeAhead), ((T + 1 + kPipeAhead) & 3) * kPipeTileBytes);
+    };
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kPipeAhead));
     __syncthreads();
-    pipe_issue<NW, GATHER>(dma, 32 * (s + 2) + 64 * kPipeAhead, ((s >> 1) + 1 + kPipeAhead) & 3);
-    maybe_rescale(st, mx, c, tau);
-    pipe_step<true, true>(ln, slot_next, slot + 8192, qf, st, s_b, s_a, mx, c);
-    s += 2;
-  }
-
-  // ---- tail: at most three steps (s is even here), the last one possibly partial
-  for (; s < nsteps; ++s) {
-    const int buf = (s >> 1) & 3, half = s & 1;
-    const bool has_next = s + 1 < nsteps;
-    if (half == 1 && has_next) {   // the next step starts a new tile
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kPipeAhead - 1)));
-      __syncthreads();
-      pipe_issue<NW, GATHER>(dma, 32 * (s + 1) + 64 * kPipeAhead, (buf + 1 + kPipeAhead) & 3);
+    const int last = (n - 1) >> 6;   // the last tile
+    if (q0w >= ge) {
+      // Every query row of this wave lies past the end of the group (last tile of a group): it only moves
+      // its share of the K/V tiles and keeps the barriers of the loop below, one for one, so that no
+      // matrix or vector work is spent on padding.
+      for (int T = 0; T < last; ++T) next_tile(T);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      return;
     }
-    maybe_rescale(st, mx, c, tau);
-    const unsigned voff = buf * kPipeTileBytes + half * 8192;
-    const unsigned koff = (half ? ((buf + 1) & 3) : buf) * kPipeTileBytes + (half ? 0 : 8192);
-    if (has_next) {
-      pipe_step<true, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
-      if (s + 1 >= nfull) {
-        mask_step(s_b, 32 * (s + 1), lane >> 4, n);
-        step_max(s_b, mx);
-      }
+    Scores<NC> s_a, s_b;   // scores of even / odd steps
+    float mx[NC];
+    step_scores<64>(ln, 0, qf, s_a);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) mx[q] = column_exponents(s_a, q, c, 0.f);
+    for (int T = 0; T < last; ++T) {
+      const unsigned slot = (T & 3) * kPipeTileBytes, next = ((T + 1) & 3) * kPipeTileBytes;
+      maybe_rescale(st, mx, s_a);
+      pipe_step<64, true, true, true, kRow32Bytes, 0>(ln, slot, slot, qf, st, s_a, s_b, mx, c, [&]() { next_tile(T); });
+      maybe_rescale(st, mx, s_b);
+      pipe_step<64, true, true, true, 0, kRow32Bytes>(ln, next, slot, qf, st, s_b, s_a, mx, c, []() {});
+    }
+    // the last tile, possibly partial
+    unsigned voff = (last & 3) * kPipeTileBytes;
+    if (n - 64 * last < 32) {
+      mask_step(s_a, 64 * last, lane >> 4, n);
+      step_max(s_a, mx);
+    }
+    if (n - 64 * last > 32) {
+      maybe_rescale(st, mx, s_a);
+      pipe_step<64, true, true, true, kRow32Bytes, 0>(ln, voff, voff, qf, st, s_a, s_b, mx, c, []() {});
+      mask_step(s_b, 64 * last + 32, lane >> 4, n);
+      step_max(s_b, mx);
       copy_scores(s_a, s_b);
-    } else {
-      pipe_step<true, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      voff += kRow32Bytes;
     }
-  }
+    maybe_rescale(st, mx, s_a);
+    pipe_step<64, true, true, false, 0, 0>(ln, 0, voff, qf, st, s_a, s_b, mx, c, []() {});
 
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  if (piece) store_piece(st, sw, sp.slot, wave);
-  else store_output<GATHER>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate, o_tok);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
+    if (piece) store_piece(st, sw, sp.slot, wave);
+    else store_output<GATHER>(st, q0w, ge, head, head_off, H, oh, lse, perm, gate, o_tok);
+  };
+  if (ROWS > 256 && ge - q0 > 256) sweep(std::integral_constant<int, ROWS / 128>());
+  else sweep(std::integral_constant<int, 2>());
 }
 
-// Pieces of every query tile of the last round: O = sum O_k 2^((m_k - m) c) / l, l = sum l_k 2^((m_k - m) c).  NaN and
-// infinite scores end as in a whole tile; only a group without keys gets zero rows.
-static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const int32_t* __restrict__ cu_q,
+// Pieces of every query tile of the last round, with their maxima m_k in exponents of two: O = sum O_k 2^(m_k - m) / l,
+// l = sum l_k 2^(m_k - m).  NaN and infinite scores end as in a whole tile; only a group without keys gets zero rows.
+static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, int rows, const int32_t* __restrict__ cu_q,
                                                                const int32_t* __restrict__ cu_k, int M, int H, int64_t N,
-                                                               float scale, unsigned short* __restrict__ oh,
+                                                               unsigned short* __restrict__ oh,
                                                                float* __restrict__ lse, const int32_t* __restrict__ perm,
                                                                const float* __restrict__ gate, unsigned short* __restrict__ o_tok) {
-  const int per_head = count_tiles(cu_q, M, kSplitRows);
+  const int per_head = count_tiles(cu_q, M, rows);
   const SplitShape s = split_shape(per_head * H);
   if (s.splits == 1 || (int)blockIdx.x >= s.left) return;
   int head, tile;
   decode_work(s.full + blockIdx.x, per_head, H, head, tile);
   TileInfo ti;
-  if (!find_tile(cu_q, M, kSplitRows, tile, ti)) return;
+  if (!find_tile(cu_q, M, rows, tile, ti)) return;
   const bool keys = cu_k[ti.group + 1] > cu_k[ti.group];
-  const float c = scale * 1.4426950408889634f;
   const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
   if (ti.tile_row + r >= ti.row_end) return;
   const size_t first = (size_t)blockIdx.x * s.splits * kSplitRows + r;   // piece k is k * kSplitRows rows further
@@ -634,7 +625,7 @@ static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const
 #pragma unroll
   for (int k = 0; k < kMaxSplits; ++k)
     if (k < s.splits) {
-      const float w = ml[k][0] == m ? 1.f : fast_exp2((ml[k][0] - m) * c);   // equal: also both -inf
+      const float w = ml[k][0] == m ? 1.f : fast_exp2(ml[k][0] - m);   // equal: also both -inf
       l += ml[k][1] * w;
       o += v[k] * w;
     }
@@ -645,7 +636,7 @@ static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, const
     const int tok = perm[ti.tile_row + r];
     *(uintx2_t*)(o_tok + ((int64_t)tok * H + head) * kHeadDim + col) = scale4(w, gate[tok]);
   }
-  if (col == 0) lse[orow] = keys ? m * scale + logf(l) : -INFINITY;
+  if (col == 0) lse[orow] = keys ? m * 0.6931471805599453f + logf(l) : -INFINITY;
 }
 
 }  // namespace moga

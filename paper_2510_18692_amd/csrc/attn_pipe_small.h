@@ -14,19 +14,6 @@ namespace moga {
 
 constexpr int kSmallTileBytes = 32 * kHeadDim * 2;   // 8 KB per K (or V) tile of 32 keys
 
-// Issue the loads of the 32-key tile starting at group-relative row kv0 into ring slot `buf`:
-// two rounds, each of the 4 waves moving 4 rows of K and 4 rows of V per round.
-__device__ __forceinline__ void small_issue_tile(const PipeDma& d, int kv0, int buf) {
-  const unsigned boff = (unsigned)buf * kSmallTileBytes;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = min(kv0 + d.row0 + 16 * i, d.last_row);
-    const unsigned off = (unsigned)row * (kHeadDim * 2) + (i ? d.chunk_off ^ 48u : d.chunk_off);   // 16 rows: chunk ^ 3
-    lds_dma16_soff(d.kbase, off, d.lds_k + boff + i * 4096);
-    lds_dma16_soff(d.vbase, off, d.lds_v + boff + i * 4096);
-  }
-}
-
 // Arguments as attn_fwd_bf16_pipe_kernel (no gather mode); tiles of 128 query rows.
 __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
@@ -36,7 +23,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     float* __restrict__ lse, const int32_t* __restrict__ perm, const float* __restrict__ gate,
     unsigned short* __restrict__ o_tok) {
   constexpr int BM = 128;
-  constexpr int kDmaPerTile = 4;   // direct-to-LDS instructions per thread per tile
+  constexpr int kDmaPerTile = 2 * kDmaLoads<4, 32>;   // direct-to-LDS instructions per thread per tile
   constexpr int kAhead = 2;        // tiles in flight beyond the one being waited for
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[4][32 * kHeadDim];
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[4][32 * kHeadDim];
@@ -54,10 +41,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
   const float c = scale * 1.4426950408889634f;
-  const float tau = 8.f / c;
 
   if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-    store_zero_rows<false>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
+    store_zero_rows<false, 2>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
     return;
   }
 
@@ -67,19 +53,16 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   PipeDma dma;
   dma.kbase = uniform_ptr(kh + (head_off_k + gs) * kHeadDim);
   dma.vbase = uniform_ptr(vh + (head_off_k + gs) * kHeadDim);
-  dma.lds_k = lds_addr_uniform(&Ks[0][0]) + wave * 1024;
-  dma.lds_v = lds_addr_uniform(&Vs[0][0]) + wave * 1024;
-  dma.row0 = 4 * wave + (lane >> 4);
-  dma.chunk_off = (unsigned)(((lane & 15) ^ lds_swizzle(dma.row0)) * 16);
+  dma_lanes<4, 32>(dma, &Ks[0][0], &Vs[0][0], wave, lane);
   dma.last_row = n - 1;
 #pragma unroll
-  for (int t = 0; t <= kAhead; ++t) small_issue_tile(dma, 32 * t, t);   // rows are clamped: always issued
+  for (int t = 0; t <= kAhead; ++t) pipe_issue<4, 32, false>(dma, 32 * t, t * kSmallTileBytes);   // rows are clamped: always issued
 
   PipeLane ln;
-  nat_addresses(ln.k, &Ks[0][0], lane);
+  ln.k = nat_address(&Ks[0][0], lane);
   tr_addresses(ln.v, &Vs[0][0], lane);
-  ln.pairs = pair_ones(lane);
-  PipeState st;
+  ln.ones = all_ones();
+  PipeState<2> st;
   pipe_state_init(st);
 
   const int nsteps = (n + 31) >> 5;
@@ -94,16 +77,20 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
     for (int s = 0; s < nsteps; ++s) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
       __syncthreads();
-      small_issue_tile(dma, 32 * (s + 1 + kAhead), (s + 1 + kAhead) & 3);
+      pipe_issue<4, 32, false>(dma, 32 * (s + 1 + kAhead), ((s + 1 + kAhead) & 3) * kSmallTileBytes);
     }
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
     return;
   }
   StepScores s_a, s_b;   // scores of even / odd steps
   float mx[2];
-  step_scores(ln, 0, qf, s_a);
-  if (nfull == 0) mask_step(s_a, 0, lane >> 4, n);
-  step_max(s_a, mx);
+  step_scores<32>(ln, 0, qf, s_a);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) mx[q] = column_exponents(s_a, q, c, 0.f);
+  if (nfull == 0) {
+    mask_step(s_a, 0, lane >> 4, n);
+    step_max(s_a, mx);
+  }
 
   // main loop.  Step s (= tile s) lives in ring slot s % 4: it reads its values from that slot and
   // the keys of step s+1 from the next one.  At the top of a step the block waits for tile s+1 and
@@ -113,9 +100,9 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
 #define MOGA_SMALL_STEP(B, SA, SB)                                                        \
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));                     \
   __syncthreads();                                                                        \
-  small_issue_tile(dma, 32 * (s + (B) + 1 + kAhead), ((B) + 1 + kAhead) & 3);             \
-  maybe_rescale(st, mx, c, tau);                                                      \
-  pipe_step<false, true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c);
+  pipe_issue<4, 32, false>(dma, 32 * (s + (B) + 1 + kAhead), (((B) + 1 + kAhead) & 3) * kSmallTileBytes);             \
+  maybe_rescale(st, mx, SA);                                                          \
+  pipe_step<32, false, false, true, (((B) + 1) & 3) * kSmallTileBytes, (B) * kSmallTileBytes>(ln, 0, 0, qf, st, SA, SB, mx, c, []() {});
   for (; s + 4 <= nfull - 1; s += 4) {   // steps s .. s+3 and their successors are full
     MOGA_SMALL_STEP(0, s_a, s_b)
     MOGA_SMALL_STEP(1, s_b, s_a)
@@ -128,25 +115,25 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   for (; s < nsteps; ++s) {
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
     __syncthreads();
-    small_issue_tile(dma, 32 * (s + 1 + kAhead), (s + 1 + kAhead) & 3);
+    pipe_issue<4, 32, false>(dma, 32 * (s + 1 + kAhead), ((s + 1 + kAhead) & 3) * kSmallTileBytes);
     const bool has_next = s + 1 < nsteps;
-    maybe_rescale(st, mx, c, tau);
+    maybe_rescale(st, mx, s_a);
     const unsigned voff = (unsigned)(s & 3) * kSmallTileBytes;
     const unsigned koff = (unsigned)((s + 1) & 3) * kSmallTileBytes;
     if (has_next) {
-      pipe_step<false, true>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<32, true, false, true, 0, 0>(ln, koff, voff, qf, st, s_a, s_b, mx, c, []() {});
       if (s + 1 >= nfull) {
         mask_step(s_b, 32 * (s + 1), lane >> 4, n);
         step_max(s_b, mx);
       }
       copy_scores(s_a, s_b);
     } else {
-      pipe_step<false, false>(ln, koff, voff, qf, st, s_a, s_b, mx, c);
+      pipe_step<32, true, false, false, 0, 0>(ln, koff, voff, qf, st, s_a, s_b, mx, c, []() {});
     }
   }
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  store_output<false>(st, q0w, ge, head, head_off, H, scale, oh, lse, perm, gate, o_tok);
+  store_output<false>(st, q0w, ge, head, head_off, H, oh, lse, perm, gate, o_tok);
 }
 
 }  // namespace moga
