@@ -70,7 +70,7 @@ size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model,
 /*
  * Bytes with which the call runs fastest (>= moga_workspace_bytes; Nk = number of key rows, N for MoGA's own calls).  The
  * bf16 attention calls with a few rounds of long blocks use room past what they need to split the last round
- * (34 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
+ * (51 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
  * summed in pieces, so its rounding differs from that of a call with less room: results repeat bit by bit between calls
  * that both have these bytes, or both less.  Host-only.
  */
@@ -220,8 +220,8 @@ size_t moga_attn_bwd_status_offset(int64_t Nq, int H);
 void moga_debug_set_spin_limit(int polls);
 
 /*
- * The BF16 attention calls have two sets of kernels: 8-wave blocks with 256-row (forward, dQ) or
- * 128-row (dK/dV) tiles, and 4-wave blocks with tiles half as large, two blocks per CU, for the small
+ * The BF16 attention calls have two sets of kernels: 8-wave blocks with 384- or 256-row (forward), 256-row (dQ) or
+ * 192-row (dK/dV) tiles, and 4-wave blocks with 128-row (forward, dQ) or 64-row tiles, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
  * group size N / M (forward: below 1152 rows from 16 rounds of 256 256-row tiles on, 2560 from one round on, 6144 from
  * half a round on, else 5632; backward: below 500, 860 and, below one round, 1450 from three quarters of it on, else 2000; the

@@ -7,7 +7,7 @@
 // to split the last round:
 //   attn_bwd_delta   : -delta[h][j] = -sum_c dO[h][j][c] * O[h][j][c], and in bf16 -lse / scale; the calls that
 //                      write dO themselves (_tokens) or are given these constants (_rows) do without it;
-//   attn_bwd_dkdv_ab : a pair of waves owns 32 key rows and sweeps the query tiles of its group, one wave with
+//   attn_bwd_dkdv_ab : a pair of waves owns 48 key rows and sweeps the query tiles of its group, one wave with
 //                      the K fragments and the dV^T accumulators, the other with the V fragments and dK^T;
 //   attn_bwd_dq_pipe : a wave owns 32 query rows and sweeps the key tiles (mirror of forward);
 //   attn_bwd_small   : both with smaller tiles in one launch, for small groups.
@@ -156,7 +156,7 @@ extern "C" size_t moga_attn_bwd_status_offset(int64_t Nq, int H) {
 
 bool moga::bwd_splits(int64_t Nq, int64_t Nk, int H, int M) {
   return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
-         (split_pays(max_tiles(Nq, M, 256) * H) || split_pays(max_tiles(Nk, M, 128) * H));
+         (split_pays(max_tiles(Nq, M, 256) * H) || split_pays(max_tiles(Nk, M, kDkdvRows) * H));
 }
 
 extern "C" size_t moga_attn_bwd_ws_bytes(int64_t N, int H, int D, int dtype) {
@@ -198,7 +198,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
     const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
-    const int bk = small ? 64 : 128, bm = small ? 128 : 256;
+    const int bk = small ? 64 : kDkdvRows, bm = small ? 128 : 256;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
     const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
     if (!grid_fits(std::max(k_blocks, q_blocks), small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
@@ -227,7 +227,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
             g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
-        split_sum_kernel<<<dim3(kCus / 2, 32), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, 128, 1.f, softmax_scale,
+        split_sum_kernel<<<dim3(kCus / 2, 2 * kDkdvRows / 8), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, kDkdvRows, 1.f, softmax_scale,
                                                             (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
       } else
         attn_bwd_dkdv_ab_kernel<<<(unsigned)k_blocks, 512, 0, st>>>(
@@ -409,7 +409,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
-  const int64_t k_blocks = (max_tiles(N, M, 128) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, 256) * H + 7) / 8 * 8;
+  const int64_t k_blocks = (max_tiles(N, M, kDkdvRows) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, 256) * H + 7) / 8 * 8;
   if (!grid_fits(k_blocks, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + 15) / 16), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate,

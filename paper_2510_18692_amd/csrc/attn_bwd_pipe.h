@@ -3,18 +3,17 @@
 //   attn_bwd_dq_pipe_kernel   : a wave owns 32 query rows (Q, dO fragments, lse, delta and
 //                               the dQ^T accumulators in registers) and sweeps 64-key tiles of
 //                               K and V; three MFMA products per tile (S^T, dP^T, dQ^T).
-//   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 32 key rows and sweeps 64-query
+//   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 48 key rows and sweeps 64-query
 //                               tiles of Q, dO, lse and delta; one wave computes S, P and dV^T,
 //                               the other dP, dS and dK^T (P handed over through LDS).
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both also come as 4-wave blocks with a two-slot ring (64 KB of
-// LDS), two blocks per CU, in one launch (attn_bwd_small_kernel), for groups of a few thousand rows or less.
-// dQ is at the power cap like the forward; dK/dV runs at 2.14 of 2.38 GHz with the matrix pipes busy 0.61 of the time.  The
-// exchange of P does not bound it (B a whole tile behind A: the same time).  LDS fragments read beside the products cost both
-// kernels matrix time: a loop of 16x16x32 products takes 7.2 ns each at the top clock, and with a fragment read for every two 8.3
-// (row fragments) or 8.6 (transposing reads).  The whole backward on 32x32x16 and on 16x16x32: 632 and 593 ms at 580,320 x 40
-// heads, 32 groups; 2.73 and 2.67 ms at 32,760 x 12, 8 groups.
+// LDS) and 32 key rows per pair, two blocks per CU, in one launch (attn_bwd_small_kernel), for groups of a few thousand rows or less.
+// All are at the power cap.  LDS fragments read beside the products cost matrix time too: a loop of 16x16x32 products takes 7.2 ns each
+// at the top clock, and with a fragment read for every two 8.3 (row fragments) or 8.6 (transposing reads).
 #pragma once
+
+#include <type_traits>
 
 #include "attn_pipe.h"
 
@@ -119,13 +118,13 @@ __device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf
 
 // Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f: to `out` (sorted order, or token order in
 // gather mode) and, not in gather mode, to `tok` in token order; either may be NULL.
-template <bool GATHER>
-__device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], float f, int row0, int ge, int head, int64_t head_off,
+template <bool GATHER, int NC>
+__device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][NC], float f, int row0, int ge, int head, int64_t head_off,
                                                int H, unsigned short* __restrict__ out, unsigned short* __restrict__ tok,
                                                const int32_t* __restrict__ perm) {
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
+  for (int c = 0; c < NC; ++c) {
     const int row = row0 + 16 * c + r;
     if (row < ge) {
       const int64_t trow = GATHER || tok ? (int64_t)perm[row] * H + head : 0;
@@ -141,15 +140,17 @@ __device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][2], flo
   }
 }
 
-__device__ __forceinline__ void store_gradient_piece(const floatx4_t (&acc)[8][2], float* rows) {
+template <int NC>
+__device__ __forceinline__ void store_gradient_piece(const floatx4_t (&acc)[8][NC], float* rows) {
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) store_partial(rows, dt, c, acc[dt][c]);
 }
+template <int NC>
 __device__ __forceinline__ void store_zero_piece(float* rows) {
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int dt = 0; dt < 8; ++dt) store_partial(rows, dt, c, floatx4_t{0.f, 0.f, 0.f, 0.f});
 }
@@ -198,7 +199,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
 
   float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 32 * wave) * kHeadDim : nullptr;
   if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
-    if (piece) store_zero_piece(piece_rows);
+    if (piece) store_zero_piece<2>(piece_rows);
     else store_zero_rows<GATHER, 2>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
     return;
   }
@@ -303,18 +304,18 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_pipe_kernel(
 
 // ---------------------------------------------------------------------------------------
 // dK, dV with two waves per SIMD: the four products are split between two waves that own the
-// same 32 key rows.  Wave A (waves 0-3) holds K and the dV^T accumulators: it computes S = Q K^T,
+// same key rows.  Wave A (waves 0-3) holds K and the dV^T accumulators: it computes S = Q K^T,
 // P = exp2(c*S - lse*log2e), hands P to its partner through LDS and accumulates dV^T += dO^T P.
 // Wave B (waves 4-7, same SIMD as its partner) holds V and the dK^T accumulators: it computes
 // dP = dO V^T - delta, takes P, forms dS = P * dP and accumulates dK^T += Q^T dS.  Each wave
-// needs 64 accumulator registers instead of 128, so two waves fit on a SIMD and fill each other's
+// needs half of the accumulators (96 registers for 48 keys), so two waves fit on a SIMD and fill each other's
 // waits.  There is one block-wide barrier per 64-query tile (tile landed, ring slot free) and one P buffer
 // per pair, and P is handed over in one of two ways:
 //   * two-slot ring (small groups, ab_tile): by a stamp in LDS.  A writes P and then the tile's number
 //     (release), B spins on the number (acquire); the roles drift apart between the barriers.  A publishes
 //     the stamp of a tile before it reaches the next barrier and waits for B nowhere else, so the spin ends,
 //     and it rewrites P only behind that barrier, which B reaches after it has taken P.
-//   * four-slot ring (ab_tile_long): by the barrier itself, which stands behind A's writes of P.  B takes P
+//   * four-slot ring (AbTile): by the barrier itself, which stands behind A's writes of P.  B takes P
 //     behind it and then counts the tile in LDS (release); A spins on that count (acquire) before it rewrites
 //     P in the next tile.  B waits for nothing between the barrier and the count, so the spin ends.
 // Both spins are bounded (spin_until), so the kernels drain whatever happens.
@@ -367,11 +368,11 @@ __device__ __forceinline__ void ab_accumulate(const bf16x8_t (&tr)[8], const bf1
 }
 
 // A: P of one 32-query unit from its scores, also written to LDS for the partner.
-template <bool MASK>
-__device__ __forceinline__ void ab_make_p(const AbLane& ln, const StepScores& sc, float c, int g, int left, int u,
-                                          bf16x8_t (&pf)[2]) {
+template <bool MASK, int NC>
+__device__ __forceinline__ void ab_make_p(const AbLane& ln, const floatx4_t (&sc)[2][NC], float c, int g, int left, int u,
+                                          bf16x8_t (&pf)[NC]) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < NC; ++k) {
     unsigned int pp[4];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -386,15 +387,16 @@ __device__ __forceinline__ void ab_make_p(const AbLane& ln, const StepScores& sc
         pp[2 * t + (i >> 1)] = pack_bf16x2(pa, pb);
       }
     pf[k] = __builtin_bit_cast(bf16x8_t, uintx4_t{pp[0], pp[1], pp[2], pp[3]});
-    lds_write_b128(ln.p_addr + u * 2048 + k * 1024, pf[k]);
+    lds_write_b128(ln.p_addr + (u * NC + k) * 1024, pf[k]);
   }
 }
 
 // B: dS = P * dP of one unit, P read from LDS.
-__device__ __forceinline__ void ab_take_p(const AbLane& ln, const StepScores& dp, int u, bf16x8_t (&dsf)[2]) {
+template <int NC>
+__device__ __forceinline__ void ab_take_p(const AbLane& ln, const floatx4_t (&dp)[2][NC], int u, bf16x8_t (&dsf)[NC]) {
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const uintx4_t pu = __builtin_bit_cast(uintx4_t, lds_read_b128(ln.p_addr + u * 2048 + k * 1024));
+  for (int k = 0; k < NC; ++k) {
+    const uintx4_t pu = __builtin_bit_cast(uintx4_t, lds_read_b128(ln.p_addr + (u * NC + k) * 1024));
     unsigned int dd[4];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -460,78 +462,167 @@ __device__ __forceinline__ void ab_tile(const AbLane& ln, int role, unsigned off
   ab_accumulate(tr1, bop[1], acc);
 }
 
-// The tile of the four-slot kernel.  Its first row fragments (nat0, ini0) were read during the tile before, and the block barrier
-// (`barrier`, which also waits for the next tile and issues a later one) stands where P is ready: it is the hand-over of P, and
-// behind it the next tile's first fragments are read under the second products, so that no wave starts a tile with its matrix
-// pipe waiting for LDS.  With the barrier at the start of the tile and a flag for P: 13.0 against 12.4-12.7 ms for the whole
-// backward at 62,400 x 12 heads, 5 groups, 2.34 against 2.27-2.31 at 32,760 x 12, 8 groups, 574 against 562 at 580,320 x 40, 32
-// groups.  (Tried on top, no gain: B one tile behind A; the same pipeline in the dQ kernel and in the forward, 0.5 to 1 % slower.)
-//   A: S | wait until B has taken the P before, P -> LDS | barrier | dV
-//   B: dP                                                | barrier | take P, dS = P * dP | dK
-// `left`: valid query rows of the tile.  `taken`: tiles whose P B has taken; the single P buffer of a pair is rewritten only then.
-// B says so right behind the barrier and waits for nobody in between, so the wait of A ends; it is bounded all the same (see ab_tile).
-template <int SOFF, int SROW, int NOFF, int NROW, typename F>
-__device__ __forceinline__ void ab_tile_long(const AbLane& ln, int role, unsigned off, unsigned off_row, unsigned noff, unsigned noff_row,
-                                             const bf16x8_t (&kvf)[2][4], floatx4_t (&acc)[8][2], float c, int g, int left,
-                                             bf16x8_t (&nat0)[2][4], floatx4_t (&ini0)[2], int* taken, int tile_no, int spin_limit,
-                                             int* status, F&& barrier) {
-  StepScores sc[2];      // S (A) or dP (B) of the two 32-query units
-  bf16x8_t bop[2][2];    // B operand of the second product: P (A) or dS (B), per unit and key half
-  bf16x8_t nat1[2][4], tr0[8], tr1[8];
-  floatx4_t ini1[2];
-  ab_load_nat<SOFF + kRow32Bytes, SROW + 128>(ln, off, off_row, nat1, ini1);
-  __builtin_amdgcn_sched_barrier(0);
-  ab_scores(nat0, ini0, kvf, sc[0]);
-  __builtin_amdgcn_sched_barrier(0);
-  ab_load_tr<SOFF>(ln, off, tr0);
-  ab_scores(nat1, ini1, kvf, sc[1]);
-  __builtin_amdgcn_sched_barrier(0);
-  if (role == 0) {
-    if (left < 64) {   // queries past the end of the group: P = 0
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (32 * u + 8 * g + 4 * t + i >= left) sc[u][t][k][i] = -INFINITY;
-    }
-    spin_until(taken, tile_no, spin_limit, status);
-    ab_make_p<false>(ln, sc[0], c, g, 64, 0, bop[0]);
-    ab_make_p<false>(ln, sc[1], c, g, 64, 1, bop[1]);
-  }
-  ab_load_tr<SOFF + kRow32Bytes>(ln, off, tr1);
-  barrier();
-  if (role == 1) {
-    ab_take_p(ln, sc[0], 0, bop[0]);
-    ab_take_p(ln, sc[1], 1, bop[1]);
-    __hip_atomic_store(taken, tile_no + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-  // The reads for the next tile and the second products go first when the SIMD's two waves compete (with the scores first: 593
-  // against 582 ms at 580,320 x 40 heads; the products alone: 1 % more on zeros, 0.6 % at 32,760 x 12).
-  wave_priority<true, 1>();
-  ab_load_nat<NOFF, NROW>(ln, noff, noff_row, nat0, ini0);
-  ab_accumulate(tr0, bop[0], acc);
-  ab_accumulate(tr1, bop[1], acc);
-  wave_priority<true, 0>();
-}
+// The tile of the four-slot kernel, a stream of instructions for each role:
+//   A: S(u0) | S(u1), P(u0) | dV(u0), P(u1) | wait until B has taken the P before, P -> LDS | barrier | dV(u1)
+//   B: dP(u0) | dP(u1) | barrier | take P(u0), dS(u0) | dK(u0), take P(u1), dS(u1) | dK(u1)
+// The tile's 32 fragments (row fragments of both units, then transposed ones) are read kAbWin ahead of their products, across the
+// tile's end, so that no wave starts a tile with its matrix pipe waiting for LDS.  `left`: valid query rows of the tile.  `taken`: tiles
+// whose P B has taken; the single P buffer of a pair is rewritten only then.
+//
+// 48 keys per pair: a fragment feeds three products instead of two, and a tile's waits (barrier, hand-over) weigh a third less.  A's exponentials
+// stand among products of its own: as one piece between its products, in a stream that both roles shared, they took 1,480 of a tile's
+// 4,780 cycles in A, for 400 of which B waited at the barrier.  B moves the tiles: A is the longer chain.  Whole backward, 145,080 x 40 heads,
+// 8 groups 149.2 -> 138.1 ms, 62,400 x 12, 5 groups 13.5 -> 12.4, 32,760 x 12, 8 groups 2.32 -> 2.23, 16,384 x 4, 2 groups 0.764 -> 0.758; matrix
+// pipes of this kernel busy 0.604 -> 0.709.  At the power cap: variants that take 3 % fewer cycles take the same time.
+constexpr int kAbWin = 3;
+constexpr int kAbKeep = 0x2 | 0x4 | 0x400;   // what may cross a scheduling barrier: vector, scalar and transcendental instructions
+struct AbAhead {   // the next tile's first fragments and row constants
+  bf16x8_t fr[kAbWin];
+  floatx4_t ini;
+};
+template <int NC>
+struct AbTile {
+  const AbLane& ln;
+  const bf16x8_t (&kvf)[NC][4];
+  floatx4_t (&acc)[8][NC];
+  AbAhead& ahead;
+  unsigned nat, tr[2], init;   // the lane's addresses in this tile (AbLane's in slot 0)
+  unsigned nnat, ninit;        // and in the next one
+  Scores<NC> sc[2];       // S (A) or dP (B) of the two 32-query units
+  bf16x8_t bop[2][NC];    // B operand of the second product: P (A) or dS (B), per unit and key column
+  bf16x8_t fr[32];
+  floatx4_t ini[4];
 
+  __device__ __forceinline__ void load(int f) {
+    if (f < 16) {
+      fr[f] = read_nat<64>(nat + (f >> 3) * kRow32Bytes, (f >> 2) & 1, f & 3);
+      if (!(f & 3)) ini[f >> 2] = lds_read_f32x4(init + (f >> 3) * 128 + ((f >> 2) & 1) * 16);
+    } else if (f < 32) {
+      fr[f] = read_tr<64>(tr, ((f - 16) >> 3) * kRow32Bytes, f & 7);
+    } else {
+      ahead.fr[f - 32] = read_nat<64>(nnat, (f >> 2) & 1, f & 3);
+      if (f == 32) ahead.ini = lds_read_f32x4(ninit);
+    }
+  }
+  __device__ __forceinline__ void begin() {
+#pragma unroll
+    for (int f = 0; f < kAbWin; ++f) fr[f] = ahead.fr[f];
+    ini[0] = ahead.ini;
+  }
+  // The products of fragments 8 U .. 8 U + 7, and among them the 4 NC steps of `vec`, which stay where they are put: left to
+  // itself the compiler collects them in front of the products.
+  template <int U, bool VEC, typename V>
+  __device__ __forceinline__ void products(V&& vec) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int f = 8 * U + i;
+      __builtin_amdgcn_sched_barrier(VEC ? 0 : kAbKeep);
+      load(f + kAbWin);
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        if constexpr (U < 2) {
+          floatx4_t& a = sc[U][i >> 2][k];
+          a = mfma16(fr[f], kvf[k][f & 3], f & 3 ? a : ini[f >> 2]);
+        } else {
+          acc[i][k] = mfma16(fr[f], bop[U - 2][k], acc[i][k]);
+        }
+      }
+      if constexpr (VEC)
+#pragma unroll
+        for (int j = 4 * NC * i / 8; j < 4 * NC * (i + 1) / 8; ++j) vec(j % NC, j / NC);
+    }
+    if constexpr (VEC) __builtin_amdgcn_sched_barrier(0);
+  }
+  // A: word w (0 .. 3) of the B operand of unit U: P = exp2(S c)
+  template <int U>
+  __device__ __forceinline__ void make_p(int k, int w, float c) {
+    const floatx4_t& v = sc[U][w >> 1][k];
+    unsigned p = pack_bf16x2(fast_exp2(v[2 * (w & 1)] * c), fast_exp2(v[2 * (w & 1) + 1] * c));
+    asm volatile("" : "+v"(p));   // here and not behind the wait for B
+    set_word(bop[U][k], w, p);
+  }
+  // B: dS = P * dP, P as A wrote it
+  template <int U>
+  __device__ __forceinline__ void make_ds(int k, int w, unsigned p) {
+    const floatx4_t& v = sc[U][w >> 1][k];
+    set_word(bop[U][k], w, pack_bf16x2(bf16_lo_to_f32(p) * v[2 * (w & 1)], bf16_hi_to_f32(p) * v[2 * (w & 1) + 1]));
+  }
+  static __device__ __forceinline__ void set_word(bf16x8_t& f, int w, unsigned x) {
+    uintx4_t u = __builtin_bit_cast(uintx4_t, f);
+    u[w] = x;
+    f = __builtin_bit_cast(bf16x8_t, u);
+  }
+  // Queries past the end of the group: P = 0
+  template <int U>
+  __device__ __forceinline__ void mask(int g, int left) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (32 * U + 8 * g + 4 * t + i >= left) sc[U][t][k][i] = -INFINITY;
+  }
+
+  template <bool MASK, typename F>
+  __device__ __forceinline__ void run_a(float c, int g, int left, int* taken, int tile_no, int spin_limit, int* status, F&& barrier) {
+    begin();
+    products<0, false>([](int, int) {});
+    if (MASK) mask<0>(g, left);
+    products<1, true>([&](int k, int w) { make_p<0>(k, w, c); });
+    if (MASK) mask<1>(g, left);
+    products<2, true>([&](int k, int w) { make_p<1>(k, w, c); });
+    spin_until(taken, tile_no, spin_limit, status);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) lds_write_b128(ln.p_addr + (u * NC + k) * 1024, bop[u][k]);
+    barrier();
+    products<3, false>([](int, int) {});
+  }
+
+  template <typename F>
+  __device__ __forceinline__ void run_b(int* taken, int tile_no, F&& barrier) {
+    begin();
+    products<0, false>([](int, int) {});
+    products<1, false>([](int, int) {});
+    __builtin_amdgcn_sched_barrier(0);
+    barrier();
+    wave_priority<true, 1>();   // A has half a tile's products left, B needs its dS first (without: 3 % slower on zeros, 1 % else)
+    uintx4_t p[NC];
+    auto take = [&](int u) {
+#pragma unroll
+      for (int k = 0; k < NC; ++k) p[k] = __builtin_bit_cast(uintx4_t, lds_read_b128(ln.p_addr + (u * NC + k) * 1024));
+    };
+    take(0);
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) make_ds<0>(k, w, p[k][w]);
+    __builtin_amdgcn_sched_barrier(0);
+    take(1);
+    products<2, true>([&](int k, int w) { make_ds<1>(k, w, p[k][w]); });
+    __hip_atomic_store(taken, tile_no + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    wave_priority<true, 0>();
+    products<3, false>([](int, int) {});
+  }
+};
+
+constexpr int kDkdvRows = 192;   // keys of a block of the large kernel: 4 pairs of waves, 48 keys each
 // NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
 // NB: ring slots of 64 queries (4 or 2, as in the dQ kernel).
-template <int NPAIR, int NB, bool GATHER>
+template <int NPAIR, int NB, int NC, bool GATHER>
 struct DkdvLds {
   __attribute__((aligned(1024))) unsigned short q[NB][64 * kHeadDim], d_o[NB][64 * kHeadDim];
-  __attribute__((aligned(1024))) unsigned char p[NPAIR][4096];   // P of one tile, per pair
+  __attribute__((aligned(1024))) unsigned char p[NPAIR][NC * 2048];   // P of one tile, per pair
   __attribute__((aligned(256))) float l[NB][64], d[NB][64];      // -lse / scale, -delta
   __attribute__((aligned(256))) int tok[GATHER ? 512 : 1];       // gather mode: tokens of eight tiles
   int flag[NPAIR];   // per pair: number of tiles whose P has been written (NB == 2) or taken (NB == 4)
 };
 
-template <bool GATHER, int NPAIR, int NB, bool SPLIT>
+template <bool GATHER, int NPAIR, int NB, int MAXNC, bool SPLIT>
 __device__ __forceinline__ void attn_bwd_dkdv_block(
-    DkdvLds<NPAIR, NB, GATHER>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
+    DkdvLds<NPAIR, NB, MAXNC, GATHER>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
     const float* __restrict__ neg_lse_over_scale, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
@@ -540,9 +631,11 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm, float* __restrict__ part,
     unsigned short* __restrict__ d_k_tok, unsigned short* __restrict__ d_v_tok) {
   constexpr int NW = 2 * NPAIR;
-  constexpr int BK = 32 * NPAIR;                   // pairs of waves x 32 keys
+  constexpr int BK = 16 * MAXNC * NPAIR;           // keys of a tile
   constexpr int kAhead = NB - 2;
-  constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64> + 2;
+  // Who moves the tiles: the large kernel leaves it to the waves B, which wait for A's P anyway.
+  constexpr int kDmaWaves = NB == 4 ? NPAIR : NW;
+  constexpr int kDmaPerTile = 2 * kDmaLoads<kDmaWaves, 64> + 2;
 
   // Ordered before its first use by the barriers below.  With NB == 4 and no polls the first wait (of P nobody needs yet) finds its
   // word not there, so that a test reaches the give-up for certain.
@@ -562,135 +655,162 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   int* flag = &lds.flag[pair];
   const int64_t head_off = (int64_t)head * Nk;
   const int64_t head_off_q = (int64_t)head * Nq;
-  const float c = scale * 1.4426950408889634f;
-  const int k0w = k0 + pair * 32;   // first key row of this pair
-  unsigned short* outp = role == 0 ? d_vh : d_kh;
-  unsigned short* tokp = role == 0 ? d_v_tok : d_k_tok;
+  const float c = uniform_float(scale * 1.4426950408889634f);
+  // A pair of waves owns 16 NC keys: three columns, or two where that is enough for the last tile of a group, which then takes
+  // two thirds of the time.
+  auto sweep = [&](auto columns) {
+    constexpr int NC = columns.value;
+    const int k0w = k0 + pair * 16 * NC;   // first key row of this pair
+    unsigned short* outp = role == 0 ? d_vh : d_kh;
+    unsigned short* tokp = role == 0 ? d_v_tok : d_k_tok;
 
-  float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 32 * pair) * kHeadDim : nullptr;   // dV, then dK
-  if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
-    if (piece) store_zero_piece(piece_rows);
-    else store_zero_rows<GATHER, 2>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);
-    return;
-  }
+    float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 16 * NC * pair) * kHeadDim : nullptr;   // dV, then dK
+    if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
+      if (piece) store_zero_piece<NC>(piece_rows);
+      else store_zero_rows<GATHER, NC>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);
+      return;
+    }
 
-  bf16x8_t kvf[2][4];   // K (A) or V (B) of the pair's 32 key rows
-  load_columns<GATHER>(kvf, role == 0 ? kh : vh, k0w, ge, head, head_off, H, perm);
+    bf16x8_t kvf[NC][4];   // K (A) or V (B) of the pair's key rows
+    load_columns<GATHER>(kvf, role == 0 ? kh : vh, k0w, ge, head, head_off, H, perm);
 
-  PipeDma dma;   // "k" = Q rows, "v" = dO rows of this head's group
-  dma.kbase = uniform_ptr(GATHER ? qh + (int64_t)head * kHeadDim : qh + (head_off_q + gs) * kHeadDim);
-  dma.vbase = uniform_ptr(GATHER ? d_oh + (int64_t)head * kHeadDim : d_oh + (head_off_q + gs) * kHeadDim);
-  dma_lanes<NW, 64>(dma, &lds.q[0][0], &lds.d_o[0][0], wave, lane);
-  dma.last_row = n - 1;
-  if constexpr (GATHER) {
-    dma.rows = uniform_ptr(perm + gs);
-    dma.tok_stride = (int64_t)H * kHeadDim * 2;
-    dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
-    pipe_issue_tokens(dma, 0);
-    pipe_issue_tokens(dma, 64);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  }
-  const void* lbase = uniform_ptr(neg_lse_over_scale + head_off_q + gs);
-  const void* dbase = uniform_ptr(neg_delta + head_off_q + gs);
-  const unsigned lds_l = lds_addr_uniform(&lds.l[0][0]), lds_d = lds_addr_uniform(&lds.d[0][0]);
-  auto issue_tile = [&](int T) {   // every wave issues the (identical) row-constant loads so that all count alike
-    const int slot = T & (NB - 1);
-    pipe_issue<NW, 64, GATHER>(dma, 64 * T, slot * kPipeTileBytes);
-    const unsigned roff = (unsigned)min(64 * T + lane, n - 1) * 4u;
-    lds_dma4_soff(lbase, roff, lds_l + slot * 256);
-    lds_dma4_soff(dbase, roff, lds_d + slot * 256);
-  };
-#pragma unroll
-  for (int t = 0; t <= kAhead; ++t) {
-    if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
-    issue_tile(t);
-  }
-
-  AbLane ln;
-  ln.nat = nat_address(role == 0 ? &lds.q[0][0] : &lds.d_o[0][0], lane);
-  tr_addresses(ln.tr, role == 0 ? &lds.d_o[0][0] : &lds.q[0][0], lane);
-  ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&lds.l[0][0] : (unsigned)(uintptr_t)&lds.d[0][0]) + 8 * (lane >> 4) * 4;
-  ln.p_addr = (unsigned)(uintptr_t)&lds.p[0][0] + pair * 4096 + lane * 16;
-
-  settle(kvf);
-  floatx4_t acc[8][2];   // dV^T (A) or dK^T (B): d tile, key half
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) acc[dt][0] = acc[dt][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-
-  const int nfull = n >> 6;   // tiles whose 64 queries are all inside the group
-  // a pair whose 32 key rows lie past the end of the group (both of its waves) only moves its share of the tiles
-  const bool active = k0w < ge;
-  int T = 0;
-  if constexpr (NB == 4) {
-    const int ntiles = (n + 63) >> 6;
-    bf16x8_t nat0[2][4];
-    floatx4_t ini0[2];
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-    __syncthreads();
-    if (active) ab_load_nat<0, 0>(ln, 0, 0, nat0, ini0);
-    // In tile t: tile t + 1 has landed (for this wave, then for all), and every wave has left the slot of tile t - 1.
-    auto barrier = [&](int t) {
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
-      __syncthreads();
-      issue_tile(t + 3);
+    PipeDma dma;   // "k" = Q rows, "v" = dO rows of this head's group
+    dma.kbase = uniform_ptr(GATHER ? qh + (int64_t)head * kHeadDim : qh + (head_off_q + gs) * kHeadDim);
+    dma.vbase = uniform_ptr(GATHER ? d_oh + (int64_t)head * kHeadDim : d_oh + (head_off_q + gs) * kHeadDim);
+    dma_lanes<kDmaWaves, 64>(dma, &lds.q[0][0], &lds.d_o[0][0], wave % kDmaWaves, lane);
+    const bool moves = NB == 2 || role == 1;
+    dma.last_row = n - 1;
+    if constexpr (GATHER) {
+      dma.rows = uniform_ptr(perm + gs);
+      dma.tok_stride = (int64_t)H * kHeadDim * 2;
+      dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
+      if (moves) {
+        pipe_issue_tokens(dma, 0);
+        pipe_issue_tokens(dma, 64);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      }
+    }
+    const void* lbase = uniform_ptr(neg_lse_over_scale + head_off_q + gs);
+    const void* dbase = uniform_ptr(neg_delta + head_off_q + gs);
+    const unsigned lds_l = lds_addr_uniform(&lds.l[0][0]), lds_d = lds_addr_uniform(&lds.d[0][0]);
+    auto issue_tile = [&](int T) {   // every wave that moves tiles issues the (identical) row-constant loads so that all count alike
+      const int slot = T & (NB - 1);
+      pipe_issue<kDmaWaves, 64, GATHER>(dma, 64 * T, slot * kPipeTileBytes);
+      const unsigned roff = (unsigned)min(64 * T + lane, n - 1) * 4u;
+      lds_dma4_soff(lbase, roff, lds_l + slot * 256);
+      lds_dma4_soff(dbase, roff, lds_d + slot * 256);
     };
-#define MOGA_AB_TILE(B)                                                                                                  \
-  if (active)                                                                                                            \
-    ab_tile_long<(B) * kPipeTileBytes, (B) * 256, (((B) + 1) & 3) * kPipeTileBytes, (((B) + 1) & 3) * 256>(              \
-        ln, role, 0, 0, 0, 0, kvf, acc, c, lane >> 4, 64, nat0, ini0, flag, T + (B), spin_limit, status,                 \
-        [&]() { barrier(T + (B)); });                                                                                    \
-  else                                                                                                                   \
-    barrier(T + (B));
-    for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
-      MOGA_AB_TILE(0)
-      MOGA_AB_TILE(1)
-      MOGA_AB_TILE(2)
-      MOGA_AB_TILE(3)
+    if (moves) {
+#pragma unroll
+      for (int t = 0; t <= kAhead; ++t) {
+        if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
+        issue_tile(t);
+      }
     }
-#undef MOGA_AB_TILE
-    for (; T < ntiles; ++T) {
-      const unsigned slot = (unsigned)T & 3u, next = (unsigned)(T + 1) & 3u;
-      if (active)
-        ab_tile_long<0, 0, 0, 0>(ln, role, slot * kPipeTileBytes, slot * 256, next * kPipeTileBytes, next * 256, kvf, acc, c,
-                                 lane >> 4, n - 64 * T, nat0, ini0, flag, T, spin_limit, status, [&]() { barrier(T); });
-      else
-        barrier(T);
-    }
-  } else {
-#define MOGA_AB_TILE(B)                                                          \
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                  \
-  __syncthreads();                                                               \
-  issue_tile(T + (B) + 1 + kAhead);                                              \
-  if (active)                                                                    \
-    ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
-                                                                              T + (B) + 1, spin_limit, status);
-    for (; T + 4 <= nfull; T += 4) {
-      MOGA_AB_TILE(0)
-      MOGA_AB_TILE(1)
-      MOGA_AB_TILE(2)
-      MOGA_AB_TILE(3)
-    }
-#undef MOGA_AB_TILE
-    for (; T < nfull; ++T) {
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-      __syncthreads();
-      issue_tile(T + 1 + kAhead);
-      if (active)
-        ab_tile<false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                             ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
-    }
-    if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
-      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-      __syncthreads();
-      if (active)
-        ab_tile<true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
-                            ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
-    }
-  }
 
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  if (piece) store_gradient_piece(acc, piece_rows);
-  else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, tokp, perm);
+    AbLane ln;
+    ln.nat = nat_address(role == 0 ? &lds.q[0][0] : &lds.d_o[0][0], lane);
+    tr_addresses(ln.tr, role == 0 ? &lds.d_o[0][0] : &lds.q[0][0], lane);
+    ln.init_addr = (role == 0 ? (unsigned)(uintptr_t)&lds.l[0][0] : (unsigned)(uintptr_t)&lds.d[0][0]) + 8 * (lane >> 4) * 4;
+    ln.p_addr = (unsigned)(uintptr_t)&lds.p[0][0] + pair * (NC * 2048) + lane * 16;
+
+    settle(kvf);
+    floatx4_t acc[8][NC];   // dV^T (A) or dK^T (B): d tile, key column
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) acc[dt][k] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+
+    const int nfull = n >> 6;   // tiles whose 64 queries are all inside the group
+    // a pair whose 32 key rows lie past the end of the group (both of its waves) only moves its share of the tiles
+    const bool active = k0w < ge;
+    int T = 0;
+    if constexpr (NB == 4) {
+      const int ntiles = (n + 63) >> 6;
+      AbAhead ahead;
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+      __syncthreads();
+      if (active) {
+#pragma unroll
+        for (int f = 0; f < kAbWin; ++f) ahead.fr[f] = read_nat<64>(ln.nat, f >> 2, f & 3);
+        ahead.ini = lds_read_f32x4(ln.init_addr);
+      }
+      // In tile t: tile t + 1 has landed (for the wave that moved it, then for all), and every wave has left the slot of tile t - 1.
+      auto barrier_b = [&]() {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
+        block_barrier();
+        issue_tile(T + 3);
+      };
+      auto addresses = [&](AbTile<NC>& t) {   // one register each, everything else is an immediate of the reads
+        const unsigned slot = (unsigned)T & 3u, next = (unsigned)(T + 1) & 3u;
+        t.nat = in_register(ln.nat + slot * kPipeTileBytes);
+        t.tr[0] = in_register(ln.tr[0] + slot * kPipeTileBytes);
+        t.tr[1] = in_register(ln.tr[1] + slot * kPipeTileBytes);
+        t.init = in_register(ln.init_addr + slot * 256);
+        t.nnat = in_register(ln.nat + next * kPipeTileBytes);
+        t.ninit = ln.init_addr + next * 256;
+      };
+      if (!active) {
+        for (; T < ntiles; ++T) {
+          if (role == 1) barrier_b();
+          else block_barrier();
+        }
+      } else if (role == 0) {
+        for (; T < (n >> 6); ++T) {
+          AbTile<NC> t = {ln, kvf, acc, ahead};
+          addresses(t);
+          t.template run_a<false>(c, lane >> 4, 64, flag, T, spin_limit, status, []() { __syncthreads(); });
+        }
+        if (n & 63) {
+          AbTile<NC> t = {ln, kvf, acc, ahead};
+          addresses(t);
+          t.template run_a<true>(c, lane >> 4, n & 63, flag, T, spin_limit, status, []() { __syncthreads(); });
+        }
+      } else {
+        for (; T < ntiles; ++T) {
+          AbTile<NC> t = {ln, kvf, acc, ahead};
+          addresses(t);
+          t.run_b(flag, T, barrier_b);
+        }
+      }
+    } else {
+#define MOGA_AB_TILE(B)                                                          \
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                  \
+    __syncthreads();                                                               \
+    issue_tile(T + (B) + 1 + kAhead);                                              \
+    if (active)                                                                    \
+      ab_tile<false, ((B) & (NB - 1)) * kPipeTileBytes, ((B) & (NB - 1)) * 256>(ln, role, 0, 0, kvf, acc, c, lane >> 4, 64, flag, \
+                                                                                T + (B) + 1, spin_limit, status);
+      for (; T + 4 <= nfull; T += 4) {
+        MOGA_AB_TILE(0)
+        MOGA_AB_TILE(1)
+        MOGA_AB_TILE(2)
+        MOGA_AB_TILE(3)
+      }
+#undef MOGA_AB_TILE
+      for (; T < nfull; ++T) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+        __syncthreads();
+        issue_tile(T + 1 + kAhead);
+        if (active)
+          ab_tile<false, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+                               ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, 64, flag, T + 1, spin_limit, status);
+      }
+      if (n & 63) {   // last, partial tile: masked queries get P = 0 and contribute nothing
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+        __syncthreads();
+        if (active)
+          ab_tile<true, 0, 0>(ln, role, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes,
+                              ((unsigned)T & (unsigned)(NB - 1)) * 256, kvf, acc, c, lane >> 4, n - 64 * T, flag, T + 1, spin_limit, status);
+      }
+    }
+
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
+    if (piece) store_gradient_piece(acc, piece_rows);
+    else store_gradient<GATHER>(acc, role == 0 ? 1.f : scale, k0w, ge, head, head_off, H, outp, tokp, perm);
+  };
+  if (MAXNC > 2 && ge - k0 > 32 * NPAIR) sweep(std::integral_constant<int, MAXNC>());
+  else sweep(std::integral_constant<int, 2>());
 }
 
 template <bool GATHER = false, bool SPLIT = false>
@@ -704,8 +824,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_ab_kernel(
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
     unsigned short* __restrict__ d_v_tok = nullptr) {
-  __shared__ DkdvLds<4, 4, GATHER> lds;
-  attn_bwd_dkdv_block<GATHER, 4, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
+  __shared__ DkdvLds<4, 4, 3, GATHER> lds;
+  attn_bwd_dkdv_block<GATHER, 4, 4, 3, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
                                            M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok, d_v_tok);
 }
 
@@ -722,13 +842,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_kernel(
     unsigned short* __restrict__ d_k_tok, unsigned short* __restrict__ d_v_tok, int dq_blocks) {
   __shared__ union {
     DqLds<2, false> dq;
-    DkdvLds<2, 2, false> dkdv;
+    DkdvLds<2, 2, 2, false> dkdv;
   } lds;
   if ((int)blockIdx.x < dq_blocks)
     attn_bwd_dq_block<4, false, 2, false>(lds.dq, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, ts_q, M, Nq,
                                           Nk, H, scale, d_qh, perm, nullptr, d_q_tok);
   else
-    attn_bwd_dkdv_block<false, 2, 2, false>(lds.dkdv, blockIdx.x - dq_blocks, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q,
+    attn_bwd_dkdv_block<false, 2, 2, 2, false>(lds.dkdv, blockIdx.x - dq_blocks, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q,
                                             cu_k, ts_k, M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, nullptr, d_k_tok,
                                             d_v_tok);
 }

@@ -3,6 +3,7 @@ leave waves idle, with either number of query rows per block, against the oracle
 import pytest
 
 from paper_2510_18692_amd import binding as mg
+from tests import test_gpu_backward as tb
 from tests import test_gpu_forward as tf
 
 pytestmark = pytest.mark.gpu
@@ -16,5 +17,13 @@ def test_forward_at_tile_edges(H):
     mg.set_small_group_rows(0)
     try:
         tf.test_group_attention_forward_matches_oracle(SIZES, H, 128, "bf16")
+    finally:
+        mg.set_small_group_rows(-1)
+
+
+def test_backward_at_tile_edges():
+    mg.set_small_group_rows(0)
+    try:
+        tb.test_group_attention_backward_matches_oracle(SIZES + [31, 33, 63, 65, 96, 143, 144, 145, 191, 192, 193, 320, 321], 2, 128, "bf16")
     finally:
         mg.set_small_group_rows(-1)
