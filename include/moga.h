@@ -220,7 +220,7 @@ size_t moga_attn_bwd_status_offset(int64_t Nq, int H);
 void moga_debug_set_spin_limit(int polls);
 
 /*
- * The BF16 attention calls have two sets of kernels: 8-wave blocks with 384- or 256-row (forward), 256-row (dQ) or
+ * The BF16 attention calls have two sets of kernels: 8-wave blocks with 384- or 256-row (forward, dQ) or
  * 192-row (dK/dV) tiles, and 4-wave blocks with 128-row (forward, dQ) or 64-row tiles, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
  * group size N / M (forward: below 1152 rows from 16 rounds of 256 256-row tiles on, 2560 from one round on, 6144 from

@@ -9,7 +9,7 @@
 //                      write dO themselves (_tokens) or are given these constants (_rows) do without it;
 //   attn_bwd_dkdv_ab : a pair of waves owns 48 key rows and sweeps the query tiles of its group, one wave with
 //                      the K fragments and the dV^T accumulators, the other with the V fragments and dK^T;
-//   attn_bwd_dq_pipe : a wave owns 32 query rows and sweeps the key tiles (mirror of forward);
+//   attn_bwd_dq_pipe : a wave owns 48 query rows and sweeps the key tiles (mirror of forward);
 //   attn_bwd_small   : both with smaller tiles in one launch, for small groups.
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
@@ -156,7 +156,7 @@ extern "C" size_t moga_attn_bwd_status_offset(int64_t Nq, int H) {
 
 bool moga::bwd_splits(int64_t Nq, int64_t Nk, int H, int M) {
   return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
-         (split_pays(max_tiles(Nq, M, 256) * H) || split_pays(max_tiles(Nk, M, kDkdvRows) * H));
+         (split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H) || split_pays(max_tiles(Nk, M, kDkdvRows) * H));
 }
 
 extern "C" size_t moga_attn_bwd_ws_bytes(int64_t N, int H, int D, int dtype) {
@@ -198,7 +198,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
     const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
-    const int bk = small ? 64 : kDkdvRows, bm = small ? 128 : 256;
+    const int rows_q = query_rows(Nq, H, M), bk = small ? 64 : kDkdvRows, bm = small ? 128 : rows_q;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
     const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
     if (!grid_fits(std::max(k_blocks, q_blocks), small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
@@ -235,17 +235,20 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
             (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
     }
-    if (split && split_pays(q_tiles * H)) {
-      attn_bwd_dq_pipe_kernel<false, true><<<(unsigned)(q_blocks + kCus), 512, 0, st>>>(
-          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
-          delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm, split_ws(split).part, d_q_tok);
-      split_sum_kernel<<<dim3(kCus / 2, 32), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, 256, softmax_scale, 0.f,
-                                                          (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
-    } else
-      attn_bwd_dq_pipe_kernel<<<(unsigned)q_blocks, 512, 0, st>>>(
-          (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
-          (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, softmax_scale,
-          (unsigned short*)d_qh, tok.perm, nullptr, d_q_tok);
+    const bool split_q = split && split_pays(q_tiles * H);
+#define MOGA_BWD_DQ(RR, SPLIT)                                                                                                  \
+  attn_bwd_dq_pipe_kernel<RR, false, SPLIT><<<(unsigned)(q_blocks + (SPLIT ? kCus : 0)), 512, 0, st>>>(                        \
+      (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta, \
+      cu_q, cu_k, SPLIT ? nullptr : ts_q, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm,                         \
+      SPLIT ? split_ws(split).part : nullptr, d_q_tok)
+    if (split_q && rows_q == 384) MOGA_BWD_DQ(384, true);
+    else if (split_q) MOGA_BWD_DQ(256, true);
+    else if (rows_q == 384) MOGA_BWD_DQ(384, false);
+    else MOGA_BWD_DQ(256, false);
+#undef MOGA_BWD_DQ
+    if (split_q)
+      split_sum_kernel<<<dim3(kCus / 2, rows_q / 8), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, rows_q, softmax_scale, 0.f,
+                                                                   (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
   } else {
     const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
     if (!grid_fits(std::max(q_tiles, k_tiles) * H, 64 * kF32Waves)) return MOGA_ERR_UNSUPPORTED;
@@ -405,11 +408,12 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
+  const int rows_q = query_rows(N, H, M);
   hipStream_t st = (hipStream_t)stream;
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
-  const int64_t k_blocks = (max_tiles(N, M, kDkdvRows) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, 256) * H + 7) / 8 * 8;
+  const int64_t k_blocks = (max_tiles(N, M, kDkdvRows) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, rows_q) * H + 7) / 8 * 8;
   if (!grid_fits(k_blocks, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + 15) / 16), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate,
@@ -418,10 +422,13 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
       lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
       (unsigned short*)d_v, g_spin_limit.load(), status, perm);
-  attn_bwd_dq_pipe_kernel<true><<<(unsigned)q_blocks, 512, 0, st>>>(
-      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-      lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q,
-      perm);
+#define MOGA_BWD_DQ(RR)                                                                                                     \
+  attn_bwd_dq_pipe_kernel<RR, true><<<(unsigned)q_blocks, 512, 0, st>>>(                                                    \
+      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
+      cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q, perm)
+  if (rows_q == 384) MOGA_BWD_DQ(384);
+  else MOGA_BWD_DQ(256);
+#undef MOGA_BWD_DQ
   return launch_status();
 }
 

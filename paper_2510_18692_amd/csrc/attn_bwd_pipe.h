@@ -1,6 +1,6 @@
 // bf16 backward kernels of the group attention (head_dim 128) on the LDS ring of attn_pipe.h.
 //
-//   attn_bwd_dq_pipe_kernel   : a wave owns 32 query rows (Q, dO fragments, lse, delta and
+//   attn_bwd_dq_pipe_kernel   : a wave owns 48 query rows (Q, dO fragments, lse, delta and
 //                               the dQ^T accumulators in registers) and sweeps 64-key tiles of
 //                               K and V; three MFMA products per tile (S^T, dP^T, dQ^T).
 //   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 48 key rows and sweeps 64-query
@@ -8,7 +8,7 @@
 //                               the other dP, dS and dK^T (P handed over through LDS).
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
 // ahead; one block-wide barrier per tile.  Both also come as 4-wave blocks with a two-slot ring (64 KB of
-// LDS) and 32 key rows per pair, two blocks per CU, in one launch (attn_bwd_small_kernel), for groups of a few thousand rows or less.
+// LDS), 32 query rows per wave and 32 key rows per pair, two blocks per CU, in one launch (attn_bwd_small_kernel), for groups of a few thousand rows or less.
 // All are at the power cap.  LDS fragments read beside the products cost matrix time too: a loop of 16x16x32 products takes 7.2 ns each
 // at the top clock, and with a fragment read for every two 8.3 (row fragments) or 8.6 (transposing reads).
 #pragma once
@@ -23,97 +23,102 @@ __device__ __forceinline__ floatx4_t lds_read_f32x4(unsigned addr) {
   return *(const floatx4_t __attribute__((address_space(3)))*)(uintptr_t)addr;
 }
 
-// dQ kernel: P = exp2(s*c - lse2) and dS = P * dP' (dP' = dP - delta) for a lane's eight scores per query column (lse2 is a
-// per-lane scalar), dS packed to bf16.
-// `limit`: keys >= limit (relative to the step's first) get P = 0 (MASK only).
-template <bool MASK>
-__device__ __forceinline__ void softmax_bwd_cols(const StepScores& s, const StepScores& dp, const float (&lse2)[2],
-                                                 float c, int g, int limit, bf16x8_t (&dsf)[2]) {
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    unsigned int dd[4];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; i += 2) {
-        float pa = fast_exp2(fmaf(s[t][q][i], c, -lse2[q]));
-        float pb = fast_exp2(fmaf(s[t][q][i + 1], c, -lse2[q]));
-        if (MASK) {
-          const int idx = 8 * g + 4 * t + i;
-          if (idx >= limit) pa = 0.f;
-          if (idx + 1 >= limit) pb = 0.f;
-        }
-        dd[2 * t + (i >> 1)] = pack_bf16x2(pa * dp[t][q][i], pb * dp[t][q][i + 1]);
-      }
-    dsf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{dd[0], dd[1], dd[2], dd[3]});
-  }
-}
-
 // ---------------------------------------------------------------------------------------
 // dQ: query-stationary
 // ---------------------------------------------------------------------------------------
-struct DqLane {
-  unsigned k_nat;     // K rows, slot 0, half 0
-  unsigned v_nat;     // V rows
-  unsigned k_tr[2];   // K transposed
+// A step of 32 keys: for either 16-key operand t of it the scores and dP, then dQ over all 32 keys, the vector work of one among the products
+// of the next:
+//   S(0) | dP(0), P(0) | S(1), dS(0) | dP(1), P(1) | dS(1), dQ
+// Bound by energy at the power cap, as the forward is: with 48 rows per wave a fragment read from LDS feeds three products instead of two,
+// and the stream of K/V tiles is a third smaller.  48 rows leave 64 registers beside Q, dO and dQ^T.  What fits them: the scores and dP of 16
+// keys at a time instead of 64; delta subtracted from dP (an accumulator that starts from it takes four registers per
+// column, for good); one address for K and V, which lie side by side in a slot; the factor c in a scalar register; and only one fragment
+// read ahead where scores, P and dP are all there (with two the 96 registers of Q and dO are kept in memory and read in every tile).
+// Whole backward, 32 and 48 rows per wave: 99,840 x 40 heads, 16 groups 32.2 -> 31.3 ms, 62,400 x 12, 5 groups 11.70 -> 11.40, 32,760 x
+// 12, 8 groups 2.15 -> 2.12, 99,840 x 12, 99 groups 2.155 -> 2.08, 8,000 x 3, 1 group 0.296 -> 0.279 (with 256-row blocks too, to which the
+// order of the work is common).  Without priorities 1 to 4 % slower, with scheduling barriers that vector work does not cross 0 to 0.5 %.
+//
+// nat, tr: the lane's addresses in the tile's slot.  The 24 fragments are read across the step's end, into `ahead` for the next step; `mid` is
+// called before the first of those, and may move nat on to the next tile.
+constexpr int kDqWin = 2;   // fragments read ahead
+// the last fragment that is read before the products of fragment i
+constexpr int dq_read_up_to(int i, int nc) { return i + (nc > 2 && i >= 4 && i < 16 ? 1 : kDqWin); }
+template <int NC>
+struct DqRows {   // a wave's own operands
+  bf16x8_t qf[NC][4], dof[NC][4];
+  float lse2[NC], neg_dlt[NC];
 };
-
-// S^T = K Q^T and dP'^T = V dO^T - delta for one 32-key half of a tile
-template <int SOFF>
-__device__ __forceinline__ void dq_scores(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[2][4],
-                                          const bf16x8_t (&dof)[2][4], const floatx4_t (&neg_dlt)[2], StepScores& s,
-                                          StepScores& dp) {
+template <bool PRIO, int U, bool MASK, bool NEXT, int NC, typename F>
+__device__ __forceinline__ void dq_step(unsigned& nat, const unsigned (&tr)[2], const DqRows<NC>& w, floatx4_t (&dq)[8][NC],
+                                        bf16x8_t (&ahead)[kDqWin], float c, int g, int left, F&& mid) {
+  constexpr int kKeep = 0x2 | 0x4 | 0x400;   // what may cross: vector, scalar and transcendental instructions
+  bf16x8_t fr[24];   // K rows, V rows of operand 0 (ks), of operand 1, then K transposed (dt)
+  floatx4_t s[NC], dp[NC];
+  unsigned dd[NC][4];
+  auto load = [&](int f) {
+    if (f < 16) fr[f] = read_nat<64>(nat + ((f >> 2) & 1) * kPipeTileBytes + U * kRow32Bytes, f >> 3, f & 3);
+    else if (f < 24) fr[f] = read_tr<64>(tr, U * kRow32Bytes, f - 16);
+    else if (NEXT) ahead[f - 24] = read_nat<64>(nat + (U == 0 ? kRow32Bytes : 0), 0, f - 24);
+  };
+  auto load_at = [&](int i) {
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+    for (int f = dq_read_up_to(i - 1, NC) + 1; f <= dq_read_up_to(i, NC); ++f) load(f);
+  };
+  auto make_ds = [&](int t, int q) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      s[t][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-      dp[t][q] = neg_dlt[q];
+    for (int i = 0; i < 4; i += 2)
+      dd[q][2 * t + (i >> 1)] = pack_bf16x2(s[q][i] * (dp[q][i] + w.neg_dlt[q]), s[q][i + 1] * (dp[q][i + 1] + w.neg_dlt[q]));
+  };
+#pragma unroll
+  for (int f = 0; f < kDqWin; ++f) fr[f] = ahead[f];
+  wave_priority<PRIO, 1>();
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    floatx4_t sn[NC];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const int f = 8 * t + ks;
+      __builtin_amdgcn_sched_barrier(kKeep);
+      load_at(f);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) sn[q] = mfma16(fr[f], w.qf[q][ks], ks == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : sn[q]);
+      if (t == 1 && ks < NC) make_ds(0, ks);
     }
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks)
+    for (int q = 0; q < NC; ++q) s[q] = sn[q];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const bf16x8_t kf = read_nat<64>(ln.k_nat + off + SOFF, t, ks);
-      const bf16x8_t vf = read_nat<64>(ln.v_nat + off + SOFF, t, ks);
+    for (int ks = 0; ks < 4; ++ks) {
+      const int f = 8 * t + 4 + ks;
+      __builtin_amdgcn_sched_barrier(kKeep);
+      load_at(f);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        s[t][q] = mfma16(kf, qf[q][ks], s[t][q]);
-        dp[t][q] = mfma16(vf, dof[q][ks], dp[t][q]);
+      for (int q = 0; q < NC; ++q) dp[q] = mfma16(fr[f], w.dof[q][ks], ks == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : dp[q]);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        s[q][ks] = fast_exp2(fmaf(s[q][ks], c, -w.lse2[q]));
+        if (MASK && 32 * U + 8 * g + 4 * t + ks >= left) s[q][ks] = 0.f;
       }
     }
-}
-
-// dQ^T += K^T dS^T for one 32-key half
-template <int SOFF>
-__device__ __forceinline__ void dq_accumulate(const DqLane& ln, unsigned off, const bf16x8_t (&dsf)[2], floatx4_t (&dq)[8][2]) {
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) {
-    const bf16x8_t a = read_tr<64>(ln.k_tr, off + SOFF, dt);
-#pragma unroll
-    for (int q = 0; q < 2; ++q) dq[dt][q] = mfma16(a, dsf[q], dq[dt][q]);
   }
-}
-
-// One 64-key tile in four phases, so that the vector work of one half overlaps the matrix
-// work of the other: scores(A) | scores(B) + softmax(A) | dQ(A) + softmax(B) | dQ(B).
-template <bool PRIO, bool MASK, int SOFF>
-__device__ __forceinline__ void dq_tile(const DqLane& ln, unsigned off, const bf16x8_t (&qf)[2][4],
-                                        const bf16x8_t (&dof)[2][4], const float (&lse2)[2], const floatx4_t (&neg_dlt)[2],
-                                        floatx4_t (&dq)[8][2], float c, int g, int left) {
-  StepScores s_a, dp_a, s_b, dp_b;
-  bf16x8_t dsf_a[2], dsf_b[2];
-  wave_priority<PRIO, 1>();   // scores and softmax before the other wave's dQ products (the other way round: no gain)
-  dq_scores<SOFF>(ln, off, qf, dof, neg_dlt, s_a, dp_a);
-  __builtin_amdgcn_sched_barrier(0);
-  dq_scores<SOFF + kRow32Bytes>(ln, off, qf, dof, neg_dlt, s_b, dp_b);
-  softmax_bwd_cols<MASK>(s_a, dp_a, lse2, c, g, left, dsf_a);
   __builtin_amdgcn_sched_barrier(0);
   wave_priority<PRIO, 0>();
-  dq_accumulate<SOFF>(ln, off, dsf_a, dq);
-  softmax_bwd_cols<MASK>(s_b, dp_b, lse2, c, g, left - 32, dsf_b);
-  __builtin_amdgcn_sched_barrier(0);
-  dq_accumulate<SOFF + kRow32Bytes>(ln, off, dsf_b, dq);
+  bf16x8_t dsf[NC];
+  auto operand = [&](int q) {
+    make_ds(1, q);
+    dsf[q] = __builtin_bit_cast(bf16x8_t, uintx4_t{dd[q][0], dd[q][1], dd[q][2], dd[q][3]});
+  };
+  operand(0);
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) {
+    if (dt == 8 - kDqWin) mid();
+    __builtin_amdgcn_sched_barrier(kKeep);
+    load_at(16 + dt);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      dq[dt][q] = mfma16(fr[16 + dt], dsf[q], dq[dt][q]);
+      if (dt == 0 && q + 1 < NC) operand(q + 1);
+    }
+  }
 }
 
 // Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f: to `out` (sorted order, or token order in
@@ -164,11 +169,13 @@ __device__ __forceinline__ void store_zero_piece(float* rows) {
 // that two 4-wave blocks share a CU -- the variant for small groups).
 template <int NB, bool GATHER>
 struct DqLds {
-  __attribute__((aligned(1024))) unsigned short k[NB][64 * kHeadDim], v[NB][64 * kHeadDim];
+  __attribute__((aligned(1024))) unsigned short kv[NB][2][64 * kHeadDim];   // a tile of K, then of V: one address for both
   __attribute__((aligned(256))) int tok[GATHER ? 512 : 1];   // gather mode: tokens of eight tiles
 };
+constexpr int kDqSlotBytes = 2 * kPipeTileBytes;
 
-template <int NW, bool GATHER, int NB, bool SPLIT>
+// ROWS: query rows of a block, 48 or 32 per wave.
+template <int NW, bool GATHER, int NB, int ROWS, bool SPLIT>
 __device__ __forceinline__ void attn_bwd_dq_block(
     DqLds<NB, GATHER>& lds, int block, const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
@@ -177,12 +184,11 @@ __device__ __forceinline__ void attn_bwd_dq_block(
     const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm, float* __restrict__ part,
     unsigned short* __restrict__ d_q_tok) {
-  constexpr int BM = NW * 32;
   constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64>;
   constexpr int kAhead = NB - 2;   // tiles in flight beyond the one being waited for
 
   WorkTile sp;
-  if (!find_work<SPLIT>(cu_q, tile_start, M, H, BM, block, sp)) return;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, ROWS, block, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -190,105 +196,143 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   int n = cu_k[ti.group + 1] - gs;               // number of keys
   const bool piece = SPLIT && sp.splits > 1;
   if (piece) split_range(sp, gs, n);
+  gs = __builtin_amdgcn_readfirstlane(gs);
+  n = __builtin_amdgcn_readfirstlane(n);
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int q0w = q0 + wave * 32;   // first query row of this wave
   const int64_t head_off = (int64_t)head * Nq;
   const int64_t head_off_k = (int64_t)head * Nk;
-  const float c = scale * 1.4426950408889634f;
+  // In a scalar register; the builtin is dropped where the compiler knows that the value is uniform.  The waits are those between a vector
+  // instruction and a lane read of its result, and between a lane read and a vector instruction.
+  float c;
+  asm("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 2" : "=s"(c) : "v"(scale * 1.4426950408889634f));
 
-  float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 32 * wave) * kHeadDim : nullptr;
-  if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
-    if (piece) store_zero_piece<2>(piece_rows);
-    else store_zero_rows<GATHER, 2>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
-    return;
-  }
+  // A wave owns 16 NC query rows: three columns, or two where that is enough for the last tile of a group, which then takes
+  // two thirds of the time.
+  auto sweep = [&](auto columns) {
+    constexpr int NC = columns.value;
+    const int q0w = q0 + wave * 16 * NC;   // first query row of this wave
+    float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 16 * NC * wave) * kHeadDim : nullptr;
+    if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
+      if (piece) store_zero_piece<NC>(piece_rows);
+      else store_zero_rows<GATHER, NC>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
+      return;
+    }
 
-  bf16x8_t qf[2][4], dof[2][4];
-  load_columns<GATHER>(qf, qh, q0w, ge, head, head_off, H, perm);
-  load_columns<GATHER>(dof, d_oh, q0w, ge, head, head_off, H, perm);
-  float lq[2];
-  floatx4_t dl[2];   // -delta of a lane's two query columns: what a dP accumulator starts from
+    DqRows<NC> w;
+    load_columns<GATHER>(w.qf, qh, q0w, ge, head, head_off, H, perm);
+    load_columns<GATHER>(w.dof, d_oh, q0w, ge, head, head_off, H, perm);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int qrow = min(q0w + 16 * q + (lane & 15), ge - 1);
-    lq[q] = -neg_lse_over_scale[head_off + qrow] * c;   // lse * log2(e)
-    const float d = neg_delta[head_off + qrow];
-    dl[q] = floatx4_t{d, d, d, d};
-  }
+    for (int q = 0; q < NC; ++q) {
+      const int qrow = min(q0w + 16 * q + (lane & 15), ge - 1);
+      w.lse2[q] = -neg_lse_over_scale[head_off + qrow] * c;   // lse * log2(e)
+      w.neg_dlt[q] = neg_delta[head_off + qrow];
+    }
 
-  PipeDma dma;
-  dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
-  dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
-  dma_lanes<NW, 64>(dma, &lds.k[0][0], &lds.v[0][0], wave, lane);
-  dma.last_row = n - 1;
-  if constexpr (GATHER) {
-    dma.rows = uniform_ptr(perm + gs);
-    dma.tok_stride = (int64_t)H * kHeadDim * 2;
-    dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
-    pipe_issue_tokens(dma, 0);
-    pipe_issue_tokens(dma, 64);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-  }
+    PipeDma dma;
+    dma.kbase = uniform_ptr(GATHER ? kh + (int64_t)head * kHeadDim : kh + (head_off_k + gs) * kHeadDim);
+    dma.vbase = uniform_ptr(GATHER ? vh + (int64_t)head * kHeadDim : vh + (head_off_k + gs) * kHeadDim);
+    dma_lanes<NW, 64>(dma, &lds.kv[0][0][0], &lds.kv[0][1][0], wave, lane);
+    dma.last_row = n - 1;
+    if constexpr (GATHER) {
+      dma.rows = uniform_ptr(perm + gs);
+      dma.tok_stride = (int64_t)H * kHeadDim * 2;
+      dma.lds_tok = lds_addr_uniform(&lds.tok[0]);
+      pipe_issue_tokens(dma, 0);
+      pipe_issue_tokens(dma, 64);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    }
+    auto issue_tile = [&](int T) { pipe_issue<NW, 64, GATHER>(dma, 64 * T, (T & (NB - 1)) * kDqSlotBytes); };
 #pragma unroll
-  for (int t = 0; t <= kAhead; ++t) {
-    if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
-    pipe_issue<NW, 64, GATHER>(dma, 64 * t, t * kPipeTileBytes);
-  }
+    for (int t = 0; t <= kAhead; ++t) {
+      if (GATHER && t == 2) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2 * kDmaPerTile));   // its tokens
+      issue_tile(t);
+    }
 
-  DqLane ln;
-  ln.k_nat = nat_address(&lds.k[0][0], lane);
-  ln.v_nat = nat_address(&lds.v[0][0], lane);
-  tr_addresses(ln.k_tr, &lds.k[0][0], lane);
-  // All of the wave's own operands are here before the loop.  Otherwise the compiler, which sees the loads above and not the
-  // direct-to-LDS loads, waits for them at their first use, inside the loop: vmcnt(4) .. vmcnt(0) in every tile, that is for
-  // the tiles that were issued a moment ago.  With the accumulators of dP started from -delta (a subtraction less per score)
-  // the whole backward went from 13.58 to 13.17 ms at 62,400 x 12 heads, 5 groups, 591.3 to 583.3 at 580,320 x 40, 32 groups.
-  settle(qf);
-  settle(dof);
+    // All of the wave's own operands are here before the loop.  Otherwise the compiler, which sees the loads above and not the
+    // direct-to-LDS loads, waits for them at their first use, inside the loop: vmcnt(4) .. vmcnt(0) in every tile, that is for
+    // the tiles that were issued a moment ago.
+    settle(w.qf);
+    settle(w.dof);
 #pragma unroll
-  for (int q = 0; q < 2; ++q) asm volatile("" : "+v"(lq[q]), "+v"(dl[q]));
+    for (int q = 0; q < NC; ++q) asm volatile("" : "+v"(w.lse2[q]), "+v"(w.neg_dlt[q]));
 
-  floatx4_t dq[8][2];
+    floatx4_t dq[8][NC];
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) dq[dt][0] = dq[dt][1] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int dt = 0; dt < 8; ++dt)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) dq[dt][q] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
-  // tile T lives in ring slot T % 4; at the top of tile T the block waits for it, and refills the
-  // slot of tile T-1 (which every wave has left) with tile T+3
-  const int nfull = n >> 6;   // tiles whose 64 keys are all inside the group
-  // a wave whose query rows all lie past the end of the group only moves its share of the tiles
-  const bool active = q0w < ge;
-  int T = 0;
-#define MOGA_DQ_TILE(B)                                                                  \
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));                      \
-  __syncthreads();                                                                       \
-  pipe_issue<NW, 64, GATHER>(dma, 64 * (T + (B) + 1 + kAhead), (((B) + 1 + kAhead) & (NB - 1)) * kPipeTileBytes); \
-  if (active) dq_tile<NB == 4, false, ((B) & (NB - 1)) * kPipeTileBytes>(ln, 0, qf, dof, lq, dl, dq, c, lane >> 4, 64);
-  for (; T + 4 <= nfull; T += 4) {   // four tiles per iteration: every LDS offset is an immediate
-    MOGA_DQ_TILE(0)
-    MOGA_DQ_TILE(1)
-    MOGA_DQ_TILE(2)
-    MOGA_DQ_TILE(3)
-  }
-#undef MOGA_DQ_TILE
-  for (; T < nfull; ++T) {
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-    __syncthreads();
-    pipe_issue<NW, 64, GATHER>(dma, 64 * (T + 1 + kAhead), ((T + 1 + kAhead) & (NB - 1)) * kPipeTileBytes);
-    if (active) dq_tile<NB == 4, false, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, 64);
-  }
-  if (n & 63) {   // last, partial tile: masked keys contribute zero
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
-    __syncthreads();
-    if (active) dq_tile<NB == 4, true, 0>(ln, ((unsigned)T & (unsigned)(NB - 1)) * kPipeTileBytes, qf, dof, lq, dl, dq, c, lane >> 4, n - 64 * T);
-  }
+    const int g = lane >> 4, last = (n - 1) >> 6;   // the last tile
+    const bool active = q0w < ge;   // a wave whose query rows all lie past the end of the group only moves its share of the tiles
+    unsigned nat = nat_address(&lds.kv[0][0][0], lane), tr[2];   // in the slot of the tile
+    tr_addresses(tr, &lds.kv[0][0][0], lane);
+    bf16x8_t ahead[kDqWin];
+    auto first_fragments = [&]() {
+#pragma unroll
+      for (int f = 0; f < kDqWin; ++f) ahead[f] = read_nat<64>(nat, 0, f);
+    };
+    auto nothing = []() {};
+    // tile T lives in ring slot T % NB
+    if constexpr (NB == 4) {
+      // In tile T the block waits for tile T + 1 and refills the slot of tile T - 1, which every wave has left, with tile T + 3.
+      auto next_tile = [&](int T) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * (kAhead - 1)));
+        block_barrier();
+        issue_tile(T + 1 + kAhead);
+      };
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(kDmaPerTile * kAhead));
+      __syncthreads();
+      if (!active) {
+        for (int T = 0; T < last; ++T) next_tile(T);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        return;
+      }
+      first_fragments();
+      for (int T = 0; T < last; ++T) {
+        const unsigned by = (T & 3) == 3 ? -3u * kDqSlotBytes : kDqSlotBytes;
+        dq_step<NB == 4, 0, false, true>(nat, tr, w, dq, ahead, c, g, 64, nothing);
+        dq_step<NB == 4, 1, false, true>(nat, tr, w, dq, ahead, c, g, 64, [&]() {
+          next_tile(T);
+          nat = in_register(nat + by);
+        });
+        tr[0] = in_register(tr[0] + by);
+        tr[1] = in_register(tr[1] + by);
+      }
+    } else {
+      for (int T = 0; T < last; ++T) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        __syncthreads();
+        issue_tile(T + 1);
+        if (active) {
+          first_fragments();
+          dq_step<NB == 4, 0, false, true>(nat, tr, w, dq, ahead, c, g, 64, nothing);
+          dq_step<NB == 4, 1, false, false>(nat, tr, w, dq, ahead, c, g, 64, nothing);
+        }
+        const unsigned by = T & 1 ? -kDqSlotBytes : kDqSlotBytes;
+        nat = in_register(nat + by);
+        tr[0] = in_register(tr[0] + by);
+        tr[1] = in_register(tr[1] + by);
+      }
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      __syncthreads();
+      if (!active) return;
+      first_fragments();
+    }
+    // the last tile, possibly partial: masked keys contribute zero
+    const int left = n - 64 * last;
+    dq_step<NB == 4, 0, true, true>(nat, tr, w, dq, ahead, c, g, left, nothing);
+    if (left > 32) dq_step<NB == 4, 1, true, false>(nat, tr, w, dq, ahead, c, g, left, nothing);
 
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-  if (piece) store_gradient_piece(dq, piece_rows);
-  else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, d_q_tok, perm);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
+    if (piece) store_gradient_piece(dq, piece_rows);
+    else store_gradient<GATHER>(dq, scale, q0w, ge, head, head_off, H, d_qh, d_q_tok, perm);
+  };
+  if (ROWS > 32 * NW && ge - q0 > 32 * NW) sweep(std::integral_constant<int, ROWS / (16 * NW)>());
+  else sweep(std::integral_constant<int, 2>());
 }
 
-template <bool GATHER = false, bool SPLIT = false>
+template <int ROWS, bool GATHER = false, bool SPLIT = false>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dq_pipe_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
@@ -298,8 +342,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dq_pipe_kernel(
     unsigned short* __restrict__ d_qh, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_q_tok = nullptr) {
   __shared__ DqLds<4, GATHER> lds;
-  attn_bwd_dq_block<8, GATHER, 4, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
-                                         M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
+  attn_bwd_dq_block<8, GATHER, 4, ROWS, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
+                                               M, Nq, Nk, H, scale, d_qh, perm, part, d_q_tok);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -845,7 +889,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_kernel(
     DkdvLds<2, 2, 2, false> dkdv;
   } lds;
   if ((int)blockIdx.x < dq_blocks)
-    attn_bwd_dq_block<4, false, 2, false>(lds.dq, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, ts_q, M, Nq,
+    attn_bwd_dq_block<4, false, 2, 128, false>(lds.dq, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, ts_q, M, Nq,
                                           Nk, H, scale, d_qh, perm, nullptr, d_q_tok);
   else
     attn_bwd_dkdv_block<false, 2, 2, 2, false>(lds.dkdv, blockIdx.x - dq_blocks, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q,

@@ -259,6 +259,19 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
   return (N + rows_per_tile - 1) / rows_per_tile + M;
 }
 
+// Query rows of a block of the large forward and dQ kernels.  384 take 3 to 6 % less time per row (a fragment read from LDS feeds three products instead
+// of two), but where there are hardly more blocks than CUs, 256 may fill their last round so much better that the call is
+// faster: 16,384 rows x 4 heads, 2 groups 0.247 ms with 384 (176 blocks), 0.219 with 256 (256 blocks); 12,000 x 12, 3 groups 0.265 and
+// 0.260 (396 and 576 blocks; a split of the last round counted: 2 and 2.25 rounds); 20,000 x 12, 4 groups 0.511 and 0.517 (672 and 960: 3
+// and 4 rounds).  The host knows the mean group only, and takes it for all.
+inline int query_rows(int64_t Nq, int H, int M) {
+  auto eighths = [&](int64_t rows) {   // of a round, the last one split if half of it is free
+    const int64_t tiles = (((Nq + M - 1) / M + rows - 1) / rows) * M * H, left = tiles % kCus;
+    return rows * (8 * (tiles / kCus) + (left ? 8 / std::min<int64_t>(kMaxSplits, kCus / left) : 0));
+  };
+  return 5 * eighths(256) < 4 * eighths(384) ? 256 : 384;
+}
+
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
 // column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a
 // register-resident loop of random operands reaches 1.94-2.18 PFLOP/s (card to card) with this shape and 1.83-1.86 with 32x32x16

@@ -30,19 +30,6 @@ static int64_t small_group_rows(int64_t Nq, int H) {
   return quarters >= 64 ? 1152 : quarters >= 4 ? 2560 : quarters >= 2 ? 6144 : 5632;
 }
 
-// Query rows of a block of the large kernel.  384 take 3 to 6 % less time per row (a fragment read from LDS feeds three products instead
-// of two), but where there are hardly more blocks than CUs, 256 may fill their last round so much better that the call is
-// faster: 16,384 rows x 4 heads, 2 groups 0.247 ms with 384 (176 blocks), 0.219 with 256 (256 blocks); 12,000 x 12, 3 groups 0.265 and
-// 0.260 (396 and 576 blocks; a split of the last round counted: 2 and 2.25 rounds); 20,000 x 12, 4 groups 0.511 and 0.517 (672 and 960: 3
-// and 4 rounds).  The host knows the mean group only, and takes it for all.
-static int fwd_rows(int64_t Nq, int H, int M) {
-  auto eighths = [&](int64_t rows) {   // of a round, the last one split if half of it is free
-    const int64_t tiles = (((Nq + M - 1) / M + rows - 1) / rows) * M * H, left = tiles % kCus;
-    return rows * (8 * (tiles / kCus) + (left ? 8 / std::min<int64_t>(kMaxSplits, kCus / left) : 0));
-  };
-  return 5 * eighths(256) < 4 * eighths(384) ? 256 : 384;
-}
-
 }  // namespace moga
 
 using namespace moga;
@@ -64,7 +51,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
   const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
-  const int rows = fwd_rows(Nq, H, M), bm = dtype == MOGA_BF16 ? (small ? 128 : rows) : kF32Rows;
+  const int rows = query_rows(Nq, H, M), bm = dtype == MOGA_BF16 ? (small ? 128 : rows) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
   if (!grid_fits(blocks, dtype == MOGA_BF16 && !small ? 512 : 256)) return MOGA_ERR_UNSUPPORTED;
@@ -165,7 +152,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (N == 0) return MOGA_OK;
   if (!q || !k || !v || !perm || !gate || !cu_seqlens || !o || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(q) && aligned16(k) && aligned16(v) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
-  const int rows = fwd_rows(N, H, M);
+  const int rows = query_rows(N, H, M);
   const int64_t blocks = (max_tiles(N, M, rows) * H + 7) / 8 * 8;
   if (!grid_fits(blocks, 512)) return MOGA_ERR_UNSUPPORTED;
 #define MOGA_FWD(RR)                                                                                                             \
@@ -180,7 +167,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
 
 // True where the forward can split its last round.
 bool moga::fwd_splits(int64_t Nq, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, fwd_rows(Nq, H, M)) * H);
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }
