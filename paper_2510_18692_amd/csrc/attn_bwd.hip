@@ -128,17 +128,20 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
 }
 
 // Mean rows per group below which the small-group bf16 kernels run, by rounds of 256 blocks of 256 rows: their finer tiles win
-// where there are few.  Against the long-group kernels, groups of equal size: 0.1 rounds (7,800 x 1 head, 3,000 x 3) 24 % faster at
-// 1,950 rows, 37 % at 1,500; 0.4 (8,000 x 3) 14 % at 1,000; 0.5 (7,800 x 4) 1 % slower at 1,950; 0.7 rounds (12,000 x 4) 7 % faster at
-// 1,500, 1 and 7 % slower at 2,000 and 3,000; 0.9 rounds (15,000 x 4) 3.5 % faster at 1,000, 1 and 6 % slower at 1,500 and 2,143; 6
-// rounds (32,760 x 12) 2 % faster at 700, 1 % slower at 900; 61 rounds (99,840 x 40) 3 % faster at 400, 5 % slower at 520.
-// The host knows only the mean.  Below one round the largest of unequal groups decides, and the long-group kernels split its
-// sweep: Zipf(1.1) / Zipf(1.45) groups 3 % faster and 4 % slower at 5,000 x 1 head, 4 groups, 6 and 14 % slower at 7,800 x 1, 14 and 3 %
-// at 7,800 x 4, 6 % faster and 15 % slower at 8,000 x 3, 8 groups, 28 and 25 % faster at 3,000 x 3, 2 groups, 25 and 23 % at 7,000 x
-// 3, 4 groups.  A lower line would cost equal groups, what a balanced router makes, up to 60 %.
+// where there are few.  Time of the small kernels against the large ones', groups of equal / Zipf(1.1) sizes:
+//   rounds 0.15 (9,830 x 1 head)  1,350 rows -43 / -2 %, 2,900 -12 / +17 %;  0.40  2,200 -2 / -24, 2,900 +5 / -23
+//          0.60                   1,700 -5 / +4, 2,900 +4 / -19;             0.85  1,100 -6 / +9, 1,700 +4 / +4
+//          1.05                   1,250 -7 / +6, 2,000 +5 / -16;             1.2   750 -1 / -16, 1,100 +6 / -13
+//          1.3                    800 -21 / -13, 1,250 -2 / -5;              1.55  1,250 -6 / 0, 2,000 +3 / -13
+//          1.9                    1,250 0 / -3, 2,000 +6 / +2;               2.9   650 -11 / -4, 1,000 -4 / +8
+//          4    (6,550 x 40)      600 -6 / +5, 750 +7 / +2;                  5.7   650 -1 / +12, 800 +7 / +15
+//          7                      400 -3 / +10, 600 -1 / +12, 750 +6 / +14;  13    400 -1 / +15, 500 +4 / +17, 750 +10 / +20
+// The host knows only the mean.  A lower line below a round would cost equal groups, what a balanced router makes, up to 60 %.
 static int64_t small_group_rows(int64_t Nq, int H) {
-  const int64_t quarters = 4 * Nq * H / (256 * kCus);
-  return quarters >= 64 ? 500 : quarters >= 4 ? 860 : quarters >= 3 ? 1450 : 2000;
+  const int64_t rounds = 100 * Nq * H / (256 * kCus);   // in hundredths
+  if (rounds < 100) return rounds < 75 ? 2000 : 1450;
+  if (rounds < 200) return rounds >= 115 && rounds < 135 ? 860 : 1300;
+  return rounds < 350 ? 860 : rounds < 600 ? 650 : 400;
 }
 
 }  // namespace moga

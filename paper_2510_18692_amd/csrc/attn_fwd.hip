@@ -19,15 +19,20 @@
 
 namespace moga {
 
-// Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of the other one: it wins by
-// finer tiles where there are few.  Small against large kernel, groups of equal size / Zipf(1.45): 23 rounds (38,400 x 40 heads) 3 and
-// 6 % slower at 1,200 rows, 29 (48,000 x 40) 2 and 6 % at 1,500; 6 rounds (32,760 x 12), equal groups, 3 % faster at 1,560 and 2,340,
-// equal at 2,047, 1 % slower at 2,730; 0.5 rounds (11,400 x 3) equal and 22 % faster at 5,700, 0.7 (45,600 x 1) 8 % slower and 18 %
-// faster; 0.35 (22,800 x 1), where the other kernel splits all of its tiles, 4 and 32 % slower at 5,700, and at 2,000 to 4,500 (9,000 to
-// 12,000 x 3), equal groups, 10 % faster.
-static int64_t small_group_rows(int64_t Nq, int H) {
-  const int64_t quarters = 4 * Nq * H / (256 * kCus);
-  return quarters >= 64 ? 1152 : quarters >= 4 ? 2560 : quarters >= 2 ? 6144 : 5632;
+// Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of 256 rows.  The lines are where
+// groups of equal size take the same time by both, or lower or higher where groups of Zipf(1.1) sizes ask for it.  Time of the small kernel
+// against the large one's, equal / Zipf:
+//   rounds 0.10 (6,550 x 1 head)  1,250 rows -4 / +63 %, 2,000 +31 / +80 %;  0.15  1,350 -8 / +72, 2,200 +27 / +84, 5,200 +91 / +129
+//          0.22                   2,000 -11 / +60, 3,400 +20 / +76;          0.30  2,200 -8 / +57, 3,800 +13 / +69
+//          0.40                   5,200 -2 / +29, 7,000 +4 / +29;            0.60  2,900 -6 / -4, 5,200 +11 / +1
+//          0.85                   3,800 +1 / -18;                            1.7   2,200 -4 / +6, 3,800 +7 / -15
+//          4    (6,550 x 40)      900 -12 / -9, 1,350 +7 / +6;               5.7   1,250 -6 / +2, 2,600 +9 / +9
+//          7                      600 -6 / +3, 750 +6 / +1, 2,200 +10 / +8;  20    600 -8 / +7, 750 +6 / +7, 2,900 +6 / +6
+// Below three quarters of a round the large kernel needs room to split its tiles; without, the line is that of the kernels unsplit.
+static int64_t small_group_rows(int64_t Nq, int H, bool split) {
+  const int64_t rounds = 100 * Nq * H / (256 * kCus);   // in hundredths
+  if (split && rounds < 75) return rounds < 20 ? 1500 : rounds < 33 ? 2700 : rounds < 50 ? 5632 : 4500;
+  return rounds < 50 ? 5632 : rounds < 100 ? 6144 : rounds < 370 ? 2560 : rounds < 600 ? 1300 : 700;
 }
 
 }  // namespace moga
@@ -50,7 +55,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
                            const TokenRows& tok, void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
-  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
+  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H, split != nullptr));
   const int rows = query_rows(Nq, H, M), bm = dtype == MOGA_BF16 ? (small ? 128 : rows) : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
@@ -167,7 +172,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
 
 // True where the forward can split its last round.
 bool moga::fwd_splits(int64_t Nq, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) && split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H);
+  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H, true)) && split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }

@@ -1,6 +1,6 @@
 // bf16 forward kernel of the group attention for SMALL groups (head_dim 128): the static groups of
-// Section 3.2 have a few hundred to a few thousand rows, where the 256-row, 8-wave kernel of
-// attn_pipe.h wastes most of its last query tile and its three-tile prologue is not amortised.
+// Section 3.2 have a few hundred to a few thousand rows, where the 8-wave kernel of attn_pipe.h, in a call of few
+// rounds, leaves CUs idle with its 384- or 256-row tiles and its three-tile prologue is not amortised.
 //
 // Same step (pipe_step) and operand layouts, but a block is 4 waves x 32 query rows (128-row
 // tiles) and streams K/V in tiles of 32 keys through a ring of four 8 KB + 8 KB slots: 64 KB of
