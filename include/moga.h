@@ -231,6 +231,12 @@ void moga_debug_set_spin_limit(int polls);
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.
  */
 void moga_debug_set_small_group_rows(int64_t rows);
+/*
+ * The blocks that a BF16 attention call of these sizes (M >= 1) takes with ws_bytes of workspace: blocks = {query rows, 1 if its last
+ * round of them is split, key rows, 1 if theirs is}, key rows 0 for a forward.  The moga_fused_* calls: thresholds overridden by 0, and
+ * moga_workspace_bytes.  For tests.  Host-only.
+ */
+void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]);
 
 /* Backward of the gather in moga_permute: d_q[perm[j]][h][:] = d_qh[h][j][:] (same for k, v). */
 int moga_permute_bwd(const void* d_qh, const void* d_kh, const void* d_vh, int dtype,

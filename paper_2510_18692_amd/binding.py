@@ -51,6 +51,7 @@ _SIGNATURES = {
     "moga_attn_bwd_status_offset": (_sz, [_i64, _i32]),
     "moga_debug_set_spin_limit": (None, [_i32]),
     "moga_debug_set_small_group_rows": (None, [_i64]),
+    "moga_debug_attn_blocks": (None, [_i32, _i64, _i64, _i32, _i32, _sz, _vp]),
     "moga_permute_bwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp]),
     "moga_route_bwd": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp,
                               _sz, _vp]),
@@ -240,6 +241,13 @@ def attn_bwd_status(ws, Nq, H):
 def set_small_group_rows(rows: int) -> None:
     """Mean group size below which the bf16 attention calls use their small-group kernels (< 0: defaults)."""
     load().moga_debug_set_small_group_rows(int(rows))
+
+
+def attn_blocks(op, Nq, Nk, H, M, ws_bytes):
+    """(query rows, their last round is split, key rows, theirs is split) of the bf16 attention call's blocks; key rows 0: a forward."""
+    out = (ctypes.c_int * 4)()
+    load().moga_debug_attn_blocks(op, Nq, Nk, H, M, ws_bytes, out)
+    return out[0], bool(out[1]), out[2], bool(out[3])
 
 
 def set_spin_limit(polls: int) -> None:

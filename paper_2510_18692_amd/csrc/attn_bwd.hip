@@ -144,6 +144,11 @@ static int64_t small_group_rows(int64_t Nq, int H) {
   return rounds < 350 ? 860 : rounds < 600 ? 650 : 400;
 }
 
+AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room) {
+  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H))) return {true, {128, false}, {64, false}};
+  return {false, query_blocks(Nq, Nk, H, M, room), {kDkdvRows, room && split_pays(max_tiles(Nk, M, kDkdvRows) * H)}};
+}
+
 }  // namespace moga
 
 using namespace moga;
@@ -155,11 +160,6 @@ static size_t bwd_rows_bytes(int64_t Nq, int H) { return round_up(2 * (size_t)Nq
 extern "C" size_t moga_attn_bwd_status_offset(int64_t Nq, int H) {
   if (Nq <= 0 || H < 1) return 0;
   return bwd_rows_bytes(Nq, H);
-}
-
-bool moga::bwd_splits(int64_t Nq, int64_t Nk, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H)) &&
-         (split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H) || split_pays(max_tiles(Nk, M, kDkdvRows) * H));
 }
 
 extern "C" size_t moga_attn_bwd_ws_bytes(int64_t N, int H, int D, int dtype) {
@@ -200,8 +200,9 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
-    const bool small = use_small_group_kernels(Nq, M, small_group_rows(Nq, H));
-    const int rows_q = query_rows(Nq, H, M), bk = small ? 64 : kDkdvRows, bm = small ? 128 : rows_q;
+    const AttnPlan plan = bwd_plan(Nq, Nk, H, M, split != nullptr);
+    const bool small = plan.small;
+    const int bk = plan.k.rows, bm = plan.q.rows;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
     const int64_t k_blocks = (k_tiles * H + 7) / 8 * 8, q_blocks = (q_tiles * H + 7) / 8 * 8;
     if (!grid_fits(std::max(k_blocks, q_blocks), small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
@@ -225,7 +226,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
       return launch_status();
     }
     if (Nk > 0) {
-      if (split && split_pays(k_tiles * H)) {
+      if (plan.k.split) {
         attn_bwd_dkdv_ab_kernel<false, true><<<(unsigned)(k_blocks + kCus), 512, 0, st>>>(
             (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
             delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
@@ -238,19 +239,19 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
             (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
             (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
     }
-    const bool split_q = split && split_pays(q_tiles * H);
+    const bool split_q = plan.q.split;
 #define MOGA_BWD_DQ(RR, SPLIT)                                                                                                  \
   attn_bwd_dq_pipe_kernel<RR, false, SPLIT><<<(unsigned)(q_blocks + (SPLIT ? kCus : 0)), 512, 0, st>>>(                        \
       (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta, \
       cu_q, cu_k, SPLIT ? nullptr : ts_q, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm,                         \
       SPLIT ? split_ws(split).part : nullptr, d_q_tok)
-    if (split_q && rows_q == 384) MOGA_BWD_DQ(384, true);
+    if (split_q && bm == 384) MOGA_BWD_DQ(384, true);
     else if (split_q) MOGA_BWD_DQ(256, true);
-    else if (rows_q == 384) MOGA_BWD_DQ(384, false);
+    else if (bm == 384) MOGA_BWD_DQ(384, false);
     else MOGA_BWD_DQ(256, false);
 #undef MOGA_BWD_DQ
     if (split_q)
-      split_sum_kernel<<<dim3(kCus / 2, rows_q / 8), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, rows_q, softmax_scale, 0.f,
+      split_sum_kernel<<<dim3(kCus / 2, bm / 8), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, bm, softmax_scale, 0.f,
                                                                    (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
   } else {
     const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
@@ -411,7 +412,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
-  const int rows_q = query_rows(N, H, M);
+  const int rows_q = query_blocks(N, N, H, M, false).rows;
   hipStream_t st = (hipStream_t)stream;
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
@@ -440,6 +441,13 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
   if (dtype != MOGA_BF16 || D != 128 || N <= 0 || Nk <= 0 || H < 1 || M < 1) return need;
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD;
-  const bool splits = (fwd && fwd_splits(N, H, M)) || (bwd && bwd_splits(N, Nk, H, M));
-  return splits ? round_up(need, 256) + 256 + kSplitBytes : need;
+  const AttnPlan plan = M > MOGA_MAX_GROUPS ? AttnPlan{} : fwd ? fwd_plan(N, Nk, H, M, true) : bwd ? bwd_plan(N, Nk, H, M, true) : AttnPlan{};
+  return plan.q.split || plan.k.split ? round_up(need, 256) + 256 + kSplitBytes : need;
+}
+
+extern "C" void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]) {
+  const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
+  const bool room = M <= MOGA_MAX_GROUPS && split_region((void*)256, moga_workspace_bytes(op, Nq, H, 128, M, 0, MOGA_BF16), ws_bytes);
+  const AttnPlan p = fwd ? fwd_plan(Nq, Nk, H, M, room) : bwd_plan(Nq, Nk, H, M, room);
+  blocks[0] = p.q.rows, blocks[1] = p.q.split, blocks[2] = p.k.rows, blocks[3] = p.k.split;
 }

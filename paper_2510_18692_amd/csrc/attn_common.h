@@ -1,6 +1,8 @@
 // Pieces shared by the forward and backward group-attention kernels.
 #pragma once
 
+#include <algorithm>
+
 #include "lds_pipe.h"
 
 namespace moga {
@@ -182,8 +184,6 @@ inline void* split_region(void* ws, size_t used, size_t ws_bytes) {
   const size_t off = round_up((size_t)(uintptr_t)ws + used, 256) - (size_t)(uintptr_t)ws;
   return ws_bytes >= off + kSplitBytes ? (char*)ws + off : nullptr;
 }
-bool fwd_splits(int64_t Nq, int H, int M);
-bool bwd_splits(int64_t Nq, int64_t Nk, int H, int M);
 inline SplitWs split_ws(void* ws) {
   return {(float*)ws, (float*)ws + kCus * kSplitRows * kHeadDim};
 }
@@ -259,18 +259,41 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
   return (N + rows_per_tile - 1) / rows_per_tile + M;
 }
 
-// Query rows of a block of the large forward and dQ kernels.  384 take 3 to 6 % less time per row (a fragment read from LDS feeds three products instead
-// of two), but where there are hardly more blocks than CUs, 256 may fill their last round so much better that the call is
-// faster: 16,384 rows x 4 heads, 2 groups 0.247 ms with 384 (176 blocks), 0.219 with 256 (256 blocks); 12,000 x 12, 3 groups 0.265 and
-// 0.260 (396 and 576 blocks; a split of the last round counted: 2 and 2.25 rounds); 20,000 x 12, 4 groups 0.511 and 0.517 (672 and 960: 3
-// and 4 rounds).  The host knows the mean group only, and takes it for all.
-inline int query_rows(int64_t Nq, int H, int M) {
-  auto eighths = [&](int64_t rows) {   // of a round, the last one split if half of it is free
-    const int64_t tiles = (((Nq + M - 1) / M + rows - 1) / rows) * M * H, left = tiles % kCus;
-    return rows * (8 * (tiles / kCus) + (left ? 8 / std::min<int64_t>(kMaxSplits, kCus / left) : 0));
+// Rows of a block of the large kernels (forward and dQ: 256 or 384 query rows), and whether the call splits its last round.  Per
+// row 384 take less time (a fragment read from LDS feeds three products instead of two, the stream of the other side is shared by more),
+// but alone on its CU a block of 384 takes 1.3 times as long as one of 256: a call of less than a round that does not split takes that much
+// longer.  So the rounds are priced: for every row of the other side a step, kStartRows of them for a block's start and end (prologue, row
+// fragments, stores), the last round by its pieces if it is split, which costs kMergeRows more.  Constants from 114 calls of equal
+// groups, 0.07 to 9.8 rounds of 256 blocks, groups of 700 to 20,000 rows, either size of block forced: the choice is the faster one or within
+// (mean / worst) 0.4 / 8 % forward, 0.2 / 3 % backward in calls that do not split, 0.2 / 9 and 0.1 / 4 % in those that do.  The host knows the
+// mean group only and takes it for all; 172 calls of Zipf(1.1) groups, where the largest decides: 4 % on average without a split, 5 with
+// (256 always 3 and 5, 384 always 17 and 8).  Milliseconds with 256 and 384 rows, forward without a split: 5,000 x 3 heads, 5 groups 0.029 and
+// 0.039; 7,000 x 4, 2 groups 0.081 and 0.111; 40,000 x 3, 4 groups 0.52 and 0.65; 99,840 x 12, 16 groups 3.33 and 3.09.
+struct Blocks {
+  int rows;
+  bool split;
+};
+inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) {
+  constexpr int64_t kStartRows = 640, kMergeRows = 1000;
+  const int64_t mean = (Nq + M - 1) / M, swept = (Nk + M - 1) / M;
+  auto splits = [&](int rows) { return room && split_pays(max_tiles(Nq, M, rows) * H); };
+  auto cost = [&](int rows, int64_t weight) {
+    const int64_t tiles = (mean + rows - 1) / rows * M * H, left = tiles % kCus;
+    const int64_t pieces = left > 0 && splits(rows) ? std::min<int64_t>(kMaxSplits, kCus / left) : 1;
+    return weight * (tiles / kCus * (swept + kStartRows) + (left > 0 ? swept / pieces + kStartRows : 0)) + (pieces > 1 ? 10 * kMergeRows : 0);
   };
-  return 5 * eighths(256) < 4 * eighths(384) ? 256 : 384;
+  const int rows = cost(256, 10) < cost(384, 13) ? 256 : 384;
+  return {rows, splits(rows)};
 }
+
+// What a bf16 call runs: the kernels for small groups, or the large ones and their blocks of queries (and of keys, backward).  room:
+// the last round can be split (M <= MOGA_MAX_GROUPS and a workspace with kSplitBytes).
+struct AttnPlan {
+  bool small;
+  Blocks q, k;
+};
+AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room);
+AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room);
 
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
 // column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a

@@ -35,6 +35,11 @@ static int64_t small_group_rows(int64_t Nq, int H, bool split) {
   return rounds < 50 ? 5632 : rounds < 100 ? 6144 : rounds < 370 ? 2560 : rounds < 600 ? 1300 : 700;
 }
 
+AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room) {
+  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H, room))) return {true, {128, false}, {}};
+  return {false, query_blocks(Nq, Nk, H, M, room), {}};
+}
+
 }  // namespace moga
 
 using namespace moga;
@@ -55,8 +60,9 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
                            const TokenRows& tok, void* split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
-  const bool small = dtype == MOGA_BF16 && use_small_group_kernels(Nq, M, small_group_rows(Nq, H, split != nullptr));
-  const int rows = query_rows(Nq, H, M), bm = dtype == MOGA_BF16 ? (small ? 128 : rows) : kF32Rows;
+  const AttnPlan plan = dtype == MOGA_BF16 ? fwd_plan(Nq, Nk, H, M, split != nullptr) : AttnPlan{};
+  const bool small = plan.small;
+  const int rows = plan.q.rows, bm = dtype == MOGA_BF16 ? rows : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
   const int64_t blocks = dtype == MOGA_BF16 ? (tiles * H + 7) / 8 * 8 : tiles * H;
   if (!grid_fits(blocks, dtype == MOGA_BF16 && !small ? 512 : 256)) return MOGA_ERR_UNSUPPORTED;
@@ -73,7 +79,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, (unsigned short*)tok.o);
-  } else if (split && split_pays(tiles * H)) {
+  } else if (plan.q.split) {
     const SplitWs sw = split_ws(split);
 #define MOGA_FWD_SPLIT(RR)                                                                                                     \
   attn_fwd_bf16_pipe_kernel<RR, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(                                       \
@@ -157,7 +163,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (N == 0) return MOGA_OK;
   if (!q || !k || !v || !perm || !gate || !cu_seqlens || !o || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(q) && aligned16(k) && aligned16(v) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
-  const int rows = query_rows(N, H, M);
+  const int rows = query_blocks(N, N, H, M, false).rows;
   const int64_t blocks = (max_tiles(N, M, rows) * H + 7) / 8 * 8;
   if (!grid_fits(blocks, 512)) return MOGA_ERR_UNSUPPORTED;
 #define MOGA_FWD(RR)                                                                                                             \
@@ -168,11 +174,6 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   else MOGA_FWD(256);
 #undef MOGA_FWD
   return launch_status();
-}
-
-// True where the forward can split its last round.
-bool moga::fwd_splits(int64_t Nq, int H, int M) {
-  return M <= MOGA_MAX_GROUPS && !use_small_group_kernels(Nq, M, small_group_rows(Nq, H, true)) && split_pays(max_tiles(Nq, M, query_rows(Nq, H, M)) * H);
 }
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }

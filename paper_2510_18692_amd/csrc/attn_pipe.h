@@ -465,7 +465,7 @@ __device__ __forceinline__ void pipe_issue(const PipeDma& d, int kv0, unsigned b
 // permutation of Alg. 1 is applied while loading, nothing is materialised) and the output row is
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
 // SPLIT: the last round is cut into pieces (find_work).
-// ROWS: query rows of a block, 384 or 256 (query_rows chooses).
+// ROWS: query rows of a block, 384 or 256 (query_blocks chooses).
 template <int ROWS, bool GATHER = false, bool SPLIT = false>
 __global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
     const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
