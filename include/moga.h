@@ -221,7 +221,7 @@ void moga_debug_set_spin_limit(int polls);
 
 /*
  * The BF16 attention calls have two sets of kernels: 8-wave blocks with 384- or 256-row (forward, dQ) or
- * 192-row (dK/dV) tiles, and 4-wave blocks with 128-row (forward, dQ) or 64-row tiles, two blocks per CU, for the small
+ * 192- or 128-row (dK/dV) tiles, and 4-wave blocks with 128-row (forward, dQ) or 64-row tiles, two blocks per CU, for the small
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
  * group size N / M and the rounds of 256 256-row tiles (forward: below 5632 rows up to half a round, 6144 up to one, 2560 up to 3.7, 1300 up
  * to 6, else 700, and with room to split a round 1500 up to 0.2, 2700 up to 0.33, 4500 from 0.5 to 0.75; backward: below 2000 up to 0.75

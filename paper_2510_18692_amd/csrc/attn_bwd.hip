@@ -7,9 +7,9 @@
 // to split the last round:
 //   attn_bwd_delta   : -delta[h][j] = -sum_c dO[h][j][c] * O[h][j][c], and in bf16 -lse / scale; the calls that
 //                      write dO themselves (_tokens) or are given these constants (_rows) do without it;
-//   attn_bwd_dkdv_ab : a pair of waves owns 48 key rows and sweeps the query tiles of its group, one wave with
+//   attn_bwd_dkdv_ab : a pair of waves owns 48 (or 32) key rows and sweeps the query tiles of its group, one wave with
 //                      the K fragments and the dV^T accumulators, the other with the V fragments and dK^T;
-//   attn_bwd_dq_pipe : a wave owns 48 query rows and sweeps the key tiles (mirror of forward);
+//   attn_bwd_dq_pipe : a wave owns 48 (or 32) query rows and sweeps the key tiles (mirror of forward);
 //   attn_bwd_small   : both with smaller tiles in one launch, for small groups.
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
@@ -146,7 +146,7 @@ static int64_t small_group_rows(int64_t Nq, int H) {
 
 AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room) {
   if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H))) return {true, {128, false}, {64, false}};
-  return {false, query_blocks(Nq, Nk, H, M, room), {kDkdvRows, room && split_pays(max_tiles(Nk, M, kDkdvRows) * H)}};
+  return {false, query_blocks(Nq, Nk, H, M, room), key_blocks(Nq, Nk, H, M, room)};
 }
 
 }  // namespace moga
@@ -226,18 +226,20 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
       return launch_status();
     }
     if (Nk > 0) {
-      if (plan.k.split) {
-        attn_bwd_dkdv_ab_kernel<false, true><<<(unsigned)(k_blocks + kCus), 512, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2,
-            delta, cu_q, cu_k, nullptr, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,
-            g_spin_limit.load(), status, tok.perm, split_ws(split).part, d_k_tok, d_v_tok);
-        split_sum_kernel<<<dim3(kCus / 2, 2 * kDkdvRows / 8), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, kDkdvRows, 1.f, softmax_scale,
-                                                            (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
-      } else
-        attn_bwd_dkdv_ab_kernel<<<(unsigned)k_blocks, 512, 0, st>>>(
-            (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh,
-            (const unsigned short*)vh, lse2, delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, softmax_scale,
-            (unsigned short*)d_kh, (unsigned short*)d_vh, g_spin_limit.load(), status, tok.perm, nullptr, d_k_tok, d_v_tok);
+      const bool split_k = plan.k.split;
+#define MOGA_BWD_DKDV(KK, SPLIT)                                                                                               \
+  attn_bwd_dkdv_ab_kernel<KK, false, SPLIT><<<(unsigned)(k_blocks + (SPLIT ? kCus : 0)), 512, 0, st>>>(                        \
+      (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta, \
+      cu_q, cu_k, SPLIT ? nullptr : ts_k, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,            \
+      g_spin_limit.load(), status, tok.perm, SPLIT ? split_ws(split).part : nullptr, d_k_tok, d_v_tok)
+      if (split_k && bk == 192) MOGA_BWD_DKDV(192, true);
+      else if (split_k) MOGA_BWD_DKDV(128, true);
+      else if (bk == 192) MOGA_BWD_DKDV(192, false);
+      else MOGA_BWD_DKDV(128, false);
+#undef MOGA_BWD_DKDV
+      if (split_k)
+        split_sum_kernel<<<dim3(kCus / 2, 2 * bk / 8), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, bk, 1.f, softmax_scale,
+                                                                     (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
     }
     const bool split_q = plan.q.split;
 #define MOGA_BWD_DQ(RR, SPLIT)                                                                                                  \
@@ -412,20 +414,24 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
-  const int rows_q = query_blocks(N, N, H, M, false).rows;
+  const int rows_q = query_blocks(N, N, H, M, false).rows, keys = key_blocks(N, N, H, M, false).rows;
   hipStream_t st = (hipStream_t)stream;
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
-  const int64_t k_blocks = (max_tiles(N, M, kDkdvRows) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, rows_q) * H + 7) / 8 * 8;
+  const int64_t k_blocks = (max_tiles(N, M, keys) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, rows_q) * H + 7) / 8 * 8;
   if (!grid_fits(k_blocks, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + 15) / 16), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate,
       status);
-  attn_bwd_dkdv_ab_kernel<true><<<(unsigned)k_blocks, 512, 0, st>>>(
-      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v,
-      lse2, delta, cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k,
-      (unsigned short*)d_v, g_spin_limit.load(), status, perm);
+#define MOGA_BWD_DKDV(KK)                                                                                                   \
+  attn_bwd_dkdv_ab_kernel<KK, true><<<(unsigned)k_blocks, 512, 0, st>>>(                                                    \
+      (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
+      cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k, (unsigned short*)d_v,               \
+      g_spin_limit.load(), status, perm)
+  if (keys == 192) MOGA_BWD_DKDV(192);
+  else MOGA_BWD_DKDV(128);
+#undef MOGA_BWD_DKDV
 #define MOGA_BWD_DQ(RR)                                                                                                     \
   attn_bwd_dq_pipe_kernel<RR, true><<<(unsigned)q_blocks, 512, 0, st>>>(                                                    \
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \

@@ -652,9 +652,9 @@ struct AbTile {
   }
 };
 
-constexpr int kDkdvRows = 192;   // keys of a block of the large kernel: 4 pairs of waves, 48 keys each
-// NPAIR: wave pairs per block (4: 128 keys, partners on one SIMD; 2: 64 keys, for small groups).
+// NPAIR: wave pairs per block (4: partners on one SIMD; 2: for small groups).
 // NB: ring slots of 64 queries (4 or 2, as in the dQ kernel).
+// NC: columns of 16 keys per pair, at most.
 template <int NPAIR, int NB, int NC, bool GATHER>
 struct DkdvLds {
   __attribute__((aligned(1024))) unsigned short q[NB][64 * kHeadDim], d_o[NB][64 * kHeadDim];
@@ -857,7 +857,8 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
   else sweep(std::integral_constant<int, 2>());
 }
 
-template <bool GATHER = false, bool SPLIT = false>
+// KEYS: keys of a block, 192 or 128 (key_blocks chooses): 48 or 32 for each of its four pairs of waves.
+template <int KEYS, bool GATHER = false, bool SPLIT = false>
 __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_ab_kernel(
     const unsigned short* __restrict__ d_oh, const unsigned short* __restrict__ qh,
     const unsigned short* __restrict__ kh, const unsigned short* __restrict__ vh,
@@ -868,9 +869,9 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_dkdv_ab_kernel(
     int spin_limit, int* __restrict__ status, const int32_t* __restrict__ perm = nullptr,
     float* __restrict__ part = nullptr, unsigned short* __restrict__ d_k_tok = nullptr,
     unsigned short* __restrict__ d_v_tok = nullptr) {
-  __shared__ DkdvLds<4, 4, 3, GATHER> lds;
-  attn_bwd_dkdv_block<GATHER, 4, 4, 3, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k, tile_start,
-                                           M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok, d_v_tok);
+  __shared__ DkdvLds<4, 4, KEYS / 64, GATHER> lds;
+  attn_bwd_dkdv_block<GATHER, 4, 4, KEYS / 64, SPLIT>(lds, blockIdx.x, d_oh, qh, kh, vh, neg_lse_over_scale, neg_delta, cu_q, cu_k,
+                                           tile_start, M, Nq, Nk, H, scale, d_kh, d_vh, spin_limit, status, perm, part, d_k_tok, d_v_tok);
 }
 
 // Both for small groups, in one launch: blocks below `dq_blocks` (a multiple of 8, for the XCDs) are dQ's, the others dK/dV's.

@@ -259,32 +259,35 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
   return (N + rows_per_tile - 1) / rows_per_tile + M;
 }
 
-// Rows of a block of the large kernels (forward and dQ: 256 or 384 query rows), and whether the call splits its last round.  Per
-// row 384 take less time (a fragment read from LDS feeds three products instead of two, the stream of the other side is shared by more),
-// but alone on its CU a block of 384 takes 1.3 times as long as one of 256: a call of less than a round that does not split takes that much
-// longer.  So the rounds are priced: for every row of the other side a step, kStartRows of them for a block's start and end (prologue, row
+// Rows of a block of the large kernels (forward and dQ: 256 or 384 query rows; dK/dV: 128 or 192 keys), and whether the call splits its
+// last round.  Per row the longer blocks take less time (a fragment read from LDS feeds three products instead of two, the stream of the
+// other side is shared by more), but alone on its CU one takes 1.3 times as long as a short one: a call of less than a round that does not
+// split takes that much longer.  So the rounds are priced: for every row of the other side a step, kStartRows of them for a block's start and end (prologue, row
 // fragments, stores), the last round by its pieces if it is split, which costs kMergeRows more.  Constants from 114 calls of equal
 // groups, 0.07 to 9.8 rounds of 256 blocks, groups of 700 to 20,000 rows, either size of block forced: the choice is the faster one or within
-// (mean / worst) 0.4 / 8 % forward, 0.2 / 3 % backward in calls that do not split, 0.2 / 9 and 0.1 / 4 % in those that do.  The host knows the
-// mean group only and takes it for all; 172 calls of Zipf(1.1) groups, where the largest decides: 4 % on average without a split, 5 with
+// (mean / worst) 0.4 / 8 % forward, 0.2 / 3 % by dQ, 0.1 / 2 % by dK/dV in calls that do not split, 0.2 / 9, 0.1 / 4 and 0.1 / 3 % in those that do.  The host knows the
+// mean group only and takes it for all; 172 calls of Zipf(1.1) groups, where the largest decides: forward 4 % on average without a split, 5 with
 // (256 always 3 and 5, 384 always 17 and 8).  Milliseconds with 256 and 384 rows, forward without a split: 5,000 x 3 heads, 5 groups 0.029 and
 // 0.039; 7,000 x 4, 2 groups 0.081 and 0.111; 40,000 x 3, 4 groups 0.52 and 0.65; 99,840 x 12, 16 groups 3.33 and 3.09.
 struct Blocks {
   int rows;
   bool split;
 };
-inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) {
+// N: rows of this side, in blocks of `few` or 3/2 of that; other: rows of the side that they sweep.
+inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, bool room) {
   constexpr int64_t kStartRows = 640, kMergeRows = 1000;
-  const int64_t mean = (Nq + M - 1) / M, swept = (Nk + M - 1) / M;
-  auto splits = [&](int rows) { return room && split_pays(max_tiles(Nq, M, rows) * H); };
+  const int64_t mean = (N + M - 1) / M, swept = (other + M - 1) / M;
+  auto splits = [&](int rows) { return room && split_pays(max_tiles(N, M, rows) * H); };
   auto cost = [&](int rows, int64_t weight) {
     const int64_t tiles = (mean + rows - 1) / rows * M * H, left = tiles % kCus;
     const int64_t pieces = left > 0 && splits(rows) ? std::min<int64_t>(kMaxSplits, kCus / left) : 1;
     return weight * (tiles / kCus * (swept + kStartRows) + (left > 0 ? swept / pieces + kStartRows : 0)) + (pieces > 1 ? 10 * kMergeRows : 0);
   };
-  const int rows = cost(256, 10) < cost(384, 13) ? 256 : 384;
+  const int rows = cost(few, 10) < cost(few / 2 * 3, 13) ? few : few / 2 * 3;
   return {rows, splits(rows)};
 }
+inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) { return large_blocks(Nq, Nk, H, M, 256, room); }
+inline Blocks key_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) { return large_blocks(Nk, Nq, H, M, 128, room); }
 
 // What a bf16 call runs: the kernels for small groups, or the large ones and their blocks of queries (and of keys, backward).  room:
 // the last round can be split (M <= MOGA_MAX_GROUPS and a workspace with kSplitBytes).

@@ -26,6 +26,15 @@ def test_query_rows_of_calls_that_cannot_split(large_kernels, N, H, M, rows):
         assert blocks(op, N, H, M, need)[:2] == (rows, False)
 
 
+@pytest.mark.parametrize("N,H,M,rows", [
+    (5000, 3, 5, 128), (7000, 4, 2, 128), (4680, 12, 3, 128), (16384, 4, 2, 128), (8000, 3, 1, 128), (28000, 1, 7, 128),
+    (12000, 12, 3, 192), (62400, 12, 5, 192), (99840, 40, 16, 192),
+])
+def test_key_rows_of_calls_that_cannot_split(large_kernels, N, H, M, rows):
+    need = mg.workspace_bytes(mg.OP_ATTN_BWD, N, H, 128, M, 0, mg.MOGA_BF16)
+    assert blocks(mg.OP_ATTN_BWD, N, H, M, need)[2:] == (rows, False)
+
+
 def test_more_groups_than_a_block_looks_up_never_split(large_kernels):
     for op in (mg.OP_VARLEN_ATTN_FWD, mg.OP_VARLEN_ATTN_BWD):
         q, q_split, k, k_split = blocks(op, 300 * 700, 3, 300, 1 << 40)

@@ -1,8 +1,12 @@
 """The large bf16 kernels at the edges of their tiles: last tiles of a group that take three columns of 16 rows per wave, two, or
 leave waves idle, with either number of query rows per block, against the oracle with the tolerances of the other bf16 cases."""
+import numpy as np
 import pytest
+import torch
 
+from oracle import moga_oracle as orc
 from paper_2510_18692_amd import binding as mg
+from tests import parity as P
 from tests import test_gpu_backward as tb
 from tests import test_gpu_forward as tf
 
@@ -29,3 +33,64 @@ def test_backward_at_tile_edges(more):
         tb.test_group_attention_backward_matches_oracle(SIZES + more, 2, 128, "bf16")
     finally:
         mg.set_small_group_rows(-1)
+
+
+def backward_at_edges(sizes, H, room):
+    """(dQ, dK, dV) and the oracle's, through the C entry with the workspace it needs (nothing is split) or with the preferred one."""
+    q, k, v, dA, cu, scale = tb.attn_bwd_case(sizes, H, 128, "bf16", seed=H)
+    q64, k64, v64, dA64 = (P.to64(t) for t in (q, k, v, dA))
+    A, lse = orc.group_attention(q64, k64, v64, cu, scale)
+    N, M = q.shape[0], len(sizes)
+    lib = mg.load()
+    need = mg.workspace_bytes(mg.OP_ATTN_BWD, N, H, 128, M, 0, mg.MOGA_BF16)
+    size = lib.moga_workspace_preferred_bytes(mg.OP_ATTN_BWD, N, N, H, 128, M, 0, mg.MOGA_BF16) if room else need
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever nothing is written
+    hat = lambda t: t.permute(1, 0, 2).contiguous().cuda()
+    oh, lse_d = torch.from_numpy(P.hat(A)).bfloat16().cuda(), torch.from_numpy(np.ascontiguousarray(lse.T)).float().cuda()
+    got = mg.moga_group_attn_bwd(hat(dA), hat(q), hat(k), hat(v), oh, lse_d, torch.from_numpy(cu).cuda(), scale, ws=ws)
+    torch.cuda.synchronize()
+    assert int(mg.attn_bwd_status(ws, N, H).item()) == 0
+    return mg.attn_blocks(mg.OP_ATTN_BWD, N, N, H, M, size), got, orc.group_attention_bwd(q64, k64, v64, dA64, cu, scale)
+
+
+# Heads with which every pair of block sizes is taken; groups of up to 769 rows go round the ring of four 64-row tiles three times.
+@pytest.mark.parametrize("H,room,blocks", [
+    (1, False, (256, False, 128, False)), (5, False, (256, False, 192, False)), (7, False, (384, False, 128, False)),
+    (9, False, (384, False, 192, False)), (1, True, (256, True, 128, True)), (10, True, (384, True, 192, True))])
+def test_backward_with_every_block_size(H, room, blocks):
+    print(f"H={H} room={room}", flush=True)
+    mg.set_small_group_rows(0)
+    try:
+        took, got, ref = backward_at_edges(SIZES, H, room)
+    finally:
+        mg.set_small_group_rows(-1)
+    print(took, flush=True)
+    assert took == blocks
+    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+        tb.check(P.unhat(a), b, name, "bf16")
+
+
+# token-order rows gathered by the kernels: the blocks of a call that does not split
+@pytest.mark.parametrize("H", [1, 5, 7, 9])
+def test_gather_fused_backward_with_every_block_size(H):
+    print(f"fused H={H}", flush=True)
+    q, k, v, d_o, cu, scale = tb.attn_bwd_case(SIZES, H, 128, "bf16", seed=H + 20)   # sorted order
+    N = q.shape[0]
+    g = torch.Generator().manual_seed(H)
+    perm, gate = torch.randperm(N, generator=g), torch.rand(N, generator=g) * 0.7 + 0.2
+    tok = lambda t: torch.empty_like(t).index_copy_(0, perm, t)   # row j of the sorted order is token perm[j]
+    gs = P.to64(gate)[perm.numpy()][:, None, None]
+    q64, k64, v64, d64 = (P.to64(t) for t in (q, k, v, d_o))
+    A, lse = orc.group_attention(q64, k64, v64, cu, scale)
+    ref = orc.group_attention_bwd(q64, k64, v64, d64 * gs, cu, scale)
+    o = tok(torch.from_numpy(A * gs).bfloat16()).cuda()
+    inv = torch.empty(N, dtype=torch.int32)
+    inv[perm] = torch.arange(N, dtype=torch.int32)
+    *got, d_gate = mg.moga_fused_attn_bwd(*(tok(t).cuda() for t in (d_o, q, k, v)), o, torch.from_numpy(np.ascontiguousarray(lse.T)).float().cuda(),
+                                          perm.int().cuda(), inv.cuda(), gate.cuda(), torch.from_numpy(cu).cuda(), scale)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+        tb.check(P.to64(a.cpu()[perm]), b, name, "bf16")
+    d_ref = np.empty(N)
+    d_ref[perm.numpy()] = (d64 * A).sum(axis=(1, 2))
+    np.testing.assert_allclose(P.to64(d_gate), d_ref, rtol=3e-2, atol=3e-2 * np.abs(d_ref).max())
