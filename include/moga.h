@@ -70,7 +70,9 @@ size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model,
 /*
  * Bytes with which the call runs fastest (>= moga_workspace_bytes; Nk = number of key rows, N for MoGA's own calls).  The
  * bf16 attention calls with a few rounds of long blocks use room past what they need to split the last round
- * (51 MB): moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
+ * (pieces of 256 rows 34 MB, of 384 rows 51 MB; with less than the preferred bytes a call takes the blocks that are fastest in
+ * the room it has):
+ * moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
  * summed in pieces, so its rounding differs from that of a call with less room: results repeat bit by bit between calls
  * that both have these bytes, or both less.  Host-only.
  */

@@ -144,7 +144,7 @@ static int64_t small_group_rows(int64_t Nq, int H) {
   return rounds < 350 ? 860 : rounds < 600 ? 650 : 400;
 }
 
-AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room) {
+AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
   if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H))) return {true, {128, false}, {64, false}};
   return {false, query_blocks(Nq, Nk, H, M, room), key_blocks(Nq, Nk, H, M, room)};
 }
@@ -186,13 +186,13 @@ struct TokenGrads {
 };
 
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
-// space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: NULL or kSplitBytes
-// for the pieces of a last round (dK/dV and dQ use it one after the other; only without ts_q / ts_k).
+// space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: room for
+// the pieces of a last round, if any (dK/dV and dQ use it one after the other; only without ts_q / ts_k).
 static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
                            const void* oh, const float* lse, int dtype, int64_t Nq, int64_t Nk, int H, int D,
                            const int32_t* cu_q, const int32_t* cu_k, int32_t* ts_q, int32_t* ts_k,
                            int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
-                           float* delta, const TokenGrads& tok, void* split, hipStream_t st) {
+                           float* delta, const TokenGrads& tok, const SplitRoom& split, hipStream_t st) {
   unsigned short *d_q_tok = (unsigned short*)tok.d_q, *d_k_tok = (unsigned short*)tok.d_k, *d_v_tok = (unsigned short*)tok.d_v;
   const int64_t rows = Nq * (int64_t)H;
   int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
@@ -200,7 +200,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
-    const AttnPlan plan = bwd_plan(Nq, Nk, H, M, split != nullptr);
+    const AttnPlan plan = bwd_plan(Nq, Nk, H, M, split.rows);
     const bool small = plan.small;
     const int bk = plan.k.rows, bm = plan.q.rows;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
@@ -231,14 +231,14 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
   attn_bwd_dkdv_ab_kernel<KK, false, SPLIT><<<(unsigned)(k_blocks + (SPLIT ? kCus : 0)), 512, 0, st>>>(                        \
       (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta, \
       cu_q, cu_k, SPLIT ? nullptr : ts_k, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_kh, (unsigned short*)d_vh,            \
-      g_spin_limit.load(), status, tok.perm, SPLIT ? split_ws(split).part : nullptr, d_k_tok, d_v_tok)
+      g_spin_limit.load(), status, tok.perm, SPLIT ? (float*)split.ws : nullptr, d_k_tok, d_v_tok)
       if (split_k && bk == 192) MOGA_BWD_DKDV(192, true);
       else if (split_k) MOGA_BWD_DKDV(128, true);
       else if (bk == 192) MOGA_BWD_DKDV(192, false);
       else MOGA_BWD_DKDV(128, false);
 #undef MOGA_BWD_DKDV
       if (split_k)
-        split_sum_kernel<<<dim3(kCus / 2, 2 * bk / 8), 256, 0, st>>>(split_ws(split).part, cu_k, M, H, Nk, bk, 1.f, softmax_scale,
+        split_sum_kernel<<<dim3(kCus / 2, 2 * bk / 8), 256, 0, st>>>((const float*)split.ws, cu_k, M, H, Nk, bk, 1.f, softmax_scale,
                                                                      (unsigned short*)d_vh, (unsigned short*)d_kh, d_v_tok, d_k_tok, tok.perm);
     }
     const bool split_q = plan.q.split;
@@ -246,14 +246,14 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
   attn_bwd_dq_pipe_kernel<RR, false, SPLIT><<<(unsigned)(q_blocks + (SPLIT ? kCus : 0)), 512, 0, st>>>(                        \
       (const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, lse2, delta, \
       cu_q, cu_k, SPLIT ? nullptr : ts_q, M, Nq, Nk, H, softmax_scale, (unsigned short*)d_qh, tok.perm,                         \
-      SPLIT ? split_ws(split).part : nullptr, d_q_tok)
+      SPLIT ? (float*)split.ws : nullptr, d_q_tok)
     if (split_q && bm == 384) MOGA_BWD_DQ(384, true);
     else if (split_q) MOGA_BWD_DQ(256, true);
     else if (bm == 384) MOGA_BWD_DQ(384, false);
     else MOGA_BWD_DQ(256, false);
 #undef MOGA_BWD_DQ
     if (split_q)
-      split_sum_kernel<<<dim3(kCus / 2, bm / 8), 256, 0, st>>>(split_ws(split).part, cu_q, M, H, Nq, bm, softmax_scale, 0.f,
+      split_sum_kernel<<<dim3(kCus / 2, bm / 8), 256, 0, st>>>((const float*)split.ws, cu_q, M, H, Nq, bm, softmax_scale, 0.f,
                                                                    (unsigned short*)d_qh, nullptr, d_q_tok, nullptr, tok.perm);
   } else {
     const int64_t q_tiles = max_tiles(Nq, M, kF32Rows), k_tiles = Nk > 0 ? max_tiles(Nk, M, kF32Rows) : 0;
@@ -309,7 +309,7 @@ extern "C" int moga_group_attn_bwd(const void* d_oh, const void* qh, const void*
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr,
-                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{}, split_region(ws, need, ws_bytes),
+                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{}, split_room(ws, need, ws_bytes),
                          (hipStream_t)stream);
 }
 
@@ -337,7 +337,7 @@ extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
                          softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm, true},
-                         split_region(ws, need, ws_bytes), (hipStream_t)stream);
+                         split_room(ws, need, ws_bytes), (hipStream_t)stream);
 }
 
 extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
@@ -373,7 +373,7 @@ static int varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
   int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
                          ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
-                         presum ? nullptr : split_region(ws, need, ws_bytes), st);
+                         presum ? SplitRoom{} : split_room(ws, need, ws_bytes), st);
 }
 
 extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
@@ -414,7 +414,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
-  const int rows_q = query_blocks(N, N, H, M, false).rows, keys = key_blocks(N, N, H, M, false).rows;
+  const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;
   hipStream_t st = (hipStream_t)stream;
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
@@ -447,13 +447,17 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
   if (dtype != MOGA_BF16 || D != 128 || N <= 0 || Nk <= 0 || H < 1 || M < 1) return need;
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD;
-  const AttnPlan plan = M > MOGA_MAX_GROUPS ? AttnPlan{} : fwd ? fwd_plan(N, Nk, H, M, true) : bwd ? bwd_plan(N, Nk, H, M, true) : AttnPlan{};
-  return plan.q.split || plan.k.split ? round_up(need, 256) + 256 + kSplitBytes : need;
+  if (M > MOGA_MAX_GROUPS || !(fwd || bwd)) return need;
+  auto plan = [&](int room) { return fwd ? fwd_plan(N, Nk, H, M, room) : bwd_plan(N, Nk, H, M, room); };
+  const AttnPlan p = plan(384), q = plan(256);
+  if (!p.q.split && !p.k.split) return need;
+  const bool same = p.small == q.small && p.q.rows == q.q.rows && p.q.split == q.q.split && p.k.rows == q.k.rows && p.k.split == q.k.split;
+  return round_up(need, 256) + 256 + split_bytes(same ? 256 : 384);
 }
 
 extern "C" void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]) {
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
-  const bool room = M <= MOGA_MAX_GROUPS && split_region((void*)256, moga_workspace_bytes(op, Nq, H, 128, M, 0, MOGA_BF16), ws_bytes);
+  const int room = M > MOGA_MAX_GROUPS ? 0 : split_room((void*)256, moga_workspace_bytes(op, Nq, H, 128, M, 0, MOGA_BF16), ws_bytes).rows;
   const AttnPlan p = fwd ? fwd_plan(Nq, Nk, H, M, room) : bwd_plan(Nq, Nk, H, M, room);
   blocks[0] = p.q.rows, blocks[1] = p.q.split, blocks[2] = p.k.rows, blocks[3] = p.k.split;
 }

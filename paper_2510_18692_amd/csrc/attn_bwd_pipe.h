@@ -212,7 +212,7 @@ __device__ __forceinline__ void attn_bwd_dq_block(
   auto sweep = [&](auto columns) {
     constexpr int NC = columns.value;
     const int q0w = q0 + wave * 16 * NC;   // first query row of this wave
-    float* const piece_rows = piece ? part + (sp.slot * kSplitRows + 16 * NC * wave) * kHeadDim : nullptr;
+    float* const piece_rows = piece ? part + ((size_t)sp.slot * ROWS + 16 * NC * wave) * kHeadDim : nullptr;
     if (n <= 0) {   // queries without keys: zero gradient (block-uniform branch)
       if (piece) store_zero_piece<NC>(piece_rows);
       else store_zero_rows<GATHER, NC>(q0w, ge, head, head_off, H, d_qh, nullptr, perm, d_q_tok);
@@ -708,7 +708,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
     unsigned short* outp = role == 0 ? d_vh : d_kh;
     unsigned short* tokp = role == 0 ? d_v_tok : d_k_tok;
 
-    float* const piece_rows = piece ? part + (sp.slot * kSplitRows + BK * role + 16 * NC * pair) * kHeadDim : nullptr;   // dV, then dK
+    float* const piece_rows = piece ? part + ((size_t)sp.slot * 2 * BK + BK * role + 16 * NC * pair) * kHeadDim : nullptr;   // dV, then dK
     if (n <= 0) {   // keys without queries: zero gradient (block-uniform branch)
       if (piece) store_zero_piece<NC>(piece_rows);
       else store_zero_rows<GATHER, NC>(k0w, ge, head, head_off, H, outp, nullptr, perm, tokp);

@@ -173,19 +173,22 @@ __device__ __forceinline__ void store_partial(float* base, int dt, int col_half,
   *(floatx4_t*)(base + (16 * col_half + (lane & 15)) * kHeadDim + 16 * dt + 4 * (lane >> 4)) = v;
 }
 
-constexpr size_t kSplitRows = 384;   // room for the result rows of a piece
-constexpr size_t kSplitBytes = kCus * kSplitRows * (kHeadDim + 2) * sizeof(float);   // results, then (max, sum) of the forward
+// A round of pieces of `rows` result rows each (dV and dK: of both), 34 MB for 256 and 51 MB for 384: results, then (max, sum) of the forward.
+constexpr size_t split_bytes(int rows) { return (size_t)kCus * rows * (kHeadDim + 2) * sizeof(float); }
 struct SplitWs {
   float *part, *stat;
 };
-// The part of a workspace past its first `used` bytes, if the pieces fit there; else NULL.
-inline void* split_region(void* ws, size_t used, size_t ws_bytes) {
-  if (!ws) return nullptr;
+inline SplitWs split_ws(void* ws, int rows) { return {(float*)ws, (float*)ws + (size_t)kCus * rows * kHeadDim}; }
+// The part of a workspace past its first `used` bytes, and the rows of the longest pieces that fit there (0: none do).
+struct SplitRoom {
+  void* ws;
+  int rows;
+};
+inline SplitRoom split_room(void* ws, size_t used, size_t ws_bytes) {
+  if (!ws) return {nullptr, 0};
   const size_t off = round_up((size_t)(uintptr_t)ws + used, 256) - (size_t)(uintptr_t)ws;
-  return ws_bytes >= off + kSplitBytes ? (char*)ws + off : nullptr;
-}
-inline SplitWs split_ws(void* ws) {
-  return {(float*)ws, (float*)ws + kCus * kSplitRows * kHeadDim};
+  const int rows = ws_bytes >= off + split_bytes(384) ? 384 : ws_bytes >= off + split_bytes(256) ? 256 : 0;
+  return {rows ? (char*)ws + off : nullptr, rows};
 }
 // Worth it for a few rounds of the kernels with long blocks; beyond 32 rounds the last one is under 3 %.
 inline bool split_pays(int64_t tiles) { return tiles <= 32 * kCus; }
@@ -211,10 +214,11 @@ static __global__ __launch_bounds__(256) void split_sum_kernel(const float* __re
   const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
   const int a = r / rows, row = ti.tile_row + r % rows;
   if (row >= ti.row_end) return;
-  const float* p = part + ((size_t)blockIdx.x * s.splits * kSplitRows + r) * kHeadDim + col;
+  const size_t piece = 8 * gridDim.y;   // rows
+  const float* p = part + ((size_t)blockIdx.x * s.splits * piece + r) * kHeadDim + col;
   floatx4_t v[kMaxSplits];   // all in flight together
 #pragma unroll
-  for (int k = 0; k < kMaxSplits; ++k) v[k] = k < s.splits ? *(const floatx4_t*)(p + (size_t)k * kSplitRows * kHeadDim) : floatx4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < kMaxSplits; ++k) v[k] = k < s.splits ? *(const floatx4_t*)(p + k * piece * kHeadDim) : floatx4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int k = 1; k < kMaxSplits; ++k) v[0] += v[k];
   unsigned short *o = a ? out1 : out0, *t = a ? tok1 : tok0;
@@ -273,11 +277,12 @@ struct Blocks {
   int rows;
   bool split;
 };
-// N: rows of this side, in blocks of `few` or 3/2 of that; other: rows of the side that they sweep.
-inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, bool room) {
+// N: rows of this side, in blocks of `few` or 3/2 of that; other: rows of the side that they sweep; arrays: results per row; room: result
+// rows of the longest piece there is room for.
+inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int arrays, int room) {
   constexpr int64_t kStartRows = 640, kMergeRows = 1000;
   const int64_t mean = (N + M - 1) / M, swept = (other + M - 1) / M;
-  auto splits = [&](int rows) { return room && split_pays(max_tiles(N, M, rows) * H); };
+  auto splits = [&](int rows) { return room >= arrays * rows && split_pays(max_tiles(N, M, rows) * H); };
   auto cost = [&](int rows, int64_t weight) {
     const int64_t tiles = (mean + rows - 1) / rows * M * H, left = tiles % kCus;
     const int64_t pieces = left > 0 && splits(rows) ? std::min<int64_t>(kMaxSplits, kCus / left) : 1;
@@ -286,17 +291,17 @@ inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, bool
   const int rows = cost(few, 10) < cost(few / 2 * 3, 13) ? few : few / 2 * 3;
   return {rows, splits(rows)};
 }
-inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) { return large_blocks(Nq, Nk, H, M, 256, room); }
-inline Blocks key_blocks(int64_t Nq, int64_t Nk, int H, int M, bool room) { return large_blocks(Nk, Nq, H, M, 128, room); }
+inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nq, Nk, H, M, 256, 1, room); }
+inline Blocks key_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nk, Nq, H, M, 128, 2, room); }
 
 // What a bf16 call runs: the kernels for small groups, or the large ones and their blocks of queries (and of keys, backward).  room:
-// the last round can be split (M <= MOGA_MAX_GROUPS and a workspace with kSplitBytes).
+// that of split_room (0 where M > MOGA_MAX_GROUPS).
 struct AttnPlan {
   bool small;
   Blocks q, k;
 };
-AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room);
-AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room);
+AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room);
+AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room);
 
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
 // column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a

@@ -35,8 +35,8 @@ static int64_t small_group_rows(int64_t Nq, int H, bool split) {
   return rounds < 50 ? 5632 : rounds < 100 ? 6144 : rounds < 370 ? 2560 : rounds < 600 ? 1300 : 700;
 }
 
-AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, bool room) {
-  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H, room))) return {true, {128, false}, {}};
+AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
+  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H, room > 0))) return {true, {128, false}, {}};
   return {false, query_blocks(Nq, Nk, H, M, room), {}};
 }
 
@@ -52,15 +52,15 @@ struct TokenRows {
   const float* gate;
 };
 
-// Shared launcher.  tile_start == NULL: tile lookup inside the kernels (M <= MOGA_MAX_GROUPS).  split: NULL or
-// kSplitBytes for the pieces of the last round (only with tile_start == NULL).
+// Shared launcher.  tile_start == NULL: tile lookup inside the kernels (M <= MOGA_MAX_GROUPS).  split: room
+// for the pieces of the last round, if any (only with tile_start == NULL).
 static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype, int64_t Nq,
                            int64_t Nk, int H, int D, const int32_t* cu_q, const int32_t* cu_k,
                            int32_t* tile_start, int M, float softmax_scale, void* oh, float* lse,
-                           const TokenRows& tok, void* split, hipStream_t st) {
+                           const TokenRows& tok, const SplitRoom& split, hipStream_t st) {
   // bf16: groups of a few thousand rows or less (the static groups of Section 3.2) take the kernel
   // with 128-row tiles and two 4-wave blocks per CU; the host only knows the mean group size
-  const AttnPlan plan = dtype == MOGA_BF16 ? fwd_plan(Nq, Nk, H, M, split != nullptr) : AttnPlan{};
+  const AttnPlan plan = dtype == MOGA_BF16 ? fwd_plan(Nq, Nk, H, M, split.rows) : AttnPlan{};
   const bool small = plan.small;
   const int rows = plan.q.rows, bm = dtype == MOGA_BF16 ? rows : kF32Rows;
   const int64_t tiles = max_tiles(Nq, M, bm);
@@ -80,7 +80,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
         (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k,
         tile_start, M, Nq, Nk, H, softmax_scale, (unsigned short*)oh, lse, tok.perm, tok.gate, (unsigned short*)tok.o);
   } else if (plan.q.split) {
-    const SplitWs sw = split_ws(split);
+    const SplitWs sw = split_ws(split.ws, rows);
 #define MOGA_FWD_SPLIT(RR)                                                                                                     \
   attn_fwd_bf16_pipe_kernel<RR, false, true><<<(unsigned)(blocks + kCus), 512, 0, st>>>(                                       \
       (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh, cu_q, cu_k, nullptr, M, Nq, Nk, H,      \
@@ -125,7 +125,7 @@ static int group_attn_fwd(const void* qh, const void* kh, const void* vh, int dt
   if (!qh || !kh || !vh || !cu_seqlens || !oh || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh) && aligned16(tok.o))) return MOGA_ERR_INVALID_ARG;
   return launch_attn_fwd(qh, kh, vh, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, M,
-                         softmax_scale, oh, lse, tok, split_region(ws, 0, ws_bytes), (hipStream_t)stream);
+                         softmax_scale, oh, lse, tok, split_room(ws, 0, ws_bytes), (hipStream_t)stream);
 }
 
 extern "C" int moga_group_attn_fwd_ws(const void* qh, const void* kh, const void* vh, int dtype,
@@ -163,7 +163,7 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
   if (N == 0) return MOGA_OK;
   if (!q || !k || !v || !perm || !gate || !cu_seqlens || !o || !lse) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(q) && aligned16(k) && aligned16(v) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
-  const int rows = query_blocks(N, N, H, M, false).rows;
+  const int rows = query_blocks(N, N, H, M, 0).rows;
   const int64_t blocks = (max_tiles(N, M, rows) * H + 7) / 8 * 8;
   if (!grid_fits(blocks, 512)) return MOGA_ERR_UNSUPPORTED;
 #define MOGA_FWD(RR)                                                                                                             \
@@ -192,7 +192,7 @@ extern "C" int moga_varlen_attn_fwd(const void* qh, const void* kh, const void* 
   if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
   if (!ws || ws_bytes < moga_varlen_attn_fwd_ws_bytes(G)) return MOGA_ERR_WORKSPACE;
   int32_t* ts = G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)ws;   // few groups: every block looks its tile up itself
-  void* split = ts ? nullptr : split_region(ws, moga_varlen_attn_fwd_ws_bytes(G), ws_bytes);
+  const SplitRoom split = ts ? SplitRoom{} : split_room(ws, moga_varlen_attn_fwd_ws_bytes(G), ws_bytes);
   return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts, G,
                          softmax_scale, oh, lse, TokenRows{}, split, (hipStream_t)stream);
 }

@@ -314,11 +314,10 @@ __device__ __forceinline__ void store_output(const PipeState<NC>& st, int q0w, i
   }
 }
 
-// A piece's O, maximum and sum of this wave's rows, not yet divided.
+// A piece's O, maximum and sum of this wave's rows (row0 on, of the workspace), not yet divided.
 template <int NC>
-__device__ __forceinline__ void store_piece(const PipeState<NC>& st, const SplitWs& sw, int slot, int wave) {
+__device__ __forceinline__ void store_piece(const PipeState<NC>& st, const SplitWs& sw, size_t row0) {
   const int lane = threadIdx.x & 63;
-  const size_t row0 = slot * kSplitRows + 16 * NC * wave;
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
     const float lt = st.l[q];
@@ -328,9 +327,8 @@ __device__ __forceinline__ void store_piece(const PipeState<NC>& st, const Split
   }
 }
 template <int NC>
-__device__ __forceinline__ void store_empty_piece(const SplitWs& sw, int slot, int wave) {
+__device__ __forceinline__ void store_empty_piece(const SplitWs& sw, size_t row0) {
   const int lane = threadIdx.x & 63;
-  const size_t row0 = slot * kSplitRows + 16 * NC * wave;
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
 #pragma unroll
@@ -500,8 +498,9 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
   auto sweep = [&](auto columns) {
     constexpr int NC = columns.value;
     const int q0w = q0 + wave * 16 * NC;   // first query row of this wave
+    const size_t piece_row = (size_t)sp.slot * ROWS + 16 * NC * wave;
     if (n <= 0) {   // queries without keys: zero output, lse = -inf (block-uniform branch)
-      if (piece) store_empty_piece<NC>(sw, sp.slot, wave);
+      if (piece) store_empty_piece<NC>(sw, piece_row);
       else store_zero_rows<GATHER, NC>(q0w, ge, head, head_off, H, oh, lse, perm, o_tok);
       return;
     }
@@ -585,7 +584,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
     pipe_step<64, true, true, false, 0, 0>(ln, 0, voff, qf, st, s_a, s_b, mx, c, []() {});
 
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
-    if (piece) store_piece(st, sw, sp.slot, wave);
+    if (piece) store_piece(st, sw, piece_row);
     else store_output<GATHER>(st, q0w, ge, head, head_off, H, oh, lse, perm, gate, o_tok);
   };
   if (ROWS > 256 && ge - q0 > 256) sweep(std::integral_constant<int, ROWS / 128>());
@@ -609,12 +608,12 @@ static __global__ __launch_bounds__(256) void split_fwd_kernel(SplitWs sw, int r
   const bool keys = cu_k[ti.group + 1] > cu_k[ti.group];
   const int col = (threadIdx.x & 31) * 4, r = blockIdx.y * 8 + (threadIdx.x >> 5);
   if (ti.tile_row + r >= ti.row_end) return;
-  const size_t first = (size_t)blockIdx.x * s.splits * kSplitRows + r;   // piece k is k * kSplitRows rows further
+  const size_t first = (size_t)blockIdx.x * s.splits * rows + r;   // piece k is k * rows further
   floatx4_t v[kMaxSplits];
   floatx2_t ml[kMaxSplits];
 #pragma unroll
   for (int k = 0; k < kMaxSplits; ++k) {
-    const size_t row = first + (k < s.splits ? k : 0) * kSplitRows;
+    const size_t row = first + (k < s.splits ? k : 0) * (size_t)rows;
     v[k] = *(const floatx4_t*)(sw.part + row * kHeadDim + col);
     ml[k] = *(const floatx2_t*)(sw.stat + row * 2);
   }

@@ -39,3 +39,18 @@ def test_more_groups_than_a_block_looks_up_never_split(large_kernels):
     for op in (mg.OP_VARLEN_ATTN_FWD, mg.OP_VARLEN_ATTN_BWD):
         q, q_split, k, k_split = blocks(op, 300 * 700, 3, 300, 1 << 40)
         assert not q_split and not k_split
+
+
+# 34 MB past what a call needs hold a round of pieces of 256 rows (or of 128 rows of dV and of dK)
+@pytest.mark.parametrize("N,H,M", [(62400, 12, 5), (32760, 12, 8), (12000, 12, 3), (28000, 3, 7), (7000, 4, 2)])
+def test_calls_split_with_room_for_short_pieces(large_kernels, N, H, M):
+    for op in (mg.OP_ATTN_FWD, mg.OP_ATTN_BWD):
+        need = mg.workspace_bytes(op, N, H, 128, M, 0, mg.MOGA_BF16)
+        room = 256 + 256 * 256 * 130 * 4
+        q, q_split, k, k_split = blocks(op, N, H, M, need + room)
+        assert q_split == (q == 256) and k_split == (k == 128)
+        assert q_split or blocks(op, N, H, M, need + 2 * room)[0] == 384
+        few = mg.load().moga_workspace_preferred_bytes(op, N, N, H, 128, M, 0, mg.MOGA_BF16)
+        assert need + room - 512 <= few <= need + room * 3 // 2 + 512
+        assert blocks(op, N, H, M, few) == blocks(op, N, H, M, 1 << 40)
+    assert blocks(mg.OP_ATTN_FWD, 7000, 4, 2, 256 + 256 * 256 * 130 * 4)[:2] == (256, True)

@@ -175,3 +175,48 @@ def test_forward_without_ws_leaves_the_workspace_alone():
     finally:
         mg.set_small_group_rows(-1)
     assert used == [False, True]
+
+
+def varlen_results(nq, nk, H, bytes_of, o_lse=None, seed=0):
+    """O, lse, dQ, dK, dV of the varlen calls with bytes_of(needed, preferred) bytes of workspace, of which the bytes past them stay as they
+    are, and the blocks that they took.  The backward takes o_lse if given (the bounds of rows_close want P and dS alike on both sides)."""
+    g = torch.Generator().manual_seed(len(nq) + H + seed)
+    Nq, Nk, G = sum(nq), sum(nk), len(nq)
+    q, d = (torch.randn((H, Nq, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    k, v = (torch.randn((H, Nk, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
+    cq, ck = (torch.from_numpy(np.concatenate([[0], np.cumsum(n)]).astype(np.int32)).cuda() for n in (nq, nk))
+    s, lib, stream = 128 ** -0.5, mg.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    took, out = [], [torch.empty_like(q), torch.empty((H, Nq), device="cuda"), torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)]
+    for op in (mg.OP_VARLEN_ATTN_FWD, mg.OP_VARLEN_ATTN_BWD):
+        need = mg.workspace_bytes(op, Nq, H, 128, G, 0, mg.MOGA_BF16)
+        size = bytes_of(need, lib.moga_workspace_preferred_bytes(op, Nq, Nk, H, 128, G, 0, mg.MOGA_BF16))
+        ws = torch.full((size + 4096,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever nothing is written
+        if op == mg.OP_VARLEN_ATTN_FWD:
+            st = lib.moga_varlen_attn_fwd(p(q), p(k), p(v), mg.MOGA_BF16, Nq, Nk, H, 128, p(cq), p(ck), G, s, p(out[0]), p(out[1]), p(ws), size,
+                                          stream)
+        else:
+            st = lib.moga_varlen_attn_bwd(p(d), p(q), p(k), p(v), *(p(t) for t in o_lse or out[:2]), mg.MOGA_BF16, Nq, Nk, H, 128, p(cq), p(ck), G, s,
+                                          *(p(t) for t in out[2:]), p(ws), size, stream)
+        assert st == 0 and (ws[size:] == 0xFF).all()
+        took.append(mg.attn_blocks(op, Nq, Nk, H, G, size))
+    torch.cuda.synchronize()
+    return out, took
+
+
+@pytest.fixture
+def large_kernels():
+    mg.set_small_group_rows(0)   # the kernels with long blocks, whatever the mean size
+    yield
+    mg.set_small_group_rows(-1)
+
+
+def test_room_for_short_pieces(large_kernels):
+    """34 MB past what a call needs: pieces of 256 rows where it would take 384 with more."""
+    n = [1700, 1600, 2]
+    print(n, flush=True)
+    short = 256 + 256 * 256 * 130 * 4
+    whole, _ = varlen_results(n, n, 6, lambda need, pref: need)
+    less, took = varlen_results(n, n, 6, lambda need, pref: need + short, whole[:2])
+    assert took == [(256, True, 0, False), (256, True, 128, True)]
+    for a, b, name in zip(less, whole, ("O", "lse", "dQ", "dK", "dV")):
+        rows_close(a, b, name)
