@@ -227,7 +227,8 @@ void moga_debug_set_spin_limit(int polls);
  * static groups of Section 3.2.  The group sizes live on the device, so a call chooses by the mean
  * group size N / M and the rounds of 256 256-row tiles (forward: below 5632 rows up to half a round, 6144 up to one, 2560 up to 3.7, 1300 up
  * to 6, else 700, and with room to split a round 1500 up to 0.2, 2700 up to 0.33, 4500 from 0.5 to 0.75; backward: below 2000 up to 0.75
- * rounds, 1450 up to one, 1300 up to 2 (from 1.15 to 1.35: 860), 860 up to 3.5, 650 up to 6, else 400; the moga_fused_* calls always take the first set).  Both sets
+ * rounds, 1450 up to one, 1300 up to 2, 860 up to 3.5, 650 up to 6, 450 up to 10, else 400, but up to 0.33 8192, or 2800 with room to split a
+ * round; the moga_fused_* calls always take the first set).  Both sets
  * give the same results up to rounding order.
  * moga_debug_set_small_group_rows overrides all thresholds (0: never the small
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.

@@ -128,24 +128,28 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
 }
 
 // Mean rows per group below which the small-group bf16 kernels run, by rounds of 256 blocks of 256 rows: their finer tiles win
-// where there are few.  Time of the small kernels against the large ones', groups of equal / Zipf(1.1) sizes:
-//   rounds 0.15 (9,830 x 1 head)  1,350 rows -43 / -2 %, 2,900 -12 / +17 %;  0.40  2,200 -2 / -24, 2,900 +5 / -23
-//          0.60                   1,700 -5 / +4, 2,900 +4 / -19;             0.85  1,100 -6 / +9, 1,700 +4 / +4
-//          1.05                   1,250 -7 / +6, 2,000 +5 / -16;             1.2   750 -1 / -16, 1,100 +6 / -13
-//          1.3                    800 -21 / -13, 1,250 -2 / -5;              1.55  1,250 -6 / 0, 2,000 +3 / -13
-//          1.9                    1,250 0 / -3, 2,000 +6 / +2;               2.9   650 -11 / -4, 1,000 -4 / +8
-//          4    (6,550 x 40)      600 -6 / +5, 750 +7 / +2;                  5.7   650 -1 / +12, 800 +7 / +15
-//          7                      400 -3 / +10, 600 -1 / +12, 750 +6 / +14;  13    400 -1 / +15, 500 +4 / +17, 750 +10 / +20
-// The host knows only the mean.  A lower line below a round would cost equal groups, what a balanced router makes, up to 60 %.
-static int64_t small_group_rows(int64_t Nq, int H) {
+// where there are few.  Time of the small kernels against the large ones' (blocks by large_blocks) with room to split a round, groups of
+// equal / Zipf(1.1) sizes, in %; in brackets equal groups without room:
+//   rounds 0.15  1,250 rows -42 / +2 [-53], 2,500 -17 / +11 [-51], 5,000 +8 / +20 [-51];  0.25  2,500 -15 / 0 [-31], 8,000 +25 / +32 [-31]
+//          0.4   1,560 +6 / -5 [+3], 2,500 +19 / -8 [+7];                0.6   1,560 +2 / -20 [+6], 2,500 +5 / -20 [+8]
+//          0.85  1,000 +2 / -10 [+8], 1,560 +10 / -3 [+14];              1.05  850 -2 / -4 [+4], 1,250 0 / -16 [+5], 1,560 +3 / -3 [+7]
+//          1.2   850 -8 / -15 [-4], 1,250 +6 / -16 [+10], 1,560 +9 / -14 [+12];  1.6  1,000 -3 / -11 [0], 1,560 +3 / -9 [+4]
+//          1.8   850 -3 / +4 [0], 1,250 +10 / -11 [+13];                 2.9   700 -8 / +9 [-5], 1,000 +3 / +4 [+5]
+//          4.5   600 -8 / +4 [-5], 700 -3 / +11 [+1];                    6.6   400 -7 / +8 [-4], 500 -2 / +17 [+1]
+//          8     400 -12 / +8 [-4], 500 -4 / +14 [0];                    12    400 -3 / +20 [-1], 500 +2 / +20 [+5]
+// The lines are where equal groups, what a balanced router makes, take the same time; between 0.33 and 2 rounds they are higher, to where
+// equal groups lose up to 10 %, since Zipf groups gain up to twice that.  The host knows only the mean.  Without room below a third
+// of a round most CUs have no block of the large kernels, and these are never the faster ones (measured to 8,000 rows).  A line with room
+// may not lie above the one without: a call that it sends to the small kernels asks for no room, and comes here again without.
+static int64_t small_group_rows(int64_t Nq, int H, bool room) {
   const int64_t rounds = 100 * Nq * H / (256 * kCus);   // in hundredths
+  if (rounds < 33) return room ? 2800 : 8192;
   if (rounds < 100) return rounds < 75 ? 2000 : 1450;
-  if (rounds < 200) return rounds >= 115 && rounds < 135 ? 860 : 1300;
-  return rounds < 350 ? 860 : rounds < 600 ? 650 : 400;
+  return rounds < 200 ? 1300 : rounds < 350 ? 860 : rounds < 600 ? 650 : rounds < 1000 ? 450 : 400;
 }
 
 AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
-  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H))) return {true, {128, false}, {64, false}};
+  if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H, room > 0))) return {true, {128, false}, {64, false}};
   return {false, query_blocks(Nq, Nk, H, M, room), key_blocks(Nq, Nk, H, M, room)};
 }
 

@@ -35,6 +35,30 @@ def test_key_rows_of_calls_that_cannot_split(large_kernels, N, H, M, rows):
     assert blocks(mg.OP_ATTN_BWD, N, H, M, need)[2:] == (rows, False)
 
 
+# mean rows on either side of the line between the kernels for small groups and the large ones, with and without room to split a round
+@pytest.mark.parametrize("H,M,below,above,room", [
+    (1, 4, 2700, 2900, True), (1, 2, 4000, None, False), (2, 4, 2000, None, False),        # a third of a round or less
+    (4, 20, 1000, 1310, True), (12, 6, 1250, 1310, True), (4, 20, 1250, 1310, False),       # 1.1 to 1.6 rounds
+    (40, 33, 440, 460, True), (40, 33, 440, 460, False), (40, 60, 390, 410, True),         # 8.9 and 14
+])
+def test_backward_line_between_the_kernel_sets(H, M, below, above, room):
+    for n, small in ((below, True), (above, False)):
+        if n:
+            need = mg.workspace_bytes(mg.OP_ATTN_BWD, n * M, H, 128, M, 0, mg.MOGA_BF16)
+            took = blocks(mg.OP_ATTN_BWD, n * M, H, M, need + (room << 27))
+            assert (took == (128, False, 64, False)) == small, n
+
+
+def test_calls_take_the_same_kernels_with_the_bytes_they_ask_for():
+    """The preferred bytes give the blocks that any amount of room gives, on either side of every line."""
+    for op in (mg.OP_ATTN_FWD, mg.OP_ATTN_BWD):
+        for H in (1, 4, 12, 40):
+            for M in (1, 2, 5, 8, 20, 60):
+                for n in range(100, 8400, 150):
+                    size = mg.load().moga_workspace_preferred_bytes(op, n * M, n * M, H, 128, M, 0, mg.MOGA_BF16)
+                    assert blocks(op, n * M, H, M, size) == blocks(op, n * M, H, M, 1 << 40), (op, H, M, n)
+
+
 def test_more_groups_than_a_block_looks_up_never_split(large_kernels):
     for op in (mg.OP_VARLEN_ATTN_FWD, mg.OP_VARLEN_ATTN_BWD):
         q, q_split, k, k_split = blocks(op, 300 * 700, 3, 300, 1 << 40)
