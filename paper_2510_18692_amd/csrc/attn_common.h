@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 
 #include "lds_pipe.h"
 
@@ -266,10 +267,12 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
 // Rows of a block of the large kernels (forward and dQ: 256 or 384 query rows; dK/dV: 128 or 192 keys), and whether the call splits its
 // last round.  Per row the longer blocks take less time (a fragment read from LDS feeds three products instead of two, the stream of the
 // other side is shared by more), but alone on its CU one takes 1.3 times as long as a short one: a call of less than a round that does not
-// split takes that much longer.  So the rounds are priced: for every row of the other side a step, kStartRows of them for a block's start and end (prologue, row
-// fragments, stores), the last round by its pieces if it is split, which costs kMergeRows more.  Constants from 114 calls of equal
-// groups, 0.07 to 9.8 rounds of 256 blocks, groups of 700 to 20,000 rows, either size of block forced: the choice is the faster one or within
-// (mean / worst) 0.4 / 8 % forward, 0.2 / 3 % by dQ, 0.1 / 2 % by dK/dV in calls that do not split, 0.2 / 9, 0.1 / 4 and 0.1 / 3 % in those that do.  The host knows the
+// split takes that much longer.  So the rounds are priced: for every row of the other side a step, kStartRows of them for a block's start
+// and end (prologue, row fragments, stores), the last round by its pieces if it is split, which costs kMergeRows more.  With every round the
+// blocks get further out of step, and the price goes over from whole rounds to the work per CU and half a block.
+// Constants from 374 calls of equal groups, 0.07 to 21 rounds of 256 blocks, groups of 500 to 20,000 rows, either size of block forced: where
+// these kernels run by default the choice is the faster one or within (mean / worst) 0.3 / 8 % forward, 0.1 / 3 % by dK/dV, and of the whole
+// backward 0.5 / 6 % by dQ, split or not (by whole rounds only 0.7 / 10, 0.2 / 6 and 0.5 / 6).  The host knows the
 // mean group only and takes it for all; 172 calls of Zipf(1.1) groups, where the largest decides: forward 4 % on average without a split, 5 with
 // (256 always 3 and 5, 384 always 17 and 8).  Milliseconds with 256 and 384 rows, forward without a split: 5,000 x 3 heads, 5 groups 0.029 and
 // 0.039; 7,000 x 4, 2 groups 0.081 and 0.111; 40,000 x 3, 4 groups 0.52 and 0.65; 99,840 x 12, 16 groups 3.33 and 3.09.
@@ -280,13 +283,17 @@ struct Blocks {
 // N: rows of this side, in blocks of `few` or 3/2 of that; other: rows of the side that they sweep; arrays: results per row; room: result
 // rows of the longest piece there is room for.
 inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int arrays, int room) {
-  constexpr int64_t kStartRows = 640, kMergeRows = 1000;
+  constexpr double kStartRows = 640, kMergeRows = 1000;
   const int64_t mean = (N + M - 1) / M, swept = (other + M - 1) / M;
   auto splits = [&](int rows) { return room >= arrays * rows && split_pays(max_tiles(N, M, rows) * H); };
-  auto cost = [&](int rows, int64_t weight) {
-    const int64_t tiles = (mean + rows - 1) / rows * M * H, left = tiles % kCus;
+  auto cost = [&](int rows, double weight) {
+    const int64_t of_group = (mean + rows - 1) / rows, tiles = of_group * M * H, full = tiles / kCus, left = tiles % kCus;
     const int64_t pieces = left > 0 && splits(rows) ? std::min<int64_t>(kMaxSplits, kCus / left) : 1;
-    return weight * (tiles / kCus * (swept + kStartRows) + (left > 0 ? swept / pieces + kStartRows : 0)) + (pieces > 1 ? 10 * kMergeRows : 0);
+    const double block = swept + kStartRows, last = left > 0 ? swept / pieces + kStartRows : 0;
+    const double in_step = full > 1 ? std::pow(0.8, full - 1) : 1;
+    const double short_end = mean - (of_group - 1) * rows <= few ? (weight - 10) * M * H : 0;   // a group's last block, of two columns a wave
+    return in_step * weight * (full * block + last) + (1 - in_step) * ((weight * tiles - short_end) / kCus * block + weight * last / 2) +
+           (pieces > 1 ? 10 * kMergeRows : 0);
   };
   const int rows = cost(few, 10) < cost(few / 2 * 3, 13) ? few : few / 2 * 3;
   return {rows, splits(rows)};
