@@ -130,13 +130,13 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
 // Mean rows per group below which the small-group bf16 kernels run, by rounds of 256 blocks of 256 rows: their finer tiles win
 // where there are few.  Time of the small kernels against the large ones' (blocks by large_blocks) with room to split a round, groups of
 // equal / Zipf(1.1) sizes, in %; in brackets equal groups without room:
-//   rounds 0.15  1,250 rows -42 / +2 [-53], 2,500 -17 / +11 [-51], 5,000 +8 / +20 [-51];  0.25  2,500 -15 / 0 [-31], 8,000 +25 / +32 [-31]
-//          0.4   1,560 +6 / -5 [+3], 2,500 +19 / -8 [+7];                0.6   1,560 +2 / -20 [+6], 2,500 +5 / -20 [+8]
-//          0.85  1,000 +2 / -10 [+8], 1,560 +10 / -3 [+14];              1.05  850 -2 / -4 [+4], 1,250 0 / -16 [+5], 1,560 +3 / -3 [+7]
-//          1.2   850 -8 / -15 [-4], 1,250 +6 / -16 [+10], 1,560 +9 / -14 [+12];  1.6  1,000 -3 / -11 [0], 1,560 +3 / -9 [+4]
-//          1.8   850 -3 / +4 [0], 1,250 +10 / -11 [+13];                 2.9   700 -8 / +9 [-5], 1,000 +3 / +4 [+5]
-//          4.5   600 -8 / +4 [-5], 700 -3 / +11 [+1];                    6.6   400 -7 / +8 [-4], 500 -2 / +17 [+1]
-//          8     400 -12 / +8 [-4], 500 -4 / +14 [0];                    12    400 -3 / +20 [-1], 500 +2 / +20 [+5]
+//   rounds 0.15  1,250 rows -42 / 0 [-53], 2,500 -17 / +11 [-52], 5,000 +9 / +22 [-51];  0.25  2,500 -15 / -1 [-31], 8,000 +25 / +36 [-31]
+//          0.4   1,560 +6 / -5 [+3], 2,500 +19 / -8 [+7];                0.6   1,560 +2 / -20 [+6], 2,500 +5 / -20 [+9]
+//          0.85  1,000 +3 / -9 [+9], 1,560 +9 / -3 [+13];                1.05  850 -3 / -4 [+2], 1,250 -1 / -16 [+4], 1,560 +3 / -3 [+7]
+//          1.2   850 -6 / -15 [-2], 1,250 +3 / -16 [+8], 1,560 +8 / -13 [+11];   1.6  1,000 -3 / -12 [0], 1,560 +5 / -10 [+4]
+//          1.8   850 -2 / +4 [+2], 1,250 +10 / -12 [+14];                2.9   700 -6 / +9 [-4], 1,000 +5 / +5 [+7]
+//          4.5   600 -6 / +7 [-3], 700 -1 / +13 [+1];                    6.6   400 -5 / +11 [-3], 500 -1 / +11 [+3]
+//          8     400 -7 / +11 [-3], 500 -3 / +11 [+4];                   12    400 -2 / +17 [0], 500 +1 / +15 [+5]
 // The lines are where equal groups, what a balanced router makes, take the same time; between 0.33 and 2 rounds they are higher, to where
 // equal groups lose up to 10 %, since Zipf groups gain up to twice that.  The host knows only the mean.  Without room below a third
 // of a round most CUs have no block of the large kernels, and these are never the faster ones (measured to 8,000 rows).  A line with room

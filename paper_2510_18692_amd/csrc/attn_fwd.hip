@@ -19,15 +19,19 @@
 
 namespace moga {
 
-// Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of 256 rows.  The lines are where
-// groups of equal size take the same time by both, or lower or higher where groups of Zipf(1.1) sizes ask for it.  Time of the small kernel
-// against the large one's, equal / Zipf:
-//   rounds 0.10 (6,550 x 1 head)  1,250 rows -4 / +63 %, 2,000 +31 / +80 %;  0.15  1,350 -8 / +72, 2,200 +27 / +84, 5,200 +91 / +129
-//          0.22                   2,000 -11 / +60, 3,400 +20 / +76;          0.30  2,200 -8 / +57, 3,800 +13 / +69
-//          0.40                   5,200 -2 / +29, 7,000 +4 / +29;            0.60  2,900 -6 / -4, 5,200 +11 / +1
-//          0.85                   3,800 +1 / -18;                            1.7   2,200 -4 / +6, 3,800 +7 / -15
-//          4    (6,550 x 40)      900 -12 / -9, 1,350 +7 / +6;               5.7   1,250 -6 / +2, 2,600 +9 / +9
-//          7                      600 -6 / +3, 750 +6 / +1, 2,200 +10 / +8;  20    600 -8 / +7, 750 +6 / +7, 2,900 +6 / +6
+// Mean rows per group below which the small-group bf16 kernel runs, by rounds of 256 blocks of 256 rows.  Time of the small kernel
+// against the large one's (blocks by large_blocks) with room to split a round, groups of equal / Zipf(1.1) sizes, in %; in brackets without room:
+//   rounds 0.15  1,560 rows -6 / +63 [-26 / -28], 2,000 +6 / +74 [-26 / -28];   0.25  2,500 -3 / +49 [-24 / -28], 3,200 +4 / +55 [-25 / -28]
+//          0.4   5,000 -2 / +21 [-26 / -28], 6,200 +4 / +23;                    0.6   3,200 +7 / -24 [+13 / -22], 5,000 +12 / -2 [+12 / -23]
+//          0.85  2,500 +8 / +1 [+13 / +3], 5,000 +7 / -18 [+10 / -17];          1.1   1,250 +11 / -16 [+18 / -15], 2,500 +21 / -20
+//          1.2   1,560 +8 / -17 [+13 / -18], 2,500 +19 / -16;                   1.6   1,560 +5 / -20 [+7 / -19], 2,500 +8 / -1
+//          2.6   1,560 +1 / 0, 2,000 +10 / -24;                                 3.4   2,000 -6 / 0, 3,200 +3 / -1
+//          4.5   1,000 -6 / -4, 1,560 +5 / +2;                                  6.6   600 -8 / +1, 700 +4 / -4
+//          8     600 -6 / +1, 700 +7 / +1;       12    600 -7 / +2, 700 +10 / 0;       20    600 -5 / +9, 700 +10 / +7
+// Below half a round and above 2.6 the lines are where groups of equal size take the same time by both.  Between, the small kernel costs
+// equal groups, what a balanced router makes, up to 20 %, and gains 16 to 24 % where groups are as unequal as Zipf's, since its finer tiles end
+// together: the lines there are those of the unequal groups, and equal ones of 1,000 rows and more pay for them.  Below a third of a round it is the other
+// way round: with room the large kernel splits a long group's keys and would be the faster one for Zipf groups down to 1,000 rows.
 // Below three quarters of a round the large kernel needs room to split its tiles; without, the line is that of the kernels unsplit.
 static int64_t small_group_rows(int64_t Nq, int H, bool split) {
   const int64_t rounds = 100 * Nq * H / (256 * kCus);   // in hundredths
