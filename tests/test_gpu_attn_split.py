@@ -36,7 +36,7 @@ def rows_close(a, b, name):
     assert ((a - b).norm(dim=-1) <= bound).all(), name
 
 
-# left: tiles of 256 query rows in the forward's last round
+# left: tiles of the forward's last round, of 256 query rows but for the last case, whose blocks have 384
 @pytest.mark.parametrize("nq,nk,H,left", [
     ([1], [1], 1, 1), ([300, 5, 70], [300, 5, 700], 1, 4),        # 8 pieces each, most of them empty
     ([200, 257, 0, 600], [500, 0, 64, 449], 3, 18),               # sides without rows
@@ -44,13 +44,14 @@ def rows_close(a, b, name):
     ([256] * 64, [130] * 64, 2, 128), ([256] * 43, [130] * 43, 3, 129),   # two pieces; none
     ([100] * 257, None, 1, 0),                                    # a round (dK/dV: and one tile)
     ([100] * 255 + [300], None, 1, 1), ([100] * 255, None, 1, 255),   # a round and one tile; a tile less than a round
-    ([3000, 2500, 100], None, 12, 20),                            # a round and more
+    ([3000, 2500, 100], None, 12, 192),                           # none (dK/dV, 192 keys: a round, and two pieces)
 ])
 def test_split_against_whole_tiles(nq, nk, H, left):
     nk = nk or nq
     if len(nq) > 256:
         nq, nk = nq[:255] + [sum(nq[255:])], nk[:255] + [sum(nk[255:])]
-    assert sum(-(-n // 256) for n in nq) * H % 256 == left
+    rows = 384 if len(nq) == 3 and nq[0] == 3000 else 256
+    assert sum(-(-n // rows) for n in nq) * H % 256 == left
     g = torch.Generator().manual_seed(len(nq) + H)
     Nq, Nk, G = sum(nq), sum(nk), len(nq)
     q, d = (torch.randn((H, Nq, 128), generator=g).to(torch.bfloat16).cuda() for _ in range(2))
@@ -64,7 +65,7 @@ def test_split_against_whole_tiles(nq, nk, H, left):
         for op, name in ((mg.OP_VARLEN_ATTN_FWD, "fwd"), (mg.OP_VARLEN_ATTN_BWD, "bwd")):
             need = mg.workspace_bytes(op, Nq, H, 128, G, 0, mg.MOGA_BF16)
             pref = lib.moga_workspace_preferred_bytes(op, Nq, Nk, H, 128, G, 0, mg.MOGA_BF16)
-            assert pref > need
+            assert pref > need and mg.attn_blocks(op, Nq, Nk, H, G, pref)[:2] == (rows, True)
             for size in (need, pref):
                 ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN wherever nothing is written
                 if name == "fwd":
@@ -113,31 +114,35 @@ def test_call_on_another_stream_takes_no_workspace_of_this_one():
         mg.set_small_group_rows(-1)
 
 
+# groups that take blocks of 256 and of 384 query rows
+@pytest.mark.parametrize("nq,rows", [([300, 900], 256), ([2083, 4412], 384)])
 @pytest.mark.parametrize("what", ["nan query", "nan key", "inf score", "all scores -inf", "inf value"])
-def test_split_keeps_nan_and_infinities(what):
+def test_split_keeps_nan_and_infinities(what, nq, rows):
     """One row of Q, K or V that is not finite: NaN and infinities come out at the same places as from whole tiles."""
-    nq, H, s = [300, 900], 2, 128 ** -0.5
+    print(what, nq, flush=True)
+    H, s = 2, 128 ** -0.5
     N = sum(nq)
     g = torch.Generator().manual_seed(7)
     q, k, v = (torch.randn((H, N, 128), generator=g) for _ in range(3))
     if what == "nan query":
         q[0, 40] = torch.nan
     elif what == "nan key":
-        k[1, 310] = torch.nan
+        k[1, nq[0] + 10] = torch.nan
     elif what == "inf score":
         k[0, 17] = 3e38
         q[0, 5] = 1.0
     elif what == "all scores -inf":
-        k[0, :300] = -k[0, :300].abs()
+        k[0, :nq[0]] = -k[0, :nq[0]].abs()
         q[0, 5] = 3e38
     else:
-        v[1, 400, 3] = torch.inf
+        v[1, nq[0] + 100, 3] = torch.inf
     q, k, v = (t.to(torch.bfloat16).cuda() for t in (q, k, v))
-    cu = torch.tensor([0, 300, N], dtype=torch.int32, device="cuda")
+    cu = torch.tensor([0, nq[0], N], dtype=torch.int32, device="cuda")
     lib, stream = mg.load(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     mg.set_small_group_rows(0)
     try:
         out = []
+        assert mg.attn_blocks(mg.OP_VARLEN_ATTN_FWD, N, N, H, 2, 1 << 30)[:2] == (rows, True)
         for size in (mg.workspace_bytes(mg.OP_VARLEN_ATTN_FWD, N, H, 128, 2, 0, mg.MOGA_BF16),
                      lib.moga_workspace_preferred_bytes(mg.OP_VARLEN_ATTN_FWD, N, N, H, 128, 2, 0, mg.MOGA_BF16)):
             ws, oh, lse = torch.empty(size, dtype=torch.uint8, device="cuda"), torch.empty_like(q), torch.empty((H, N), device="cuda")
@@ -219,4 +224,22 @@ def test_room_for_short_pieces(large_kernels):
     less, took = varlen_results(n, n, 6, lambda need, pref: need + short, whole[:2])
     assert took == [(256, True, 0, False), (256, True, 128, True)]
     for a, b, name in zip(less, whole, ("O", "lse", "dQ", "dK", "dV")):
+        rows_close(a, b, name)
+
+
+# Blocks of 384 query rows (forward, dQ) and of `keys` keys; left: their tiles in the last round
+@pytest.mark.parametrize("n,H,left,keys,keys_left", [
+    ([2083, 4412], 2, 36, 192, 68), ([3803], 6, 60, 192, 120),                      # 7 and 4 pieces; 3 and 2
+    ([6144, 6144], 4, 128, 192, 0), ([384] * 43, 3, 129, 128, 131),                 # two pieces; none
+    ([384] * 64 + [1], 4, 4, 192, 4),                                               # a round (dK/dV: two) and a few tiles
+    ([700] * 16, 12, 128, 192, 0), ([3000, 2500, 100], 12, 192, 192, 116),          # a round and more
+])
+def test_split_of_long_blocks_against_whole_tiles(large_kernels, n, H, left, keys, keys_left):
+    print(n, H, flush=True)
+    whole, none = varlen_results(n, n, H, lambda need, pref: need)
+    pieces, took = varlen_results(n, n, H, lambda need, pref: pref, whole[:2])
+    assert not any(b[1] or b[3] for b in none) and took == [(384, True, 0, False), (384, True, keys, True)]
+    assert sum(-(-i // 384) for i in n) * H % 256 == left and sum(-(-i // keys) for i in n) * H % 256 == keys_left
+    for a, b, name in zip(pieces, whole, ("O", "lse", "dQ", "dK", "dV")):
+        close(a, b, name)
         rows_close(a, b, name)

@@ -1,5 +1,5 @@
 """The bf16 attention calls choose between two sets of kernels from the mean group size (8-wave blocks
-with 256 / 128-row tiles, or 4-wave blocks with tiles half as large for small groups).  The shape cases
+of 384 or 256 query rows and 192 or 128 keys, or 4-wave blocks of 128 query rows and 64 keys for small groups).  The shape cases
 of the other GPU tests are small, so by default they all land on the small-group set: here the same
 cases (tile edges, empty groups, separate query and key lists) run with each set forced in turn, each
 against the oracle."""

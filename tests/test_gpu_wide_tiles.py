@@ -1,5 +1,6 @@
 """The large bf16 kernels at the edges of their tiles: last tiles of a group that take three columns of 16 rows per wave, two, or
-leave waves idle, with either number of query rows per block, against the oracle with the tolerances of the other bf16 cases."""
+leave waves idle, with either number of query rows and of keys per block, in pieces and whole, against the oracle with the tolerances
+of the other bf16 cases."""
 import numpy as np
 import pytest
 import torch
@@ -15,7 +16,7 @@ pytestmark = pytest.mark.gpu
 SIZES = [1, 47, 48, 49, 95, 97, 127, 128, 129, 255, 256, 257, 383, 384, 385, 639, 640, 641, 767, 769]
 
 
-# one head: 256 query rows per block; two: 384
+# in pieces, which is what the binding's workspace leads to for so few tiles
 @pytest.mark.parametrize("H", [1, 2])
 def test_forward_at_tile_edges(H):
     mg.set_small_group_rows(0)
@@ -25,14 +26,40 @@ def test_forward_at_tile_edges(H):
         mg.set_small_group_rows(-1)
 
 
-# with the key tiles' edges: 256 query rows per block (dQ); without: 384
-@pytest.mark.parametrize("more", [[], [31, 33, 63, 65, 96, 143, 144, 145, 191, 192, 193, 320, 321]], ids=["384 rows", "256 rows"])
+# in pieces; with the edges of 192-key tiles too
+@pytest.mark.parametrize("more", [[], [31, 33, 63, 65, 96, 143, 144, 145, 191, 192, 193, 320, 321]], ids=["rows", "rows and keys"])
 def test_backward_at_tile_edges(more):
     mg.set_small_group_rows(0)
     try:
         tb.test_group_attention_backward_matches_oracle(SIZES + more, 2, 128, "bf16")
     finally:
         mg.set_small_group_rows(-1)
+
+
+# Heads with which either size of block is taken; 769 keys go round the ring of four 64-key tiles three times.  moga_group_attn_fwd has no
+# room to split (every wave writes its finished rows), the others' workspace has.
+@pytest.mark.parametrize("H,room,rows", [(1, False, 256), (5, False, 256), (7, False, 384), (9, False, 384), (1, True, 256), (10, True, 384)])
+def test_forward_with_every_block_size(H, room, rows):
+    print(f"H={H} room={room}", flush=True)
+    q, k, v, cu, scale = tf.attn_case(SIZES, H, 128, "bf16", seed=H)
+    A, lse = orc.group_attention(P.to64(q), P.to64(k), P.to64(v), cu, scale)
+    N, M, lib = q.shape[0], len(SIZES), mg.load()
+    mg.set_small_group_rows(0)
+    try:
+        size = lib.moga_workspace_preferred_bytes(mg.OP_ATTN_FWD, N, N, H, 128, M, 0, mg.MOGA_BF16) if room else 0
+        assert mg.attn_blocks(mg.OP_ATTN_FWD, N, N, H, M, size)[:2] == (rows, room)
+        hat = lambda t: t.permute(1, 0, 2).contiguous().cuda()
+        qh, kh, vh, cu_d = hat(q), hat(k), hat(v), torch.from_numpy(cu).cuda()
+        ws = torch.full((max(size, 16),), 0xFF, dtype=torch.uint8, device="cuda")
+        oh, l = torch.empty_like(qh), torch.empty((H, N), device="cuda")
+        fn = lib.moga_group_attn_fwd_ws if room else lib.moga_group_attn_fwd
+        assert fn(qh.data_ptr(), kh.data_ptr(), vh.data_ptr(), mg.MOGA_BF16, N, H, 128, cu_d.data_ptr(), M, scale, oh.data_ptr(), l.data_ptr(),
+                  ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+    finally:
+        mg.set_small_group_rows(-1)
+    P.assert_close_bf16(P.unhat(oh), A, "O")
+    np.testing.assert_allclose(P.to64(l).T, lse, rtol=1e-3, atol=2e-3)
 
 
 def backward_at_edges(sizes, H, room):
@@ -72,7 +99,7 @@ def test_backward_with_every_block_size(H, room, blocks):
 
 # token-order rows gathered by the kernels: the blocks of a call that does not split
 @pytest.mark.parametrize("H", [1, 5, 7, 9])
-def test_gather_fused_backward_with_every_block_size(H):
+def test_gather_fused_calls_with_every_block_size(H):
     print(f"fused H={H}", flush=True)
     q, k, v, d_o, cu, scale = tb.attn_bwd_case(SIZES, H, 128, "bf16", seed=H + 20)   # sorted order
     N = q.shape[0]
@@ -86,6 +113,9 @@ def test_gather_fused_backward_with_every_block_size(H):
     o = tok(torch.from_numpy(A * gs).bfloat16()).cuda()
     inv = torch.empty(N, dtype=torch.int32)
     inv[perm] = torch.arange(N, dtype=torch.int32)
+    o_got, lse_got = mg.moga_fused_attn_fwd(*(tok(t).cuda() for t in (q, k, v)), perm.int().cuda(), gate.cuda(), torch.from_numpy(cu).cuda(), scale)
+    P.assert_close_bf16(P.to64(o_got.cpu()[perm]), A * gs, "O")
+    np.testing.assert_allclose(P.to64(lse_got).T, lse, rtol=1e-3, atol=2e-3)
     *got, d_gate = mg.moga_fused_attn_bwd(*(tok(t).cuda() for t in (d_o, q, k, v)), o, torch.from_numpy(np.ascontiguousarray(lse.T)).float().cuda(),
                                           perm.int().cuda(), inv.cuda(), gate.cuda(), torch.from_numpy(cu).cuda(), scale)
     torch.cuda.synchronize()
