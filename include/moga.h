@@ -74,7 +74,7 @@ size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, int d_model,
  * the room it has):
  * moga_group_attn_fwd_ws (MOGA_OP_ATTN_FWD), moga_group_attn_bwd, their _tokens forms and the moga_varlen_* calls.  A split row is
  * summed in pieces, so its rounding differs from that of a call with less room: results repeat bit by bit between calls
- * that both have these bytes, or both less.  Host-only.
+ * that both have these bytes, or the same number of fewer.  Host-only.
  */
 size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, int H, int D, int M, int d_model, int dtype);
 
@@ -228,8 +228,8 @@ void moga_debug_set_spin_limit(int polls);
  * group size N / M and the rounds of 256 256-row tiles (forward: below 5632 rows up to half a round, 6144 up to one, 2560 up to 3.7, 1300 up
  * to 6, else 700, and with room to split a round 1500 up to 0.2, 2700 up to 0.33, 4500 from 0.5 to 0.75; backward: below 2000 up to 0.75
  * rounds, 1450 up to one, 1300 up to 2, 860 up to 3.5, 650 up to 6, 450 up to 10, else 400, but up to 0.33 8192, or 2800 with room to split a
- * round; the moga_fused_* calls always take the first set).  Both sets
- * give the same results up to rounding order.
+ * round; the moga_fused_* calls always take the first set).  Of the large
+ * kernels' two sizes of block a call takes the one that the price of its rounds makes faster.  All give the same results up to rounding order.
  * moga_debug_set_small_group_rows overrides all thresholds (0: never the small
  * kernels; a huge value: always; negative: the defaults) so that tests can run either set on any shape.
  */

@@ -203,7 +203,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
   if (dtype == MOGA_BF16) {
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
-    // two-slot ring, two blocks per CU, and tiles half as large; the host only knows the mean group size
+    // two-slot ring, two blocks per CU, and smaller tiles; the host only knows the mean group size
     const AttnPlan plan = bwd_plan(Nq, Nk, H, M, split.rows);
     const bool small = plan.small;
     const int bk = plan.k.rows, bm = plan.q.rows;

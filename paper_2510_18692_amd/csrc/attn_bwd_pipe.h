@@ -1,9 +1,9 @@
 // bf16 backward kernels of the group attention (head_dim 128) on the LDS ring of attn_pipe.h.
 //
-//   attn_bwd_dq_pipe_kernel   : a wave owns 48 query rows (Q, dO fragments, lse, delta and
+//   attn_bwd_dq_pipe_kernel   : a wave owns 48 (or 32) query rows (Q, dO fragments, lse, delta and
 //                               the dQ^T accumulators in registers) and sweeps 64-key tiles of
 //                               K and V; three MFMA products per tile (S^T, dP^T, dQ^T).
-//   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 48 key rows and sweeps 64-query
+//   attn_bwd_dkdv_ab_kernel   : a pair of waves on one SIMD owns 48 (or 32) key rows and sweeps 64-query
 //                               tiles of Q, dO, lse and delta; one wave computes S, P and dV^T,
 //                               the other dP, dS and dK^T (P handed over through LDS).
 // Tiles are streamed global -> LDS by direct-to-LDS loads into a ring of four slots, two tiles
@@ -121,7 +121,7 @@ __device__ __forceinline__ void dq_step(unsigned& nat, const unsigned (&tr)[2], 
   }
 }
 
-// Gradient rows of a wave (columns r and 16 + r of its 32 rows from row0), times f: to `out` (sorted order, or token order in
+// Gradient rows of a wave (columns r, 16 + r .. of its 16 NC rows from row0), times f: to `out` (sorted order, or token order in
 // gather mode) and, not in gather mode, to `tok` in token order; either may be NULL.
 template <bool GATHER, int NC>
 __device__ __forceinline__ void store_gradient(const floatx4_t (&acc)[8][NC], float f, int row0, int ge, int head, int64_t head_off,
@@ -766,7 +766,7 @@ __device__ __forceinline__ void attn_bwd_dkdv_block(
       for (int k = 0; k < NC; ++k) acc[dt][k] = floatx4_t{0.f, 0.f, 0.f, 0.f};
 
     const int nfull = n >> 6;   // tiles whose 64 queries are all inside the group
-    // a pair whose 32 key rows lie past the end of the group (both of its waves) only moves its share of the tiles
+    // a pair whose key rows all lie past the end of the group (both of its waves) only moves its share of the tiles
     const bool active = k0w < ge;
     int T = 0;
     if constexpr (NB == 4) {

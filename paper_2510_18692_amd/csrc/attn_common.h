@@ -168,10 +168,10 @@ __device__ __forceinline__ void split_range(const WorkTile& s, int& first, int& 
   n = end - 64 * t0;
 }
 
-// A wave's 32 result columns as fp32 rows of a slot; `base` is the wave's first row.
-__device__ __forceinline__ void store_partial(float* base, int dt, int col_half, const floatx4_t& v) {
+// Column `col` (16 result rows) of a wave, d tile dt, as fp32 rows of a slot; `base` is the wave's first row.
+__device__ __forceinline__ void store_partial(float* base, int dt, int col, const floatx4_t& v) {
   const int lane = threadIdx.x & 63;
-  *(floatx4_t*)(base + (16 * col_half + (lane & 15)) * kHeadDim + 16 * dt + 4 * (lane >> 4)) = v;
+  *(floatx4_t*)(base + (16 * col + (lane & 15)) * kHeadDim + 16 * dt + 4 * (lane >> 4)) = v;
 }
 
 // A round of pieces of `rows` result rows each (dV and dK: of both), 34 MB for 256 and 51 MB for 384: results, then (max, sum) of the forward.
@@ -313,8 +313,8 @@ AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room);
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or
 // column (B) r at k = 8 g .. 8 g + 7, and rows 4 g .. 4 g + 3 of column r of the result.  At the board's power cap a
 // register-resident loop of random operands reaches 1.94-2.18 PFLOP/s (card to card) with this shape and 1.83-1.86 with 32x32x16
-// (whose accumulators are read and written twice as often per product), and an A fragment from LDS still feeds 32
-// columns when a wave keeps two B fragments.
+// (whose accumulators are read and written twice as often per product), and an A fragment from LDS feeds 16 columns for every B
+// fragment that a wave keeps (two or three).
 __device__ __forceinline__ floatx4_t mfma16(bf16x8_t a, bf16x8_t b, floatx4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }

@@ -1,7 +1,7 @@
 // Variable-length attention inside groups (Alg. 1 step 3 of the paper; Eq. 1 per group/head).
 //
 // bf16 kernel, head_dim 128, 16x16x32 bf16 MFMA:
-//   * scores are computed transposed, S^T = K Q^T, so that each lane owns two query columns:
+//   * scores are computed transposed, S^T = K Q^T, so that each lane owns two or three query columns:
 //     their softmax statistics are per-lane scalars, and the four lanes of a query only meet when
 //     its maximum is raised and at the end;
 //   * the K rows fed to the MFMA are permuted (attn_common.h, step_row) so a lane's eight scores of a

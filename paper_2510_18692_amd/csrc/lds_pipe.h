@@ -6,13 +6,6 @@
 
 namespace moga {
 
-// Transposed LDS read: the 16 lanes of a block each point at 4 consecutive bf16; lane i gets,
-// for e = 0..3, element i%4 of the 4 bf16 that lane 4e + i/4 pointed at.
-__device__ __forceinline__ short4_t lds_read_tr16(const unsigned short* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (short4_t __attribute__((address_space(3)))*)(p));
-}
-
 // Direct global -> LDS load of 16 bytes per lane: the wave writes 1 KB starting at the
 // wave-uniform LDS byte address `lds_wave_base`, lane i at byte 16*i.  Issued through inline
 // assembly so that the compiler does not make later LDS reads of *other* buffers wait for it;
@@ -60,6 +53,8 @@ __device__ __forceinline__ void lds_dma16_soff(const void* base, unsigned byte_o
 __device__ __forceinline__ bf16x8_t lds_read_b128(unsigned addr) {
   return *(const bf16x8_t __attribute__((address_space(3)))*)(uintptr_t)addr;
 }
+// Transposed LDS read: the 16 lanes of a block each point at 4 consecutive bf16; lane i gets,
+// for e = 0..3, element i%4 of the 4 bf16 that lane 4e + i/4 pointed at.
 __device__ __forceinline__ short4_t lds_read_tr16_addr(unsigned addr) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4_t __attribute__((address_space(3)))*)(uintptr_t)addr);
 }

@@ -442,7 +442,7 @@ Command (from the repository root on one MI355X):
     python -m paper_2510_18692_amd.profiling energy --out profiles/mfma_energy_probe.md
 
 `moga_bench_mix_loop` (libmoga_bench.so): 256 blocks of 8 waves (two per SIMD), {reps} launches of {iters} iterations of
-8 pairs of register-resident 16x16x32 bf16 MFMAs per wave (a pair shares its A operand, as in the attention kernels); per
+8 pairs of register-resident 16x16x32 bf16 MFMAs per wave (a pair shares its A operand); per
 pair the stated number of 1 KB LDS fragment reads (16 bytes per
 lane, conflict-free, the fragment is the A or B operand six pairs later), fp32 fmas and exp2s.  Power: hwmon
 `power1_input` sampled every 10 ms during the launches (cap {cap} W, idle {idle} W).  "busy x GHz" = MFMA pipe cycles
@@ -455,8 +455,8 @@ per SIMD per nanosecond (2.4 = every cycle of the top clock).  J/PFLOP = board p
 On random operands the power management trades clock for switching activity, so the rate is set by the energy per
 pair and its companions.  Differences against the plain loop
 ({jpf(base):.0f} J/PFLOP): one 1 KB LDS fragment read per pair costs {lds1:.0f} J/PFLOP ({100 * lds1 / jpf(base):.0f} % of a pair), one fma
-{fma1:.0f} ({100 * fma1 / jpf(base):.1f} %), one exp2 {exp1:.0f} ({100 * exp1 / jpf(base):.1f} %).  The forward kernel reads one 1 KB fragment and evaluates one
-exp2 per pair (32 rows per wave).
+{fma1:.0f} ({100 * fma1 / jpf(base):.1f} %), one exp2 {exp1:.0f} ({100 * exp1 / jpf(base):.1f} %).  The forward kernel reads 0.63 fragments and evaluates 0.94 exp2
+per pair with 48 rows per wave, where a fragment feeds three products, and 0.94 fragments with 32.
 """
     open(args.out, "w").write(txt)
     print(txt)
