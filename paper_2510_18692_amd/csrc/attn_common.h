@@ -273,8 +273,10 @@ inline int64_t max_tiles(int64_t N, int M, int rows_per_tile) {
 // Constants from 374 calls of equal groups, 0.07 to 21 rounds of 256 blocks, groups of 500 to 20,000 rows, either size of block forced: where
 // these kernels run by default the choice is the faster one or within (mean / worst) 0.3 / 8 % forward, 0.1 / 3 % by dK/dV, and of the whole
 // backward 0.5 / 6 % by dQ, split or not (by whole rounds only 0.7 / 10, 0.2 / 6 and 0.5 / 6).  The host knows the
-// mean group only and takes it for all; 172 calls of Zipf(1.1) groups, where the largest decides: forward 4 % on average without a split, 5 with
-// (256 always 3 and 5, 384 always 17 and 8).  Milliseconds with 256 and 384 rows, forward without a split: 5,000 x 3 heads, 5 groups 0.029 and
+// mean group only and takes it for all.  Where groups are unequal the longest block may be the whole call's time: from two to four rounds of
+// 256-row blocks 384 rows took Zipf(1.1) groups 9 % more time than 256 without a split and 11 % with, up to 36 %, and gained 3 % with equal
+// groups, so there they have to be a fifth cheaper (nobody slower on average, at worst 2 %).  Over 172 calls of Zipf(1.1) groups the
+// choice is within 4 % of the faster one forward, 2 % backward.  Milliseconds with 256 and 384 rows, forward without a split: 5,000 x 3 heads, 5 groups 0.029 and
 // 0.039; 7,000 x 4, 2 groups 0.081 and 0.111; 40,000 x 3, 4 groups 0.52 and 0.65; 99,840 x 12, 16 groups 3.33 and 3.09.
 struct Blocks {
   int rows;
@@ -295,7 +297,8 @@ inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int 
     return in_step * weight * (full * block + last) + (1 - in_step) * ((weight * tiles - short_end) / kCus * block + weight * last / 2) +
            (pieces > 1 ? 10 * kMergeRows : 0);
   };
-  const int rows = cost(few, 10) < cost(few / 2 * 3, 13) ? few : few / 2 * 3;
+  const bool by_far = arrays == 1 && N * H >= 2 * 256 * kCus && N * H < 4 * 256 * kCus;
+  const int rows = cost(few, 10) < (by_far ? 1.2 : 1.) * cost(few / 2 * 3, 13) ? few : few / 2 * 3;
   return {rows, splits(rows)};
 }
 inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nq, Nk, H, M, 256, 1, room); }

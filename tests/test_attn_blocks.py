@@ -18,7 +18,8 @@ def blocks(op, N, H, M, ws):
 # N, H, M, query rows where no last round is split: 256 and 384 rows take as many rounds, or 384 fewer
 @pytest.mark.parametrize("N,H,M,rows", [
     (5000, 3, 5, 256), (7000, 4, 2, 256), (8348, 12, 8, 256), (40000, 3, 4, 256), (32760, 4, 4, 256), (32760, 4, 8, 256),
-    (16384, 4, 2, 256), (8000, 3, 1, 256), (12000, 12, 3, 384), (62400, 12, 5, 384), (99840, 40, 16, 384), (580320, 40, 32, 384),
+    (16384, 4, 2, 256), (8000, 3, 1, 256), (12000, 12, 3, 256), (62400, 12, 5, 384), (99840, 40, 16, 384), (580320, 40, 32, 384),
+    (48985, 3, 8, 256), (54990, 4, 16, 256),      # 2.2 and 3.4 rounds: 384 rows not by far cheaper
     (12750, 40, 15, 384), (13000, 40, 13, 384),   # more whole rounds than with 256 rows by price, out of step by then
 ])
 def test_query_rows_of_calls_that_cannot_split(large_kernels, N, H, M, rows):

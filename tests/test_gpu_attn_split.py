@@ -232,7 +232,7 @@ def test_room_for_short_pieces(large_kernels):
     ([2083, 4412], 2, 36, 192, 68), ([3803], 6, 60, 192, 120),                      # 7 and 4 pieces; 3 and 2
     ([6144, 6144], 4, 128, 192, 0), ([384] * 43, 3, 129, 128, 131),                 # two pieces; none
     ([384] * 64 + [1], 4, 4, 192, 4),                                               # a round (dK/dV: two) and a few tiles
-    ([700] * 16, 12, 128, 192, 0), ([3000, 2500, 100], 12, 192, 192, 116),          # a round and more
+    ([700] * 15, 12, 104, 192, 208), ([3000, 2500, 100], 12, 192, 192, 116),        # a round and more
 ])
 def test_split_of_long_blocks_against_whole_tiles(large_kernels, n, H, left, keys, keys_left):
     print(n, H, flush=True)
