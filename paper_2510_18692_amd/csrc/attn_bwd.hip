@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void attn_bwd_fused_prepass_kernel(
 //          0.4   1,560 +6 / -5 [+3], 2,500 +19 / -8 [+7];                0.6   1,560 +2 / -20 [+6], 2,500 +5 / -20 [+9]
 //          0.85  1,000 +3 / -9 [+9], 1,560 +9 / -3 [+13];                1.05  850 -3 / -4 [+2], 1,250 -1 / -16 [+4], 1,560 +3 / -3 [+7]
 //          1.2   850 -6 / -15 [-2], 1,250 +3 / -16 [+8], 1,560 +8 / -13 [+11];   1.6  1,000 -3 / -12 [0], 1,560 +5 / -10 [+4]
-//          1.8   850 -2 / +4 [+2], 1,250 +10 / -12 [+14];                2.9   700 -6 / +9 [-4], 1,000 +5 / +5 [+7]
+//          1.8   850 -2 / +4 [+2], 1,250 +10 / -12 [+14];                2.9   700 -5 / +8 [-1], 1,000 +4 / +4 [+5]
 //          4.5   600 -6 / +7 [-3], 700 -1 / +13 [+1];                    6.6   400 -5 / +11 [-3], 500 -1 / +11 [+3]
 //          8     400 -7 / +11 [-3], 500 -3 / +11 [+4];                   12    400 -2 / +17 [0], 500 +1 / +15 [+5]
 // The lines are where equal groups, what a balanced router makes, take the same time; between 0.33 and 2 rounds they are higher, to where

@@ -25,10 +25,10 @@ namespace moga {
 //          0.4   5,000 -2 / +21 [-26 / -28], 6,200 +4 / +23;                    0.6   3,200 +7 / -24 [+13 / -22], 5,000 +12 / -2 [+12 / -23]
 //          0.85  2,500 +8 / +1 [+13 / +3], 5,000 +7 / -18 [+10 / -17];          1.1   1,250 +11 / -16 [+18 / -15], 2,500 +21 / -20
 //          1.2   1,560 +8 / -17 [+13 / -18], 2,500 +19 / -16;                   1.6   1,560 +5 / -20 [+7 / -19], 2,500 +8 / -1
-//          2.6   1,560 +1 / 0, 2,000 +10 / -24;                                 3.4   2,000 -6 / 0, 3,200 +3 / -1
+//          2.6   1,560 +1 / 0, 2,000 +4 / -1;                                   3.4   2,000 -4 / +2, 3,200 +2 / +2
 //          4.5   1,000 -6 / -4, 1,560 +5 / +2;                                  6.6   600 -8 / +1, 700 +4 / -4
 //          8     600 -6 / +1, 700 +7 / +1;       12    600 -7 / +2, 700 +10 / 0;       20    600 -5 / +9, 700 +10 / +7
-// Below half a round and above 2.6 the lines are where groups of equal size take the same time by both.  Between, the small kernel costs
+// Below half a round and above two the lines are where groups of equal size take about the same time by both.  Between, the small kernel costs
 // equal groups, what a balanced router makes, up to 20 %, and gains 16 to 24 % where groups are as unequal as Zipf's, since its finer tiles end
 // together: the lines there are those of the unequal groups, and equal ones of 1,000 rows and more pay for them.  Below a third of a round it is the other
 // way round: with room the large kernel splits a long group's keys and would be the faster one for Zipf groups down to 1,000 rows.
