@@ -267,6 +267,15 @@ int moga_route_bwd_balanced(const void* x, int x_dtype, const float* w, const fl
                             void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * The two calls above (frac NULL: moga_route_bwd, and alpha, d_loss and d_loss_device_or_null are not read) with d_x in the type
+ * dx_dtype: MOGA_BF16 writes the fp32 values of the other calls rounded to nearest even.
+ */
+int moga_route_bwd_typed(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group,
+                         const float* gate, const float* d_gate, const float* frac_or_null, float alpha, float d_loss,
+                         const float* d_loss_device_or_null, int64_t N, int d_model, int M, float* d_w, void* d_x_or_null,
+                         int dx_dtype, void* ws, size_t ws_bytes, void* stream);
+
+/*
  * Alg. 1 steps 3-4 without materialising the permuted tensors: the kernel loads the rows of group g
  * through perm (row j of the sorted order is token perm[j]) from the token-order tensors
  * q, k, v [N, H, D], and writes o[perm[j]][h][:] = gate[perm[j]] * attention row j (Eq. 5) in

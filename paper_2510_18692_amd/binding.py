@@ -57,6 +57,8 @@ _SIGNATURES = {
                               _sz, _vp]),
     "moga_route_bwd_balanced": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _f32, _f32, _vp, _i64, _i32, _i32, _vp, _vp, _vp,
                                        _sz, _vp]),
+    "moga_route_bwd_typed": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _f32, _f32, _vp, _i64, _i32, _i32, _vp, _vp, _i32, _vp,
+                                    _sz, _vp]),
     "moga_fused_attn_fwd": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _i32, _f32, _vp, _vp, _vp]),
     "moga_fused_attn_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i32, _f32,
                                    _vp, _vp, _vp, _vp, _vp, _sz, _vp]),

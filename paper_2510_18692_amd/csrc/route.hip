@@ -615,10 +615,28 @@ __global__ __launch_bounds__(512) void route_bwd_dw_reduce_kernel(const float* _
   }
 }
 
+// dX as fp32 or rounded to bf16: 4 or 8 adjacent columns of a row leave as one store of 8 or 16 bytes.
+template <int COLS>
+__device__ __forceinline__ void store_dx(float* p, const float (&v)[COLS]) {
+#pragma unroll
+  for (int i = 0; i < COLS; i += 4) *(floatx4_t*)(p + i) = floatx4_t{v[i], v[i + 1], v[i + 2], v[i + 3]};
+}
+template <int COLS>
+__device__ __forceinline__ void store_dx(unsigned short* p, const float (&v)[COLS]) {
+  unsigned u[COLS / 2];
+#pragma unroll
+  for (int i = 0; i < COLS; i += 2) u[i / 2] = pack_bf16x2(v[i], v[i + 1]);
+  if constexpr (COLS == 8) *(uintx4_t*)p = uintx4_t{u[0], u[1], u[2], u[3]};
+  else *(uintx2_t*)p = uintx2_t{u[0], u[1]};
+}
+__device__ __forceinline__ void store_dx1(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store_dx1(unsigned short* p, float v) { *p = f32_to_bf16_bits(v); }
+
+template <typename OT>
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
     const float* __restrict__ w, const float* __restrict__ probs,
     const int32_t* __restrict__ group, const float* __restrict__ gate,
-    GateGrad gg, int64_t N, int d, int M, float* __restrict__ d_x) {
+    GateGrad gg, int64_t N, int d, int M, OT* __restrict__ d_x) {
   __shared__ float s_dr[kRbTok][kRbMB];
   const int c = blockIdx.y * 256 + threadIdx.x;
   const int64_t tb = (int64_t)blockIdx.x * kRbTok;
@@ -653,37 +671,41 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
   if (c < d) {
 #pragma unroll
     for (int ti = 0; ti < kRbTok; ++ti)
-      if (ti < nt) d_x[(tb + ti) * (int64_t)d + c] = out[ti];
+      if (ti < nt) store_dx1(d_x + (tb + ti) * (int64_t)d + c, out[ti]);
   }
 }
 
-// dX for M <= 32 and d a multiple of 4: a thread owns four adjacent columns and keeps their 32
-// weights in registers; a block sweeps kDxTokens tokens in tiles of kRbTok, whose dr rows are staged
-// in LDS and read back as broadcast 16-byte pieces (8 LDS reads for 128 FMAs per token).  Every
-// output row leaves as 16-byte stores, 1 KB contiguous per wave.  Sums run over the groups in
-// ascending order: exact fp32 FMA chains, the same for every launch.
-constexpr int kDxTokens = 512;   // tokens per block
+// dX for M <= 32 and d a multiple of 4: a thread owns COLS adjacent columns and keeps their MW >= M weights in registers; a block
+// sweeps `tokens` tokens in tiles of kDxTile, whose dr rows are staged in LDS and read back as broadcast 16-byte pieces.  A wave's
+// store of a row is 512 bytes or 1 KB.  Sums run over the groups in ascending order: exact fp32 FMA chains, the same for every launch.
+// Bound by its stores.  With 32 weights per column whatever M is, 512 tokens per block whatever N is, and the rounding to bf16 left to a
+// pass of its own, the two took 348 us at 62,400 x 1536, 5 groups (now some 45); a training step of 1,560 tokens x 4 heads
+// (x 512, 8 groups) 282 us (now 110), of 9,000 x 12 (x 1536, 10) 607 (374), of 20,000 x 40 (x 5120, 20) 2,625 (2,389).
+constexpr int kDxTile = 32;
 
+template <typename OT, int MW, int COLS>
 __global__ __launch_bounds__(256) void route_bwd_dx_cols_kernel(
-    const float* __restrict__ w, const float* __restrict__ probs,
-    const int32_t* __restrict__ group, const float* __restrict__ gate,
-    GateGrad gg, int64_t N, int d, int M, float* __restrict__ d_x) {
-  __shared__ __attribute__((aligned(16))) float s_dr[kRbTok][32];
-  const int c0 = (blockIdx.y * 256 + threadIdx.x) * 4;
+    const float* __restrict__ w, const float* __restrict__ probs, const int32_t* __restrict__ group, const float* __restrict__ gate,
+    GateGrad gg, int64_t N, int d, int M, int tokens, OT* __restrict__ d_x) {
+  __shared__ __attribute__((aligned(16))) float s_dr[kDxTile][MW];
+  const int c0 = (blockIdx.y * blockDim.x + threadIdx.x) * COLS;
   const bool valid = c0 < d;
-  floatx4_t wreg[32];
+  float wreg[MW][COLS];
 #pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const floatx4_t z = {0.f, 0.f, 0.f, 0.f};
-    wreg[j] = (valid && j < M) ? *(const floatx4_t*)(w + (int64_t)j * d + c0) : z;
-  }
-  const int64_t t_begin = (int64_t)blockIdx.x * kDxTokens;
-  const int64_t t_end = min(N, t_begin + kDxTokens);
-  for (int64_t tb = t_begin; tb < t_end; tb += kRbTok) {
-    const int nt = (int)min((int64_t)kRbTok, t_end - tb);
+  for (int j = 0; j < MW; ++j)
+#pragma unroll
+    for (int i = 0; i < COLS; i += 4) {
+      const floatx4_t v = valid && j < M ? *(const floatx4_t*)(w + (int64_t)j * d + c0 + i) : floatx4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wreg[j][i + e] = v[e];
+    }
+  const int64_t t_begin = (int64_t)blockIdx.x * tokens;
+  const int64_t t_end = min(N, t_begin + tokens);
+  for (int64_t tb = t_begin; tb < t_end; tb += kDxTile) {
+    const int nt = (int)min((int64_t)kDxTile, t_end - tb);
     __syncthreads();
-    for (int idx = threadIdx.x; idx < kRbTok * 32; idx += 256) {
-      const int ti = idx >> 5, j = idx & 31;
+    for (int idx = threadIdx.x; idx < kDxTile * MW; idx += blockDim.x) {
+      const int ti = idx / MW, j = idx % MW;
       float v = 0.f;
       if (ti < nt && j < M) {
         const int64_t tok = tb + ti;
@@ -697,20 +719,18 @@ __global__ __launch_bounds__(256) void route_bwd_dx_cols_kernel(
     __syncthreads();
     if (valid) {
       for (int ti = 0; ti < nt; ++ti) {
-        floatx4_t acc = {0.f, 0.f, 0.f, 0.f};
+        float acc[COLS];
 #pragma unroll
-        for (int j4 = 0; j4 < 8; ++j4) {
-          const floatx4_t r = *(const floatx4_t*)&s_dr[ti][4 * j4];
+        for (int i = 0; i < COLS; ++i) acc[i] = 0.f;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const floatx4_t wv = wreg[4 * j4 + e];
-            acc[0] = fmaf(r[e], wv[0], acc[0]);
-            acc[1] = fmaf(r[e], wv[1], acc[1]);
-            acc[2] = fmaf(r[e], wv[2], acc[2]);
-            acc[3] = fmaf(r[e], wv[3], acc[3]);
-          }
+        for (int j4 = 0; j4 < MW; j4 += 4) {
+          const floatx4_t r = *(const floatx4_t*)&s_dr[ti][j4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < COLS; ++i) acc[i] = fmaf(r[e], wreg[j4 + e][i], acc[i]);
         }
-        *(floatx4_t*)(d_x + (tb + ti) * (int64_t)d + c0) = acc;
+        store_dx<COLS>(d_x + (tb + ti) * (int64_t)d + c0, acc);
       }
     }
   }
@@ -947,11 +967,46 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
   return launch_status();
 }
 
+// Blocks of dX: threads of a block so that the fewest lie past the last column (the most of those), and tokens so that there are some
+// 8,192 waves, 16 to 512 of them: 1,560 x 512, 8 groups ran on four blocks of 512 tokens.
+template <int MW, int COLS, typename OT>
+static void launch_dx_cols(const float* w, const float* probs, const int32_t* group, const float* gate, const GateGrad& gg, int64_t N,
+                           int d, int M, OT* d_x, hipStream_t st) {
+  const int cols = (d + COLS - 1) / COLS;
+  int threads = 256;
+  for (int t = 192; t >= 64; t -= 64)
+    if ((cols + t - 1) / t * t < (cols + threads - 1) / threads * threads) threads = t;
+  const int slabs = (cols + threads - 1) / threads;
+  int64_t tokens = (N * slabs * (threads / 64) / 8192 + 15) / 16 * 16;
+  tokens = std::min<int64_t>(512, std::max<int64_t>(16, tokens));
+  route_bwd_dx_cols_kernel<OT, MW, COLS><<<dim3((unsigned)((N + tokens - 1) / tokens), slabs), threads, 0, st>>>(w, probs, group, gate, gg, N,
+                                                                                                           d, M, (int)tokens, d_x);
+}
+template <typename OT>
+static void launch_dx(const float* w, const float* probs, const int32_t* group, const float* gate, const GateGrad& gg, int64_t N, int d,
+                      int M, OT* d_x, hipStream_t st) {
+  constexpr bool kHalf = sizeof(OT) == 2;
+  const bool wide = kHalf && d % 8 == 0 && aligned16(d_x);   // 16-byte stores of bf16
+  if (M > 32 || d % 4 != 0 || ((uintptr_t)d_x & (4 * sizeof(OT) - 1)) != 0 || !aligned16(w)) {
+    route_bwd_dx_kernel<<<dim3((unsigned)((N + kRbTok - 1) / kRbTok), (d + 255) / 256), 256, 0, st>>>(w, probs, group, gate, gg, N, d, M, d_x);
+  } else if (M > 16) {
+    launch_dx_cols<32, 4>(w, probs, group, gate, gg, N, d, M, d_x, st);   // with 8 columns 256 weights, which do not fit the registers
+  } else if (wide) {
+    if (M <= 8) launch_dx_cols<8, 8>(w, probs, group, gate, gg, N, d, M, d_x, st);
+    else launch_dx_cols<16, 8>(w, probs, group, gate, gg, N, d, M, d_x, st);
+  } else if (M <= 8) {
+    launch_dx_cols<8, 4>(w, probs, group, gate, gg, N, d, M, d_x, st);
+  } else {
+    launch_dx_cols<16, 4>(w, probs, group, gate, gg, N, d, M, d_x, st);
+  }
+}
+
 static int launch_route_bwd(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group, const float* gate,
-                            const GateGrad& gg, int64_t N, int d_model, int M, float* d_w, float* d_x, void* ws, size_t ws_bytes,
-                            void* stream) {
+                            const GateGrad& gg, int64_t N, int d_model, int M, float* d_w, void* d_x, int dx_dtype, void* ws,
+                            size_t ws_bytes, void* stream) {
   if (N < 0 || d_model < 1 || M < 1) return MOGA_ERR_INVALID_ARG;
   if (x_dtype != MOGA_F32 && x_dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
+  if (d_x && dx_dtype != MOGA_F32 && dx_dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
   if (M > MOGA_MAX_GROUPS || N >= ((int64_t)1 << 31)) return MOGA_ERR_UNSUPPORTED;
   if (d_model > (1 << 24)) return MOGA_ERR_UNSUPPORTED;
   if (!d_w) return MOGA_ERR_INVALID_ARG;
@@ -1006,13 +1061,8 @@ static int launch_route_bwd(const void* x, int x_dtype, const float* w, const fl
     route_bwd_dw_reduce_kernel<false><<<(unsigned)((md + 63) / 64), 512, 0, st>>>(partial, splits, md, d_model, M, M, d_w);
   }
   if (d_x) {
-    if (M <= 32 && d_model % 4 == 0 && aligned16(d_x) && aligned16(w)) {
-      dim3 gx((unsigned)((N + kDxTokens - 1) / kDxTokens), (d_model + 1023) / 1024);
-      route_bwd_dx_cols_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, gg, N, d_model, M, d_x);
-    } else {
-      dim3 gx((unsigned)((N + kRbTok - 1) / kRbTok), (d_model + 255) / 256);
-      route_bwd_dx_kernel<<<gx, 256, 0, st>>>(w, probs, group, gate, gg, N, d_model, M, d_x);
-    }
+    if (dx_dtype == MOGA_BF16) launch_dx(w, probs, group, gate, gg, N, d_model, M, (unsigned short*)d_x, st);
+    else launch_dx(w, probs, group, gate, gg, N, d_model, M, (float*)d_x, st);
   }
   return launch_status();
 }
@@ -1021,8 +1071,8 @@ extern "C" int moga_route_bwd(const void* x, int x_dtype, const float* w, const 
                               const int32_t* group, const float* gate, const float* d_gate,
                               int64_t N, int d_model, int M, float* d_w, float* d_x,
                               void* ws, size_t ws_bytes, void* stream) {
-  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, nullptr, 0.f, nullptr}, N, d_model, M, d_w, d_x, ws,
-                          ws_bytes, stream);
+  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, nullptr, 0.f, nullptr}, N, d_model, M, d_w, d_x,
+                          MOGA_F32, ws, ws_bytes, stream);
 }
 
 extern "C" int moga_route_bwd_balanced(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group,
@@ -1031,6 +1081,15 @@ extern "C" int moga_route_bwd_balanced(const void* x, int x_dtype, const float* 
                                        size_t ws_bytes, void* stream) {
   if (N > 0 && !frac) return MOGA_ERR_INVALID_ARG;
   const float coef = N > 0 ? (float)((double)d_loss * (double)alpha * (double)M / (double)N) : 0.f;   // as moga_balance_loss_bwd
-  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, frac, coef, d_loss_dev}, N, d_model, M, d_w, d_x, ws,
-                          ws_bytes, stream);
+  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, frac, coef, d_loss_dev}, N, d_model, M, d_w, d_x,
+                          MOGA_F32, ws, ws_bytes, stream);
+}
+
+extern "C" int moga_route_bwd_typed(const void* x, int x_dtype, const float* w, const float* probs, const int32_t* group,
+                                    const float* gate, const float* d_gate, const float* frac, float alpha, float d_loss,
+                                    const float* d_loss_dev, int64_t N, int d_model, int M, float* d_w, void* d_x, int dx_dtype,
+                                    void* ws, size_t ws_bytes, void* stream) {
+  const float coef = frac && N > 0 ? (float)((double)d_loss * (double)alpha * (double)M / (double)N) : 0.f;
+  return launch_route_bwd(x, x_dtype, w, probs, group, gate, GateGrad{d_gate, frac, coef, frac ? d_loss_dev : nullptr}, N, d_model, M,
+                          d_w, d_x, dx_dtype, ws, ws_bytes, stream);
 }

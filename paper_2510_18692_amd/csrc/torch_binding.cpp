@@ -275,42 +275,43 @@ Tensor device_scalar(const Tensor& t, const Call& call) {
   return t.reshape({1}).to(at::kFloat);
 }
 
-// frac: also the balancing loss's share of the gate's gradient.
+// frac: also the balancing loss's share of the gate's gradient.  dx: the type of d_x, none: not wanted.
 std::tuple<Tensor, OptTensor> route_bwd_with(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
-                                             const Tensor& d_gate, const OptTensor& frac, double alpha, const OptTensor& d_loss, bool want_dx,
-                                             const OptStream& stream) {
+                                             const Tensor& d_gate, const OptTensor& frac, double alpha, const OptTensor& d_loss,
+                                             std::optional<at::ScalarType> dx, const OptStream& stream) {
   require(x, w, probs, group, gate, d_gate, frac);
   const Call call(stream);
   need_dims(x, 2);
   const int64_t N = x.size(0), d = x.size(1), M = w.size(0);
   Tensor d_w = call.make({M, d}, x, at::kFloat);
   OptTensor d_x, dev;
-  if (want_dx) d_x = call.make({N, d}, x, at::kFloat);
+  if (dx) d_x = call.make({N, d}, x, *dx);
   Tensor ws = call.workspace(moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), x);
   if (frac) {
     TORCH_CHECK(frac->size(0) == M, "frac of ", frac->size(0), " groups for a router of ", M);
     if (d_loss) dev = device_scalar(*d_loss, call);
-    check("moga_route_bwd_balanced",
-          moga_route_bwd_balanced(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate), as<float>(d_gate),
-                                  as<float>(frac), (float)alpha, 1.f, as<float>(dev), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x),
-                                  ptr(ws), ws.numel(), call.stream()));
-  } else {
-    check("moga_route_bwd", moga_route_bwd(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate),
-                                           as<float>(d_gate), N, (int)d, (int)M, as<float>(d_w), as<float>(d_x), ptr(ws), ws.numel(),
-                                           call.stream()));
   }
+  check(frac ? "moga_route_bwd_balanced" : "moga_route_bwd",
+        moga_route_bwd_typed(ptr(x), dt(x), as<float>(w), as<float>(probs), as<int32_t>(group), as<float>(gate), as<float>(d_gate),
+                             as<float>(frac), (float)alpha, 1.f, as<float>(dev), N, (int)d, (int)M, as<float>(d_w), ptr(d_x),
+                             d_x ? dt(*d_x) : MOGA_F32, ptr(ws), ws.numel(), call.stream()));
   return {d_w, d_x};
+}
+
+std::optional<at::ScalarType> dx_fp32(bool want_dx) {
+  if (want_dx) return at::kFloat;
+  return std::nullopt;
 }
 
 std::tuple<Tensor, OptTensor> route_bwd(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group, const Tensor& gate,
                                         const Tensor& d_gate, bool want_dx, const OptStream& stream) {
-  return route_bwd_with(x, w, probs, group, gate, d_gate, std::nullopt, 0., std::nullopt, want_dx, stream);
+  return route_bwd_with(x, w, probs, group, gate, d_gate, std::nullopt, 0., std::nullopt, dx_fp32(want_dx), stream);
 }
 
 std::tuple<Tensor, OptTensor> route_bwd_balanced(const Tensor& x, const Tensor& w, const Tensor& probs, const Tensor& group,
                                                  const Tensor& gate, const Tensor& d_gate, const Tensor& frac, double alpha,
                                                  const Tensor& d_loss, bool want_dx, const OptStream& stream) {
-  return route_bwd_with(x, w, probs, group, gate, d_gate, frac, alpha, d_loss, want_dx, stream);
+  return route_bwd_with(x, w, probs, group, gate, d_gate, frac, alpha, d_loss, dx_fp32(want_dx), stream);
 }
 
 std::tuple<Tensor, Tensor> fused_attn_fwd(const Tensor& q, const Tensor& k, const Tensor& v, const Tensor& perm, const Tensor& gate,
@@ -556,10 +557,9 @@ struct Attention : public torch::autograd::Function<Attention> {
     g.d_oh.reset();
     const bool balanced = alpha && grads[1].defined();
     auto [d_w, d_x] = route_bwd_with(x, w, probs, group, gate, g.d_gate, balanced ? OptTensor(frac) : std::nullopt, alpha.value_or(0.),
-                                     balanced ? OptTensor(grads[1]) : std::nullopt, grad_x, std::nullopt);
-    Tensor dx;
-    if (d_x) dx = d_x->to(x.scalar_type());
-    return {dx, d_w, g.d_q, g.d_k, g.d_v, Tensor(), Tensor(), Tensor()};
+                                     balanced ? OptTensor(grads[1]) : std::nullopt,
+                                     grad_x ? std::optional<at::ScalarType>(x.scalar_type()) : std::nullopt, std::nullopt);
+    return {d_x.value_or(Tensor()), d_w, g.d_q, g.d_k, g.d_v, Tensor(), Tensor(), Tensor()};
   }
 };
 
