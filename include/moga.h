@@ -414,6 +414,16 @@ int moga_gather3_bwd(const void* g_moga, const int32_t* inv_moga, const void* g_
                      int D, void* d_src, void* stream);
 
 /*
+ * The same for Q, K and V in one launch, with the lists of moga_gather3_fwd: q_slot [N] the slots of the queries, inv_cu [N+1] and
+ * inv_slots [Nk] those of the keys.  gq_* [H, N, D]; gk_stga, gv_stga [H, Nk, D].
+ */
+int moga_gather3_bwd_qkv(const void* gq_moga, const void* gk_moga, const void* gv_moga, const int32_t* inv_moga,
+                         const void* gq_stga, const void* gk_stga, const void* gv_stga, const int32_t* q_slot,
+                         const int32_t* inv_cu, const int32_t* inv_slots, int64_t Nk,
+                         const void* gq_frame, const void* gk_frame, const void* gv_frame, const int32_t* inv_frame,
+                         int dtype, int64_t N, int H, int D, void* d_q, void* d_k, void* d_v, void* stream);
+
+/*
  * Mean of the three branches of Section 3.2 fused into one scatter:
  *   o[t][h][:] = ( gate[t] * a_moga[h][inv_moga[t]][:] + a_stga[h][inv_stga[t]][:]
  *                  + a_frame[h][inv_frame[t]][:] ) / 3

@@ -76,6 +76,8 @@ _SIGNATURES = {
     "moga_gather3_fwd": (_i32, [_vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _vp, _vp, _vp,
                                 _vp, _vp, _vp, _vp, _vp]),
     "moga_gather3_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _vp]),
+    "moga_gather3_bwd_qkv": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32,
+                                    _vp, _vp, _vp, _vp]),
     "moga_merge3_fwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp]),
     "moga_merge3_bwd": (_i32, [_vp, _vp, _i32, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp, _vp]),
     "moga_merge3_bwd_rows": (_i32, [_vp, _vp, _vp, _vp, _i32, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _f32, _i64, _i32, _i32, _vp, _vp, _vp,
@@ -346,6 +348,11 @@ def moga_gather3_bwd(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_f
     return _nat.gather3_bwd(g_moga, inv_moga, g_stga, inv_cu, inv_slots, g_frame, inv_frame, _st(stream))
 
 
+def moga_gather3_bwd_qkv(g_moga, inv_moga, g_stga, q_slot, inv_cu, inv_slots, g_frame, inv_frame=None, stream=None):
+    """g_*: the gradients of q, k and v from a branch -> d_q, d_k, d_v [N, H, D]"""
+    return _nat.gather3_bwd_qkv(*g_moga, inv_moga, *g_stga, q_slot, inv_cu, inv_slots, *g_frame, inv_frame, _st(stream))
+
+
 def moga_merge3_fwd(a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, stream=None):
     """Three [H, N, D] branch outputs -> their mean [N, H, D] in token order (dynamic branch gated)."""
     return _nat.merge3_fwd(a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, _st(stream))
@@ -431,7 +438,7 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
 
 def visual_backward(fwd, x, w, d_o, softmax_scale, stream=None):
     """Backward of `visual_forward` -> dict(d_q, d_k, d_v [N, H, D], d_w [M, d_model], d_gate [N])."""
-    pm, si, ident = fwd["pm"], fwd["si"], fwd["ident"]
+    pm, si = fwd["pm"], fwd["si"]
     d_m, d_s, d_f, d_gate, ws_m, ws_s, ws_f = moga_merge3_bwd_rows(
         d_o, fwd["a_m"], fwd["a_s"], fwd["a_f"], pm["inv_perm"], si["q_slot"], None, fwd["gate"],
         (fwd["lse_m"], fwd["lse_s"], fwd["lse_f"]), softmax_scale, pm["cu_seqlens"], si["cu_q"], fwd["ks"].shape[1], fwd["cu_f"],
@@ -447,9 +454,8 @@ def visual_backward(fwd, x, w, d_o, softmax_scale, stream=None):
     del d_f, ws_f
     # every token-order gradient is written once: MoGA rows through inv_perm, the static rows through
     # their slot lists (queries are listed once, keys possibly several times), the frame rows in place
-    d_q = moga_gather3_bwd(dqm, pm["inv_perm"], dqs, ident, si["q_slot"], dqf, stream=stream)
-    d_k = moga_gather3_bwd(dkm, pm["inv_perm"], dks, si["inv_cu"], si["inv_slots"], dkf, stream=stream)
-    d_v = moga_gather3_bwd(dvm, pm["inv_perm"], dvs, si["inv_cu"], si["inv_slots"], dvf, stream=stream)
+    d_q, d_k, d_v = moga_gather3_bwd_qkv((dqm, dkm, dvm), pm["inv_perm"], (dqs, dks, dvs), si["q_slot"], si["inv_cu"], si["inv_slots"],
+                                         (dqf, dkf, dvf), stream=stream)
     del dqm, dkm, dvm, dqs, dks, dvs, dqf, dkf, dvf
     d_w, _ = moga_route_bwd(x, w, fwd["probs"], fwd["group"], fwd["gate"], d_gate, stream=stream)
     return {"d_q": d_q, "d_k": d_k, "d_v": d_v, "d_w": d_w, "d_gate": d_gate}

@@ -12,6 +12,7 @@
 // Data part: 16-byte-per-lane row copies between token order [N, H, D] and head-major
 // group-contiguous order [H, N, D]; the scatter back multiplies by the gate (Eq. 5).
 #include <mutex>
+#include <type_traits>
 
 #include "moga_common.h"
 
@@ -262,7 +263,19 @@ __global__ __launch_bounds__(1024) void permute_single_block_kernel(const int32_
 // ---------------------------------------------------------------------------------------
 // row movers.  A (token, head) row is D*elem bytes = LPR lanes of 16 bytes.
 // ---------------------------------------------------------------------------------------
-constexpr int kSlotsPerBlock = 16;
+// A block of four waves takes SLOTS tokens or slots and all heads, a wave every fourth head; a wave has 16 rows of a tensor in flight, of one
+// head (SLOTS = 16) or of four (4).  Four slots: four times the blocks, which few tokens need, and writes that are as good (1 KB to a place).
+// us with 16 and 4: gather for three branches 3,120 x 16 heads 38.3 and 34.0, 99,840 x 40 2,423 and 2,390; its backward 40.1 and 34.4, 2,417
+// and 2,379; mean of three branches 15.7 and 10.9, 800 and 776; gather 62,400 x 12 205 and 202; scatter 1,253 x 40 12.8 and 8.4, 60,000 x 40 251
+// and 243.
+constexpr int kManySlots = 16, kFewSlots = 4;
+// HIP takes fewer than 2^32 threads in a grid.
+inline bool few_slots(int64_t N) { return grid_fits((N + kFewSlots - 1) / kFewSlots, 256); }
+// The kernels that also sum over the heads of a token and write its row constants keep more in registers: 3,120 x 16 heads 30.6 and 24.3 us
+// (backward of the mean of three branches), 4,680 x 12 29.0 and 28.5, 6,240 x 12 33.0 and 37.9, 32,760 x 12 151 and 161; scatter backward
+// 1,253 x 40 18.3 and 10.8, 5,600 x 12 15.4 and 13.6, 8,000 x 12 18.1 and 18.6, 16,000 x 12 28.8 and 31.8.
+inline bool few_slots_of_sums(int64_t N) { return N <= 6000; }
+constexpr int kGatherSlots = 16;   // tokens per block of permute_gather
 
 struct Rows3 {
   const void* src[3];
@@ -270,14 +283,15 @@ struct Rows3 {
 };
 
 // token order -> head-major sorted order:  dst[h][j] = src[perm[j]][h]
-template <int LPR>
+template <int LPR, int SLOTS>
 __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t* __restrict__ perm,
                                                           int64_t N, int H) {
   constexpr int RPW = 64 / LPR;  // rows per wave instruction
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t j0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t j0 = (int64_t)blockIdx.x * SLOTS;
   const uintx4_t* __restrict__ src = (const uintx4_t*)p.src[blockIdx.y];
   uintx4_t* __restrict__ dst = (uintx4_t*)p.dst[blockIdx.y];
   int64_t tok[IT];
@@ -288,16 +302,20 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Rows3 p, const int32_t
     ok[it] = j < N;
     tok[it] = ok[it] ? perm[j] : 0;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t v[IT];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t v[HU][IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) v[it] = src[(tok[it] * H + h) * LPR + part];
+    for (int u = 0; u < HU; ++u)
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int64_t j = j0 + it * RPW + rsub;
-      if (ok[it]) dst[((int64_t)h * N + j) * LPR + part] = v[it];
-    }
+      for (int it = 0; it < IT; ++it)
+        if (ok[it] && h0 + 4 * u < H) v[u][it] = src[(tok[it] * H + h0 + 4 * u) * LPR + part];
+#pragma unroll
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int64_t j = j0 + it * RPW + rsub;
+        if (ok[it] && h0 + 4 * u < H) dst[((int64_t)(h0 + 4 * u) * N + j) * LPR + part] = v[u][it];
+      }
   }
 }
 
@@ -326,7 +344,7 @@ inline bool use_permute_gather(int64_t N, int M, int64_t row_bytes) {
 // groups 59.6, 71.6 and 56.5; 9,000, 8 groups 121, 123 and 114; 8,192 (two full rounds) 107, 97 and 103.  16 heads, 10,007, 8 groups
 // 53.7, 52.3 and 48.0, 9 groups 54.7, 56.1 and 57.5.
 inline bool permute_gather_per_tensor(int64_t N, int M, int64_t row_bytes) {
-  return N <= 4096 || (row_bytes >= (M <= 8 ? 4096 : 6144) && (N - 1) / kSlotsPerBlock % 256 < 224);
+  return N <= 4096 || (row_bytes >= (M <= 8 ? 4096 : 6144) && (N - 1) / kGatherSlots % 256 < 224);
 }
 
 template <int LPR, int WORDS, int PER>   // WORDS * 4 >= groups, PER * 256 >= tokens
@@ -335,12 +353,12 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int3
                                                              int32_t* __restrict__ max_seqlen, int32_t* __restrict__ perm,
                                                              int32_t* __restrict__ inv_perm) {
   constexpr int RPW = 64 / LPR;  // rows per wave instruction
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = kGatherSlots / RPW;
   __shared__ int s_sum[4][2][2 * WORDS];   // per wave: all tokens, those before the block's; groups 4 w + f and 4 w + f + 2 at 2 w + f
   __shared__ int s_count[4 * WORDS], s_cu[4 * WORDS];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int t0 = blockIdx.x * kSlotsPerBlock;
+  const int t0 = blockIdx.x * kGatherSlots;
   constexpr int BATCH = PER < 16 ? PER : 16;
   int id[BATCH], ahead[BATCH];   // a batch of ids in flight together, and the next one
   auto load_ids = [&](int (&to)[BATCH], int i0) {
@@ -348,8 +366,8 @@ __global__ __launch_bounds__(256) void permute_gather_kernel(Rows3 p, const int3
     for (int i = 0; i < BATCH; ++i) to[i] = group[min(256 * (i0 + i) + (int)threadIdx.x, N - 1)];
   };
   load_ids(id, 0);
-  const bool own = lane < kSlotsPerBlock && t0 + lane < N;
-  const int g = clamp_group(group[min(t0 + (lane & (kSlotsPerBlock - 1)), N - 1)], M);
+  const bool own = lane < kGatherSlots && t0 + lane < N;
+  const int g = clamp_group(group[min(t0 + (lane & (kGatherSlots - 1)), N - 1)], M);
   uintx4_t v[IT];
   auto load_rows = [&](const uintx4_t* __restrict__ src, int h) {
 #pragma unroll
@@ -451,15 +469,16 @@ __device__ __forceinline__ float dot16(uintx4_t a, uintx4_t b) {
 }
 
 // head-major sorted order -> token order: dst[perm[j]][h] = gate[perm[j]] * src[h][j]
-template <int LPR, bool BF16>
+template <int LPR, bool BF16, int SLOTS>
 __global__ __launch_bounds__(256) void scatter_rows_kernel(Rows3 p, const int32_t* __restrict__ perm,
                                                            const float* __restrict__ gate,
                                                            int64_t N, int H) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t j0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t j0 = (int64_t)blockIdx.x * SLOTS;
   const uintx4_t* __restrict__ src = (const uintx4_t*)p.src[blockIdx.y];
   uintx4_t* __restrict__ dst = (uintx4_t*)p.dst[blockIdx.y];
   int64_t tok[IT];
@@ -472,20 +491,21 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(Rows3 p, const int32_
     tok[it] = ok[it] ? perm[j] : 0;
     g[it] = (gate && ok[it]) ? gate[tok[it]] : 1.f;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t v[IT];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t v[HU][IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int64_t j = j0 + it * RPW + rsub;
-      if (ok[it]) v[it] = src[((int64_t)h * N + j) * LPR + part];
-    }
+    for (int u = 0; u < HU; ++u)
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      if (ok[it]) {
-        uintx4_t o = gate ? scale16<BF16>(v[it], g[it]) : v[it];
-        dst[(tok[it] * H + h) * LPR + part] = o;
+      for (int it = 0; it < IT; ++it) {
+        const int64_t j = j0 + it * RPW + rsub;
+        if (ok[it] && h0 + 4 * u < H) v[u][it] = src[((int64_t)(h0 + 4 * u) * N + j) * LPR + part];
       }
-    }
+#pragma unroll
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it)
+        if (ok[it] && h0 + 4 * u < H)
+          dst[(tok[it] * H + h0 + 4 * u) * LPR + part] = gate ? scale16<BF16>(v[u][it], g[it]) : v[u][it];
   }
 }
 
@@ -493,18 +513,19 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(Rows3 p, const int32_
 // DELTA: also the row constants of the attention backward, -delta = -rowsum(d_oh * oh) (of the rounded d_oh) and, in bf16,
 // -lse / scale, and its status word.  Both tensors are in registers here; attn_bwd_delta_kernel reads them again (10,007 x 12
 // heads: 12 us, 32,760 x 12: 38 us).  Same sums in the same order as there.
-template <int LPR, bool BF16, bool DELTA>
+template <int LPR, bool BF16, bool DELTA, int SLOTS>
 __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
     const uintx4_t* __restrict__ d_o, const uintx4_t* __restrict__ oh,
     const int32_t* __restrict__ perm, const float* __restrict__ gate, int64_t N, int H,
     uintx4_t* __restrict__ d_oh, float* __restrict__ d_gate, RowConstants rc) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
-  __shared__ float s_part[4][kSlotsPerBlock];
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
+  __shared__ float s_part[4][SLOTS];
   if (DELTA && blockIdx.x == 0 && threadIdx.x == 0) *rc.status = 0;   // read by the kernels that follow
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t j0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t j0 = (int64_t)blockIdx.x * SLOTS;
   int64_t tok[IT];
   float g[IT], acc[IT];
   bool ok[IT];
@@ -516,35 +537,41 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
     g[it] = ok[it] ? gate[tok[it]] : 0.f;
     acc[it] = 0.f;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t a[IT], b[IT];
-    float l[IT];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t a[HU][IT], b[HU][IT];
+    float l[HU][IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int64_t j = j0 + it * RPW + rsub;
-      if (ok[it]) {
-        a[it] = d_o[(tok[it] * H + h) * LPR + part];
-        b[it] = oh[((int64_t)h * N + j) * LPR + part];
-        if (DELTA && BF16) l[it] = rc.lse[(int64_t)h * N + j];
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        const int64_t j = j0 + it * RPW + rsub;
+        if (ok[it] && h < H) {
+          a[u][it] = d_o[(tok[it] * H + h) * LPR + part];
+          b[u][it] = oh[((int64_t)h * N + j) * LPR + part];
+          if (DELTA && BF16) l[u][it] = rc.lse[(int64_t)h * N + j];
+        }
       }
-    }
 #pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const int64_t j = j0 + it * RPW + rsub;
-      if (ok[it]) {   // the same for all lanes of a row
-        acc[it] += dot16<BF16>(a[it], b[it]);
-        const uintx4_t s = scale16<BF16>(a[it], g[it]);
-        d_oh[((int64_t)h * N + j) * LPR + part] = s;
-        if (DELTA) {
-          float dl = dot16<BF16>(s, b[it]);
-          dl = lanes_sum<LPR>(dl);
-          if (part == 0) {
-            rc.neg_delta[(int64_t)h * N + j] = -dl;
-            if (BF16) rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[it] * rc.inv_scale;
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        const int64_t j = j0 + it * RPW + rsub;
+        if (ok[it] && h < H) {   // the same for all lanes of a row
+          acc[it] += dot16<BF16>(a[u][it], b[u][it]);
+          const uintx4_t s = scale16<BF16>(a[u][it], g[it]);
+          d_oh[((int64_t)h * N + j) * LPR + part] = s;
+          if (DELTA) {
+            float dl = dot16<BF16>(s, b[u][it]);
+            dl = lanes_sum<LPR>(dl);
+            if (part == 0) {
+              rc.neg_delta[(int64_t)h * N + j] = -dl;
+              if (BF16) rc.neg_lse_over_scale[(int64_t)h * N + j] = -l[u][it] * rc.inv_scale;
+            }
           }
         }
       }
-    }
   }
   // reduce over the LPR lanes of a row, then over the four waves
 #pragma unroll
@@ -553,7 +580,7 @@ __global__ __launch_bounds__(256) void unpermute_bwd_kernel(
     if (part == 0) s_part[wave][it * RPW + rsub] = s;
   }
   __syncthreads();
-  if (threadIdx.x < kSlotsPerBlock) {
+  if (threadIdx.x < SLOTS) {
     const int64_t j = j0 + threadIdx.x;
     if (j < N) {
       const float s = (s_part[0][threadIdx.x] + s_part[1][threadIdx.x]) +
@@ -599,10 +626,10 @@ __global__ __launch_bounds__(256) void gather_rows_bwd_kernel(
     const int32_t* __restrict__ inv_slots, int64_t N, int64_t Nk, int H, int accumulate,
     uintx4_t* __restrict__ d_src) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = kManySlots / RPW;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t t0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * kManySlots;
   for (int it = 0; it < IT; ++it) {
     const int64_t t = t0 + it * RPW + rsub;
     if (t >= N) continue;
@@ -627,14 +654,15 @@ struct Gather3 {
   int64_t rows[3];                       // of the static list
 };
 
-template <int LPR>
+template <int LPR, int SLOTS>
 __global__ __launch_bounds__(256) void gather3_kernel(Gather3 p, const int32_t* __restrict__ inv_m, const int32_t* __restrict__ inv_f,
                                                       int64_t N, int H) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, y = blockIdx.y;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t t0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * SLOTS;
   const uintx4_t* __restrict__ src = p.src[y];
   const int32_t* __restrict__ slots = p.slots[y];
   const int32_t* __restrict__ inv_cu = p.inv_cu[y];
@@ -652,17 +680,23 @@ __global__ __launch_bounds__(256) void gather3_kernel(Gather3 p, const int32_t* 
     end[it] = inv_cu ? inv_cu[tok[it] + 1] : (int)tok[it] + 1;
     first[it] = beg[it] < end[it] ? slots[beg[it]] : -1;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t v[IT];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t v[HU][IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it) v[it] = src[(tok[it] * H + h) * LPR + part];
+    for (int u = 0; u < HU; ++u)
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        p.m[y][((int64_t)h * N + jm[it]) * LPR + part] = v[it];
-        p.f[y][((int64_t)h * N + jf[it]) * LPR + part] = v[it];
-        if (first[it] >= 0) p.s[y][((int64_t)h * p.rows[y] + first[it]) * LPR + part] = v[it];
-        for (int j = beg[it] + 1; j < end[it]; ++j) p.s[y][((int64_t)h * p.rows[y] + slots[j]) * LPR + part] = v[it];
+      for (int it = 0; it < IT; ++it) v[u][it] = src[(tok[it] * H + min(h0 + 4 * u, H - 1)) * LPR + part];
+#pragma unroll
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          p.m[y][((int64_t)h * N + jm[it]) * LPR + part] = v[u][it];
+          p.f[y][((int64_t)h * N + jf[it]) * LPR + part] = v[u][it];
+          if (first[it] >= 0) p.s[y][((int64_t)h * p.rows[y] + first[it]) * LPR + part] = v[u][it];
+          for (int j = beg[it] + 1; j < end[it]; ++j) p.s[y][((int64_t)h * p.rows[y] + slots[j]) * LPR + part] = v[u][it];
+        }
       }
   }
 }
@@ -671,19 +705,32 @@ __global__ __launch_bounds__(256) void gather3_kernel(Gather3 p, const int32_t* 
 //   d_src[t][h] = g_m[h][inv_m[t]] + sum over the slots j of t of g_s[h][j] + g_f[h][inv_f[t]]
 // (inv_f NULL = identity).  One fp32 sum per element in this fixed order, rounded once: a single
 // pass instead of a scatter followed by two accumulating gather-backwards.
-template <int LPR, bool BF16>
-__global__ __launch_bounds__(256) void gather3_bwd_kernel(
-    const uintx4_t* __restrict__ g_m, const int32_t* __restrict__ inv_m,
-    const uintx4_t* __restrict__ g_s, const int32_t* __restrict__ inv_cu,
-    const int32_t* __restrict__ inv_slots, int64_t Nk, const uintx4_t* __restrict__ g_f,
-    const int32_t* __restrict__ inv_f, int64_t N, int H, uintx4_t* __restrict__ d_src) {
+// The slots of a token do not depend on the head: the first two (keys of a boundary frame are listed twice) are read once, and their
+// rows are in flight with the others.
+struct Gather3Bwd {
+  const uintx4_t *g_m[3], *g_s[3], *g_f[3];
+  const int32_t *inv_cu[3], *slots[3];   // as in Gather3
+  int64_t rows[3];
+  uintx4_t* d_src[3];
+};
+template <int LPR, bool BF16, int SLOTS>
+__global__ __launch_bounds__(256) void gather3_bwd_kernel(Gather3Bwd p, const int32_t* __restrict__ inv_m, const int32_t* __restrict__ inv_f,
+                                                          int64_t N, int H) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, y = blockIdx.y;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t t0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * SLOTS;
+  const uintx4_t* __restrict__ g_m = p.g_m[y];
+  const uintx4_t* __restrict__ g_s = p.g_s[y];
+  const uintx4_t* __restrict__ g_f = p.g_f[y];
+  const int32_t* __restrict__ slots = p.slots[y];
+  const int32_t* __restrict__ inv_cu = p.inv_cu[y];
+  uintx4_t* __restrict__ d_src = p.d_src[y];
+  const int64_t Nk = p.rows[y];
   int64_t jm[IT], jf[IT];
-  int beg[IT], end[IT];
+  int beg[IT], end[IT], js[IT][2];
   bool ok[IT];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
@@ -691,43 +738,59 @@ __global__ __launch_bounds__(256) void gather3_bwd_kernel(
     ok[it] = t < N;
     jm[it] = ok[it] ? inv_m[t] : 0;
     jf[it] = ok[it] ? (inv_f ? inv_f[t] : t) : 0;
-    beg[it] = ok[it] ? inv_cu[t] : 0;
-    end[it] = ok[it] ? inv_cu[t + 1] : 0;
-  }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t vm[IT], vf[IT];
+    beg[it] = ok[it] ? (inv_cu ? inv_cu[t] : (int)t) : 0;
+    end[it] = ok[it] ? (inv_cu ? inv_cu[t + 1] : (int)t + 1) : 0;
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        vm[it] = g_m[((int64_t)h * N + jm[it]) * LPR + part];
-        vf[it] = g_f[((int64_t)h * N + jf[it]) * LPR + part];
+    for (int i = 0; i < 2; ++i) js[it][i] = beg[it] + i < end[it] ? slots[beg[it] + i] : -1;
+  }
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t vm[HU][IT], vf[HU][IT], vs[HU][IT][2];
+#pragma unroll
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          vm[u][it] = g_m[((int64_t)h * N + jm[it]) * LPR + part];
+          vf[u][it] = g_f[((int64_t)h * N + jf[it]) * LPR + part];
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (js[it][i] >= 0) vs[u][it][i] = g_s[((int64_t)h * Nk + js[it][i]) * LPR + part];
+        }
       }
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        const int64_t t = t0 + it * RPW + rsub;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        add16<BF16>(acc, vm[it]);
-        for (int j = beg[it]; j < end[it]; ++j)
-          add16<BF16>(acc, g_s[((int64_t)h * Nk + inv_slots[j]) * LPR + part]);
-        add16<BF16>(acc, vf[it]);
-        d_src[(t * H + h) * LPR + part] = pack16<BF16>(acc);
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          const int64_t t = t0 + it * RPW + rsub;
+          float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          add16<BF16>(acc, vm[u][it]);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            if (js[it][i] >= 0) add16<BF16>(acc, vs[u][it][i]);
+          for (int j = beg[it] + 2; j < end[it]; ++j) add16<BF16>(acc, g_s[((int64_t)h * Nk + slots[j]) * LPR + part]);
+          add16<BF16>(acc, vf[u][it]);
+          d_src[(t * H + h) * LPR + part] = pack16<BF16>(acc);
+        }
       }
   }
 }
 
 // o[t][h] = alpha * (gate[t] * a_m[h][inv_m[t]] + a_s[h][inv_s[t]] + a_f[h][inv_f[t]]); a NULL
 // inverse list means the identity (the branch keeps token order).
-template <int LPR, bool BF16>
+template <int LPR, bool BF16, int SLOTS>
 __global__ __launch_bounds__(256) void merge3_fwd_kernel(
     const uintx4_t* __restrict__ a_m, const uintx4_t* __restrict__ a_s, const uintx4_t* __restrict__ a_f,
     const int32_t* __restrict__ inv_m, const int32_t* __restrict__ inv_s, const int32_t* __restrict__ inv_f,
     const float* __restrict__ gate, float alpha, int64_t N, int H, uintx4_t* __restrict__ o) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t t0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * SLOTS;
   int64_t jm[IT], js[IT], jf[IT];
   float g[IT];
   bool ok[IT];
@@ -740,28 +803,36 @@ __global__ __launch_bounds__(256) void merge3_fwd_kernel(
     jf[it] = ok[it] ? (inv_f ? inv_f[t] : t) : 0;
     g[it] = ok[it] ? gate[t] : 0.f;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t vm[IT], vs[IT], vf[IT];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t vm[HU][IT], vs[HU][IT], vf[HU][IT];
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        vm[it] = a_m[((int64_t)h * N + jm[it]) * LPR + part];
-        vs[it] = a_s[((int64_t)h * N + js[it]) * LPR + part];
-        vf[it] = a_f[((int64_t)h * N + jf[it]) * LPR + part];
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          vm[u][it] = a_m[((int64_t)h * N + jm[it]) * LPR + part];
+          vs[u][it] = a_s[((int64_t)h * N + js[it]) * LPR + part];
+          vf[u][it] = a_f[((int64_t)h * N + jf[it]) * LPR + part];
+        }
       }
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        add16<BF16>(acc, vm[it]);
+    for (int u = 0; u < HU; ++u)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] *= g[it];
-        add16<BF16>(acc, vs[it]);
-        add16<BF16>(acc, vf[it]);
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          add16<BF16>(acc, vm[u][it]);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] *= alpha;
-        const int64_t t = t0 + it * RPW + rsub;
-        o[(t * H + h) * LPR + part] = pack16<BF16>(acc);
+          for (int e = 0; e < 8; ++e) acc[e] *= g[it];
+          add16<BF16>(acc, vs[u][it]);
+          add16<BF16>(acc, vf[u][it]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] *= alpha;
+          const int64_t t = t0 + it * RPW + rsub;
+          o[(t * H + h) * LPR + part] = pack16<BF16>(acc);
+        }
       }
   }
 }
@@ -784,19 +855,20 @@ __device__ __forceinline__ void put_row_constants(const RowConstants& rc, int64_
   }
 }
 
-template <int LPR, bool BF16, bool ROWS>
+template <int LPR, bool BF16, bool ROWS, int SLOTS>
 __global__ __launch_bounds__(256) void merge3_bwd_kernel(
     const uintx4_t* __restrict__ d_o, const uintx4_t* __restrict__ a_m,
     const int32_t* __restrict__ inv_m, const int32_t* __restrict__ inv_s, const int32_t* __restrict__ inv_f,
     const float* __restrict__ gate, float alpha, int64_t N, int H, uintx4_t* __restrict__ d_m,
     uintx4_t* __restrict__ d_s, uintx4_t* __restrict__ d_f, float* __restrict__ d_gate, Merge3Rows rows) {
   constexpr int RPW = 64 / LPR;
-  constexpr int IT = kSlotsPerBlock / RPW;
-  __shared__ float s_part[4][kSlotsPerBlock];
+  constexpr int IT = SLOTS / RPW;
+  constexpr int HU = kManySlots / SLOTS;   // heads in flight
+  __shared__ float s_part[4][SLOTS];
   if (ROWS && blockIdx.x == 0 && threadIdx.x == 0) *rows.m.status = *rows.s.status = *rows.f.status = 0;   // read by the kernels that follow
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int part = lane % LPR, rsub = lane / LPR;
-  const int64_t t0 = (int64_t)blockIdx.x * kSlotsPerBlock;
+  const int64_t t0 = (int64_t)blockIdx.x * SLOTS;
   int64_t jm[IT], js[IT], jf[IT];
   float g[IT], acc[IT];
   bool ok[IT];
@@ -810,38 +882,46 @@ __global__ __launch_bounds__(256) void merge3_bwd_kernel(
     g[it] = ok[it] ? gate[t] * alpha : 0.f;
     acc[it] = 0.f;
   }
-  for (int h = wave; h < H; h += 4) {
-    uintx4_t a[IT], b[IT], as[IT], af[IT];
-    float l[IT][3];
+  for (int h0 = wave; h0 < H; h0 += 4 * HU) {
+    uintx4_t a[HU][IT], b[HU][IT], as[HU][IT], af[HU][IT];
+    float l[HU][IT][3];
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        const int64_t t = t0 + it * RPW + rsub;
-        a[it] = d_o[(t * H + h) * LPR + part];
-        b[it] = a_m[((int64_t)h * N + jm[it]) * LPR + part];
-        if (ROWS) {
-          as[it] = rows.a_s[((int64_t)h * N + js[it]) * LPR + part];
-          af[it] = rows.a_f[((int64_t)h * N + jf[it]) * LPR + part];
-          if (BF16) {
-            l[it][0] = rows.m.lse[(int64_t)h * N + jm[it]];
-            l[it][1] = rows.s.lse[(int64_t)h * N + js[it]];
-            l[it][2] = rows.f.lse[(int64_t)h * N + jf[it]];
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          const int64_t t = t0 + it * RPW + rsub;
+          a[u][it] = d_o[(t * H + h) * LPR + part];
+          b[u][it] = a_m[((int64_t)h * N + jm[it]) * LPR + part];
+          if (ROWS) {
+            as[u][it] = rows.a_s[((int64_t)h * N + js[it]) * LPR + part];
+            af[u][it] = rows.a_f[((int64_t)h * N + jf[it]) * LPR + part];
+            if (BF16) {
+              l[u][it][0] = rows.m.lse[(int64_t)h * N + jm[it]];
+              l[u][it][1] = rows.s.lse[(int64_t)h * N + js[it]];
+              l[u][it][2] = rows.f.lse[(int64_t)h * N + jf[it]];
+            }
           }
         }
       }
 #pragma unroll
-    for (int it = 0; it < IT; ++it)
-      if (ok[it]) {
-        acc[it] += dot16<BF16>(a[it], b[it]);
-        const uintx4_t sm = scale16<BF16>(a[it], g[it]);
-        d_m[((int64_t)h * N + jm[it]) * LPR + part] = sm;
-        const uintx4_t sc = scale16<BF16>(a[it], alpha);
-        d_s[((int64_t)h * N + js[it]) * LPR + part] = sc;
-        d_f[((int64_t)h * N + jf[it]) * LPR + part] = sc;
-        if (ROWS) {
-          put_row_constants<BF16, LPR>(rows.m, (int64_t)h * N + jm[it], sm, b[it], l[it][0], part);
-          put_row_constants<BF16, LPR>(rows.s, (int64_t)h * N + js[it], sc, as[it], l[it][1], part);
-          put_row_constants<BF16, LPR>(rows.f, (int64_t)h * N + jf[it], sc, af[it], l[it][2], part);
+    for (int u = 0; u < HU; ++u)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const int h = h0 + 4 * u;
+        if (ok[it] && h < H) {
+          acc[it] += dot16<BF16>(a[u][it], b[u][it]);
+          const uintx4_t sm = scale16<BF16>(a[u][it], g[it]);
+          d_m[((int64_t)h * N + jm[it]) * LPR + part] = sm;
+          const uintx4_t sc = scale16<BF16>(a[u][it], alpha);
+          d_s[((int64_t)h * N + js[it]) * LPR + part] = sc;
+          d_f[((int64_t)h * N + jf[it]) * LPR + part] = sc;
+          if (ROWS) {
+            put_row_constants<BF16, LPR>(rows.m, (int64_t)h * N + jm[it], sm, b[u][it], l[u][it][0], part);
+            put_row_constants<BF16, LPR>(rows.s, (int64_t)h * N + js[it], sc, as[u][it], l[u][it][1], part);
+            put_row_constants<BF16, LPR>(rows.f, (int64_t)h * N + jf[it], sc, af[u][it], l[u][it][2], part);
+          }
         }
       }
   }
@@ -851,7 +931,7 @@ __global__ __launch_bounds__(256) void merge3_bwd_kernel(
     if (part == 0) s_part[wave][it * RPW + rsub] = s;
   }
   __syncthreads();
-  if (threadIdx.x < kSlotsPerBlock) {
+  if (threadIdx.x < SLOTS) {
     const int64_t t = t0 + threadIdx.x;
     if (t < N)
       d_gate[t] = alpha * ((s_part[0][threadIdx.x] + s_part[1][threadIdx.x]) +
@@ -865,18 +945,27 @@ static int bits_for(int M) {
   return b;
 }
 
+// Runs f(std::integral_constant<int, SLOTS>, blocks).
+template <typename F>
+static void with_slots(bool few, int64_t N, F&& f) {
+  if (few) f(std::integral_constant<int, kFewSlots>(), (unsigned)((N + kFewSlots - 1) / kFewSlots));
+  else f(std::integral_constant<int, kManySlots>(), (unsigned)((N + kManySlots - 1) / kManySlots));
+}
+
 template <int LPR>
 static void launch_gather(const Rows3& p, int ntensors, const int32_t* perm, int64_t N, int H,
                           hipStream_t st) {
-  dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), ntensors);
-  gather_rows_kernel<LPR><<<grid, 256, 0, st>>>(p, perm, N, H);
+  with_slots(few_slots(N), N, [&](auto slots, unsigned blocks) {
+    gather_rows_kernel<LPR, slots.value><<<dim3(blocks, ntensors), 256, 0, st>>>(p, perm, N, H);
+  });
 }
 
 template <int LPR, bool BF16>
 static void launch_scatter(const Rows3& p, int ntensors, const int32_t* perm, const float* gate,
                            int64_t N, int H, hipStream_t st) {
-  dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), ntensors);
-  scatter_rows_kernel<LPR, BF16><<<grid, 256, 0, st>>>(p, perm, gate, N, H);
+  with_slots(few_slots(N), N, [&](auto slots, unsigned blocks) {
+    scatter_rows_kernel<LPR, BF16, slots.value><<<dim3(blocks, ntensors), 256, 0, st>>>(p, perm, gate, N, H);
+  });
 }
 
 // Returns lanes per (token, head) row, or 0 when the combination is not covered.
@@ -889,7 +978,7 @@ static int lanes_per_row(int dtype, int D) {
 static int check_rows_args(int dtype, int64_t N, int H, int D) {
   if (N < 0 || H < 1 || D < 1) return MOGA_ERR_INVALID_ARG;
   if (dtype != MOGA_F32 && dtype != MOGA_BF16) return MOGA_ERR_UNSUPPORTED;
-  if (!grid_fits((N + kSlotsPerBlock - 1) / kSlotsPerBlock, 256) || lanes_per_row(dtype, D) == 0) return MOGA_ERR_UNSUPPORTED;
+  if (!grid_fits((N + kManySlots - 1) / kManySlots, 256) || lanes_per_row(dtype, D) == 0) return MOGA_ERR_UNSUPPORTED;
   return MOGA_OK;
 }
 
@@ -914,7 +1003,7 @@ static int permute_impl(const int32_t* group, int64_t N, int M, const void* q, c
   const int64_t row_bytes = (int64_t)H * lanes_per_row(dtype, D) * 16;
   if (with_data && N > 0 && use_permute_gather(N, M, row_bytes)) {
     const Rows3 p = {{q, k, v}, {qh, kh, vh}};
-    const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), permute_gather_per_tensor(N, M, row_bytes) ? 3 : 1);
+    const dim3 grid((unsigned)((N + kGatherSlots - 1) / kGatherSlots), permute_gather_per_tensor(N, M, row_bytes) ? 3 : 1);
 #define MOGA_PERMUTE_GATHER(LPR, WORDS, PER)                                                                                  \
   permute_gather_kernel<LPR, WORDS, PER><<<grid, 256, 0, st>>>(p, group, (int)N, H, M, nbits, counts, cu_seqlens, max_seqlen, \
                                                                perm, inv_perm)
@@ -1090,11 +1179,12 @@ int moga::launch_unpermute_bwd(const void* d_o, const void* oh, int dtype, const
   if (N == 0) return MOGA_OK;
   if (!d_o || !oh || !perm || !gate || !d_oh || !d_gate) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(d_o) && aligned16(oh) && aligned16(d_oh))) return MOGA_ERR_INVALID_ARG;
-  const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
   const int lpr = lanes_per_row(dtype, D);
-#define MOGA_UNPERMUTE_BWD(LPR, BF, DELTA)                                                                              \
-  unpermute_bwd_kernel<LPR, BF, DELTA><<<blocks, 256, 0, st>>>((const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, N, \
-                                                               H, (uintx4_t*)d_oh, d_gate, rc ? *rc : RowConstants{})
+#define MOGA_UNPERMUTE_BWD(LPR, BF, DELTA)                                                                                          \
+  with_slots(few_slots_of_sums(N), N, [&](auto slots, unsigned blocks) {                                                            \
+    unpermute_bwd_kernel<LPR, BF, DELTA, slots.value><<<blocks, 256, 0, st>>>((const uintx4_t*)d_o, (const uintx4_t*)oh, perm, gate, \
+                                                                              N, H, (uintx4_t*)d_oh, d_gate, rc ? *rc : RowConstants{}); \
+  })
   if (dtype == MOGA_BF16 && rc) MOGA_UNPERMUTE_BWD(16, true, true);
   else if (dtype == MOGA_BF16) MOGA_UNPERMUTE_BWD(16, true, false);
   else if (lpr == 16 && rc) MOGA_UNPERMUTE_BWD(16, false, true);
@@ -1139,7 +1229,7 @@ extern "C" int moga_gather_rows_bwd(const void* d_dst, int dtype, const int32_t*
   if (!inv_cu || !d_src || (Nk > 0 && (!d_dst || !inv_slots))) return MOGA_ERR_INVALID_ARG;
   if (!aligned16(d_dst) || !aligned16(d_src)) return MOGA_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
+  const unsigned blocks = (unsigned)((N + kManySlots - 1) / kManySlots);
   const int lpr = lanes_per_row(dtype, D);
   if (dtype == MOGA_BF16)
     gather_rows_bwd_kernel<16, true><<<blocks, 256, 0, st>>>((const uintx4_t*)d_dst, inv_cu, inv_slots, N, Nk, H,
@@ -1171,9 +1261,28 @@ extern "C" int moga_gather3_fwd(const void* q, const void* k, const void* v, int
   typedef uintx4_t* out;
   const Gather3 p = {{(in)q, (in)k, (in)v}, {(out)qm, (out)km, (out)vm}, {(out)qs, (out)ks, (out)vs}, {(out)qf, (out)kf, (out)vf},
                      {nullptr, inv_cu, inv_cu}, {q_slot, inv_slots, inv_slots}, {N, Nk, Nk}};
-  const dim3 grid((unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock), 3);
-  if (lanes_per_row(dtype, D) == 16) gather3_kernel<16><<<grid, 256, 0, (hipStream_t)stream>>>(p, inv_moga, inv_frame, N, H);
-  else gather3_kernel<32><<<grid, 256, 0, (hipStream_t)stream>>>(p, inv_moga, inv_frame, N, H);
+  hipStream_t st = (hipStream_t)stream;
+  with_slots(few_slots(N), N, [&](auto slots, unsigned blocks) {
+    if (lanes_per_row(dtype, D) == 16) gather3_kernel<16, slots.value><<<dim3(blocks, 3), 256, 0, st>>>(p, inv_moga, inv_frame, N, H);
+    else gather3_kernel<32, slots.value><<<dim3(blocks, 3), 256, 0, st>>>(p, inv_moga, inv_frame, N, H);
+  });
+  return launch_status();
+}
+
+static int gather3_bwd(const Gather3Bwd& p, int tensors, const int32_t* inv_moga, const int32_t* inv_frame, int dtype, int64_t N, int H,
+                       int D, hipStream_t st) {
+  for (int i = 0; i < tensors; ++i)
+    for (const void* t : {(const void*)p.g_m[i], (const void*)p.g_s[i], (const void*)p.g_f[i], (const void*)p.d_src[i]})
+      if (!aligned16(t)) return MOGA_ERR_INVALID_ARG;
+  const int lpr = lanes_per_row(dtype, D);
+#define MOGA_GATHER3(LPR, BF)                                                                                        \
+  with_slots(few_slots(N), N, [&](auto slots, unsigned blocks) {                                                     \
+    gather3_bwd_kernel<LPR, BF, slots.value><<<dim3(blocks, tensors), 256, 0, st>>>(p, inv_moga, inv_frame, N, H);   \
+  })
+  if (dtype == MOGA_BF16) MOGA_GATHER3(16, true);
+  else if (lpr == 16) MOGA_GATHER3(16, false);
+  else MOGA_GATHER3(32, false);
+#undef MOGA_GATHER3
   return launch_status();
 }
 
@@ -1187,21 +1296,29 @@ extern "C" int moga_gather3_bwd(const void* g_moga, const int32_t* inv_moga, con
   if (N == 0) return MOGA_OK;
   if (!g_moga || !inv_moga || !inv_cu || !g_frame || !d_src || (Nk > 0 && (!g_stga || !inv_slots)))
     return MOGA_ERR_INVALID_ARG;
-  if (!(aligned16(g_moga) && aligned16(g_stga) && aligned16(g_frame) && aligned16(d_src)))
+  typedef const uintx4_t* in;
+  const Gather3Bwd p = {{(in)g_moga}, {(in)g_stga}, {(in)g_frame}, {inv_cu}, {inv_slots}, {Nk}, {(uintx4_t*)d_src}};
+  return gather3_bwd(p, 1, inv_moga, inv_frame, dtype, N, H, D, (hipStream_t)stream);
+}
+
+extern "C" int moga_gather3_bwd_qkv(const void* gq_moga, const void* gk_moga, const void* gv_moga, const int32_t* inv_moga,
+                                    const void* gq_stga, const void* gk_stga, const void* gv_stga, const int32_t* q_slot,
+                                    const int32_t* inv_cu, const int32_t* inv_slots, int64_t Nk, const void* gq_frame,
+                                    const void* gk_frame, const void* gv_frame, const int32_t* inv_frame, int dtype, int64_t N, int H,
+                                    int D, void* d_q, void* d_k, void* d_v, void* stream) {
+  const int bad = check_rows_args(dtype, N, H, D);
+  if (bad) return bad;
+  if (Nk < 0 || Nk >= ((int64_t)1 << 31)) return MOGA_ERR_INVALID_ARG;
+  if (N == 0) return MOGA_OK;
+  if (!gq_moga || !gk_moga || !gv_moga || !inv_moga || !gq_stga || !q_slot || !inv_cu || !gq_frame || !gk_frame || !gv_frame || !d_q ||
+      !d_k || !d_v || (Nk > 0 && (!gk_stga || !gv_stga || !inv_slots)))
     return MOGA_ERR_INVALID_ARG;
-  hipStream_t st = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
-  const int lpr = lanes_per_row(dtype, D);
-#define MOGA_GATHER3(LPR, BF)                                                                         \
-  gather3_bwd_kernel<LPR, BF><<<blocks, 256, 0, st>>>((const uintx4_t*)g_moga, inv_moga,              \
-                                                      (const uintx4_t*)g_stga, inv_cu, inv_slots, Nk, \
-                                                      (const uintx4_t*)g_frame, inv_frame, N, H,      \
-                                                      (uintx4_t*)d_src)
-  if (dtype == MOGA_BF16) MOGA_GATHER3(16, true);
-  else if (lpr == 16) MOGA_GATHER3(16, false);
-  else MOGA_GATHER3(32, false);
-#undef MOGA_GATHER3
-  return launch_status();
+  typedef const uintx4_t* in;
+  typedef uintx4_t* out;
+  const Gather3Bwd p = {{(in)gq_moga, (in)gk_moga, (in)gv_moga}, {(in)gq_stga, (in)gk_stga, (in)gv_stga},
+                        {(in)gq_frame, (in)gk_frame, (in)gv_frame}, {nullptr, inv_cu, inv_cu}, {q_slot, inv_slots, inv_slots},
+                        {N, Nk, Nk}, {(out)d_q, (out)d_k, (out)d_v}};
+  return gather3_bwd(p, 3, inv_moga, inv_frame, dtype, N, H, D, (hipStream_t)stream);
 }
 
 extern "C" int moga_merge3_fwd(const void* a_moga, const void* a_stga, const void* a_frame, int dtype,
@@ -1213,13 +1330,14 @@ extern "C" int moga_merge3_fwd(const void* a_moga, const void* a_stga, const voi
   if (!a_moga || !a_stga || !a_frame || !gate || !o) return MOGA_ERR_INVALID_ARG;
   if (!(aligned16(a_moga) && aligned16(a_stga) && aligned16(a_frame) && aligned16(o))) return MOGA_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
   const float alpha = 1.f / 3.f;
   const int lpr = lanes_per_row(dtype, D);
-#define MOGA_MERGE_FWD(LPR, BF)                                                                          \
-  merge3_fwd_kernel<LPR, BF><<<blocks, 256, 0, st>>>((const uintx4_t*)a_moga, (const uintx4_t*)a_stga,   \
-                                                     (const uintx4_t*)a_frame, inv_moga, inv_stga,       \
-                                                     inv_frame, gate, alpha, N, H, (uintx4_t*)o)
+#define MOGA_MERGE_FWD(LPR, BF)                                                                                                    \
+  with_slots(few_slots(N), N, [&](auto slots, unsigned blocks) {                                                                   \
+    merge3_fwd_kernel<LPR, BF, slots.value><<<blocks, 256, 0, st>>>((const uintx4_t*)a_moga, (const uintx4_t*)a_stga,              \
+                                                                    (const uintx4_t*)a_frame, inv_moga, inv_stga, inv_frame, gate, \
+                                                                    alpha, N, H, (uintx4_t*)o);                                    \
+  })
   if (dtype == MOGA_BF16) MOGA_MERGE_FWD(16, true);
   else if (lpr == 16) MOGA_MERGE_FWD(16, false);
   else MOGA_MERGE_FWD(32, false);
@@ -1237,15 +1355,15 @@ static int merge3_bwd(const void* d_o, const void* a_moga, int dtype, const int3
   if (!(aligned16(d_o) && aligned16(a_moga) && aligned16(d_a_moga) && aligned16(d_a_stga) && aligned16(d_a_frame)))
     return MOGA_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)stream;
-  const unsigned blocks = (unsigned)((N + kSlotsPerBlock - 1) / kSlotsPerBlock);
   const float alpha = 1.f / 3.f;
   const int lpr = lanes_per_row(dtype, D);
-#define MOGA_MERGE_BWD(LPR, BF, ROWS)                                                                    \
-  merge3_bwd_kernel<LPR, BF, ROWS><<<blocks, 256, 0, st>>>((const uintx4_t*)d_o, (const uintx4_t*)a_moga,      \
-                                                     inv_moga, inv_stga, inv_frame, gate, alpha, N, H,   \
-                                                     (uintx4_t*)d_a_moga, (uintx4_t*)d_a_stga,           \
-                                                     (uintx4_t*)d_a_frame, d_gate,                        \
-                                                     rows ? *rows : Merge3Rows{})
+#define MOGA_MERGE_BWD(LPR, BF, ROWS)                                                                                                  \
+  with_slots(few_slots_of_sums(N), N, [&](auto slots, unsigned blocks) {                                                               \
+    merge3_bwd_kernel<LPR, BF, ROWS, slots.value><<<blocks, 256, 0, st>>>((const uintx4_t*)d_o, (const uintx4_t*)a_moga, inv_moga,     \
+                                                                          inv_stga, inv_frame, gate, alpha, N, H, (uintx4_t*)d_a_moga, \
+                                                                          (uintx4_t*)d_a_stga, (uintx4_t*)d_a_frame, d_gate,           \
+                                                                          rows ? *rows : Merge3Rows{});                                \
+  })
   if (dtype == MOGA_BF16 && rows) MOGA_MERGE_BWD(16, true, true);
   else if (dtype == MOGA_BF16) MOGA_MERGE_BWD(16, true, false);
   else if (lpr == 16 && rows) MOGA_MERGE_BWD(16, false, true);

@@ -423,6 +423,23 @@ Tensor gather3_bwd(const Tensor& g_moga, const Tensor& inv_moga, const Tensor& g
   return d_src;
 }
 
+std::tuple<Tensor, Tensor, Tensor> gather3_bwd_qkv(const Tensor& gq_m, const Tensor& gk_m, const Tensor& gv_m, const Tensor& inv_moga,
+                                                   const Tensor& gq_s, const Tensor& gk_s, const Tensor& gv_s, const Tensor& q_slot,
+                                                   const Tensor& inv_cu, const Tensor& inv_slots, const Tensor& gq_f, const Tensor& gk_f,
+                                                   const Tensor& gv_f, const OptTensor& inv_frame, const OptStream& stream) {
+  require(gq_m, gk_m, gv_m, inv_moga, gq_s, gk_s, gv_s, q_slot, inv_cu, inv_slots, gq_f, gk_f, gv_f, inv_frame);
+  const Call call(stream);
+  need_dims(gq_m, 3);
+  need_dims(gk_s, 3);
+  const int64_t H = gq_m.size(0), N = gq_m.size(1), D = gq_m.size(2), Nk = gk_s.size(1);
+  Tensor d_q = call.make({N, H, D}, gq_m), d_k = call.make({N, H, D}, gk_m), d_v = call.make({N, H, D}, gv_m);
+  check("moga_gather3_bwd_qkv",
+        moga_gather3_bwd_qkv(ptr(gq_m), ptr(gk_m), ptr(gv_m), as<int32_t>(inv_moga), ptr(gq_s), ptr(gk_s), ptr(gv_s), as<int32_t>(q_slot),
+                             as<int32_t>(inv_cu), as<int32_t>(inv_slots), Nk, ptr(gq_f), ptr(gk_f), ptr(gv_f), as<int32_t>(inv_frame),
+                             dt(gq_m), N, (int)H, (int)D, ptr(d_q), ptr(d_k), ptr(d_v), call.stream()));
+  return {d_q, d_k, d_v};
+}
+
 Tensor merge3_fwd(const Tensor& a_moga, const Tensor& a_stga, const Tensor& a_frame, const OptTensor& inv_moga, const OptTensor& inv_stga,
                   const OptTensor& inv_frame, const Tensor& gate, const OptStream& stream) {
   require(a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate);
@@ -605,6 +622,7 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("gather_rows_bwd", &gather_rows_bwd, nogil);
   m.def("gather3_fwd", &gather3_fwd);
   m.def("gather3_bwd", &gather3_bwd, nogil);
+  m.def("gather3_bwd_qkv", &gather3_bwd_qkv, nogil);
   m.def("merge3_fwd", &merge3_fwd, nogil);
   m.def("merge3_bwd", &merge3_bwd, nogil);
   m.def("merge3_bwd_rows", &merge3_bwd_rows, nogil);
