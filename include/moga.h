@@ -38,6 +38,7 @@ extern "C" {
 
 #define MOGA_MAX_GROUPS 256          /* router groups M */
 #define MOGA_MAX_SEGMENTS (1 << 24)  /* static groups G of the moga_varlen_* calls */
+#define MOGA_MAX_CALLS 3             /* calls of moga_varlen_attn_fwd_calls and moga_varlen_attn_bwd_rows_calls */
 
 typedef enum {
   MOGA_OK = 0,
@@ -343,6 +344,35 @@ int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, 
                               const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k, int G,
                               float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
                               void* ws, size_t ws_bytes, void* stream);
+
+/*
+ * n independent calls (1 .. MOGA_MAX_CALLS) of moga_varlen_attn_fwd, or of moga_varlen_attn_bwd_rows, of the same dtype, H, D and scale:
+ * the branches of Section 3.2's block.  Arguments, checks and results as there (all are checked before anything is launched); the BF16
+ * ones run together, so that the blocks of one fill the last round of another, and their last rounds are not split.
+ */
+typedef struct {
+  const void *qh, *kh, *vh;
+  const int32_t *cu_seqlens_q, *cu_seqlens_k;
+  int64_t Nq, Nk;
+  int G;
+  void* oh;
+  float* lse;
+  void* ws;
+  size_t ws_bytes;
+} moga_attn_fwd_call;
+typedef struct {
+  const void *d_oh, *qh, *kh, *vh, *oh;
+  const float* lse;
+  const int32_t *cu_seqlens_q, *cu_seqlens_k;
+  int64_t Nq, Nk;
+  int G;
+  void *d_qh, *d_kh, *d_vh;
+  void* ws;
+  size_t ws_bytes;
+} moga_attn_bwd_call;
+int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n, int dtype, int H, int D, float softmax_scale, void* stream);
+int moga_varlen_attn_bwd_rows_calls(const moga_attn_bwd_call* calls, int n, int dtype, int H, int D, float softmax_scale,
+                                    void* stream);
 
 /*
  * Static groups of Section 3.2 ("Spatial-Temporal Group Attention"), built on the HOST: the lists

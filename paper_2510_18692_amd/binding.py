@@ -68,6 +68,8 @@ _SIGNATURES = {
                                     _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_varlen_attn_bwd_rows": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i64, _i32, _i32, _vp, _vp, _i32,
                                          _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "moga_varlen_attn_fwd_calls": (_i32, [_vp, _i32, _i32, _i32, _i32, _f32, _vp]),
+    "moga_varlen_attn_bwd_rows_calls": (_i32, [_vp, _i32, _i32, _i32, _i32, _f32, _vp]),
     "moga_stga_index_sizes": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _vp, _vp]),
     "moga_stga_build_index": (_i32, [_i32, _i32, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _vp, _vp, _vp, _vp, _vp,
                                      _vp, _vp]),
@@ -304,6 +306,16 @@ def moga_varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, 
     return _nat.varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, softmax_scale, _st(stream))
 
 
+def moga_varlen_attn_fwd_calls(calls, softmax_scale, stream=None):
+    """calls: up to three (qh, kh, vh, cu_seqlens_q, cu_seqlens_k), run together -> [(oh, lse)]"""
+    return _nat.varlen_attn_fwd_calls(calls, softmax_scale, _st(stream))
+
+
+def moga_varlen_attn_bwd_rows_calls(calls, softmax_scale, stream=None):
+    """calls: up to three (d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, ws), run together -> [(d_qh, d_kh, d_vh)]"""
+    return _nat.varlen_attn_bwd_rows_calls(calls, softmax_scale, _st(stream))
+
+
 def moga_stga_build_index(T, Hh, Ww, wh, ww, tg, shot_of_frame, a_prev=1, a_next=1, device="cuda"):
     """Static index lists (host builder), uploaded to `device` (None keeps them as numpy arrays)."""
     import numpy as np
@@ -421,15 +433,15 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
     pm = moga_permute(group, w.shape[0], stream=stream)
     pm["qh"], pm["kh"], pm["vh"], qs, ks, vs, qf, kf, vf = moga_gather3_fwd(q, k, v, pm["inv_perm"], si["q_slot"], si["inv_cu"],
                                                                             si["inv_slots"], stream=stream)
-    a_m, lse_m = moga_group_attn_fwd(pm["qh"], pm["kh"], pm["vh"], pm["cu_seqlens"], softmax_scale, stream=stream)
-    a_s, lse_s = moga_varlen_attn_fwd(qs, ks, vs, si["cu_q"], si["cu_k"], softmax_scale, stream=stream)
     ident = torch.arange(N + 1, dtype=torch.int32, device=dev)
     cu_f = torch.arange(0, N + 1, Hh * Ww, dtype=torch.int32, device=dev)
     if stream is not None and stream != torch.cuda.current_stream():   # made on the current stream, read on `stream`
         stream.wait_stream(torch.cuda.current_stream())
         for t in (ident, cu_f):
             t.record_stream(stream)
-    a_f, lse_f = moga_varlen_attn_fwd(qf, kf, vf, cu_f, cu_f, softmax_scale, stream=stream)
+    calls = [(pm["qh"], pm["kh"], pm["vh"], pm["cu_seqlens"], pm["cu_seqlens"]), (qs, ks, vs, si["cu_q"], si["cu_k"]),
+             (qf, kf, vf, cu_f, cu_f)]
+    (a_m, lse_m), (a_s, lse_s), (a_f, lse_f) = moga_varlen_attn_fwd_calls(calls, softmax_scale, stream=stream)
     o = moga_merge3_fwd(a_m, a_s, a_f, pm["inv_perm"], si["q_slot"], None, gate, stream=stream)
     return {"o": o, "group": group, "gate": gate, "probs": probs, "pm": pm, "a_m": a_m, "lse_m": lse_m,
             "qs": qs, "ks": ks, "vs": vs, "a_s": a_s, "lse_s": lse_s, "qf": qf, "kf": kf, "vf": vf,
@@ -443,15 +455,20 @@ def visual_backward(fwd, x, w, d_o, softmax_scale, stream=None):
         d_o, fwd["a_m"], fwd["a_s"], fwd["a_f"], pm["inv_perm"], si["q_slot"], None, fwd["gate"],
         (fwd["lse_m"], fwd["lse_s"], fwd["lse_f"]), softmax_scale, pm["cu_seqlens"], si["cu_q"], fwd["ks"].shape[1], fwd["cu_f"],
         stream=stream)
-    dqm, dkm, dvm = moga_varlen_attn_bwd_rows(d_m, pm["qh"], pm["kh"], pm["vh"], fwd["a_m"], fwd["lse_m"],
-                                              pm["cu_seqlens"], pm["cu_seqlens"], softmax_scale, ws_m, stream=stream)
-    del d_m, ws_m
-    dqs, dks, dvs = moga_varlen_attn_bwd_rows(d_s, fwd["qs"], fwd["ks"], fwd["vs"], fwd["a_s"], fwd["lse_s"],
-                                              si["cu_q"], si["cu_k"], softmax_scale, ws_s, stream=stream)
-    del d_s, ws_s
-    dqf, dkf, dvf = moga_varlen_attn_bwd_rows(d_f, fwd["qf"], fwd["kf"], fwd["vf"], fwd["a_f"], fwd["lse_f"],
-                                              fwd["cu_f"], fwd["cu_f"], softmax_scale, ws_f, stream=stream)
-    del d_f, ws_f
+    calls = [(d_m, pm["qh"], pm["kh"], pm["vh"], fwd["a_m"], fwd["lse_m"], pm["cu_seqlens"], pm["cu_seqlens"], ws_m),
+             (d_s, fwd["qs"], fwd["ks"], fwd["vs"], fwd["a_s"], fwd["lse_s"], si["cu_q"], si["cu_k"], ws_s),
+             (d_f, fwd["qf"], fwd["kf"], fwd["vf"], fwd["a_f"], fwd["lse_f"], fwd["cu_f"], fwd["cu_f"], ws_f)]
+    del d_m, d_s, d_f, ws_m, ws_s, ws_f
+    # Together the three fill each other's last rounds (2 % at 64 frames x 12 heads, 20 % at 8 x 3).  Of tensors above 2 GiB, whose calls have
+    # hundreds of rounds, one at a time, so that what a call read is free for the next.
+    together = d_o.numel() * d_o.element_size() <= 2 << 30
+    grads = []
+    while calls:
+        n = len(calls) if together else 1
+        grads += moga_varlen_attn_bwd_rows_calls(calls[:n], softmax_scale, stream=stream)
+        del calls[:n]
+    (dqm, dkm, dvm), (dqs, dks, dvs), (dqf, dkf, dvf) = grads
+    del grads
     # every token-order gradient is written once: MoGA rows through inv_perm, the static rows through
     # their slot lists (queries are listed once, keys possibly several times), the frame rows in place
     d_q, d_k, d_v = moga_gather3_bwd_qkv((dqm, dkm, dvm), pm["inv_perm"], (dqs, dks, dvs), si["q_slot"], si["inv_cu"], si["inv_slots"],

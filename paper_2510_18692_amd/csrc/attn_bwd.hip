@@ -17,6 +17,7 @@
 // LDS read.  fp32 (attn_f32.h): delta, then dQ and dK/dV in one launch.
 #include <algorithm>
 #include <atomic>
+#include <climits>
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
@@ -164,6 +165,15 @@ static int64_t small_group_rows(int64_t Nq, int H, bool room) {
   if (rounds < 33) return room ? 2800 : 8192;
   if (rounds < 100) return rounds < 75 ? 2000 : 1450;
   return rounds < 200 ? 1300 : rounds < 350 ? 860 : rounds < 600 ? 650 : rounds < 1000 ? 450 : 400;
+}
+
+// The same for the calls of one launch, all of them with `rows` queries: a second launch, for the other kernels, costs more than the finer tiles
+// of some give.  Blocks of all three branches, forward and backward, with the large kernels for all against the small ones for groups of less than
+// 300 / 700 / 1,200 rows: 2.6 rounds 0.538 ms and 0.590 / 0.590 / 0.569, 3.4 0.743 and 0.743 / 0.742 / 0.799, 5.1 1.200 and 1.241 / 1.241 /
+// 1.241; groups of 104 queries, 4.3 rounds 0.883 and 0.901, 34 rounds 9.12 and 8.92, 69 rounds 15.5 and 15.25.
+static int64_t calls_small_group_rows(int64_t rows, int H) {
+  const int64_t rounds = 100 * rows * H / (256 * kCus);
+  return rounds < 100 ? small_group_rows(rows, H, false) : rounds < 800 ? 0 : 300;
 }
 
 AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
@@ -367,35 +377,38 @@ extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
   return bwd_rows_bytes(Nq, H) + 16 + 2 * ((size_t)G + 1) * sizeof(int32_t);
 }
 
-static int varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse,
-                           int dtype, int64_t Nq, int64_t Nk, int H, int D, const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k,
-                           int G, float softmax_scale, void* d_qh, void* d_kh, void* d_vh, bool row_constants, void* ws,
-                           size_t ws_bytes, void* stream) {
-  const int bad = check_attn_bwd_args(Nq, Nk, H, D, G, softmax_scale, dtype);
+static int check_varlen_bwd(const moga_attn_bwd_call& c, int dtype, int H, int D, float softmax_scale) {
+  const int bad = check_attn_bwd_args(c.Nq, c.Nk, H, D, c.G, softmax_scale, dtype);
   if (bad) return bad;
-  if (G > MOGA_MAX_SEGMENTS) return MOGA_ERR_UNSUPPORTED;
-  if (Nq == 0 && Nk == 0) return MOGA_OK;
-  if (!cu_seqlens_q || !cu_seqlens_k) return MOGA_ERR_INVALID_ARG;
-  if (Nq > 0 && (!d_oh || !qh || !oh || !lse || !d_qh)) return MOGA_ERR_INVALID_ARG;
-  if (Nk > 0 && (!kh || !vh || !d_kh || !d_vh)) return MOGA_ERR_INVALID_ARG;
-  if (!(aligned16(d_oh) && aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh) &&
-        aligned16(d_qh) && aligned16(d_kh) && aligned16(d_vh)))
+  if (c.G > MOGA_MAX_SEGMENTS) return MOGA_ERR_UNSUPPORTED;
+  if (c.Nq == 0 && c.Nk == 0) return MOGA_OK;
+  if (!c.cu_seqlens_q || !c.cu_seqlens_k) return MOGA_ERR_INVALID_ARG;
+  if (c.Nq > 0 && (!c.d_oh || !c.qh || !c.oh || !c.lse || !c.d_qh)) return MOGA_ERR_INVALID_ARG;
+  if (c.Nk > 0 && (!c.kh || !c.vh || !c.d_kh || !c.d_vh)) return MOGA_ERR_INVALID_ARG;
+  if (!(aligned16(c.d_oh) && aligned16(c.qh) && aligned16(c.kh) && aligned16(c.vh) && aligned16(c.oh) &&
+        aligned16(c.d_qh) && aligned16(c.d_kh) && aligned16(c.d_vh)))
     return MOGA_ERR_INVALID_ARG;
+  if (c.Nq > 0 && (!c.ws || c.ws_bytes < moga_varlen_attn_bwd_ws_bytes(c.Nq, H, c.G) || !aligned16(c.ws))) return MOGA_ERR_WORKSPACE;
+  return MOGA_OK;
+}
+
+static int varlen_attn_bwd(const moga_attn_bwd_call& c, int dtype, int H, int D, float softmax_scale, bool row_constants, void* stream) {
+  const int bad = check_varlen_bwd(c, dtype, H, D, softmax_scale);
+  if (bad || (c.Nq == 0 && c.Nk == 0)) return bad;
   hipStream_t st = (hipStream_t)stream;
-  if (Nq == 0) {   // keys without any query: zero gradients
-    const int64_t nf = Nk * (int64_t)H * D / (dtype == MOGA_BF16 ? 2 : 1);
-    launch_fill_zero((float*)d_kh, nf, st);
-    launch_fill_zero((float*)d_vh, nf, st);
+  if (c.Nq == 0) {   // keys without any query: zero gradients
+    const int64_t nf = c.Nk * (int64_t)H * D / (dtype == MOGA_BF16 ? 2 : 1);
+    launch_fill_zero((float*)c.d_kh, nf, st);
+    launch_fill_zero((float*)c.d_vh, nf, st);
     return launch_status();
   }
-  const size_t need = moga_varlen_attn_bwd_ws_bytes(Nq, H, G);
-  if (!ws || ws_bytes < need || !aligned16(ws)) return MOGA_ERR_WORKSPACE;
-  const bool presum = G > MOGA_MAX_GROUPS;   // few groups: every block looks its tile up itself
-  int32_t* ts_q = presum ? (int32_t*)((char*)ws + bwd_rows_bytes(Nq, H) + 16) : nullptr;
-  int32_t* ts_k = presum ? ts_q + (G + 1) : nullptr;
-  return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts_q,
-                         ts_k, G, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
-                         presum ? SplitRoom{} : split_room(ws, need, ws_bytes), st);
+  const size_t need = moga_varlen_attn_bwd_ws_bytes(c.Nq, H, c.G);
+  const bool presum = c.G > MOGA_MAX_GROUPS;   // few groups: every block looks its tile up itself
+  int32_t* ts_q = presum ? (int32_t*)((char*)c.ws + bwd_rows_bytes(c.Nq, H) + 16) : nullptr;
+  int32_t* ts_k = presum ? ts_q + (c.G + 1) : nullptr;
+  return launch_attn_bwd(c.d_oh, c.qh, c.kh, c.vh, c.oh, c.lse, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, ts_q, ts_k, c.G,
+                         softmax_scale, c.d_qh, c.d_kh, c.d_vh, (float*)c.ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
+                         presum ? SplitRoom{} : split_room(c.ws, need, c.ws_bytes), st);
 }
 
 extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
@@ -404,8 +417,8 @@ extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void
                                     const int32_t* cu_seqlens_k, int G, float softmax_scale,
                                     void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
                                     void* stream) {
-  return varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, G, softmax_scale, d_qh, d_kh,
-                         d_vh, false, ws, ws_bytes, stream);
+  return varlen_attn_bwd({d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, Nq, Nk, G, d_qh, d_kh, d_vh, ws, ws_bytes}, dtype, H, D,
+                         softmax_scale, false, stream);
 }
 
 extern "C" int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, const void* vh,
@@ -414,8 +427,94 @@ extern "C" int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const
                                          const int32_t* cu_seqlens_k, int G, float softmax_scale,
                                          void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
                                          void* stream) {
-  return varlen_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, G, softmax_scale, d_qh, d_kh,
-                         d_vh, true, ws, ws_bytes, stream);
+  return varlen_attn_bwd({d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, Nq, Nk, G, d_qh, d_kh, d_vh, ws, ws_bytes}, dtype, H, D,
+                         softmax_scale, true, stream);
+}
+
+// The bf16 calls `which` in one launch of the kernels for small groups, or of the large ones with `bm` query rows and `bk` keys per block.
+static int launch_bwd_calls(const moga_attn_bwd_call* calls, const int* which, int n, bool small, int bm, int bk, int H, float softmax_scale,
+                            hipStream_t st) {
+  AttnBwdCalls a = {};
+  struct Segment {
+    int what;
+    int64_t blocks;
+    double length;   // of a block
+  } seg[2 * kMaxCalls];
+  std::fill(a.first, a.first + 2 * kMaxCalls, INT_MAX);
+  int32_t* ts[kMaxCalls];
+  int segments = 0;
+  for (int i = 0; i < n; ++i) {
+    const moga_attn_bwd_call& c = calls[which[i]];
+    char* ws = (char*)c.ws;
+    ts[i] = c.G > MOGA_MAX_GROUPS ? (int32_t*)(ws + bwd_rows_bytes(c.Nq, H) + 16) : nullptr;
+    a.c[i] = {(const unsigned short*)c.d_oh, (const unsigned short*)c.qh, (const unsigned short*)c.kh, (const unsigned short*)c.vh,
+              (float*)ws + c.Nq * (int64_t)H, (float*)ws, c.cu_seqlens_q, c.cu_seqlens_k, ts[i], ts[i] ? ts[i] + (c.G + 1) : nullptr, c.Nq,
+              c.Nk, (unsigned short*)c.d_qh, (unsigned short*)c.d_kh, (unsigned short*)c.d_vh, (int*)(ws + bwd_rows_bytes(c.Nq, H)), c.G};
+    // products: three of bm rows a key, four of bk keys a query
+    seg[segments++] = {2 * i, (max_tiles(c.Nq, c.G, bm) * H + 7) / 8 * 8, 3. * bm * (double)c.Nk / c.G};
+    if (c.Nk > 0) seg[segments++] = {2 * i + 1, (max_tiles(c.Nk, c.G, bk) * H + 7) / 8 * 8, 4. * bk * (double)c.Nq / c.G};
+  }
+  std::stable_sort(seg, seg + segments, [](const Segment& x, const Segment& y) { return x.length > y.length; });
+  int64_t blocks = 0;
+  for (int s = 0; s < segments; ++s) {
+    a.first[s] = (int)blocks;
+    a.what[s] = seg[s].what;
+    blocks += seg[s].blocks;
+    if (!grid_fits(blocks, small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
+  }
+  for (int i = 0; i < n; ++i)
+    if (ts[i]) {
+      if (a.c[i].Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(a.c[i].cu_k, a.c[i].M, bk, ts[i] + (a.c[i].M + 1));
+      tile_start_kernel<<<1, 1024, 0, st>>>(a.c[i].cu_q, a.c[i].M, bm, ts[i]);
+    }
+  const int spin = g_spin_limit.load();
+  if (small) attn_bwd_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale, spin);
+  else if (bm == 384) attn_bwd_calls_kernel<192, 384><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin);
+  else attn_bwd_calls_kernel<128, 256><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin);
+  return launch_status();
+}
+
+extern "C" int moga_varlen_attn_bwd_rows_calls(const moga_attn_bwd_call* calls, int n, int dtype, int H, int D, float softmax_scale,
+                                               void* stream) {
+  if (!calls || n < 1 || n > MOGA_MAX_CALLS) return MOGA_ERR_INVALID_ARG;
+  int64_t rows = 0;
+  int order[kMaxCalls], count = 0;
+  bool together = dtype == MOGA_BF16;
+  for (int i = 0; i < n; ++i) {
+    const moga_attn_bwd_call& c = calls[i];
+    const int bad = check_varlen_bwd(c, dtype, H, D, softmax_scale);
+    if (bad) return bad;
+    if (dtype == MOGA_BF16 && !bf16_rows_ok(c.Nq, c.Nk)) return MOGA_ERR_UNSUPPORTED;
+    rows += c.Nq;
+    if (c.Nq > 0) order[count++] = i;
+    else if (c.Nk > 0) together = false;   // keys without any query
+  }
+  if (!together || count < 2) {
+    for (int i = 0; i < n; ++i) {
+      const int rc = varlen_attn_bwd(calls[i], dtype, H, D, softmax_scale, true, stream);
+      if (rc != MOGA_OK) return rc;
+    }
+    return MOGA_OK;
+  }
+  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H)); };
+  int* const mid = std::stable_partition(order, order + count, [&](int i) { return !small(i); });
+  const int large = (int)(mid - order);
+  if (large > 0) {
+    SideShape q[kMaxCalls], k[kMaxCalls];
+    for (int i = 0; i < large; ++i) {
+      const moga_attn_bwd_call& c = calls[order[i]];
+      q[i] = {c.Nq, c.Nk, c.G};
+      k[i] = {c.Nk, c.Nq, c.G};
+    }
+    auto cost = [&](int bm, int bk, double weight) {   // three products a pair of rows in dQ, four in dK/dV; a block of keys is half as long
+      return 3 * calls_cost(q, large, H, bm, 256, weight) + 2 * calls_cost(k, large, H, bk, 128, weight);
+    };
+    const bool few = cost(256, 128, 10) < cost(384, 192, 13);
+    const int rc = launch_bwd_calls(calls, order, large, false, few ? 256 : 384, few ? 128 : 192, H, softmax_scale, (hipStream_t)stream);
+    if (rc != MOGA_OK) return rc;
+  }
+  if (count > large) return launch_bwd_calls(calls, mid, count - large, true, 128, 64, H, softmax_scale, (hipStream_t)stream);
+  return MOGA_OK;
 }
 
 extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k, const void* v,

@@ -9,6 +9,7 @@
 namespace moga {
 
 constexpr int kHeadDim = 128;  // head_dim of the bf16 MFMA kernels
+constexpr int kMaxCalls = MOGA_MAX_CALLS;   // of one launch
 
 // Tile schedule.  Every group g with n_g rows contributes ceil(n_g / rows_per_tile) tiles;
 // tiles never straddle a group boundary.  `tile` is a flat index over all groups in order.
@@ -303,6 +304,24 @@ inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int 
 }
 inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nq, Nk, H, M, 256, 1, room); }
 inline Blocks key_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nk, Nq, H, M, 128, 2, room); }
+
+// The same for the large-group calls of one launch, by work per CU: tiles of all of them, and half a block of the shortest for the end.
+struct SideShape {
+  int64_t N, other;   // rows of this side; of the side that they sweep
+  int M;
+};
+inline double calls_cost(const SideShape* c, int n, int H, int rows, int few, double weight) {
+  constexpr double kStartRows = 640;
+  double work = 0, last = 0;
+  for (int i = 0; i < n; ++i) {
+    const int64_t mean = (c[i].N + c[i].M - 1) / c[i].M, of_group = (mean + rows - 1) / rows;
+    const double block = (double)((c[i].other + c[i].M - 1) / c[i].M) + kStartRows;
+    const double short_end = mean - (of_group - 1) * rows <= few ? weight - 10 : 0;
+    work += (weight * of_group - short_end) * c[i].M * H * block;
+    last = i == 0 ? block : std::min(last, block);
+  }
+  return work / kCus + weight * last / 2;
+}
 
 // What a bf16 call runs: the kernels for small groups, or the large ones and their blocks of queries (and of keys, backward).  room:
 // that of split_room (0 where M > MOGA_MAX_GROUPS).

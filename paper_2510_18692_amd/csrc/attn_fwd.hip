@@ -11,6 +11,7 @@
 //   * the kernel itself (software pipeline, LDS ring, direct-to-LDS loads) is in attn_pipe.h.
 // fp32 kernel (fp32 matrix instruction, full precision throughout): attn_f32.h.
 #include <algorithm>
+#include <climits>
 
 #include "attn_common.h"
 #include "attn_f32.h"
@@ -37,6 +38,12 @@ static int64_t small_group_rows(int64_t Nq, int H, bool split) {
   const int64_t rounds = 100 * Nq * H / (256 * kCus);   // in hundredths
   if (split && rounds < 75) return rounds < 20 ? 1500 : rounds < 33 ? 2700 : rounds < 50 ? 5632 : 4500;
   return rounds < 50 ? 5632 : rounds < 100 ? 6144 : rounds < 370 ? 2560 : rounds < 600 ? 1300 : 700;
+}
+
+// The same for the calls of one launch, all of them with `rows` queries (measured for both directions, see attn_bwd.hip).
+static int64_t calls_small_group_rows(int64_t rows, int H) {
+  const int64_t rounds = 100 * rows * H / (256 * kCus);
+  return rounds < 100 ? small_group_rows(rows, H, false) : rounds < 800 ? 0 : 300;
 }
 
 AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
@@ -182,21 +189,87 @@ extern "C" int moga_fused_attn_fwd(const void* q, const void* k, const void* v, 
 
 extern "C" size_t moga_varlen_attn_fwd_ws_bytes(int G) { return ((size_t)G + 1) * sizeof(int32_t); }
 
+static int check_varlen_fwd(const moga_attn_fwd_call& c, int dtype, int H, int D, float softmax_scale) {
+  const int bad = check_attn_args(c.Nq, c.Nk, H, D, c.G, softmax_scale, dtype);
+  if (bad) return bad;
+  if (c.G > MOGA_MAX_SEGMENTS) return MOGA_ERR_UNSUPPORTED;
+  if (c.Nq == 0) return MOGA_OK;
+  if (!c.qh || !c.cu_seqlens_q || !c.cu_seqlens_k || !c.oh || !c.lse) return MOGA_ERR_INVALID_ARG;
+  if (c.Nk > 0 && (!c.kh || !c.vh)) return MOGA_ERR_INVALID_ARG;
+  if (!(aligned16(c.qh) && aligned16(c.kh) && aligned16(c.vh) && aligned16(c.oh))) return MOGA_ERR_INVALID_ARG;
+  if (!c.ws || c.ws_bytes < moga_varlen_attn_fwd_ws_bytes(c.G)) return MOGA_ERR_WORKSPACE;
+  return MOGA_OK;
+}
+
 extern "C" int moga_varlen_attn_fwd(const void* qh, const void* kh, const void* vh, int dtype,
                                     int64_t Nq, int64_t Nk, int H, int D,
                                     const int32_t* cu_seqlens_q, const int32_t* cu_seqlens_k, int G,
                                     float softmax_scale, void* oh, float* lse, void* ws,
                                     size_t ws_bytes, void* stream) {
-  const int bad = check_attn_args(Nq, Nk, H, D, G, softmax_scale, dtype);
+  const int bad = check_varlen_fwd({qh, kh, vh, cu_seqlens_q, cu_seqlens_k, Nq, Nk, G, oh, lse, ws, ws_bytes}, dtype, H, D, softmax_scale);
   if (bad) return bad;
-  if (G > MOGA_MAX_SEGMENTS) return MOGA_ERR_UNSUPPORTED;
   if (Nq == 0) return MOGA_OK;
-  if (!qh || !cu_seqlens_q || !cu_seqlens_k || !oh || !lse) return MOGA_ERR_INVALID_ARG;
-  if (Nk > 0 && (!kh || !vh)) return MOGA_ERR_INVALID_ARG;
-  if (!(aligned16(qh) && aligned16(kh) && aligned16(vh) && aligned16(oh))) return MOGA_ERR_INVALID_ARG;
-  if (!ws || ws_bytes < moga_varlen_attn_fwd_ws_bytes(G)) return MOGA_ERR_WORKSPACE;
   int32_t* ts = G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)ws;   // few groups: every block looks its tile up itself
   const SplitRoom split = ts ? SplitRoom{} : split_room(ws, moga_varlen_attn_fwd_ws_bytes(G), ws_bytes);
   return launch_attn_fwd(qh, kh, vh, dtype, Nq, Nk, H, D, cu_seqlens_q, cu_seqlens_k, ts, G,
                          softmax_scale, oh, lse, TokenRows{}, split, (hipStream_t)stream);
+}
+
+// The bf16 calls `which` in one launch of the kernels for small groups, or of the large ones with `rows` per block.
+static int launch_fwd_calls(const moga_attn_fwd_call* calls, const int* which, int n, bool small, int rows, int H, float softmax_scale,
+                            hipStream_t st) {
+  AttnFwdCalls a = {};
+  int64_t blocks = 0;
+  std::fill(a.first, a.first + kMaxCalls, INT_MAX);
+  for (int i = 0; i < n; ++i) {
+    const moga_attn_fwd_call& c = calls[which[i]];
+    a.first[i] = (int)blocks;
+    blocks += (max_tiles(c.Nq, c.G, rows) * H + 7) / 8 * 8;
+    if (!grid_fits(blocks, small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
+    int32_t* ts = c.G <= MOGA_MAX_GROUPS ? nullptr : (int32_t*)c.ws;
+    a.c[i] = {(const unsigned short*)c.qh, (const unsigned short*)c.kh, (const unsigned short*)c.vh, c.cu_seqlens_q, c.cu_seqlens_k, ts, c.Nq,
+              c.Nk, (unsigned short*)c.oh, c.lse, c.G};
+  }
+  for (int i = 0; i < n; ++i)
+    if (a.c[i].tile_start) tile_start_kernel<<<1, 1024, 0, st>>>(a.c[i].cu_q, a.c[i].M, rows, (int32_t*)calls[which[i]].ws);
+  if (small) attn_fwd_bf16_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale);
+  else if (rows == 384) attn_fwd_bf16_pipe_calls_kernel<384><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale);
+  else attn_fwd_bf16_pipe_calls_kernel<256><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale);
+  return launch_status();
+}
+
+extern "C" int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n, int dtype, int H, int D, float softmax_scale,
+                                          void* stream) {
+  if (!calls || n < 1 || n > MOGA_MAX_CALLS) return MOGA_ERR_INVALID_ARG;
+  int64_t rows = 0;
+  int order[kMaxCalls], count = 0;
+  for (int i = 0; i < n; ++i) {
+    const int bad = check_varlen_fwd(calls[i], dtype, H, D, softmax_scale);
+    if (bad) return bad;
+    rows += calls[i].Nq;
+    if (calls[i].Nq > 0) order[count++] = i;
+  }
+  if (dtype != MOGA_BF16 || count < 2) {
+    for (int i = 0; i < count; ++i) {
+      const moga_attn_fwd_call& c = calls[order[i]];
+      const int rc = moga_varlen_attn_fwd(c.qh, c.kh, c.vh, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, c.G, softmax_scale,
+                                          c.oh, c.lse, c.ws, c.ws_bytes, stream);
+      if (rc != MOGA_OK) return rc;
+    }
+    return MOGA_OK;
+  }
+  // longest blocks first, the calls of the large kernels before those of the small ones
+  std::stable_sort(order, order + count, [&](int a, int b) { return calls[a].Nk * calls[b].G > calls[b].Nk * calls[a].G; });
+  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H)); };
+  int* const mid = std::stable_partition(order, order + count, [&](int i) { return !small(i); });
+  const int large = (int)(mid - order);
+  if (large > 0) {
+    SideShape q[kMaxCalls];
+    for (int i = 0; i < large; ++i) q[i] = {calls[order[i]].Nq, calls[order[i]].Nk, calls[order[i]].G};
+    const int bm = calls_cost(q, large, H, 256, 256, 10) < calls_cost(q, large, H, 384, 256, 13) ? 256 : 384;
+    const int rc = launch_fwd_calls(calls, order, large, false, bm, H, softmax_scale, (hipStream_t)stream);
+    if (rc != MOGA_OK) return rc;
+  }
+  if (count > large) return launch_fwd_calls(calls, mid, count - large, true, 128, H, softmax_scale, (hipStream_t)stream);
+  return MOGA_OK;
 }

@@ -464,14 +464,14 @@ __device__ __forceinline__ void pipe_issue(const PipeDma& d, int kv0, unsigned b
 // multiplied by gate[token] (Eq. 5) and written to its token.  lse stays in sorted order [H, N].
 // SPLIT: the last round is cut into pieces (find_work).
 // ROWS: query rows of a block, 384 or 256 (query_blocks chooses).
-template <int ROWS, bool GATHER = false, bool SPLIT = false>
-__global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
-    const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
+template <int ROWS, bool GATHER, bool SPLIT>
+__device__ __forceinline__ void attn_fwd_block(
+    int block, const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
-    float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
-    const float* __restrict__ gate = nullptr, SplitWs sw = {}, unsigned short* __restrict__ o_tok = nullptr) {
+    float* __restrict__ lse, const int32_t* __restrict__ perm,
+    const float* __restrict__ gate, SplitWs sw, unsigned short* __restrict__ o_tok) {
   constexpr int NW = 8;
   constexpr int kDmaPerTile = 2 * kDmaLoads<NW, 64>;   // direct-to-LDS instructions per thread per tile
   __shared__ __attribute__((aligned(1024))) unsigned short Ks[kPipeNBuf][64 * kHeadDim];
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
   __shared__ __attribute__((aligned(256))) int toks[GATHER ? 512 : 1];   // gather mode: tokens of eight tiles
 
   WorkTile sp;
-  if (!find_work<SPLIT>(cu_q, tile_start, M, H, ROWS, blockIdx.x, sp)) return;
+  if (!find_work<SPLIT>(cu_q, tile_start, M, H, ROWS, block, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -589,6 +589,45 @@ __global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
   };
   if (ROWS > 256 && ge - q0 > 256) sweep(std::integral_constant<int, ROWS / 128>());
   else sweep(std::integral_constant<int, 2>());
+}
+
+template <int ROWS, bool GATHER = false, bool SPLIT = false>
+__global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_kernel(
+    const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
+    const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
+    const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
+    int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
+    float* __restrict__ lse, const int32_t* __restrict__ perm = nullptr,
+    const float* __restrict__ gate = nullptr, SplitWs sw = {}, unsigned short* __restrict__ o_tok = nullptr) {
+  attn_fwd_block<ROWS, GATHER, SPLIT>(blockIdx.x, qh, kh, vh, cu_q, cu_k, tile_start, M, Nq, Nk, H, scale, oh, lse, perm, gate, sw, o_tok);
+}
+
+// Several calls in one launch (the branches of Section 3.2's block): call i takes the blocks from first[i] on, a multiple of 8 (the XCDs).
+struct AttnFwdCall {
+  const unsigned short *qh, *kh, *vh;
+  const int32_t *cu_q, *cu_k, *tile_start;
+  int64_t Nq, Nk;
+  unsigned short* oh;
+  float* lse;
+  int M;
+};
+struct AttnFwdCalls {
+  AttnFwdCall c[kMaxCalls];
+  int first[kMaxCalls];   // INT_MAX: none
+};
+template <typename T>
+__device__ __forceinline__ int call_of_block(const T& calls, int block) {
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < kMaxCalls; ++k) i += block >= calls.first[k];
+  return i;
+}
+template <int ROWS>
+__global__ __launch_bounds__(512) void attn_fwd_bf16_pipe_calls_kernel(AttnFwdCalls calls, int H, float scale) {
+  const int i = call_of_block(calls, blockIdx.x);
+  const AttnFwdCall& c = calls.c[i];
+  attn_fwd_block<ROWS, false, false>(blockIdx.x - calls.first[i], c.qh, c.kh, c.vh, c.cu_q, c.cu_k, c.tile_start, c.M, c.Nq, c.Nk, H, scale,
+                                     c.oh, c.lse, nullptr, nullptr, SplitWs{}, nullptr);
 }
 
 // Pieces of every query tile of the last round, with their maxima m_k in exponents of two: O = sum O_k 2^(m_k - m) / l,

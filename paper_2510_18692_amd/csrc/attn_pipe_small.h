@@ -15,8 +15,8 @@ namespace moga {
 constexpr int kSmallTileBytes = 32 * kHeadDim * 2;   // 8 KB per K (or V) tile of 32 keys
 
 // Arguments as attn_fwd_bf16_pipe_kernel (no gather mode); tiles of 128 query rows.
-__global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
-    const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
+__device__ __forceinline__ void attn_fwd_small_block(
+    int block, const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
     const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned short Vs[4][32 * kHeadDim];
 
   WorkTile sp;
-  if (!find_work<false>(cu_q, tile_start, M, H, BM, blockIdx.x, sp)) return;
+  if (!find_work<false>(cu_q, tile_start, M, H, BM, block, sp)) return;
   const TileInfo& ti = sp.ti;
   const int head = sp.head;
   const int ge = ti.row_end, q0 = ti.tile_row;   // query rows of the group end at ge
@@ -134,6 +134,23 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
 
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the look-ahead loads before the LDS is released
   store_output<false>(st, q0w, ge, head, head_off, H, oh, lse, perm, gate, o_tok);
+}
+
+__global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_kernel(
+    const unsigned short* __restrict__ qh, const unsigned short* __restrict__ kh,
+    const unsigned short* __restrict__ vh, const int32_t* __restrict__ cu_q,
+    const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
+    int64_t Nq, int64_t Nk, int H, float scale, unsigned short* __restrict__ oh,
+    float* __restrict__ lse, const int32_t* __restrict__ perm, const float* __restrict__ gate,
+    unsigned short* __restrict__ o_tok) {
+  attn_fwd_small_block(blockIdx.x, qh, kh, vh, cu_q, cu_k, tile_start, M, Nq, Nk, H, scale, oh, lse, perm, gate, o_tok);
+}
+
+__global__ __launch_bounds__(256, 2) void attn_fwd_bf16_small_calls_kernel(AttnFwdCalls calls, int H, float scale) {
+  const int i = call_of_block(calls, blockIdx.x);
+  const AttnFwdCall& c = calls.c[i];
+  attn_fwd_small_block(blockIdx.x - calls.first[i], c.qh, c.kh, c.vh, c.cu_q, c.cu_k, c.tile_start, c.M, c.Nq, c.Nk, H, scale, c.oh, c.lse,
+                       nullptr, nullptr, nullptr);
 }
 
 }  // namespace moga

@@ -13,6 +13,7 @@
 
 #include <optional>
 #include <tuple>
+#include <vector>
 
 #include "moga.h"
 
@@ -371,6 +372,55 @@ std::tuple<Tensor, Tensor, Tensor> varlen_attn_bwd(const Tensor& d_oh, const Ten
   return {d_qh, d_kh, d_vh};
 }
 
+// (qh, kh, vh, cu_q, cu_k) of each call -> (oh, lse)
+using FwdCallIn = std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor>;
+std::vector<std::tuple<Tensor, Tensor>> varlen_attn_fwd_calls(const std::vector<FwdCallIn>& in, double scale, const OptStream& stream) {
+  TORCH_CHECK(!in.empty() && in.size() <= MOGA_MAX_CALLS, "one to ", MOGA_MAX_CALLS, " calls");
+  const Call call(stream);
+  const Tensor& first = std::get<0>(in[0]);
+  std::vector<std::tuple<Tensor, Tensor>> out;
+  std::vector<Tensor> ws;
+  std::vector<moga_attn_fwd_call> c;
+  for (const auto& [qh, kh, vh, cu_q, cu_k] : in) {
+    require(qh, kh, vh, cu_q, cu_k);
+    need_dims(qh, 3);
+    TORCH_CHECK(qh.scalar_type() == first.scalar_type() && qh.size(0) == first.size(0) && qh.size(2) == first.size(2),
+                "calls of one type, number of heads and head size");
+    const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
+    out.emplace_back(call.make({H, Nq, D}, qh), call.make({H, Nq}, qh, at::kFloat));
+    ws.push_back(call.workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_FWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh));
+    c.push_back({ptr(qh), ptr(kh), ptr(vh), as<int32_t>(cu_q), as<int32_t>(cu_k), Nq, Nk, (int)G, ptr(std::get<0>(out.back())),
+                 as<float>(std::get<1>(out.back())), ptr(ws.back()), (size_t)ws.back().numel()});
+  }
+  check("moga_varlen_attn_fwd_calls", moga_varlen_attn_fwd_calls(c.data(), (int)c.size(), dt(first), (int)first.size(0), (int)first.size(2),
+                                                                 (float)scale, call.stream()));
+  return out;
+}
+
+// (d_oh, qh, kh, vh, oh, lse, cu_q, cu_k, ws) of each call -> (d_qh, d_kh, d_vh)
+using BwdCallIn = std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor, Tensor, Tensor, Tensor, Tensor>;
+std::vector<std::tuple<Tensor, Tensor, Tensor>> varlen_attn_bwd_rows_calls(const std::vector<BwdCallIn>& in, double scale,
+                                                                           const OptStream& stream) {
+  TORCH_CHECK(!in.empty() && in.size() <= MOGA_MAX_CALLS, "one to ", MOGA_MAX_CALLS, " calls");
+  const Call call(stream);
+  const Tensor& first = std::get<1>(in[0]);
+  std::vector<std::tuple<Tensor, Tensor, Tensor>> out;
+  std::vector<moga_attn_bwd_call> c;
+  for (const auto& [d_oh, qh, kh, vh, oh, lse, cu_q, cu_k, ws] : in) {
+    require(d_oh, qh, kh, vh, oh, lse, cu_q, cu_k, ws);
+    need_dims(qh, 3);
+    TORCH_CHECK(qh.scalar_type() == first.scalar_type() && qh.size(0) == first.size(0) && qh.size(2) == first.size(2),
+                "calls of one type, number of heads and head size");
+    out.emplace_back(call.make(qh.sizes(), qh), call.make(kh.sizes(), kh), call.make(vh.sizes(), vh));
+    const auto& [d_qh, d_kh, d_vh] = out.back();
+    c.push_back({ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), as<int32_t>(cu_q), as<int32_t>(cu_k), qh.size(1), kh.size(1),
+                 (int)cu_q.size(0) - 1, ptr(d_qh), ptr(d_kh), ptr(d_vh), ptr(ws), (size_t)ws.numel()});
+  }
+  check("moga_varlen_attn_bwd_rows_calls", moga_varlen_attn_bwd_rows_calls(c.data(), (int)c.size(), dt(first), (int)first.size(0),
+                                                                           (int)first.size(2), (float)scale, call.stream()));
+  return out;
+}
+
 Tensor gather_rows(const Tensor& src, const Tensor& index, const OptStream& stream) {
   require(src, index);
   const Call call(stream);
@@ -618,6 +668,8 @@ PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
   m.def("fused_attn_bwd", &fused_attn_bwd, nogil);
   m.def("varlen_attn_fwd", &varlen_attn_fwd, nogil);
   m.def("varlen_attn_bwd", &varlen_attn_bwd, nogil);
+  m.def("varlen_attn_fwd_calls", &varlen_attn_fwd_calls, nogil);
+  m.def("varlen_attn_bwd_rows_calls", &varlen_attn_bwd_rows_calls, nogil);
   m.def("gather_rows", &gather_rows, nogil);
   m.def("gather_rows_bwd", &gather_rows_bwd, nogil);
   m.def("gather3_fwd", &gather3_fwd);
