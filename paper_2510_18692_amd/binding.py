@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libmoga.so")
 
 MOGA_F32, MOGA_BF16 = 0, 1
 (OP_ROUTE, OP_PERMUTE, OP_ATTN_FWD, OP_ATTN_BWD, OP_ROUTE_BWD, OP_BALANCE_LOSS, OP_VARLEN_ATTN_FWD,
- OP_VARLEN_ATTN_BWD) = range(8)
+ OP_VARLEN_ATTN_BWD, OP_ATTN_BWD_JOINT) = range(9)
 
 _c = ctypes
 _vp, _i64, _i32, _f32, _sz = _c.c_void_p, _c.c_int64, _c.c_int, _c.c_float, _c.c_size_t
@@ -46,7 +46,11 @@ _SIGNATURES = {
     "moga_unpermute_bwd": (_i32, [_vp, _vp, _i32, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp]),
     "moga_group_attn_bwd": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32,
                                    _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "moga_group_attn_bwd_joint": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32,
+                                   _f32, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_group_attn_bwd_tokens": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32, _f32, _vp, _vp,
+                                          _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
+    "moga_group_attn_bwd_tokens_joint": (_i32, [_vp, _vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _i32, _vp, _i32, _f32, _vp, _vp,
                                           _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]),
     "moga_attn_bwd_status_offset": (_sz, [_i64, _i32]),
     "moga_debug_set_spin_limit": (None, [_i32]),

@@ -10,7 +10,8 @@
 //   attn_bwd_dkdv_ab : a pair of waves owns 48 (or 32) key rows and sweeps the query tiles of its group, one wave with
 //                      the K fragments and the dV^T accumulators, the other with the V fragments and dK^T;
 //   attn_bwd_dq_pipe : a wave owns 48 (or 32) query rows and sweeps the key tiles (mirror of forward);
-//   attn_bwd_small   : both with smaller tiles in one launch, for small groups.
+//   attn_bwd_small   : both with smaller tiles in one launch, for small groups;
+//   attn_bwd_calls   : dq_pipe's and dkdv_ab's blocks in one launch, of one call or of several (attn_bwd_small_calls: of small groups).
 // The bf16 MFMA kernels are in attn_bwd_pipe.h: they keep the contraction index of the second
 // product in the accumulator registers of the first (row permutation of the LDS operand), and
 // read the transposed operands (dO^T, Q^T, K^T) from row-major LDS tiles with the transposing
@@ -18,6 +19,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <map>
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
@@ -181,6 +183,84 @@ AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
   return {false, query_blocks(Nq, Nk, H, M, room), key_blocks(Nq, Nk, H, M, room)};
 }
 
+// dQ and dK/dV of one call in one launch: mean rows per group below which the small-group kernels run.  Time of the large kernels against
+// the small ones', both in one launch, groups of iid / Zipf(1.1) tokens, in %:
+//   rounds 0.5   400 rows -2 / -7, 500 +6 / -4, 650 -10 / -15;    1.0   400 +5 / -10, 500 +8 / -14, 650 -2 / -8
+//          1.4   400 +11 / -11, 500 +3 / -11, 650 +2 / -9;        1.9   400 +9 / -4, 500 +1 / -9, 650 -3 / -9
+//          3.5   300 +10 / -8, 400 +9 / -7, 500 +1 / -10, 650 -5 / -14;   8   400 +7 / -8, 500 -1 / -9, 650 -7 / -14
+// Below a fifth of a round most CUs have no large block: 0.14 rounds, 650 rows +27 / +27, 1,700 +23 / +24, 3,200 +8 / +8; 0.2 rounds 650 -5 /
+// -10, 1,700 -12 / -12, 3,200 -12 / -12.  About one round the blocks of 500 equal groups often just miss the first round (+6), those of 650 less so.
+static int64_t joint_small_rows(int64_t N, int H) {
+  const int64_t rounds = 100 * N * H / (256 * kCus);   // in hundredths
+  return rounds < 18 ? 8192 : rounds < 50 ? 500 : rounds < 130 ? 650 : rounds < 300 ? 600 : 500;
+}
+
+// Blocks of dQ and of dK/dV of up to kMaxCalls calls as one list, longest first, on kCus CUs.
+struct BwdSegment {
+  int what;          // 2 * call, + 1 for dK/dV
+  int64_t blocks;
+  double length;     // of a block: products times rows swept
+};
+struct BwdBlocks {
+  int bm, bk;        // query rows of a block, keys
+  double price;      // in the units of large_blocks: three products a pair of rows in dQ, four in dK/dV (whose blocks have half the rows)
+};
+static double list_end(const BwdSegment* seg, int n) {
+  std::map<double, int64_t> free = {{0., kCus}};   // time -> CUs that are free from then on
+  double end = 0;
+  for (int i = 0; i < n; ++i)
+    for (int64_t left = seg[i].blocks; left > 0;) {
+      const auto f = free.begin();
+      const double t = f->first + seg[i].length;
+      const int64_t k = std::min(left, f->second);
+      left -= k;
+      if (k == f->second) free.erase(f);
+      else f->second -= k;
+      free[t] += k;
+      end = std::max(end, t);
+    }
+  return end;
+}
+// With equal groups; a block sweeps kStartRows more rows than there are.  Up to 1.2 rounds (of 256 blocks of 256 rows) the price is the end of
+// the list, and the long blocks, of which one may be the whole call's time, have to be a fifth cheaper: 0.33 rounds, groups of 800 iid / Zipf(1.1)
+// rows 51 / 87 us with the short ones and 49 / 118 with the long ones.  Beyond, work per CU and half of a last block, since the blocks get out of
+// step: over 72 calls of 1.2 to 20 rounds 1 % faster than by the list with iid groups, 2.5 % with Zipf's.
+static BwdBlocks bwd_blocks(const SideShape* q, int n, int H) {
+  int64_t rows = 0;
+  for (int i = 0; i < n; ++i) rows += q[i].N;
+  const bool listed = 10 * rows * H < 12 * 256 * kCus;
+  auto cost = [&](int bm, int bk, double weight) {
+    BwdSegment seg[2 * kMaxCalls];
+    double work = 0;
+    for (int i = 0; i < n; ++i) {
+      const SideShape& c = q[i];
+      const int64_t nk = (c.other + c.M - 1) / c.M, nq = (c.N + c.M - 1) / c.M, tq = (nq + bm - 1) / bm, tk = (nk + bk - 1) / bk;
+      seg[2 * i] = {2 * i, tq * c.M * H, 3 * weight * (nk + kStartRows)};
+      seg[2 * i + 1] = {2 * i + 1, tk * c.M * H, 2 * weight * (nq + kStartRows)};
+      // a group's last block, of two columns a wave
+      work += (tq - (nq - (tq - 1) * bm <= 256 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i].length;
+      work += (tk - (nk - (tk - 1) * bk <= 128 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i + 1].length;
+    }
+    std::stable_sort(seg, seg + 2 * n, [](const BwdSegment& x, const BwdSegment& y) { return x.length > y.length; });
+    return listed ? list_end(seg, 2 * n) : work / kCus + seg[2 * n - 1].length / 2;
+  };
+  const double few = cost(256, 128, 10), many = cost(384, 192, 13);
+  return few < (listed ? 1.2 : 1.) * many ? BwdBlocks{256, 128, few} : BwdBlocks{384, 192, many};
+}
+// One call whose dQ and dK/dV are better launched apart: few long blocks, which leave CUs idle together and do not with their last rounds split (8,000
+// rows x 3 heads, 1 group 0.357 and 0.283 ms); and where many rounds make a last one little, and one launch takes 0 to 2 % longer (60,000 x 16 in
+// equal groups of 8,000 9.37 and 9.56 ms; 580,320 x 40, 32 groups, step 698 and 705 ms).
+static bool many_rounds(int64_t N, int H, int M) { return N * H >= 16 * 256 * kCus || (N * H >= 7 * 256 * kCus && N >= 8000 * (int64_t)M); }
+static bool bwd_apart(int64_t N, int H, int M, int room) {
+  if (many_rounds(N, H, M)) return true;
+  if (room == 0 || N * H > 4 * 256 * kCus) return false;   // from four rounds on at most 2 %
+  if (use_small_group_kernels(N, M, joint_small_rows(N, H)) || bwd_plan(N, N, H, M, room).small) return false;
+  double pq, pk;
+  const Blocks q = large_blocks(N, N, H, M, 256, 1, room, &pq), k = large_blocks(N, N, H, M, 128, 2, room, &pk);
+  const SideShape side = {N, N, M};
+  return (q.split || k.split) && 3 * pq + 2 * pk < 0.95 * bwd_blocks(&side, 1, H).price;
+}
+
 }  // namespace moga
 
 using namespace moga;
@@ -217,22 +297,86 @@ struct TokenGrads {
   bool row_constants;   // already in the workspace
 };
 
+// dQ and dK/dV of n bf16 calls in one launch: the blocks of one fill the last round of the other.  Against two launches with their last rounds
+// split (32 MB of pieces, and a launch to add them up, each), groups of iid / Zipf(1.1) rows, backward of the attention in us: 9,000 x 12, 5 groups
+// 317 -> 287 / 497 -> 432; 20,000 x 12, 10 groups 717 -> 679 / 1,437 -> 1,332; 15,000 x 40, 16 groups 974 -> 931; gather-fused step, whose launches
+// cannot split, 700 x 12 71 -> 48, 1,253 x 40 159 -> 137, 5,225 x 40 720 -> 660.  Of the kernels for small groups or of the large ones (with their rows read through perm: GATHER).
+// c: everything but ts_q and ts_k, for which ts[i] has room if call i has more than MOGA_MAX_GROUPS groups.
+enum class BwdKernels { kSmall, kLarge, kGather };
+static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, BwdKernels kernels, int H, float softmax_scale, hipStream_t st) {
+  int bm = 128, bk = 64;
+  const int threads = kernels == BwdKernels::kSmall ? 256 : 512;
+  if (kernels != BwdKernels::kSmall) {
+    SideShape q[kMaxCalls];
+    for (int i = 0; i < n; ++i) q[i] = {c[i].Nq, c[i].Nk, c[i].M};
+    const BwdBlocks rows = bwd_blocks(q, n, H);
+    bm = rows.bm, bk = rows.bk;
+  }
+  BwdSegment seg[2 * kMaxCalls];
+  int segments = 0;
+  for (int i = 0; i < n; ++i) {   // three products of bm rows a key, four of bk keys a query
+    seg[segments++] = {2 * i, (max_tiles(c[i].Nq, c[i].M, bm) * H + 7) / 8 * 8, 3. * bm * (double)c[i].Nk / c[i].M};
+    if (c[i].Nk > 0) seg[segments++] = {2 * i + 1, (max_tiles(c[i].Nk, c[i].M, bk) * H + 7) / 8 * 8, 4. * bk * (double)c[i].Nq / c[i].M};
+  }
+  std::stable_sort(seg, seg + segments, [](const BwdSegment& x, const BwdSegment& y) { return x.length > y.length; });
+  AttnBwdCalls a = {};
+  std::copy(c, c + n, a.c);
+  std::fill(a.first, a.first + 2 * kMaxCalls, INT_MAX);
+  int64_t blocks = 0;
+  for (int s = 0; s < segments; ++s) {
+    a.first[s] = (int)blocks;
+    a.what[s] = seg[s].what;
+    blocks += seg[s].blocks;
+    if (!grid_fits(blocks, threads)) return MOGA_ERR_UNSUPPORTED;
+  }
+  for (int i = 0; i < n; ++i)
+    if (c[i].M > MOGA_MAX_GROUPS) {
+      int32_t *ts_q = ts[i], *ts_k = ts_q + (c[i].M + 1);
+      if (c[i].Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(c[i].cu_k, c[i].M, bk, ts_k);
+      tile_start_kernel<<<1, 1024, 0, st>>>(c[i].cu_q, c[i].M, bm, ts_q);
+      a.c[i].ts_q = ts_q, a.c[i].ts_k = ts_k;
+    }
+  const int spin = g_spin_limit.load();
+#define MOGA_BWD_CALLS(KK, RR)                                                                                                            \
+  if (kernels == BwdKernels::kGather) attn_bwd_calls_kernel<KK, RR, true><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin); \
+  else attn_bwd_calls_kernel<KK, RR, false><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin)
+  if (kernels == BwdKernels::kSmall) {
+    attn_bwd_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale, spin);
+  } else if (bm == 384) {
+    MOGA_BWD_CALLS(192, 384);
+  } else {
+    MOGA_BWD_CALLS(128, 256);
+  }
+#undef MOGA_BWD_CALLS
+  return launch_status();
+}
+
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
 // space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: room for
-// the pieces of a last round, if any (dK/dV and dQ use it one after the other; only without ts_q / ts_k).
+// the pieces of a last round, if any (dK/dV and dQ use it one after the other; only without ts_q / ts_k).  joint: bf16, dQ and dK/dV in one
+// launch, which needs neither lists nor room (M <= MOGA_MAX_GROUPS).
 static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
                            const void* oh, const float* lse, int dtype, int64_t Nq, int64_t Nk, int H, int D,
                            const int32_t* cu_q, const int32_t* cu_k, int32_t* ts_q, int32_t* ts_k,
                            int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
-                           float* delta, const TokenGrads& tok, const SplitRoom& split, hipStream_t st) {
+                           float* delta, const TokenGrads& tok, const SplitRoom& split, bool joint, hipStream_t st) {
   unsigned short *d_q_tok = (unsigned short*)tok.d_q, *d_k_tok = (unsigned short*)tok.d_k, *d_v_tok = (unsigned short*)tok.d_v;
   const int64_t rows = Nq * (int64_t)H;
   int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
   if (dtype == MOGA_BF16) {
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
+    const bool joint_small = joint && use_small_group_kernels(Nq, M, joint_small_rows(Nq, H));
+    if (joint && !joint_small) {
+      if (!grid_fits(((max_tiles(Nk, M, 128) + max_tiles(Nq, M, 256)) * H + 14), 512)) return MOGA_ERR_UNSUPPORTED;
+      if (!tok.row_constants) launch_delta<16, true>(d_oh, oh, lse, rows, 1.f / softmax_scale, delta, delta + rows, status, st);
+      const AttnBwdCall c = {(const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh,
+                             delta + rows, delta, cu_q, cu_k, nullptr, nullptr, Nq, Nk, (unsigned short*)d_qh, (unsigned short*)d_kh,
+                             (unsigned short*)d_vh, d_q_tok, d_k_tok, d_v_tok, tok.perm, status, M};
+      return launch_bwd_calls(&c, nullptr, 1, BwdKernels::kLarge, H, softmax_scale, st);
+    }
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and smaller tiles; the host only knows the mean group size
-    const AttnPlan plan = bwd_plan(Nq, Nk, H, M, split.rows);
+    const AttnPlan plan = joint ? AttnPlan{true, {128, false}, {64, false}} : bwd_plan(Nq, Nk, H, M, split.rows);
     const bool small = plan.small;
     const int bk = plan.k.rows, bm = plan.q.rows;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
@@ -324,7 +468,7 @@ static int check_attn_bwd_args(int64_t Nq, int64_t Nk, int H, int D, int M, floa
   return MOGA_OK;
 }
 
-extern "C" int moga_group_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
+static int group_attn_bwd(bool joint, const void* d_oh, const void* qh, const void* kh, const void* vh,
                                    const void* oh, const float* lse, int dtype, int64_t N, int H,
                                    int D, const int32_t* cu_seqlens, int M, float softmax_scale,
                                    void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes,
@@ -340,12 +484,14 @@ extern "C" int moga_group_attn_bwd(const void* d_oh, const void* qh, const void*
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
+  const SplitRoom room = split_room(ws, need, ws_bytes);
+  const bool together = joint && !(dtype == MOGA_BF16 && bwd_apart(N, H, M, room.rows));
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr,
-                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{}, split_room(ws, need, ws_bytes),
-                         (hipStream_t)stream);
+                         nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{},
+                         together ? SplitRoom{} : room, together, (hipStream_t)stream);
 }
 
-extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh,
+static int group_attn_bwd_tokens(bool joint, const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh,
                                           const float* lse, int dtype, int64_t N, int H, int D, const int32_t* cu_seqlens, int M,
                                           float softmax_scale, const int32_t* perm, const float* gate, void* d_oh, float* d_gate,
                                           void* d_qh, void* d_kh, void* d_vh, void* d_q, void* d_k, void* d_v, void* ws,
@@ -363,13 +509,40 @@ extern "C" int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
+  const SplitRoom room = split_room(ws, need, ws_bytes);
+  const bool together = joint && !(dtype == MOGA_BF16 && bwd_apart(N, H, M, room.rows));
   float* delta = (float*)ws;
   const RowConstants rc = {lse, 1.f / softmax_scale, delta, delta + N * (int64_t)H, (int*)((char*)ws + bwd_rows_bytes(N, H))};
   const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, &rc, (hipStream_t)stream);
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
                          softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm, true},
-                         split_room(ws, need, ws_bytes), (hipStream_t)stream);
+                         together ? SplitRoom{} : room, together, (hipStream_t)stream);
+}
+
+extern "C" int moga_group_attn_bwd(
+    const void* d_oh, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse, int dtype, int64_t N, int H, int D,
+    const int32_t* cu_seqlens, int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes, void* stream) {
+  return group_attn_bwd(false, d_oh, qh, kh, vh, oh, lse, dtype, N, H, D, cu_seqlens, M, softmax_scale, d_qh, d_kh, d_vh, ws, ws_bytes, stream);
+}
+extern "C" int moga_group_attn_bwd_joint(
+    const void* d_oh, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse, int dtype, int64_t N, int H, int D,
+    const int32_t* cu_seqlens, int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh, void* ws, size_t ws_bytes, void* stream) {
+  return group_attn_bwd(true, d_oh, qh, kh, vh, oh, lse, dtype, N, H, D, cu_seqlens, M, softmax_scale, d_qh, d_kh, d_vh, ws, ws_bytes, stream);
+}
+extern "C" int moga_group_attn_bwd_tokens(
+    const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse, int dtype, int64_t N, int H, int D,
+    const int32_t* cu_seqlens, int M, float softmax_scale, const int32_t* perm, const float* gate, void* d_oh, float* d_gate, void* d_qh,
+    void* d_kh, void* d_vh, void* d_q, void* d_k, void* d_v, void* ws, size_t ws_bytes, void* stream) {
+  return group_attn_bwd_tokens(false, d_o, qh, kh, vh, oh, lse, dtype, N, H, D, cu_seqlens, M, softmax_scale, perm, gate, d_oh, d_gate, d_qh,
+                               d_kh, d_vh, d_q, d_k, d_v, ws, ws_bytes, stream);
+}
+extern "C" int moga_group_attn_bwd_tokens_joint(
+    const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh, const float* lse, int dtype, int64_t N, int H, int D,
+    const int32_t* cu_seqlens, int M, float softmax_scale, const int32_t* perm, const float* gate, void* d_oh, float* d_gate, void* d_qh,
+    void* d_kh, void* d_vh, void* d_q, void* d_k, void* d_v, void* ws, size_t ws_bytes, void* stream) {
+  return group_attn_bwd_tokens(true, d_o, qh, kh, vh, oh, lse, dtype, N, H, D, cu_seqlens, M, softmax_scale, perm, gate, d_oh, d_gate, d_qh,
+                               d_kh, d_vh, d_q, d_k, d_v, ws, ws_bytes, stream);
 }
 
 extern "C" size_t moga_varlen_attn_bwd_ws_bytes(int64_t Nq, int H, int G) {
@@ -408,7 +581,7 @@ static int varlen_attn_bwd(const moga_attn_bwd_call& c, int dtype, int H, int D,
   int32_t* ts_k = presum ? ts_q + (c.G + 1) : nullptr;
   return launch_attn_bwd(c.d_oh, c.qh, c.kh, c.vh, c.oh, c.lse, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, ts_q, ts_k, c.G,
                          softmax_scale, c.d_qh, c.d_kh, c.d_vh, (float*)c.ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
-                         presum ? SplitRoom{} : split_room(c.ws, need, c.ws_bytes), st);
+                         presum ? SplitRoom{} : split_room(c.ws, need, c.ws_bytes), false, st);
 }
 
 extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
@@ -429,49 +602,6 @@ extern "C" int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const
                                          void* stream) {
   return varlen_attn_bwd({d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, Nq, Nk, G, d_qh, d_kh, d_vh, ws, ws_bytes}, dtype, H, D,
                          softmax_scale, true, stream);
-}
-
-// The bf16 calls `which` in one launch of the kernels for small groups, or of the large ones with `bm` query rows and `bk` keys per block.
-static int launch_bwd_calls(const moga_attn_bwd_call* calls, const int* which, int n, bool small, int bm, int bk, int H, float softmax_scale,
-                            hipStream_t st) {
-  AttnBwdCalls a = {};
-  struct Segment {
-    int what;
-    int64_t blocks;
-    double length;   // of a block
-  } seg[2 * kMaxCalls];
-  std::fill(a.first, a.first + 2 * kMaxCalls, INT_MAX);
-  int32_t* ts[kMaxCalls];
-  int segments = 0;
-  for (int i = 0; i < n; ++i) {
-    const moga_attn_bwd_call& c = calls[which[i]];
-    char* ws = (char*)c.ws;
-    ts[i] = c.G > MOGA_MAX_GROUPS ? (int32_t*)(ws + bwd_rows_bytes(c.Nq, H) + 16) : nullptr;
-    a.c[i] = {(const unsigned short*)c.d_oh, (const unsigned short*)c.qh, (const unsigned short*)c.kh, (const unsigned short*)c.vh,
-              (float*)ws + c.Nq * (int64_t)H, (float*)ws, c.cu_seqlens_q, c.cu_seqlens_k, ts[i], ts[i] ? ts[i] + (c.G + 1) : nullptr, c.Nq,
-              c.Nk, (unsigned short*)c.d_qh, (unsigned short*)c.d_kh, (unsigned short*)c.d_vh, (int*)(ws + bwd_rows_bytes(c.Nq, H)), c.G};
-    // products: three of bm rows a key, four of bk keys a query
-    seg[segments++] = {2 * i, (max_tiles(c.Nq, c.G, bm) * H + 7) / 8 * 8, 3. * bm * (double)c.Nk / c.G};
-    if (c.Nk > 0) seg[segments++] = {2 * i + 1, (max_tiles(c.Nk, c.G, bk) * H + 7) / 8 * 8, 4. * bk * (double)c.Nq / c.G};
-  }
-  std::stable_sort(seg, seg + segments, [](const Segment& x, const Segment& y) { return x.length > y.length; });
-  int64_t blocks = 0;
-  for (int s = 0; s < segments; ++s) {
-    a.first[s] = (int)blocks;
-    a.what[s] = seg[s].what;
-    blocks += seg[s].blocks;
-    if (!grid_fits(blocks, small ? 256 : 512)) return MOGA_ERR_UNSUPPORTED;
-  }
-  for (int i = 0; i < n; ++i)
-    if (ts[i]) {
-      if (a.c[i].Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(a.c[i].cu_k, a.c[i].M, bk, ts[i] + (a.c[i].M + 1));
-      tile_start_kernel<<<1, 1024, 0, st>>>(a.c[i].cu_q, a.c[i].M, bm, ts[i]);
-    }
-  const int spin = g_spin_limit.load();
-  if (small) attn_bwd_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale, spin);
-  else if (bm == 384) attn_bwd_calls_kernel<192, 384><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin);
-  else attn_bwd_calls_kernel<128, 256><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin);
-  return launch_status();
 }
 
 extern "C" int moga_varlen_attn_bwd_rows_calls(const moga_attn_bwd_call* calls, int n, int dtype, int H, int D, float softmax_scale,
@@ -498,23 +628,29 @@ extern "C" int moga_varlen_attn_bwd_rows_calls(const moga_attn_bwd_call* calls, 
   }
   auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H)); };
   int* const mid = std::stable_partition(order, order + count, [&](int i) { return !small(i); });
-  const int large = (int)(mid - order);
-  if (large > 0) {
-    SideShape q[kMaxCalls], k[kMaxCalls];
-    for (int i = 0; i < large; ++i) {
-      const moga_attn_bwd_call& c = calls[order[i]];
-      q[i] = {c.Nq, c.Nk, c.G};
-      k[i] = {c.Nk, c.Nq, c.G};
+  auto launch = [&](const int* first, const int* last, BwdKernels kernels) -> int {
+    if (first == last) return MOGA_OK;
+    AttnBwdCall a[kMaxCalls];
+    int32_t* ts[kMaxCalls];
+    const int m = (int)(last - first);
+    for (int i = 0; i < m; ++i) {
+      const moga_attn_bwd_call& c = calls[first[i]];
+      char* ws = (char*)c.ws;
+      ts[i] = (int32_t*)(ws + bwd_rows_bytes(c.Nq, H) + 16);
+      a[i] = {(const unsigned short*)c.d_oh, (const unsigned short*)c.qh, (const unsigned short*)c.kh, (const unsigned short*)c.vh,
+              (float*)ws + c.Nq * (int64_t)H, (float*)ws, c.cu_seqlens_q, c.cu_seqlens_k, nullptr, nullptr, c.Nq, c.Nk,
+              (unsigned short*)c.d_qh, (unsigned short*)c.d_kh, (unsigned short*)c.d_vh, nullptr, nullptr, nullptr, nullptr,
+              (int*)(ws + bwd_rows_bytes(c.Nq, H)), c.G};
     }
-    auto cost = [&](int bm, int bk, double weight) {   // three products a pair of rows in dQ, four in dK/dV; a block of keys is half as long
-      return 3 * calls_cost(q, large, H, bm, 256, weight) + 2 * calls_cost(k, large, H, bk, 128, weight);
-    };
-    const bool few = cost(256, 128, 10) < cost(384, 192, 13);
-    const int rc = launch_bwd_calls(calls, order, large, false, few ? 256 : 384, few ? 128 : 192, H, softmax_scale, (hipStream_t)stream);
-    if (rc != MOGA_OK) return rc;
-  }
-  if (count > large) return launch_bwd_calls(calls, mid, count - large, true, 128, 64, H, softmax_scale, (hipStream_t)stream);
-  return MOGA_OK;
+    int rc = launch_bwd_calls(a, ts, m, kernels, H, softmax_scale, (hipStream_t)stream);
+    if (rc == MOGA_ERR_UNSUPPORTED) {   // millions of groups: together too many threads for a grid
+      rc = MOGA_OK;
+      for (int i = 0; i < m && rc == MOGA_OK; ++i) rc = varlen_attn_bwd(calls[first[i]], dtype, H, D, softmax_scale, true, stream);
+    }
+    return rc;
+  };
+  const int rc = launch(order, mid, BwdKernels::kLarge);
+  return rc != MOGA_OK ? rc : launch(mid, order + count, BwdKernels::kSmall);
 }
 
 extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k, const void* v,
@@ -535,39 +671,47 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     return MOGA_ERR_INVALID_ARG;
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
-  const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;
   hipStream_t st = (hipStream_t)stream;
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
-  const int64_t k_blocks = (max_tiles(N, M, keys) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, rows_q) * H + 7) / 8 * 8;
-  if (!grid_fits(k_blocks, 512)) return MOGA_ERR_UNSUPPORTED;
+  if (!grid_fits((max_tiles(N, M, 128) + max_tiles(N, M, 256)) * H + 14, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + kPrepassTokens - 1) / kPrepassTokens), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate, status);
+  if (many_rounds(N, H, M)) {
+    const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;
+    const unsigned k_blocks = (unsigned)((max_tiles(N, M, keys) * H + 7) / 8 * 8), q_blocks = (unsigned)((max_tiles(N, M, rows_q) * H + 7) / 8 * 8);
 #define MOGA_BWD_DKDV(KK)                                                                                                   \
-  attn_bwd_dkdv_ab_kernel<KK, true><<<(unsigned)k_blocks, 512, 0, st>>>(                                                    \
+  attn_bwd_dkdv_ab_kernel<KK, true><<<k_blocks, 512, 0, st>>>(                                                              \
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
       cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k, (unsigned short*)d_v,               \
       g_spin_limit.load(), status, perm)
-  if (keys == 192) MOGA_BWD_DKDV(192);
-  else MOGA_BWD_DKDV(128);
+    if (keys == 192) MOGA_BWD_DKDV(192);
+    else MOGA_BWD_DKDV(128);
 #undef MOGA_BWD_DKDV
 #define MOGA_BWD_DQ(RR)                                                                                                     \
-  attn_bwd_dq_pipe_kernel<RR, true><<<(unsigned)q_blocks, 512, 0, st>>>(                                                    \
+  attn_bwd_dq_pipe_kernel<RR, true><<<q_blocks, 512, 0, st>>>(                                                              \
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
       cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q, perm)
-  if (rows_q == 384) MOGA_BWD_DQ(384);
-  else MOGA_BWD_DQ(256);
+    if (rows_q == 384) MOGA_BWD_DQ(384);
+    else MOGA_BWD_DQ(256);
 #undef MOGA_BWD_DQ
-  return launch_status();
+    return launch_status();
+  }
+  const AttnBwdCall c = {(const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta,
+                         cu_seqlens, cu_seqlens, nullptr, nullptr, N, N, (unsigned short*)d_q, (unsigned short*)d_k, (unsigned short*)d_v,
+                         nullptr, nullptr, nullptr, perm, status, M};
+  return launch_bwd_calls(&c, nullptr, 1, BwdKernels::kGather, H, softmax_scale, st);
 }
 
 extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, int H, int D, int M, int d_model, int dtype) {
   const size_t need = moga_workspace_bytes(op, N, H, D, M, d_model, dtype);
   if (dtype != MOGA_BF16 || D != 128 || N <= 0 || Nk <= 0 || H < 1 || M < 1) return need;
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
-  const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD;
-  if (M > MOGA_MAX_GROUPS || !(fwd || bwd)) return need;
+  const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD || op == MOGA_OP_ATTN_BWD_JOINT;
+  if (M > MOGA_MAX_GROUPS) return need;
+  if (op == MOGA_OP_ATTN_BWD_JOINT && (N != Nk || !bwd_apart(N, H, M, 384))) return need;
+  if (!fwd && !bwd) return need;
   auto plan = [&](int room) { return fwd ? fwd_plan(N, Nk, H, M, room) : bwd_plan(N, Nk, H, M, room); };
   const AttnPlan p = plan(384), q = plan(256);
   if (!p.q.split && !p.k.split) return need;

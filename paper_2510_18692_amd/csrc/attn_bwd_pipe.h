@@ -907,7 +907,9 @@ struct AttnBwdCall {
   const float *neg_lse_over_scale, *neg_delta;
   const int32_t *cu_q, *cu_k, *ts_q, *ts_k;
   int64_t Nq, Nk;
-  unsigned short *d_qh, *d_kh, *d_vh;
+  unsigned short *d_qh, *d_kh, *d_vh;      // NULL where only the token-order rows are wanted
+  unsigned short *d_q_tok, *d_k_tok, *d_v_tok;   // NULL, or the rows in token order as well
+  const int32_t* perm;
   int* status;
   int M;
 };
@@ -922,21 +924,21 @@ __device__ __forceinline__ int segment_of_block(const AttnBwdCalls& calls, int b
   for (int k = 1; k < 2 * kMaxCalls; ++k) s += block >= calls.first[k];
   return s;
 }
-template <int KEYS, int ROWS>
+template <int KEYS, int ROWS, bool GATHER>
 __global__ __launch_bounds__(512, 1) void attn_bwd_calls_kernel(AttnBwdCalls calls, int H, float scale, int spin_limit) {
   __shared__ union {
-    DqLds<4, false> dq;
-    DkdvLds<4, 4, KEYS / 64, false> dkdv;
+    DqLds<4, GATHER> dq;
+    DkdvLds<4, 4, KEYS / 64, GATHER> dkdv;
   } lds;
   const int s = segment_of_block(calls, blockIdx.x), what = calls.what[s], block = blockIdx.x - calls.first[s];
   const AttnBwdCall& c = calls.c[what >> 1];
   if (what & 1)
-    attn_bwd_dkdv_block<false, 4, 4, KEYS / 64, false>(lds.dkdv, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q,
-                                                       c.cu_k, c.ts_k, c.M, c.Nq, c.Nk, H, scale, c.d_kh, c.d_vh, spin_limit, c.status,
-                                                       nullptr, nullptr, nullptr, nullptr);
+    attn_bwd_dkdv_block<GATHER, 4, 4, KEYS / 64, false>(lds.dkdv, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q,
+                                                        c.cu_k, c.ts_k, c.M, c.Nq, c.Nk, H, scale, c.d_kh, c.d_vh, spin_limit, c.status,
+                                                        c.perm, nullptr, c.d_k_tok, c.d_v_tok);
   else
-    attn_bwd_dq_block<8, false, 4, ROWS, false>(lds.dq, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q, c.cu_k,
-                                                c.ts_q, c.M, c.Nq, c.Nk, H, scale, c.d_qh, nullptr, nullptr, nullptr);
+    attn_bwd_dq_block<8, GATHER, 4, ROWS, false>(lds.dq, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q, c.cu_k,
+                                                 c.ts_q, c.M, c.Nq, c.Nk, H, scale, c.d_qh, c.perm, nullptr, c.d_q_tok);
 }
 __global__ __launch_bounds__(256, 2) void attn_bwd_small_calls_kernel(AttnBwdCalls calls, int H, float scale, int spin_limit) {
   __shared__ union {
@@ -947,11 +949,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_calls_kernel(AttnBwdCal
   const AttnBwdCall& c = calls.c[what >> 1];
   if (what & 1)
     attn_bwd_dkdv_block<false, 2, 2, 2, false>(lds.dkdv, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q, c.cu_k,
-                                               c.ts_k, c.M, c.Nq, c.Nk, H, scale, c.d_kh, c.d_vh, spin_limit, c.status, nullptr, nullptr,
-                                               nullptr, nullptr);
+                                               c.ts_k, c.M, c.Nq, c.Nk, H, scale, c.d_kh, c.d_vh, spin_limit, c.status, c.perm, nullptr,
+                                               c.d_k_tok, c.d_v_tok);
   else
     attn_bwd_dq_block<4, false, 2, 128, false>(lds.dq, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q, c.cu_k,
-                                               c.ts_q, c.M, c.Nq, c.Nk, H, scale, c.d_qh, nullptr, nullptr, nullptr);
+                                               c.ts_q, c.M, c.Nq, c.Nk, H, scale, c.d_qh, c.perm, nullptr, c.d_q_tok);
 }
 
 }  // namespace moga

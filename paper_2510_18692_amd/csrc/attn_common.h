@@ -285,8 +285,8 @@ struct Blocks {
 };
 // N: rows of this side, in blocks of `few` or 3/2 of that; other: rows of the side that they sweep; arrays: results per row; room: result
 // rows of the longest piece there is room for.
-inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int arrays, int room) {
-  constexpr double kStartRows = 640, kMergeRows = 1000;
+constexpr double kStartRows = 640, kMergeRows = 1000;
+inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int arrays, int room, double* price = nullptr) {
   const int64_t mean = (N + M - 1) / M, swept = (other + M - 1) / M;
   auto splits = [&](int rows) { return room >= arrays * rows && split_pays(max_tiles(N, M, rows) * H); };
   auto cost = [&](int rows, double weight) {
@@ -299,7 +299,9 @@ inline Blocks large_blocks(int64_t N, int64_t other, int H, int M, int few, int 
            (pieces > 1 ? 10 * kMergeRows : 0);
   };
   const bool by_far = arrays == 1 && N * H >= 2 * 256 * kCus && N * H < 4 * 256 * kCus;
-  const int rows = cost(few, 10) < (by_far ? 1.2 : 1.) * cost(few / 2 * 3, 13) ? few : few / 2 * 3;
+  const double short_cost = cost(few, 10), long_cost = cost(few / 2 * 3, 13);
+  const int rows = short_cost < (by_far ? 1.2 : 1.) * long_cost ? few : few / 2 * 3;
+  if (price) *price = rows == few ? short_cost : long_cost;
   return {rows, splits(rows)};
 }
 inline Blocks query_blocks(int64_t Nq, int64_t Nk, int H, int M, int room) { return large_blocks(Nq, Nk, H, M, 256, 1, room); }
@@ -311,7 +313,6 @@ struct SideShape {
   int M;
 };
 inline double calls_cost(const SideShape* c, int n, int H, int rows, int few, double weight) {
-  constexpr double kStartRows = 640;
   double work = 0, last = 0;
   for (int i = 0; i < n; ++i) {
     const int64_t mean = (c[i].N + c[i].M - 1) / c[i].M, of_group = (mean + rows - 1) / rows;

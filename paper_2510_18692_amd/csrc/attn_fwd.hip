@@ -249,27 +249,29 @@ extern "C" int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n
     rows += calls[i].Nq;
     if (calls[i].Nq > 0) order[count++] = i;
   }
-  if (dtype != MOGA_BF16 || count < 2) {
-    for (int i = 0; i < count; ++i) {
-      const moga_attn_fwd_call& c = calls[order[i]];
-      const int rc = moga_varlen_attn_fwd(c.qh, c.kh, c.vh, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, c.G, softmax_scale,
-                                          c.oh, c.lse, c.ws, c.ws_bytes, stream);
-      if (rc != MOGA_OK) return rc;
+  auto one_by_one = [&](const int* first, const int* last) {
+    int rc = MOGA_OK;
+    for (; first != last && rc == MOGA_OK; ++first) {
+      const moga_attn_fwd_call& c = calls[*first];
+      rc = moga_varlen_attn_fwd(c.qh, c.kh, c.vh, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, c.G, softmax_scale, c.oh, c.lse,
+                                c.ws, c.ws_bytes, stream);
     }
-    return MOGA_OK;
-  }
+    return rc;
+  };
+  if (dtype != MOGA_BF16 || count < 2) return one_by_one(order, order + count);
   // longest blocks first, the calls of the large kernels before those of the small ones
   std::stable_sort(order, order + count, [&](int a, int b) { return calls[a].Nk * calls[b].G > calls[b].Nk * calls[a].G; });
   auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H)); };
   int* const mid = std::stable_partition(order, order + count, [&](int i) { return !small(i); });
   const int large = (int)(mid - order);
-  if (large > 0) {
-    SideShape q[kMaxCalls];
-    for (int i = 0; i < large; ++i) q[i] = {calls[order[i]].Nq, calls[order[i]].Nk, calls[order[i]].G};
-    const int bm = calls_cost(q, large, H, 256, 256, 10) < calls_cost(q, large, H, 384, 256, 13) ? 256 : 384;
-    const int rc = launch_fwd_calls(calls, order, large, false, bm, H, softmax_scale, (hipStream_t)stream);
-    if (rc != MOGA_OK) return rc;
-  }
-  if (count > large) return launch_fwd_calls(calls, mid, count - large, true, 128, H, softmax_scale, (hipStream_t)stream);
-  return MOGA_OK;
+  auto launch = [&](const int* first, const int* last, bool few, int rows) {
+    if (first == last) return (int)MOGA_OK;
+    const int rc = launch_fwd_calls(calls, first, (int)(last - first), few, rows, H, softmax_scale, (hipStream_t)stream);
+    return rc == MOGA_ERR_UNSUPPORTED ? one_by_one(first, last) : rc;   // millions of groups: together too many threads for a grid
+  };
+  SideShape q[kMaxCalls];
+  for (int i = 0; i < large; ++i) q[i] = {calls[order[i]].Nq, calls[order[i]].Nk, calls[order[i]].G};
+  const int bm = calls_cost(q, large, H, 256, 256, 10) < calls_cost(q, large, H, 384, 256, 13) ? 256 : 384;
+  const int rc = launch(order, mid, false, bm);
+  return rc != MOGA_OK ? rc : launch(mid, order + count, true, 128);
 }

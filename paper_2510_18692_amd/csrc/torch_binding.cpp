@@ -218,10 +218,12 @@ std::tuple<Tensor, Tensor, Tensor> group_attn_bwd(const Tensor& d_oh, const Tens
   need_dims(qh, 3);
   const int64_t H = qh.size(0), N = qh.size(1), D = qh.size(2), M = cu.size(0) - 1;
   Tensor d_qh = call.make({H, N, D}, qh), d_kh = call.make(kh.sizes(), kh), d_vh = call.make(vh.sizes(), vh);
-  OptTensor ws = ws_in ? ws_in : call.attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
-  check("moga_group_attn_bwd", moga_group_attn_bwd(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H,
-                                                   (int)D, as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh),
-                                                   ptr(ws), bytes_of(ws), call.stream()));
+  // dQ and dK/dV in one launch where that is the better form, unless the caller brings a workspace of its own
+  OptTensor ws = ws_in ? ws_in : call.attn_workspace(MOGA_OP_ATTN_BWD_JOINT, N, N, H, D, M, qh);
+  const auto fn = ws_in ? moga_group_attn_bwd : moga_group_attn_bwd_joint;
+  check("moga_group_attn_bwd", fn(ptr(d_oh), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H, (int)D,
+                                  as<int32_t>(cu), (int)M, (float)scale, ptr(d_qh), ptr(d_kh), ptr(d_vh), ptr(ws), bytes_of(ws),
+                                  call.stream()));
   return {d_qh, d_kh, d_vh};
 }
 
@@ -249,11 +251,12 @@ TokenGrads group_attn_bwd_tokens(const Tensor& d_o, const Tensor& qh, const Tens
   g.d_q = call.make({N, H, D}, qh);
   g.d_k = call.make({N, H, D}, kh);
   g.d_v = call.make({N, H, D}, vh);
-  OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_BWD, N, N, H, D, M, qh);
+  OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_BWD_JOINT, N, N, H, D, M, qh);
   check("moga_group_attn_bwd_tokens",
-        moga_group_attn_bwd_tokens(ptr(d_o), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H, (int)D, as<int32_t>(cu),
-                                   (int)M, (float)scale, as<int32_t>(perm), as<float>(gate), ptr(g.d_oh), as<float>(g.d_gate), ptr(g.d_qh),
-                                   ptr(g.d_kh), ptr(g.d_vh), ptr(g.d_q), ptr(g.d_k), ptr(g.d_v), ptr(ws), bytes_of(ws), call.stream()));
+        moga_group_attn_bwd_tokens_joint(ptr(d_o), ptr(qh), ptr(kh), ptr(vh), ptr(oh), as<float>(lse), dt(qh), N, (int)H, (int)D,
+                                         as<int32_t>(cu), (int)M, (float)scale, as<int32_t>(perm), as<float>(gate), ptr(g.d_oh),
+                                         as<float>(g.d_gate), ptr(g.d_qh), ptr(g.d_kh), ptr(g.d_vh), ptr(g.d_q), ptr(g.d_k), ptr(g.d_v),
+                                         ptr(ws), bytes_of(ws), call.stream()));
   return g;
 }
 

@@ -73,6 +73,40 @@ def test_calls_together(name, small_rows, dtype):
         assert int(c[8][8 * q.shape[1] * H:].view(torch.int32)[0] if q.shape[1] else 0) == 0   # no wave gave up
 
 
+# one launch for dQ and dK/dV against the two of the call with a workspace of its own: no round is split, so only the small-group kernels and
+# the large ones differ in their bits
+@pytest.mark.parametrize("sizes,H", [([300, 0, 77], 3), ([1], 1), ([900, 1300, 2100, 5], 4), ([640] * 9, 12), ([1536] * 4, 16), ([3000], 1)])
+@pytest.mark.parametrize("small_rows", [0, 1 << 40])
+def test_one_launch_gives_the_bits_of_two(sizes, H, small_rows):
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v, d_o = (torch.randn((H, sum(sizes), 128), generator=gen, device="cuda").bfloat16() for _ in range(4))
+    cu, scale = torch.tensor(sums(sizes), dtype=torch.int32, device="cuda"), 128 ** -0.5
+    need = mg.workspace_bytes(mg.OP_ATTN_BWD_JOINT, q.shape[1], H, 128, len(sizes), 0, mg.MOGA_BF16)
+    lib, stream = mg.load(), torch.cuda.current_stream().cuda_stream
+    ptr = lambda *t: [x.data_ptr() for x in t]
+    try:
+        mg.set_small_group_rows(small_rows)
+        oh, lse = mg.moga_group_attn_fwd(q, k, v, cu, scale)
+
+        def run(fn):
+            ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+            g = [torch.full_like(q, float("nan")) for _ in range(3)]
+            assert fn(*ptr(d_o, q, k, v, oh, lse), mg.MOGA_BF16, q.shape[1], H, 128, cu.data_ptr(), len(sizes), scale, *ptr(*g, ws), need, stream) == 0
+            torch.cuda.synchronize()
+            return g, int(mg.attn_bwd_status(ws, q.shape[1], H))
+
+        got, flag = run(lib.moga_group_attn_bwd_joint)
+        want, _ = run(lib.moga_group_attn_bwd)
+        assert flag == 0
+        for x, y in zip(got, want):
+            assert torch.equal(x, y)
+        mg.set_spin_limit(0)
+        assert run(lib.moga_group_attn_bwd_joint)[1] != 0   # the waits are bounded: every wave gave up, and the kernel drained
+    finally:
+        mg.set_spin_limit(1 << 24)
+        mg.set_small_group_rows(-1)
+
+
 def test_calls_that_are_refused():
     t = torch.zeros((2, 8, 128), device="cuda", dtype=torch.bfloat16)
     cu = torch.tensor([0, 8], dtype=torch.int32, device="cuda")
