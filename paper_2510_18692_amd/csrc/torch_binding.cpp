@@ -592,24 +592,64 @@ Tensor balance_loss_bwd(const Tensor& group, const Tensor& frac, double alpha, d
 }
 
 // ---- autograd: Alg. 1 with Eq. 5 and, when alpha is given, the balancing loss of Eqs. 6-8 ----
+// Parts of one allocation.  The calls of a step are made directly, with what is small in one tensor (saved for the backward) and what is only needed
+// during the pass in another: a step of 1,560 tokens, 4 heads is bound by the host, and an allocation costs 1 us, three in the engine's thread.
+class Parts {
+ public:
+  size_t add(size_t bytes) {
+    const size_t at = size_;
+    size_ += (bytes + 255) / 256 * 256;
+    return at;
+  }
+  size_t size() const { return size_; }
+
+ private:
+  size_t size_ = 0;
+};
+template <typename T> T* part(const Tensor& t, size_t at) { return reinterpret_cast<T*>(static_cast<char*>(t.data_ptr()) + at); }
+
+struct SavedParts : Parts {   // what the forward leaves for the backward beside the rows
+  size_t gate, probs, cu, perm, lse, frac;
+  SavedParts(int64_t N, int64_t H, int64_t M)
+      : gate(add(4 * N)), probs(add(4 * N * M)), cu(add(4 * (M + 1))), perm(add(4 * N)), lse(add(4 * H * N)), frac(add(4 * M)) {}
+};
+
 struct Attention : public torch::autograd::Function<Attention> {
   static torch::autograd::variable_list forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& w, const Tensor& q,
                                                 const Tensor& k, const Tensor& v, double scale, std::optional<double> alpha, bool grad_x) {
-    const int64_t M = w.size(0);
-    auto [group, gate, probs, logits] = route(x, w, std::nullopt, true, false, std::nullopt);
-    Permuted p = permute(group, M, q, k, v, std::nullopt);
-    auto [oh, lse, o] = group_attn_fwd_tokens(*p.qh, *p.kh, *p.vh, p.cu_seqlens, scale, p.perm, gate, std::nullopt);
-    Tensor loss, frac;
-    if (alpha) {
-      loss = at::empty({}, x.options().dtype(at::kFloat));
-      frac = std::get<0>(balance_into(loss, group, gate, M, *alpha, std::nullopt));
-    } else {
-      loss = at::zeros({}, x.options().dtype(at::kFloat));
-    }
-    ctx->save_for_backward({x, w, group, gate, *probs, p.cu_seqlens, p.perm, *p.qh, *p.kh, *p.vh, oh, lse, frac});
-    ctx->saved_data["scale"] = scale;
-    ctx->saved_data["alpha"] = alpha;
-    ctx->saved_data["grad_x"] = grad_x;
+    require(x, w, q, k, v);
+    const Call call(std::nullopt);
+    need_dims(x, 2);
+    need_dims(q, 3);
+    const int64_t N = x.size(0), d = x.size(1), M = w.size(0), H = q.size(1), D = q.size(2);
+    Tensor group = call.make({N}, x, at::kInt), o = call.make({N, H, D}, q);
+    Tensor loss = alpha ? at::empty({}, x.options().dtype(at::kFloat)) : at::zeros({}, x.options().dtype(at::kFloat));
+    Tensor qh = call.make({H, N, D}, q), kh = call.make({H, N, D}, k), vh = call.make({H, N, D}, v), oh = call.make({H, N, D}, q);
+    const SavedParts at(N, H, M);
+    Tensor saved = call.workspace(at.size(), x);
+    Parts t;   // of this pass
+    const size_t counts = t.add(4 * M), longest = t.add(4), inv_perm = t.add(4 * N), prob = t.add(4 * M);
+    const size_t sort_bytes = moga_workspace_bytes(MOGA_OP_PERMUTE, N, (int)H, (int)D, (int)M, 0, dt(q)), sort_ws = t.add(sort_bytes);
+    const size_t loss_bytes = alpha ? moga_workspace_bytes(MOGA_OP_BALANCE_LOSS, N, 0, 0, (int)M, 0, MOGA_F32) : 0, loss_ws = t.add(loss_bytes);
+    Tensor pass = call.workspace(t.size(), x);
+    float *gate = part<float>(saved, at.gate), *lse = part<float>(saved, at.lse);
+    int32_t *cu = part<int32_t>(saved, at.cu), *perm = part<int32_t>(saved, at.perm);
+    check("moga_route", moga_route(ptr(x), dt(x), as<float>(w), nullptr, N, (int)d, (int)M, as<int32_t>(group), gate,
+                                   part<float>(saved, at.probs), nullptr, nullptr, 0, call.stream()));
+    check("moga_permute",
+          moga_permute(as<int32_t>(group), N, (int)M, ptr(q), ptr(k), ptr(v), dt(q), (int)H, (int)D, part<int32_t>(pass, counts), cu,
+                       part<int32_t>(pass, longest), perm, part<int32_t>(pass, inv_perm), ptr(qh), ptr(kh), ptr(vh),
+                       part<void>(pass, sort_ws), sort_bytes, call.stream()));
+    OptTensor ws = call.attn_workspace(MOGA_OP_ATTN_FWD, N, N, H, D, M, qh);
+    check("moga_group_attn_fwd_tokens",
+          moga_group_attn_fwd_tokens(ptr(qh), ptr(kh), ptr(vh), dt(qh), N, (int)H, (int)D, cu, (int)M, (float)scale, perm, gate, ptr(oh), lse,
+                                     ptr(o), ptr(ws), bytes_of(ws), call.stream()));
+    if (alpha)
+      check("moga_balance_loss", moga_balance_loss(as<int32_t>(group), gate, N, (int)M, (float)*alpha, as<float>(loss),
+                                                   part<float>(saved, at.frac), part<float>(pass, prob), part<void>(pass, loss_ws), loss_bytes,
+                                                   call.stream()));
+    ctx->save_for_backward({x, w, group, saved, qh, kh, vh, oh});
+    ctx->saved_data["args"] = std::vector<double>{scale, alpha.value_or(0.), alpha ? 1. : 0., grad_x ? 1. : 0.};
     ctx->mark_non_differentiable({group});
     ctx->set_materialize_grads(false);
     return {o, loss, group};
@@ -617,19 +657,45 @@ struct Attention : public torch::autograd::Function<Attention> {
 
   static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, const torch::autograd::variable_list& grads) {
     const auto s = ctx->get_saved_variables();
-    const Tensor &x = s[0], &w = s[1], &group = s[2], &gate = s[3], &probs = s[4], &cu = s[5], &perm = s[6], &qh = s[7], &kh = s[8],
-                 &vh = s[9], &oh = s[10], &lse = s[11], &frac = s[12];
-    const double scale = ctx->saved_data["scale"].toDouble();
-    const auto alpha = ctx->saved_data["alpha"].toOptional<double>();
-    const bool grad_x = ctx->saved_data["grad_x"].toBool();
-    Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros({qh.size(1), qh.size(0), qh.size(2)}, qh.options());
-    TokenGrads g = group_attn_bwd_tokens(d_o, qh, kh, vh, oh, lse, cu, scale, perm, gate, false, std::nullopt);
-    g.d_oh.reset();
-    const bool balanced = alpha && grads[1].defined();
-    auto [d_w, d_x] = route_bwd_with(x, w, probs, group, gate, g.d_gate, balanced ? OptTensor(frac) : std::nullopt, alpha.value_or(0.),
-                                     balanced ? OptTensor(grads[1]) : std::nullopt,
-                                     grad_x ? std::optional<at::ScalarType>(x.scalar_type()) : std::nullopt, std::nullopt);
-    return {d_x.value_or(Tensor()), d_w, g.d_q, g.d_k, g.d_v, Tensor(), Tensor(), Tensor()};
+    const Tensor &x = s[0], &w = s[1], &group = s[2], &saved = s[3], &qh = s[4], &kh = s[5], &vh = s[6], &oh = s[7];
+    const std::vector<double> args = ctx->saved_data["args"].toDoubleVector();
+    const double scale = args[0];
+    const bool balanced = args[2] != 0. && grads[1].defined();
+    require(x, w, group, saved, qh, kh, vh, oh);
+    const Call call(std::nullopt);
+    const int64_t N = x.size(0), d = x.size(1), M = w.size(0), H = qh.size(0), D = qh.size(2);
+    const SavedParts at(N, H, M);
+    Tensor d_o = grads[0].defined() ? grads[0].contiguous() : at::zeros({N, H, D}, qh.options());
+    Tensor d_q = call.make({N, H, D}, qh), d_k = call.make({N, H, D}, kh), d_v = call.make({N, H, D}, vh), d_w = call.make({M, d}, x, at::kFloat);
+    Parts t;
+    const size_t need = moga_workspace_bytes(MOGA_OP_ATTN_BWD_JOINT, N, (int)H, (int)D, (int)M, 0, dt(qh));
+    const bool own_ws = moga_workspace_preferred_bytes(MOGA_OP_ATTN_BWD_JOINT, N, N, (int)H, (int)D, (int)M, 0, dt(qh)) > need;
+    const bool own_rows = oh.nbytes() > (64 << 20);   // given back before the router's gradients are made
+    const size_t d_gate = t.add(4 * N), attn_ws = t.add(own_ws ? 0 : need);
+    const size_t route_bytes = moga_workspace_bytes(MOGA_OP_ROUTE_BWD, N, 0, 0, (int)M, (int)d, dt(x)), route_ws = t.add(route_bytes);
+    const size_t rows = t.add(own_rows ? 0 : oh.nbytes());
+    Tensor pass = call.workspace(t.size(), x);
+    const float *gate = part<float>(saved, at.gate), *lse = part<float>(saved, at.lse);
+    const int32_t *cu = part<int32_t>(saved, at.cu), *perm = part<int32_t>(saved, at.perm);
+    {
+      OptTensor ws, d_oh;
+      if (own_ws) ws = call.attn_workspace(MOGA_OP_ATTN_BWD_JOINT, N, N, H, D, M, qh);
+      if (own_rows) d_oh = call.make({H, N, D}, oh);
+      check("moga_group_attn_bwd_tokens",
+            moga_group_attn_bwd_tokens_joint(ptr(d_o), ptr(qh), ptr(kh), ptr(vh), ptr(oh), lse, dt(qh), N, (int)H, (int)D, cu, (int)M,
+                                             (float)scale, perm, gate, d_oh ? ptr(*d_oh) : part<void>(pass, rows), part<float>(pass, d_gate),
+                                             nullptr, nullptr, nullptr, ptr(d_q), ptr(d_k), ptr(d_v), ws ? ptr(*ws) : part<void>(pass, attn_ws),
+                                             ws ? bytes_of(ws) : need, call.stream()));
+    }
+    Tensor d_x, d_loss;
+    if (args[3] != 0.) d_x = call.make({N, d}, x);
+    if (balanced) d_loss = grads[1].scalar_type() == at::kFloat ? grads[1] : device_scalar(grads[1], call);
+    check("moga_route_bwd",
+          moga_route_bwd_typed(ptr(x), dt(x), as<float>(w), part<float>(saved, at.probs), as<int32_t>(group), gate, part<float>(pass, d_gate),
+                               balanced ? part<float>(saved, at.frac) : nullptr, (float)args[1], 1.f, balanced ? as<float>(d_loss) : nullptr, N,
+                               (int)d, (int)M, as<float>(d_w), d_x.defined() ? ptr(d_x) : nullptr, dt(x), part<void>(pass, route_ws),
+                               route_bytes, call.stream()));
+    return {d_x, d_w, d_q, d_k, d_v, Tensor(), Tensor(), Tensor()};
   }
 };
 
