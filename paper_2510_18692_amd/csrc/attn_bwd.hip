@@ -439,13 +439,14 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     if (ts_k && Nk > 0) tile_start_kernel<<<1, 1024, 0, st>>>(cu_k, M, kF32Rows, ts_k);
     if (ts_q) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, kF32Rows, ts_q);
     auto launch = [&](int64_t dq_blocks, int64_t dkdv_blocks) {
-#define MOGA_BWD_F32(DD)                                                                                              \
-  attn_bwd_f32_kernel<DD><<<(unsigned)(dq_blocks + dkdv_blocks), 64 * kF32Waves, 0, st>>>(                           \
+#define MOGA_BWD_F32(DD, TT)                                                                                          \
+  attn_bwd_f32_kernel<DD, TT><<<(unsigned)(dq_blocks + dkdv_blocks), 64 * kF32Waves, 0, st>>>(                       \
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k, ts_q, ts_k, M, Nq,   \
       Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)dkdv_blocks, (float*)d_qh, (float*)d_kh, (float*)d_vh,          \
       tok.perm, (float*)tok.d_q, (float*)tok.d_k, (float*)tok.d_v)
-      if (D == 64) MOGA_BWD_F32(64);
-      else MOGA_BWD_F32(128);
+      if (D == 64 && std::max(Nq, Nk) > (int64_t)kF32LongGroupBwd * M) MOGA_BWD_F32(64, 2);
+      else if (D == 64) MOGA_BWD_F32(64, 1);
+      else MOGA_BWD_F32(128, 1);
 #undef MOGA_BWD_F32
     };
     if (grid_fits((q_tiles + k_tiles) * H, 64 * kF32Waves)) {

@@ -16,7 +16,7 @@
 // Streamed rows reach the scores, and in the backward the second products too, through the wave's own LDS.  Loaded straight as A
 // operands, the 16 lanes that a load serves at a time were in 16 rows, a cache line each for 16 bytes, and the vector cache's rate
 // of lines was the bound (10 TB/s from L2).  Forward / backward in us, so and now: 4,096 x 2 heads x 64, 8 groups 22.6 / 61.2 and
-// 19.9 / 50.7; 8,192 x 4 x 64, 8 groups 116 / 354 and 88 / 284; 16,384 x 4 x 64, 4 groups 822 / 2,591 and 594 / 1,986 (116 and 121
+// 20.3 / 49.0; 8,192 x 4 x 64, 8 groups 116 / 354 and 88 / 267; 16,384 x 4 x 64, 4 groups 822 / 2,591 and 594 / 1,986 (116 and 121
 // TFLOP/s executed of the 157 that the instruction has); x 128 1,328 / 4,775 and 1,184 / 3,902.  Bound by the matrix instruction
 // at large groups, at small ones by a few dependent steps between launch, first loads and the final sums.  The 32-row blocks of
 // eight waves that these replaced (32x32x2 instruction, rows straight from memory) took 29.5 / 86.3, 124 / 384, 739 / 2,454 and
@@ -29,7 +29,14 @@ namespace moga {
 
 constexpr int kF32Rows = 16;
 constexpr int kF32Waves = 4;
-template <int D> constexpr int kF32Tiles = D == 64 ? 2 : 1;   // T: with D = 128 two would not fit the registers
+// T, the 16-row tiles of a step, is one; with D = 64 and long groups two (with D = 128 two would not fit the registers).
+// Forward from a mean of 768 streamed rows on: us with one and two, 4,096 rows x 2 heads, 8 groups 20.3 and 20.9, 2,000 x 4, 5
+// groups 15.5 and 16.0, 8,000 x 1, 20 groups 12.6 and 14.0, but 8,192 x 4, 8 groups 89.0 and 88.1, 8,000 x 4, 2 groups 290 and 280.
+// Backward from 2,048 on.  One tile leaves registers for three waves per SIMD instead of two: 4,096 x 2, 8 groups 49.0 and 51.6,
+// 1,024 x 2, 4 groups 15.2 and 17.0, 8,192 x 4, 8 groups 267 and 284 (four waves spill: 57.5, 4,096 x 2).  But it adds twice as many
+// sums to the gradients, which in long groups shows: their errors against float64 in the 2-norm, one and two, one group of 512
+// rows 4.85e-7 and 4.87e-7, 1,024 5.18e-7 and 5.21e-7, 2,048 6.08e-7 both, 3,000 6.30e-7 and 6.28e-7, 8,192 7.42e-7 and 7.30e-7.
+constexpr int kF32LongGroup = 768, kF32LongGroupBwd = 2048;
 
 __device__ __forceinline__ floatx4_t f32_mfma(float a, float b, floatx4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -75,10 +82,9 @@ __device__ __forceinline__ void f32_settle(F32Frag<D>& f) {
   for (int j = 0; j < D / 16; ++j) asm volatile("" : "+v"(f.v[j]));
 }
 
-// A wave's 16 T streamed rows of one tensor in its own LDS: 8 KB, in direct-to-LDS loads of 1 KB (whole rows).  Straight from
+// A wave's 16 T streamed rows of one tensor in its own LDS, in direct-to-LDS loads of 1 KB (whole rows).  Straight from
 // memory as A operands, every lane of a load is in a row of its own: sixteen cache lines for 256 bytes.  Chunk c (16 bytes) of
 // row j is stored at c ^ swizzle(j), which spreads both kinds of reads below over all banks.
-constexpr int kF32TileBytes = 8192;
 __device__ __forceinline__ constexpr int f32_swizzle(int row) { return (row & 15) ^ ((row & 4) << 1); }
 
 template <int D, int T>
@@ -201,8 +207,8 @@ template <int D> struct F32Sums { __attribute__((aligned(16))) float v[kF32Waves
 
 // LDS of a block that stages `tensors` tensors and then holds as many sums.
 template <int D>
-constexpr int f32_lds_bytes(int tensors) {
-  return tensors * (kF32Waves * kF32TileBytes > (int)sizeof(F32Sums<D>) ? kF32Waves * kF32TileBytes : (int)sizeof(F32Sums<D>));
+constexpr int f32_lds_bytes(int tensors, int tile) {
+  return tensors * (kF32Waves * tile > (int)sizeof(F32Sums<D>) ? kF32Waves * tile : (int)sizeof(F32Sums<D>));
 }
 
 template <int D>
@@ -239,14 +245,14 @@ __device__ __forceinline__ bool f32_find(const int32_t* __restrict__ cu, const i
 }
 
 // ---- forward ---------------------------------------------------------------------------
-template <int D>
+template <int D, int T>
 __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_fwd_f32_kernel(
     const float* __restrict__ qh, const float* __restrict__ kh, const float* __restrict__ vh,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M,
     int64_t Nq, int64_t Nk, int H, float scale, int tiles_per_head, float* __restrict__ oh, float* __restrict__ lse,
     const int32_t* __restrict__ perm, const float* __restrict__ gate, float* __restrict__ o_tok) {
-  constexpr int NW = kF32Waves, T = kF32Tiles<D>, STEP = 16 * T;
-  __shared__ __attribute__((aligned(1024))) unsigned char s_mem[f32_lds_bytes<D>(1)];
+  constexpr int NW = kF32Waves, STEP = 16 * T;
+  __shared__ __attribute__((aligned(1024))) unsigned char s_mem[f32_lds_bytes<D>(1, 16 * T * D * 4)];
   __shared__ float s_m[NW][16], s_l[NW][16];
   F32Sums<D>& s_o = *(F32Sums<D>*)s_mem;   // after the loop
   int head;
@@ -259,7 +265,7 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_fwd_f32_
   const float* vb = vh + ((int64_t)head * Nk + gs) * D;
   const float c = scale * 1.4426950408889634f;
 
-  const unsigned lds = lds_addr_uniform(s_mem) + wave * kF32TileBytes;
+  const unsigned lds = lds_addr_uniform(s_mem) + wave * (16 * T * D * 4);
   if (STEP * wave < n) f32_stage<D, T>(lds, kb, STEP * wave, n, lane);
   F32Frag<D> qf;
   f32_load<D>(qf, qh + (head_off + min(ti.tile_row + r, ti.row_end - 1)) * D, g);
@@ -329,13 +335,13 @@ __global__ __launch_bounds__(64 * kF32Waves, D == 64 ? 4 : 2) void attn_fwd_f32_
 }
 
 // ---- backward: -delta = -rowsum(dO * O) comes from the caller ------------------------------
-template <int D>
+template <int D, int T>
 __device__ __forceinline__ void f32_dq_block(
     unsigned char* s_mem, int block, const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh,
     const float* __restrict__ vh, const float* __restrict__ lse, const float* __restrict__ neg_delta, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M, int64_t Nq, int64_t Nk, int H, float scale,
     int tiles_per_head, float* __restrict__ d_qh, const int32_t* __restrict__ perm, float* __restrict__ d_q_tok) {
-  constexpr int NW = kF32Waves, T = kF32Tiles<D>, STEP = 16 * T;
+  constexpr int NW = kF32Waves, STEP = 16 * T, kTile = 16 * T * D * 4;
   int head;
   TileInfo ti;
   if (!f32_find(cu_q, tile_start, M, block, tiles_per_head, head, ti)) return;
@@ -352,7 +358,7 @@ __device__ __forceinline__ void f32_dq_block(
   floatx4_t dq[D / 16];
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) dq[dt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  const unsigned lds_k = lds_addr_uniform(s_mem) + wave * 2 * kF32TileBytes, lds_v = lds_k + kF32TileBytes;
+  const unsigned lds_k = lds_addr_uniform(s_mem) + wave * 2 * kTile, lds_v = lds_k + kTile;
   auto stage = [&](int row0) {
     f32_stage<D, T>(lds_k, kb, row0, n, lane);
     f32_stage<D, T>(lds_v, vb, row0, n, lane);
@@ -391,14 +397,14 @@ __device__ __forceinline__ void f32_dq_block(
   f32_write<D>(sums, one, scale, 1.f, row, f32_sorted_row<D>(d_qh, head_off + j), f32_token_row<D>(d_q_tok, perm, j, head, H));
 }
 
-template <int D>
+template <int D, int T>
 __device__ __forceinline__ void f32_dkdv_block(
     unsigned char* s_mem, int block, const float* __restrict__ d_oh, const float* __restrict__ qh,
     const float* __restrict__ kh, const float* __restrict__ vh, const float* __restrict__ lse, const float* __restrict__ neg_delta,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const int32_t* __restrict__ tile_start, int M, int64_t Nq,
     int64_t Nk, int H, float scale, int tiles_per_head, float* __restrict__ d_kh, float* __restrict__ d_vh,
     const int32_t* __restrict__ perm, float* __restrict__ d_k_tok, float* __restrict__ d_v_tok) {
-  constexpr int NW = kF32Waves, T = kF32Tiles<D>, STEP = 16 * T;
+  constexpr int NW = kF32Waves, STEP = 16 * T, kTile = 16 * T * D * 4;
   int head;
   TileInfo ti;   // tiles run over the key rows of the groups
   if (!f32_find(cu_k, tile_start, M, block, tiles_per_head, head, ti)) return;
@@ -415,7 +421,7 @@ __device__ __forceinline__ void f32_dkdv_block(
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) dk[dt] = dv[dt] = floatx4_t{0.f, 0.f, 0.f, 0.f};
   __shared__ __attribute__((aligned(16))) float s_stat[NW][2][32];
-  const unsigned lds_q = lds_addr_uniform(s_mem) + wave * 2 * kF32TileBytes, lds_o = lds_q + kF32TileBytes;
+  const unsigned lds_q = lds_addr_uniform(s_mem) + wave * 2 * kTile, lds_o = lds_q + kTile;
   float stat = 0.f;
   auto stage = [&](int row0) {
     stat = f32_load_stat<T>(lse + q_off, neg_delta + q_off, row0, n, lane);
@@ -467,19 +473,19 @@ __device__ __forceinline__ void f32_dkdv_block(
 }
 
 // Blocks below `k_blocks` are dK/dV's (four products to three: the longer ones first), the others dQ's.
-template <int D>
-__global__ __launch_bounds__(64 * kF32Waves, 2) void attn_bwd_f32_kernel(
+template <int D, int T>
+__global__ __launch_bounds__(64 * kF32Waves, D == 64 && T == 1 ? 3 : 2) void attn_bwd_f32_kernel(
     const float* __restrict__ d_oh, const float* __restrict__ qh, const float* __restrict__ kh, const float* __restrict__ vh,
     const float* __restrict__ lse, const float* __restrict__ neg_delta, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k,
     const int32_t* __restrict__ ts_q, const int32_t* __restrict__ ts_k, int M, int64_t Nq, int64_t Nk, int H, float scale, int q_tiles,
     int k_tiles, int k_blocks, float* __restrict__ d_qh, float* __restrict__ d_kh, float* __restrict__ d_vh,
     const int32_t* __restrict__ perm, float* __restrict__ d_q_tok, float* __restrict__ d_k_tok, float* __restrict__ d_v_tok) {
-  __shared__ __attribute__((aligned(1024))) unsigned char s_mem[f32_lds_bytes<D>(2)];
+  __shared__ __attribute__((aligned(1024))) unsigned char s_mem[f32_lds_bytes<D>(2, 16 * T * D * 4)];
   if ((int)blockIdx.x < k_blocks)
-    f32_dkdv_block<D>(s_mem, blockIdx.x, d_oh, qh, kh, vh, lse, neg_delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, scale, k_tiles, d_kh,
+    f32_dkdv_block<D, T>(s_mem, blockIdx.x, d_oh, qh, kh, vh, lse, neg_delta, cu_q, cu_k, ts_k, M, Nq, Nk, H, scale, k_tiles, d_kh,
                        d_vh, perm, d_k_tok, d_v_tok);
   else
-    f32_dq_block<D>(s_mem, blockIdx.x - k_blocks, d_oh, qh, kh, vh, lse, neg_delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, scale, q_tiles, d_qh,
+    f32_dq_block<D, T>(s_mem, blockIdx.x - k_blocks, d_oh, qh, kh, vh, lse, neg_delta, cu_q, cu_k, ts_q, M, Nq, Nk, H, scale, q_tiles, d_qh,
                      perm, d_q_tok);
 }
 

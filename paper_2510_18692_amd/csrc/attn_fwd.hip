@@ -79,12 +79,13 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   if (!grid_fits(blocks, dtype == MOGA_BF16 && !small ? 512 : 256)) return MOGA_ERR_UNSUPPORTED;
   if (tile_start) tile_start_kernel<<<1, 1024, 0, st>>>(cu_q, M, bm, tile_start);
   if (dtype == MOGA_F32) {
-#define MOGA_FWD_F32(DD)                                                                                                   \
-  attn_fwd_f32_kernel<DD><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                                    \
+#define MOGA_FWD_F32(DD, TT)                                                                                               \
+  attn_fwd_f32_kernel<DD, TT><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                                \
       (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, \
       (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o)
-    if (D == 64) MOGA_FWD_F32(64);
-    else MOGA_FWD_F32(128);
+    if (D == 64 && Nk >= (int64_t)kF32LongGroup * M) MOGA_FWD_F32(64, 2);
+    else if (D == 64) MOGA_FWD_F32(64, 1);
+    else MOGA_FWD_F32(128, 1);
 #undef MOGA_FWD_F32
   } else if (small) {
     attn_fwd_bf16_small_kernel<<<(unsigned)blocks, 256, 0, st>>>(
