@@ -235,13 +235,16 @@ __device__ __forceinline__ void route_finish(const floatx16_t& total, int64_t to
 // own in each of twelve loads (10,007 x 1536, 20 groups: 17.1 us).  16-byte chunks are XOR-swizzled by the row so that the reads
 // hit all banks.  W is split into its limbs in registers.  The other kernel's time and this one's, in us: 1,560 x 512, 8 groups
 // 9.5 and 5.1; 1,560 x 1536, 16 groups 18.6 and 8.1; 10,007 x 1536, 20 groups 19.1 and 11.7; 8,192 x 5120, 16 groups 60 and 23;
-// 16,384 x 1536, 8 groups 21.7 and 13.8 (3.6 TB/s).  Eight waves to a block are slower from 10,007 tokens on (15.0).
+// 16,384 x 1536, 8 groups 21.7 and 13.8 (3.6 TB/s).  A block alone on its CU waits for its waves' own chains (splitting W, twelve dependent
+// products a k block; two more k blocks in flight: 1 us slower): eight waves instead of four where a CU has one block and they have many
+// k blocks, 1,253 x 5120, 4 groups 17.6 -> 15.4, 5,225 x 5120, 20 groups 19.3 -> 17.3, but 8,192 x 5120, 16 groups 20.6 and 20.8, 1,560 x 1536 8.3
+// and 8.1, 10,007 x 1536 11.9 and 15.0.
 constexpr int kFewW = 32 * 256, kFewX = 32 * 128;   // bytes of a wave's k block
 
-__global__ __launch_bounds__(256, 3) void route_mfma_few_kernel(
+template <int NWV>
+__global__ __launch_bounds__(64 * NWV, NWV == 4 ? 3 : 1) void route_mfma_few_kernel(
     const unsigned short* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias, int64_t N, int d, int M,
     int32_t* __restrict__ group, float* __restrict__ gate, float* __restrict__ probs, float* __restrict__ logits) {
-  constexpr int NWV = 4;
   __shared__ __attribute__((aligned(1024))) unsigned char s_k[NWV][kFewW + kFewX];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int r = lane & 31, h = lane >> 5;
@@ -944,8 +947,11 @@ extern "C" int moga_route(const void* x, int x_dtype, const float* w, const floa
                                                      group, gate, probs, logits);
     } else if (use_route_few(N, d_model, M)) {
       const unsigned blocks = (unsigned)((N + 31) / 32);
-      route_mfma_few_kernel<<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
-                                                       group, gate, probs, logits);
+#define MOGA_ROUTE_FEW(NWV)                                                                                                            \
+  route_mfma_few_kernel<NWV><<<blocks, 64 * NWV, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M, group, gate, probs, logits)
+      if (blocks <= 192 && d_model >= 2560) MOGA_ROUTE_FEW(8);
+      else MOGA_ROUTE_FEW(4);
+#undef MOGA_ROUTE_FEW
     } else {
       const unsigned blocks = (unsigned)((N + 127) / 128);
       route_mfma_kernel<1, 4><<<blocks, 256, 0, st>>>((const unsigned short*)x, w, bias, N, d_model, M,
