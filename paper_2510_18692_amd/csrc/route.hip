@@ -492,23 +492,32 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
         partial[((int64_t)split * M + j0 + j) * d + c] = (acc[j] + s_acc[0][j][lane]) + (s_acc[1][j][lane] + s_acc[2][j][lane]);
 }
 
-// dW of few tokens in one launch (where the matrix-core path below applies): a block takes 64 columns and all tokens, its sixteen waves
-// every sixteenth run of 16 tokens, and they are added through LDS at the end.  dr is made in registers, in two bf16 limbs as in
-// route_bwd_dr_pack_kernel, as the A operand (groups x tokens) of the 32x32x16 matrix instruction; X is the B operand: a lane loads
-// columns 2 r and 2 r + 1 of eight tokens, one column for each of two accumulators.  The three launches of that path against this
-// one, in us: 64 x 512, 8 groups 10.3 and 4.6; 390 x 1536, 8 groups 12.3 and 4.9; 1,560 x 1536, 4 groups 13.2 and 10.3; 1,560 x
-// 5120, 32 groups 20.8 and 10.7; 2,048 x 1536 13.3 and 12.5, from where they draw level (d / 64 blocks do all the work).
+// dW of up to some ten thousand tokens (where the matrix-core path below applies): a block takes 64 columns and a run of tokens, its
+// sixteen waves every sixteenth 16 of them, and they are added through LDS at the end; the sums of several blocks by
+// route_bwd_dw_reduce_kernel.  dr is made in registers, in two bf16 limbs as in route_bwd_dr_pack_kernel, as the A operand (groups x
+// tokens) of the 32x32x16 matrix instruction; X is the B operand: a lane loads columns 2 r and 2 r + 1 of eight tokens, one column for
+// each of two accumulators, 64 KB of a CU's loads in flight.  The three launches of that path against this one, in us: 64 x 512, 8 groups
+// 10.3 and 4.6; 390 x 1536, 8 groups 12.3 and 4.9; split over blocks, 5,000 x 1536, 20 groups 17.5 and 8.7; 10,007 x 1536, 20 groups
+// 19.5 and 13.1 (2.3 TB/s of X); 16,384 x 512, 8 groups 15.1 and 8.3; 32,760 x 1536, 20 groups 32.3 and 26.5 (3.8 TB/s); 10,007 x 5120, 32
+// groups 33.5 and 27.3.
 constexpr int kDwFewWaves = 16, kDwFewTok = 16;   // waves per block, tokens per run
-constexpr int kDwFewTokens = 2048;
+constexpr int kDwFewTokens = 8192;                // of one block
 
 __global__ __launch_bounds__(64 * kDwFewWaves) void route_bwd_dw_few_kernel(
     const unsigned short* __restrict__ x, const float* __restrict__ probs, const int32_t* __restrict__ group, const float* __restrict__ gate,
-    GateGrad gg, int N, int d, int M, float* __restrict__ d_w) {
+    GateGrad gg, int64_t n_all, int tokens, int d, int M, float* __restrict__ out) {
   constexpr int STEP = kDwFewTok * kDwFewWaves;
-  __shared__ float s_acc[kDwFewWaves][2][16][64];
-  __shared__ __attribute__((aligned(16))) float s_coef[kDwFewTokens];   // of all tokens, 0 past the end
-  __shared__ __attribute__((aligned(16))) int s_group[kDwFewTokens];
+  typedef float Acc[2][16][64];
+  __shared__ __attribute__((aligned(16))) unsigned char s_mem[kDwFewWaves * sizeof(Acc)];
+  float* s_coef = (float*)s_mem;                         // of the block's tokens, 0 past the end
+  int* s_group = (int*)s_mem + kDwFewTokens;
+  Acc* s_acc = (Acc*)s_mem;                              // after the loop
+  static_assert(8 * kDwFewTokens <= (int)sizeof(s_mem));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  const int64_t first_tok = (int64_t)blockIdx.y * tokens;
+  const int N = (int)min((int64_t)tokens, n_all - first_tok);   // the block's tokens
+  x += first_tok * d;
+  probs += first_tok * M;
   const unsigned short* xc = x + 64 * blockIdx.x + 2 * r;
   const float* pc = probs + min(r, M - 1);
   struct Run {
@@ -526,9 +535,9 @@ __global__ __launch_bounds__(64 * kDwFewWaves) void route_bwd_dw_few_kernel(
   Run cur, next;
   const int first = kDwFewTok * wave;
   if (first < N) load(cur, first);
-  for (int t = threadIdx.x; t < kDwFewTokens; t += 64 * kDwFewWaves) {
-    const int g = t < N ? group[t] : -1;
-    s_coef[t] = t < N ? gate_grad(gg, t, g, M) * gate[t] : 0.f;
+  for (int t = threadIdx.x; t < (N + kDwFewTok - 1) / kDwFewTok * kDwFewTok; t += 64 * kDwFewWaves) {
+    const int g = t < N ? group[first_tok + t] : -1;
+    s_coef[t] = t < N ? gate_grad(gg, first_tok + t, g, M) * gate[first_tok + t] : 0.f;
     s_group[t] = g;
   }
   __syncthreads();
@@ -573,6 +582,7 @@ __global__ __launch_bounds__(64 * kDwFewWaves) void route_bwd_dw_few_kernel(
     acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b1, acc[1], 0, 0, 0);
     cur = next;
   }
+  __syncthreads();
 #pragma unroll
   for (int c = 0; c < 2; ++c)
 #pragma unroll
@@ -586,7 +596,7 @@ __global__ __launch_bounds__(64 * kDwFewWaves) void route_bwd_dw_few_kernel(
     sum[1] += s_acc[k][1][wave][lane];
   }
   const int j = 8 * (wave >> 2) + 4 * h + (wave & 3);
-  if (j < M) *(floatx2_t*)(d_w + (int64_t)j * d + 64 * blockIdx.x + 2 * r) = sum;
+  if (j < M) *(floatx2_t*)(out + ((int64_t)blockIdx.y * M + j) * d + 64 * blockIdx.x + 2 * r) = sum;
 }
 
 // Sum of the splits, in a fixed order: 64 elements per block, eight waves that take every eighth split
@@ -893,6 +903,25 @@ static bool route_bwd_mfma_ok(int x_dtype, int M, int d) {
   return x_dtype == MOGA_BF16 && M <= 32 && d % kDwCols == 0;
 }
 
+// Plan of route_bwd_dw_few_kernel: `splits` blocks of `tokens` tokens for each 64 columns, one round of 256 blocks (a block has its
+// CU to itself), or no splits where the kernels of DwPlan are the better ones.  One split up to 2,048 tokens: two launches take the
+// device less from 1,024 on (1,560 x 1536, 4 groups 11.3 and 6.9 us), but the host more, which calls of so few tokens wait for (a whole
+// training step through autograd, 1,560 x 512, 99.7 and 103.7).  The DwPlan kernels beyond 1e8 activations (in us, them and this: 65,000 x
+// 1536, 32 groups 49.6 and 48.5; 87,000 x 1536 58.5 and 58.4; 32,760 x 5120 98.5 and 98.9) and beyond 65,536 tokens, where a block's
+// dr for 64 columns is what it waits for (512, 32 groups: 65,000 30.0 and 27.9; 87,000 33.8 and 34.5; 130,000 42.4 and 49.8).
+struct DwFewPlan {
+  int splits, tokens;
+};
+
+static DwFewPlan route_bwd_few_plan(int64_t N, int d) {
+  if (N > 65536 || N * d > 100000000) return {0, 0};
+  const int64_t room = std::max(1, 256 / (d / 64));
+  const int64_t splits = N <= 2048 ? 1 : std::min(room, N / 256);
+  const int64_t tokens = ((N + splits - 1) / splits + kDwFewTok - 1) / kDwFewTok * kDwFewTok;
+  if (tokens > kDwFewTokens) return {0, 0};
+  return {(int)((N + tokens - 1) / tokens), (int)tokens};
+}
+
 static DwPlan route_bwd_plan(int64_t N, int M, int d) {
   DwPlan p;
   p.mp = (M + 7) / 8 * 8;
@@ -923,6 +952,7 @@ extern "C" size_t moga_route_bwd_ws_bytes(int64_t N, int M, int d_model) {
   if (N > 0 && route_bwd_mfma_ok(MOGA_BF16, M, d_model)) {
     const DwPlan p = route_bwd_plan(N, M, d_model);
     need = std::max(need, 2 * p.dr_bytes + p.partial_bytes);
+    need = std::max(need, (size_t)route_bwd_few_plan(N, d_model).splits * (size_t)M * (size_t)d_model * sizeof(float));
   }
   return need;
 }
@@ -1029,9 +1059,12 @@ static int launch_route_bwd(const void* x, int x_dtype, const float* w, const fl
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   const bool mfma = route_bwd_mfma_ok(x_dtype, M, d_model);
   if (mfma && (!aligned16(x) || !aligned16(ws))) return MOGA_ERR_INVALID_ARG;
-  if (mfma && N <= kDwFewTokens && ((uintptr_t)d_w & 7) == 0) {
-    route_bwd_dw_few_kernel<<<(unsigned)(d_model / 64), 64 * kDwFewWaves, 0, st>>>((const unsigned short*)x, probs, group, gate, gg,
-                                                                                  (int)N, d_model, M, d_w);
+  const DwFewPlan few = mfma ? route_bwd_few_plan(N, d_model) : DwFewPlan{0, 0};
+  if (few.splits > 1 || (few.splits == 1 && ((uintptr_t)d_w & 7) == 0)) {
+    route_bwd_dw_few_kernel<<<dim3(d_model / 64, few.splits), 64 * kDwFewWaves, 0, st>>>(
+        (const unsigned short*)x, probs, group, gate, gg, N, few.tokens, d_model, M, few.splits > 1 ? (float*)ws : d_w);
+    if (few.splits > 1)
+      route_bwd_dw_reduce_kernel<false><<<(unsigned)((md + 63) / 64), 512, 0, st>>>((const float*)ws, few.splits, md, d_model, M, M, d_w);
   } else if (mfma) {
     const DwPlan p = route_bwd_plan(N, M, d_model);
     uintx4_t* dr_hi = (uintx4_t*)ws;
