@@ -321,14 +321,28 @@ static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, Bwd
   std::stable_sort(seg, seg + segments, [](const BwdSegment& x, const BwdSegment& y) { return x.length > y.length; });
   AttnBwdCalls a = {};
   std::copy(c, c + n, a.c);
-  std::fill(a.first, a.first + 2 * kMaxCalls, INT_MAX);
-  int64_t blocks = 0;
-  for (int s = 0; s < segments; ++s) {
-    a.first[s] = (int)blocks;
-    a.what[s] = seg[s].what;
-    blocks += seg[s].blocks;
-    if (!grid_fits(blocks, threads)) return MOGA_ERR_UNSUPPORTED;
-  }
+  // the blocks of the segments [first, last) as one grid, or 0 if it cannot hold them
+  auto grid = [&](int first, int last) -> int64_t {
+    std::fill(a.first, a.first + 2 * kMaxCalls, INT_MAX);
+    int64_t blocks = 0;
+    for (int s = first; s < last; ++s) {
+      a.first[s - first] = (int)blocks;
+      a.what[s - first] = seg[s].what;
+      blocks += seg[s].blocks;
+      if (!grid_fits(blocks, threads)) return 0;
+    }
+    return blocks;
+  };
+  // dK/dV of all calls, then dQ of all, from 12 rounds on: what one launch saves of a last round is little there, and blocks of both kinds side
+  // by side take longer.  Step of a three-branch block, two launches before (apart call by call, last rounds split), one and these two, in us, in brackets
+  // the rounds: 8 x 3 heads (4.5 of small and large blocks) 1,001, 793 and 903; 11 x 12 (9) 3,955, 3,440 and 3,508; 5 x 40 (14) 2,838, 2,545 and
+  // 2,565; 15 x 12 (13) 5,120, 5,001 and 4,927; 21 x 12 (18) 4,385, 4,257 and 4,179, with fewer and longer groups 8,615, 8,535 and 8,451 (8,788 and 8,904 with
+  // one on another card); 30 x 12 (26) 15,960, 15,705 and 15,637.
+  int64_t rows = 0;
+  for (int i = 0; i < n; ++i) rows += c[i].Nq;
+  const int mid = n > 1 && kernels == BwdKernels::kLarge && rows * H >= 12 * 256 * kCus
+                      ? (int)(std::stable_partition(seg, seg + segments, [](const BwdSegment& x) { return (x.what & 1) != 0; }) - seg) : segments;
+  if ((mid > 0 && grid(0, mid) == 0) || (mid < segments && grid(mid, segments) == 0)) return MOGA_ERR_UNSUPPORTED;
   for (int i = 0; i < n; ++i)
     if (c[i].M > MOGA_MAX_GROUPS) {
       int32_t *ts_q = ts[i], *ts_k = ts_q + (c[i].M + 1);
@@ -340,12 +354,16 @@ static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, Bwd
 #define MOGA_BWD_CALLS(KK, RR)                                                                                                            \
   if (kernels == BwdKernels::kGather) attn_bwd_calls_kernel<KK, RR, true><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin); \
   else attn_bwd_calls_kernel<KK, RR, false><<<(unsigned)blocks, 512, 0, st>>>(a, H, softmax_scale, spin)
-  if (kernels == BwdKernels::kSmall) {
-    attn_bwd_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale, spin);
-  } else if (bm == 384) {
-    MOGA_BWD_CALLS(192, 384);
-  } else {
-    MOGA_BWD_CALLS(128, 256);
+  for (int first = 0, last = mid; first < segments; first = last, last = segments) {
+    if (first == last) continue;   // no keys
+    const int64_t blocks = grid(first, last);
+    if (kernels == BwdKernels::kSmall) {
+      attn_bwd_small_calls_kernel<<<(unsigned)blocks, 256, 0, st>>>(a, H, softmax_scale, spin);
+    } else if (bm == 384) {
+      MOGA_BWD_CALLS(192, 384);
+    } else {
+      MOGA_BWD_CALLS(128, 256);
+    }
   }
 #undef MOGA_BWD_CALLS
   return launch_status();

@@ -24,12 +24,14 @@ def sums(sizes):
 
 
 # (queries, keys) of the groups of each call: empty groups, groups without keys or without queries, ends inside a tile, more than 256 groups (the
-# tiles are summed by a kernel of their own), one call, calls without queries; the last has blocks of 384 queries and 192 keys
+# tiles are summed by a kernel of their own), one call, calls without queries; "wide" has blocks of 384 queries and 192 keys, "many
+# rounds" (64 heads) dQ and dK/dV of all calls in a launch each
 CALLS = {
     "mixed": [([700, 0, 33, 385], [700, 0, 33, 385]), ([130, 64, 1], [300, 0, 65]), ([100, 100], [7, 129])],
     "many groups": [([3] * 300, [5] * 300), ([1000], [900])],
     "one": [([200, 100], [100, 90])],
     "no queries": [([0, 0], [10, 20]), ([40], [50]), ([300], [300])],
+    "many rounds": [([1024] * 8, [1000] * 8), ([1024, 1100, 500], [1024, 1100, 0]), ([2000], [2])],
     "wide": [([1536] * 4, [1536] * 4), ([384, 100, 500], [700, 200, 193]), ([1000], [1001])],
 }
 
@@ -39,7 +41,7 @@ CASES = [(name, rows, torch.bfloat16) for name in CALLS for rows in (-1, 0, 1 <<
 
 @pytest.mark.parametrize("name,small_rows,dtype", CASES)
 def test_calls_together(name, small_rows, dtype):
-    H, D = (16 if name == "wide" else 3), 128
+    H, D = {"wide": 16, "many rounds": 64}.get(name, 3), 128
     gen = torch.Generator(device="cuda").manual_seed(7)
     rnd = lambda n: torch.randn((H, n, D), generator=gen, device="cuda").to(dtype)
     scale, shapes = D ** -0.5, CALLS[name]
