@@ -32,7 +32,8 @@ constexpr int kF32Waves = 4;
 // T, the 16-row tiles of a step, is one; with D = 64 and long groups two (with D = 128 two would not fit the registers).
 // Forward from a mean of 768 streamed rows on: us with one and two, 4,096 rows x 2 heads, 8 groups 20.3 and 20.9, 2,000 x 4, 5
 // groups 15.5 and 16.0, 8,000 x 1, 20 groups 12.6 and 14.0, but 8,192 x 4, 8 groups 89.0 and 88.1, 8,000 x 4, 2 groups 290 and 280.
-// Backward from 2,048 on.  One tile leaves registers for three waves per SIMD instead of two: 4,096 x 2, 8 groups 49.0 and 51.6,
+// Backward from 2,048 on, and from 32,768 rows in all whatever the number of groups: empty groups at the end of a long list then
+// change no bit of the others' gradients.  One tile leaves registers for three waves per SIMD instead of two: 4,096 x 2, 8 groups 49.0 and 51.6,
 // 1,024 x 2, 4 groups 15.2 and 17.0, 8,192 x 4, 8 groups 267 and 284 (four waves spill: 57.5, 4,096 x 2).  But it adds twice as many
 // sums to the gradients, which in long groups shows: their errors against float64 in the 2-norm, one and two, one group of 512
 // rows 4.85e-7 and 4.87e-7, 1,024 5.18e-7 and 5.21e-7, 2,048 6.08e-7 both, 3,000 6.30e-7 and 6.28e-7, 8,192 7.42e-7 and 7.30e-7.
