@@ -462,7 +462,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
       (const float*)d_oh, (const float*)qh, (const float*)kh, (const float*)vh, lse, delta, cu_q, cu_k, ts_q, ts_k, M, Nq,   \
       Nk, H, softmax_scale, (int)q_tiles, (int)k_tiles, (int)dkdv_blocks, (float*)d_qh, (float*)d_kh, (float*)d_vh,          \
       tok.perm, (float*)tok.d_q, (float*)tok.d_k, (float*)tok.d_v)
-      if (D == 64 && std::max(Nq, Nk) > (int64_t)kF32LongGroupBwd * std::min(M, 16)) MOGA_BWD_F32(64, 2);
+      if (D == 64 && std::max(Nq, Nk) > kF32ShortCall) MOGA_BWD_F32(64, 2);
       else if (D == 64) MOGA_BWD_F32(64, 1);
       else MOGA_BWD_F32(128, 1);
 #undef MOGA_BWD_F32

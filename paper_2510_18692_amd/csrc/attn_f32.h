@@ -16,7 +16,7 @@
 // Streamed rows reach the scores, and in the backward the second products too, through the wave's own LDS.  Loaded straight as A
 // operands, the 16 lanes that a load serves at a time were in 16 rows, a cache line each for 16 bytes, and the vector cache's rate
 // of lines was the bound (10 TB/s from L2).  Forward / backward in us, so and now: 4,096 x 2 heads x 64, 8 groups 22.6 / 61.2 and
-// 20.3 / 49.0; 8,192 x 4 x 64, 8 groups 116 / 354 and 88 / 267; 16,384 x 4 x 64, 4 groups 822 / 2,591 and 594 / 1,986 (116 and 121
+// 20.9 / 51.6; 8,192 x 4 x 64, 8 groups 116 / 354 and 88 / 284; 16,384 x 4 x 64, 4 groups 822 / 2,591 and 594 / 1,986 (116 and 121
 // TFLOP/s executed of the 157 that the instruction has); x 128 1,328 / 4,775 and 1,184 / 3,902.  Bound by the matrix instruction
 // at large groups, at small ones by a few dependent steps between launch, first loads and the final sums.  The 32-row blocks of
 // eight waves that these replaced (32x32x2 instruction, rows straight from memory) took 29.5 / 86.3, 124 / 384, 739 / 2,454 and
@@ -29,15 +29,14 @@ namespace moga {
 
 constexpr int kF32Rows = 16;
 constexpr int kF32Waves = 4;
-// T, the 16-row tiles of a step, is one; with D = 64 and long groups two (with D = 128 two would not fit the registers).
-// Forward from a mean of 768 streamed rows on: us with one and two, 4,096 rows x 2 heads, 8 groups 20.3 and 20.9, 2,000 x 4, 5
-// groups 15.5 and 16.0, 8,000 x 1, 20 groups 12.6 and 14.0, but 8,192 x 4, 8 groups 89.0 and 88.1, 8,000 x 4, 2 groups 290 and 280.
-// Backward from 2,048 on, and from 32,768 rows in all whatever the number of groups: empty groups at the end of a long list then
-// change no bit of the others' gradients.  One tile leaves registers for three waves per SIMD instead of two: 4,096 x 2, 8 groups 49.0 and 51.6,
-// 1,024 x 2, 4 groups 15.2 and 17.0, 8,192 x 4, 8 groups 267 and 284 (four waves spill: 57.5, 4,096 x 2).  But it adds twice as many
-// sums to the gradients, which in long groups shows: their errors against float64 in the 2-norm, one and two, one group of 512
-// rows 4.85e-7 and 4.87e-7, 1,024 5.18e-7 and 5.21e-7, 2,048 6.08e-7 both, 3,000 6.30e-7 and 6.28e-7, 8,192 7.42e-7 and 7.30e-7.
-constexpr int kF32LongGroup = 768, kF32LongGroupBwd = 2048;
+// T, the 16-row tiles of a step, is one in calls of at most kF32ShortCall rows with D = 64, else two (with D = 128 two would not fit the
+// registers).  One tile leaves registers for three waves per SIMD in the backward instead of two (1,024 rows x 2 heads, 4 groups 15.2 and 17.0 us)
+// but adds twice as many sums to the results, which in long groups shows.  Errors against float64 in the 2-norm, in 1e-7, with one tile and two,
+// by the rows of one group: O 512 3.04 and 3.10, 1,536 3.22 and 3.24, 2,048 3.28 and 3.28, 4,096 3.42 and 3.35, 8,192 3.76 and 3.56, 30,000 5.04
+// and 4.28; dQ 512 4.21 and 4.25, 1,536 4.58 and 4.59, 2,048 5.19 and 5.19, 4,096 5.40 and 5.35, 8,192 5.76 and 5.62, 30,000 6.98 and 6.44; dK and
+// dV alike.  The line is by the rows of the call, which no group can exceed and empty groups do not change: by the mean group, one tile took
+// 4,096 x 2, 8 groups from 51.6 to 49.0 us backward, and a group that has most of the rows with it.
+constexpr int kF32ShortCall = 1536;
 
 __device__ __forceinline__ floatx4_t f32_mfma(float a, float b, floatx4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);

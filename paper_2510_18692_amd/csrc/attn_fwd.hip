@@ -83,7 +83,7 @@ static int launch_attn_fwd(const void* qh, const void* kh, const void* vh, int d
   attn_fwd_f32_kernel<DD, TT><<<(unsigned)blocks, 64 * kF32Waves, 0, st>>>(                                                \
       (const float*)qh, (const float*)kh, (const float*)vh, cu_q, cu_k, tile_start, M, Nq, Nk, H, softmax_scale, (int)tiles, \
       (float*)oh, lse, tok.perm, tok.gate, (float*)tok.o)
-    if (D == 64 && Nk >= (int64_t)kF32LongGroup * M) MOGA_FWD_F32(64, 2);
+    if (D == 64 && Nk > kF32ShortCall) MOGA_FWD_F32(64, 2);
     else if (D == 64) MOGA_FWD_F32(64, 1);
     else MOGA_FWD_F32(128, 1);
 #undef MOGA_FWD_F32
