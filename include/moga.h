@@ -209,9 +209,10 @@ int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, 
                                void* ws, size_t ws_bytes, void* stream);
 
 /*
- * The same two with dQ and dK/dV of BF16 in one launch, whose blocks fill each other's last rounds: 5 to 15 % faster in calls of one to
- * ten rounds of blocks.  Calls of many rounds, and given moga_workspace_preferred_bytes(MOGA_OP_ATTN_BWD_JOINT, ...) those of a few long
- * blocks, are launched apart after all, as by the others.  Needed workspace as for the others.
+ * The same two with dQ and dK/dV of BF16 in one launch, whose blocks fill each other's last rounds: over calls of one to ten rounds of blocks
+ * 2 % less time on average, up to 20 % less with short groups.  Calls of ten rounds and more, and given
+ * moga_workspace_preferred_bytes(MOGA_OP_ATTN_BWD_JOINT, ...) those of long groups, are launched apart after all, as by the others, and some of
+ * few rounds as blocks for small groups.  Needed workspace as for the others.
  */
 int moga_group_attn_bwd_joint(const void* d_oh, const void* qh, const void* kh, const void* vh,
                               const void* oh, const float* lse, int dtype,
@@ -258,7 +259,7 @@ void moga_debug_set_small_group_rows(int64_t rows);
 /*
  * The blocks that a BF16 attention call of these sizes (M >= 1) takes with ws_bytes of workspace: blocks = {query rows, 1 if its last
  * round of them is split, key rows, 1 if theirs is}, key rows 0 for a forward.  The moga_fused_* calls: thresholds overridden by 0, and
- * moga_workspace_bytes.  For tests.  Host-only.
+ * moga_workspace_bytes.  MOGA_OP_ATTN_BWD_JOINT: 2 for both splits if dQ and dK/dV run in one launch of the first set.  For tests.  Host-only.
  */
 void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]);
 

@@ -254,10 +254,11 @@ def set_small_group_rows(rows: int) -> None:
 
 
 def attn_blocks(op, Nq, Nk, H, M, ws_bytes):
-    """(query rows, their last round is split, key rows, theirs is split) of the bf16 attention call's blocks; key rows 0: a forward."""
+    """(query rows, their last round is split, key rows, theirs is split) of the bf16 attention call's blocks; key rows 0: a forward; 2 for
+    the splits: OP_ATTN_BWD_JOINT, dQ and dK/dV in one launch of the large-group kernels."""
     out = (ctypes.c_int * 4)()
     load().moga_debug_attn_blocks(op, Nq, Nk, H, M, ws_bytes, out)
-    return out[0], bool(out[1]), out[2], bool(out[3])
+    return tuple(out)
 
 
 def set_spin_limit(polls: int) -> None:

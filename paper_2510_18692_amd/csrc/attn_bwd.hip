@@ -19,7 +19,6 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
-#include <map>
 
 #include "attn_common.h"
 #include "attn_bwd_pipe.h"
@@ -192,73 +191,115 @@ AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
 // -10, 1,700 -12 / -12, 3,200 -12 / -12.  About one round the blocks of 500 equal groups often just miss the first round (+6), those of 650 less so.
 static int64_t joint_small_rows(int64_t N, int H) {
   const int64_t rounds = 100 * N * H / (256 * kCus);   // in hundredths
-  return rounds < 18 ? 8192 : rounds < 50 ? 500 : rounds < 130 ? 650 : rounds < 300 ? 600 : 500;
+  return rounds < 18 ? 8192 : rounds < 50 ? 500 : rounds < 300 ? 650 : 500;
 }
 
-// Blocks of dQ and of dK/dV of up to kMaxCalls calls as one list, longest first, on kCus CUs.
+// Blocks of dQ and of dK/dV of up to kMaxCalls calls as one list, longest first.
 struct BwdSegment {
   int what;          // 2 * call, + 1 for dK/dV
   int64_t blocks;
   double length;     // of a block: products times rows swept
 };
-struct BwdBlocks {
-  int bm, bk;        // query rows of a block, keys
-  double price;      // in the units of large_blocks: three products a pair of rows in dQ, four in dK/dV (whose blocks have half the rows)
-};
-static double list_end(const BwdSegment* seg, int n) {
-  std::map<double, int64_t> free = {{0., kCus}};   // time -> CUs that are free from then on
+struct BwdBlocks { int bm, bk; };   // query rows of a block, keys
+static double list_end(const BwdSegment* seg, int n, int places) {
+  struct { double time; int64_t places; } free[2 * kMaxCalls + 1] = {{0., places}};   // soonest first; a segment adds one at most
+  int count = 1;
   double end = 0;
   for (int i = 0; i < n; ++i)
     for (int64_t left = seg[i].blocks; left > 0;) {
-      const auto f = free.begin();
-      const double t = f->first + seg[i].length;
-      const int64_t k = std::min(left, f->second);
+      const double t = free[0].time + seg[i].length;
+      const int64_t k = std::min(left, free[0].places);
       left -= k;
-      if (k == f->second) free.erase(f);
-      else f->second -= k;
-      free[t] += k;
+      if ((free[0].places -= k) == 0) std::copy(free + 1, free + count--, free);
+      int at = count;
+      while (at > 0 && free[at - 1].time >= t) --at;
+      if (at < count && free[at].time == t) {
+        free[at].places += k;
+      } else {
+        std::copy_backward(free + at, free + count, free + count + 1);
+        free[at] = {t, k};
+        ++count;
+      }
       end = std::max(end, t);
     }
   return end;
 }
-// With equal groups; a block sweeps kStartRows more rows than there are.  Up to 1.2 rounds (of 256 blocks of 256 rows) the price is the end of
-// the list, and the long blocks, of which one may be the whole call's time, have to be a fifth cheaper: 0.33 rounds, groups of 800 iid / Zipf(1.1)
-// rows 51 / 87 us with the short ones and 49 / 118 with the long ones.  Beyond, work per CU and half of a last block, since the blocks get out of
-// step: over 72 calls of 1.2 to 20 rounds 1 % faster than by the list with iid groups, 2.5 % with Zipf's.
-static BwdBlocks bwd_blocks(const SideShape* q, int n, int H) {
+// Price of blocks of bm query rows and bk keys, in the units of large_blocks: three products a pair of rows in dQ, four in dK/dV (whose blocks have
+// half the rows).  With equal groups; a block sweeps kStartRows more rows than there are.  Up to 1.2 rounds (of 256
+// blocks of 256 rows) the end of the list.  Beyond, work per CU and half of a last block, since the blocks get out of step: over 72 calls of 1.2 to
+// 20 rounds 1 % faster than by the list with iid groups, 2.5 % with Zipf's.
+static bool few_rounds(int64_t rows, int H) { return 10 * rows * H < 12 * 256 * kCus; }
+static double bwd_price(const SideShape* q, int n, int H, int bm, int bk, double weight, bool listed, int places) {
+  BwdSegment seg[2 * kMaxCalls];
+  double work = 0;
+  for (int i = 0; i < n; ++i) {
+    const SideShape& c = q[i];
+    const int64_t nk = (c.other + c.M - 1) / c.M, nq = (c.N + c.M - 1) / c.M, tq = (nq + bm - 1) / bm, tk = (nk + bk - 1) / bk;
+    seg[2 * i] = {2 * i, tq * c.M * H, 3 * weight * (nk + kStartRows)};
+    seg[2 * i + 1] = {2 * i + 1, tk * c.M * H, 2 * weight * (nq + kStartRows)};
+    // a group's last block, of two columns a wave
+    work += (tq - (nq - (tq - 1) * bm <= 256 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i].length;
+    work += (tk - (nk - (tk - 1) * bk <= 128 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i + 1].length;
+  }
+  std::stable_sort(seg, seg + 2 * n, [](const BwdSegment& x, const BwdSegment& y) { return x.length > y.length; });
+  return listed ? list_end(seg, 2 * n, places) : work / kCus + seg[2 * n - 1].length / 2;
+}
+// Where the list ends in few rounds the long blocks, of which one may be the whole call's time, have to be a fifth cheaper: 0.33 rounds, groups of
+// 800 iid / Zipf(1.1) rows 51 / 87 us with the short ones and 49 / 118 with the long ones.  With the rows read through perm a seventh (27 of 1,350
+// calls more than 3 % slower than with two launches; with a fifth 35).
+static BwdBlocks bwd_blocks(const SideShape* q, int n, int H, bool gather) {
   int64_t rows = 0;
   for (int i = 0; i < n; ++i) rows += q[i].N;
-  const bool listed = 10 * rows * H < 12 * 256 * kCus;
-  auto cost = [&](int bm, int bk, double weight) {
-    BwdSegment seg[2 * kMaxCalls];
-    double work = 0;
-    for (int i = 0; i < n; ++i) {
-      const SideShape& c = q[i];
-      const int64_t nk = (c.other + c.M - 1) / c.M, nq = (c.N + c.M - 1) / c.M, tq = (nq + bm - 1) / bm, tk = (nk + bk - 1) / bk;
-      seg[2 * i] = {2 * i, tq * c.M * H, 3 * weight * (nk + kStartRows)};
-      seg[2 * i + 1] = {2 * i + 1, tk * c.M * H, 2 * weight * (nq + kStartRows)};
-      // a group's last block, of two columns a wave
-      work += (tq - (nq - (tq - 1) * bm <= 256 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i].length;
-      work += (tk - (nk - (tk - 1) * bk <= 128 ? 1 - 10 / weight : 0)) * c.M * H * seg[2 * i + 1].length;
-    }
-    std::stable_sort(seg, seg + 2 * n, [](const BwdSegment& x, const BwdSegment& y) { return x.length > y.length; });
-    return listed ? list_end(seg, 2 * n) : work / kCus + seg[2 * n - 1].length / 2;
-  };
-  const double few = cost(256, 128, 10), many = cost(384, 192, 13);
-  return few < (listed ? 1.2 : 1.) * many ? BwdBlocks{256, 128, few} : BwdBlocks{384, 192, many};
+  const bool listed = few_rounds(rows, H);
+  const double few = bwd_price(q, n, H, 256, 128, 10, listed, kCus), many = bwd_price(q, n, H, 384, 192, 13, listed, kCus);
+  return few < (!listed ? 1. : gather ? 1.15 : 1.2) * many ? BwdBlocks{256, 128} : BwdBlocks{384, 192};
 }
-// One call whose dQ and dK/dV are better launched apart: few long blocks, which leave CUs idle together and do not with their last rounds split (8,000
-// rows x 3 heads, 1 group 0.357 and 0.283 ms); and where many rounds make a last one little, and one launch takes 0 to 2 % longer (60,000 x 16 in
-// equal groups of 8,000 9.37 and 9.56 ms; 580,320 x 40, 32 groups, step 698 and 705 ms).
-static bool many_rounds(int64_t N, int H, int M) { return N * H >= 16 * 256 * kCus || (N * H >= 7 * 256 * kCus && N >= 8000 * (int64_t)M); }
-static bool bwd_apart(int64_t N, int H, int M, int room) {
-  if (many_rounds(N, H, M)) return true;
-  if (room == 0 || N * H > 4 * 256 * kCus) return false;   // from four rounds on at most 2 %
-  if (use_small_group_kernels(N, M, joint_small_rows(N, H)) || bwd_plan(N, N, H, M, room).small) return false;
-  double pq, pk;
-  const Blocks q = large_blocks(N, N, H, M, 256, 1, room, &pq), k = large_blocks(N, N, H, M, 128, 2, room, &pk);
+
+// How dQ and dK/dV of one call are launched, if the caller lets the call choose: together, as small-group blocks, or apart as by the other
+// entry points (the large kernels with their last rounds split, or the small ones).  Time of what is chosen here over the time apart, 1,100 calls of 0.06 to
+// 18 rounds, groups of 100 to 22,000 rows of equal, iid and Zipf(1.1) sizes: mean 0.981, 16 of the 3,300 above 1.03, the worst 1.13 (always together
+// between four and 16 rounds and by the price of equal groups alone below: 0.971, but 65 of 1,350 above 1.03, to 1.29).
+enum class BwdForm { kApart, kSmall, kTogether };
+// Apart in many rounds, where a last one is little (10 to 18 rounds together: 0.97 to 1.01).
+static bool many_rounds(int64_t N, int H, int M) { return N * H >= 10 * 256 * kCus || (N * H >= 7 * 256 * kCus && N >= 8000 * (int64_t)M); }
+// Long groups, with room to split a round: few blocks, each of them long.  From 2,800 rows on, 0.2 to 8 rounds, together 0.81 to 1.17 with equal groups and to
+// 1.23 with Zipf's (8,000 rows x 3 heads, 1 group 357 us and 283 apart; 24,325 x 4, 5 groups 709 and 663; 45,453 x 4, 16 Zipf groups 2,574 and 2,194).
+constexpr int64_t kLongGroup = 2800;
+// Places of the 256 that count where the end of a list is held against another form's: of 243 to 253 blocks of equal groups a second round starts
+// (6,900 x 3 heads, 3 groups 114 us and 91 as small blocks; 6,800 x 3, 4 groups 89 and 70; 2,603 x 12, 1 group 177 and 148 apart), and routed
+// groups have some blocks more than equal ones (4,900 x 4, 5 groups, 240 blocks if equal: 45 us, iid 59 and 46 as small blocks).
+constexpr int kSurePlaces = 232;
+static bool together_fits(int64_t N, int H, int M) { return grid_fits((max_tiles(N, M, 128) + max_tiles(N, M, 256)) * H + 14, 512); }
+static BwdForm bwd_form(int64_t N, int H, int M, int room) {
+  if (many_rounds(N, H, M) || (room > 0 && N >= kLongGroup * M) || !together_fits(N, H, M)) return BwdForm::kApart;
   const SideShape side = {N, N, M};
-  return (q.split || k.split) && 3 * pq + 2 * pk < 0.95 * bwd_blocks(&side, 1, H).price;
+  const bool listed = few_rounds(N, H);
+  auto price = [&](int bm) { return bwd_price(&side, 1, H, bm, bm / 2, bm == 256 ? 10 : 13, listed, kSurePlaces); };
+  int64_t line = joint_small_rows(N, H);
+  if (N / M >= line && N / M < small_group_rows(N, H, room > 0)) {
+    // Between the lines the small kernels are what runs apart.  They stay up to a quarter of a round with more than five groups (the largest of
+    // Zipf groups, alone on its CUs: 13,228 rows, 10 groups 140 us together, 116 so), and in few rounds where their list ends sooner: a small block
+    // starts for 500 rows and takes 12 per row, on half a CU.  Over 80 calls the two ends are in the proportion of the times to 5 %.
+    bool small = 4 * N * H < 256 * kCus && M > 5;
+    if (!small && listed) {
+      const int64_t rows = (N + M - 1) / M;
+      const BwdSegment seg[2] = {{0, (rows + 127) / 128 * M * H, 36. * (rows + 500)}, {1, (rows + 63) / 64 * M * H, 24. * (rows + 500)}};
+      small = std::min(price(256), price(384)) > 0.95 * list_end(seg, 2, 2 * kCus);
+    }
+    if (small) line = INT64_MAX;
+  }
+  if (use_small_group_kernels(N, M, line)) return BwdForm::kSmall;
+  if (room > 0 && N * H <= 4 * 256 * kCus && !bwd_plan(N, N, H, M, room).small) {   // from four rounds on at most 2 %
+    double pq, pk;
+    const Blocks q = large_blocks(N, N, H, M, 256, 1, room, &pq), k = large_blocks(N, N, H, M, 128, 2, room, &pk);
+    if ((q.split || k.split) && 3 * pq + 2 * pk < 0.95 * price(bwd_blocks(&side, 1, H, false).bm)) return BwdForm::kApart;
+  }
+  return BwdForm::kTogether;
+}
+// The gather-fused call has no small kernels and splits nothing: together 0.89 of the time apart (same calls; mean), up to 1.12 with long groups from half
+// a round on (15,012 x 3, 3 groups 379 us and 338 apart).
+static bool fused_apart(int64_t N, int H, int M) {
+  return many_rounds(N, H, M) || (2 * N * H >= 256 * kCus && N >= kLongGroup * M);
 }
 
 }  // namespace moga
@@ -309,7 +350,7 @@ static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, Bwd
   if (kernels != BwdKernels::kSmall) {
     SideShape q[kMaxCalls];
     for (int i = 0; i < n; ++i) q[i] = {c[i].Nq, c[i].Nk, c[i].M};
-    const BwdBlocks rows = bwd_blocks(q, n, H);
+    const BwdBlocks rows = bwd_blocks(q, n, H, kernels == BwdKernels::kGather);
     bm = rows.bm, bk = rows.bk;
   }
   BwdSegment seg[2 * kMaxCalls];
@@ -371,21 +412,19 @@ static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, Bwd
 
 // Shared launcher.  ts_q / ts_k: NULL (tile lookup inside the kernels, M <= MOGA_MAX_GROUPS) or
 // space for the pre-summed first-tile indices over query rows / key rows (M + 1 ints each).  split: room for
-// the pieces of a last round, if any (dK/dV and dQ use it one after the other; only without ts_q / ts_k).  joint: bf16, dQ and dK/dV in one
-// launch, which needs neither lists nor room (M <= MOGA_MAX_GROUPS).
+// the pieces of a last round, if any (dK/dV and dQ use it one after the other; only without ts_q / ts_k).  form: bf16; together and small
+// need neither lists nor room (M <= MOGA_MAX_GROUPS).
 static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
                            const void* oh, const float* lse, int dtype, int64_t Nq, int64_t Nk, int H, int D,
                            const int32_t* cu_q, const int32_t* cu_k, int32_t* ts_q, int32_t* ts_k,
                            int M, float softmax_scale, void* d_qh, void* d_kh, void* d_vh,
-                           float* delta, const TokenGrads& tok, const SplitRoom& split, bool joint, hipStream_t st) {
+                           float* delta, const TokenGrads& tok, const SplitRoom& split, BwdForm form, hipStream_t st) {
   unsigned short *d_q_tok = (unsigned short*)tok.d_q, *d_k_tok = (unsigned short*)tok.d_k, *d_v_tok = (unsigned short*)tok.d_v;
   const int64_t rows = Nq * (int64_t)H;
   int* status = (int*)((char*)delta + bwd_rows_bytes(Nq, H));
   if (dtype == MOGA_BF16) {
     if (!bf16_rows_ok(Nq, Nk)) return MOGA_ERR_UNSUPPORTED;
-    const bool joint_small = joint && use_small_group_kernels(Nq, M, joint_small_rows(Nq, H));
-    if (joint && !joint_small) {
-      if (!grid_fits(((max_tiles(Nk, M, 128) + max_tiles(Nq, M, 256)) * H + 14), 512)) return MOGA_ERR_UNSUPPORTED;
+    if (form == BwdForm::kTogether) {
       if (!tok.row_constants) launch_delta<16, true>(d_oh, oh, lse, rows, 1.f / softmax_scale, delta, delta + rows, status, st);
       const AttnBwdCall c = {(const unsigned short*)d_oh, (const unsigned short*)qh, (const unsigned short*)kh, (const unsigned short*)vh,
                              delta + rows, delta, cu_q, cu_k, nullptr, nullptr, Nq, Nk, (unsigned short*)d_qh, (unsigned short*)d_kh,
@@ -394,7 +433,7 @@ static int launch_attn_bwd(const void* d_oh, const void* qh, const void* kh, con
     }
     // groups of a few thousand rows or less (the static groups of Section 3.2): 4-wave blocks with a
     // two-slot ring, two blocks per CU, and smaller tiles; the host only knows the mean group size
-    const AttnPlan plan = joint ? AttnPlan{true, {128, false}, {64, false}} : bwd_plan(Nq, Nk, H, M, split.rows);
+    const AttnPlan plan = form == BwdForm::kSmall ? AttnPlan{true, {128, false}, {64, false}} : bwd_plan(Nq, Nk, H, M, split.rows);
     const bool small = plan.small;
     const int bk = plan.k.rows, bm = plan.q.rows;
     const int64_t k_tiles = Nk > 0 ? max_tiles(Nk, M, bk) : 0, q_tiles = max_tiles(Nq, M, bm);
@@ -504,10 +543,10 @@ static int group_attn_bwd(bool joint, const void* d_oh, const void* qh, const vo
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   const SplitRoom room = split_room(ws, need, ws_bytes);
-  const bool together = joint && !(dtype == MOGA_BF16 && bwd_apart(N, H, M, room.rows));
+  const BwdForm form = joint && dtype == MOGA_BF16 ? bwd_form(N, H, M, room.rows) : BwdForm::kApart;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr,
                          nullptr, M, softmax_scale, d_qh, d_kh, d_vh, (float*)ws, TokenGrads{},
-                         together ? SplitRoom{} : room, together, (hipStream_t)stream);
+                         form == BwdForm::kApart ? room : SplitRoom{}, form, (hipStream_t)stream);
 }
 
 static int group_attn_bwd_tokens(bool joint, const void* d_o, const void* qh, const void* kh, const void* vh, const void* oh,
@@ -529,14 +568,14 @@ static int group_attn_bwd_tokens(bool joint, const void* d_o, const void* qh, co
   const size_t need = moga_attn_bwd_ws_bytes(N, H, D, dtype);
   if (!ws || ws_bytes < need) return MOGA_ERR_WORKSPACE;
   const SplitRoom room = split_room(ws, need, ws_bytes);
-  const bool together = joint && !(dtype == MOGA_BF16 && bwd_apart(N, H, M, room.rows));
+  const BwdForm form = joint && dtype == MOGA_BF16 ? bwd_form(N, H, M, room.rows) : BwdForm::kApart;
   float* delta = (float*)ws;
   const RowConstants rc = {lse, 1.f / softmax_scale, delta, delta + N * (int64_t)H, (int*)((char*)ws + bwd_rows_bytes(N, H))};
   const int rows = launch_unpermute_bwd(d_o, oh, dtype, perm, gate, N, H, D, d_oh, d_gate, &rc, (hipStream_t)stream);
   if (rows != MOGA_OK) return rows;
   return launch_attn_bwd(d_oh, qh, kh, vh, oh, lse, dtype, N, N, H, D, cu_seqlens, cu_seqlens, nullptr, nullptr, M,
                          softmax_scale, d_qh, d_kh, d_vh, delta, TokenGrads{d_q, d_k, d_v, perm, true},
-                         together ? SplitRoom{} : room, together, (hipStream_t)stream);
+                         form == BwdForm::kApart ? room : SplitRoom{}, form, (hipStream_t)stream);
 }
 
 extern "C" int moga_group_attn_bwd(
@@ -600,7 +639,7 @@ static int varlen_attn_bwd(const moga_attn_bwd_call& c, int dtype, int H, int D,
   int32_t* ts_k = presum ? ts_q + (c.G + 1) : nullptr;
   return launch_attn_bwd(c.d_oh, c.qh, c.kh, c.vh, c.oh, c.lse, dtype, c.Nq, c.Nk, H, D, c.cu_seqlens_q, c.cu_seqlens_k, ts_q, ts_k, c.G,
                          softmax_scale, c.d_qh, c.d_kh, c.d_vh, (float*)c.ws, TokenGrads{nullptr, nullptr, nullptr, nullptr, row_constants},
-                         presum ? SplitRoom{} : split_room(c.ws, need, c.ws_bytes), false, st);
+                         presum ? SplitRoom{} : split_room(c.ws, need, c.ws_bytes), BwdForm::kApart, st);
 }
 
 extern "C" int moga_varlen_attn_bwd(const void* d_oh, const void* qh, const void* kh, const void* vh,
@@ -697,7 +736,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
   if (!grid_fits((max_tiles(N, M, 128) + max_tiles(N, M, 256)) * H + 14, 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + kPrepassTokens - 1) / kPrepassTokens), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate, status);
-  if (many_rounds(N, H, M)) {
+  if (fused_apart(N, H, M)) {
     const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;
     const unsigned k_blocks = (unsigned)((max_tiles(N, M, keys) * H + 7) / 8 * 8), q_blocks = (unsigned)((max_tiles(N, M, rows_q) * H + 7) / 8 * 8);
 #define MOGA_BWD_DKDV(KK)                                                                                                   \
@@ -729,7 +768,7 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD || op == MOGA_OP_ATTN_BWD_JOINT;
   if (M > MOGA_MAX_GROUPS) return need;
-  if (op == MOGA_OP_ATTN_BWD_JOINT && (N != Nk || !bwd_apart(N, H, M, 384))) return need;
+  if (op == MOGA_OP_ATTN_BWD_JOINT && (N != Nk || bwd_form(N, H, M, 384) != BwdForm::kApart)) return need;
   if (!fwd && !bwd) return need;
   auto plan = [&](int room) { return fwd ? fwd_plan(N, Nk, H, M, room) : bwd_plan(N, Nk, H, M, room); };
   const AttnPlan p = plan(384), q = plan(256);
@@ -741,6 +780,14 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
 extern "C" void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]) {
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const int room = M > MOGA_MAX_GROUPS ? 0 : split_room((void*)256, moga_workspace_bytes(op, Nq, H, 128, M, 0, MOGA_BF16), ws_bytes).rows;
-  const AttnPlan p = fwd ? fwd_plan(Nq, Nk, H, M, room) : bwd_plan(Nq, Nk, H, M, room);
+  const BwdForm form = op == MOGA_OP_ATTN_BWD_JOINT ? bwd_form(Nq, H, M, room) : BwdForm::kApart;
+  AttnPlan p = fwd ? fwd_plan(Nq, Nk, H, M, room) : bwd_plan(Nq, Nk, H, M, room);
+  if (form == BwdForm::kSmall) p = {true, {128, false}, {64, false}};
   blocks[0] = p.q.rows, blocks[1] = p.q.split, blocks[2] = p.k.rows, blocks[3] = p.k.split;
+  if (form == BwdForm::kTogether) {
+    const SideShape side = {Nq, Nq, M};
+    const BwdBlocks b = bwd_blocks(&side, 1, H, false);
+    blocks[0] = b.bm, blocks[2] = b.bk;
+    blocks[1] = blocks[3] = 2;
+  }
 }

@@ -80,3 +80,36 @@ def test_calls_split_with_room_for_short_pieces(large_kernels, N, H, M):
         assert need + room - 512 <= few <= need + room * 3 // 2 + 512
         assert blocks(op, N, H, M, few) == blocks(op, N, H, M, 1 << 40)
     assert blocks(mg.OP_ATTN_FWD, 7000, 4, 2, 256 + 256 * 256 * 130 * 4)[:2] == (256, True)
+
+
+def preferred(op, N, H, M):
+    return mg.load().moga_workspace_preferred_bytes(op, N, N, H, 128, M, 0, mg.MOGA_BF16)
+
+
+SMALL, SHORT, LONG = (128, 0, 64, 0), (256, 2, 128, 2), (384, 2, 192, 2)
+
+
+# dQ and dK/dV of one call: together in one launch of the large kernels, as small blocks, or apart (None: the blocks of the other entry points)
+@pytest.mark.parametrize("N,H,M,took", [
+    (6900, 3, 3, SMALL), (6800, 3, 4, SMALL), (20791, 1, 11, SMALL),   # 243 to 253 large blocks, which took two rounds together
+    (13228, 1, 10, SMALL), (14781, 2, 2, None), (5675, 1, 2, None),    # more than five groups, a quarter of a round; long groups
+    (8000, 3, 1, None), (24325, 4, 5, None), (45453, 4, 16, None),     # long groups, whose last rounds are split
+    (62400, 12, 16, None), (40000, 4, 100, SMALL),                     # ten rounds; the smallest groups
+    (4095, 4, 4, SHORT), (9000, 12, 5, LONG), (20000, 12, 10, LONG), (15000, 40, 16, LONG),
+])
+def test_joint_backward_is_launched_in_its_faster_form(N, H, M, took):
+    apart = blocks(mg.OP_ATTN_BWD, N, H, M, preferred(mg.OP_ATTN_BWD, N, H, M))
+    assert blocks(mg.OP_ATTN_BWD_JOINT, N, H, M, preferred(mg.OP_ATTN_BWD_JOINT, N, H, M)) == (took or apart)
+
+
+def test_joint_backward_takes_the_same_form_with_the_bytes_it_asks_for():
+    for H in (1, 4, 12, 40):
+        for M in (1, 2, 5, 8, 20, 60):
+            for n in range(100, 8400, 150):
+                size = preferred(mg.OP_ATTN_BWD_JOINT, n * M, H, M)
+                need = mg.workspace_bytes(mg.OP_ATTN_BWD_JOINT, n * M, H, 128, M, 0, mg.MOGA_BF16)
+                took = blocks(mg.OP_ATTN_BWD_JOINT, n * M, H, M, 1 << 40)
+                if size > need:   # asked for only if a round is split
+                    assert blocks(mg.OP_ATTN_BWD_JOINT, n * M, H, M, size) == took and 1 in (took[1], took[3]), (H, M, n)
+                else:
+                    assert 1 not in (took[1], took[3]), (H, M, n)
