@@ -299,7 +299,7 @@ static BwdForm bwd_form(int64_t N, int H, int M, int room) {
 // The gather-fused call has no small kernels and splits nothing: together 0.89 of the time apart (same calls; mean), up to 1.12 with long groups from half
 // a round on (15,012 x 3, 3 groups 379 us and 338 apart).
 static bool fused_apart(int64_t N, int H, int M) {
-  return many_rounds(N, H, M) || (2 * N * H >= 256 * kCus && N >= kLongGroup * M);
+  return many_rounds(N, H, M) || (2 * N * H >= 256 * kCus && N >= kLongGroup * M) || !together_fits(N, H, M);
 }
 
 }  // namespace moga
@@ -733,14 +733,15 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
   float* delta = (float*)ws;
   float* lse2 = delta + N * (int64_t)H;
   int* status = (int*)((char*)ws + bwd_rows_bytes(N, H));
-  if (!grid_fits((max_tiles(N, M, 128) + max_tiles(N, M, 256)) * H + 14, 512)) return MOGA_ERR_UNSUPPORTED;
+  const bool apart = fused_apart(N, H, M);
+  const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;   // apart
+  const int64_t k_blocks = (max_tiles(N, M, keys) * H + 7) / 8 * 8, q_blocks = (max_tiles(N, M, rows_q) * H + 7) / 8 * 8;
+  if (apart && !grid_fits(std::max(k_blocks, q_blocks), 512)) return MOGA_ERR_UNSUPPORTED;
   attn_bwd_fused_prepass_kernel<<<(unsigned)((N + kPrepassTokens - 1) / kPrepassTokens), 256, 0, st>>>(
       (const uintx4_t*)d_o, (const uintx4_t*)o, lse, inv_perm, gate, N, H, 1.f / softmax_scale, lse2, delta, d_gate, status);
-  if (fused_apart(N, H, M)) {
-    const int rows_q = query_blocks(N, N, H, M, 0).rows, keys = key_blocks(N, N, H, M, 0).rows;
-    const unsigned k_blocks = (unsigned)((max_tiles(N, M, keys) * H + 7) / 8 * 8), q_blocks = (unsigned)((max_tiles(N, M, rows_q) * H + 7) / 8 * 8);
+  if (apart) {
 #define MOGA_BWD_DKDV(KK)                                                                                                   \
-  attn_bwd_dkdv_ab_kernel<KK, true><<<k_blocks, 512, 0, st>>>(                                                              \
+  attn_bwd_dkdv_ab_kernel<KK, true><<<(unsigned)k_blocks, 512, 0, st>>>(                                                    \
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
       cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_k, (unsigned short*)d_v,               \
       g_spin_limit.load(), status, perm)
@@ -748,7 +749,7 @@ extern "C" int moga_fused_attn_bwd(const void* d_o, const void* q, const void* k
     else MOGA_BWD_DKDV(128);
 #undef MOGA_BWD_DKDV
 #define MOGA_BWD_DQ(RR)                                                                                                     \
-  attn_bwd_dq_pipe_kernel<RR, true><<<q_blocks, 512, 0, st>>>(                                                              \
+  attn_bwd_dq_pipe_kernel<RR, true><<<(unsigned)q_blocks, 512, 0, st>>>(                                                    \
       (const unsigned short*)d_o, (const unsigned short*)q, (const unsigned short*)k, (const unsigned short*)v, lse2, delta, \
       cu_seqlens, cu_seqlens, nullptr, M, N, N, H, softmax_scale, (unsigned short*)d_q, perm)
     if (rows_q == 384) MOGA_BWD_DQ(384);

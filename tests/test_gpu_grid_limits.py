@@ -85,3 +85,26 @@ def test_more_tiles_than_a_grid_holds_are_refused(D, dtype):
     for call in (lambda: mg.moga_varlen_attn_fwd(t, t, t, cu, cu, 0.1), lambda: mg.moga_varlen_attn_bwd(t, t, t, t, t, lse, cu, cu, 0.1)):
         with pytest.raises(mg.MogaError, match="MOGA_ERR_UNSUPPORTED"):
             call()
+
+
+# Both kernels of the gather-fused backward fit a grid each, and not one together: blocks are counted by groups x heads, most of them empty here.
+# By rounds of blocks the call would be launched together (30 tokens) or apart (100)
+@pytest.mark.parametrize("N", [30, 100])
+def test_gather_fused_backward_of_many_heads_and_groups(N):
+    H, M, D = 20000, 256, 128
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v, d_o = (torch.randn((N, H, D), generator=g, device="cuda").bfloat16() for _ in range(4))
+    group = torch.arange(N, device="cuda").int() % 7 * 30
+    gate = torch.rand(N, generator=g, device="cuda") + 0.2
+    pm = mg.moga_permute(group, M)
+    o, lse = mg.moga_fused_attn_fwd(q, k, v, pm["perm"], gate, pm["cu_seqlens"], D ** -0.5)
+    *got, d_gate = mg.moga_fused_attn_bwd(d_o, q, k, v, o, lse, pm["perm"], pm["inv_perm"], gate, pm["cu_seqlens"], D ** -0.5)
+    other = (group[:, None] != group[None, :]).cpu()
+    for h in (0, 7777, H - 1):
+        q64, k64, v64 = (t[:, h].double().cpu().requires_grad_(True) for t in (q, k, v))
+        p = torch.softmax((q64 @ k64.T * D ** -0.5).masked_fill(other, float("-inf")), dim=1)
+        want = torch.autograd.grad(gate.double().cpu()[:, None] * (p @ v64), (q64, k64, v64), d_o[:, h].double().cpu())
+        for x, w in zip(got, want):
+            assert (x[:, h].double().cpu() - w).norm() <= 1e-2 * w.norm()
+    want = sum((a.double() * b.double()).sum((1, 2)) for a, b in zip(d_o.split(2000, 1), o.split(2000, 1))) / gate.double()
+    assert (d_gate.double() - want).norm() <= 1e-4 * want.norm()   # the same products in fp32
