@@ -59,7 +59,8 @@ typedef enum {
   MOGA_OP_BALANCE_LOSS = 5,
   MOGA_OP_VARLEN_ATTN_FWD = 6, /* N = Nq, M = G */
   MOGA_OP_VARLEN_ATTN_BWD = 7, /* N = Nq, M = G */
-  MOGA_OP_ATTN_BWD_JOINT = 8   /* moga_group_attn_bwd_joint, moga_group_attn_bwd_tokens_joint */
+  MOGA_OP_ATTN_BWD_JOINT = 8,  /* moga_group_attn_bwd_joint, moga_group_attn_bwd_tokens_joint */
+  MOGA_OP_ATTN_FWD_CALL = 9    /* one of the calls of moga_varlen_attn_fwd_calls; N = Nq, M = G */
 } moga_op;
 
 /* Human-readable name of a status code (static storage, never NULL). */
@@ -369,7 +370,8 @@ int moga_varlen_attn_bwd_rows(const void* d_oh, const void* qh, const void* kh, 
 /*
  * n independent calls (1 .. MOGA_MAX_CALLS) of moga_varlen_attn_fwd, or of moga_varlen_attn_bwd_rows, of the same dtype, H, D and scale:
  * the branches of Section 3.2's block.  Arguments, checks and results as there (all are checked before anything is launched); the BF16
- * ones run together, so that the blocks of one fill the last round of another, and their last rounds are not split.
+ * ones run together, so that the blocks of one fill the last round of another, and their last rounds are not split.  A forward call of long groups
+ * with moga_workspace_preferred_bytes(MOGA_OP_ATTN_FWD_CALL, ...) runs by itself, as by moga_varlen_attn_fwd.
  */
 typedef struct {
   const void *qh, *kh, *vh;

@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libmoga.so")
 
 MOGA_F32, MOGA_BF16 = 0, 1
 (OP_ROUTE, OP_PERMUTE, OP_ATTN_FWD, OP_ATTN_BWD, OP_ROUTE_BWD, OP_BALANCE_LOSS, OP_VARLEN_ATTN_FWD,
- OP_VARLEN_ATTN_BWD, OP_ATTN_BWD_JOINT) = range(9)
+ OP_VARLEN_ATTN_BWD, OP_ATTN_BWD_JOINT, OP_ATTN_FWD_CALL) = range(10)
 
 _c = ctypes
 _vp, _i64, _i32, _f32, _sz = _c.c_void_p, _c.c_int64, _c.c_int, _c.c_float, _c.c_size_t

@@ -43,7 +43,8 @@ extern "C" size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, i
     case MOGA_OP_ATTN_BWD_JOINT: return moga_attn_bwd_ws_bytes(N, H, D, dtype);
     case MOGA_OP_ROUTE_BWD: return moga_route_bwd_ws_bytes(N, M, d_model);
     case MOGA_OP_BALANCE_LOSS: return moga_balance_ws_bytes(M);
-    case MOGA_OP_VARLEN_ATTN_FWD: return moga_varlen_attn_fwd_ws_bytes(M);
+    case MOGA_OP_VARLEN_ATTN_FWD:
+    case MOGA_OP_ATTN_FWD_CALL: return moga_varlen_attn_fwd_ws_bytes(M);
     case MOGA_OP_VARLEN_ATTN_BWD: return moga_varlen_attn_bwd_ws_bytes(N, H, M);
     default: return 0;
   }

@@ -169,12 +169,15 @@ static int64_t small_group_rows(int64_t Nq, int H, bool room) {
 }
 
 // The same for the calls of one launch, all of them with `rows` queries: a second launch, for the other kernels, costs more than the finer tiles
-// of some give.  Blocks of all three branches, forward and backward, with the large kernels for all against the small ones for groups of less than
-// 300 / 700 / 1,200 rows: 2.6 rounds 0.538 ms and 0.590 / 0.590 / 0.569, 3.4 0.743 and 0.743 / 0.742 / 0.799, 5.1 1.200 and 1.241 / 1.241 /
-// 1.241; groups of 104 queries, 4.3 rounds 0.883 and 0.901, 34 rounds 9.12 and 8.92, 69 rounds 15.5 and 15.25.
+// of some give.  Blocks of three branches from one to eight rounds, over the time of the calls one by one, with the large kernels for all / with the small
+// ones for the windows, mean and range: windows of 4 tokens 1.34 (1.07 to 1.64) / 0.97 (0.88 to 1.08), 6 to 15 1.14 (0.93 to 1.35) / 0.92 (0.82 to 0.97),
+// 15 to 24 1.03 (0.87 to 1.17) / 0.92 (0.81 to 1.06), 24 to 40 0.95 (0.81 to 1.02) / 0.92 (0.80 to 1.06), 40 to 100 0.90 / 0.88, 100 to 300 0.88 / 0.86.  Forward and
+// backward with the large kernels for all against the small ones for groups of less than 300 / 700 / 1,200 rows: 2.6 rounds 0.538 ms and
+// 0.590 / 0.590 / 0.569, 3.4 0.743 and 0.743 / 0.742 / 0.799, 5.1 1.200 and 1.241 / 1.241 / 1.241; groups of 104 queries, 4.3 rounds 0.883 and 0.901,
+// 34 rounds 9.12 and 8.92, 69 rounds 15.5 and 15.25.
 static int64_t calls_small_group_rows(int64_t rows, int H) {
   const int64_t rounds = 100 * rows * H / (256 * kCus);
-  return rounds < 100 ? small_group_rows(rows, H, false) : rounds < 800 ? 0 : 300;
+  return rounds < 100 ? small_group_rows(rows, H, false) : rounds < 800 ? 24 : 300;
 }
 
 AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
@@ -769,6 +772,7 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const bool bwd = op == MOGA_OP_ATTN_BWD || op == MOGA_OP_VARLEN_ATTN_BWD || op == MOGA_OP_ATTN_BWD_JOINT;
   if (M > MOGA_MAX_GROUPS) return need;
+  if (op == MOGA_OP_ATTN_FWD_CALL) return fwd_call_alone(N, H, M) ? moga_workspace_preferred_bytes(MOGA_OP_VARLEN_ATTN_FWD, N, Nk, H, D, M, d_model, dtype) : need;
   if (op == MOGA_OP_ATTN_BWD_JOINT && (N != Nk || bwd_form(N, H, M, 384) != BwdForm::kApart)) return need;
   if (!fwd && !bwd) return need;
   auto plan = [&](int room) { return fwd ? fwd_plan(N, Nk, H, M, room) : bwd_plan(N, Nk, H, M, room); };

@@ -40,11 +40,21 @@ static int64_t small_group_rows(int64_t Nq, int H, bool split) {
   return rounds < 50 ? 5632 : rounds < 100 ? 6144 : rounds < 370 ? 2560 : rounds < 600 ? 1300 : 700;
 }
 
-// The same for the calls of one launch, all of them with `rows` queries (measured for both directions, see attn_bwd.hip).
-static int64_t calls_small_group_rows(int64_t rows, int H) {
+// The same for the calls of one launch, all of them with `rows` queries, the shortest groups with `shortest` rows on average.  From one to eight rounds
+// all take the small kernels unless all have long groups.  Blocks of three branches (windows, frames of 1,560 tokens, routed groups of up to 8,400), over
+// the time of the calls one by one, with the large kernels for all / with the small ones, mean and range: windows of 4 tokens 1.28 (1.10 to 1.43) /
+// 0.91 (0.77 to 1.00), 6 to 15 1.07 (0.85 to 1.24) / 0.86 (0.70 to 0.98), 24 to 40 0.93 (0.74 to 1.05) / 0.85 (0.72 to 0.98), 100 to 300 0.86 (0.70 to
+// 1.05) / 0.85 (0.72 to 0.97), 300 to 1,500 0.90 (0.75 to 1.07) / 0.87 (0.73 to 0.99), longer ones 0.91 (0.86 to 0.94) / 0.93 (0.88 to 0.98).  From
+// eight rounds on windows of less than 300 tokens take them: 4 tokens 0.96 (with the large kernels 1.38), 40 to 100 0.92 (0.94).
+static int64_t calls_small_group_rows(int64_t rows, int H, int64_t shortest) {
   const int64_t rounds = 100 * rows * H / (256 * kCus);
-  return rounds < 100 ? small_group_rows(rows, H, false) : rounds < 800 ? 0 : 300;
+  if (rounds < 100) return small_group_rows(rows, H, false);
+  return rounds < 800 ? (shortest < 1500 ? INT64_MAX : 0) : 300;
 }
+// One of the calls of a launch that runs by itself, with its last round split: long groups, whose few blocks the others are too short to even out.
+// With it in the launch the three took up to 1.42 of the time of the calls one by one (24,960 x 4 heads, 2 groups, windows of 64 tokens 1.25; 99,840 x 1,
+// 4 groups 1.40), with the small kernels for all up to 1.19.  The bound is on its rows and stands for eight rounds of three branches.
+bool fwd_call_alone(int64_t Nq, int H, int G) { return G <= MOGA_MAX_GROUPS && Nq >= 8192 * (int64_t)G && 3 * Nq * H < 8 * 256 * kCus; }
 
 AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room) {
   if (use_small_group_kernels(Nq, M, small_group_rows(Nq, H, room > 0))) return {true, {128, false}, {}};
@@ -242,12 +252,10 @@ static int launch_fwd_calls(const moga_attn_fwd_call* calls, const int* which, i
 extern "C" int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n, int dtype, int H, int D, float softmax_scale,
                                           void* stream) {
   if (!calls || n < 1 || n > MOGA_MAX_CALLS) return MOGA_ERR_INVALID_ARG;
-  int64_t rows = 0;
   int order[kMaxCalls], count = 0;
   for (int i = 0; i < n; ++i) {
     const int bad = check_varlen_fwd(calls[i], dtype, H, D, softmax_scale);
     if (bad) return bad;
-    rows += calls[i].Nq;
     if (calls[i].Nq > 0) order[count++] = i;
   }
   auto one_by_one = [&](const int* first, const int* last) {
@@ -260,19 +268,30 @@ extern "C" int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n
     return rc;
   };
   if (dtype != MOGA_BF16 || count < 2) return one_by_one(order, order + count);
+  int* const first = std::stable_partition(order, order + count, [&](int i) {
+    const moga_attn_fwd_call& c = calls[i];
+    return fwd_call_alone(c.Nq, H, c.G) && split_room(c.ws, moga_varlen_attn_fwd_ws_bytes(c.G), c.ws_bytes).rows > 0;
+  });
+  const int alone = one_by_one(order, first);
+  if (alone != MOGA_OK || order + count - first < 2) return alone != MOGA_OK ? alone : one_by_one(first, order + count);
+  int64_t rows = 0, shortest = INT64_MAX;
+  for (const int* i = first; i != order + count; ++i) {
+    rows += calls[*i].Nq;
+    shortest = std::min(shortest, calls[*i].Nq / calls[*i].G);
+  }
   // longest blocks first, the calls of the large kernels before those of the small ones
-  std::stable_sort(order, order + count, [&](int a, int b) { return calls[a].Nk * calls[b].G > calls[b].Nk * calls[a].G; });
-  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H)); };
-  int* const mid = std::stable_partition(order, order + count, [&](int i) { return !small(i); });
-  const int large = (int)(mid - order);
-  auto launch = [&](const int* first, const int* last, bool few, int rows) {
-    if (first == last) return (int)MOGA_OK;
-    const int rc = launch_fwd_calls(calls, first, (int)(last - first), few, rows, H, softmax_scale, (hipStream_t)stream);
-    return rc == MOGA_ERR_UNSUPPORTED ? one_by_one(first, last) : rc;   // millions of groups: together too many threads for a grid
+  std::stable_sort(first, order + count, [&](int a, int b) { return calls[a].Nk * calls[b].G > calls[b].Nk * calls[a].G; });
+  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H, shortest)); };
+  int* const mid = std::stable_partition(first, order + count, [&](int i) { return !small(i); });
+  const int large = (int)(mid - first);
+  auto launch = [&](const int* from, const int* last, bool few, int block) {
+    if (from == last) return (int)MOGA_OK;
+    const int rc = launch_fwd_calls(calls, from, (int)(last - from), few, block, H, softmax_scale, (hipStream_t)stream);
+    return rc == MOGA_ERR_UNSUPPORTED ? one_by_one(from, last) : rc;   // millions of groups: together too many threads for a grid
   };
   SideShape q[kMaxCalls];
-  for (int i = 0; i < large; ++i) q[i] = {calls[order[i]].Nq, calls[order[i]].Nk, calls[order[i]].G};
+  for (int i = 0; i < large; ++i) q[i] = {calls[first[i]].Nq, calls[first[i]].Nk, calls[first[i]].G};
   const int bm = calls_cost(q, large, H, 256, 256, 10) < calls_cost(q, large, H, 384, 256, 13) ? 256 : 384;
-  const int rc = launch(order, mid, false, bm);
+  const int rc = launch(first, mid, false, bm);
   return rc != MOGA_OK ? rc : launch(mid, order + count, true, 128);
 }

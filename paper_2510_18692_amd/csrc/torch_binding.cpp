@@ -382,7 +382,7 @@ std::vector<std::tuple<Tensor, Tensor>> varlen_attn_fwd_calls(const std::vector<
   const Call call(stream);
   const Tensor& first = std::get<0>(in[0]);
   std::vector<std::tuple<Tensor, Tensor>> out;
-  std::vector<Tensor> ws;
+  std::vector<OptTensor> ws;
   std::vector<moga_attn_fwd_call> c;
   for (const auto& [qh, kh, vh, cu_q, cu_k] : in) {
     require(qh, kh, vh, cu_q, cu_k);
@@ -391,9 +391,9 @@ std::vector<std::tuple<Tensor, Tensor>> varlen_attn_fwd_calls(const std::vector<
                 "calls of one type, number of heads and head size");
     const int64_t H = qh.size(0), Nq = qh.size(1), D = qh.size(2), Nk = kh.size(1), G = cu_q.size(0) - 1;
     out.emplace_back(call.make({H, Nq, D}, qh), call.make({H, Nq}, qh, at::kFloat));
-    ws.push_back(call.workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_FWD, Nq, (int)H, (int)D, (int)G, 0, dt(qh)), qh));
+    ws.push_back(call.attn_workspace(MOGA_OP_ATTN_FWD_CALL, Nq, Nk, H, D, G, qh));
     c.push_back({ptr(qh), ptr(kh), ptr(vh), as<int32_t>(cu_q), as<int32_t>(cu_k), Nq, Nk, (int)G, ptr(std::get<0>(out.back())),
-                 as<float>(std::get<1>(out.back())), ptr(ws.back()), (size_t)ws.back().numel()});
+                 as<float>(std::get<1>(out.back())), ptr(ws.back()), bytes_of(ws.back())});
   }
   check("moga_varlen_attn_fwd_calls", moga_varlen_attn_fwd_calls(c.data(), (int)c.size(), dt(first), (int)first.size(0), (int)first.size(2),
                                                                  (float)scale, call.stream()));
