@@ -263,6 +263,11 @@ void moga_debug_set_small_group_rows(int64_t rows);
  * moga_workspace_bytes.  MOGA_OP_ATTN_BWD_JOINT: 2 for both splits if dQ and dK/dV run in one launch of the first set.  For tests.  Host-only.
  */
 void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]);
+/*
+ * Bit i: of n BF16 calls together (moga_varlen_attn_fwd_calls with op MOGA_OP_VARLEN_ATTN_FWD, else moga_varlen_attn_bwd_rows_calls) call i, with
+ * Nq[i] queries in G[i] groups, takes the second set of kernels.  For tests.  Host-only.
+ */
+int moga_debug_small_calls(int op, int n, const int64_t* Nq, const int* G, int H);
 
 /* Backward of the gather in moga_permute: d_q[perm[j]][h][:] = d_qh[h][j][:] (same for k, v). */
 int moga_permute_bwd(const void* d_qh, const void* d_kh, const void* d_vh, int dtype,

@@ -55,6 +55,7 @@ _SIGNATURES = {
     "moga_attn_bwd_status_offset": (_sz, [_i64, _i32]),
     "moga_debug_set_spin_limit": (None, [_i32]),
     "moga_debug_set_small_group_rows": (None, [_i64]),
+    "moga_debug_small_calls": (_i32, [_i32, _i32, _vp, _vp, _i32]),
     "moga_debug_attn_blocks": (None, [_i32, _i64, _i64, _i32, _i32, _sz, _vp]),
     "moga_permute_bwd": (_i32, [_vp, _vp, _vp, _i32, _vp, _i64, _i32, _i32, _vp, _vp, _vp, _vp]),
     "moga_route_bwd": (_i32, [_vp, _i32, _vp, _vp, _vp, _vp, _vp, _i64, _i32, _i32, _vp, _vp, _vp,
@@ -259,6 +260,13 @@ def attn_blocks(op, Nq, Nk, H, M, ws_bytes):
     out = (ctypes.c_int * 4)()
     load().moga_debug_attn_blocks(op, Nq, Nk, H, M, ws_bytes, out)
     return tuple(out)
+
+
+def small_calls(op, sizes, H):
+    """sizes: (queries, groups) of each of up to three bf16 calls together -> whether it takes the kernels for small groups."""
+    n = len(sizes)
+    bits = load().moga_debug_small_calls(op, n, (ctypes.c_int64 * n)(*(q for q, _ in sizes)), (ctypes.c_int * n)(*(g for _, g in sizes)), H)
+    return tuple(bool(bits >> i & 1) for i in range(n))
 
 
 def set_spin_limit(polls: int) -> None:

@@ -796,3 +796,15 @@ extern "C" void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, in
     blocks[1] = blocks[3] = 2;
   }
 }
+
+extern "C" int moga_debug_small_calls(int op, int n, const int64_t* Nq, const int* G, int H) {
+  int64_t rows = 0, shortest = INT64_MAX;
+  for (int i = 0; i < n; ++i) {
+    rows += Nq[i];
+    shortest = std::min(shortest, Nq[i] / G[i]);
+  }
+  const int64_t line = op == MOGA_OP_VARLEN_ATTN_FWD ? fwd_calls_small_rows(rows, H, shortest) : calls_small_group_rows(rows, H);
+  int small = 0;
+  for (int i = 0; i < n; ++i) small |= use_small_group_kernels(Nq[i], G[i], line) << i;
+  return small;
+}

@@ -332,6 +332,7 @@ struct AttnPlan {
 };
 AttnPlan fwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room);
 AttnPlan bwd_plan(int64_t Nq, int64_t Nk, int H, int M, int room);
+int64_t fwd_calls_small_rows(int64_t rows, int H, int64_t shortest);
 bool fwd_call_alone(int64_t Nq, int H, int G);   // of moga_varlen_attn_fwd_calls: by itself, if its last round can be split
 
 // Matrix products of the bf16 kernels: 16x16x32 (A 16 x 32, B 32 x 16).  Lane l = 16 g + r holds row (A) or

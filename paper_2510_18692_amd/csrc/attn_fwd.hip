@@ -46,7 +46,7 @@ static int64_t small_group_rows(int64_t Nq, int H, bool split) {
 // 0.91 (0.77 to 1.00), 6 to 15 1.07 (0.85 to 1.24) / 0.86 (0.70 to 0.98), 24 to 40 0.93 (0.74 to 1.05) / 0.85 (0.72 to 0.98), 100 to 300 0.86 (0.70 to
 // 1.05) / 0.85 (0.72 to 0.97), 300 to 1,500 0.90 (0.75 to 1.07) / 0.87 (0.73 to 0.99), longer ones 0.91 (0.86 to 0.94) / 0.93 (0.88 to 0.98).  From
 // eight rounds on windows of less than 300 tokens take them: 4 tokens 0.96 (with the large kernels 1.38), 40 to 100 0.92 (0.94).
-static int64_t calls_small_group_rows(int64_t rows, int H, int64_t shortest) {
+int64_t fwd_calls_small_rows(int64_t rows, int H, int64_t shortest) {
   const int64_t rounds = 100 * rows * H / (256 * kCus);
   if (rounds < 100) return small_group_rows(rows, H, false);
   return rounds < 800 ? (shortest < 1500 ? INT64_MAX : 0) : 300;
@@ -281,7 +281,7 @@ extern "C" int moga_varlen_attn_fwd_calls(const moga_attn_fwd_call* calls, int n
   }
   // longest blocks first, the calls of the large kernels before those of the small ones
   std::stable_sort(first, order + count, [&](int a, int b) { return calls[a].Nk * calls[b].G > calls[b].Nk * calls[a].G; });
-  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, calls_small_group_rows(rows, H, shortest)); };
+  auto small = [&](int i) { return use_small_group_kernels(calls[i].Nq, calls[i].G, fwd_calls_small_rows(rows, H, shortest)); };
   int* const mid = std::stable_partition(first, order + count, [&](int i) { return !small(i); });
   const int large = (int)(mid - first);
   auto launch = [&](const int* from, const int* last, bool few, int block) {

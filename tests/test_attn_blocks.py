@@ -113,3 +113,30 @@ def test_joint_backward_takes_the_same_form_with_the_bytes_it_asks_for():
                     assert blocks(mg.OP_ATTN_BWD_JOINT, n * M, H, M, size) == took and 1 in (took[1], took[3]), (H, M, n)
                 else:
                     assert 1 not in (took[1], took[3]), (H, M, n)
+
+
+# (queries, groups) of a block's branches: routed groups, windows, frames.  From one to eight rounds of blocks: forward the small kernels for all if a
+# branch has short groups, backward for windows of a few tokens; from eight on for windows of less than 300
+@pytest.mark.parametrize("T,H,M,window,fwd,bwd", [
+    (3, 12, 5, 4, (True, True, True), (False, True, False)), (3, 12, 5, 16, (True, True, True), (False, True, False)),
+    (3, 12, 5, 30, (True, True, True), (False, False, False)), (6, 12, 10, 195, (True, True, True), (False, False, False)),
+    (6, 12, 10, 780, (True, True, True), (False, False, False)),
+    (10, 12, 5, 4, (False, True, False), (False, True, False)), (10, 12, 5, 390, (False, False, False), (False, False, False)),
+])
+def test_branches_with_small_windows_take_the_small_kernels(T, H, M, window, fwd, bwd):
+    N = 1560 * T
+    sizes = [(N, M), (N, N // window), (N, T)]
+    assert mg.small_calls(mg.OP_VARLEN_ATTN_FWD, sizes, H) == fwd
+    assert mg.small_calls(mg.OP_VARLEN_ATTN_BWD, sizes, H) == bwd
+
+
+def test_long_groups_of_all_branches_take_the_large_kernels():
+    sizes = [(37440, 5), (37440, 12), (37440, 24)]   # 7,488, 3,120 and 1,560 rows
+    for op in (mg.OP_VARLEN_ATTN_FWD, mg.OP_VARLEN_ATTN_BWD):
+        assert mg.small_calls(op, sizes, 3) == (False, False, False)
+
+
+def test_forward_call_of_long_groups_asks_for_room_to_run_by_itself():
+    for N, H, G, alone in ((8300, 3, 1, True), (24960, 4, 2, True), (24960, 4, 8, False), (99840, 12, 1, False)):
+        size = (N, H, 128, G, 0, mg.MOGA_BF16)
+        assert (mg.load().moga_workspace_preferred_bytes(mg.OP_ATTN_FWD_CALL, N, *size) > mg.workspace_bytes(mg.OP_ATTN_FWD_CALL, *size)) == alone

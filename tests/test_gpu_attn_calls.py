@@ -123,40 +123,3 @@ def test_calls_that_are_refused():
         mg.moga_varlen_attn_fwd_calls([ok, (t[:1].contiguous(), t[:1].contiguous(), t[:1].contiguous(), cu, cu)], 0.1)
     with pytest.raises(mg.MogaError):
         mg.moga_varlen_attn_fwd_calls([ok, ok], float("inf"))
-
-
-# From one to eight rounds of blocks: forward the small kernels for all calls if one of them has short groups, backward for windows of a few tokens
-def test_calls_with_small_windows_take_the_small_kernels():
-    H, scale = 12, 128 ** -0.5
-    gen = torch.Generator(device="cuda").manual_seed(3)
-    rnd = lambda n: torch.randn((H, n, 128), generator=gen, device="cuda").bfloat16()
-    dev = lambda t: torch.tensor(t, dtype=torch.int32, device="cuda")
-    calls = [(rnd(sum(q)), rnd(sum(k)), rnd(sum(k)), dev(sums(q)), dev(sums(k))) for q, k in CALLS["windows"]]
-    grads = [rnd(c[0].shape[1]) for c in calls]
-
-    def run(rows_fwd, rows_bwd):
-        try:
-            mg.set_small_group_rows(rows_fwd)
-            fwd = mg.moga_varlen_attn_fwd_calls(calls, scale)
-            mg.set_small_group_rows(rows_bwd)
-            bwd = []
-            for c, (oh, lse), d_o in zip(calls, fixed, grads):
-                n = c[0].shape[1] * H
-                ws = torch.zeros(mg.workspace_bytes(mg.OP_VARLEN_ATTN_BWD, c[0].shape[1], H, 128, len(c[3]) - 1, 0, mg.MOGA_BF16), dtype=torch.uint8, device="cuda")
-                ws[:8 * n].view(torch.float32)[:] = torch.cat([-(d_o.float() * oh.float()).sum(2).flatten(), -lse.flatten() / scale])
-                bwd.append((d_o, *c[:3], oh, lse, *c[3:], ws))
-            return fwd, mg.moga_varlen_attn_bwd_rows_calls(bwd, scale)
-        finally:
-            mg.set_small_group_rows(-1)
-
-    fixed = mg.moga_varlen_attn_fwd_calls(calls, scale)
-    (fwd, bwd), (small, windows) = run(-1, -1), run(1 << 40, 24)
-    for got, want in zip(fwd + bwd, small + windows):
-        for a, b in zip(got, want):
-            assert torch.equal(a, b)
-
-
-def test_forward_call_of_long_groups_asks_for_room_to_run_by_itself():
-    for N, H, G, alone in ((8300, 3, 1, True), (24960, 4, 2, True), (24960, 4, 8, False), (99840, 12, 1, False)):
-        size = (N, H, 128, G, 0, mg.MOGA_BF16)
-        assert (mg.load().moga_workspace_preferred_bytes(mg.OP_ATTN_FWD_CALL, N, *size) > mg.workspace_bytes(mg.OP_ATTN_FWD_CALL, *size)) == alone
