@@ -389,11 +389,12 @@ def moga_merge3_bwd(d_o, a_moga, inv_moga, inv_stga, inv_frame, gate, stream=Non
 
 
 def moga_merge3_bwd_rows(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, lse, softmax_scale, cu_moga, cu_q, n_keys,
-                         cu_frame, stream=None):
+                         cu_frame, stream=None, room=True):
     """moga_merge3_bwd with the row constants of the three attention backwards; `lse`: those of the three branches
-    -> (d_a_moga, d_a_stga, d_a_frame [H, N, D], d_gate f32 [N], three workspaces for moga_varlen_attn_bwd_rows)"""
+    -> (d_a_moga, d_a_stga, d_a_frame [H, N, D], d_gate f32 [N], three workspaces for moga_varlen_attn_bwd_rows).  room: with what a call
+    by itself runs fastest with (34 or 51 MB each, where it splits its last round); calls that run together use what they need."""
     return _nat.merge3_bwd_rows(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, *lse, softmax_scale, cu_moga, cu_q,
-                                n_keys, cu_frame, _st(stream))
+                                n_keys, cu_frame, room, _st(stream))
 
 
 def moga_varlen_attn_bwd_rows(d_oh, qh, kh, vh, oh, lse, cu_seqlens_q, cu_seqlens_k, softmax_scale, ws, stream=None):
@@ -464,17 +465,18 @@ def visual_forward(x, w, q, k, v, softmax_scale, grid, static_index, stream=None
 def visual_backward(fwd, x, w, d_o, softmax_scale, stream=None):
     """Backward of `visual_forward` -> dict(d_q, d_k, d_v [N, H, D], d_w [M, d_model], d_gate [N])."""
     pm, si = fwd["pm"], fwd["si"]
+    # Together the three fill each other's last rounds (2 % at 64 frames x 12 heads, 20 % at 8 x 3).  Of tensors above 2 GiB, whose calls have
+    # hundreds of rounds, one at a time.  Either way the most that is held at once is what the gather below reads and writes, nine gradients of rows
+    # and three of tokens; together that is held from the attention on, with the row constants.
+    together = d_o.numel() * d_o.element_size() <= 2 << 30
     d_m, d_s, d_f, d_gate, ws_m, ws_s, ws_f = moga_merge3_bwd_rows(
         d_o, fwd["a_m"], fwd["a_s"], fwd["a_f"], pm["inv_perm"], si["q_slot"], None, fwd["gate"],
         (fwd["lse_m"], fwd["lse_s"], fwd["lse_f"]), softmax_scale, pm["cu_seqlens"], si["cu_q"], fwd["ks"].shape[1], fwd["cu_f"],
-        stream=stream)
+        stream=stream, room=not together)
     calls = [(d_m, pm["qh"], pm["kh"], pm["vh"], fwd["a_m"], fwd["lse_m"], pm["cu_seqlens"], pm["cu_seqlens"], ws_m),
              (d_s, fwd["qs"], fwd["ks"], fwd["vs"], fwd["a_s"], fwd["lse_s"], si["cu_q"], si["cu_k"], ws_s),
              (d_f, fwd["qf"], fwd["kf"], fwd["vf"], fwd["a_f"], fwd["lse_f"], fwd["cu_f"], fwd["cu_f"], ws_f)]
     del d_m, d_s, d_f, ws_m, ws_s, ws_f
-    # Together the three fill each other's last rounds (2 % at 64 frames x 12 heads, 20 % at 8 x 3).  Of tensors above 2 GiB, whose calls have
-    # hundreds of rounds, one at a time, so that what a call read is free for the next.
-    together = d_o.numel() * d_o.element_size() <= 2 << 30
     grads = []
     while calls:
         n = len(calls) if together else 1

@@ -523,14 +523,16 @@ using Rows3Out = std::tuple<Tensor, Tensor, Tensor, Tensor, Tensor, Tensor, Tens
 Rows3Out merge3_bwd_rows(const Tensor& d_o, const Tensor& a_moga, const Tensor& a_stga, const Tensor& a_frame, const OptTensor& inv_moga,
                          const OptTensor& inv_stga, const OptTensor& inv_frame, const Tensor& gate, const Tensor& lse_moga,
                          const Tensor& lse_stga, const Tensor& lse_frame, double scale, const Tensor& cu_moga, const Tensor& cu_q,
-                         int64_t n_keys, const Tensor& cu_frame, const OptStream& stream) {
+                         int64_t n_keys, const Tensor& cu_frame, bool room, const OptStream& stream) {
   require(d_o, a_moga, a_stga, a_frame, inv_moga, inv_stga, inv_frame, gate, lse_moga, lse_stga, lse_frame, cu_moga, cu_q, cu_frame);
   const Call call(stream);
   need_dims(d_o, 3);
   const int64_t N = d_o.size(0), H = d_o.size(1), D = d_o.size(2);
   Tensor d_m = call.make({H, N, D}, d_o), d_s = call.make({H, N, D}, d_o), d_f = call.make({H, N, D}, d_o), d_gate = call.make({N}, d_o, at::kFloat);
   auto ws = [&](int64_t Nk, const Tensor& cu) {
-    const OptTensor t = call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, N, Nk, H, D, cu.size(0) - 1, d_o);
+    const int64_t G = cu.size(0) - 1;
+    if (!room) return call.workspace(moga_workspace_bytes(MOGA_OP_VARLEN_ATTN_BWD, N, (int)H, (int)D, (int)G, 0, dt(d_o)), d_o);
+    const OptTensor t = call.attn_workspace(MOGA_OP_VARLEN_ATTN_BWD, N, Nk, H, D, G, d_o);
     return t ? *t : call.workspace(0, d_o);   // no rows
   };
   Tensor ws_m = ws(N, cu_moga), ws_s = ws(n_keys, cu_q), ws_f = ws(N, cu_frame);

@@ -144,3 +144,23 @@ def test_three_branch_block_forward_and_backward(dtype, D, H, d_model):
         rl = P.rel_l2(P.to64(bwd["d_w"]), refb["dW"])
         say(f"  dW l2 {rl:.2e}")
         assert rl <= 5e-3
+
+
+# Nine gradients of rows and three more tensors at once, with 8 bytes a row of constants for each branch: no room that calls together do not use
+def test_block_backward_holds_no_more_than_its_gradients():
+    T, H, M = 21, 3, 2
+    N, scale = T * 1560, 128 ** -0.5
+    g = torch.Generator(device="cuda").manual_seed(5)
+    Q, K, V, dO = (torch.randn((N, H, 128), generator=g, device="cuda").bfloat16() for _ in range(4))
+    X, W = torch.randn((N, 256), generator=g, device="cuda").bfloat16(), torch.randn((M, 256), generator=g, device="cuda") * 0.1
+    si = mg.moga_stga_build_index(T, 30, 52, 15, 26, T, [t * 3 // T for t in range(T)])
+    fwd = mg.visual_forward(X, W, Q, K, V, scale, (T, 30, 52), si)
+    torch.cuda.synchronize()
+    held = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    bwd = mg.visual_backward(fwd, X, W, dO, scale)
+    torch.cuda.synchronize()
+    row = H * 256
+    most = (9 + 1) * N * row + 2 * fwd["ks"].shape[1] * row + 3 * (8 * N * H + 4096) + (4 << 20)   # the static branch's keys; the router's workspace
+    assert torch.cuda.max_memory_allocated() - held <= most
+    del bwd
