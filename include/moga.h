@@ -60,7 +60,8 @@ typedef enum {
   MOGA_OP_VARLEN_ATTN_FWD = 6, /* N = Nq, M = G */
   MOGA_OP_VARLEN_ATTN_BWD = 7, /* N = Nq, M = G */
   MOGA_OP_ATTN_BWD_JOINT = 8,  /* moga_group_attn_bwd_joint, moga_group_attn_bwd_tokens_joint */
-  MOGA_OP_ATTN_FWD_CALL = 9    /* one of the calls of moga_varlen_attn_fwd_calls; N = Nq, M = G */
+  MOGA_OP_ATTN_FWD_CALL = 9,   /* one of the calls of moga_varlen_attn_fwd_calls; N = Nq, M = G */
+  MOGA_OP_FUSED_ATTN_BWD = 10  /* moga_fused_attn_bwd (the bytes of MOGA_OP_ATTN_BWD) */
 } moga_op;
 
 /* Human-readable name of a status code (static storage, never NULL). */
@@ -259,8 +260,8 @@ void moga_debug_set_spin_limit(int polls);
 void moga_debug_set_small_group_rows(int64_t rows);
 /*
  * The blocks that a BF16 attention call of these sizes (M >= 1) takes with ws_bytes of workspace: blocks = {query rows, 1 if its last
- * round of them is split, key rows, 1 if theirs is}, key rows 0 for a forward.  The moga_fused_* calls: thresholds overridden by 0, and
- * moga_workspace_bytes.  MOGA_OP_ATTN_BWD_JOINT: 2 for both splits if dQ and dK/dV run in one launch of the first set.  For tests.  Host-only.
+ * round of them is split, key rows, 1 if theirs is}, key rows 0 for a forward.  moga_fused_attn_fwd: MOGA_OP_ATTN_FWD, thresholds overridden by
+ * 0, and moga_workspace_bytes.  MOGA_OP_ATTN_BWD_JOINT, MOGA_OP_FUSED_ATTN_BWD: 2 for both splits if dQ and dK/dV run in one launch of the first set.  For tests.  Host-only.
  */
 void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]);
 /*

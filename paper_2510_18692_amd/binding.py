@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libmoga.so")
 
 MOGA_F32, MOGA_BF16 = 0, 1
 (OP_ROUTE, OP_PERMUTE, OP_ATTN_FWD, OP_ATTN_BWD, OP_ROUTE_BWD, OP_BALANCE_LOSS, OP_VARLEN_ATTN_FWD,
- OP_VARLEN_ATTN_BWD, OP_ATTN_BWD_JOINT, OP_ATTN_FWD_CALL) = range(10)
+ OP_VARLEN_ATTN_BWD, OP_ATTN_BWD_JOINT, OP_ATTN_FWD_CALL, OP_FUSED_ATTN_BWD) = range(11)
 
 _c = ctypes
 _vp, _i64, _i32, _f32, _sz = _c.c_void_p, _c.c_int64, _c.c_int, _c.c_float, _c.c_size_t
@@ -256,7 +256,7 @@ def set_small_group_rows(rows: int) -> None:
 
 def attn_blocks(op, Nq, Nk, H, M, ws_bytes):
     """(query rows, their last round is split, key rows, theirs is split) of the bf16 attention call's blocks; key rows 0: a forward; 2 for
-    the splits: OP_ATTN_BWD_JOINT, dQ and dK/dV in one launch of the large-group kernels."""
+    the splits: OP_ATTN_BWD_JOINT, OP_FUSED_ATTN_BWD, dQ and dK/dV in one launch of the large-group kernels."""
     out = (ctypes.c_int * 4)()
     load().moga_debug_attn_blocks(op, Nq, Nk, H, M, ws_bytes, out)
     return tuple(out)

@@ -40,6 +40,7 @@ extern "C" size_t moga_workspace_bytes(int op, int64_t N, int H, int D, int M, i
   switch (op) {
     case MOGA_OP_PERMUTE: return moga_permute_ws_bytes(N, M);
     case MOGA_OP_ATTN_BWD:
+    case MOGA_OP_FUSED_ATTN_BWD:
     case MOGA_OP_ATTN_BWD_JOINT: return moga_attn_bwd_ws_bytes(N, H, D, dtype);
     case MOGA_OP_ROUTE_BWD: return moga_route_bwd_ws_bytes(N, M, d_model);
     case MOGA_OP_BALANCE_LOSS: return moga_balance_ws_bytes(M);

@@ -785,13 +785,16 @@ extern "C" size_t moga_workspace_preferred_bytes(int op, int64_t N, int64_t Nk, 
 extern "C" void moga_debug_attn_blocks(int op, int64_t Nq, int64_t Nk, int H, int M, size_t ws_bytes, int blocks[4]) {
   const bool fwd = op == MOGA_OP_ATTN_FWD || op == MOGA_OP_VARLEN_ATTN_FWD;
   const int room = M > MOGA_MAX_GROUPS ? 0 : split_room((void*)256, moga_workspace_bytes(op, Nq, H, 128, M, 0, MOGA_BF16), ws_bytes).rows;
-  const BwdForm form = op == MOGA_OP_ATTN_BWD_JOINT ? bwd_form(Nq, H, M, room) : BwdForm::kApart;
+  const bool gather = op == MOGA_OP_FUSED_ATTN_BWD;
+  const BwdForm form = gather ? (fused_apart(Nq, H, M) ? BwdForm::kApart : BwdForm::kTogether)
+                              : op == MOGA_OP_ATTN_BWD_JOINT ? bwd_form(Nq, H, M, room) : BwdForm::kApart;
   AttnPlan p = fwd ? fwd_plan(Nq, Nk, H, M, room) : bwd_plan(Nq, Nk, H, M, room);
   if (form == BwdForm::kSmall) p = {true, {128, false}, {64, false}};
+  if (gather) p = {false, query_blocks(Nq, Nk, H, M, 0), key_blocks(Nq, Nk, H, M, 0)};
   blocks[0] = p.q.rows, blocks[1] = p.q.split, blocks[2] = p.k.rows, blocks[3] = p.k.split;
   if (form == BwdForm::kTogether) {
     const SideShape side = {Nq, Nq, M};
-    const BwdBlocks b = bwd_blocks(&side, 1, H, false);
+    const BwdBlocks b = bwd_blocks(&side, 1, H, gather);
     blocks[0] = b.bm, blocks[2] = b.bk;
     blocks[1] = blocks[3] = 2;
   }
