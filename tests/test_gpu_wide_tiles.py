@@ -26,12 +26,23 @@ def test_forward_at_tile_edges(H):
         mg.set_small_group_rows(-1)
 
 
-# in pieces; with the edges of 192-key tiles too
+# in one launch, which the binding chooses for these, and apart in pieces; with the edges of 192-key tiles too
+@pytest.mark.parametrize("pieces", [False, True], ids=["together", "pieces"])
 @pytest.mark.parametrize("more", [[], [31, 33, 63, 65, 96, 143, 144, 145, 191, 192, 193, 320, 321]], ids=["rows", "rows and keys"])
-def test_backward_at_tile_edges(more):
+def test_backward_at_tile_edges(more, pieces):
+    sizes = SIZES + more
     mg.set_small_group_rows(0)
     try:
-        tb.test_group_attention_backward_matches_oracle(SIZES + more, 2, 128, "bf16")
+        if pieces:
+            took, got, ref = backward_at_edges(sizes, 2, True)
+            assert took[1] == took[3] == 1
+            for name, a, b in zip(("dQ", "dK", "dV"), got, ref):
+                tb.check(P.unhat(a), b, name, "bf16")
+        else:
+            size = (sum(sizes), 2, 128, len(sizes), 0, mg.MOGA_BF16)
+            ws = mg.load().moga_workspace_preferred_bytes(mg.OP_ATTN_BWD_JOINT, size[0], *size)
+            assert mg.attn_blocks(mg.OP_ATTN_BWD_JOINT, size[0], size[0], 2, len(sizes), ws)[1] == 2
+            tb.test_group_attention_backward_matches_oracle(sizes, 2, 128, "bf16")
     finally:
         mg.set_small_group_rows(-1)
 
@@ -97,7 +108,8 @@ def test_backward_with_every_block_size(H, room, blocks):
         tb.check(P.unhat(a), b, name, "bf16")
 
 
-# token-order rows gathered by the kernels: the blocks of a call that does not split
+# token-order rows gathered by the kernels: forward blocks of either size that do not split; backward in one launch (both forms:
+# test_gpu_fused_forms.py)
 @pytest.mark.parametrize("H", [1, 5, 7, 9])
 def test_gather_fused_calls_with_every_block_size(H):
     print(f"fused H={H}", flush=True)
