@@ -901,7 +901,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_kernel(
 // Several calls in one launch: the blocks of dQ and of dK/dV of each are a segment of the grid, from first[s] on (a multiple of 8), in an order
 // that the host chooses: longest blocks first (by product, or shortest first, up to 24 % slower).  The branches of Section 3.2's block, whose last
 // rounds are short blocks of other calls instead of pieces: attention backward of 8 frames x 3 heads 0.41 -> 0.27 ms, whole block forward and
-// backward 2 x 16 0.59 -> 0.53, 8 x 3 0.98 -> 0.78, 11 x 12 3.93 -> 3.48, 5 x 40 2.72 -> 2.57, 21 x 12 8.67 -> 8.58, 64 x 40 75.9 -> 74.9.
+// backward 2 x 16 0.60 -> 0.46, 8 x 3 0.66 -> 0.51, 11 x 12 2.47 -> 2.22, 5 x 40 3.50 -> 3.15, 30 x 12 9.93 -> 9.64, 21 x 12 with longer groups
+// 8.73 -> 8.54; 64 x 40 75.9 and 75.6, within what two runs of one side differ by.
 struct AttnBwdCall {
   const unsigned short *d_oh, *qh, *kh, *vh;
   const float *neg_lse_over_scale, *neg_delta;

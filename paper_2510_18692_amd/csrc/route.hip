@@ -492,7 +492,7 @@ __global__ __launch_bounds__(256) void route_bwd_dw_partial_kernel(
         partial[((int64_t)split * M + j0 + j) * d + c] = (acc[j] + s_acc[0][j][lane]) + (s_acc[1][j][lane] + s_acc[2][j][lane]);
 }
 
-// dW of up to some ten thousand tokens (where the matrix-core path below applies): a block takes 64 columns and a run of tokens, its
+// dW of up to 65,536 tokens (where the matrix-core path below applies; route_bwd_few_plan has the lines): a block takes 64 columns and a run of tokens, its
 // sixteen waves every sixteenth 16 of them, and they are added through LDS at the end; the sums of several blocks by
 // route_bwd_dw_reduce_kernel.  dr is made in registers, in two bf16 limbs as in route_bwd_dr_pack_kernel, as the A operand (groups x
 // tokens) of the 32x32x16 matrix instruction; X is the B operand: a lane loads columns 2 r and 2 r + 1 of eight tokens, one column for

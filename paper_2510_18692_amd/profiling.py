@@ -304,7 +304,7 @@ def write_block(args):
 
 Command (run from the repository root on one MI355X):
 
-    rocprofv3 --kernel-trace --stats -d gpurun_out/prof_block -o blk --output-format csv -- python3 bench.py --block --steps {line.get('steps')} --warmup {line.get('warmup')}
+    rocprofv3 --kernel-trace --stats -d gpurun_out/prof_block -o blk --output-format csv -- python3 bench.py --block --workload {args.workload} --steps {line.get('steps')} --warmup {line.get('warmup')}
     python -m paper_2510_18692_amd.profiling block ...   (writes this file)
 
 | kernel | calls | avg ms | total ms | % of GPU time |
@@ -313,8 +313,8 @@ Command (run from the repository root on one MI355X):
 
 bench.py line of the same run: {line['ms_per_step']} ms per pass, {line['value']} effective TFLOP/s over all three branches.
 
-Attention kernels of the last pass in launch order (forward: MoGA, spatial-temporal, per-frame; then the backward
-of each branch, dK/dV before dQ), ms:
+Attention kernels of the last pass in launch order (forward: the three branches in one launch; backward: dK/dV of the three, then dQ, or, of
+tensors above 2 GiB, both for MoGA, the spatial-temporal and the per-frame branch in turn), ms:
 
 """ + "\n".join(f"- {k}: {ms:.2f}" for k, ms in last) + "\n"
     open(args.out, "w").write(txt)
@@ -480,6 +480,7 @@ def main():
     b.add_argument("--out", required=True)
     b.set_defaults(fn=write_counters)
     c = sub.add_parser("block")
+    c.add_argument("--workload", default="C4b")
     c.add_argument("--stats", required=True)
     c.add_argument("--trace", required=True)
     c.add_argument("--bench-log", required=True)
