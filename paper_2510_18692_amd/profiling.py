@@ -178,7 +178,7 @@ def write_layer(args):
         ms = calls.get(c, {}).get("ms")
         rate = f"{b / ms / 1e6:.0f} GB/s over {ms:.2f} ms" if ms else "-"
         ctab.append(f"| {c} | {b / 1e9:.2f} GB | {rate} |")
-    cmd = ("rocprofv3 --pmc {c} --kernel-trace -d gpurun_out/pmc_{n} -o {n} --output-format csv -- "
+    cmd = ("rocprofv3 --pmc {c} --kernel-trace -d out/pmc_{n} -o {n} --output-format csv -- "
            f"python3 bench.py --workload {wl} --steps 1 --warmup 0 --no-cpu-baseline --no-measured-peaks --calibrate-copy")
     txt = f"""# HBM traffic per kernel launch (rocprofv3 PMC), workload {wl}
 
@@ -214,7 +214,7 @@ Per C-ABI call (bench.py reads this table for `roofline.traffic`; rates use the 
 
 Command (run from the repository root on one MI355X):
 
-    rocprofv3 --kernel-trace --stats -d gpurun_out/prof_{wl} -o {wl} --output-format csv -- python3 bench.py --workload {wl} --steps {line.get('steps')} --warmup {line.get('warmup')} --no-cpu-baseline
+    rocprofv3 --kernel-trace --stats -d out/prof_{wl} -o {wl} --output-format csv -- python3 bench.py --workload {wl} --steps {line.get('steps')} --warmup {line.get('warmup')} --no-cpu-baseline
 
 {steps} launches of every kernel (warm-up and timed steps).  Library kernels only (torch's input-generation kernels omitted):
 
@@ -270,7 +270,7 @@ def write_counters(args):
         {c for d in read_counters(p).values() for c in d})) for i, p in enumerate(args.csv))
     txt = f"""# MFMA and LDS counters of the matrix-core kernels (rocprofv3 PMC), workload {args.workload}
 
-Commands (one run per counter set, each `timeout -s KILL 300 rocprofv3 --pmc <set> --kernel-trace -d gpurun_out/<dir>
+Commands (one run per counter set, each `timeout -s KILL 300 rocprofv3 --pmc <set> --kernel-trace -d out/<dir>
 -o <name> --output-format csv -- python3 bench.py --workload {args.workload} --steps 1 --warmup 0 --no-cpu-baseline
 --no-measured-peaks`):
 
@@ -304,7 +304,7 @@ def write_block(args):
 
 Command (run from the repository root on one MI355X):
 
-    rocprofv3 --kernel-trace --stats -d gpurun_out/prof_block -o blk --output-format csv -- python3 bench.py --block --workload {args.workload} --steps {line.get('steps')} --warmup {line.get('warmup')}
+    rocprofv3 --kernel-trace --stats -d out/prof_block -o blk --output-format csv -- python3 bench.py --block --workload {args.workload} --steps {line.get('steps')} --warmup {line.get('warmup')}
     python -m paper_2510_18692_amd.profiling block ...   (writes this file)
 
 | kernel | calls | avg ms | total ms | % of GPU time |
@@ -356,8 +356,8 @@ def write_power(args):
 Commands (from the repository root on one MI355X; the second run clears Q, K, V and dO after they are drawn, so
 routing, group sizes, grids and every instruction executed are identical, only the switching activity differs):
 
-    rocprofv3 --pmc GRBM_GUI_ACTIVE SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES --kernel-trace -d gpurun_out/pmc_rand -o rand --output-format csv -- python3 bench.py --workload {args.workload} --steps 2 --warmup 1 --no-cpu-baseline
-    rocprofv3 --pmc GRBM_GUI_ACTIVE SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES --kernel-trace -d gpurun_out/pmc_zero -o zero --output-format csv -- python3 bench.py --workload {args.workload} --steps 2 --warmup 1 --values zeros --no-cpu-baseline
+    rocprofv3 --pmc GRBM_GUI_ACTIVE SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES --kernel-trace -d out/pmc_rand -o rand --output-format csv -- python3 bench.py --workload {args.workload} --steps 2 --warmup 1 --no-cpu-baseline
+    rocprofv3 --pmc GRBM_GUI_ACTIVE SQ_BUSY_CU_CYCLES SQ_VALU_MFMA_BUSY_CYCLES --kernel-trace -d out/pmc_zero -o zero --output-format csv -- python3 bench.py --workload {args.workload} --steps 2 --warmup 1 --values zeros --no-cpu-baseline
     python -m paper_2510_18692_amd.profiling power ...   (writes this file)
 
 | kernel | random: ms | clock GHz | MFMA busy | zeros: ms | clock GHz | MFMA busy | time ratio |
