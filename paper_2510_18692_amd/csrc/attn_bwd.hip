@@ -259,9 +259,10 @@ static BwdBlocks bwd_blocks(const SideShape* q, int n, int H, bool gather) {
 }
 
 // How dQ and dK/dV of one call are launched, if the caller lets the call choose: together, as small-group blocks, or apart as by the other
-// entry points (the large kernels with their last rounds split, or the small ones).  Time of what is chosen here over the time apart, 1,100 calls of 0.06 to
-// 18 rounds, groups of 100 to 22,000 rows of equal, iid and Zipf(1.1) sizes: mean 0.981, 16 of the 3,300 above 1.03, the worst 1.13 (always together
-// between four and 16 rounds and by the price of equal groups alone below: 0.971, but 65 of 1,350 above 1.03, to 1.29).
+// entry points (the large kernels with their last rounds split, or the small ones).  Time of what is chosen here over the time apart, 420 calls of 0.1 to 14
+// rounds, groups of 100 to 20,000 rows of equal, iid and Zipf(1.1) sizes: mean 0.985, 0.987 and 0.980, 8 of the 1,260 above 1.03, the worst with 4 heads and many
+// Zipf groups, whose largest decides when the list ends (20,936 rows, 32 groups 1.37; 45,758, 20 groups 1.21; others to 1.12).  Always together
+// between four and 16 rounds and by the price of equal groups alone below: mean 0.971, but 65 of 1,350 above 1.03, with equal groups to 1.29.
 enum class BwdForm { kApart, kSmall, kTogether };
 // Apart in many rounds, where a last one is little (10 to 18 rounds together: 0.97 to 1.01).
 static bool many_rounds(int64_t N, int H, int M) { return N * H >= 10 * 256 * kCus || (N * H >= 7 * 256 * kCus && N >= 8000 * (int64_t)M); }
@@ -299,7 +300,7 @@ static BwdForm bwd_form(int64_t N, int H, int M, int room) {
   }
   return BwdForm::kTogether;
 }
-// The gather-fused call has no small kernels and splits nothing: together 0.89 of the time apart (same calls; mean), up to 1.12 with long groups from half
+// The gather-fused call has no small kernels and splits nothing: together 0.82 to 0.89 of the time apart (means of four sets of calls), up to 1.12 with long groups from half
 // a round on (15,012 x 3, 3 groups 379 us and 338 apart).
 static bool fused_apart(int64_t N, int H, int M) {
   return many_rounds(N, H, M) || (2 * N * H >= 256 * kCus && N >= kLongGroup * M) || !together_fits(N, H, M);
