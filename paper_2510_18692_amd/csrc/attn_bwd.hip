@@ -388,6 +388,11 @@ static int launch_bwd_calls(const AttnBwdCall* c, int32_t* const* ts, int n, Bwd
   const int mid = n > 1 && kernels == BwdKernels::kLarge && rows * H >= 12 * 256 * kCus
                       ? (int)(std::stable_partition(seg, seg + segments, [](const BwdSegment& x) { return (x.what & 1) != 0; }) - seg) : segments;
   if ((mid > 0 && grid(0, mid) == 0) || (mid < segments && grid(mid, segments) == 0)) return MOGA_ERR_UNSUPPORTED;
+  if (n == 1 && segments == 2 && c[0].M <= MOGA_MAX_GROUPS) {
+    const bool keys = seg[0].what & 1;
+    a.rows0 = keys ? bk : bm;
+    a.sure = (int)(((keys ? c[0].Nk : c[0].Nq) + a.rows0 - 1) / a.rows0 * H);
+  }
   for (int i = 0; i < n; ++i)
     if (c[i].M > MOGA_MAX_GROUPS) {
       int32_t *ts_q = ts[i], *ts_k = ts_q + (c[i].M + 1);

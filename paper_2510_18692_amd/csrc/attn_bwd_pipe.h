@@ -914,16 +914,29 @@ struct AttnBwdCall {
   int* status;
   int M;
 };
+// The host sizes a segment for the most tiles that its groups can have, so blocks without a tile lie behind its real ones.  Between the two segments
+// of a call by itself they cost a round: an XCD deals its blocks to its four shader engines of eight CUs in turn, whether they have work or not, and
+// with the turn shifted one engine gets a ninth block while another keeps a CU free.  There the second segment starts where the tiles of the first
+// really end (rounded up to 8): 243 blocks (2,304 rows x 9 heads) 115 us -> 84, 252 (1,536 x 14) 82 -> 62, 253 (1,920 x 11) 98 -> 74; 240 (2,560 x 8)
+// 90 and 91, 285 sets of groups of 0.15 to 9 rounds 0.75 to 1.04, mean 0.995.
 struct AttnBwdCalls {
   AttnBwdCall c[kMaxCalls];
   int first[2 * kMaxCalls];   // INT_MAX: none
   int what[2 * kMaxCalls];    // 2 * call, + 1 for dK/dV
+  int rows0, sure;            // one call: rows of a tile of the first segment, blocks that it has at least; else 0
 };
-__device__ __forceinline__ int segment_of_block(const AttnBwdCalls& calls, int block) {
+struct BwdPlace { int segment, block; };
+__device__ __forceinline__ BwdPlace place_of_block(const AttnBwdCalls& calls, int H, int block) {
+  if (calls.rows0 > 0) {
+    if (block < calls.sure) return {0, block};
+    const AttnBwdCall& c = calls.c[0];
+    const int tiles = (max(count_tiles(calls.what[0] & 1 ? c.cu_k : c.cu_q, c.M, calls.rows0) * H, calls.sure) + 7) & ~7;
+    return block < tiles ? BwdPlace{0, block} : BwdPlace{1, block - tiles};
+  }
   int s = 0;
 #pragma unroll
   for (int k = 1; k < 2 * kMaxCalls; ++k) s += block >= calls.first[k];
-  return s;
+  return {s, block - calls.first[s]};
 }
 template <int KEYS, int ROWS, bool GATHER>
 __global__ __launch_bounds__(512, 1) void attn_bwd_calls_kernel(AttnBwdCalls calls, int H, float scale, int spin_limit) {
@@ -931,7 +944,8 @@ __global__ __launch_bounds__(512, 1) void attn_bwd_calls_kernel(AttnBwdCalls cal
     DqLds<4, GATHER> dq;
     DkdvLds<4, 4, KEYS / 64, GATHER> dkdv;
   } lds;
-  const int s = segment_of_block(calls, blockIdx.x), what = calls.what[s], block = blockIdx.x - calls.first[s];
+  const BwdPlace at = place_of_block(calls, H, blockIdx.x);
+  const int what = calls.what[at.segment], block = at.block;
   const AttnBwdCall& c = calls.c[what >> 1];
   if (what & 1)
     attn_bwd_dkdv_block<GATHER, 4, 4, KEYS / 64, false>(lds.dkdv, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q,
@@ -946,7 +960,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_small_calls_kernel(AttnBwdCal
     DqLds<2, false> dq;
     DkdvLds<2, 2, 2, false> dkdv;
   } lds;
-  const int s = segment_of_block(calls, blockIdx.x), what = calls.what[s], block = blockIdx.x - calls.first[s];
+  const BwdPlace at = place_of_block(calls, H, blockIdx.x);
+  const int what = calls.what[at.segment], block = at.block;
   const AttnBwdCall& c = calls.c[what >> 1];
   if (what & 1)
     attn_bwd_dkdv_block<false, 2, 2, 2, false>(lds.dkdv, block, c.d_oh, c.qh, c.kh, c.vh, c.neg_lse_over_scale, c.neg_delta, c.cu_q, c.cu_k,

@@ -78,8 +78,10 @@ def test_calls_together(name, small_rows, dtype):
 
 
 # one launch for dQ and dK/dV against the two of the call with a workspace of its own: no round is split, so only the small-group kernels and
-# the large ones differ in their bits
-@pytest.mark.parametrize("sizes,H", [([300, 0, 77], 3), ([1], 1), ([900, 1300, 2100, 5], 4), ([640] * 9, 12), ([1536] * 4, 16), ([3000], 1)])
+# the large ones differ in their bits.  The tiles of the first product end before, at and after the blocks that it has for sure, and far before
+# those that the host counts (empty groups)
+@pytest.mark.parametrize("sizes,H", [([300, 0, 77], 3), ([1], 1), ([900, 1300, 2100, 5], 4), ([640] * 9, 12), ([1536] * 4, 16), ([3000], 1),
+                                     ([1536] + [0] * 60, 14), ([0] * 70 + [1, 129, 257] + [0] * 30, 3), ([1] * 255 + [900], 1), ([2048], 8)])
 @pytest.mark.parametrize("small_rows", [0, 1 << 40])
 def test_one_launch_gives_the_bits_of_two(sizes, H, small_rows):
     gen = torch.Generator(device="cuda").manual_seed(H)
