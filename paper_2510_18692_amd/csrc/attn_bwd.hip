@@ -300,11 +300,10 @@ static BwdForm bwd_form(int64_t N, int H, int M, int room) {
   }
   return BwdForm::kTogether;
 }
-// The gather-fused call has no small kernels and splits nothing: together 0.82 to 0.89 of the time apart (means of four sets of calls), up to 1.12 with long groups from half
-// a round on (15,012 x 3, 3 groups 379 us and 338 apart).
-static bool fused_apart(int64_t N, int H, int M) {
-  return many_rounds(N, H, M) || (2 * N * H >= 256 * kCus && N >= kLongGroup * M) || !together_fits(N, H, M);
-}
+// The gather-fused call has no small kernels and splits nothing: together 0.89 of the time apart over 1,440 sets of groups of 0.15 to 9 rounds, 49 of them above 1.03, to 1.16
+// (48,188 rows x 2 heads, 15 Zipf groups).  No line at long groups: apart from 2,800 rows and half a round on, the mean is 0.906 (15 above 1.03), and two
+// groups of 5,777 rows x 12 and five of 7,374 x 3 take 6 % longer than together.
+static bool fused_apart(int64_t N, int H, int M) { return many_rounds(N, H, M) || !together_fits(N, H, M); }
 
 }  // namespace moga
 
