@@ -212,7 +212,7 @@ int moga_group_attn_bwd_tokens(const void* d_o, const void* qh, const void* kh, 
 
 /*
  * The same two with dQ and dK/dV of BF16 in one launch, whose blocks fill each other's last rounds: over calls of one to ten rounds of blocks
- * 2 % less time on average, 6 % less where groups of 650 to 2,500 rows run together.  Calls of ten rounds and more, and given
+ * 3 % less time on average, 7 % less where groups of 650 to 2,500 rows run together.  Calls of ten rounds and more, and given
  * moga_workspace_preferred_bytes(MOGA_OP_ATTN_BWD_JOINT, ...) those of long groups, are launched apart after all, as by the others, and some of
  * few rounds as blocks for small groups.  Needed workspace as for the others.
  */

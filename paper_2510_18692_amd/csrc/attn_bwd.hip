@@ -259,26 +259,28 @@ static BwdBlocks bwd_blocks(const SideShape* q, int n, int H, bool gather) {
 }
 
 // How dQ and dK/dV of one call are launched, if the caller lets the call choose: together, as small-group blocks, or apart as by the other
-// entry points (the large kernels with their last rounds split, or the small ones).  Time of what is chosen here over the time apart, 420 calls of 0.1 to 14
-// rounds, groups of 100 to 20,000 rows of equal, iid and Zipf(1.1) sizes: mean 0.985, 0.987 and 0.980, 8 of the 1,260 above 1.03, the worst with 4 heads and many
-// Zipf groups, whose largest decides when the list ends (20,936 rows, 32 groups 1.37; 45,758, 20 groups 1.21; others to 1.12).  Always together
-// between four and 16 rounds and by the price of equal groups alone below: mean 0.971, but 65 of 1,350 above 1.03, with equal groups to 1.29.
+// entry points (the large kernels with their last rounds split, or the small ones).  Time of what is chosen here over the time apart, 730 calls of 0.1 to 14
+// rounds, groups of 100 to 20,000 rows of equal, iid and Zipf(1.1) sizes: mean 0.975, 37 of the 2,190 above 1.03, the worst
+// with few or many Zipf groups, whose largest decides when the list ends (24,059 rows x 4 heads, 20 groups 1.20; 12,364 x 1, 5 groups 1.19).  Always together
+// between four and 16 rounds and by the price of equal groups alone below: 65 of 1,350 above 1.03, with equal groups to 1.29.
 enum class BwdForm { kApart, kSmall, kTogether };
 // Apart in many rounds, where a last one is little (10 to 18 rounds together: 0.97 to 1.01).
 static bool many_rounds(int64_t N, int H, int M) { return N * H >= 10 * 256 * kCus || (N * H >= 7 * 256 * kCus && N >= 8000 * (int64_t)M); }
-// Long groups, with room to split a round: few blocks, each of them long.  From 2,800 rows on, 0.2 to 8 rounds, together 0.81 to 1.17 with equal groups and to
-// 1.23 with Zipf's (8,000 rows x 3 heads, 1 group 357 us and 283 apart; 24,325 x 4, 5 groups 709 and 663; 45,453 x 4, 16 Zipf groups 2,574 and 2,194).
-constexpr int64_t kLongGroup = 2800;
-// Places of the 256 that count where the end of a list is held against another form's: of 243 to 253 blocks of equal groups a second round starts
-// (6,900 x 3 heads, 3 groups 114 us and 91 as small blocks; 6,800 x 3, 4 groups 89 and 70; 2,603 x 12, 1 group 177 and 148 apart), and routed
-// groups have some blocks more than equal ones (4,900 x 4, 5 groups, 240 blocks if equal: 45 us, iid 59 and 46 as small blocks).
-constexpr int kSurePlaces = 232;
+// Long groups, with room to split a round: few blocks, each of them long.  Together 0.83 to 1.14 of the time apart from 3,400 rows on and 0.15 to three rounds,
+// 67 of 231 sets above 1.03 (up to a fifth of a round the small-group kernels are the others, from 2,800 rows on); from three to seven rounds 0.90 to 1.04
+// (3 of 54) with up to 8,000 rows, 0.89 to 1.06 (8 of 111) with more.
+static bool long_groups(int64_t N, int H, int M) {
+  return N >= (5 * N * H < 256 * kCus ? 2800 : N * H < 3 * 256 * kCus ? 3400 : 8000) * (int64_t)M;
+}
+// Places of the 256 that count where the end of a list is held against small blocks: routed groups have some blocks more than equal ones (4,900 x 4,
+// 5 groups, 240 blocks if equal: 45 us, iid 59 and 46 as small blocks), and the first of the two kinds is rounded up to 8.
+constexpr int kSurePlaces = 240;
 static bool together_fits(int64_t N, int H, int M) { return grid_fits((max_tiles(N, M, 128) + max_tiles(N, M, 256)) * H + 14, 512); }
 static BwdForm bwd_form(int64_t N, int H, int M, int room) {
-  if (many_rounds(N, H, M) || (room > 0 && N >= kLongGroup * M) || !together_fits(N, H, M)) return BwdForm::kApart;
+  if (many_rounds(N, H, M) || (room > 0 && long_groups(N, H, M)) || !together_fits(N, H, M)) return BwdForm::kApart;
   const SideShape side = {N, N, M};
   const bool listed = few_rounds(N, H);
-  auto price = [&](int bm) { return bwd_price(&side, 1, H, bm, bm / 2, bm == 256 ? 10 : 13, listed, kSurePlaces); };
+  auto price = [&](int bm, int places) { return bwd_price(&side, 1, H, bm, bm / 2, bm == 256 ? 10 : 13, listed, places); };
   int64_t line = joint_small_rows(N, H);
   if (N / M >= line && N / M < small_group_rows(N, H, room > 0)) {
     // Between the lines the small kernels are what runs apart.  They stay up to a quarter of a round with more than five groups (the largest of
@@ -288,7 +290,7 @@ static BwdForm bwd_form(int64_t N, int H, int M, int room) {
     if (!small && listed) {
       const int64_t rows = (N + M - 1) / M;
       const BwdSegment seg[2] = {{0, (rows + 127) / 128 * M * H, 36. * (rows + 500)}, {1, (rows + 63) / 64 * M * H, 24. * (rows + 500)}};
-      small = std::min(price(256), price(384)) > 0.95 * list_end(seg, 2, 2 * kCus);
+      small = std::min(price(256, kSurePlaces), price(384, kSurePlaces)) > 0.95 * list_end(seg, 2, 2 * kCus);
     }
     if (small) line = INT64_MAX;
   }
@@ -296,7 +298,7 @@ static BwdForm bwd_form(int64_t N, int H, int M, int room) {
   if (room > 0 && N * H <= 4 * 256 * kCus && !bwd_plan(N, N, H, M, room).small) {   // from four rounds on at most 2 %
     double pq, pk;
     const Blocks q = large_blocks(N, N, H, M, 256, 1, room, &pq), k = large_blocks(N, N, H, M, 128, 2, room, &pk);
-    if ((q.split || k.split) && 3 * pq + 2 * pk < 0.95 * price(bwd_blocks(&side, 1, H, false).bm)) return BwdForm::kApart;
+    if ((q.split || k.split) && 3 * pq + 2 * pk < 0.95 * price(bwd_blocks(&side, 1, H, false).bm, kCus)) return BwdForm::kApart;
   }
   return BwdForm::kTogether;
 }

@@ -91,11 +91,12 @@ SMALL, SHORT, LONG = (128, 0, 64, 0), (256, 2, 128, 2), (384, 2, 192, 2)
 
 # dQ and dK/dV of one call: together in one launch of the large kernels, as small blocks, or apart (None: the blocks of the other entry points)
 @pytest.mark.parametrize("N,H,M,took", [
-    (6900, 3, 3, SMALL), (6800, 3, 4, SMALL), (20791, 1, 11, SMALL),   # 243 to 253 large blocks, which took two rounds together
+    (6900, 3, 3, SMALL), (6800, 3, 4, SMALL), (20791, 1, 11, SMALL),   # 243 to 253 large blocks: a full round, which routed groups exceed
     (13228, 1, 10, SMALL), (14781, 2, 2, None), (5675, 1, 2, None),    # more than five groups, a quarter of a round; long groups
-    (8000, 3, 1, None), (24325, 4, 5, None), (45453, 4, 16, None),     # long groups, whose last rounds are split
+    (8000, 3, 1, None), (24325, 4, 5, None),                           # long groups, whose last rounds are split
+    (54400, 3, 16, None), (54384, 3, 16, LONG), (64000, 5, 8, None), (63992, 5, 8, LONG),   # on either side of the line: 2.5 and 4.9 rounds
     (62400, 12, 16, None), (40000, 4, 100, SMALL),                     # ten rounds; the smallest groups
-    (4095, 4, 4, SHORT), (9000, 12, 5, LONG), (20000, 12, 10, LONG), (15000, 40, 16, LONG),
+    (4095, 4, 4, SHORT), (9000, 12, 5, LONG), (45453, 4, 16, LONG), (20000, 12, 10, LONG), (15000, 40, 16, LONG),
 ])
 def test_joint_backward_is_launched_in_its_faster_form(N, H, M, took):
     apart = blocks(mg.OP_ATTN_BWD, N, H, M, preferred(mg.OP_ATTN_BWD, N, H, M))
