@@ -916,14 +916,14 @@ struct AttnBwdCall {
 };
 // The host sizes a segment for the most tiles that its groups can have, so blocks without a tile lie behind its real ones.  Between the two segments
 // of a call by itself they cost a round: an XCD deals its blocks to its four shader engines of eight CUs in turn, whether they have work or not, and
-// with the turn shifted one engine gets a ninth block while another keeps a CU free.  There the second segment starts where the tiles of the first
-// really end (rounded up to 8): 243 blocks (2,304 rows x 9 heads) 115 us -> 84, 252 (1,536 x 14) 82 -> 62, 253 (1,920 x 11) 98 -> 74; 240 (2,560 x 8)
-// 90 and 91, 285 sets of groups of 0.15 to 9 rounds 0.75 to 1.04, mean 0.995.
+// with the turn shifted one engine gets a ninth block while another keeps a CU free.  Where the blocks may be one round (rows0) the second segment
+// starts where the tiles of the first really end (rounded up to 8): 243 blocks (2,304 rows x 9 heads) 115 us -> 84, 252 (1,536 x 14) 82 -> 62, 253 (1,920 x 11) 98 -> 74; 240 (2,560 x 8)
+// 90 and 91.
 struct AttnBwdCalls {
   AttnBwdCall c[kMaxCalls];
   int first[2 * kMaxCalls];   // INT_MAX: none
   int what[2 * kMaxCalls];    // 2 * call, + 1 for dK/dV
-  int rows0, sure;            // one call: rows of a tile of the first segment, blocks that it has at least; else 0
+  int rows0, sure;            // rows of a tile of the first segment, blocks that it has at least; 0: the segments start at first
 };
 struct BwdPlace { int segment, block; };
 __device__ __forceinline__ BwdPlace place_of_block(const AttnBwdCalls& calls, int H, int block) {
